@@ -536,18 +536,19 @@ k_live_flags(int64_t n_sel, const int32_t* __restrict__ rowsel, const float* __r
   if (threadIdx.x == 0) blk_live[blockIdx.x] = any;
 }
 // Shares of the dW tile groups per XCD for k_gemm_dh_dw: every XCD first works through its dH groups (contiguous
-// ranges, as tile_coords hands them out; a group costs about Vp K-steps per tile), then dW groups (k_len K-steps per
-// tile) go to the XCDs so that all finish as evenly as whole groups allow, at most max_groups to one XCD (the grid has
+// ranges, slice after slice; a group costs about Vp / slices of K per tile), then dW groups (k_len of K
+// per tile) go to the XCDs so that all finish as evenly as whole groups allow, at most max_groups to one XCD (the grid has
 // no more; 8 max_groups cover all groups).
-__device__ void share_dw_groups(int tiles_r, int tiles_v, int tiles_d, int64_t Vp, int64_t k_len, int max_groups, XcdGroups* out) {
-  const int64_t groups_dh = static_cast<int64_t>((tiles_r + kGM - 1) / kGM) * ((tiles_d + kGN - 1) / kGN);
+constexpr int64_t kTileOverheadK = 768;   // what a tile costs besides its K steps (first loads, epilogue), as a length of K
+__device__ void share_dw_groups(int tiles_r, int tiles_v, int tiles_d, int64_t Vp, int slices, int64_t k_len, int max_groups, XcdGroups* out) {
+  const int64_t groups_dh = static_cast<int64_t>((tiles_r + kGM - 1) / kGM) * ((tiles_d + kGN - 1) / kGN) * slices;
   const int64_t per_xcd = (groups_dh + 7) / 8;
   int64_t load[8];
   int cnt[8] = {};
   for (int x = 0; x < 8; ++x) {
     int64_t n = groups_dh - x * per_xcd;
     n = n < 0 ? 0 : (n > per_xcd ? per_xcd : n);
-    load[x] = n * Vp;
+    load[x] = n * (Vp / slices + kTileOverheadK);
   }
   const int64_t groups_dw = static_cast<int64_t>((tiles_v + kGM - 1) / kGM) * ((tiles_d + kGN - 1) / kGN);
   if (k_len <= 0) {                                    // nothing to even out
@@ -587,7 +588,7 @@ inline int max_dw_groups_per_xcd(int tiles_v, int tiles_d) {   // 8 x this many 
 }
 // One workgroup per chunk: packs the live blocks (all of them with all_live), blk0 = first block of the chunk.
 __global__ void __launch_bounds__(512)
-k_live_scan(int blk0, int nblk, int64_t rows, int all_live, int tiles_v, int tiles_d, int64_t Vp, int max_groups,
+k_live_scan(int blk0, int nblk, int64_t rows, int all_live, int tiles_v, int tiles_d, int64_t Vp, int slices, int max_groups,
             const int32_t* __restrict__ blk_live, int32_t* __restrict__ blk_cidx, int32_t* __restrict__ blk_orig,
             LiveInfo* __restrict__ info) {
   __shared__ int smem[32];
@@ -606,7 +607,8 @@ k_live_scan(int blk0, int nblk, int64_t rows, int all_live, int tiles_v, int til
     info->n_live = total;
     const int64_t last_rows = rows - static_cast<int64_t>(nblk - 1) * 256;     // rows of the chunk's last block
     info->k_rows = static_cast<int32_t>(s_last_live ? static_cast<int64_t>(total - 1) * 256 + last_rows : static_cast<int64_t>(total) * 256);
-    share_dw_groups(total, tiles_v, tiles_d, Vp, static_cast<int64_t>(total) * 256, max_groups, &info->dw_groups);
+    share_dw_groups(total, tiles_v, tiles_d, Vp, slices, total > 0 ? static_cast<int64_t>(total) * 256 + kTileOverheadK : 0, max_groups,
+                    &info->dw_groups);
   }
 }
 
@@ -810,12 +812,12 @@ __device__ __forceinline__ void zero_acc(floatx4 (&acc)[C::MI][C::NI]) {
 #pragma unroll
     for (int j = 0; j < C::NI; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 }
-// K-contiguous operand tile: block row `row_blk` of the blocked [rows, vocabulary] operand; K runs over the vocabulary,
-// four steps of 64 per block
+// K-contiguous operand tile: block row `row_blk` of the blocked [rows, vocabulary] operand from vocabulary block `voc_blk`
+// on; K runs over the vocabulary, four steps of 64 per block
 template <class C>
-__device__ __forceinline__ KContig blocked_rows_tile(const uint16_t* X, int64_t tiles_v, int64_t row_blk) {
+__device__ __forceinline__ KContig blocked_rows_tile(const uint16_t* X, int64_t tiles_v, int64_t row_blk, int voc_blk) {
   KContig c;
-  c.rsrc = make_rsrc(X + blk_offset(row_blk, 0, tiles_v));
+  c.rsrc = make_rsrc(X + blk_offset(row_blk, voc_blk, tiles_v));
   c.hi_bytes = static_cast<uint32_t>(kBlkElems * 2 - 4 * 128);        // from the fourth step of a block to the next block
   const uint32_t kofs = ring2_kofs();
 #pragma unroll
@@ -823,8 +825,51 @@ __device__ __forceinline__ KContig blocked_rows_tile(const uint16_t* X, int64_t 
   return c;
 }
 
+// A tile's accumulators go out as float32 rows (or are added to what is there).  A 16x16 block's registers cover 64
+// bytes of four rows each; stored like that, half a line at a time, they kept the dW tiles of short selections waiting
+// (725 rows of 2048 against 151 936: both products 2.1 ms, through LDS 1.3 ms).  Every wavefront turns its 128 x 64 block
+// through its own part of LDS, 64 rows at a time, and stores 256 bytes of four rows.  at(row, column): where the tile's
+// row has its four columns from there, or NULL when they do not exist.
+constexpr int kAccPitch = 64 * 4 + 16;                               // a staged row: 64 floats
+static_assert(Cfg::WTN == 64 && Cfg::WM * Cfg::WN * 64 * kAccPitch <= MixedLdsBytes<Cfg>::value, "the staged halves fit the tile buffers");
+template <class F>
+__device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[Cfg::MI][Cfg::NI], uint16_t* lds, F at, int accumulate) {
+  using C = Cfg;
+  typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // dW has the alignment of a float
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  char* stage = reinterpret_cast<char*>(lds) + wave * (64 * kAccPitch);
+  const int r0 = wave / C::WN * C::WTM, c0 = wave % C::WN * C::WTN + (lane & 15) * 4;
+#pragma unroll
+  for (int h = 0; h < C::MI / 4; ++h) {
+#pragma unroll
+    for (int bj = 0; bj < C::NI; ++bj)
+#pragma unroll
+      for (int bi = 0; bi < 4; ++bi)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          *reinterpret_cast<float*>(stage + (bi * 16 + (lane >> 4) * 4 + r) * kAccPitch + (bj * 16 + (lane & 15)) * 4) = acc[h * 4 + bi][bj][r];
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll 8
+    for (int i = 0; i < 16; ++i) {
+      const int row = i * 4 + (lane >> 4);
+      if (f32x4_a4* dst = reinterpret_cast<f32x4_a4*>(at(r0 + h * 64 + row, c0))) {
+        f32x4_a4 x = *reinterpret_cast<const floatx4*>(stage + row * kAccPitch + (lane & 15) * 16);
+        if (accumulate) x += *dst;
+        __builtin_nontemporal_store(x, dst);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+// What the sliced products leave behind: partial sums in blocks of 256 x 256 floats [slice][row tile][column tile].
+struct DhSlices {
+  int n;                // slices of the vocabulary (1: the tiles write dH themselves)
+  int voc_blks;         // vocabulary blocks of 256 per slice (the last slice may have fewer)
+  float* part;
+};
 // tile_m counts the chunk's live blocks of rows; orig_blk is the block's place in the chunk
-__device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, const uint16_t* __restrict__ dZ, int64_t Vp,
+__device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, int slice, const DhSlices& sl, int tiles_r, int tiles_d,
+                                        const uint16_t* __restrict__ dZ, int64_t Vp,
                                         const uint16_t* __restrict__ W, int d, int V, uint16_t* __restrict__ dH,
                                         const int32_t* __restrict__ rowsel, int64_t c0, int64_t rows,
                                         const int32_t* __restrict__ ids, const float* __restrict__ g_c,
@@ -832,18 +877,25 @@ __device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, co
   using C = Cfg;
   const int64_t m0 = static_cast<int64_t>(orig_blk) * C::BM;
   const int n0 = tile_n * C::BN;
-  const KContig ca = blocked_rows_tile<C>(dZ, Vp >> 8, tile_m);
+  const int voc_blk = slice * sl.voc_blks, tiles_v = static_cast<int>(Vp >> 8);
+  const int k_len = min(sl.voc_blks, tiles_v - voc_blk) * 256;       // a multiple of 256, at least 256
+  const KContig ca = blocked_rows_tile<C>(dZ, tiles_v, tile_m, voc_blk);
   KMajor kb;
-  kb.base = reinterpret_cast<const char*>(W + n0);
+  kb.base = reinterpret_cast<const char*>(W + static_cast<int64_t>(voc_blk) * 256 * d + n0);
   kb.ld_bytes = static_cast<int64_t>(d) * 2;
   kb.hi_bytes = 0;
   kb.rowmap = nullptr;
-  kb.k_rows = V;                                                     // dz is zero for vocabulary ids past V
+  kb.k_rows = V - voc_blk * 256;                                     // dz is zero for vocabulary ids past V
   kb.n_units = min(32, (d - n0) / 8);
   floatx4 acc[C::MI][C::NI];
   zero_acc<C>(acc);
   // the third LDS stage goes to W: every group of row tiles streams all of it (twice the bytes of the [rows, V] operand)
-  mfma_mainloop_mixed<C, false, true, false, 2>(ca, KMajor{}, KContig{}, kb, static_cast<int>(Vp), lds, acc);
+  mfma_mainloop_mixed<C, false, true, false, 2>(ca, KMajor{}, KContig{}, kb, k_len, lds, acc);
+  if (sl.n > 1) {
+    float* out = sl.part + ((static_cast<int64_t>(slice) * tiles_r + tile_m) * tiles_d + tile_n) * (C::BM * C::BN);
+    store_acc_f32(acc, lds, [&](int r, int c) { return out + r * C::BN + c; }, 0);
+    return;
+  }
 #pragma unroll
   for (int bj = 0; bj < C::NI; ++bj) {
     const int j = n0 + acc_col<C>(bj);
@@ -892,41 +944,71 @@ __device__ __forceinline__ void dw_tile(int tile_m, int tile_n, const uint16_t* 
     if (rowmap) mfma_mainloop_mixed<C, true, true, true>(KContig{}, ka, KContig{}, kb, k_len, lds, acc);
     else mfma_mainloop_mixed<C, true, true, false>(KContig{}, ka, KContig{}, kb, k_len, lds, acc);
   }
-#pragma unroll
-  for (int bj = 0; bj < C::NI; ++bj) {
-    const int j = n0 + acc_col<C>(bj);
-    if (j >= d) continue;
-#pragma unroll
-    for (int bi = 0; bi < C::MI; ++bi)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t v = m0 + acc_row<C>(bi, r);
-        if (v >= V) continue;
-        float* dst = dW + v * d + j;
-        *dst = accumulate ? *dst + acc[bi][bj][r] : acc[bi][bj][r];
-      }
-  }
+  const int64_t v_end = V;
+  store_acc_f32(acc, lds, [&](int r, int c) -> float* {
+    return m0 + r < v_end && n0 + c < d ? dW + (m0 + r) * d + n0 + c : nullptr;     // d is a multiple of 8: four columns are all inside or all outside
+  }, accumulate);
 }
-// Both products in one launch: the first grid_dh workgroups take the dH tiles, the rest the dW tiles.  dH has few,
-// long tiles (K = vocabulary) and on its own leaves a fifth of the last round idle; here an XCD that runs out of dH
-// tiles goes on with dW tiles, and the host gives every XCD the share of dW groups that evens out the sum.
+// Both products in one launch, in groups of 4 x 8 tiles that run on one XCD.  Every XCD owns a contiguous range of the dH
+// groups (slice after slice, so that its workgroups share a slice of both operands) and behind it the share of the dW
+// groups that evens out the sum (share_dw_groups): dH tiles are long (K = vocabulary, or a slice of it) and few, on their
+// own they leave a fifth of the last round idle; they go first and the many short dW tiles fill up.  (Sliced dH groups and
+// dW groups taking turns instead: +-1 % at 725 rows, 8 % slower at 203.)
 __global__ void __launch_bounds__(Cfg::T)
 k_gemm_dh_dw(const uint16_t* __restrict__ dZ, int64_t Vp, int64_t mcp, const uint16_t* __restrict__ W,
              const uint16_t* __restrict__ Hx, int hx_blocked, const int32_t* __restrict__ h_rowmap, int d, int V, int tiles_v,
-             int tiles_d, unsigned grid_dh, const LiveInfo* __restrict__ info, const int32_t* __restrict__ blk_orig,
+             int tiles_d, DhSlices sl, int tiles_r, const LiveInfo* __restrict__ info, const int32_t* __restrict__ blk_orig,
              uint16_t* __restrict__ dH, float* __restrict__ dW, int accumulate, const int32_t* __restrict__ rowsel,
              int64_t c0, int64_t rows, const int32_t* __restrict__ ids, const float* __restrict__ g_c,
              const float* __restrict__ sc) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[MixedLdsBytes<Cfg>::value / 2];
   const int n_live = info->n_live;                     // live blocks of rows: dH row tiles, dW K blocks
+  const int xcd = static_cast<int>(blockIdx.x & 7), seq = static_cast<int>(blockIdx.x >> 3) / (kGM * kGN), within = static_cast<int>(blockIdx.x >> 3) % (kGM * kGN);
+  const int groups_mn = (n_live + kGM - 1) / kGM * ((tiles_d + kGN - 1) / kGN), groups_dh = groups_mn * sl.n;
+  const int per_xcd = (groups_dh + 7) / 8, first_dh = xcd * per_xcd;
+  const int n_dh = max(0, min(per_xcd, groups_dh - first_dh)), first_dw = info->dw_groups.first[xcd], n_dw = info->dw_groups.first[xcd + 1] - first_dw;
+  if (seq >= n_dh + n_dw) return;
   int tile_m, tile_n;
-  if (blockIdx.x < grid_dh) {
-    if (!tile_coords<kGM, kGN>(n_live, tiles_d, &tile_m, &tile_n)) return;
-    dh_tile(tile_m, blk_orig[(c0 >> 8) + tile_m], tile_n, dZ, Vp, W, d, V, dH, rowsel, c0, rows, ids, g_c, sc, lds);
+  if (seq < n_dh) {
+    const int grp = first_dh + seq, slice = grp / max(groups_mn, 1);
+    if (!tile_of_group<kGM, kGN>(grp - slice * groups_mn, within, n_live, tiles_d, &tile_m, &tile_n)) return;
+    dh_tile(tile_m, blk_orig[(c0 >> 8) + tile_m], tile_n, slice, sl, tiles_r, tiles_d, dZ, Vp, W, d, V, dH, rowsel, c0, rows, ids, g_c, sc, lds);
   } else {
-    if (!tile_coords_shared<kGM, kGN>(tiles_v, tiles_d, blockIdx.x - grid_dh, info->dw_groups, &tile_m, &tile_n)) return;
+    if (!tile_of_group<kGM, kGN>(first_dw + seq - n_dh, within, tiles_v, tiles_d, &tile_m, &tile_n)) return;
     dw_tile(tile_m, tile_n, dZ, mcp, Vp, Hx, hx_blocked, d, V, h_rowmap, n_live * 256, info->k_rows, dW, accumulate, lds);
   }
+}
+
+// The slices' partial sums of dH added up in slice order, with what the tile epilogue does otherwise: row factor, one-hot
+// part, bf16 row through the selection.  One workgroup per (row of the live blocks, 1024 columns), four columns a thread.
+__global__ void __launch_bounds__(256)
+k_dh_reduce(DhSlices sl, int tiles_r, int tiles_d, const uint16_t* __restrict__ W, int d, const LiveInfo* __restrict__ info,
+            const int32_t* __restrict__ blk_orig, uint16_t* __restrict__ dH, const int32_t* __restrict__ rowsel, int64_t c0,
+            int64_t rows, const int32_t* __restrict__ ids, const float* __restrict__ g_c, const float* __restrict__ sc) {
+  const int tile_m = blockIdx.x >> 8, r = blockIdx.x & 255;
+  if (tile_m >= info->n_live) return;
+  const int64_t m = static_cast<int64_t>(blk_orig[(c0 >> 8) + tile_m]) * 256 + r;
+  const int j = (blockIdx.y * 256 + threadIdx.x) * 4;
+  if (m >= rows || j >= d) return;
+  const float* src = sl.part + (static_cast<int64_t>(tile_m) * tiles_d + (j >> 8)) * 65536 + r * 256 + (j & 255);
+  const int64_t stride = static_cast<int64_t>(tiles_r) * tiles_d * 65536;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int k0 = 0; k0 < sl.n; k0 += 8) {                             // eight slices in flight
+    float4 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = k0 + q < sl.n ? *reinterpret_cast<const float4*>(src + (k0 + q) * stride) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) { s.x += v[q].x; s.y += v[q].y; s.z += v[q].z; s.w += v[q].w; }
+  }
+  const int64_t row = rowsel ? rowsel[c0 + m] : c0 + m;
+  const float f = sc ? sc[c0 + m] : 1.f, g = g_c[c0 + m];
+  s.x *= f; s.y *= f; s.z *= f; s.w *= f;
+  if (g != 0.f) {                                                    // g = 0 for invalid ids
+    const uint2 w = *reinterpret_cast<const uint2*>(W + static_cast<int64_t>(ids[row]) * d + j);
+    s.x += g * __uint_as_float(w.x << 16); s.y += g * __uint_as_float(w.x & 0xffff0000u);
+    s.z += g * __uint_as_float(w.y << 16); s.w += g * __uint_as_float(w.y & 0xffff0000u);
+  }
+  *reinterpret_cast<uint2*>(dH + row * d + j) = make_uint2(pack_bf16x2(s.x, s.y), pack_bf16x2(s.z, s.w));
 }
 
 // One-hot part of dW: dW[y_n, :] += g_n h_n for every selected row, in float32.  Rows that took the same token add
@@ -1135,6 +1217,30 @@ size_t chunk_bytes(int64_t mc, int d, int V, umas_dtype dt) {
   const int64_t Vp = round_up(V, 256), mcp = round_up(mc, 256);
   return align_up(static_cast<size_t>(mcp) * Vp * 2) + align_up(static_cast<size_t>(mcp) * round_up(d, 256) * 2);
 }
+// How the dH product of a chunk is cut along the vocabulary.  dH has tiles_r x tiles_d tiles of the whole vocabulary's K
+// each; with few row tiles that is fewer long tiles than compute units, and the launch lasts as long as one of them (3.6 ms
+// at V = 151 936 whether there are 64 rows or 2000).  Below kDhSliceTiles, one tile per compute unit, they are cut into about
+// 512 / tiles slices, two pieces per compute unit, so that the rounds fill evenly; partial sums cost 256 KB a piece.  Update call, whole: 203
+// rows of 2048 3745 -> 1260 us (of 3584: 4205 -> 1890), 725 rows 4150 -> 1680, 2900 rows 5990 -> 4950.  (Cut as well,
+// 280 tiles gain 5 %, 448 nothing; above the line dH stays bit for bit the same however the rows are chunked.)  A quarter and half as many slices are up to 15 % and 7 %
+// slower at 64 to 500 rows, half as many again within 2 %.
+constexpr int kDhSliceTiles = 256;
+struct DhPlan {
+  int slices, voc_blks;
+};
+size_t dh_part_bytes(const DhPlan& p, int tiles_r, int tiles_d) {
+  return p.slices > 1 ? static_cast<size_t>(p.slices) * tiles_r * tiles_d * (256 * 256 * sizeof(float)) : 0;
+}
+DhPlan plan_dh(int64_t tiles_r, int64_t tiles_d, int tiles_v, size_t room) {
+  if (tiles_r * tiles_d >= kDhSliceTiles) return DhPlan{1, tiles_v};
+  int want = static_cast<int>((512 + tiles_r * tiles_d - 1) / (tiles_r * tiles_d));
+  const size_t one = static_cast<size_t>(tiles_r * tiles_d) * (256 * 256 * sizeof(float));
+  if (static_cast<size_t>(want) > room / one) want = static_cast<int>(room / one);
+  if (want > tiles_v) want = tiles_v;
+  if (want < 2) return DhPlan{1, tiles_v};
+  const int blks = (tiles_v + want - 1) / want;
+  return DhPlan{(tiles_v + blks - 1) / blks, blks};
+}
 size_t carve_ppo(Carver& c, PpoWs& w, int64_t n_sel, int d, int V, umas_dtype dt, int n_roles) {
   (void)d;                                      // the per-chunk buffers depend on d, the fixed part does not
   carve_score(c, w.score, n_sel, V, dt, true);
@@ -1327,7 +1433,12 @@ extern "C" size_t umas_ppo_loss_workspace_bytes(int64_t n_sel, int32_t d, int32_
     const int64_t nchunk = (mc + cap - 1) / cap;
     mc = round_up((mc + nchunk - 1) / nchunk, 256);
   }
-  return c.off + chunk_bytes(mc, d, V, dtype);
+  size_t part = 0;
+  if (dtype == UMAS_BF16) {
+    const int tiles_r = static_cast<int>(round_up(mc, 256) / 256), tiles_d = (d + 255) / 256;
+    part = dh_part_bytes(plan_dh(tiles_r, tiles_d, (V + 255) / 256, SIZE_MAX), tiles_r, tiles_d);
+  }
+  return c.off + chunk_bytes(mc, d, V, dtype) + part;
 }
 
 extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_dtype dtype, int64_t n_rows, int32_t d,
@@ -1392,6 +1503,34 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
   const uint16_t* Wb = static_cast<const uint16_t*>(W);
   const uint16_t* Hb = static_cast<const uint16_t*>(H);
 
+  // both gradient products of the chunk of `rows` rows from c0 on, and what the slices of dH leave; the partial sums lie
+  // behind the chunk's operands or, once the scoring pass's own partials have been merged, in their place
+  auto dh_plan = [&](int64_t rows, DhSlices* sl) {
+    const int tiles_r = static_cast<int>(cdiv(rows, 256)), tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
+    const size_t used = chunk_bytes(rows, d, V, dtype), behind = room > used ? room - used : 0;
+    const size_t front = static_cast<size_t>(reinterpret_cast<char*>(w.score.logp_c) - reinterpret_cast<char*>(w.score.partial));
+    const bool aligned = reinterpret_cast<uintptr_t>(dH) % 8 == 0;      // the reducing kernel stores four columns at once
+    const DhPlan p = plan_dh(tiles_r, tiles_d, tiles_v, aligned ? (behind > front ? behind : front) : 0);
+    *sl = DhSlices{p.slices, p.voc_blks, behind > front ? reinterpret_cast<float*>(w.chunk + used) : reinterpret_cast<float*>(w.score.partial)};
+  };
+  auto gradients = [&](int64_t c0, int64_t rows, const DhSlices& sl, const uint16_t* op, const uint16_t* Hx, int hx_blocked,
+                       const int32_t* h_rowmap, const float* sc) -> umas_status {
+    const int64_t mcp = round_up(rows, 256);
+    const int tiles_r = static_cast<int>(mcp / 256), tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
+    const unsigned grid_dh = tile_grid<kGM, kGN>(tiles_r, tiles_d, 1, sl.n);
+    const unsigned grid_dw = static_cast<unsigned>(max_dw_groups_per_xcd(tiles_v, tiles_d)) * kGM * kGN * 8;
+    hipLaunchKernelGGL(k_gemm_dh_dw, dim3(grid_dh + grid_dw), dim3(Cfg::T), 0, st, op, Vp, mcp, Wb, Hx, hx_blocked, h_rowmap, d, V, tiles_v,
+                       tiles_d, sl, tiles_r, w.live, w.blk_orig, static_cast<uint16_t*>(dH), dW, (accumulate_dW || c0 > 0) ? 1 : 0,
+                       rowsel, c0, rows, ids, w.g_c, sc);
+    UMAS_LAUNCHED("k_gemm_dh_dw");
+    if (sl.n > 1) {
+      hipLaunchKernelGGL(k_dh_reduce, dim3(static_cast<unsigned>(mcp), cdiv(d, 1024)), dim3(256), 0, st, sl, tiles_r, tiles_d, Wb, d, w.live,
+                         w.blk_orig, static_cast<uint16_t*>(dH), rowsel, c0, rows, ids, w.g_c, sc);
+      UMAS_LAUNCHED("k_dh_reduce");
+    }
+    return UMAS_OK;
+  };
+
   if (!keep) {
     // forward scoring and the surrogate
     s = run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w.score, logp_new, nullptr, nullptr, st);
@@ -1417,8 +1556,10 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       const int tiles_r = static_cast<int>(mcp / 256);
       uint16_t* E = reinterpret_cast<uint16_t*>(w.chunk);
       uint16_t* Hs = reinterpret_cast<uint16_t*>(w.chunk + align_up(static_cast<size_t>(mcp) * Vp * 2));
+      DhSlices sl;
+      dh_plan(rows, &sl);
       hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, static_cast<int>(c0 >> 8), tiles_r, rows, kl_coef != 0.f ? 1 : 0, tiles_v,
-                         tiles_d, Vp, max_groups, w.blk_live, w.blk_cidx, w.blk_orig, w.live);   // a KL term gives every row a gradient
+                         tiles_d, Vp, sl.n, max_groups, w.blk_live, w.blk_cidx, w.blk_orig, w.live);   // a KL term gives every row a gradient
       UMAS_LAUNCHED("k_live_scan");
       hipLaunchKernelGGL(k_score_keep_tiles, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, kTilesPerWg)), dim3(Cfg::T), 0, st,
                          Wb, Hb, d, V, rowsel, c0, rows, ids, tiles_v, tiles_r, w.score.partial, n_pad, w.cref, E, Vp, w.flags,
@@ -1440,12 +1581,8 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       hipLaunchKernelGGL(k_keep_rows, dim3(cdiv(rows, 4)), dim3(256), 0, st, Hb, d, V, rowsel, c0, rows, ids, E,
                          static_cast<int64_t>(tiles_v), w.score.lse_c, w.a_c, w.cref, w.flags, w.blk_cidx, w.sc, Hs, mcp);
       UMAS_LAUNCHED("k_keep_rows");
-      const unsigned grid_dh = tile_grid<kGM, kGN>(tiles_r, tiles_d);
-      hipLaunchKernelGGL(k_gemm_dh_dw, dim3(grid_dh + static_cast<unsigned>(max_groups) * kGM * kGN * 8), dim3(Cfg::T), 0, st,
-                         E, Vp, mcp, Wb, Hs, 1, static_cast<const int32_t*>(nullptr), d, V, tiles_v, tiles_d, grid_dh,
-                         w.live, w.blk_orig, static_cast<uint16_t*>(dH), dW, (accumulate_dW || c0 > 0) ? 1 : 0, rowsel, c0,
-                         rows, ids, w.g_c, w.sc);
-      UMAS_LAUNCHED("k_gemm_dh_dw");
+      s = gradients(c0, rows, sl, E, Hs, 1, nullptr, w.sc);
+      if (s != UMAS_OK) return s;
     }
   }
   hipLaunchKernelGGL(k_ppo_stats, dim3(1), dim3(256), 0, st, nblk, n_roles, entropy_coef, norm_rows, w.blk_stats, stats);
@@ -1487,16 +1624,13 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
                        ids);
     UMAS_LAUNCHED("k_zero_label");
     // with an entropy bonus every row has a gradient: all blocks are live
-    const int max_groups = max_dw_groups_per_xcd(tiles_v, tiles_d);
-    hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, static_cast<int>(c0 >> 8), tiles_r, rows, 1, tiles_v, tiles_d, Vp,
-                       max_groups, w.blk_live, w.blk_cidx, w.blk_orig, w.live);
+    DhSlices sl;
+    dh_plan(rows, &sl);
+    hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, static_cast<int>(c0 >> 8), tiles_r, rows, 1, tiles_v, tiles_d, Vp, sl.n,
+                       max_dw_groups_per_xcd(tiles_v, tiles_d), w.blk_live, w.blk_cidx, w.blk_orig, w.live);
     UMAS_LAUNCHED("k_live_scan");
-    const unsigned grid_dh = tile_grid<kGM, kGN>(tiles_r, tiles_d);
-    hipLaunchKernelGGL(k_gemm_dh_dw, dim3(grid_dh + static_cast<unsigned>(max_groups) * kGM * kGN * 8), dim3(Cfg::T), 0, st,
-                       dZ, Vp, mcp, Wb, rowsel ? Hb : Hb + c0 * d, 0, rowsel ? rowsel + c0 : static_cast<const int32_t*>(nullptr), d,
-                       V, tiles_v, tiles_d, grid_dh, w.live, w.blk_orig, static_cast<uint16_t*>(dH), dW,
-                       (accumulate_dW || c0 > 0) ? 1 : 0, rowsel, c0, rows, ids, w.g_c, static_cast<const float*>(nullptr));
-    UMAS_LAUNCHED("k_gemm_dh_dw");
+    s = gradients(c0, rows, sl, dZ, rowsel ? Hb : Hb + c0 * d, 0, rowsel ? rowsel + c0 : nullptr, nullptr);
+    if (s != UMAS_OK) return s;
   }
   hipLaunchKernelGGL(k_dw_onehot, dim3(cdiv(n_sel, kOneHotRows)), dim3(256), 0, st, Hb, d, rowsel, n_sel, ids, w.g_c, dW);
   UMAS_LAUNCHED("k_dw_onehot");

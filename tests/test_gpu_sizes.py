@@ -1,0 +1,68 @@
+"""Sizes at which the update's dispatch changes: edges of tiles, slices and workspaces, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+from oracle import umas_oracle as orc
+from tests import parity as P
+import paper_2605_26646_amd as umas
+
+pytestmark = pytest.mark.gpu
+
+
+def check_update(rng, n, d, V, *, select=0.8, workspace=None, shift_dH=0, entropy_coef=0.0, accumulate=False, scale=1.0, **kw):
+    """One update of random rows against the oracle, every entry within the bounds that the arithmetic gives."""
+    H = wl.round_to_bf16((rng.normal(size=(n, d)) / np.sqrt(d) * 3).astype(np.float32))
+    W = wl.round_to_bf16((scale * rng.normal(size=(V, d))).astype(np.float32))
+    ids = rng.integers(0, V, size=n).astype(np.int32)
+    sel = np.sort(rng.choice(n, size=max(1, int(select * n)), replace=False)).astype(np.int32)
+    rng.shuffle(sel)
+    adv = rng.normal(size=n).astype(np.float32)
+    logp_o, lse_o, ent_o = orc.score(H, W, ids, sel)
+    logp_old = np.zeros(n, np.float32)
+    logp_old[sel] = (logp_o[sel] + 0.05 * rng.normal(size=len(sel))).astype(np.float32)
+    _, g_o = orc.ppo_loss(logp_o, logp_old, adv, ent_o, sel, np.zeros(n, np.int32), 0, 0.2)
+    k_ent = entropy_coef / len(sel)
+    if k_ent:
+        dH_o, dW_o = orc.lm_head_backward_entropy(H, W, ids, lse_o, ent_o, g_o, entropy_coef, len(sel), sel)
+    else:
+        dH_o, dW_o = orc.lm_head_backward(H, W, ids, lse_o, g_o, sel)
+    buf = torch.empty(n * d + 8, dtype=torch.bfloat16, device="cuda")
+    dW0 = (0.01 * rng.normal(size=(V, d))).astype(np.float32) if accumulate else None
+    stats, logp_new, dH, dW = umas.umas_ppo_loss_fwd_bwd(
+        P.to_dev(H, torch.bfloat16), P.to_dev(W, torch.bfloat16), P.to_dev(ids), P.to_dev(sel), P.to_dev(logp_old), P.to_dev(adv),
+        None, 0, 0.2, entropy_coef=entropy_coef, dH=buf[shift_dH:shift_dH + n * d].view(n, d), workspace=workspace,
+        accumulate_dW=accumulate, dW=P.to_dev(dW0) if accumulate else None, **kw)
+    what = f"n={n} d={d} V={V}"
+    assert int(umas.read_stats(stats)["n_scored"][0]) == len(sel), what
+    assert np.abs(logp_new.cpu().numpy()[sel] - logp_o[sel]).max() <= 2e-2, what
+    dH_g = dH.float().cpu().numpy()
+    assert not dH_g[np.setdiff1d(np.arange(n), sel)].any(), what
+    dz = P.oracle_dz(H, W, ids, lse_o, g_o, sel, ent_o, k_ent)
+    bound_h, bound_w = P.bf16_gradient_bounds(H, W, dz, dH_o, dW_o, sel, ids, lse_o, g_o)
+    P.close_bounded(dH_g, dH_o, bound_h, 1e-2, "dH, " + what)
+    if accumulate:
+        bound_w = bound_w + 2.0 ** -23 * (np.abs(dW0) + np.abs(dW_o))
+    P.close_bounded(dW.cpu().numpy() - (dW0 if accumulate else 0), dW_o, bound_w, 1e-2, "dW, " + what)
+
+
+# one to several row tiles, one and several column tiles (ragged ones too), slices of one vocabulary block and of several,
+# a last slice that is short and a last vocabulary block that is nearly empty
+@pytest.mark.parametrize("n,d,V", [(1, 64, 513), (30, 8, 1283), (320, 264, 2561), (650, 64, 9000), (400, 1032, 5121)])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_update_with_dh_cut_along_the_vocabulary(n, d, V, accumulate):
+    check_update(np.random.default_rng(n + d), n, d, V, accumulate=accumulate)
+
+
+# workspaces between the smallest and the recommended one: no room for slices, room in the scoring pass's place (many rows
+# in small chunks), room for two
+@pytest.mark.parametrize("n,d,V,extra_tiles", [(300, 64, 3000, 0), (300, 64, 3000, 2), (1500, 64, 20000, 0), (700, 128, 5000, 5)])
+def test_update_with_room_for_few_slices(n, d, V, extra_tiles):
+    n_sel = max(1, int(0.8 * n))
+    nbytes = umas.ppo_workspace_bytes(n_sel, d, V, torch.bfloat16, 0, minimum=True) + extra_tiles * (256 * 256 * 4)
+    check_update(np.random.default_rng(n), n, d, V, workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+
+
+def test_update_with_dh_at_an_address_that_is_not_a_multiple_of_eight():
+    check_update(np.random.default_rng(5), 300, 64, 3000, shift_dH=2)
