@@ -171,7 +171,7 @@ __device__ __forceinline__ void mfma_mainloop_ring2(__amdgpu_buffer_rsrc_t ra, c
   char* base = reinterpret_cast<char*>(lds);
   const int nsub = K / R::BK;
 
-  static_assert(R::NA == 4, "the wait before the barrier leaves four loads outstanding");
+  static_assert(R::NA < 16, "the wait before the barrier leaves the loads of A outstanding");
   auto gload_a = [&](int sub, int ia) {
     const int kbytes = sub * R::BK * 2;
     char* sa = base + ia * R::ASTAGE + wave * 8 * R::ROWB;
@@ -251,9 +251,9 @@ __device__ __forceinline__ void mfma_mainloop_ring2(__amdgpu_buffer_rsrc_t ra, c
     mfmas(0, 1, 0);
     interleave(HA, 0);
     __builtin_amdgcn_sched_barrier(0);
-    // own reads of this step done, own loads for the next step landed (the four youngest, A of the step after
+    // own reads of this step done, own loads for the next step landed (the youngest, A of the step after
     // next, may still be on their way); then everybody's
-    __builtin_amdgcn_s_waitcnt(0x0074);              // vmcnt(4) and lgkmcnt(0), expcnt untouched (gfx9 encoding)
+    __builtin_amdgcn_s_waitcnt(0x0070 | R::NA);      // vmcnt(NA) and lgkmcnt(0), expcnt untouched (gfx9 encoding)
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     fload_b(0, ib ^ 1, 0);
@@ -533,23 +533,27 @@ __device__ __forceinline__ int acc_col(int j) {
 // logical tile order, and order tiles in groups of GM x GN so that the workgroups resident on
 // one XCD share operand rows through its L2.  A workgroup handles `per_wg` tiles one after the other:
 // the tile with the same place in `per_wg` consecutive groups, so that the workgroups of an XCD keep
-// working on one group at a time.  Returns false when iteration `it` of this workgroup has no tile.
+// working on one group at a time.  With at most GN column tiles the tiles themselves are numbered, column tiles of a row
+// tile next to each other, one to a workgroup: the same sharing, and the few rounds there are come out even (groups
+// half or more empty left 96 of 256 compute units idle with one column tile).
+// Returns false when iteration `it` of this workgroup has no tile.
 template <int GM, int GN>
-__device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int* tm, int* tn, int it = 0, int per_wg = 1) {
+__device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int* tm, int* tn, int it, int per_wg) {
+  const int xcd = static_cast<int>(blockIdx.x & 7), w = static_cast<int>(blockIdx.x >> 3);   // w: workgroup number inside its XCD
+  if (tiles_n <= GN) {
+    const int per_xcd = (tiles_m * tiles_n + 7) / 8, t = xcd * per_xcd + w;
+    *tm = t / tiles_n;
+    *tn = t % tiles_n;
+    return it == 0 && w < per_xcd && *tm < tiles_m;
+  }
   const int total_groups_n = (tiles_n + GN - 1) / GN;
-  const int total_groups_m = (tiles_m + GM - 1) / GM;
-  const long long groups = static_cast<long long>(total_groups_m) * total_groups_n;
-  const long long groups_per_xcd = (groups + 7) / 8;                       // contiguous range of groups per XCD
-  const long long bid = blockIdx.x;
-  const long long w = bid >> 3;                                            // workgroup number inside its XCD
-  const long long grp_in_xcd = (w / (GM * GN)) * per_wg + it;
-  const int within = static_cast<int>(w % (GM * GN));
-  if (grp_in_xcd >= groups_per_xcd) return false;
-  const long long grp = (bid & 7) * groups_per_xcd + grp_in_xcd;
-  if (grp >= groups) return false;
-  const int gm = static_cast<int>(grp / total_groups_n), gn = static_cast<int>(grp % total_groups_n);
+  const int groups = (tiles_m + GM - 1) / GM * total_groups_n;
+  const int groups_per_xcd = (groups + 7) / 8;                             // contiguous range of groups per XCD
+  const int grp_in_xcd = w / (GM * GN) * per_wg + it, within = w % (GM * GN), grp = xcd * groups_per_xcd + grp_in_xcd;
+  if (grp_in_xcd >= groups_per_xcd || grp >= groups) return false;
+  const int gm = grp / total_groups_n;
   *tm = gm * GM + within % GM;
-  *tn = gn * GN + within / GM;
+  *tn = (grp - gm * total_groups_n) * GN + within / GM;
   return *tm < tiles_m && *tn < tiles_n;
 }
 // Shares of a sequence of groups per XCD: XCD x owns groups first[x] .. first[x + 1] - 1.
@@ -565,11 +569,17 @@ __device__ __forceinline__ bool tile_of_group(int grp, int within, int tiles_m, 
   return *tm < tiles_m && *tn < tiles_n;
 }
 template <int GM, int GN>
-inline unsigned tile_grid(int tiles_m, int tiles_n, int per_wg = 1, int slices = 1) {
-  const long long groups = static_cast<long long>((tiles_m + GM - 1) / GM) * ((tiles_n + GN - 1) / GN) * slices;
+inline unsigned tile_grid(int tiles_m, int tiles_n, int per_wg) {           // workgroups tile_coords needs
+  if (tiles_n <= GN) return static_cast<unsigned>((static_cast<long long>(tiles_m) * tiles_n + 7) / 8 * 8);
+  const long long groups = static_cast<long long>((tiles_m + GM - 1) / GM) * ((tiles_n + GN - 1) / GN);
   const long long groups_per_xcd = (groups + 7) / 8;
   const long long wg_groups = (groups_per_xcd + per_wg - 1) / per_wg;       // groups of workgroups per XCD
   return static_cast<unsigned>(wg_groups * (GM * GN) * 8);
+}
+template <int GM, int GN>
+inline unsigned group_grid(int tiles_m, int tiles_n, int slices) {          // whole groups, slices times
+  const long long groups = static_cast<long long>((tiles_m + GM - 1) / GM) * ((tiles_n + GN - 1) / GN) * slices;
+  return static_cast<unsigned>((groups + 7) / 8 * (GM * GN) * 8);
 }
 
 }  // namespace umas

@@ -17,6 +17,7 @@
 // The float32 path is a plain, unblocked implementation for small shapes.
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "umas_common.h"
@@ -146,13 +147,13 @@ struct KeepArgs {
   const int32_t* cidx; // per block of 256 selected rows: its place among the chunk's live blocks, -1 for a dead one
 };
 
-template <bool KEEP>
+template <bool KEEP, class C>
 __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
                                             const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc,
                                             const int32_t* __restrict__ ids, int tiles_m, int tiles_n,
                                             float4* __restrict__ partial, int64_t n_pad, const KeepArgs& keep,
                                             uint16_t* lds) {
-  using C = Cfg;
+  static_assert(!KEEP || C::BM * C::BN == Cfg::BM * Cfg::BN, "kept numerators lie in whole blocks");
   for (int it = 0; it < kTilesPerWg; ++it) {     // a workgroup walks the same place of kTilesPerWg consecutive tile groups
   int tile_m, tile_n;
   if (!tile_coords<kGM, kGN>(tiles_m, tiles_n, &tile_m, &tile_n, it, kTilesPerWg)) continue;
@@ -305,7 +306,19 @@ k_score_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, in
               const int32_t* __restrict__ rowsel, int64_t n_sel, const int32_t* __restrict__ ids,
               int tiles_m, int tiles_n, float4* __restrict__ partial, int64_t n_pad) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[kLogitLds / 2];
-  score_tiles<false>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, tiles_n, partial, n_pad, KeepArgs{}, lds);
+  score_tiles<false, Cfg>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, tiles_n, partial, n_pad, KeepArgs{}, lds);
+}
+// Up to 128 selected rows: half-size tiles with a pipeline of their own, two workgroups to a compute unit, so that one
+// fills its stages while the other multiplies (64 rows of 2048 / 3584 against 151 936: 156 / 215 us against 182 / 274 with
+// the large tiles; 128x256 and 256x128 tiles 213 / 347 and 167 / 234).
+using NarrowCfg = TileCfg<128, 128, 2, 2>;
+constexpr int kNarrowLds = Ring2Cfg<NarrowCfg>::LDS_BYTES > NarrowCfg::LDS_BYTES ? Ring2Cfg<NarrowCfg>::LDS_BYTES : NarrowCfg::LDS_BYTES;
+__global__ void __launch_bounds__(NarrowCfg::T)
+k_score_narrow(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
+               const int32_t* __restrict__ rowsel, int64_t n_sel, const int32_t* __restrict__ ids,
+               int tiles_m, int tiles_n, float4* __restrict__ partial, int64_t n_pad) {
+  __shared__ __attribute__((aligned(16))) uint16_t lds[kNarrowLds / 2];
+  score_tiles<false, NarrowCfg>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, tiles_n, partial, n_pad, KeepArgs{}, lds);
 }
 __global__ void __launch_bounds__(Cfg::T)
 k_score_keep_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
@@ -314,29 +327,160 @@ k_score_keep_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ 
                    const float* __restrict__ cref, uint16_t* __restrict__ E, int64_t Vp, int32_t* __restrict__ flags,
                    const int32_t* __restrict__ cidx) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[kLogitLds / 2];
-  score_tiles<true>(W, H, d, V, rowsel, c0, mc, ids, tiles_m, tiles_n, partial, n_pad, KeepArgs{cref, E, Vp, flags, cidx}, lds);
+  score_tiles<true, Cfg>(W, H, d, V, rowsel, c0, mc, ids, tiles_m, tiles_n, partial, n_pad, KeepArgs{cref, E, Vp, flags, cidx}, lds);
 }
 
-// Merge the per-tile partials of each selected row; compact results and optional scatter.  Eight lanes
-// share a row (lane = 8 * part + row within the group of 8 rows, so a load still covers whole 128-byte lines).
-constexpr int kFinParts = 8;
+// ------------------------------------------------------------------ bf16: a few rows
+// Up to 32 selected rows (64 up to d = 2048): the pass is bound by reading W once, and a 256x256 tile with most of its columns empty spends
+// its time filling and draining.  Here the rows of H stay in registers and W streams past them: the eight wavefronts of a
+// workgroup split the hidden dimension (each takes PPW pieces of 64, next to each other across the wavefronts, so that a
+// row of W is read in whole lines), a wavefront holds its pieces of up to 16 NI rows as MFMA operands for the whole kernel
+// and walks a contiguous range of the vocabulary MB blocks of 16 entries at a time, W going straight to registers; a
+// piece's registers are loaded again for the next step as soon as they have been used, so that 8 KB and more are in flight
+// per wavefront all the time.  The eight partial logits meet in LDS (one barrier a step, two buffers), and every thread
+// keeps the softmax statistics of one (row, place in the block of 16) over its workgroup's whole range.  One workgroup per
+// compute unit; partials [workgroup][row].
+// 24 rows of 2048 (3584) against 151 936: 256x256 tiles 183 (279) us, this kernel 117 (199) us = 5.3 (5.5) TB/s of W; 64
+// rows of 2048 182 -> 122 us.
+constexpr int kFewWaves = 8, kFewT = kFewWaves * kWave;
+inline int few_pieces(int d) { return static_cast<int>(cdiv(d, kFewWaves * 64)); }   // PPW
+inline int few_rows(int d) { return few_pieces(d) <= 4 ? 64 : few_pieces(d) <= 8 ? 32 : 0; }   // what the registers hold
+template <int NI, int PPW>
+__global__ void __launch_bounds__(kFewT)
+k_score_few(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel, int n_sel,
+            const int32_t* __restrict__ ids, float4* __restrict__ partial, int n_pad) {
+  constexpr int MB = PPW <= 4 && NI <= 2 ? 2 : 1;            // blocks of 16 vocabulary entries per step
+  constexpr int NL = (NI + 1) / 2;                           // logits per thread and block
+  __shared__ __attribute__((aligned(16))) float s_z[2][kFewWaves][MB][NI][16][16];   // [.][wavefront][block][.][row][entry]
+  __shared__ float4 s_part[NI * 16][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int piece = (lane >> 4) * 8;
+  bf16x8 hf[PPW][2][NI];
+#pragma unroll
+  for (int p = 0; p < PPW; ++p)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) {
+        const int n = min(j * 16 + (lane & 15), n_sel - 1), k = (p * kFewWaves + wave) * 64 + q * 32 + piece;
+        const int64_t row = rowsel ? rowsel[n] : n;
+        const uint4 v = k < d ? *reinterpret_cast<const uint4*>(H + row * d + k) : make_uint4(0u, 0u, 0u, 0u);
+        hf[p][q][j] = __builtin_bit_cast(bf16x8, v);
+      }
+  // this workgroup's blocks of 16 vocabulary entries
+  const int blocks = (V + 15) / 16;
+  const int per = (blocks + static_cast<int>(gridDim.x) - 1) / static_cast<int>(gridDim.x);
+  const int b0 = static_cast<int>(blockIdx.x) * per, b1 = min(b0 + per, blocks);
+  uint4 w[MB][PPW][2];
+  auto load = [&](int b, int p, int q, int i) {              // past the hidden size: some entry of the row, met by zeros of H
+    const int v = min((b + i) * 16 + (lane & 15), V - 1), k = min((p * kFewWaves + wave) * 64 + q * 32 + piece, d - 8);
+    w[i][p][q] = *reinterpret_cast<const uint4*>(W + static_cast<int64_t>(v) * d + k);
+  };
+  if (b0 < b1)
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int p = 0; p < PPW; ++p) { load(b0, p, 0, i); load(b0, p, 1, i); }
+  // thread -> (row, place): statistics of the logits of that row at that place of every block
+  const bool mine = tid < NI * 256;
+  const int my_n = (tid >> 4) & 15, my_v = tid & 15;
+  int y[NL];
+  float m[NL], s[NL], t[NL], zy[NL];
+#pragma unroll
+  for (int l = 0; l < NL; ++l) {
+    const int n = (2 * l + (tid >> 8)) * 16 + my_n;
+    y[l] = mine && n < n_sel ? ids[rowsel ? rowsel[n] : n] : -1;
+    m[l] = kNegInf; s[l] = t[l] = zy[l] = 0.f;
+  }
+  int buf = 0;
+  for (int b = b0; b < b1; b += MB, buf ^= 1) {
+    floatx4 acc[MB][NI];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int nb = b + MB < b1 ? b + MB : b;                 // past the range: loaded again, not used
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int p = 0; p < PPW; ++p)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const bf16x8 a = __builtin_bit_cast(bf16x8, w[i][p][q]);
+#pragma unroll
+          for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, hf[p][q][j], acc[i][j], 0, 0, 0);
+          load(nb, p, q, i);
+        }
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) *reinterpret_cast<floatx4*>(&s_z[buf][wave][i][j][lane & 15][(lane >> 4) * 4]) = acc[i][j];
+    __syncthreads();
+    if (mine) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+          float z = 0.f;
+#pragma unroll
+          for (int k = 0; k < kFewWaves; ++k) z += s_z[buf][k][i][2 * l + (tid >> 8)][my_n][my_v];
+          const int v = (b + i) * 16 + my_v;
+          if (v < V && b + i < b1) {
+            if (v == y[l]) zy[l] = z;
+            const float gap = z - m[l], e = __expf(-fabsf(gap));  // one exponential: of the smaller relative to the larger
+            if (gap > 0.f) { s[l] = fmaf(s[l], e, 1.f); t[l] = fmaf(t[l], e, z); m[l] = z; }
+            else { s[l] += e; t[l] = fmaf(e, z, t[l]); }
+          }
+        }
+    }
+  }
+#pragma unroll
+  for (int l = 0; l < NL; ++l)
+    if (mine) s_part[(2 * l + (tid >> 8)) * 16 + my_n][my_v] = make_float4(m[l], s[l], t[l], zy[l]);
+  __syncthreads();
+  if (tid < NI * 16) {
+    Part p{kNegInf, 0.f, 0.f};
+    float z = 0.f;
+    for (int k = 0; k < 16; ++k) {
+      const float4 q = s_part[tid][k];
+      p = part_merge(p, Part{q.x, q.y, q.z});
+      z += q.w;
+    }
+    partial[static_cast<int64_t>(blockIdx.x) * n_pad + tid] = make_float4(p.m, p.s, p.t, z);
+  }
+}
+
+// Merge the per-tile partials of each selected row; compact results and optional scatter.  Eight lanes of a wavefront
+// share a row (lane = 8 * part + row within the group of 8 rows, so a load covers whole 128-byte lines), four loads in
+// flight each.  Where there are few rows the four wavefronts of the workgroup share the group's tiles as well (SPLIT):
+// 24 rows of 594 tiles 41 -> 7 us, 16 100 rows 53 -> 36; with enough rows to fill the chip the extra merge only costs
+// (39 000 rows, 373 MB: 82 us split, 69 not).
+constexpr int64_t kFinSplitRows = 20000;
+template <bool SPLIT>
 __global__ void __launch_bounds__(256)
 k_score_finalize(const float4* __restrict__ partial, int tiles_m, int64_t n_pad, int64_t n_begin,
                  int64_t n_end, const float* __restrict__ zy_c, const int32_t* __restrict__ rowsel,
                  const int32_t* __restrict__ ids, int V,
                  float* __restrict__ logp_c, float* __restrict__ lse_c, float* __restrict__ ent_c,
                  float* __restrict__ logp, float* __restrict__ lse, float* __restrict__ entropy) {
+  __shared__ float4 s_part[4][8];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int part = lane >> 3;
-  const int64_t n = n_begin + (static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + wave) * 8 + (lane & 7);
-  const bool live = n < n_end;                                // whole groups of lanes; the shuffles below need every lane
+  const int64_t n = n_begin + (SPLIT ? static_cast<int64_t>(blockIdx.x) : static_cast<int64_t>(blockIdx.x) * 4 + wave) * 8 + (lane & 7);
+  const bool live = n < n_end;
+  constexpr int kParts = SPLIT ? 32 : 8;
   Part p{kNegInf, 0.f, 0.f};
   float zy = 0.f;
   if (live) {
-    for (int tm = part; tm < tiles_m; tm += kFinParts) {
-      const float4 q = partial[static_cast<int64_t>(tm) * n_pad + n];
-      p = part_merge(p, Part{q.x, q.y, q.z});
-      zy += q.w;
+    for (int t0 = SPLIT ? threadIdx.x >> 3 : lane >> 3; t0 < tiles_m; t0 += 4 * kParts) {
+      float4 q[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        q[k] = t0 + k * kParts < tiles_m ? partial[static_cast<int64_t>(t0 + k * kParts) * n_pad + n] : make_float4(kNegInf, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        p = part_merge(p, Part{q[k].x, q[k].y, q[k].z});
+        zy += q[k].w;
+      }
     }
   }
 #pragma unroll
@@ -345,7 +489,19 @@ k_score_finalize(const float4* __restrict__ partial, int tiles_m, int64_t n_pad,
     p = part_merge(p, q);
     zy += __shfl_xor(zy, o, kWave);
   }
-  if (!live || part != 0) return;
+  if constexpr (SPLIT) {
+    if (lane < 8) s_part[wave][lane] = make_float4(p.m, p.s, p.t, zy);
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int k = 1; k < 4; ++k) {
+        const float4 q = s_part[k][lane & 7];
+        p = part_merge(p, Part{q.x, q.y, q.z});
+        zy += q.w;
+      }
+    }
+  }
+  if (lane >= 8 || !live || (SPLIT && wave != 0)) return;
   if (zy_c) zy = zy_c[n];                                   // taken logits computed beforehand
   const int64_t row = rowsel ? rowsel[n] : n;
   const int y = ids[row];
@@ -1291,22 +1447,72 @@ umas_status check_ws(void* ws, size_t have, size_t need) {
   return UMAS_OK;
 }
 
+int device_cus() {
+  int dev = 0, n_cu = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
+    n_cu = 64;
+  return n_cu;
+}
+template <int PPW, class... Args>
+void launch_score_few_ppw(int ni, unsigned grid, hipStream_t st, Args... args) {
+  if constexpr (PPW <= 4)
+    if (ni > 2) { hipLaunchKernelGGL((k_score_few<4, PPW>), dim3(grid), dim3(kFewT), 0, st, args...); return; }
+  if (ni <= 1) hipLaunchKernelGGL((k_score_few<1, PPW>), dim3(grid), dim3(kFewT), 0, st, args...);
+  else hipLaunchKernelGGL((k_score_few<2, PPW>), dim3(grid), dim3(kFewT), 0, st, args...);
+}
+template <class... Args>
+void launch_score_few(int ppw, Args... args) {
+  switch (ppw) {
+    case 1: return launch_score_few_ppw<1>(args...);
+    case 2: return launch_score_few_ppw<2>(args...);
+    case 3: return launch_score_few_ppw<3>(args...);
+    case 4: return launch_score_few_ppw<4>(args...);
+    case 5: return launch_score_few_ppw<5>(args...);
+    case 6: return launch_score_few_ppw<6>(args...);
+    case 7: return launch_score_few_ppw<7>(args...);
+    default: return launch_score_few_ppw<8>(args...);
+  }
+}
+
+// decided by the rows of the call, not of the chunk: a row's result does not depend on how the rows are chunked
+template <class... Args>
+void launch_finalize(int64_t rows, int64_t n_sel, hipStream_t st, Args... args) {
+  if (n_sel < kFinSplitRows) hipLaunchKernelGGL(k_score_finalize<true>, dim3(cdiv(rows, 8)), dim3(256), 0, st, args...);
+  else hipLaunchKernelGGL(k_score_finalize<false>, dim3(cdiv(rows, 32)), dim3(256), 0, st, args...);
+}
+
 // Forward scoring of the selected rows into compact arrays and/or scattered outputs.
 umas_status run_score(const void* H, const void* W, umas_dtype dt, int d, int V, const int32_t* ids,
                       const int32_t* rowsel, int64_t n_sel, const ScoreWs& w, float* logp, float* lse,
                       float* entropy, hipStream_t st) {
   if (n_sel == 0) return UMAS_OK;
   if (dt == UMAS_BF16) {
-    const int tiles_m = (V + Cfg::BM - 1) / Cfg::BM;
+    int tiles_m = (V + Cfg::BM - 1) / Cfg::BM;
     const int tiles_n = static_cast<int>((n_sel + Cfg::BN - 1) / Cfg::BN);
-    const int64_t n_pad = round_up(n_sel, Cfg::BN);
-    hipLaunchKernelGGL(k_score_tiles, dim3(tile_grid<kGM, kGN>(tiles_m, tiles_n, kTilesPerWg)), dim3(Cfg::T), 0, st,
-                       static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), d, V, rowsel, n_sel, ids,
-                       tiles_m, tiles_n, w.partial, n_pad);
-    UMAS_LAUNCHED("k_score_tiles");
-    hipLaunchKernelGGL(k_score_finalize, dim3(cdiv(n_sel, 32)), dim3(256), 0, st, w.partial, tiles_m, n_pad,
-                       static_cast<int64_t>(0), n_sel, static_cast<const float*>(nullptr), rowsel, ids, V, w.logp_c, w.lse_c,
-                       w.ent_c, logp, lse, entropy);
+    int64_t n_pad = round_up(n_sel, Cfg::BN);
+    if (n_sel <= few_rows(d)) {
+      // partials [workgroups][rows rounded to 16]: no more than the tiles' [V / 256][rows rounded to 256]
+      const int ni = n_sel <= 16 ? 1 : n_sel <= 32 ? 2 : 4;
+      n_pad = ni * 16;
+      tiles_m = std::min(std::min(device_cus(), tiles_m * static_cast<int>(Cfg::BN / n_pad)), static_cast<int>(cdiv(V, 16)));
+      launch_score_few(few_pieces(d), ni, tiles_m, st, static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), d, V, rowsel,
+                       static_cast<int>(n_sel), ids, w.partial, static_cast<int>(n_pad));
+      UMAS_LAUNCHED("k_score_few");
+    } else if (n_sel <= NarrowCfg::BN) {                     // ceil(V / 128) 128 <= ceil(V / 256) 256: the partials fit as well
+      n_pad = NarrowCfg::BN;
+      tiles_m = (V + NarrowCfg::BM - 1) / NarrowCfg::BM;
+      hipLaunchKernelGGL(k_score_narrow, dim3(tile_grid<kGM, kGN>(tiles_m, 1, kTilesPerWg)), dim3(NarrowCfg::T), 0, st,
+                         static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), d, V, rowsel, n_sel, ids,
+                         tiles_m, 1, w.partial, n_pad);
+      UMAS_LAUNCHED("k_score_narrow");
+    } else {
+      hipLaunchKernelGGL(k_score_tiles, dim3(tile_grid<kGM, kGN>(tiles_m, tiles_n, kTilesPerWg)), dim3(Cfg::T), 0, st,
+                         static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), d, V, rowsel, n_sel, ids,
+                         tiles_m, tiles_n, w.partial, n_pad);
+      UMAS_LAUNCHED("k_score_tiles");
+    }
+    launch_finalize(n_sel, n_sel, st, w.partial, tiles_m, n_pad, static_cast<int64_t>(0), n_sel, static_cast<const float*>(nullptr), rowsel, ids, V,
+                    w.logp_c, w.lse_c, w.ent_c, logp, lse, entropy);
     UMAS_LAUNCHED("k_score_finalize");
   } else {
     hipLaunchKernelGGL(k_score_f32, dim3(static_cast<unsigned>(n_sel)), dim3(256), d * sizeof(float), st,
@@ -1517,7 +1723,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
                        const int32_t* h_rowmap, const float* sc) -> umas_status {
     const int64_t mcp = round_up(rows, 256);
     const int tiles_r = static_cast<int>(mcp / 256), tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
-    const unsigned grid_dh = tile_grid<kGM, kGN>(tiles_r, tiles_d, 1, sl.n);
+    const unsigned grid_dh = group_grid<kGM, kGN>(tiles_r, tiles_d, sl.n);
     const unsigned grid_dw = static_cast<unsigned>(max_dw_groups_per_xcd(tiles_v, tiles_d)) * kGM * kGN * 8;
     hipLaunchKernelGGL(k_gemm_dh_dw, dim3(grid_dh + grid_dw), dim3(Cfg::T), 0, st, op, Vp, mcp, Wb, Hx, hx_blocked, h_rowmap, d, V, tiles_v,
                        tiles_d, sl, tiles_r, w.live, w.blk_orig, static_cast<uint16_t*>(dH), dW, (accumulate_dW || c0 > 0) ? 1 : 0,
@@ -1565,9 +1771,8 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
                          Wb, Hb, d, V, rowsel, c0, rows, ids, tiles_v, tiles_r, w.score.partial, n_pad, w.cref, E, Vp, w.flags,
                          w.blk_cidx);
       UMAS_LAUNCHED("k_score_keep_tiles");
-      hipLaunchKernelGGL(k_score_finalize, dim3(cdiv(rows, 32)), dim3(256), 0, st, w.score.partial, tiles_v, n_pad, c0,
-                         c0 + rows, w.cref, rowsel, ids, V, w.score.logp_c, w.score.lse_c, w.score.ent_c, logp_new,
-                         static_cast<float*>(nullptr), static_cast<float*>(nullptr));
+      launch_finalize(rows, n_sel, st, w.score.partial, tiles_v, n_pad, c0, c0 + rows, w.cref, rowsel, ids, V, w.score.logp_c, w.score.lse_c,
+                      w.score.ent_c, logp_new, static_cast<float*>(nullptr), static_cast<float*>(nullptr));
       UMAS_LAUNCHED("k_score_finalize");
       hipLaunchKernelGGL(k_ppo_rows, dim3(cdiv(rows, kRowBlock)), dim3(kRowBlock), (1 + n_roles) * kStat * sizeof(double),
                          st, norm, c0, c0 + rows, rowsel, ids, V, w.score.logp_c, w.score.ent_c, logp_old, adv, tok_role,

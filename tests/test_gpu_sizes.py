@@ -66,3 +66,37 @@ def test_update_with_room_for_few_slices(n, d, V, extra_tiles):
 
 def test_update_with_dh_at_an_address_that_is_not_a_multiple_of_eight():
     check_update(np.random.default_rng(5), 300, 64, 3000, shift_dH=2)
+
+
+def check_scores(rng, n_sel, d, V, select, static):
+    n = n_sel + 7 if select else n_sel
+    H = wl.round_to_bf16((rng.normal(size=(n, d)) / np.sqrt(d) * 3).astype(np.float32))
+    W = wl.round_to_bf16(rng.normal(size=(V, d)).astype(np.float32))
+    ids = rng.integers(0, V, size=n).astype(np.int32)
+    sel = rng.permutation(n)[:n_sel].astype(np.int32)
+    ids[sel[-1]] = V + 1 if n_sel > 1 else V - 1
+    good = sel[ids[sel] < V]
+    logp_o, lse_o, ent_o = orc.score(H, W, np.minimum(ids, V - 1), sel)
+    fn = umas.umas_policy_logprobs_static if static else umas.umas_policy_logprobs
+    out = [x.cpu().numpy() for x in fn(P.to_dev(H, torch.bfloat16), P.to_dev(W, torch.bfloat16), P.to_dev(ids), P.to_dev(sel) if select else None)]
+    # products are exact in float32: a logit carries d 2^-24 of the sum of its terms' magnitudes, a logsumexp no more
+    bound = (d + 64) * 2.0 ** -24 * (np.abs(H[sel]).astype(np.float64) @ np.abs(W).T.astype(np.float64)).max() + 1e-5
+    for name, x, o in zip(("logp", "lse", "entropy"), out, (logp_o, lse_o, ent_o)):
+        rows = sel if name == "lse" else good
+        assert np.abs(x[rows] - o[rows]).max() <= (3 if name == "entropy" else 2) * bound, (name, n_sel, d, V)
+    assert not out[0][np.setdiff1d(np.arange(n), good)].any() and not out[2][np.setdiff1d(np.arange(n), good)].any()
+
+
+# the three scoring kernels for few rows: edges of their row counts, hidden sizes below, at and above a multiple of what
+# eight wavefronts share (512), the last one the register-resident kernel takes and the first it does not; vocabularies
+# smaller than one block of 16, than the device's workgroups, and with a last block that is nearly empty
+@pytest.mark.parametrize("d,V", [(8, 5), (200, 257), (512, 4097), (520, 3000), (2048, 1030), (2056, 700), (4096, 2500), (4104, 300)])
+@pytest.mark.parametrize("n_sel", [1, 16, 17, 33, 64, 65, 128, 129])
+def test_scoring_of_few_rows(n_sel, d, V):
+    check_scores(np.random.default_rng(n_sel + d), n_sel, d, V, select=n_sel % 2 == 1, static=n_sel in (16, 33, 65))
+
+
+# enough rows for the merge that does not split a row's tiles over the workgroup, and one less
+@pytest.mark.parametrize("n_sel", [19999, 20000])
+def test_scoring_of_many_rows(n_sel):
+    check_scores(np.random.default_rng(n_sel), n_sel, 64, 700, select=False, static=False)
