@@ -589,16 +589,21 @@ k_ppo_rows(int64_t norm, int64_t n_begin, int64_t n_end, const int32_t* __restri
            float dual_clip, float k_ent, const float* __restrict__ logp_ref, float kl_coef, int label_apart,
            const float* __restrict__ lse_c, float* __restrict__ g_c,
            float* __restrict__ a_c, float* __restrict__ kz_c, double* __restrict__ blk_stats) {
-  extern __shared__ double s_acc[];   // [(1+n_roles) * kStat]
+  extern __shared__ double s_acc[];   // [wavefronts][(1+n_roles) * kStat]
   const int nacc = (1 + n_roles) * kStat;
-  for (int i = threadIdx.x; i < nacc; i += blockDim.x) s_acc[i] = 0.0;
-  __syncthreads();
+  const int lane = threadIdx.x & (kWave - 1);
+  double* const w_acc = s_acc + threadIdx.x / kWave * nacc;
+  for (int i = lane; i < nacc; i += kWave) w_acc[i] = 0.0;
+  __builtin_amdgcn_wave_barrier();
+  float L = 0.f, clipped = 0.f, en = 0.f, kl = 0.f;
+  int role = -1, valid = 0;
   const int64_t n = n_begin + static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;   // n_begin is a multiple of the block size
   if (n < n_end) {
     const int64_t row = rowsel ? rowsel[n] : n;
     const int y = ids[row];
     const bool ok = y >= 0 && y < V;
-    float L = 0.f, g = 0.f, clipped = 0.f, en = 0.f, kl = 0.f, lp = 0.f;
+    float g = 0.f, lp = 0.f;
+    valid = ok;
     if (ok) {
       lp = logp_c[n];
       const float lo = logp_old ? logp_old[row] : lp, A = adv[row];   // no old log-probs: the update is on-policy, ratio 1
@@ -629,49 +634,59 @@ k_ppo_rows(int64_t norm, int64_t n_begin, int64_t n_end, const int32_t* __restri
     // entropy bonus k_ent p (log p + entropy); a row with an invalid id has neither
     a_c[n] = ok ? -g + k_ent * (en - lse_c[n]) : 0.f;
     kz_c[n] = ok ? k_ent : 0.f;
-    const int role = (tok_role && n_roles > 0) ? tok_role[row] : -1;
-    for (int pass = 0; pass < 2; ++pass) {
-      if (pass == 1 && (role < 0 || role >= n_roles)) break;
-      double* a = s_acc + (pass == 0 ? 0 : (1 + role) * kStat);
-      atomicAdd(a + 0, static_cast<double>(L));
-      atomicAdd(a + 1, static_cast<double>(clipped));
-      atomicAdd(a + 2, static_cast<double>(en));
-      atomicAdd(a + 3, static_cast<double>(kl));
-      atomicAdd(a + 4, 1.0);
-      atomicAdd(a + 5, ok ? 0.0 : 1.0);
-    }
+    role = (tok_role && n_roles > 0) ? tok_role[row] : -1;
+  }
+  // Sums over the wavefront's rows, the model's and then each role's that occurs among them (usually one or two); the
+  // wavefronts' sums are added in a fixed order.  (256 threads adding to six float64 words by atomics took 18 us.)
+  const unsigned long long in = __ballot(n < n_end);
+  auto sum_into = [&](unsigned long long group, double* acc) {
+    const bool mine = (group >> lane) & 1;
+    const double sl = wave_sum(mine ? static_cast<double>(L) : 0.0), se = wave_sum(mine ? static_cast<double>(en) : 0.0);
+    const double sk = wave_sum(mine ? static_cast<double>(kl) : 0.0);
+    const int c = __popcll(__ballot(mine && clipped != 0.f)), bad = __popcll(__ballot(mine && !valid));
+    if (lane == 0) { acc[0] = sl; acc[1] = c; acc[2] = se; acc[3] = sk; acc[4] = __popcll(group); acc[5] = bad; }
+  };
+  sum_into(in, w_acc);
+  unsigned long long left = in & __ballot(role >= 0 && role < n_roles);
+  while (left) {                                              // the same for every lane
+    const int r = __shfl(role, __ffsll(static_cast<long long>(left)) - 1, kWave);
+    const unsigned long long group = left & __ballot(role == r);
+    sum_into(group, w_acc + (1 + r) * kStat);
+    left &= ~group;
   }
   __syncthreads();
   const int64_t blk = n_begin / kRowBlock + blockIdx.x;
-  for (int i = threadIdx.x; i < nacc; i += blockDim.x) blk_stats[blk * nacc + i] = s_acc[i];
+  for (int i = threadIdx.x; i < nacc; i += blockDim.x) {
+    double v = 0.0;
+    for (int w = 0; w < kRowBlock / kWave; ++w) v += s_acc[w * nacc + i];
+    blk_stats[blk * nacc + i] = v;
+  }
 }
 
+// One workgroup for the model and one for each role.
 __global__ void __launch_bounds__(256)
 k_ppo_stats(int nblk, int n_roles, float entropy_coef, int64_t norm_rows, const double* __restrict__ blk_stats,
             umas_loss_stats* __restrict__ stats) {
   __shared__ double smem[32];
-  const int nacc = (1 + n_roles) * kStat;
-  for (int k = 0; k <= n_roles; ++k) {
-    double sum[kStat];
-    for (int j = 0; j < kStat; ++j) {
-      double v = 0.0;
-      for (int b = threadIdx.x; b < nblk; b += blockDim.x) v += blk_stats[static_cast<int64_t>(b) * nacc + k * kStat + j];
-      sum[j] = block_sum<double>(v, smem);
-    }
-    if (threadIdx.x == 0) {
-      const double cnt = sum[4];
-      umas_loss_stats s;
-      // the model's loss over the caller's normaliser when one is given: micro-batch losses then add up
-      const double den = (k == 0 && norm_rows > 0) ? static_cast<double>(norm_rows) : cnt;
-      s.loss = cnt > 0 ? static_cast<float>((sum[0] - static_cast<double>(entropy_coef) * sum[2]) / den) : 0.f;
-      s.clip_frac = cnt > 0 ? static_cast<float>(sum[1] / cnt) : 0.f;
-      s.entropy_mean = cnt > 0 ? static_cast<float>(sum[2] / cnt) : 0.f;
-      s.approx_kl = cnt > 0 ? static_cast<float>(sum[3] / cnt) : 0.f;
-      s.n_scored = static_cast<int64_t>(cnt);
-      s.n_invalid_ids = static_cast<int64_t>(sum[5]);
-      stats[k] = s;
-    }
-  }
+  const int nacc = (1 + n_roles) * kStat, k = blockIdx.x;
+  double v[kStat] = {}, sum[kStat];
+  for (int b = threadIdx.x; b < nblk; b += blockDim.x)
+#pragma unroll
+    for (int j = 0; j < kStat; ++j) v[j] += blk_stats[static_cast<int64_t>(b) * nacc + k * kStat + j];
+#pragma unroll
+  for (int j = 0; j < kStat; ++j) sum[j] = block_sum<double>(v[j], smem);
+  if (threadIdx.x != 0) return;
+  const double cnt = sum[4];
+  umas_loss_stats s;
+  // the model's loss over the caller's normaliser when one is given: micro-batch losses then add up
+  const double den = (k == 0 && norm_rows > 0) ? static_cast<double>(norm_rows) : cnt;
+  s.loss = cnt > 0 ? static_cast<float>((sum[0] - static_cast<double>(entropy_coef) * sum[2]) / den) : 0.f;
+  s.clip_frac = cnt > 0 ? static_cast<float>(sum[1] / cnt) : 0.f;
+  s.entropy_mean = cnt > 0 ? static_cast<float>(sum[2] / cnt) : 0.f;
+  s.approx_kl = cnt > 0 ? static_cast<float>(sum[3] / cnt) : 0.f;
+  s.n_scored = static_cast<int64_t>(cnt);
+  s.n_invalid_ids = static_cast<int64_t>(sum[5]);
+  stats[k] = s;
 }
 
 // ------------------------------------------------------------------ bf16: blocks of rows that have a gradient
@@ -684,64 +699,88 @@ struct LiveInfo {
   int32_t k_rows;        // rows of the packed operands that exist (the chunk's last block may be partly filled)
   XcdGroups dw_groups;   // dW tile groups per XCD (see share_dw_groups)
 };
-__global__ void __launch_bounds__(256)
-k_live_flags(int64_t n_sel, const int32_t* __restrict__ rowsel, const float* __restrict__ adv, int32_t* __restrict__ blk_live) {
-  const int64_t n = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  const int live = n < n_sel && adv[rowsel ? rowsel[n] : n] != 0.f;
-  const int any = __syncthreads_or(live);
-  if (threadIdx.x == 0) blk_live[blockIdx.x] = any;
-}
 // Shares of the dW tile groups per XCD for k_gemm_dh_dw: every XCD first works through its dH groups (contiguous
 // ranges, slice after slice; a group costs about Vp / slices of K per tile), then dW groups (k_len of K
 // per tile) go to the XCDs so that all finish as evenly as whole groups allow, at most max_groups to one XCD (the grid has
 // no more; 8 max_groups cover all groups).
 constexpr int64_t kTileOverheadK = 768;   // what a tile costs besides its K steps (first loads, epilogue), as a length of K
+// Called by one wavefront; lane x of every eight works for XCD x (all eights do the same).  (One thread walking the eight XCDs took 20 us.)
 __device__ void share_dw_groups(int tiles_r, int tiles_v, int tiles_d, int64_t Vp, int slices, int64_t k_len, int max_groups, XcdGroups* out) {
-  const int64_t groups_dh = static_cast<int64_t>((tiles_r + kGM - 1) / kGM) * ((tiles_d + kGN - 1) / kGN) * slices;
-  const int64_t per_xcd = (groups_dh + 7) / 8;
-  int64_t load[8];
-  int cnt[8] = {};
-  for (int x = 0; x < 8; ++x) {
-    int64_t n = groups_dh - x * per_xcd;
-    n = n < 0 ? 0 : (n > per_xcd ? per_xcd : n);
-    load[x] = n * (Vp / slices + kTileOverheadK);
-  }
-  const int64_t groups_dw = static_cast<int64_t>((tiles_v + kGM - 1) / kGM) * ((tiles_d + kGN - 1) / kGN);
+  const int x = threadIdx.x & 7;
+  auto sum8 = [](int v) {
+#pragma unroll
+    for (int o = 4; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    return v;
+  };
+  const int groups_dh = (tiles_r + kGM - 1) / kGM * ((tiles_d + kGN - 1) / kGN) * slices;
+  const int per_xcd = (groups_dh + 7) / 8;
+  const int n_dh = max(0, min(groups_dh - x * per_xcd, per_xcd));
+  const int64_t load = n_dh * (Vp / slices + kTileOverheadK);
+  const int groups_dw = (tiles_v + kGM - 1) / kGM * ((tiles_d + kGN - 1) / kGN);
+  int cnt;
   if (k_len <= 0) {                                    // nothing to even out
-    for (int x = 0; x < 8; ++x) cnt[x] = static_cast<int>(groups_dw / 8 + (x < groups_dw % 8 ? 1 : 0));
+    cnt = groups_dw / 8 + (x < groups_dw % 8 ? 1 : 0);
   } else {
     // the lowest level T up to which the XCDs can be filled with whole groups so that all groups are placed ...
-    auto take = [&](int x, int64_t T) {
+    auto take = [&](int64_t T) {
       // (a double quotient: the operands stay far below 2^53 and 64-bit integer division is slow here)
-      const int64_t n = T > load[x] ? static_cast<int64_t>(static_cast<double>(T - load[x]) / static_cast<double>(k_len)) : 0;
+      const int64_t n = T > load ? static_cast<int64_t>(static_cast<double>(T - load) / static_cast<double>(k_len)) : 0;
       return static_cast<int>(n < max_groups ? n : max_groups);
     };
-    int64_t lo = load[0], hi = load[0];
-    for (int x = 1; x < 8; ++x) { lo = load[x] < lo ? load[x] : lo; hi = load[x] > hi ? load[x] : hi; }
-    hi += groups_dw * k_len;
-    while (lo < hi) {
-      const int64_t mid = lo + (hi - lo) / 2;
-      int64_t sum = 0;
-      for (int x = 0; x < 8; ++x) sum += take(x, mid);
-      if (sum >= groups_dw) hi = mid; else lo = mid + 1;
+    int64_t lo = load, hi = load;
+#pragma unroll
+    for (int o = 4; o > 0; o >>= 1) {
+      lo = min(lo, static_cast<int64_t>(__shfl_xor(static_cast<long long>(lo), o, kWave)));
+      hi = max(hi, static_cast<int64_t>(__shfl_xor(static_cast<long long>(hi), o, kWave)));
     }
-    int64_t total = 0;
-    for (int x = 0; x < 8; ++x) { cnt[x] = take(x, lo); total += cnt[x]; }
+    hi += groups_dw * k_len;
+    while (lo < hi) {                                  // the same in every lane
+      const int64_t mid = lo + (hi - lo) / 2;
+      if (sum8(take(mid)) >= groups_dw) hi = mid; else lo = mid + 1;
+    }
+    cnt = take(lo);
     // ... and the few groups too many at that level come off the XCDs that would finish last
-    for (; total > groups_dw; --total) {
-      int worst = -1;
-      for (int x = 0; x < 8; ++x)
-        if (cnt[x] > 0 && (worst < 0 || load[x] + cnt[x] * k_len > load[worst] + cnt[worst] * k_len)) worst = x;
-      --cnt[worst];
+    for (int total = sum8(cnt); total > groups_dw; --total) {
+      int64_t worst = cnt > 0 ? load + cnt * k_len : -1;
+#pragma unroll
+      for (int o = 4; o > 0; o >>= 1) worst = max(worst, static_cast<int64_t>(__shfl_xor(static_cast<long long>(worst), o, kWave)));
+      const unsigned long long who = __ballot(cnt > 0 && load + cnt * k_len == worst);
+      if (x == __ffsll(static_cast<long long>(who)) - 1) --cnt;
     }
   }
-  out->first[0] = 0;
-  for (int x = 0; x < 8; ++x) out->first[x + 1] = out->first[x] + cnt[x];
+  int first = cnt;                                     // inclusive prefix sums: where the next XCD's groups start
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) {
+    const int t = __shfl_up(first, o, kWave);
+    if (x >= o) first += t;
+  }
+  if (threadIdx.x == 0) out->first[0] = 0;
+  if (threadIdx.x < 8) out->first[x + 1] = first;
 }
 inline int max_dw_groups_per_xcd(int tiles_v, int tiles_d) {   // 8 x this many cover every group with room to even out
   const int64_t groups_dw = static_cast<int64_t>((tiles_v + kGM - 1) / kGM) * ((tiles_d + kGN - 1) / kGN);
   return static_cast<int>((groups_dw + 7) / 8 + 20);
 }
+// What opens the keeping update, in one launch: the first nblk workgroups mark the live blocks of 256 selected rows and
+// clear their flags, the others take the rows' references and clear what the call defines everywhere (logp_new when rows
+// are left out, dH), each its share.
+struct OpenArgs {
+  const uint16_t* H;
+  const uint16_t* W;
+  int d, V;
+  const int32_t* rowsel;
+  int64_t n_sel;
+  const int32_t* ids;
+  const float* adv;
+  int nblk;
+  int32_t* blk_live;
+  int32_t* flags;
+  float* cref;
+  uint32_t* dH;          // n_rows * d bf16 as words
+  int64_t dh_words;
+  float* logp_new;       // NULL: nothing to clear
+  int64_t n_rows;
+};
 // One workgroup per chunk: packs the live blocks (all of them with all_live), blk0 = first block of the chunk.
 __global__ void __launch_bounds__(512)
 k_live_scan(int blk0, int nblk, int64_t rows, int all_live, int tiles_v, int tiles_d, int64_t Vp, int slices, int max_groups,
@@ -763,6 +802,8 @@ k_live_scan(int blk0, int nblk, int64_t rows, int all_live, int tiles_v, int til
     info->n_live = total;
     const int64_t last_rows = rows - static_cast<int64_t>(nblk - 1) * 256;     // rows of the chunk's last block
     info->k_rows = static_cast<int32_t>(s_last_live ? static_cast<int64_t>(total - 1) * 256 + last_rows : static_cast<int64_t>(total) * 256);
+  }
+  if (t < kWave) {
     share_dw_groups(total, tiles_v, tiles_d, Vp, slices, total > 0 ? static_cast<int64_t>(total) * 256 + kTileOverheadK : 0, max_groups,
                     &info->dw_groups);
   }
@@ -775,33 +816,54 @@ __device__ __forceinline__ void bf16x8_to_f32(const uint4 v, float (&o)[8]) {
   o[4] = __uint_as_float(v.z << 16); o[5] = __uint_as_float(v.z & 0xffff0000u);
   o[6] = __uint_as_float(v.w << 16); o[7] = __uint_as_float(v.w & 0xffff0000u);
 }
-// cref[n] = h_n . W[y_n], the taken token's logit (never above the row's logsumexp); NaN for an invalid id.
-// One wavefront per selected row.
 __global__ void __launch_bounds__(256)
-k_label_logit(const uint16_t* __restrict__ H, const uint16_t* __restrict__ W, int d, int V,
-              const int32_t* __restrict__ rowsel, int64_t n_sel, const int32_t* __restrict__ ids,
-              float* __restrict__ cref) {
-  const int lane = threadIdx.x & 63;
-  const int64_t n = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave;
-  if (n >= n_sel) return;
-  const int64_t row = rowsel ? rowsel[n] : n;
-  const int y = ids[row];
-  if (y < 0 || y >= V) {
-    if (lane == 0) cref[n] = NAN;
+k_update_open(OpenArgs A) {
+  if (static_cast<int>(blockIdx.x) < A.nblk) {
+    const int64_t n = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int live = n < A.n_sel && A.adv[A.rowsel ? A.rowsel[n] : n] != 0.f;
+    const int any = __syncthreads_or(live);
+    if (threadIdx.x == 0) {
+      A.blk_live[blockIdx.x] = any;
+      A.flags[blockIdx.x] = 0;
+    }
     return;
   }
-  const uint4* h = reinterpret_cast<const uint4*>(H + row * d);
-  const uint4* w = reinterpret_cast<const uint4*>(W + static_cast<int64_t>(y) * d);
-  float s = 0.f;
-  for (int k = lane; k < d / 8; k += kWave) {
-    float a[8], b[8];
-    bf16x8_to_f32(h[k], a);
-    bf16x8_to_f32(w[k], b);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) s = fmaf(a[j], b[j], s);
+  const int64_t blk = static_cast<int64_t>(blockIdx.x) - A.nblk, nb = static_cast<int64_t>(gridDim.x) - A.nblk;
+  {
+    const int64_t n4 = A.dh_words / 4, stride = nb * 256;
+    uint4* const p = reinterpret_cast<uint4*>(A.dH);
+    if (reinterpret_cast<uintptr_t>(p) % 16 == 0) {
+      for (int64_t i = blk * 256 + threadIdx.x; i < n4; i += stride) p[i] = make_uint4(0u, 0u, 0u, 0u);
+      for (int64_t i = 4 * n4 + blk * 256 + threadIdx.x; i < A.dh_words; i += stride) A.dH[i] = 0u;
+    } else {
+      for (int64_t i = blk * 256 + threadIdx.x; i < A.dh_words; i += stride) A.dH[i] = 0u;
+    }
+    if (A.logp_new)
+      for (int64_t i = blk * 256 + threadIdx.x; i < A.n_rows; i += stride) A.logp_new[i] = 0.f;
   }
-  s = wave_sum(s);
-  if (lane == 0) cref[n] = s;
+  // cref[n] = h_n . W[y_n], the taken token's logit (never above the row's logsumexp); NaN for an invalid id.
+  // One wavefront per selected row.
+  const int lane = threadIdx.x & 63;
+  for (int64_t n = blk * 4 + threadIdx.x / kWave; n < A.n_sel; n += nb * 4) {
+    const int64_t row = A.rowsel ? A.rowsel[n] : n;
+    const int y = A.ids[row];
+    if (y < 0 || y >= A.V) {
+      if (lane == 0) A.cref[n] = NAN;
+      continue;
+    }
+    const uint4* h = reinterpret_cast<const uint4*>(A.H + row * A.d);
+    const uint4* w = reinterpret_cast<const uint4*>(A.W + static_cast<int64_t>(y) * A.d);
+    float s = 0.f;
+    for (int k = lane; k < A.d / 8; k += kWave) {
+      float a[8], b[8];
+      bf16x8_to_f32(h[k], a);
+      bf16x8_to_f32(w[k], b);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) s = fmaf(a[j], b[j], s);
+    }
+    s = wave_sum(s);
+    if (lane == 0) A.cref[n] = s;
+  }
 }
 // Row factor sc[n] = a_n exp(c_n - lse_n) of dz = sc E, and Hs[n - c0, :] = bf16(sc[n] h_n), the operand dW reads, in
 // column blocks [d / 256][mcp][256].
@@ -1174,16 +1236,17 @@ k_dh_reduce(DhSlices sl, int tiles_r, int tiles_d, const uint16_t* __restrict__ 
 // every token in the group is its leader; a wavefront sums the leader and its followers in registers, 2048 columns at
 // a time (16-byte loads, a lane owning eight consecutive columns of each of four pieces), turns every piece through
 // its corner of LDS so that consecutive lanes hold consecutive columns, and issues one atomic per element of the sum.
+// A wavefront needs about a microsecond per token, so with few groups each is worked on by several workgroups.
 constexpr int kOneHotRows = 128;
 constexpr int kOneHotPieces = 4;                    // pieces of 512 columns a wavefront holds at a time
 __global__ void __launch_bounds__(256)
 k_dw_onehot(const uint16_t* __restrict__ H, int d, const int32_t* __restrict__ rowsel, int64_t n_sel,
             const int32_t* __restrict__ ids, const float* __restrict__ g_c, float* __restrict__ dW) {
-  __shared__ int32_t s_id[kOneHotRows];             // token of the row, -1 when the row adds nothing
+  __shared__ __attribute__((aligned(16))) int32_t s_id[kOneHotRows];   // token of the row, -1 when the row adds nothing
   __shared__ float s_g[kOneHotRows];
   __shared__ int64_t s_row[kOneHotRows];
   __shared__ int32_t s_leader[kOneHotRows];         // the group's leaders, compacted
-  __shared__ int32_t s_n_leader;
+  __shared__ int32_t s_n_leader[kOneHotRows / kWave];
   __shared__ float s_turn[256 / kWave][8 * kWave];  // one piece per wavefront, in column order
   const int tid = threadIdx.x, lane = tid & 63, wave = tid / kWave;
   if (tid < kOneHotRows) {
@@ -1198,18 +1261,29 @@ k_dw_onehot(const uint16_t* __restrict__ H, int d, const int32_t* __restrict__ r
     }
     s_id[tid] = id; s_g[tid] = g; s_row[tid] = row;
   }
-  if (tid == 0) s_n_leader = 0;
   __syncthreads();
+  bool leader = false;
   if (tid < kOneHotRows) {
     const int32_t id = s_id[tid];
-    bool leader = id >= 0;
-    for (int u = 0; u < tid && leader; ++u) leader = s_id[u] != id;
-    if (leader) s_leader[atomicAdd(&s_n_leader, 1)] = tid;
+    int earlier = 0;                                // rows of the group in front of this one with its token
+#pragma unroll 8
+    for (int u = 0; u < kOneHotRows; u += 4) {
+      const int4 o = *reinterpret_cast<const int4*>(s_id + u);
+      earlier += (o.x == id && u < tid) + (o.y == id && u + 1 < tid) + (o.z == id && u + 2 < tid) + (o.w == id && u + 3 < tid);
+    }
+    leader = id >= 0 && earlier == 0;
   }
+  const unsigned long long leaders = __ballot(leader);       // listed in row order: every workgroup of the group has the same list
+  if (lane == 0 && wave < kOneHotRows / kWave) s_n_leader[wave] = __popcll(leaders);
   __syncthreads();
-  const int n_leader = s_n_leader;
+  int n_leader = 0, before = 0;
+#pragma unroll
+  for (int k = 0; k < kOneHotRows / kWave; ++k) { before += k < wave ? s_n_leader[k] : 0; n_leader += s_n_leader[k]; }
+  if (leader) s_leader[before + __popcll(leaders & ((1ull << lane) - 1))] = tid;
+  __syncthreads();
   float* turn = s_turn[wave];
-  for (int li = wave; li < n_leader; li += 256 / kWave) {
+  // the group's tokens are spread over the wavefronts of gridDim.y workgroups
+  for (int li = wave + blockIdx.y * (256 / kWave); li < n_leader; li += 256 / kWave * gridDim.y) {
     const int32_t id = s_id[s_leader[li]];
     float* dst = dW + static_cast<int64_t>(id) * d;
     unsigned long long same[kOneHotRows / kWave];   // the rows of the group that took this token
@@ -1447,6 +1521,12 @@ umas_status check_ws(void* ws, size_t have, size_t need) {
   return UMAS_OK;
 }
 
+// Four workgroups per compute unit, at most one wavefront per row: 203 rows of 3584 145 -> 29 us, 725 rows of 2048 88 ->
+// 25 us, 39 000 rows (307 groups, three workgroups each) 203 -> 195 us; twice and four times as many are no faster.
+dim3 onehot_grid(int64_t n_sel) {
+  const unsigned groups = cdiv(n_sel, kOneHotRows);
+  return dim3(groups, std::min(std::max(1024 / groups, 1u), static_cast<unsigned>(kOneHotRows / 4)));
+}
 int device_cus() {
   int dev = 0, n_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
@@ -1678,11 +1758,15 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
   PpoWs w;
   carve_ppo(c, w, n_sel, d, V, dtype, n_roles);
 
-  // rows that are not selected, and (bf16 without an entropy bonus) selected rows in blocks without any gradient,
+  // Without an entropy bonus dz is a row factor times the softmax: the scoring pass keeps the numerators
+  // and the logits are not computed a second time.
+  const bool keep = dtype == UMAS_BF16 && entropy_coef == 0.f && n_sel > 0;
+  // rows that are not selected, and (keeping path, see k_update_open) selected rows in blocks without any gradient,
   // are not visited by the backward
-  const bool skips_dead_blocks = dtype == UMAS_BF16 && entropy_coef == 0.f;
-  if (rowsel && n_rows > 0 && logp_new) UMAS_HIP(fill_bytes_zero(logp_new, n_rows * sizeof(float), st));
-  if ((rowsel || skips_dead_blocks) && n_rows > 0) UMAS_HIP(fill_bytes_zero(dH, static_cast<size_t>(n_rows) * d * esz, st));
+  if (!keep && rowsel && n_rows > 0) {
+    if (logp_new) UMAS_HIP(fill_bytes_zero(logp_new, n_rows * sizeof(float), st));
+    UMAS_HIP(fill_bytes_zero(dH, static_cast<size_t>(n_rows) * d * esz, st));
+  }
   if (!accumulate_dW && n_sel == 0) UMAS_HIP(fill_bytes_zero(dW, static_cast<size_t>(V) * d * sizeof(float), st));
 
   // chunks of selected rows sized to the workspace
@@ -1700,11 +1784,9 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
                "workspace cannot hold one chunk of %lld rows", static_cast<long long>(mc));
 
   const int nblk = cdiv(n_sel > 0 ? n_sel : 1, kRowBlock);
+  const size_t kPpoLds = (kRowBlock / kWave) * (1 + n_roles) * kStat * sizeof(double);
   const int64_t norm = norm_rows > 0 ? norm_rows : n_sel;   // rows the token mean is taken over
   const float k_ent = norm > 0 ? entropy_coef / static_cast<float>(norm) : 0.f;
-  // Without an entropy bonus dz is a row factor times the softmax: the scoring pass keeps the numerators
-  // and the logits are not computed a second time.
-  const bool keep = dtype == UMAS_BF16 && entropy_coef == 0.f && n_sel > 0;
   const int64_t Vp = round_up(V, 256);
   const uint16_t* Wb = static_cast<const uint16_t*>(W);
   const uint16_t* Hb = static_cast<const uint16_t*>(H);
@@ -1741,18 +1823,18 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     // forward scoring and the surrogate
     s = run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w.score, logp_new, nullptr, nullptr, st);
     if (s != UMAS_OK) return s;
-    hipLaunchKernelGGL(k_ppo_rows, dim3(nblk), dim3(kRowBlock), (1 + n_roles) * kStat * sizeof(double), st, norm,
+    hipLaunchKernelGGL(k_ppo_rows, dim3(nblk), dim3(kRowBlock), kPpoLds, st, norm,
                        static_cast<int64_t>(0), n_sel, rowsel, ids, V, w.score.logp_c, w.score.ent_c, logp_old, adv,
                        tok_role, n_roles, clip_eps, dual_clip, k_ent, logp_ref, kl_coef, dtype == UMAS_BF16 ? 1 : 0, w.score.lse_c,
                        w.g_c, w.a_c, w.kz_c,
                        w.blk_stats);
     UMAS_LAUNCHED("k_ppo_rows");
   } else {
-    hipLaunchKernelGGL(k_label_logit, dim3(cdiv(n_sel, 4)), dim3(256), 0, st, Hb, Wb, d, V, rowsel, n_sel, ids, w.cref);
-    UMAS_LAUNCHED("k_label_logit");
-    UMAS_HIP(fill_bytes_zero(w.flags, static_cast<size_t>(nblk) * sizeof(int32_t), st));
-    hipLaunchKernelGGL(k_live_flags, dim3(nblk), dim3(256), 0, st, n_sel, rowsel, adv, w.blk_live);
-    UMAS_LAUNCHED("k_live_flags");
+    OpenArgs O{Hb, Wb, d, V, rowsel, n_sel, ids, adv, nblk, w.blk_live, w.flags, w.cref, static_cast<uint32_t*>(dH),
+               n_rows * static_cast<int64_t>(d) / 2, rowsel ? logp_new : nullptr, n_rows};
+    // a wavefront per row up to 8192 workgroups; at least 1024 for the clearing
+    hipLaunchKernelGGL(k_update_open, dim3(nblk + std::min<unsigned>(std::max<unsigned>(cdiv(n_sel, 4), 1024), 8192)), dim3(256), 0, st, O);
+    UMAS_LAUNCHED("k_update_open");
     const int64_t n_pad = round_up(n_sel, Cfg::BN);
     const int tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
     const int max_groups = max_dw_groups_per_xcd(tiles_v, tiles_d);
@@ -1774,8 +1856,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       launch_finalize(rows, n_sel, st, w.score.partial, tiles_v, n_pad, c0, c0 + rows, w.cref, rowsel, ids, V, w.score.logp_c, w.score.lse_c,
                       w.score.ent_c, logp_new, static_cast<float*>(nullptr), static_cast<float*>(nullptr));
       UMAS_LAUNCHED("k_score_finalize");
-      hipLaunchKernelGGL(k_ppo_rows, dim3(cdiv(rows, kRowBlock)), dim3(kRowBlock), (1 + n_roles) * kStat * sizeof(double),
-                         st, norm, c0, c0 + rows, rowsel, ids, V, w.score.logp_c, w.score.ent_c, logp_old, adv, tok_role,
+      hipLaunchKernelGGL(k_ppo_rows, dim3(cdiv(rows, kRowBlock)), dim3(kRowBlock), kPpoLds, st, norm, c0, c0 + rows, rowsel, ids, V, w.score.logp_c, w.score.ent_c, logp_old, adv, tok_role,
                          n_roles, clip_eps, dual_clip, k_ent, logp_ref, kl_coef, 1, w.score.lse_c, w.g_c, w.a_c, w.kz_c,
                          w.blk_stats);
       UMAS_LAUNCHED("k_ppo_rows");
@@ -1790,11 +1871,11 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       if (s != UMAS_OK) return s;
     }
   }
-  hipLaunchKernelGGL(k_ppo_stats, dim3(1), dim3(256), 0, st, nblk, n_roles, entropy_coef, norm_rows, w.blk_stats, stats);
+  hipLaunchKernelGGL(k_ppo_stats, dim3(1 + n_roles), dim3(256), 0, st, nblk, n_roles, entropy_coef, norm_rows, w.blk_stats, stats);
   UMAS_LAUNCHED("k_ppo_stats");
   if (n_sel == 0) return UMAS_OK;
   if (keep) {
-    hipLaunchKernelGGL(k_dw_onehot, dim3(cdiv(n_sel, kOneHotRows)), dim3(256), 0, st, Hb, d, rowsel, n_sel, ids, w.g_c, dW);
+    hipLaunchKernelGGL(k_dw_onehot, onehot_grid(n_sel), dim3(256), 0, st, Hb, d, rowsel, n_sel, ids, w.g_c, dW);
     UMAS_LAUNCHED("k_dw_onehot");
     return UMAS_OK;
   }
@@ -1837,7 +1918,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     s = gradients(c0, rows, sl, dZ, rowsel ? Hb : Hb + c0 * d, 0, rowsel ? rowsel + c0 : nullptr, nullptr);
     if (s != UMAS_OK) return s;
   }
-  hipLaunchKernelGGL(k_dw_onehot, dim3(cdiv(n_sel, kOneHotRows)), dim3(256), 0, st, Hb, d, rowsel, n_sel, ids, w.g_c, dW);
+  hipLaunchKernelGGL(k_dw_onehot, onehot_grid(n_sel), dim3(256), 0, st, Hb, d, rowsel, n_sel, ids, w.g_c, dW);
   UMAS_LAUNCHED("k_dw_onehot");
   return UMAS_OK;
 }

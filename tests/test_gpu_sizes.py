@@ -100,3 +100,33 @@ def test_scoring_of_few_rows(n_sel, d, V):
 @pytest.mark.parametrize("n_sel", [19999, 20000])
 def test_scoring_of_many_rows(n_sel):
     check_scores(np.random.default_rng(n_sel), n_sel, 64, 700, select=False, static=False)
+
+
+# the one-hot rows of dW: one group of 128 rows spread over many workgroups, several groups over a few, every row the same
+# token and every row another; and statistics per role when a wavefront holds one role, many, and roles outside the range
+@pytest.mark.parametrize("n,n_tokens", [(1, 1), (127, 1), (129, 129), (700, 3), (5000, 400)])
+def test_one_hot_rows_and_statistics_per_role(n, n_tokens):
+    rng = np.random.default_rng(n)
+    d, V, n_roles = 72, 512, 64
+    H = wl.round_to_bf16(rng.normal(size=(n, d)).astype(np.float32) / 4)
+    W = wl.round_to_bf16(rng.normal(size=(V, d)).astype(np.float32) / 4)
+    ids = rng.integers(0, n_tokens, size=n).astype(np.int32)
+    role = np.where(np.arange(n) % 256 < 64, 5, rng.integers(-1, n_roles + 1, size=n)).astype(np.int32)
+    adv = rng.normal(size=n).astype(np.float32)
+    logp_o, lse_o, ent_o = orc.score(H, W, ids)
+    logp_old = (logp_o + 0.1 * rng.normal(size=n)).astype(np.float32)
+    inside = np.where((role >= 0) & (role < n_roles), role, n_roles)
+    st_o, g_o = orc.ppo_loss(logp_o, logp_old, adv, ent_o, None, inside, n_roles + 1, 0.2)
+    dH_o, dW_o = orc.lm_head_backward(H, W, ids, lse_o, g_o)
+    stats, _, dH, dW = umas.umas_ppo_loss_fwd_bwd(P.to_dev(H, torch.bfloat16), P.to_dev(W, torch.bfloat16), P.to_dev(ids), None,
+                                                  P.to_dev(logp_old), P.to_dev(adv), P.to_dev(role), n_roles, 0.2)
+    sg = umas.read_stats(stats)
+    assert np.array_equal(sg["n_scored"], st_o[:1 + n_roles, 4].astype(np.int64))
+    for j, name in enumerate(("loss", "clip_frac", "entropy_mean", "approx_kl")):
+        o = st_o[:1 + n_roles, j]
+        # log-probs within 1e-5 move a row's ratio, and a row on the clip boundary by its whole share
+        lim = 2.0 / np.maximum(st_o[:1 + n_roles, 4], 1) if name == "clip_frac" else 1e-4 * np.maximum(np.abs(o), 1)
+        assert (np.abs(sg[name] - o) <= lim).all(), name
+    bound_h, bound_w = P.bf16_gradient_bounds(H, W, P.oracle_dz(H, W, ids, lse_o, g_o, np.arange(n)), dH_o, dW_o, np.arange(n), ids, lse_o, g_o)
+    P.close_bounded(dH.float().cpu().numpy(), dH_o, bound_h, 1e-2, "dH")
+    P.close_bounded(dW.cpu().numpy(), dW_o, bound_w, 1e-2, "dW")
