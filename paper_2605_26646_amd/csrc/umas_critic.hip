@@ -8,8 +8,8 @@
 //   dH_i = g_i w,  dw = sum_i g_i h_i,  db = sum_i g_i
 // The whole step is one pass over H: one wavefront per row keeps the row in registers, forms the dot
 // product and the row's g, writes dH and adds g h to its dw accumulators; the next row is already in
-// flight.  Per-wavefront partial sums are reduced by small kernels in a fixed order, so results do not
-// depend on scheduling.
+// flight.  A workgroup's partial sums meet in LDS, the workgroups' in one small kernel, both in a fixed order, so
+// results do not depend on scheduling.
 #include <type_traits>
 
 #include <algorithm>
@@ -24,6 +24,7 @@ constexpr int kVWaves = kVT / kWave;
 constexpr int kMaxKV = 16;               // 16-byte column vectors per lane: d <= 64 * 16 * (8 bf16 | 4 float)
 constexpr int kMaxGrid = 1024;           // workgroups of the row kernel at most (the launch takes no more than are resident at once)
 constexpr int kVStat = 4;                // (sum L, clipped rows, sum V, rows)
+__host__ __device__ constexpr int part_pitch(int d) { return (d + 1 + 15) / 16 * 16; }   // floats of a partial row: dw, then db
 
 __device__ __forceinline__ uint16_t f2bf(float x) { return __builtin_bit_cast(uint16_t, static_cast<__bf16>(x)); }
 
@@ -66,6 +67,37 @@ __global__ void k_zero_u32(uint32_t* __restrict__ p, int64_t n) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
   for (; i < n; i += stride) p[i] = 0u;
 }
+// Opens the update of a selection, in one launch: value_new[n] (may be NULL) and n16 16-byte words of `big` are cleared.
+__global__ void __launch_bounds__(256)
+k_value_open(uint32_t* __restrict__ value_new, int64_t n, uint4* __restrict__ big, int64_t n16) {
+  const int64_t i0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x, stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+  for (int64_t i = i0; i < n16; i += stride) big[i] = make_uint4(0u, 0u, 0u, 0u);
+  if (value_new)
+    for (int64_t i = i0; i < n; i += stride) value_new[i] = 0u;
+}
+// Large selections: dH is cleared only where the row kernel does not write it.  A byte per row says which rows are selected
+// (in the memory of the partial sums, which come later); clearing all of dH first wrote the selected rows twice (39 224 of
+// 49 030 rows of 2048: 26.6 us, mark and clear together 13).
+__global__ void __launch_bounds__(256)
+k_value_mark(const int32_t* __restrict__ rowsel, int64_t n_sel, int64_t n_rows, uint8_t* __restrict__ map) {
+  const int64_t n = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (n >= n_sel) return;
+  const int64_t row = rowsel[n];
+  if (row >= 0 && row < n_rows) map[row] = 1;
+}
+constexpr int kClearRows = 64;             // rows of one workgroup: one ballot of a wavefront
+__global__ void __launch_bounds__(256)
+k_value_clear_rest(const uint8_t* __restrict__ map, int64_t n_rows, int row16, uint4* __restrict__ dH) {
+  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kClearRows;
+  const int64_t mine = r0 + (threadIdx.x & (kWave - 1));
+  // every wavefront looks at the same rows and takes its share of each unselected one
+  for (unsigned long long rest = __ballot(mine < n_rows && map[mine] == 0); rest; rest &= rest - 1) {
+    uint4* p = dH + (r0 + __ffsll(static_cast<long long>(rest)) - 1) * row16;
+    for (int i = threadIdx.x; i < row16; i += 256) p[i] = make_uint4(0u, 0u, 0u, 0u);
+  }
+}
+// Below this many bytes of selected rows the two launches more cost as much as they save.
+constexpr int64_t kMarkBytes = int64_t{48} << 20;
 
 // Forward only: one wavefront per selected row.
 template <typename T>
@@ -99,6 +131,9 @@ k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d
              const int32_t* __restrict__ tok_role, int n_roles, float clip_eps, float* __restrict__ value_new,
              T* __restrict__ dH, int accumulate_dH, float* __restrict__ part_dw, double* __restrict__ blk_stats) {
   __shared__ double s_acc[(1 + UMAS_MAX_ROLES) * kVStat];
+  __shared__ float s_g[kVWaves];
+  extern __shared__ __attribute__((aligned(16))) char s_raw[];
+  AccT<T>* const s_dw = reinterpret_cast<AccT<T>*>(s_raw);       // [d]
   constexpr int N = Vec<T>::N;
   const int nvec = d / N;
   const int nacc = (1 + n_roles) * kVStat;
@@ -189,72 +224,78 @@ k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d
       }
     }
   }
-  // every wavefront leaves its own partial row: [blocks * waves][d + 1]
-  float* pd = part_dw + (static_cast<size_t>(blockIdx.x) * kVWaves + wave) * (d + 1);
+  // the wavefronts' sums meet in LDS one after the other; the workgroup leaves one partial row: [blocks][part_pitch(d)].
+  // (Four partial rows a workgroup, reduced in two launches, and the statistics of all roles in one workgroup took
+  // 36 us after the rows; now 7.)
+  for (int k = 0; k < kVWaves; ++k) {
+    if (k == wave) {
 #pragma unroll
-  for (int k = 0; k < KV; ++k) {
-    const int cv = lane + k * kWave;
-    if (cv < nvec)
+      for (int q = 0; q < KV; ++q) {
+        const int cv = lane + q * kWave;
+        if (cv < nvec)
 #pragma unroll
-      for (int i = 0; i < N; ++i) pd[cv * N + i] = static_cast<float>(acc[k][i]);
+          for (int i = 0; i < N; ++i) s_dw[cv * N + i] = k == 0 ? acc[q][i] : s_dw[cv * N + i] + acc[q][i];
+      }
+      if (lane == 0) s_g[wave] = gsum;
+    }
+    __syncthreads();
   }
-  if (lane == 0) pd[d] = gsum;
-  __syncthreads();
+  float* pd = part_dw + static_cast<size_t>(blockIdx.x) * part_pitch(d);
+  for (int j = threadIdx.x; j < d; j += kVT) pd[j] = static_cast<float>(s_dw[j]);
+  if (threadIdx.x == 0) pd[d] = (s_g[0] + s_g[1]) + (s_g[2] + s_g[3]);
   for (int i = threadIdx.x; i < nacc; i += kVT) blk_stats[static_cast<size_t>(blockIdx.x) * nacc + i] = s_acc[i];
 }
 
-// out[o][j] = sum of the rows o*group .. o*group + group - 1 of in[n_in][ld] (fixed order); the last stage adds
-// into or overwrites dw (columns < d) and db (column d).
-__global__ void __launch_bounds__(256)
-k_value_reduce(const float* __restrict__ in, int n_in, int ld, int group, float* __restrict__ out, int d, int final_stage,
-               int accumulate, float* __restrict__ dw, float* __restrict__ db) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  const int o = blockIdx.y;
-  if (j >= ld) return;
-  const int b0 = o * group, b1 = b0 + group < n_in ? b0 + group : n_in;
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-  int b = b0;
-  for (; b + 4 <= b1; b += 4) {
-    s0 += in[static_cast<size_t>(b) * ld + j];
-    s1 += in[static_cast<size_t>(b + 1) * ld + j];
-    s2 += in[static_cast<size_t>(b + 2) * ld + j];
-    s3 += in[static_cast<size_t>(b + 3) * ld + j];
+// What the workgroups of the row kernel left, added up in a fixed order.  The first col_blocks workgroups take 16 columns
+// each (64-byte pieces of the partial rows; thread = 16 * group of rows + column) and add into or overwrite dw (columns
+// < d) and db (column d); the others one statistics record each.
+constexpr int kFinCols = 16, kFinT = 1024, kFinGroups = kFinT / kFinCols;
+__global__ void __launch_bounds__(kFinT)
+k_value_finish(const float* __restrict__ part, int nblk, int d, int col_blocks, int accumulate, float* __restrict__ dw,
+               float* __restrict__ db, int n_roles, int64_t norm_rows, const double* __restrict__ blk_stats,
+               umas_value_stats* __restrict__ stats) {
+  const int tid = threadIdx.x;
+  if (static_cast<int>(blockIdx.x) < col_blocks) {
+    __shared__ float s_sum[kFinGroups][kFinCols + 1];
+    const int col = tid & (kFinCols - 1), grp = tid / kFinCols, j = blockIdx.x * kFinCols + col;
+    const size_t pitch = part_pitch(d);
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    if (j <= d)
+      for (int b = grp; b < nblk; b += 4 * kFinGroups)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (b + k * kFinGroups < nblk) s[k] += part[static_cast<size_t>(b + k * kFinGroups) * pitch + j];
+    s_sum[grp][col] = (s[0] + s[1]) + (s[2] + s[3]);
+    for (int o = kFinGroups / 2; o > 0; o >>= 1) {
+      __syncthreads();
+      if (grp < o) s_sum[grp][col] += s_sum[grp + o][col];
+    }
+    if (grp == 0 && j <= d) {
+      float* dst = j < d ? dw + j : db;
+      if (dst) *dst = accumulate ? *dst + s_sum[0][col] : s_sum[0][col];
+    }
+    return;
   }
-  for (; b < b1; ++b) s0 += in[static_cast<size_t>(b) * ld + j];
-  const float s = (s0 + s1) + (s2 + s3);
-  if (!final_stage) {
-    out[static_cast<size_t>(o) * ld + j] = s;
-  } else {
-    float* dst = j < d ? dw + j : db;
-    if (dst) *dst = accumulate ? *dst + s : s;
-  }
-}
-__global__ void __launch_bounds__(256)
-k_value_stats(int nblk, int n_roles, int64_t norm_rows, const double* __restrict__ blk_stats, umas_value_stats* __restrict__ stats) {
   __shared__ double smem[32];
-  const int nacc = (1 + n_roles) * kVStat;
-  for (int k = 0; k <= n_roles; ++k) {
-    double sum[kVStat];
-    for (int j = 0; j < kVStat; ++j) {
-      double v = 0.0;
-      for (int b = threadIdx.x; b < nblk; b += blockDim.x) v += blk_stats[static_cast<size_t>(b) * nacc + k * kVStat + j];
-      sum[j] = block_sum<double>(v, smem);
-    }
-    if (threadIdx.x == 0) {
-      const double cnt = sum[3];
-      umas_value_stats s;
-      const double den = (k == 0 && norm_rows > 0) ? static_cast<double>(norm_rows) : cnt;   // the caller's normaliser
-      s.loss = cnt > 0 ? static_cast<float>(sum[0] / den) : 0.f;
-      s.clip_frac = cnt > 0 ? static_cast<float>(sum[1] / cnt) : 0.f;
-      s.value_mean = cnt > 0 ? static_cast<float>(sum[2] / cnt) : 0.f;
-      s.reserved = 0.f;
-      s.n_scored = static_cast<int64_t>(cnt);
-      stats[k] = s;
-    }
-  }
+  const int nacc = (1 + n_roles) * kVStat, k = blockIdx.x - col_blocks;
+  double sum[kVStat];
+#pragma unroll
+  for (int j = 0; j < kVStat; ++j) sum[j] = tid < nblk ? blk_stats[static_cast<size_t>(tid) * nacc + k * kVStat + j] : 0.0;   // nblk <= kMaxGrid
+#pragma unroll
+  for (int j = 0; j < kVStat; ++j) sum[j] = block_sum<double>(sum[j], smem);
+  if (tid != 0) return;
+  const double cnt = sum[3];
+  umas_value_stats s;
+  const double den = (k == 0 && norm_rows > 0) ? static_cast<double>(norm_rows) : cnt;   // the caller's normaliser
+  s.loss = cnt > 0 ? static_cast<float>(sum[0] / den) : 0.f;
+  s.clip_frac = cnt > 0 ? static_cast<float>(sum[1] / cnt) : 0.f;
+  s.value_mean = cnt > 0 ? static_cast<float>(sum[2] / cnt) : 0.f;
+  s.reserved = 0.f;
+  s.n_scored = static_cast<int64_t>(cnt);
+  stats[k] = s;
 }
+static_assert(kMaxGrid <= kFinT, "one thread per workgroup of the row kernel in the statistics");
 
-constexpr int kReduceGroup = 64;
 unsigned value_grid(int64_t n_sel) {
   const int64_t b = (n_sel + kVWaves - 1) / kVWaves;
   return static_cast<unsigned>(b < 1 ? 1 : b > kMaxGrid ? kMaxGrid : b);
@@ -270,7 +311,8 @@ unsigned resident_value_blocks() {
   int dev = 0, n_cu = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
     n_cu = 64;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_value_rows<T, K>, kVT, 0) != hipSuccess || per_cu < 1) per_cu = 1;
+  constexpr size_t kLds = static_cast<size_t>(K) * kWave * Vec<T>::N * sizeof(AccT<T>);   // the widest rows of the instance
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_value_rows<T, K>, kVT, kLds) != hipSuccess || per_cu < 1) per_cu = 1;
   cached = static_cast<unsigned>(per_cu) * static_cast<unsigned>(n_cu);
   return cached;
 }
@@ -290,7 +332,7 @@ void launch_value_rows(int kv, unsigned grid, hipStream_t st, const void* H, con
                        const int32_t* tok_role, int n_roles, float clip_eps, float* value_new, void* dH, int acc_dH,
                        float* part_dw, double* blk_stats) {
 #define UMAS_VALUE_CASE(K)                                                                                              \
-  hipLaunchKernelGGL((k_value_rows<T, K>), dim3(grid), dim3(kVT), 0, st, static_cast<const T*>(H), static_cast<const T*>(w), \
+  hipLaunchKernelGGL((k_value_rows<T, K>), dim3(grid), dim3(kVT), d * sizeof(AccT<T>), st, static_cast<const T*>(H), static_cast<const T*>(w), \
                      bias, d, rowsel, n_sel, norm, rpb, value_old, ret, tok_role, n_roles, clip_eps, value_new,         \
                      static_cast<T*>(dH), acc_dH, part_dw, blk_stats)
   if (kv <= 1) UMAS_VALUE_CASE(1);
@@ -324,8 +366,7 @@ extern "C" size_t umas_value_workspace_bytes(int64_t n_sel, int32_t d, umas_dtyp
   (void)dtype;
   const unsigned grid = value_grid(n_sel);
   Carver c(nullptr);
-  c.take<float>(static_cast<size_t>(grid) * kVWaves * (d + 1));                                  // one partial row per wavefront
-  c.take<float>(static_cast<size_t>(cdiv(grid * kVWaves, kReduceGroup)) * (d + 1));             // first reduction stage
+  c.take<float>(static_cast<size_t>(grid) * part_pitch(d));                                      // one partial row per workgroup
   c.take<double>(static_cast<size_t>(grid) * (1 + n_roles) * kVStat);
   return c.off;
 }
@@ -380,10 +421,9 @@ extern "C" umas_status umas_value_loss_fwd_bwd(const void* H, const void* w, flo
   // at most value_grid(n_sel) workgroups (what the workspace is sized for), and no more than are resident at once
   const unsigned resident = dtype == UMAS_BF16 ? resident_value_blocks_kv<uint16_t>(kv) : resident_value_blocks_kv<float>(kv);
   const unsigned grid = std::min(value_grid(n_sel), resident);
-  const int n_part = static_cast<int>(grid) * kVWaves, n_part2 = static_cast<int>(cdiv(n_part, kReduceGroup));
+  const size_t part_bytes = static_cast<size_t>(grid) * part_pitch(d) * sizeof(float);
   Carver c(workspace);
-  float* part_dw = c.take<float>(static_cast<size_t>(n_part) * (d + 1));
-  float* part2 = c.take<float>(static_cast<size_t>(n_part2) * (d + 1));
+  float* part_dw = c.take<float>(part_bytes / sizeof(float));
   double* blk_stats = c.take<double>(static_cast<size_t>(grid) * (1 + n_roles) * kVStat);
 
   auto zero = [&](void* p, size_t bytes) -> hipError_t {
@@ -396,8 +436,20 @@ extern "C" umas_status umas_value_loss_fwd_bwd(const void* H, const void* w, flo
     return e;
   };
   if (rowsel && n_rows > 0) {
-    if (value_new) UMAS_HIP(zero(value_new, n_rows * sizeof(float)));
-    if (!accumulate_dH) UMAS_HIP(zero(dH, static_cast<size_t>(n_rows) * d * esz));
+    const size_t row_bytes = static_cast<size_t>(d) * esz;           // a multiple of 16
+    const bool mark = !accumulate_dH && n_sel * static_cast<int64_t>(row_bytes) >= kMarkBytes && align_up(n_rows, 16) <= part_bytes;
+    const int64_t n16 = accumulate_dH ? 0 : static_cast<int64_t>(mark ? align_up(n_rows, 16) / 16 : n_rows * row_bytes / 16);
+    uint8_t* map = reinterpret_cast<uint8_t*>(part_dw);
+    hipLaunchKernelGGL(k_value_open, dim3(std::min(std::max(cdiv(n16, 1024), cdiv(n_rows, 1024)), 8192u)), dim3(256), 0, st,
+                       reinterpret_cast<uint32_t*>(value_new), n_rows, static_cast<uint4*>(mark ? static_cast<void*>(map) : dH), n16);
+    UMAS_LAUNCHED("k_value_open");
+    if (mark) {
+      hipLaunchKernelGGL(k_value_mark, dim3(cdiv(n_sel, 256)), dim3(256), 0, st, rowsel, n_sel, n_rows, map);
+      UMAS_LAUNCHED("k_value_mark");
+      hipLaunchKernelGGL(k_value_clear_rest, dim3(cdiv(n_rows, kClearRows)), dim3(256), 0, st, map, n_rows, static_cast<int>(row_bytes / 16),
+                         static_cast<uint4*>(dH));
+      UMAS_LAUNCHED("k_value_clear_rest");
+    }
   }
   if (n_sel > 0) {
     const int64_t rpb = (n_sel + grid - 1) / grid;                 // rows per workgroup; every wavefront writes its partial row
@@ -410,16 +462,12 @@ extern "C" umas_status umas_value_loss_fwd_bwd(const void* H, const void* w, flo
     UMAS_LAUNCHED("k_value_rows");
   } else {
     // an empty selection still defines the outputs: zero partials give zero statistics and gradients
-    UMAS_HIP(zero(part_dw, static_cast<size_t>(n_part) * (d + 1) * sizeof(float)));
+    UMAS_HIP(zero(part_dw, part_bytes));
     UMAS_HIP(zero(blk_stats, static_cast<size_t>(grid) * (1 + n_roles) * kVStat * sizeof(double)));
   }
-  hipLaunchKernelGGL(k_value_reduce, dim3(cdiv(d + 1, 256), n_part2), dim3(256), 0, st, part_dw, n_part, d + 1, kReduceGroup,
-                     part2, d, 0, 0, static_cast<float*>(nullptr), static_cast<float*>(nullptr));
-  UMAS_LAUNCHED("k_value_reduce");
-  hipLaunchKernelGGL(k_value_reduce, dim3(cdiv(d + 1, 256), 1), dim3(256), 0, st, part2, n_part2, d + 1, n_part2,
-                     static_cast<float*>(nullptr), d, 1, accumulate_dw, dw, db);
-  UMAS_LAUNCHED("k_value_reduce");
-  hipLaunchKernelGGL(k_value_stats, dim3(1), dim3(256), 0, st, static_cast<int>(grid), n_roles, norm_rows, blk_stats, stats);
-  UMAS_LAUNCHED("k_value_stats");
+  const int col_blocks = static_cast<int>(cdiv(d + 1, kFinCols));
+  hipLaunchKernelGGL(k_value_finish, dim3(col_blocks + 1 + n_roles), dim3(kFinT), 0, st, part_dw, static_cast<int>(grid), d, col_blocks,
+                     accumulate_dw, dw, db, n_roles, norm_rows, blk_stats, stats);
+  UMAS_LAUNCHED("k_value_finish");
   return UMAS_OK;
 }

@@ -130,3 +130,46 @@ def test_one_hot_rows_and_statistics_per_role(n, n_tokens):
     bound_h, bound_w = P.bf16_gradient_bounds(H, W, P.oracle_dz(H, W, ids, lse_o, g_o, np.arange(n)), dH_o, dW_o, np.arange(n), ids, lse_o, g_o)
     P.close_bounded(dH.float().cpu().numpy(), dH_o, bound_h, 1e-2, "dH")
     P.close_bounded(dW.cpu().numpy(), dW_o, bound_w, 1e-2, "dW")
+
+
+# the critic's update on both sides of the size from which dH is cleared only where no selected row lies (48 MiB of selected
+# rows), with selections that are nearly everything, half and shuffled; more rows than the partial sums have bytes; every
+# wavefront of the last workgroup busy and one; the widest rows
+@pytest.mark.parametrize("n,n_sel,d,dt", [(1, 1, 8, "bf16"), (70, 5, 8192, "bf16"), (6200, 3071, 8192, "bf16"), (3073, 3072, 8192, "bf16"),
+                                          (6209, 3073, 4096, "f32"), (3200000, 3145729, 8, "bf16"), (130001, 98305, 260, "f32"),
+                                          (500, 0, 64, "bf16")])
+def test_critic_update_clears_the_rows_that_are_not_selected(n, n_sel, d, dt):
+    gen = torch.Generator(device="cuda").manual_seed(n + d)
+    dtype = torch.bfloat16 if dt == "bf16" else torch.float32
+    H = torch.randn(n, d, device="cuda", generator=gen).to(dtype)
+    w = (torch.randn(d, device="cuda", generator=gen) / np.sqrt(d)).to(dtype)
+    sel = torch.randperm(n, device="cuda", generator=gen)[:n_sel].to(torch.int32)
+    R = torch.randn(n, device="cuda", generator=gen)
+    dH = torch.full((n, d), 7.0, device="cuda", dtype=dtype)
+    value_new = torch.full((n,), 7.0, device="cuda")
+    stats, V, dH, dw, db = umas.umas_value_loss_fwd_bwd(H, w, 0.25, sel, torch.zeros(n, device="cuda"), R, None, 0, 1e9,
+                                                        dH=dH, value_new=value_new)
+    sl = sel.long()
+    rest = torch.ones(n, dtype=torch.bool, device="cuda")
+    rest[sl] = False
+    assert not dH[rest].any() and not V[rest].any()
+    s = umas.read_value_stats(stats)
+    assert int(s["n_scored"][0]) == n_sel
+    if n_sel == 0:
+        assert not dw.any() and not db.any()
+        return
+    Hd, wd = H[sl].double(), w.double()
+    V_o = Hd @ wd + 0.25
+    err_V = (d + 8) * 2.0 ** -24 * (Hd.abs() @ wd.abs() + 1)          # a float32 dot product of exact products
+    assert ((V[sl].double() - V_o).abs() <= err_V).all()
+    g = (V_o - R[sl].double()) / n_sel                                # the clip range is wide: every row keeps its gradient
+    err_g = (err_V + 2.0 ** -22 * (V_o - R[sl].double()).abs()) / n_sel
+    rnd = 2.0 ** -8 if dt == "bf16" else 2.0 ** -23
+    want = g[:, None] * wd[None, :]
+    assert ((dH[sl].double() - want).abs() <= rnd * want.abs() + 2 * err_g[:, None] * wd.abs()[None, :] + 1e-38).all()
+    # sums of float32 terms: a wavefront's rows, four wavefronts, then the workgroups; 2^-24 of the magnitudes per addition
+    adds = n_sel / min((n_sel + 3) // 4, 256) + 64
+    lim = (err_g[:, None] * Hd.abs()).sum(0) + adds * 2.0 ** -24 * (g.abs()[:, None] * Hd.abs()).sum(0)
+    assert ((dw.double() - (g[:, None] * Hd).sum(0)).abs() <= lim).all()
+    assert abs(float(db) - float(g.sum())) <= float(err_g.sum() + adds * 2.0 ** -24 * g.abs().sum())
+    assert abs(float(s["loss"][0]) - float(0.5 * (V_o - R[sl].double()).square().mean())) <= 1e-5 * (1 + float(V_o.square().mean()))
