@@ -1,0 +1,426 @@
+// The float32 path of scoring and update: float32 operands, every product and sum in float64 (a float32 dot product of d
+// terms would cost up to d 2^-24 of the sum of its terms' magnitudes), results rounded to float32 once.
+//
+// All four products (logits for the scoring pass, logits for dz, dH = dz W, dW = dz^T H) are contractions and run on the
+// float64 matrix cores: v_mfma_f64_16x16x4 sustains 74 TFLOP/s here and asks for one converted float per lane and operand
+// every 64 cycles, so a wavefront's 32 x 32 tile (2 x 2 blocks) is fed straight from L1 / L2 into registers, 16 k at a time, the
+// next 16 in flight; no LDS, no barrier in the loop.  The k of an instruction may be any four as long as both operands
+// agree: lane group l / 16 takes k = 4 (l / 16) .. + 3 of the 16 over four instructions, so that a K-contiguous operand is
+// read 16 bytes a lane.  With one thread per output element and scalar float64 chains dz, dH and dW took 17, 52 and 189 us at
+// 768 rows of 64 against 512, now 14, 12 and 17; a step of 847 rows of 512 against 8192 took 10.1 ms, now 0.88.
+//
+// Operand layout of a block (lane l): index l % 16, k by lane group l / 16.  Accumulator r of lane l: row 4 r + l / 16 (A
+// side), column l % 16 (B side); checked on the device.
+#pragma once
+
+#include "umas_common.h"
+
+namespace umas {
+namespace f32 {
+
+typedef double double4v __attribute__((ext_vector_type(4)));
+constexpr int kK = 16;                       // k of one round
+constexpr int kTile = 32;                    // a wavefront's tile, both ways
+
+// Operand stored K-contiguous: row i of the tile is a run of K floats.
+struct Rows {
+  const float* p[2];                         // the lane's row of each block
+  bool vec;                                  // every row starts at a multiple of 16 bytes and K is a multiple of 4
+  __device__ __forceinline__ void ahead(int, int) {}
+  __device__ __forceinline__ void load(int k0, int K, float (&x)[2][4]) const {
+    const int k = k0 + 4 * ((threadIdx.x & 63) >> 4);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if (vec) {
+        const float4 v = k < K ? *reinterpret_cast<const float4*>(p[i] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+        x[i][0] = v.x; x[i][1] = v.y; x[i][2] = v.z; x[i][3] = v.w;
+      } else {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) x[i][s] = k + s < K ? p[i][k + s] : 0.f;
+      }
+    }
+  }
+};
+// Operand stored K-major: k-row k (row map[k] of the matrix, where there is a map) holds the tile's entries next to each other.
+struct Cols {
+  const float* p[2];                         // the lane's entry of each block in k-row 0
+  int64_t ld;
+  const int32_t* map;
+  int32_t row[4];                            // k-rows of the next round
+  __device__ __forceinline__ void ahead(int k0, int K) {
+    const int k = k0 + 4 * ((threadIdx.x & 63) >> 4);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) row[s] = map ? map[k + s < K ? k + s : K - 1] : k + s;
+  }
+  __device__ __forceinline__ void load(int k0, int K, float (&x)[2][4]) const {
+    const int k = k0 + 4 * ((threadIdx.x & 63) >> 4);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) x[i][s] = k + s < K ? p[i][row[s] * ld] : 0.f;
+  }
+};
+
+// acc += A[., k] B[., k] over k in [k0, k1), K of them altogether; k0 a multiple of 16
+template <class OA, class OB>
+__device__ __forceinline__ void product(OA& a, OB& b, int k0, int k1, int K, double4v (&acc)[2][2]) {
+  if (k0 >= k1) return;
+  float xa[2][4], xb[2][4];
+  a.ahead(k0, K);
+  b.ahead(k0, K);
+  a.load(k0, K, xa);
+  b.load(k0, K, xb);
+  a.ahead(k0 + kK, K);
+  b.ahead(k0 + kK, K);
+  for (int k = k0; k < k1; k += kK) {
+    float na[2][4], nb[2][4];
+    a.load(k + kK, K, na);                   // past the end: zeros, no access
+    b.load(k + kK, K, nb);
+    a.ahead(k + 2 * kK, K);
+    b.ahead(k + 2 * kK, K);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const double a0 = xa[0][s], a1 = xa[1][s], b0 = xb[0][s], b1 = xb[1][s];
+      acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
+      acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
+      acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
+      acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) { xa[i][s] = na[i][s]; xb[i][s] = nb[i][s]; }
+  }
+}
+__device__ __forceinline__ void zero(double4v (&acc)[2][2]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = double4v{0.0, 0.0, 0.0, 0.0};
+}
+__device__ __forceinline__ int blk_index(int i) { return i * 16 + (threadIdx.x & 15); }                       // operand entry / column
+__device__ __forceinline__ int blk_row(int i, int r) { return i * 16 + 4 * r + ((threadIdx.x & 63) >> 4); }   // accumulator row
+
+// ------------------------------------------------------------------ scoring
+// Softmax statistics of part of a row's logits: maximum, sum exp(z - m), sum exp(z - m) z, the second without the taken
+// token, and the taken token's logit (0 elsewhere).
+struct Stat {
+  double m, s, t, rest, zy;
+};
+__device__ __forceinline__ Stat empty_stat() { return Stat{0.0, 0.0, 0.0, 0.0, 0.0}; }
+__device__ __forceinline__ Stat merge(const Stat& x, const Stat& y) {
+  if (x.s == 0.0) return Stat{y.m, y.s, y.t, y.rest, x.zy + y.zy};
+  if (y.s == 0.0) return Stat{x.m, x.s, x.t, x.rest, x.zy + y.zy};
+  const double M = fmax(x.m, y.m), ex = exp(x.m - M), ey = exp(y.m - M);
+  return Stat{M, x.s * ex + y.s * ey, x.t * ex + y.t * ey, x.rest * ex + y.rest * ey, x.zy + y.zy};
+}
+__device__ __forceinline__ Stat shfl_xor(const Stat& x, int o) {
+  return Stat{__shfl_xor(x.m, o, kWave), __shfl_xor(x.s, o, kWave), __shfl_xor(x.t, o, kWave), __shfl_xor(x.rest, o, kWave),
+              __shfl_xor(x.zy, o, kWave)};
+}
+struct ScoreOut {
+  double* rest_c;                            // compact arrays (NULL: none): sum of the probabilities of the tokens not taken
+  float *logp_c, *lse_c, *ent_c;
+  float *logp, *lse, *entropy;               // scattered (NULL: none)
+};
+__device__ __forceinline__ void write_scores(const Stat& a, int64_t n, int64_t row, int y, int V, const ScoreOut& o) {
+  const bool ok = y >= 0 && y < V;
+  const double l = a.m + log(a.s);
+  const float lf = static_cast<float>(l);
+  const float lp = ok ? static_cast<float>(a.zy - l) : 0.f;
+  const float en = ok ? static_cast<float>(l - a.t / a.s) : 0.f;
+  if (o.logp_c) {
+    o.logp_c[n] = lp; o.lse_c[n] = lf; o.ent_c[n] = en;
+    o.rest_c[n] = a.rest * exp(a.m - static_cast<double>(lf));   // relative to the rounded logsumexp, as dz is
+  }
+  if (o.logp) o.logp[row] = lp;
+  if (o.lse) o.lse[row] = lf;
+  if (o.entropy) o.entropy[row] = en;
+}
+
+// A workgroup takes 32 rows and every gridDim.y-th block of 128 vocabulary entries, 32 to a wavefront; a lane holds 8
+// entries of each of two rows.  With one workgroup per row block the scores are final, else the statistics go to
+// part[gridDim.y][n_sel].
+constexpr int kWaves = 4, kVocBlock = kWaves * kTile;
+__global__ void __launch_bounds__(kWaves* kWave)
+k_score_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel, int64_t n_sel,
+            const int32_t* __restrict__ ids, Stat* __restrict__ part, ScoreOut out) {
+  __shared__ Stat s_stat[kWaves][kTile];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t n0 = static_cast<int64_t>(blockIdx.x) * kTile;
+  Rows h;
+  h.vec = d % 4 == 0;
+  int y[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int64_t n = min(n0 + blk_index(j), n_sel - 1), row = rowsel ? rowsel[n] : n;
+    h.p[j] = H + row * d;
+    y[j] = ids[row];
+  }
+  Stat st[2] = {empty_stat(), empty_stat()};
+  for (int64_t vb = static_cast<int64_t>(blockIdx.y) * kVocBlock; vb < V; vb += static_cast<int64_t>(gridDim.y) * kVocBlock) {
+    const int v0 = static_cast<int>(vb) + wave * kTile;
+    if (v0 >= V) continue;
+    Rows w;
+    w.vec = h.vec;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) w.p[i] = W + static_cast<int64_t>(min(v0 + blk_index(i), V - 1)) * d;
+    double4v acc[2][2];
+    zero(acc);
+    product(w, h, 0, d, d, acc);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      double m = -1e300;                     // below every finite logit that matters; infinities and NaN pass through the sums
+      int have = 0;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (v0 + blk_row(i, r) < V) { m = fmax(m, acc[i][j][r]); have = 1; }
+      if (!have) continue;
+      Stat q{m, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int v = v0 + blk_row(i, r);
+          if (v >= V) continue;
+          const double z = acc[i][j][r], e = exp(z - m);
+          q.s += e;
+          q.t = fma(e, z, q.t);
+          if (v == y[j]) q.zy = z; else q.rest += e;
+        }
+      st[j] = merge(st[j], q);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    st[j] = merge(st[j], shfl_xor(st[j], 16));
+    st[j] = merge(st[j], shfl_xor(st[j], 32));
+    if (lane < 16) s_stat[wave][blk_index(j)] = st[j];
+  }
+  __syncthreads();
+  const int64_t n = n0 + threadIdx.x;
+  if (threadIdx.x >= kTile || n >= n_sel) return;
+  Stat a = s_stat[0][threadIdx.x];
+  for (int k = 1; k < kWaves; ++k) a = merge(a, s_stat[k][threadIdx.x]);
+  if (gridDim.y > 1) {
+    part[static_cast<int64_t>(blockIdx.y) * n_sel + n] = a;
+    return;
+  }
+  const int64_t row = rowsel ? rowsel[n] : n;
+  write_scores(a, n, row, ids[row], V, out);
+}
+// One workgroup per row, every thread walks the vocabulary entries tid, tid + 256, ...: one launch and no room needed.
+__global__ void __launch_bounds__(256)
+k_score_f32_row(const float* __restrict__ W, const float* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel,
+                const int32_t* __restrict__ ids, ScoreOut out) {
+  extern __shared__ float s_h[];             // [d]
+  __shared__ Stat s_stat[256 / kWave];
+  const int64_t n = blockIdx.x, row = rowsel ? rowsel[n] : n;
+  for (int k = threadIdx.x; k < d; k += 256) s_h[k] = H[row * d + k];
+  __syncthreads();
+  const int y = ids[row];
+  Stat a = empty_stat();
+  for (int v = threadIdx.x; v < V; v += 256) {
+    const float* w = W + static_cast<int64_t>(v) * d;
+    double z = 0.0;
+    for (int k = 0; k < d; ++k) z = fma(static_cast<double>(s_h[k]), static_cast<double>(w[k]), z);
+    a = merge(a, Stat{z, 1.0, z, v == y ? 0.0 : 1.0, v == y ? z : 0.0});
+  }
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) a = merge(a, shfl_xor(a, o));
+  if ((threadIdx.x & 63) == 0) s_stat[threadIdx.x >> 6] = a;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int k = 1; k < 256 / kWave; ++k) a = merge(a, s_stat[k]);
+  write_scores(a, n, row, y, V, out);
+}
+// One wavefront per row.
+__global__ void __launch_bounds__(256)
+k_score_f32_merge(const Stat* __restrict__ part, int splits, int V, const int32_t* __restrict__ rowsel, int64_t n_sel,
+                  const int32_t* __restrict__ ids, ScoreOut out) {
+  const int lane = threadIdx.x & 63;
+  const int64_t n = static_cast<int64_t>(blockIdx.x) * (256 / kWave) + threadIdx.x / kWave;
+  if (n >= n_sel) return;
+  Stat a = empty_stat();
+  for (int k = lane; k < splits; k += kWave) a = merge(a, part[static_cast<int64_t>(k) * n_sel + n]);
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) a = merge(a, shfl_xor(a, o));
+  if (lane != 0) return;
+  const int64_t row = rowsel ? rowsel[n] : n;
+  write_scores(a, n, row, ids[row], V, out);
+}
+
+// ------------------------------------------------------------------ backward
+// dz[n, v] = g (onehot - exp(z - lse)) + entropy term for a chunk of selected rows, z recomputed with the sums of the
+// forward pass.  The taken token's entry g (1 - p_y): for a confident token (p_y > 1/2) 1 - p_y cancels down to the error
+// of p_y, and the sum of the other probabilities, which carries only their relative error, is taken in its place.
+// Rows on the A side, so that sixteen lanes store consecutive vocabulary entries.
+__global__ void __launch_bounds__(kWaves* kWave)
+k_dz_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel, int64_t c0,
+         int64_t rows, const int32_t* __restrict__ ids, const float* __restrict__ lse_c, const double* __restrict__ rest_c,
+         const float* __restrict__ g_c, const float* __restrict__ ent_c, const float* __restrict__ kz_c, float* __restrict__ dz) {
+  const int wave = threadIdx.x >> 6;
+  const int64_t n0 = static_cast<int64_t>(blockIdx.y) * kTile, vb = static_cast<int64_t>(blockIdx.x) * kVocBlock + wave * kTile;
+  if (vb >= V) return;
+  const int v0 = static_cast<int>(vb);
+  Rows h, w;
+  h.vec = w.vec = d % 4 == 0;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int64_t n = c0 + min(n0 + blk_index(i), rows - 1);
+    h.p[i] = H + (rowsel ? rowsel[n] : n) * static_cast<int64_t>(d);
+    w.p[i] = W + static_cast<int64_t>(min(v0 + blk_index(i), V - 1)) * d;
+  }
+  double4v acc[2][2];
+  zero(acc);
+  product(h, w, 0, d, d, acc);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t m = n0 + blk_row(i, r);
+      if (m >= rows) continue;
+      const int64_t n = c0 + m;
+      const int y = ids[rowsel ? rowsel[n] : n];
+      const double l = lse_c[n], g = g_c[n], en = ent_c[n], k_ent = kz_c[n];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int v = v0 + blk_index(j);
+        if (v >= V) continue;
+        const double z = acc[i][j][r], p = exp(z - l);
+        const double e = k_ent != 0.0 ? k_ent * p * ((z - l) + en) : 0.0;     // entropy bonus: k p (log p + entropy)
+        const double dense = v == y ? g * (p > 0.5 ? rest_c[n] : 1.0 - p) : -g * p;
+        dz[m * V + v] = static_cast<float>(dense + e);
+      }
+    }
+}
+
+// The two gradient products.  A workgroup of eight wavefronts takes WM x WN tiles of 32 x 32 and 8 / (WM WN) parts of K,
+// whose sums meet in LDS in a fixed order.  <1, 1> spreads small products over the chip (dW of 512 x 64: 32 workgroups);
+// from 256 tiles of 64 x 64 on <2, 2> reads half as much from L2.
+constexpr int kGradWaves = 8, kGradT = kGradWaves * kWave;
+template <int WM, int WN, class OA, class OB, class F>
+__device__ __forceinline__ void gradient_tile(OA& a, OB& b, int K, F store) {
+  constexpr int WK = kGradWaves / (WM * WN);
+  __shared__ double s_acc[kGradWaves / 2][16][kWave];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, part = wave / (WM * WN);
+  const int per = ((K + kK - 1) / kK + WK - 1) / WK * kK;            // k of one part
+  double4v acc[2][2];
+  zero(acc);
+  product(a, b, min(part * per, K), min((part + 1) * per, K), K, acc);
+#pragma unroll
+  for (int o = WK / 2; o > 0; o >>= 1) {                             // parts o .. 2 o - 1 hand their sums to parts 0 .. o - 1
+    const int slot = wave % (o * WM * WN);
+    if (part >= o && part < 2 * o)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) s_acc[slot][q][lane] = acc[q >> 3][(q >> 2) & 1][q & 3];
+    __syncthreads();
+    if (part < o)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[q >> 3][(q >> 2) & 1][q & 3] += s_acc[slot][q][lane];
+    __syncthreads();
+  }
+  if (part != 0) return;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) store(blk_row(i, r), blk_index(j), acc[i][j][r]);
+}
+// dH[row(n), j] = sum_v dz[n, v] W[v, j]
+template <int WM, int WN>
+__global__ void __launch_bounds__(kGradT)
+k_dh_f32(const float* __restrict__ dz, const float* __restrict__ W, int d, int V, const int32_t* __restrict__ rowsel, int64_t c0,
+         int64_t rows, float* __restrict__ dH) {
+  const int wave = threadIdx.x >> 6;
+  const int64_t n0 = (static_cast<int64_t>(blockIdx.x) * WM + wave / WN % WM) * kTile;
+  const int j0 = (static_cast<int>(blockIdx.y) * WN + wave % WN) * kTile;
+  Rows a;
+  a.vec = V % 4 == 0;
+  Cols b;
+  b.ld = d;
+  b.map = nullptr;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    a.p[i] = dz + min(n0 + blk_index(i), rows - 1) * V;
+    b.p[i] = W + min(j0 + blk_index(i), d - 1);
+  }
+  gradient_tile<WM, WN>(a, b, V, [&](int r, int c, double x) {
+    const int64_t m = n0 + r;
+    const int j = j0 + c;
+    if (m < rows && j < d) dH[(rowsel ? rowsel[c0 + m] : c0 + m) * d + j] = static_cast<float>(x);
+  });
+}
+// dW[v, j] (+)= sum_n dz[n, v] H[row(n), j]
+template <int WM, int WN>
+__global__ void __launch_bounds__(kGradT)
+k_dw_f32(const float* __restrict__ dz, const float* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel, int64_t c0,
+         int64_t rows, int accumulate, float* __restrict__ dW) {
+  const int wave = threadIdx.x >> 6;
+  const int64_t v0 = (static_cast<int64_t>(blockIdx.x) * WM + wave / WN % WM) * kTile;
+  const int j0 = (static_cast<int>(blockIdx.y) * WN + wave % WN) * kTile;
+  Cols a, b;
+  a.ld = V;
+  a.map = nullptr;
+  b.ld = d;
+  b.map = rowsel ? rowsel + c0 : nullptr;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    a.p[i] = dz + min(v0 + blk_index(i), static_cast<int64_t>(V) - 1);
+    b.p[i] = (rowsel ? H : H + c0 * d) + min(j0 + blk_index(i), d - 1);
+  }
+  gradient_tile<WM, WN>(a, b, static_cast<int>(rows), [&](int r, int c, double x) {
+    const int64_t v = v0 + r;
+    const int j = j0 + c;
+    if (v >= V || j >= d) return;
+    float* dst = dW + v * d + j;
+    *dst = accumulate ? static_cast<float>(static_cast<double>(*dst) + x) : static_cast<float>(x);
+  });
+}
+
+// ------------------------------------------------------------------ launches
+// Workgroups per block of 32 rows: enough of them to fill the chip, as far as the vocabulary and the room for their
+// statistics go.
+inline int score_splits(int64_t n_sel, int V, size_t room) {
+  const int64_t row_blks = (n_sel + kTile - 1) / kTile;
+  int64_t k = (1024 + row_blks - 1) / row_blks;
+  k = k < cdiv(V, kVocBlock) ? k : cdiv(V, kVocBlock);
+  const int64_t fit = static_cast<int64_t>(room / (static_cast<size_t>(n_sel) * sizeof(Stat)));
+  return static_cast<int>(k < fit ? k : fit < 1 ? 1 : fit);
+}
+inline size_t score_room(int64_t n_sel, int V) {
+  if (n_sel <= 0) return 0;
+  const int k = score_splits(n_sel, V, SIZE_MAX);
+  return k > 1 ? static_cast<size_t>(k) * n_sel * sizeof(Stat) : 0;
+}
+// The row kernel where a thread of its has little to do (about 30 ns a product at 512 x 8192; the tiles cost a launch more):
+// 24 rows against 512 of width 64 / 128 take 10 / 13 us, in tiles 20 / 22, 768 rows of 64 19 and 18, 1 row of 128 against 3000
+// 47 and 20.  And where there is no room for statistics, as long as its workgroups outnumber the row blocks by more than
+// the tiles are faster: 16 rows of 512 against 8192 0.55 ms (in tiles by a single workgroup 2), 20 000 rows of 64 against
+// 512 320 us (80).
+inline umas_status score(const float* W, const float* H, int d, int V, const int32_t* rowsel, int64_t n_sel, const int32_t* ids, void* room,
+                         size_t room_bytes, const ScoreOut& out, hipStream_t st) {
+  const int splits = score_splits(n_sel, V, room_bytes);
+  const int64_t per_thread = static_cast<int64_t>(cdiv(V, 256)) * d;
+  if ((n_sel <= 1024 && per_thread <= 128) || (n_sel <= 128 && per_thread <= 256) || (splits == 1 && V > kVocBlock && n_sel < 1024)) {
+    hipLaunchKernelGGL(k_score_f32_row, dim3(static_cast<unsigned>(n_sel)), dim3(256), d * sizeof(float), st, W, H, d, V, rowsel, ids, out);
+    UMAS_LAUNCHED("k_score_f32_row");
+    return UMAS_OK;
+  }
+  hipLaunchKernelGGL(k_score_f32, dim3(cdiv(n_sel, kTile), splits), dim3(kWaves * kWave), 0, st, W, H, d, V, rowsel, n_sel, ids,
+                     static_cast<Stat*>(room), out);
+  UMAS_LAUNCHED("k_score_f32");
+  if (splits > 1) {
+    hipLaunchKernelGGL(k_score_f32_merge, dim3(cdiv(n_sel, 256 / kWave)), dim3(256), 0, st, static_cast<const Stat*>(room), splits, V,
+                       rowsel, n_sel, ids, out);
+    UMAS_LAUNCHED("k_score_f32_merge");
+  }
+  return UMAS_OK;
+}
+inline bool large_product(int64_t m, int64_t n) { return cdiv(m, 2 * kTile) * static_cast<int64_t>(cdiv(n, 2 * kTile)) >= 256; }
+
+}  // namespace f32
+}  // namespace umas

@@ -14,13 +14,14 @@
 // the taken token's logit, and the row factor -g exp(z_y - lse) is applied where dH is written and folded
 // into the copy of H that dW reads; the logits are computed once.  With an entropy bonus (and for blocks
 // of rows whose logits spread too far for E) dz is recomputed tile by tile from H, W and lse instead.
-// The float32 path is a plain, unblocked implementation for small shapes.
+// The float32 path, for small shapes, carries its sums in float64 (umas_f32.h).
 #include <math.h>
 
 #include <algorithm>
 #include <mutex>
 
 #include "umas_common.h"
+#include "umas_f32.h"
 #include "umas_mfma.h"
 
 namespace umas {
@@ -513,68 +514,6 @@ k_score_finalize(const float4* __restrict__ partial, int tiles_m, int64_t n_pad,
   if (logp) logp[row] = lp;
   if (lse) lse[row] = l;
   if (entropy) entropy[row] = en;
-}
-
-// ------------------------------------------------------------------ float32: plain scoring
-// One block per selected row; every thread walks vocabulary entries v = tid, tid + T, ...  The float32 path is the
-// plain one for small shapes: its speed does not matter, so dot products and softmax statistics are carried in
-// float64 and only the results are rounded to float32 (a float32 dot product of d terms would cost up to
-// d 2^-24 of the sum of its terms' magnitudes).
-struct PartD {
-  double m, s, t;
-};
-__device__ __forceinline__ PartD partd_merge(PartD x, PartD y) {
-  if (x.s == 0.0) return y;
-  if (y.s == 0.0) return x;
-  const double M = fmax(x.m, y.m);
-  const double ex = exp(x.m - M), ey = exp(y.m - M);
-  return PartD{M, x.s * ex + y.s * ey, x.t * ex + y.t * ey};
-}
-__device__ __forceinline__ double dot_f64(const float* __restrict__ a, const float* __restrict__ b, int d) {
-  double z = 0.0;
-  for (int k = 0; k < d; ++k) z = fma(static_cast<double>(a[k]), static_cast<double>(b[k]), z);
-  return z;
-}
-__global__ void __launch_bounds__(256)
-k_score_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int V,
-            const int32_t* __restrict__ rowsel, const int32_t* __restrict__ ids,
-            float* __restrict__ logp_c, float* __restrict__ lse_c, float* __restrict__ ent_c,
-            float* __restrict__ logp, float* __restrict__ lse, float* __restrict__ entropy) {
-  extern __shared__ float s_h[];   // [d]
-  __shared__ double s_m[4], s_s[4], s_t[4], s_zy;
-  const int64_t n = blockIdx.x;
-  const int64_t row = rowsel ? rowsel[n] : n;
-  for (int k = threadIdx.x; k < d; k += blockDim.x) s_h[k] = H[row * d + k];
-  if (threadIdx.x == 0) s_zy = 0.0;
-  __syncthreads();
-  const int y = ids[row];
-  PartD p{0.0, 0.0, 0.0};
-  for (int v = threadIdx.x; v < V; v += blockDim.x) {
-    const double z = dot_f64(s_h, W + static_cast<int64_t>(v) * d, d);
-    if (v == y) s_zy = z;
-    p = partd_merge(p, PartD{z, 1.0, z});
-  }
-  // merge over the block: lanes, then wavefronts
-  for (int o = 32; o > 0; o >>= 1) {
-    PartD q{__shfl_xor(p.m, o, kWave), __shfl_xor(p.s, o, kWave), __shfl_xor(p.t, o, kWave)};
-    p = partd_merge(p, q);
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) { s_m[wave] = p.m; s_s[wave] = p.s; s_t[wave] = p.t; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    PartD a{0.0, 0.0, 0.0};
-    for (int w = 0; w < 4; ++w) a = partd_merge(a, PartD{s_m[w], s_s[w], s_t[w]});
-    const bool ok = y >= 0 && y < V;
-    const double l = a.m + log(a.s);
-    const float lf = static_cast<float>(l);
-    const float lp = ok ? static_cast<float>(s_zy - l) : 0.f;
-    const float en = ok ? static_cast<float>(l - a.t / a.s) : 0.f;
-    if (logp_c) { logp_c[n] = lp; lse_c[n] = lf; ent_c[n] = en; }
-    if (logp) logp[row] = lp;
-    if (lse) lse[row] = lf;
-    if (entropy) entropy[row] = en;
-  }
 }
 
 // ------------------------------------------------------------------ clipped surrogate
@@ -1337,68 +1276,6 @@ k_dw_onehot(const uint16_t* __restrict__ H, int d, const int32_t* __restrict__ r
   }
 }
 
-// ------------------------------------------------------------------ float32: plain backward
-// dz[n, v] = g (onehot - exp(z - lse)) for a chunk of selected rows, z recomputed with the same float64 dot
-// product as the forward pass; sums are carried in float64 here too.
-__global__ void __launch_bounds__(256)
-k_dz_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel,
-         int64_t c0, const int32_t* __restrict__ ids, const float* __restrict__ lse_c, const float* __restrict__ g_c,
-         const float* __restrict__ ent_c, const float* __restrict__ kz_c, float* __restrict__ dz) {
-  extern __shared__ float s_h[];
-  const int64_t n = blockIdx.x;
-  const int64_t row = rowsel ? rowsel[c0 + n] : c0 + n;
-  for (int k = threadIdx.x; k < d; k += blockDim.x) s_h[k] = H[row * d + k];
-  __syncthreads();
-  __shared__ double s_red[32];
-  const int y = ids[row];
-  const double l = lse_c[c0 + n], g = g_c[c0 + n], en = ent_c[c0 + n], k_ent = kz_c[c0 + n];
-  // The taken token's entry g (1 - p_y): for a confident token (p_y > 1/2) 1 - p_y cancels down to the error of p_y,
-  // and the sum of the other probabilities, which carries only their relative error, is taken in its place.
-  double rest = 0.0, label_ent = 0.0, p_label = 0.0;
-  for (int v = threadIdx.x; v < V; v += blockDim.x) {
-    const double z = dot_f64(s_h, W + static_cast<int64_t>(v) * d, d);
-    const double p = exp(z - l);
-    const double e = k_ent != 0.0 ? k_ent * p * ((z - l) + en) : 0.0;     // entropy bonus: k p (log p + entropy)
-    if (v == y) {
-      label_ent = e;
-      p_label = p;
-    } else {
-      rest += p;
-      dz[n * V + v] = static_cast<float>(-g * p + e);
-    }
-  }
-  rest = block_sum<double>(rest, s_red);
-  if (y >= 0 && y < V && threadIdx.x == y % static_cast<int>(blockDim.x))
-    dz[n * V + y] = static_cast<float>(g * (p_label > 0.5 ? rest : 1.0 - p_label) + label_ent);
-}
-// dH[row, j] = sum_v dz[n, v] W[v, j]
-__global__ void __launch_bounds__(256)
-k_dh_f32(const float* __restrict__ dz, const float* __restrict__ W, int d, int V, const int32_t* __restrict__ rowsel,
-         int64_t c0, float* __restrict__ dH) {
-  const int64_t n = blockIdx.x;
-  const int64_t row = rowsel ? rowsel[c0 + n] : c0 + n;
-  for (int j = threadIdx.x; j < d; j += blockDim.x) {
-    double s = 0.0;
-    for (int v = 0; v < V; ++v) s = fma(static_cast<double>(dz[n * V + v]), static_cast<double>(W[static_cast<int64_t>(v) * d + j]), s);
-    dH[row * d + j] = static_cast<float>(s);
-  }
-}
-// dW[v, j] (+)= sum_n dz[n, v] H[row(n), j]
-__global__ void __launch_bounds__(256)
-k_dw_f32(const float* __restrict__ dz, const float* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel,
-         int64_t c0, int64_t mc, int accumulate, float* __restrict__ dW) {
-  const int v = blockIdx.x;
-  for (int j = threadIdx.x; j < d; j += blockDim.x) {
-    double s = 0.0;
-    for (int64_t n = 0; n < mc; ++n) {
-      const int64_t row = rowsel ? rowsel[c0 + n] : c0 + n;
-      s = fma(static_cast<double>(dz[n * V + v]), static_cast<double>(H[row * d + j]), s);
-    }
-    float* dst = dW + static_cast<int64_t>(v) * d + j;
-    *dst = accumulate ? static_cast<float>(static_cast<double>(*dst) + s) : static_cast<float>(s);
-  }
-}
-
 // ------------------------------------------------------------------ host side
 constexpr int64_t kF32ChunkRows = 4096;
 constexpr double kF32MaxWork = 137438953472.0;   // 2^37 multiply-adds per product
@@ -1432,6 +1309,7 @@ struct PpoWs {
   float* kz_c;
   float* cref;       // keeping pass: per selected row, the reference of E and the row factor of dz = sc E
   float* sc;
+  double* rest;      // float32 path, in place of these two: sum of the probabilities of the tokens not taken
   int32_t* flags;    // keeping pass: blocks of 256 selected rows whose dz must be recomputed
   int32_t* blk_live; // per block of 256 selected rows: some row has a gradient
   int32_t* blk_cidx; // its place among the live blocks of its chunk, -1 for a dead one
@@ -1478,8 +1356,14 @@ size_t carve_ppo(Carver& c, PpoWs& w, int64_t n_sel, int d, int V, umas_dtype dt
   w.g_c = c.take<float>(n_pad);
   w.a_c = c.take<float>(n_pad);
   w.kz_c = c.take<float>(n_pad);
-  w.cref = c.take<float>(n_pad);
-  w.sc = c.take<float>(n_pad);
+  w.cref = w.sc = nullptr;
+  w.rest = nullptr;
+  if (dt == UMAS_F32) {
+    w.rest = c.take<double>(n_pad);
+  } else {
+    w.cref = c.take<float>(n_pad);
+    w.sc = c.take<float>(n_pad);
+  }
   w.flags = c.take<int32_t>(static_cast<size_t>(cdiv(n_pad, kRowBlock)));
   w.blk_live = c.take<int32_t>(static_cast<size_t>(cdiv(n_pad, kRowBlock)));
   w.blk_cidx = c.take<int32_t>(static_cast<size_t>(cdiv(n_pad, kRowBlock)));
@@ -1498,7 +1382,7 @@ umas_status check_model_args(const void* H, const void* W, umas_dtype dt, int64_
   UMAS_REQUIRE(d >= 1 && V >= 1, UMAS_ESHAPE, "d=%d and V=%d must be positive", d, V);
   UMAS_REQUIRE(dt != UMAS_BF16 || d % 8 == 0, UMAS_ESHAPE, "bf16 needs d %% 8 == 0 (d=%d)", d);
   UMAS_REQUIRE(dt != UMAS_F32 || d <= 8192, UMAS_ESHAPE, "the float32 path supports d <= 8192 (d=%d)", d);
-  // the float32 path is the plain, untiled one (every thread walks whole rows of W): small shapes only
+  // the float32 path sums in float64: small shapes only
   UMAS_REQUIRE(dt != UMAS_F32 || static_cast<double>(n_sel) * V * d <= kF32MaxWork, UMAS_ESHAPE,
                "the float32 path is for small shapes: n_sel * V * d = %.3g exceeds %.3g; use bf16",
                static_cast<double>(n_sel) * V * d, kF32MaxWork);
@@ -1561,10 +1445,11 @@ void launch_finalize(int64_t rows, int64_t n_sel, hipStream_t st, Args... args) 
   else hipLaunchKernelGGL(k_score_finalize<false>, dim3(cdiv(rows, 32)), dim3(256), 0, st, args...);
 }
 
-// Forward scoring of the selected rows into compact arrays and/or scattered outputs.
+// Forward scoring of the selected rows into compact arrays and/or scattered outputs.  float32: `room` holds statistics of
+// parts of the vocabulary (no room: one workgroup per 32 rows walks all of it), rest_c goes with the compact arrays.
 umas_status run_score(const void* H, const void* W, umas_dtype dt, int d, int V, const int32_t* ids,
-                      const int32_t* rowsel, int64_t n_sel, const ScoreWs& w, float* logp, float* lse,
-                      float* entropy, hipStream_t st) {
+                      const int32_t* rowsel, int64_t n_sel, const ScoreWs& w, void* room, size_t room_bytes, double* rest_c,
+                      float* logp, float* lse, float* entropy, hipStream_t st) {
   if (n_sel == 0) return UMAS_OK;
   if (dt == UMAS_BF16) {
     int tiles_m = (V + Cfg::BM - 1) / Cfg::BM;
@@ -1595,10 +1480,8 @@ umas_status run_score(const void* H, const void* W, umas_dtype dt, int d, int V,
                     w.logp_c, w.lse_c, w.ent_c, logp, lse, entropy);
     UMAS_LAUNCHED("k_score_finalize");
   } else {
-    hipLaunchKernelGGL(k_score_f32, dim3(static_cast<unsigned>(n_sel)), dim3(256), d * sizeof(float), st,
-                       static_cast<const float*>(W), static_cast<const float*>(H), d, V, rowsel, ids, w.logp_c,
-                       w.lse_c, w.ent_c, logp, lse, entropy);
-    UMAS_LAUNCHED("k_score_f32");
+    return f32::score(static_cast<const float*>(W), static_cast<const float*>(H), d, V, rowsel, n_sel, ids, room, room_bytes,
+                      f32::ScoreOut{rest_c, w.logp_c, w.lse_c, w.ent_c, logp, lse, entropy}, st);
   }
   return UMAS_OK;
 }
@@ -1613,7 +1496,7 @@ extern "C" size_t umas_policy_logprobs_workspace_bytes(int64_t n_sel, int32_t d,
   if (n_sel < 0 || V < 1) return 0;
   Carver c(nullptr);
   ScoreWs w;
-  const size_t b = carve_score(c, w, n_sel, V, dtype, false);
+  const size_t b = carve_score(c, w, n_sel, V, dtype, false) + (dtype == UMAS_F32 ? align_up(f32::score_room(n_sel, V)) : 0);
   return b > 0 ? b : kAlign;
 }
 
@@ -1625,7 +1508,8 @@ extern "C" umas_status umas_policy_logprobs(const void* H, const void* W, umas_d
   if (s != UMAS_OK) return s;
   UMAS_REQUIRE((logp && lse) || n_rows == 0, UMAS_EINVAL, "logp and lse must not be NULL");
   UMAS_REQUIRE(n_sel < (1LL << 31), UMAS_ESHAPE, "at most 2^31-1 selected rows");
-  s = check_ws(workspace, workspace_bytes, umas_policy_logprobs_workspace_bytes(n_sel, d, V, dtype));
+  // float32 scores without any room as well
+  s = check_ws(workspace, workspace_bytes, dtype == UMAS_F32 ? kAlign : umas_policy_logprobs_workspace_bytes(n_sel, d, V, dtype));
   if (s != UMAS_OK) return s;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   prof_mark(st);
@@ -1637,7 +1521,7 @@ extern "C" umas_status umas_policy_logprobs(const void* H, const void* W, umas_d
   Carver c(workspace);
   ScoreWs w;
   carve_score(c, w, n_sel, V, dtype, false);
-  return run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w, logp, lse, entropy, st);
+  return run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w, workspace, workspace_bytes, nullptr, logp, lse, entropy, st);
 }
 
 // ------------------------------------------------------------------ scoring without any allocation
@@ -1676,7 +1560,7 @@ extern "C" umas_status umas_policy_logprobs_static(const void* H, const void* W,
   if (s != UMAS_OK) return s;
   UMAS_REQUIRE((logp && lse) || n_rows == 0, UMAS_EINVAL, "logp and lse must not be NULL");
   UMAS_REQUIRE(n_sel < (1LL << 31), UMAS_ESHAPE, "at most 2^31-1 selected rows");
-  const size_t need = umas_policy_logprobs_workspace_bytes(n_sel, d, V, dtype);
+  const size_t need = dtype == UMAS_F32 ? 0 : umas_policy_logprobs_workspace_bytes(n_sel, d, V, dtype);   // float32 uses none
   UMAS_REQUIRE(need <= static_cast<size_t>(UMAS_STATIC_SCRATCH_BYTES), UMAS_EWORKSPACE,
                "%lld selected rows against a vocabulary of %d need %zu bytes of scratch, the static scratch holds %zu: "
                "score fewer rows per call or use umas_policy_logprobs with a workspace",
@@ -1694,7 +1578,7 @@ extern "C" umas_status umas_policy_logprobs_static(const void* H, const void* W,
   Carver c(ws);
   ScoreWs w;
   carve_score(c, w, n_sel, V, dtype, false);
-  return run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w, logp, lse, entropy, st);
+  return run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w, nullptr, 0, nullptr, logp, lse, entropy, st);
 }
 
 extern "C" size_t umas_ppo_loss_workspace_bytes_min(int64_t n_sel, int32_t d, int32_t V, umas_dtype dtype,
@@ -1821,7 +1705,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
 
   if (!keep) {
     // forward scoring and the surrogate
-    s = run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w.score, logp_new, nullptr, nullptr, st);
+    s = run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w.score, w.chunk, room, w.rest, logp_new, nullptr, nullptr, st);
     if (s != UMAS_OK) return s;
     hipLaunchKernelGGL(k_ppo_rows, dim3(nblk), dim3(kRowBlock), kPpoLds, st, norm,
                        static_cast<int64_t>(0), n_sel, rowsel, ids, V, w.score.logp_c, w.score.ent_c, logp_old, adv,
@@ -1884,15 +1768,21 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     float* dz = reinterpret_cast<float*>(w.chunk);
     for (int64_t c0 = 0; c0 < n_sel; c0 += mc) {
       const int64_t rows = n_sel - c0 < mc ? n_sel - c0 : mc;
-      hipLaunchKernelGGL(k_dz_f32, dim3(static_cast<unsigned>(rows)), dim3(256), d * sizeof(float), st,
-                         static_cast<const float*>(W), static_cast<const float*>(H), d, V, rowsel, c0, ids,
-                         w.score.lse_c, w.g_c, w.score.ent_c, w.kz_c, dz);
+      const float *Wf = static_cast<const float*>(W), *Hf = static_cast<const float*>(H);
+      hipLaunchKernelGGL(f32::k_dz_f32, dim3(cdiv(V, f32::kVocBlock), cdiv(rows, f32::kTile)), dim3(f32::kWaves * kWave), 0, st, Wf, Hf, d, V,
+                         rowsel, c0, rows, ids, w.score.lse_c, w.rest, w.g_c, w.score.ent_c, w.kz_c, dz);
       UMAS_LAUNCHED("k_dz_f32");
-      hipLaunchKernelGGL(k_dh_f32, dim3(static_cast<unsigned>(rows)), dim3(256), 0, st, dz,
-                         static_cast<const float*>(W), d, V, rowsel, c0, static_cast<float*>(dH));
+      auto grid = [](int64_t m, int64_t n, int tiles) { return dim3(cdiv(m, tiles * f32::kTile), cdiv(n, tiles * f32::kTile)); };
+      if (f32::large_product(rows, d))
+        hipLaunchKernelGGL((f32::k_dh_f32<2, 2>), grid(rows, d, 2), dim3(f32::kGradT), 0, st, dz, Wf, d, V, rowsel, c0, rows, static_cast<float*>(dH));
+      else
+        hipLaunchKernelGGL((f32::k_dh_f32<1, 1>), grid(rows, d, 1), dim3(f32::kGradT), 0, st, dz, Wf, d, V, rowsel, c0, rows, static_cast<float*>(dH));
       UMAS_LAUNCHED("k_dh_f32");
-      hipLaunchKernelGGL(k_dw_f32, dim3(static_cast<unsigned>(V)), dim3(256), 0, st, dz, static_cast<const float*>(H),
-                         d, V, rowsel, c0, rows, (accumulate_dW || c0 > 0) ? 1 : 0, dW);
+      const int acc_dW = accumulate_dW || c0 > 0 ? 1 : 0;
+      if (f32::large_product(V, d))
+        hipLaunchKernelGGL((f32::k_dw_f32<2, 2>), grid(V, d, 2), dim3(f32::kGradT), 0, st, dz, Hf, d, V, rowsel, c0, rows, acc_dW, dW);
+      else
+        hipLaunchKernelGGL((f32::k_dw_f32<1, 1>), grid(V, d, 1), dim3(f32::kGradT), 0, st, dz, Hf, d, V, rowsel, c0, rows, acc_dW, dW);
       UMAS_LAUNCHED("k_dw_f32");
     }
     return UMAS_OK;

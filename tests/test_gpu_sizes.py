@@ -173,3 +173,49 @@ def test_critic_update_clears_the_rows_that_are_not_selected(n, n_sel, d, dt):
     assert ((dw.double() - (g[:, None] * Hd).sum(0)).abs() <= lim).all()
     assert abs(float(db) - float(g.sum())) <= float(err_g.sum() + adds * 2.0 ** -24 * g.abs().sum())
     assert abs(float(s["loss"][0]) - float(0.5 * (V_o - R[sl].double()).square().mean())) <= 1e-5 * (1 + float(V_o.square().mean()))
+
+
+# the float32 products: edges of the 32-entry tiles and of the 16 k of a round, hidden and vocabulary sizes that are not
+# multiples of four, K parts that get nothing, the 64 x 64 tiles (V / 64 x d / 64 >= 256) and what just misses them, two
+# chunks of rows, and scoring with statistics of many parts, of two and of one
+@pytest.mark.parametrize("n,d,V", [(1, 1, 1), (3, 5, 2), (33, 31, 33), (40, 16, 129), (17, 130, 700), (200, 64, 512), (70, 100, 4097),
+                                   (90, 1022, 1030), (1100, 1024, 1023), (4500, 24, 77)])
+@pytest.mark.parametrize("entropy_coef", [0.0, 0.05])
+def test_float32_products(n, d, V, entropy_coef):
+    rng = np.random.default_rng(n + d)
+    H = rng.normal(size=(n, d)).astype(np.float32)
+    H /= np.sqrt(np.mean(H.astype(np.float64) ** 2, 1, keepdims=True)).astype(np.float32)
+    W = (rng.normal(size=(V, d)) / np.sqrt(d)).astype(np.float32)
+    ids = rng.integers(0, V, size=n).astype(np.int32)
+    sel = rng.permutation(n)[:max(1, n - n // 5)].astype(np.int32)
+    ids[sel[-1]] = V if len(sel) > 1 else 0
+    good = sel[ids[sel] < V]
+    safe = np.minimum(ids, V - 1)
+    adv = rng.normal(size=n).astype(np.float32)
+    adv[ids >= V] = 0                                                  # a row without a valid id has no gradient
+    logp_o, lse_o, ent_o = orc.score(H, W, safe, sel)
+    dev = [P.to_dev(x) for x in (H, W, ids, sel)]
+    full = [x.cpu().numpy() for x in umas.umas_policy_logprobs(*dev)]
+    alone = [x.cpu().numpy() for x in umas.umas_policy_logprobs_static(*dev)]
+    nbytes = umas.ppo_workspace_bytes(len(sel), d, V, torch.float32, 0, minimum=True)
+    for a, b, o, rows in zip(full, alone, (logp_o, lse_o, ent_o), (good, sel, good)):
+        # float64 sums, one rounding to float32 (log V + |z| bounds every quantity that is subtracted)
+        assert np.abs(a[rows] - o[rows]).max() <= 2.0 ** -22 * (np.abs(lse_o[sel]).max() + 1)
+        assert np.abs(a - b).max() <= 2.0 ** -22 * (np.abs(lse_o[sel]).max() + 1)
+    logp_old = np.zeros(n, np.float32)
+    logp_old[sel] = (logp_o[sel] + 0.01 * rng.normal(size=len(sel))).astype(np.float32)
+    _, g_o = orc.ppo_loss(logp_o, logp_old, adv, ent_o, sel, np.zeros(n, np.int32), 0, 0.2)
+    if entropy_coef:
+        dH_o, dW_o = orc.lm_head_backward_entropy(H, W, safe, lse_o, ent_o, g_o, entropy_coef, len(sel), good)
+    else:
+        dH_o, dW_o = orc.lm_head_backward(H, W, safe, lse_o, g_o, sel)
+    dW0 = (0.01 * rng.normal(size=(V, d))).astype(np.float32)
+    for workspace in (None, torch.empty(nbytes, dtype=torch.uint8, device="cuda")):
+        stats, logp_new, dH, dW = umas.umas_ppo_loss_fwd_bwd(*dev, P.to_dev(logp_old), P.to_dev(adv), None, 0, 0.2, workspace=workspace,
+                                                             entropy_coef=entropy_coef, accumulate_dW=True, dW=P.to_dev(dW0))
+        assert int(umas.read_stats(stats)["n_scored"][0]) == len(sel)
+        dH_g, dW_g = dH.cpu().numpy(), dW.cpu().numpy()
+        # dz is rounded to float32 (its g carries the rounding of a ratio, 1e-6 of it), each result once more
+        scale_h = np.abs(dH_o).max() + 1e-12
+        assert np.abs(dH_g - dH_o).max() <= 1e-5 * scale_h, (n, d, V)
+        assert np.abs(dW_g - dW0 - dW_o).max() <= 1e-5 * (np.abs(dW_o).max() + 1e-12) + 2.0 ** -23 * (np.abs(dW0) + np.abs(dW_o)).max(), (n, d, V)
