@@ -120,6 +120,14 @@ __device__ __forceinline__ void mfma_mainloop(const uint16_t* const (&pa)[C::NA]
   }
 }
 
+// The thread's number as a value that the compiler takes for a new one every time: what a tile derives from it (addresses of
+// loads and fragments, dozens of registers for each kind of tile) is then not kept over a loop of tiles.
+__device__ __forceinline__ int tile_thread() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0xFFFFFFFF, 0x00020000);
 }
@@ -151,11 +159,10 @@ struct Ring2Cfg {
   static_assert(C::T % 64 == 0 && (C::BM * 8) % C::T == 0 && (C::BN * 8) % C::T == 0, "load slots divide evenly");
 };
 template <class C>
-__device__ __forceinline__ int ring2_row(int i) { return i * (C::T / 8) + (threadIdx.x >> 3); }
+__device__ __forceinline__ int ring2_row(int i, int t = threadIdx.x) { return i * (C::T / 8) + (t >> 3); }
 // K offset (elements) of the chunk this lane fetches: slot (tid & 7) of row ring2_row holds chunk slot ^ ((row >> 1) & 7);
 // rows per pass and wavefront row offsets are multiples of 8, so (row >> 1) & 7 = ((tid >> 3) >> 1) & 7 with tid >> 3 < 64
-__device__ __forceinline__ int ring2_kofs() {
-  const int t = threadIdx.x;
+__device__ __forceinline__ int ring2_kofs(int t = threadIdx.x) {
   return 8 * ((t & 7) ^ (((t >> 3) >> 1) & 7));
 }
 
@@ -305,8 +312,9 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
   using R = Ring2Cfg<C>;
   static_assert(C::BM == 256 && C::BN == 256 && C::T == 512 && R::NA == 4 && R::NB == 4, "written for 256x256 tiles, 8 wavefronts");
   constexpr int HA = C::MI / 2;                      // A blocks of one half of the wavefront's sub-tile
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tid = tile_thread();
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / C::WN, wn = wave % C::WN;
   char* base = reinterpret_cast<char*>(lds);
   const int nsub = K / R::BK;
@@ -519,13 +527,13 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
 
 // Position of accumulator element r of block (i, j) inside the workgroup tile: row 4 (l / 16) + r, column l % 16 of the block.
 template <class C>
-__device__ __forceinline__ int acc_row(int i, int r) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__device__ __forceinline__ int acc_row(int i, int r, int t = threadIdx.x) {
+  const int lane = t & 63, wave = t >> 6;
   return (wave / C::WN) * C::WTM + i * 16 + (lane >> 4) * 4 + r;
 }
 template <class C>
-__device__ __forceinline__ int acc_col(int j) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__device__ __forceinline__ int acc_col(int j, int t = threadIdx.x) {
+  const int lane = t & 63, wave = t >> 6;
   return (wave % C::WN) * C::WTN + j * 16 + (lane & 15);
 }
 
@@ -556,17 +564,18 @@ __device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int* tm, i
   *tn = (grp - gm * total_groups_n) * GN + within / GM;
   return *tm < tiles_m && *tn < tiles_n;
 }
-// Shares of a sequence of groups per XCD: XCD x owns groups first[x] .. first[x + 1] - 1.
-struct XcdGroups {
+// Shares of a sequence of tiles per XCD: XCD x owns tiles first[x] .. first[x + 1] - 1.
+struct XcdShares {
   int first[9];
 };
-// Tile number `within` of group `grp`; false when the group is cut off by the matrix's edge there.
+// Tile number t of tiles_m x tiles_n, numbered group of GM x GN after group (row of groups after row of groups; the groups at
+// the edges are smaller), so that any run of GM GN numbers shares operand rows.
 template <int GM, int GN>
-__device__ __forceinline__ bool tile_of_group(int grp, int within, int tiles_m, int tiles_n, int* tm, int* tn) {
-  const int groups_n = (tiles_n + GN - 1) / GN;
-  *tm = grp / groups_n * GM + within % GM;
-  *tn = grp % groups_n * GN + within / GM;
-  return *tm < tiles_m && *tn < tiles_n;
+__device__ __forceinline__ void tile_of_groups(int t, int tiles_m, int tiles_n, int* tm, int* tn) {
+  const int gm = t / (GM * tiles_n), in_row = t - gm * (GM * tiles_n), rows = min(GM, tiles_m - gm * GM);
+  const int gn = in_row / (rows * GN), in_group = in_row - gn * (rows * GN), c = in_group / rows;
+  *tm = gm * GM + in_group - c * rows;
+  *tn = gn * GN + c;
 }
 template <int GM, int GN>
 inline unsigned tile_grid(int tiles_m, int tiles_n, int per_wg) {           // workgroups tile_coords needs
@@ -575,11 +584,6 @@ inline unsigned tile_grid(int tiles_m, int tiles_n, int per_wg) {           // w
   const long long groups_per_xcd = (groups + 7) / 8;
   const long long wg_groups = (groups_per_xcd + per_wg - 1) / per_wg;       // groups of workgroups per XCD
   return static_cast<unsigned>(wg_groups * (GM * GN) * 8);
-}
-template <int GM, int GN>
-inline unsigned group_grid(int tiles_m, int tiles_n, int slices) {          // whole groups, slices times
-  const long long groups = static_cast<long long>((tiles_m + GM - 1) / GM) * ((tiles_n + GN - 1) / GN) * slices;
-  return static_cast<unsigned>((groups + 7) / 8 * (GM * GN) * 8);
 }
 
 }  // namespace umas

@@ -636,50 +636,53 @@ k_ppo_stats(int nblk, int n_roles, float entropy_coef, int64_t norm_rows, const 
 struct LiveInfo {
   int32_t n_live;        // live blocks of the chunk
   int32_t k_rows;        // rows of the packed operands that exist (the chunk's last block may be partly filled)
-  XcdGroups dw_groups;   // dW tile groups per XCD (see share_dw_groups)
+  XcdShares dw;          // dW tiles per XCD (see share_dw)
+  int32_t next[8];       // per XCD: next place of its sequence of tiles, counted up by the workgroups of k_gemm_dh_dw
 };
-// Shares of the dW tile groups per XCD for k_gemm_dh_dw: every XCD first works through its dH groups (contiguous
-// ranges, slice after slice; a group costs about Vp / slices of K per tile), then dW groups (k_len of K
-// per tile) go to the XCDs so that all finish as evenly as whole groups allow, at most max_groups to one XCD (the grid has
-// no more; 8 max_groups cover all groups).
+// Shares of the dW tiles per XCD for k_gemm_dh_dw: every XCD first works through its eighth of the dH tiles (contiguous
+// ranges, slice after slice; a tile costs about Vp / slices of K), then dW tiles (k_len of K each) go to the XCDs so that all
+// finish as evenly as possible.  Shares are whole groups where there are many: an XCD's workgroups that work on parts of two
+// groups at a time read a third more through its L2 (39 000 rows of 2048: 6 % of the step).
 constexpr int64_t kTileOverheadK = 768;   // what a tile costs besides its K steps (first loads, epilogue), as a length of K
+__device__ __forceinline__ int share_unit(int tiles, int slices) { return slices == 1 && tiles >= 8 * kGM * kGN ? kGM * kGN : 1; }
+__device__ __forceinline__ int dh_first(int tiles_dh, int slices, int xcd) {
+  const int unit = share_unit(tiles_dh, slices), units = (tiles_dh + unit - 1) / unit;
+  return min(static_cast<int>(static_cast<int64_t>(units) * xcd / 8) * unit, tiles_dh);
+}
 // Called by one wavefront; lane x of every eight works for XCD x (all eights do the same).  (One thread walking the eight XCDs took 20 us.)
-__device__ void share_dw_groups(int tiles_r, int tiles_v, int tiles_d, int64_t Vp, int slices, int64_t k_len, int max_groups, XcdGroups* out) {
+__device__ void share_dw(int tiles_r, int tiles_v, int tiles_d, int64_t Vp, int slices, int64_t k_len, XcdShares* out) {
   const int x = threadIdx.x & 7;
-  auto sum8 = [](int v) {
+  auto sum8 = [](int64_t v) {
 #pragma unroll
-    for (int o = 4; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    for (int o = 4; o > 0; o >>= 1) v += static_cast<int64_t>(__shfl_xor(static_cast<long long>(v), o, kWave));
     return v;
   };
-  const int groups_dh = (tiles_r + kGM - 1) / kGM * ((tiles_d + kGN - 1) / kGN) * slices;
-  const int per_xcd = (groups_dh + 7) / 8;
-  const int n_dh = max(0, min(groups_dh - x * per_xcd, per_xcd));
-  const int64_t load = n_dh * (Vp / slices + kTileOverheadK);
-  const int groups_dw = (tiles_v + kGM - 1) / kGM * ((tiles_d + kGN - 1) / kGN);
-  int cnt;
+  const int tiles_dh = tiles_r * tiles_d * slices;
+  const int64_t load = (dh_first(tiles_dh, slices, x + 1) - dh_first(tiles_dh, slices, x)) * (Vp / slices + kTileOverheadK);
+  const int tiles_dw = tiles_v * tiles_d, unit = share_unit(tiles_dw, 1);
+  const int64_t units = (tiles_dw + unit - 1) / unit;
+  k_len *= unit;
+  int64_t cnt;
   if (k_len <= 0) {                                    // nothing to even out
-    cnt = groups_dw / 8 + (x < groups_dw % 8 ? 1 : 0);
+    cnt = units / 8 + (x < units % 8 ? 1 : 0);
   } else {
-    // the lowest level T up to which the XCDs can be filled with whole groups so that all groups are placed ...
-    auto take = [&](int64_t T) {
-      // (a double quotient: the operands stay far below 2^53 and 64-bit integer division is slow here)
-      const int64_t n = T > load ? static_cast<int64_t>(static_cast<double>(T - load) / static_cast<double>(k_len)) : 0;
-      return static_cast<int>(n < max_groups ? n : max_groups);
-    };
+    // the lowest level T up to which the XCDs can be filled with whole units so that all are placed ...
+    // (a double quotient: the operands stay far below 2^53 and 64-bit integer division is slow here)
+    auto take = [&](int64_t T) { return T > load ? static_cast<int64_t>(static_cast<double>(T - load) / static_cast<double>(k_len)) : int64_t{0}; };
     int64_t lo = load, hi = load;
 #pragma unroll
     for (int o = 4; o > 0; o >>= 1) {
       lo = min(lo, static_cast<int64_t>(__shfl_xor(static_cast<long long>(lo), o, kWave)));
       hi = max(hi, static_cast<int64_t>(__shfl_xor(static_cast<long long>(hi), o, kWave)));
     }
-    hi += groups_dw * k_len;
+    hi += units * k_len;
     while (lo < hi) {                                  // the same in every lane
       const int64_t mid = lo + (hi - lo) / 2;
-      if (sum8(take(mid)) >= groups_dw) hi = mid; else lo = mid + 1;
+      if (sum8(take(mid)) >= units) hi = mid; else lo = mid + 1;
     }
     cnt = take(lo);
-    // ... and the few groups too many at that level come off the XCDs that would finish last
-    for (int total = sum8(cnt); total > groups_dw; --total) {
+    // ... and the few units too many at that level come off the XCDs that would finish last
+    for (int64_t total = sum8(cnt); total > units; --total) {
       int64_t worst = cnt > 0 ? load + cnt * k_len : -1;
 #pragma unroll
       for (int o = 4; o > 0; o >>= 1) worst = max(worst, static_cast<int64_t>(__shfl_xor(static_cast<long long>(worst), o, kWave)));
@@ -687,18 +690,14 @@ __device__ void share_dw_groups(int tiles_r, int tiles_v, int tiles_d, int64_t V
       if (x == __ffsll(static_cast<long long>(who)) - 1) --cnt;
     }
   }
-  int first = cnt;                                     // inclusive prefix sums: where the next XCD's groups start
+  int first = static_cast<int>(cnt);                   // inclusive prefix sums: where the next XCD's units start
 #pragma unroll
   for (int o = 1; o < 8; o <<= 1) {
     const int t = __shfl_up(first, o, kWave);
     if (x >= o) first += t;
   }
   if (threadIdx.x == 0) out->first[0] = 0;
-  if (threadIdx.x < 8) out->first[x + 1] = first;
-}
-inline int max_dw_groups_per_xcd(int tiles_v, int tiles_d) {   // 8 x this many cover every group with room to even out
-  const int64_t groups_dw = static_cast<int64_t>((tiles_v + kGM - 1) / kGM) * ((tiles_d + kGN - 1) / kGN);
-  return static_cast<int>((groups_dw + 7) / 8 + 20);
+  if (threadIdx.x < 8) out->first[x + 1] = static_cast<int>(min(static_cast<int64_t>(first) * unit, static_cast<int64_t>(tiles_dw)));
 }
 // What opens the keeping update, in one launch: the first nblk workgroups mark the live blocks of 256 selected rows and
 // clear their flags, the others take the rows' references and clear what the call defines everywhere (logp_new when rows
@@ -722,7 +721,7 @@ struct OpenArgs {
 };
 // One workgroup per chunk: packs the live blocks (all of them with all_live), blk0 = first block of the chunk.
 __global__ void __launch_bounds__(512)
-k_live_scan(int blk0, int nblk, int64_t rows, int all_live, int tiles_v, int tiles_d, int64_t Vp, int slices, int max_groups,
+k_live_scan(int blk0, int nblk, int64_t rows, int all_live, int tiles_v, int tiles_d, int64_t Vp, int slices,
             const int32_t* __restrict__ blk_live, int32_t* __restrict__ blk_cidx, int32_t* __restrict__ blk_orig,
             LiveInfo* __restrict__ info) {
   __shared__ int smem[32];
@@ -742,10 +741,8 @@ k_live_scan(int blk0, int nblk, int64_t rows, int all_live, int tiles_v, int til
     const int64_t last_rows = rows - static_cast<int64_t>(nblk - 1) * 256;     // rows of the chunk's last block
     info->k_rows = static_cast<int32_t>(s_last_live ? static_cast<int64_t>(total - 1) * 256 + last_rows : static_cast<int64_t>(total) * 256);
   }
-  if (t < kWave) {
-    share_dw_groups(total, tiles_v, tiles_d, Vp, slices, total > 0 ? static_cast<int64_t>(total) * 256 + kTileOverheadK : 0, max_groups,
-                    &info->dw_groups);
-  }
+  if (t < 8) info->next[t] = 0;
+  if (t < kWave) share_dw(total, tiles_v, tiles_d, Vp, slices, total > 0 ? static_cast<int64_t>(total) * 256 + kTileOverheadK : 0, &info->dw);
 }
 
 // ------------------------------------------------------------------ bf16: row references and row factors of the keeping pass
@@ -976,9 +973,10 @@ __device__ __forceinline__ KContig blocked_rows_tile(const uint16_t* X, int64_t 
   KContig c;
   c.rsrc = make_rsrc(X + blk_offset(row_blk, voc_blk, tiles_v));
   c.hi_bytes = static_cast<uint32_t>(kBlkElems * 2 - 4 * 128);        // from the fourth step of a block to the next block
-  const uint32_t kofs = ring2_kofs();
+  const int tid = tile_thread();
+  const uint32_t kofs = ring2_kofs(tid);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) c.off[i] = (static_cast<uint32_t>(ring2_row<C>(i)) * 256u + kofs) * 2u;
+  for (int i = 0; i < 4; ++i) c.off[i] = (static_cast<uint32_t>(ring2_row<C>(i, tid)) * 256u + kofs) * 2u;
   return c;
 }
 
@@ -993,7 +991,7 @@ template <class F>
 __device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[Cfg::MI][Cfg::NI], uint16_t* lds, F at, int accumulate) {
   using C = Cfg;
   typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // dW has the alignment of a float
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int tid = tile_thread(), lane = tid & 63, wave = tid >> 6;
   char* stage = reinterpret_cast<char*>(lds) + wave * (64 * kAccPitch);
   const int r0 = wave / C::WN * C::WTM, c0 = wave % C::WN * C::WTN + (lane & 15) * 4;
 #pragma unroll
@@ -1053,15 +1051,16 @@ __device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, in
     store_acc_f32(acc, lds, [&](int r, int c) { return out + r * C::BN + c; }, 0);
     return;
   }
+  const int tid = tile_thread();
 #pragma unroll
   for (int bj = 0; bj < C::NI; ++bj) {
-    const int j = n0 + acc_col<C>(bj);
+    const int j = n0 + acc_col<C>(bj, tid);
     if (j >= d) continue;
 #pragma unroll
     for (int bi = 0; bi < C::MI; ++bi)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t m = m0 + acc_row<C>(bi, r);
+        const int64_t m = m0 + acc_row<C>(bi, r, tid);
         if (m >= rows) continue;
         const int64_t row = rowsel ? rowsel[c0 + m] : c0 + m;
         const float g = g_c[c0 + m];
@@ -1106,33 +1105,74 @@ __device__ __forceinline__ void dw_tile(int tile_m, int tile_n, const uint16_t* 
     return m0 + r < v_end && n0 + c < d ? dW + (m0 + r) * d + n0 + c : nullptr;     // d is a multiple of 8: four columns are all inside or all outside
   }, accumulate);
 }
-// Both products in one launch, in groups of 4 x 8 tiles that run on one XCD.  Every XCD owns a contiguous range of the dH
-// groups (slice after slice, so that its workgroups share a slice of both operands) and behind it the share of the dW
-// groups that evens out the sum (share_dw_groups): dH tiles are long (K = vocabulary, or a slice of it) and few, on their
-// own they leave a fifth of the last round idle; they go first and the many short dW tiles fill up.  (Sliced dH groups and
-// dW groups taking turns instead: +-1 % at 725 rows, 8 % slower at 203.)
+// Both products in one launch, in groups of 4 x 8 tiles that are worked on together on one XCD.  Every XCD owns a contiguous
+// range of the dH tiles (slice after slice, so that its workgroups share a slice of both operands) and behind it the share
+// of the dW tiles that evens out the sum (share_dw): dH tiles are long (K = vocabulary, or a slice of it) and few, on their
+// own they leave a fifth of the last round idle; they go first and the many short dW tiles fill up.  (Sliced dH tiles and
+// dW tiles taking turns instead: +-1 % at 725 rows, 8 % slower at 203.)
+// One workgroup per compute unit stays for the whole launch and takes the next place of its XCD's sequence whenever it is done
+// (the number of the next place is fetched a tile ahead): a workgroup per tile paid for its start at every tile, of which short
+// selections have many short ones, and workgroups without a tile (groups cut off by the edge, places kept free because
+// the shares are known on the device only) waited for a whole compute unit like the others.  A workgroup whose sequence is at
+// its end goes on with the one that has most left.  203 rows of 3584 1316 -> 845 us, 64 rows of 2048 841 -> 455, 725 rows
+// 1098 -> 930, 2000 rows of 3584 3.93 -> 3.52 ms, 39 000 rows of 2048 37.5 -> 36.5 ms.
 __global__ void __launch_bounds__(Cfg::T)
 k_gemm_dh_dw(const uint16_t* __restrict__ dZ, int64_t Vp, int64_t mcp, const uint16_t* __restrict__ W,
              const uint16_t* __restrict__ Hx, int hx_blocked, const int32_t* __restrict__ h_rowmap, int d, int V, int tiles_v,
-             int tiles_d, DhSlices sl, int tiles_r, const LiveInfo* __restrict__ info, const int32_t* __restrict__ blk_orig,
+             int tiles_d, DhSlices sl, int tiles_r, LiveInfo* __restrict__ info, const int32_t* __restrict__ blk_orig,
              uint16_t* __restrict__ dH, float* __restrict__ dW, int accumulate, const int32_t* __restrict__ rowsel,
              int64_t c0, int64_t rows, const int32_t* __restrict__ ids, const float* __restrict__ g_c,
              const float* __restrict__ sc) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[MixedLdsBytes<Cfg>::value / 2];
   const int n_live = info->n_live;                     // live blocks of rows: dH row tiles, dW K blocks
-  const int xcd = static_cast<int>(blockIdx.x & 7), seq = static_cast<int>(blockIdx.x >> 3) / (kGM * kGN), within = static_cast<int>(blockIdx.x >> 3) % (kGM * kGN);
-  const int groups_mn = (n_live + kGM - 1) / kGM * ((tiles_d + kGN - 1) / kGN), groups_dh = groups_mn * sl.n;
-  const int per_xcd = (groups_dh + 7) / 8, first_dh = xcd * per_xcd;
-  const int n_dh = max(0, min(per_xcd, groups_dh - first_dh)), first_dw = info->dw_groups.first[xcd], n_dw = info->dw_groups.first[xcd + 1] - first_dw;
-  if (seq >= n_dh + n_dw) return;
-  int tile_m, tile_n;
-  if (seq < n_dh) {
-    const int grp = first_dh + seq, slice = grp / max(groups_mn, 1);
-    if (!tile_of_group<kGM, kGN>(grp - slice * groups_mn, within, n_live, tiles_d, &tile_m, &tile_n)) return;
-    dh_tile(tile_m, blk_orig[(c0 >> 8) + tile_m], tile_n, slice, sl, tiles_r, tiles_d, dZ, Vp, W, d, V, dH, rowsel, c0, rows, ids, g_c, sc, lds);
-  } else {
-    if (!tile_of_group<kGM, kGN>(first_dw + seq - n_dh, within, tiles_v, tiles_d, &tile_m, &tile_n)) return;
-    dw_tile(tile_m, tile_n, dZ, mcp, Vp, Hx, hx_blocked, d, V, h_rowmap, n_live * 256, info->k_rows, dW, accumulate, lds);
+  const int k_rows = info->k_rows, tiles_mn = n_live * tiles_d, tiles_dh = tiles_mn * sl.n;
+  // whose sequence of tiles the workgroup takes from, and the sequence: dH tiles, then dW tiles
+  int xcd = static_cast<int>(blockIdx.x & 7), first_dh, n_dh, first_dw, n_all;
+  auto sequence = [&]() {
+    first_dh = dh_first(tiles_dh, sl.n, xcd);
+    n_dh = dh_first(tiles_dh, sl.n, xcd + 1) - first_dh;
+    first_dw = info->dw.first[xcd];
+    n_all = n_dh + info->dw.first[xcd + 1] - first_dw;
+  };
+  sequence();
+  volatile int* const word = reinterpret_cast<volatile int*>(lds);   // wavefront 0's own at the end of a tile
+  int taken = threadIdx.x == 0 ? atomicAdd(&info->next[xcd], 1) : 0;
+  for (;;) {
+    if (threadIdx.x == 0) *word = taken;
+    __syncthreads();
+    int seq = __builtin_amdgcn_readfirstlane(*word);
+    __syncthreads();
+    while (seq >= n_all) {                               // the sequence is at its end: on with the one that has most left
+      if (threadIdx.x < kWave) {
+        const int x = threadIdx.x & 7;
+        const int length = dh_first(tiles_dh, sl.n, x + 1) - dh_first(tiles_dh, sl.n, x) + info->dw.first[x + 1] - info->dw.first[x];
+        const int left = length - __hip_atomic_load(&info->next[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int most = left;
+#pragma unroll
+        for (int o = 4; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, kWave));
+        if (most > 0) xcd = __ffsll(static_cast<long long>(__ballot(left == most))) - 1;
+        if (threadIdx.x == 0) {
+          word[0] = most > 0 ? atomicAdd(&info->next[xcd], 1) : -1;
+          word[1] = xcd;
+        }
+      }
+      __syncthreads();
+      seq = __builtin_amdgcn_readfirstlane(word[0]);
+      xcd = __builtin_amdgcn_readfirstlane(word[1]);
+      __syncthreads();
+      if (seq < 0) return;
+      sequence();
+    }
+    if (threadIdx.x == 0) taken = atomicAdd(&info->next[xcd], 1);
+    int tile_m, tile_n;
+    if (seq < n_dh) {
+      const int t = first_dh + seq, slice = t / tiles_mn;
+      tile_of_groups<kGM, kGN>(t - slice * tiles_mn, n_live, tiles_d, &tile_m, &tile_n);
+      dh_tile(tile_m, blk_orig[(c0 >> 8) + tile_m], tile_n, slice, sl, tiles_r, tiles_d, dZ, Vp, W, d, V, dH, rowsel, c0, rows, ids, g_c, sc, lds);
+    } else {
+      tile_of_groups<kGM, kGN>(first_dw + seq - n_dh, tiles_v, tiles_d, &tile_m, &tile_n);
+      dw_tile(tile_m, tile_n, dZ, mcp, Vp, Hx, hx_blocked, d, V, h_rowmap, n_live * 256, k_rows, dW, accumulate, lds);
+    }
   }
 }
 
@@ -1328,10 +1368,10 @@ size_t chunk_bytes(int64_t mc, int d, int V, umas_dtype dt) {
 // How the dH product of a chunk is cut along the vocabulary.  dH has tiles_r x tiles_d tiles of the whole vocabulary's K
 // each; with few row tiles that is fewer long tiles than compute units, and the launch lasts as long as one of them (3.6 ms
 // at V = 151 936 whether there are 64 rows or 2000).  Below kDhSliceTiles, one tile per compute unit, they are cut into about
-// 512 / tiles slices, two pieces per compute unit, so that the rounds fill evenly; partial sums cost 256 KB a piece.  Update call, whole: 203
-// rows of 2048 3745 -> 1260 us (of 3584: 4205 -> 1890), 725 rows 4150 -> 1680, 2900 rows 5990 -> 4950.  (Cut as well,
-// 280 tiles gain 5 %, 448 nothing; above the line dH stays bit for bit the same however the rows are chunked.)  A quarter and half as many slices are up to 15 % and 7 %
-// slower at 64 to 500 rows, half as many again within 2 %.
+// 256 / tiles slices, a piece per compute unit (the dW tiles behind them fill the last round); partial sums cost 256 KB a
+// piece.  Gradients and k_dh_reduce together with 256 / 384 / 512 / 768 pieces: 64 rows of 2048 467 / 460 / 480 / 488 us, 203 rows
+// of 3584 859 / 875 / 869 / 892, 725 rows of 2048 947 / 956 / 959 / 984, 6000 rows 5.91 / 5.90 / 5.98 / 5.90 ms; whole
+// tiles took 3.6 to 4 ms for the first three.  Above the line dH stays bit for bit the same however the rows are chunked.
 constexpr int kDhSliceTiles = 256;
 struct DhPlan {
   int slices, voc_blks;
@@ -1341,7 +1381,7 @@ size_t dh_part_bytes(const DhPlan& p, int tiles_r, int tiles_d) {
 }
 DhPlan plan_dh(int64_t tiles_r, int64_t tiles_d, int tiles_v, size_t room) {
   if (tiles_r * tiles_d >= kDhSliceTiles) return DhPlan{1, tiles_v};
-  int want = static_cast<int>((512 + tiles_r * tiles_d - 1) / (tiles_r * tiles_d));
+  int want = static_cast<int>((kDhSliceTiles + tiles_r * tiles_d - 1) / (tiles_r * tiles_d));
   const size_t one = static_cast<size_t>(tiles_r * tiles_d) * (256 * 256 * sizeof(float));
   if (static_cast<size_t>(want) > room / one) want = static_cast<int>(room / one);
   if (want > tiles_v) want = tiles_v;
@@ -1689,9 +1729,8 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
                        const int32_t* h_rowmap, const float* sc) -> umas_status {
     const int64_t mcp = round_up(rows, 256);
     const int tiles_r = static_cast<int>(mcp / 256), tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
-    const unsigned grid_dh = group_grid<kGM, kGN>(tiles_r, tiles_d, sl.n);
-    const unsigned grid_dw = static_cast<unsigned>(max_dw_groups_per_xcd(tiles_v, tiles_d)) * kGM * kGN * 8;
-    hipLaunchKernelGGL(k_gemm_dh_dw, dim3(grid_dh + grid_dw), dim3(Cfg::T), 0, st, op, Vp, mcp, Wb, Hx, hx_blocked, h_rowmap, d, V, tiles_v,
+    const unsigned grid = static_cast<unsigned>(round_up(device_cus(), 8));      // every XCD's sequence needs somebody
+    hipLaunchKernelGGL(k_gemm_dh_dw, dim3(grid), dim3(Cfg::T), 0, st, op, Vp, mcp, Wb, Hx, hx_blocked, h_rowmap, d, V, tiles_v,
                        tiles_d, sl, tiles_r, w.live, w.blk_orig, static_cast<uint16_t*>(dH), dW, (accumulate_dW || c0 > 0) ? 1 : 0,
                        rowsel, c0, rows, ids, w.g_c, sc);
     UMAS_LAUNCHED("k_gemm_dh_dw");
@@ -1721,7 +1760,6 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     UMAS_LAUNCHED("k_update_open");
     const int64_t n_pad = round_up(n_sel, Cfg::BN);
     const int tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
-    const int max_groups = max_dw_groups_per_xcd(tiles_v, tiles_d);
     for (int64_t c0 = 0; c0 < n_sel; c0 += mc) {
       const int64_t rows = n_sel - c0 < mc ? n_sel - c0 : mc;
       const int64_t mcp = round_up(rows, 256);
@@ -1731,7 +1769,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       DhSlices sl;
       dh_plan(rows, &sl);
       hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, static_cast<int>(c0 >> 8), tiles_r, rows, kl_coef != 0.f ? 1 : 0, tiles_v,
-                         tiles_d, Vp, sl.n, max_groups, w.blk_live, w.blk_cidx, w.blk_orig, w.live);   // a KL term gives every row a gradient
+                         tiles_d, Vp, sl.n, w.blk_live, w.blk_cidx, w.blk_orig, w.live);   // a KL term gives every row a gradient
       UMAS_LAUNCHED("k_live_scan");
       hipLaunchKernelGGL(k_score_keep_tiles, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, kTilesPerWg)), dim3(Cfg::T), 0, st,
                          Wb, Hb, d, V, rowsel, c0, rows, ids, tiles_v, tiles_r, w.score.partial, n_pad, w.cref, E, Vp, w.flags,
@@ -1803,7 +1841,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     DhSlices sl;
     dh_plan(rows, &sl);
     hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, static_cast<int>(c0 >> 8), tiles_r, rows, 1, tiles_v, tiles_d, Vp, sl.n,
-                       max_dw_groups_per_xcd(tiles_v, tiles_d), w.blk_live, w.blk_cidx, w.blk_orig, w.live);
+                       w.blk_live, w.blk_cidx, w.blk_orig, w.live);
     UMAS_LAUNCHED("k_live_scan");
     s = gradients(c0, rows, sl, dZ, rowsel ? Hb : Hb + c0 * d, 0, rowsel ? rowsel + c0 : nullptr, nullptr);
     if (s != UMAS_OK) return s;
