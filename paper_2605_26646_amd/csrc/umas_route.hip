@@ -749,6 +749,37 @@ k_rowsel(SelArgs A) {
 }
 
 // ------------------------------------------------------------------ host side
+// The trajectories of every group that occurs, by group and ascending in it: members as a CSR with offsets off.  Groups that
+// arrive in order (members next to each other) need no sorting, group numbers that are not much larger than the number of
+// trajectories are counted, a stable sort by comparison is left for the rest: 32 768 trajectories in order 617 -> 19 us, in any
+// order 50.
+void group_members(const int32_t* group, int n, std::vector<int32_t>* off, std::vector<int32_t>* mem) {
+  mem->resize(n);
+  off->reserve(static_cast<size_t>(n) + 1);
+  off->push_back(0);
+  if (std::is_sorted(group, group + n)) {
+    for (int b = 0; b < n; ++b) (*mem)[b] = b;
+    for (int b = 1; b < n; ++b)
+      if (group[b] != group[b - 1]) off->push_back(b);
+  } else {
+    const int32_t top = *std::max_element(group, group + n);
+    if (top < 4 * static_cast<int64_t>(n) + 1024) {
+      std::vector<int32_t> at(static_cast<size_t>(top) + 2, 0);
+      for (int b = 0; b < n; ++b) ++at[group[b] + 1];
+      for (int32_t k = 0; k <= top; ++k) {
+        if (at[k + 1] > 0 && at[k] > 0) off->push_back(at[k]);
+        at[k + 1] += at[k];
+      }
+      for (int b = 0; b < n; ++b) (*mem)[at[group[b]]++] = b;
+    } else {
+      for (int b = 0; b < n; ++b) (*mem)[b] = b;
+      std::stable_sort(mem->begin(), mem->end(), [&](int32_t x, int32_t y) { return group[x] < group[y]; });
+      for (int i = 1; i < n; ++i)
+        if (group[(*mem)[i]] != group[(*mem)[i - 1]]) off->push_back(i);
+    }
+  }
+  off->push_back(n);
+}
 umas_status validate(const umas_graph* g, const umas_rewards* r, const umas_streams* o) {
   UMAS_REQUIRE(g && r && o, UMAS_EINVAL, "graph, rewards and out must not be NULL");
   UMAS_REQUIRE(g->n_roles >= 1 && g->n_roles <= UMAS_MAX_ROLES, UMAS_ESHAPE, "n_roles=%d outside [1,%d]",
@@ -844,14 +875,7 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
   int n_groups = 0;
   std::vector<int32_t> goff, gmem;
   if (g->traj_group && r->traj_reward && B > 0) {
-    gmem.resize(B);
-    for (int b = 0; b < B; ++b) gmem[b] = b;
-    std::stable_sort(gmem.begin(), gmem.end(),
-                     [&](int32_t x, int32_t y) { return g->traj_group[x] < g->traj_group[y]; });
-    goff.push_back(0);
-    for (int i = 1; i < B; ++i)
-      if (g->traj_group[gmem[i]] != g->traj_group[gmem[i - 1]]) goff.push_back(i);
-    goff.push_back(B);
+    group_members(g->traj_group, B, &goff, &gmem);
     n_groups = static_cast<int>(goff.size()) - 1;
   }
 

@@ -90,6 +90,30 @@ def test_malformed_graphs_are_rejected_before_any_launch(lib, kw, code, needle):
     assert needle in lib.umas_last_error().decode()
 
 
+# one bad entry among many: the array is checked as a whole first, the message still names the entry
+@pytest.mark.parametrize("name,at,value,needle", [
+    ("turn_role", 171, 2, "turn_role[171]=2"), ("turn_role", 0, -1, "turn_role[0]=-1"), ("turn_tok_off", 130, 900, "turn_tok_off decreases at 130"),
+    ("traj_turn_off", 7, 99, "traj_turn_off decreases at 7"), ("turn_pred_off", 64, 1, "turn_pred_off decreases at 63"),
+    ("turn_pred", 101, 104, "predecessor 104 of turn 103"), ("turn_pred", 100, 99, "predecessor 99 of turn 102"),
+    ("traj_group", 39, -5, "traj_group[39]"), ("traj_group", 39, 2 ** 31 - 1, "16-byte aligned"), ("turn_pred", 0, 0, "16-byte aligned")])
+def test_the_malformed_entry_is_named(lib, name, at, value, needle):
+    from paper_2605_26646_amd import binding as b
+    n_traj, turns = 40, 5                # every turn but a trajectory's first two has the one before as its predecessor
+    first = np.arange(200) % turns < 2
+    kw = dict(traj_turn_off=np.arange(n_traj + 1) * turns, turn_role=np.arange(200) % 2, turn_tok_off=np.arange(201) * 3,
+              turn_pred_off=np.concatenate([[0], np.cumsum(~first)]), turn_pred=np.nonzero(~first)[0] - 1, traj_group=np.arange(n_traj) // 4)
+    kw = {k: np.array(v) for k, v in kw.items()}
+    if name == "turn_pred":
+        at = int(kw["turn_pred_off"][at + 2]) if at else 0
+        value = value if value else int(kw["turn_pred"][0])
+    kw[name][at] = value
+    g, keep = graph(**kw)
+    r = b._Rewards(None, None, None, None, None, None, 0, 1e-6)
+    s = b._Streams(*([1] * 16))
+    assert lib.umas_assign_token_rewards(C.addressof(g), C.addressof(r), 1, C.addressof(s), 256, 1 << 20, None) == -1
+    assert needle in lib.umas_last_error().decode()
+
+
 def test_bad_scalar_arguments(lib):
     assert lib.umas_policy_logprobs(256, 256, 7, 4, 8, 8, 256, None, 4, 256, 256, None, 256, 1 << 20, None) == -3
     assert lib.umas_policy_logprobs(256, 256, 1, 4, 12, 8, 256, None, 4, 256, 256, None, 256, 1 << 20, None) == -2

@@ -219,3 +219,23 @@ def test_float32_products(n, d, V, entropy_coef):
         scale_h = np.abs(dH_o).max() + 1e-12
         assert np.abs(dH_g - dH_o).max() <= 1e-5 * scale_h, (n, d, V)
         assert np.abs(dW_g - dW0 - dW_o).max() <= 1e-5 * (np.abs(dW_o).max() + 1e-12) + 2.0 ** -23 * (np.abs(dW0) + np.abs(dW_o)).max(), (n, d, V)
+
+
+def test_group_numbers_in_order_counted_and_sorted_give_the_same_streams():
+    rng = np.random.default_rng(11)
+    n_traj, n_roles = 513, 3
+    same = rng.permutation(np.arange(n_traj) // 4)                     # the partition; its members lie anywhere
+    order = np.argsort(same, kind="stable")
+    reward = rng.random(n_traj).astype(np.float32)
+    kw = dict(n_roles=n_roles, n_models=1, role_to_model=np.zeros(n_roles, np.int32), traj_turn_off=np.arange(n_traj + 1) * n_roles,
+              turn_role=np.tile(np.arange(n_roles), n_traj), turn_tok_off=np.arange(n_traj * n_roles + 1) * 5,
+              tok_mask_global=torch.ones(n_traj * n_roles * 5, dtype=torch.uint8, device="cuda"))
+
+    def scalars(group, r):
+        return umas.umas_assign_token_rewards(traj_group=group.astype(np.int32), traj_reward=r, **kw).turn_scalar.cpu().numpy().reshape(n_traj, n_roles)
+
+    counted = scalars(same, reward)
+    assert np.abs(counted).max() > 0.5
+    assert np.array_equal(counted, scalars(same * 10 ** 7 + 3, reward))                    # sorted
+    assert np.array_equal(counted[order], scalars(same[order], reward[order]))             # in order
+    assert np.array_equal(counted, scalars(same.max() - same, reward))
