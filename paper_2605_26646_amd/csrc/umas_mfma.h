@@ -296,7 +296,6 @@ struct KMajor {                 // an operand tile stored K-major
   const char* base;             // byte address of (k-row 0, first entry of the tile)
   int64_t ld_bytes;             // bytes between consecutive k-rows
   int64_t hi_bytes;             // added once more per 256 k-rows (an operand stored in blocks of 256 rows), else 0
-  const int32_t* rowmap;        // with BMAP: k-row k lives in row rowmap[k] of the matrix (ld_bytes apart, from base)
   int k_rows;                   // k-rows that exist; later ones read the last one (the other operand is zero there)
   int n_units;                  // 16-byte units of a k-row that exist from base on (<= 32); later ones read the last one
 };
@@ -306,7 +305,7 @@ struct KContig {                // an operand tile stored K-contiguous: per-slot
   uint32_t hi_bytes;            // added once more per 256 k (an operand stored in blocks of 256 columns), else 0
 };
 
-template <class C, bool ATR, bool BTR, bool BMAP = false, int AHEAD = (BMAP ? 0 : 1)>
+template <class C, bool ATR, bool BTR, int AHEAD>
 __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMajor& ka, const KContig& cb, const KMajor& kb,
                                                     int K, uint16_t* lds, floatx4 (&acc)[C::MI][C::NI]) {
   using R = Ring2Cfg<C>;
@@ -320,9 +319,8 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
   const int nsub = K / R::BK;
   // LDS: five stages of 32 KB.  One operand (AHEAD = 1: A, AHEAD = 2: B) has three of them and is loaded two steps
   // ahead, the other two, one step ahead; the callers give the third stage to the operand that comes from farther
-  // away.  With a row map on B (loads of two kinds in flight, which do not return in one order) AHEAD is 0 and both
-  // stay one step ahead.
-  static_assert(AHEAD >= 0 && AHEAD <= 2 && !(BMAP && AHEAD != 0), "which operand is loaded two steps ahead");
+  // away.
+  static_assert(AHEAD == 1 || AHEAD == 2, "which operand is loaded two steps ahead");
   constexpr int kAStage = C::BM * R::ROWB, kBStage = C::BN * R::ROWB;
   constexpr int kABase = AHEAD == 2 ? 3 * kBStage : 0, kBBase = AHEAD == 2 ? 0 : 3 * kAStage;
   static_assert(3 * kAStage + 2 * kBStage <= MixedLdsBytes<C>::value && kAStage == kBStage, "LDS of the mixed loop");
@@ -331,28 +329,15 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
   // l & 31 of row k = 16 p + 2 wave + (l >> 5) and fetches unit slot ^ 4 (k & 3) ^ 2 ((k >> 3) & 1)
   const int tr_krow = 2 * wave + (lane >> 5);        // + 16 p
   const int tr_slot_unit = (lane & 31) ^ (4 * (tr_krow & 3)) ^ (2 * ((tr_krow >> 3) & 1));
-  int32_t rows_a[4] = {0, 0, 0, 0}, rows_b[4] = {0, 0, 0, 0};   // rows of the step after next when a rowmap is set
-  auto map_rows = [&](const KMajor& k, int sub, int32_t (&rows)[4]) {
-#pragma unroll
-    for (int p = 0; p < 4; ++p) rows[p] = k.rowmap[min(sub * R::BK + 16 * p + tr_krow, k.k_rows - 1)];
-  };
-  auto gload_kmajor = [&](const KMajor& k, const int32_t (&rows)[4], int sub, char* region, auto mapped) {
+  auto gload_kmajor = [&](const KMajor& k, int sub, char* region) {
     const uint32_t ubytes = static_cast<uint32_t>(min(tr_slot_unit, k.n_units - 1)) * 16u;
-    if constexpr (decltype(mapped)::value) {
-      const __amdgpu_buffer_rsrc_t r = make_rsrc(k.base);
+    const int k0 = min(sub * R::BK, ((k.k_rows - 1) / R::BK) * R::BK);          // first k-row of the (clamped) step
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(k.base + static_cast<int64_t>(k0) * k.ld_bytes + (k0 >> 8) * k.hi_bytes);
 #pragma unroll
-      for (int p = 0; p < 4; ++p)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, reinterpret_cast<uint32_t*>(region + (16 * p + 2 * wave) * 512), 16,
-                                                 static_cast<uint32_t>(rows[p]) * static_cast<uint32_t>(k.ld_bytes) + ubytes, 0, 0, 0);
-    } else {
-      const int k0 = min(sub * R::BK, ((k.k_rows - 1) / R::BK) * R::BK);          // first k-row of the (clamped) step
-      const __amdgpu_buffer_rsrc_t r = make_rsrc(k.base + static_cast<int64_t>(k0) * k.ld_bytes + (k0 >> 8) * k.hi_bytes);
-#pragma unroll
-      for (int p = 0; p < 4; ++p)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, reinterpret_cast<uint32_t*>(region + (16 * p + 2 * wave) * 512), 16,
-                                                 static_cast<uint32_t>(min(16 * p + tr_krow, k.k_rows - 1 - k0)) * static_cast<uint32_t>(k.ld_bytes) + ubytes,
-                                                 0, 0, 0);
-    }
+    for (int p = 0; p < 4; ++p)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, reinterpret_cast<uint32_t*>(region + (16 * p + 2 * wave) * 512), 16,
+                                               static_cast<uint32_t>(min(16 * p + tr_krow, k.k_rows - 1 - k0)) * static_cast<uint32_t>(k.ld_bytes) + ubytes,
+                                               0, 0, 0);
   };
   auto gload_kcontig = [&](const KContig& c, int sub, char* region) {
     const int kbytes = sub * R::BK * 2 + (sub >> 2) * static_cast<int>(c.hi_bytes);
@@ -363,11 +348,11 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
   };
   auto gload_a = [&](int sub, int ia) {
     char* sa = base + kABase + ia * kAStage;
-    if (ATR) gload_kmajor(ka, rows_a, sub, sa, std::false_type{}); else gload_kcontig(ca, sub, sa);
+    if (ATR) gload_kmajor(ka, sub, sa); else gload_kcontig(ca, sub, sa);
   };
   auto gload_b = [&](int sub, int ib) {
     char* sb = base + kBBase + ib * kBStage;
-    if (BTR) gload_kmajor(kb, rows_b, sub, sb, std::integral_constant<bool, BMAP>{}); else gload_kcontig(cb, sub, sb);
+    if (BTR) gload_kmajor(kb, sub, sb); else gload_kcontig(cb, sub, sb);
   };
 
   // fragment addresses (K-contiguous operands as in mfma_mainloop_ring2)
@@ -462,12 +447,10 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
   auto clamp_sub = [&](int sub) { return sub < nsub ? sub : nsub - 1; };   // past the end the last step is loaded again (nobody reads it)
-  if (BTR && BMAP) map_rows(kb, 0, rows_b);
   gload_a(0, 0);
   gload_b(0, 0);
   if (AHEAD == 1) gload_a(clamp_sub(1), 1);
   if (AHEAD == 2) gload_b(clamp_sub(1), 1);
-  if (BTR && BMAP) map_rows(kb, clamp_sub(1), rows_b);
   __builtin_amdgcn_s_waitcnt(0x0070);
   __builtin_amdgcn_s_barrier();
   fload_b(0, 0, I0{});
@@ -482,14 +465,10 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
     if (AHEAD == 1) {                                // the loads that may stay outstanding go out last
       gload_b(clamp_sub(j + 1), ib1);
       gload_a(clamp_sub(j + 2), next3(ia1));
-    } else if (AHEAD == 2) {
-      gload_a(clamp_sub(j + 1), ia1);
-      gload_b(clamp_sub(j + 2), next3(ib1));
     } else {
       gload_a(clamp_sub(j + 1), ia1);
-      gload_b(clamp_sub(j + 1), ib1);
+      gload_b(clamp_sub(j + 2), next3(ib1));
     }
-    if (BTR && BMAP) map_rows(kb, clamp_sub(j + 2), rows_b);
     fload_a(1, ia, I0{}, I1{});
     mfmas(0, 0, 0);
     interleave(kDsA, 8);
@@ -508,8 +487,7 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
     __builtin_amdgcn_sched_barrier(0);
     // own LDS reads of this step done and own loads for the next step landed: with three A stages the four
     // youngest loads (A of the step after next) may still be on their way; then everybody's
-    if (AHEAD != 0) __builtin_amdgcn_s_waitcnt(0x0074);   // vmcnt(4), lgkmcnt(0)
-    else __builtin_amdgcn_s_waitcnt(0x0070);         // vmcnt(0), lgkmcnt(0)
+    __builtin_amdgcn_s_waitcnt(0x0074);              // vmcnt(4), lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     tr_wait_a(1);

@@ -942,21 +942,27 @@ k_dz_flagged(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int
   }
 }
 
-// The taken token's entry of every row of the chunk's blocked dZ is cleared: that column goes through g_c in float32
-// (see k_ppo_rows).  One thread per row.
+// What the gradient products need besides dZ: the taken token's entry of every row is cleared (that column goes through
+// g_c in float32, see k_ppo_rows), and the row of H goes to the operand that dW reads, in the column blocks of k_keep_rows.
+// One wavefront per row.  (dW reading the rows through the selection: two kinds of loads in flight, whose waits have to be
+// for all of them, 16 100 rows of 2048: both products 16.3 ms, with the copy, 25 us, 14.9.)
 __global__ void __launch_bounds__(256)
-k_zero_label(uint16_t* __restrict__ dZ, int64_t tiles_v, int V, const int32_t* __restrict__ rowsel, int64_t c0, int64_t rows,
-             const int32_t* __restrict__ ids) {
-  const int64_t m = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+k_dz_rows(const uint16_t* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel, int64_t c0, int64_t rows,
+          const int32_t* __restrict__ ids, uint16_t* __restrict__ dZ, int64_t tiles_v, uint16_t* __restrict__ Hs, int64_t mcp) {
+  const int lane = threadIdx.x & 63;
+  const int64_t m = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave;
   if (m >= rows) return;
-  const int y = ids[rowsel ? rowsel[c0 + m] : c0 + m];
-  if (y >= 0 && y < V) dZ[blk_offset(m >> 8, y >> 8, tiles_v) + (m & 255) * 256 + (y & 255)] = 0;
+  const int64_t row = rowsel ? rowsel[c0 + m] : c0 + m;
+  const int y = ids[row];
+  if (lane == 0 && y >= 0 && y < V) dZ[blk_offset(m >> 8, y >> 8, tiles_v) + (m & 255) * 256 + (y & 255)] = 0;
+  const uint4* h = reinterpret_cast<const uint4*>(H + row * d);
+  for (int k = lane; k < d / 8; k += kWave) reinterpret_cast<uint4*>(Hs + (static_cast<int64_t>(k >> 5) * mcp + m) * 256)[k & 31] = h[k];
 }
 
 // ------------------------------------------------------------------ bf16: the two gradient products
 // dH = dZ W: A = dZ [mcp, Vp] (or the kept numerators E) is K-contiguous (K = vocabulary), B = W [V, d] is K-major and is read as it lies.
 //   dH[rowsel[c0 + m], j] = bf16(sc[m] C[m, j] + g[m] W[y[m], j]) for m < mc (sc: the keeping pass's row factor, else 1)
-// dW = dZ^T H: K = rows of the chunk; A = dZ [mcp, Vp] and B = the selected rows of H [*, d] are both K-major.
+// dW = dZ^T H: K = rows of the chunk; A = dZ [mcp, Vp] and B = the selected rows of H, copied (and scaled), are both K-major.
 //   dW[v, j] (+)= C[v, j]
 // (kernel templates whose bodies use buffer resources do not get their host stubs emitted: plain kernels)
 template <class C>
@@ -1039,13 +1045,12 @@ __device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, in
   kb.base = reinterpret_cast<const char*>(W + static_cast<int64_t>(voc_blk) * 256 * d + n0);
   kb.ld_bytes = static_cast<int64_t>(d) * 2;
   kb.hi_bytes = 0;
-  kb.rowmap = nullptr;
   kb.k_rows = V - voc_blk * 256;                                     // dz is zero for vocabulary ids past V
   kb.n_units = min(32, (d - n0) / 8);
   floatx4 acc[C::MI][C::NI];
   zero_acc<C>(acc);
   // the third LDS stage goes to W: every group of row tiles streams all of it (twice the bytes of the [rows, V] operand)
-  mfma_mainloop_mixed<C, false, true, false, 2>(ca, KMajor{}, KContig{}, kb, k_len, lds, acc);
+  mfma_mainloop_mixed<C, false, true, 2>(ca, KMajor{}, KContig{}, kb, k_len, lds, acc);
   if (sl.n > 1) {
     float* out = sl.part + ((static_cast<int64_t>(slice) * tiles_r + tile_m) * tiles_d + tile_n) * (C::BM * C::BN);
     store_acc_f32(acc, lds, [&](int r, int c) { return out + r * C::BN + c; }, 0);
@@ -1070,12 +1075,11 @@ __device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, in
       }
   }
 }
-// Hx: the rows of H that go with the rows of dZ: H itself (through rowsel, or from row c0 on), or, with hx_blocked, the
-// scaled compact copy, which lies in column blocks [d / 256][mcp][256] so that a tile's k-rows are one run of memory
+// Hs: the rows of H that go with the rows of dZ (scaled by the keeping pass), in column blocks [d / 256][mcp][256] so that a
+// tile's k-rows are one run of memory
 // k_len: rows of the packed [rows, V] operand (a multiple of 256, 0 when no block is live); rows: those that exist
 __device__ __forceinline__ void dw_tile(int tile_m, int tile_n, const uint16_t* __restrict__ dZ, int64_t mcp, int64_t Vp,
-                                        const uint16_t* __restrict__ Hx, int hx_blocked, int d, int V,
-                                        const int32_t* __restrict__ rowmap, int k_len, int rows, float* __restrict__ dW,
+                                        const uint16_t* __restrict__ Hs, int d, int V, int k_len, int rows, float* __restrict__ dW,
                                         int accumulate, uint16_t* lds) {
   using C = Cfg;
   const int64_t m0 = static_cast<int64_t>(tile_m) * C::BM;
@@ -1084,22 +1088,17 @@ __device__ __forceinline__ void dw_tile(int tile_m, int tile_n, const uint16_t* 
   ka.base = reinterpret_cast<const char*>(dZ + blk_offset(0, tile_m, Vp >> 8));
   ka.ld_bytes = 512;
   ka.hi_bytes = (Vp >> 8) * kBlkElems * 2 - 256 * 512;               // from the last row of a block to the block below
-  ka.rowmap = nullptr;
   ka.k_rows = k_len;
   ka.n_units = 32;
   KMajor kb;                                                         // rows of H: k = row of the chunk, entries = hidden columns
-  kb.base = reinterpret_cast<const char*>(hx_blocked ? Hx + static_cast<int64_t>(tile_n) * mcp * 256 : Hx + n0);
-  kb.ld_bytes = hx_blocked ? 512 : static_cast<int64_t>(d) * 2;
+  kb.base = reinterpret_cast<const char*>(Hs + static_cast<int64_t>(tile_n) * mcp * 256);
+  kb.ld_bytes = 512;
   kb.hi_bytes = 0;
-  kb.rowmap = rowmap;
   kb.k_rows = rows;                                                  // dz is zero for rows past the chunk
   kb.n_units = min(32, (d - n0) / 8);
   floatx4 acc[C::MI][C::NI];
   zero_acc<C>(acc);
-  if (k_len > 0) {
-    if (rowmap) mfma_mainloop_mixed<C, true, true, true>(KContig{}, ka, KContig{}, kb, k_len, lds, acc);
-    else mfma_mainloop_mixed<C, true, true, false>(KContig{}, ka, KContig{}, kb, k_len, lds, acc);
-  }
+  if (k_len > 0) mfma_mainloop_mixed<C, true, true, 1>(KContig{}, ka, KContig{}, kb, k_len, lds, acc);
   const int64_t v_end = V;
   store_acc_f32(acc, lds, [&](int r, int c) -> float* {
     return m0 + r < v_end && n0 + c < d ? dW + (m0 + r) * d + n0 + c : nullptr;     // d is a multiple of 8: four columns are all inside or all outside
@@ -1118,7 +1117,7 @@ __device__ __forceinline__ void dw_tile(int tile_m, int tile_n, const uint16_t* 
 // 1098 -> 930, 2000 rows of 3584 3.93 -> 3.52 ms, 39 000 rows of 2048 37.5 -> 36.5 ms.
 __global__ void __launch_bounds__(Cfg::T)
 k_gemm_dh_dw(const uint16_t* __restrict__ dZ, int64_t Vp, int64_t mcp, const uint16_t* __restrict__ W,
-             const uint16_t* __restrict__ Hx, int hx_blocked, const int32_t* __restrict__ h_rowmap, int d, int V, int tiles_v,
+             const uint16_t* __restrict__ Hs, int d, int V, int tiles_v,
              int tiles_d, DhSlices sl, int tiles_r, LiveInfo* __restrict__ info, const int32_t* __restrict__ blk_orig,
              uint16_t* __restrict__ dH, float* __restrict__ dW, int accumulate, const int32_t* __restrict__ rowsel,
              int64_t c0, int64_t rows, const int32_t* __restrict__ ids, const float* __restrict__ g_c,
@@ -1171,7 +1170,7 @@ k_gemm_dh_dw(const uint16_t* __restrict__ dZ, int64_t Vp, int64_t mcp, const uin
       dh_tile(tile_m, blk_orig[(c0 >> 8) + tile_m], tile_n, slice, sl, tiles_r, tiles_d, dZ, Vp, W, d, V, dH, rowsel, c0, rows, ids, g_c, sc, lds);
     } else {
       tile_of_groups<kGM, kGN>(first_dw + seq - n_dh, tiles_v, tiles_d, &tile_m, &tile_n);
-      dw_tile(tile_m, tile_n, dZ, mcp, Vp, Hx, hx_blocked, d, V, h_rowmap, n_live * 256, k_rows, dW, accumulate, lds);
+      dw_tile(tile_m, tile_n, dZ, mcp, Vp, Hs, d, V, n_live * 256, k_rows, dW, accumulate, lds);
     }
   }
 }
@@ -1725,12 +1724,11 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     const DhPlan p = plan_dh(tiles_r, tiles_d, tiles_v, aligned ? (behind > front ? behind : front) : 0);
     *sl = DhSlices{p.slices, p.voc_blks, behind > front ? reinterpret_cast<float*>(w.chunk + used) : reinterpret_cast<float*>(w.score.partial)};
   };
-  auto gradients = [&](int64_t c0, int64_t rows, const DhSlices& sl, const uint16_t* op, const uint16_t* Hx, int hx_blocked,
-                       const int32_t* h_rowmap, const float* sc) -> umas_status {
+  auto gradients = [&](int64_t c0, int64_t rows, const DhSlices& sl, const uint16_t* op, const uint16_t* Hs, const float* sc) -> umas_status {
     const int64_t mcp = round_up(rows, 256);
     const int tiles_r = static_cast<int>(mcp / 256), tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
     const unsigned grid = static_cast<unsigned>(round_up(device_cus(), 8));      // every XCD's sequence needs somebody
-    hipLaunchKernelGGL(k_gemm_dh_dw, dim3(grid), dim3(Cfg::T), 0, st, op, Vp, mcp, Wb, Hx, hx_blocked, h_rowmap, d, V, tiles_v,
+    hipLaunchKernelGGL(k_gemm_dh_dw, dim3(grid), dim3(Cfg::T), 0, st, op, Vp, mcp, Wb, Hs, d, V, tiles_v,
                        tiles_d, sl, tiles_r, w.live, w.blk_orig, static_cast<uint16_t*>(dH), dW, (accumulate_dW || c0 > 0) ? 1 : 0,
                        rowsel, c0, rows, ids, w.g_c, sc);
     UMAS_LAUNCHED("k_gemm_dh_dw");
@@ -1789,7 +1787,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       hipLaunchKernelGGL(k_keep_rows, dim3(cdiv(rows, 4)), dim3(256), 0, st, Hb, d, V, rowsel, c0, rows, ids, E,
                          static_cast<int64_t>(tiles_v), w.score.lse_c, w.a_c, w.cref, w.flags, w.blk_cidx, w.sc, Hs, mcp);
       UMAS_LAUNCHED("k_keep_rows");
-      s = gradients(c0, rows, sl, E, Hs, 1, nullptr, w.sc);
+      s = gradients(c0, rows, sl, E, Hs, w.sc);
       if (s != UMAS_OK) return s;
     }
   }
@@ -1834,16 +1832,17 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     hipLaunchKernelGGL(k_dz_tiles, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, kTilesPerWg)), dim3(Cfg::T), 0, st, Wb, Hb, d, V, rowsel,
                        c0, rows, w.score.lse_c, w.a_c, w.kz_c, tiles_v, tiles_r, dZ, Vp);
     UMAS_LAUNCHED("k_dz_tiles");
-    hipLaunchKernelGGL(k_zero_label, dim3(cdiv(rows, 256)), dim3(256), 0, st, dZ, static_cast<int64_t>(tiles_v), V, rowsel, c0, rows,
-                       ids);
-    UMAS_LAUNCHED("k_zero_label");
+    uint16_t* Hs = reinterpret_cast<uint16_t*>(w.chunk + align_up(static_cast<size_t>(mcp) * Vp * 2));
+    hipLaunchKernelGGL(k_dz_rows, dim3(cdiv(rows, 4)), dim3(256), 0, st, Hb, d, V, rowsel, c0, rows, ids, dZ, static_cast<int64_t>(tiles_v), Hs,
+                       mcp);
+    UMAS_LAUNCHED("k_dz_rows");
     // with an entropy bonus every row has a gradient: all blocks are live
     DhSlices sl;
     dh_plan(rows, &sl);
     hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, static_cast<int>(c0 >> 8), tiles_r, rows, 1, tiles_v, tiles_d, Vp, sl.n,
                        w.blk_live, w.blk_cidx, w.blk_orig, w.live);
     UMAS_LAUNCHED("k_live_scan");
-    s = gradients(c0, rows, sl, dZ, rowsel ? Hb : Hb + c0 * d, 0, rowsel ? rowsel + c0 : nullptr, nullptr);
+    s = gradients(c0, rows, sl, dZ, Hs, nullptr);
     if (s != UMAS_OK) return s;
   }
   hipLaunchKernelGGL(k_dw_onehot, onehot_grid(n_sel), dim3(256), 0, st, Hb, d, rowsel, n_sel, ids, w.g_c, dW);
