@@ -15,7 +15,7 @@
 // from its incoming state.
 //
 // One pass over memory (17 bytes per token).  Segments are independent, so the stream is cut into ranges of about
-// `chunk` tokens at segment boundaries; a workgroup walks the tiles of one range from right to left and carries the
+// `chunk` tokens (chunk_tokens) at segment boundaries; a workgroup walks the tiles of one range from right to left and carries the
 // state from tile to tile itself, the loads of the next tile in flight.  Ranges of ordinary segments need nothing
 // from each other: one workgroup per range, in any order (k_gae_scan).
 // Only a segment longer than kLongSegment tokens is cut inside.  A range whose right end lies inside such a segment
@@ -35,8 +35,14 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kIpt = 4;                          // tokens per thread: one 16-byte load per array, no transposition
 constexpr int kTile = kThreads * kIpt;           // tokens per tile
-constexpr int kChunkTiles = 8;                   // nominal tiles per range
-constexpr int64_t kChunk = static_cast<int64_t>(kChunkTiles) * kTile;
+constexpr int kChunkTiles = 8;                   // nominal tiles per range at most
+// Nominal tokens per range: a range's tiles are done one after the other, so a stream that makes fewer ranges than there are
+// compute units is cut finer (49 152 tokens: 6 ranges of eight tiles 19 us, 48 of one 7 us; the call, waited for, 40 -> 28 us,
+// 400 000 tokens 43 -> 33, 225 000 in segments that are cut 91 -> 60; 25 million 62 us both ways).
+inline int64_t chunk_tokens(int64_t n_tokens) {
+  const int64_t tiles = n_tokens / (static_cast<int64_t>(kTile) * 512);
+  return (tiles < 1 ? 1 : tiles > kChunkTiles ? kChunkTiles : tiles) * kTile;
+}
 constexpr int64_t kLongSegment = 16 * kTile;     // a segment end farther away than this does not move a range's edge
 constexpr int kAhead = 1;                        // tiles whose loads are in flight beyond the one in work
 
@@ -89,6 +95,7 @@ constexpr unsigned long long kReady = 1ull << 32;  // mark in the upper half of 
 
 struct ScanParams {
   int64_t n_tokens;
+  int64_t chunk;                    // nominal tokens per range
   uint32_t n_ranges;
   Range* ranges;                    // [n_ranges], written by k_gae_scan
   const int64_t* seg_off;           // [n_seg_entries + 1] ascending segment offsets, from 0 to n_tokens
@@ -354,7 +361,7 @@ k_gae_scan(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
   if (tid < 2 * kWave) {
     const int which = tid / kWave;                   // wavefront 0: left edge, wavefront 1: right edge
     int cut;
-    const int64_t edge = range_edge(P.seg_off, P.n_seg_entries, P.n_tokens, (i + which) * kChunk, &cut);
+    const int64_t edge = range_edge(P.seg_off, P.n_seg_entries, P.n_tokens, (i + which) * P.chunk, &cut);
     if ((tid & (kWave - 1)) == 0) { s_edge[which] = edge; s_cut[which] = cut; }
   }
   __syncthreads();
@@ -411,7 +418,7 @@ k_gae_scan_cut(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
   }
 }
 
-inline int64_t scan_ranges(int64_t n_tokens) { return (n_tokens + kChunk - 1) / kChunk; }
+inline int64_t scan_ranges(int64_t n_tokens) { return (n_tokens + chunk_tokens(n_tokens) - 1) / chunk_tokens(n_tokens); }
 
 }  // namespace
 }  // namespace umas
@@ -450,6 +457,7 @@ extern "C" umas_status umas_advantages(const umas_streams* s, int64_t n_tokens, 
   const int64_t n_ranges = scan_ranges(n_tokens);
   ScanParams P;
   P.n_tokens = n_tokens;
+  P.chunk = chunk_tokens(n_tokens);
   P.n_ranges = static_cast<uint32_t>(n_ranges);
   Range* ranges = static_cast<Range*>(workspace);
   P.ranges = ranges;
@@ -470,6 +478,7 @@ extern "C" umas_status umas_advantages(const umas_streams* s, int64_t n_tokens, 
       value ? (decay ? k_gae_scan<true, true> : k_gae_scan<true, false>) : (decay ? k_gae_scan<false, true> : k_gae_scan<false, false>);
   hipLaunchKernelGGL(kernel, dim3(P.n_ranges), dim3(kThreads), 0, st, P, adv, ret);
   UMAS_LAUNCHED("k_gae_scan");
+  if (n_tokens - P.chunk < kLongSegment) return UMAS_OK;   // no segment reaches far enough past a range's edge to be cut
   // The ranges cut inside long segments: persistent workgroups that wait for each other's maps.  At most one workgroup
   // per compute unit, far fewer than the device holds at once: whatever else is running, all of them get to run
   // together, so no workgroup waits for one that cannot start.

@@ -239,3 +239,45 @@ def test_group_numbers_in_order_counted_and_sorted_give_the_same_streams():
     assert np.array_equal(counted, scalars(same * 10 ** 7 + 3, reward))                    # sorted
     assert np.array_equal(counted[order], scalars(same[order], reward[order]))             # in order
     assert np.array_equal(counted, scalars(same.max() - same, reward))
+
+
+# one segment as long as the stream: a single range, ranges of one tile that cannot be cut and the first that can, and the
+# sizes at which ranges grow from one tile to two
+@pytest.mark.parametrize("n", [1, 1023, 1025, 17407, 17408, 40001, 2 * 512 * 1024 - 1, 2 * 512 * 1024 + 5])
+@pytest.mark.parametrize("with_value", [False, True])
+def test_scan_of_one_segment(n, with_value):
+    from scipy.signal import lfilter
+    rng = np.random.default_rng(n)
+    gamma, lam = 0.99, 0.95
+    reward = rng.normal(size=n).astype(np.float32)
+    value = rng.normal(size=n).astype(np.float32) if with_value else None
+    st = umas.umas_assign_token_rewards(n_roles=1, n_models=1, role_to_model=[0], traj_turn_off=[0, 1], turn_role=[0], turn_tok_off=[0, n],
+                                        tok_mask_global=torch.ones(n, dtype=torch.uint8, device="cuda"))
+    st.tok_reward.copy_(P.to_dev(reward))
+    adv, ret = umas.umas_advantages(st, None if value is None else P.to_dev(value), gamma, lam)
+    v = np.zeros(n) if value is None else value.astype(np.float64)
+    delta = reward.astype(np.float64) + gamma * np.append(v[1:], 0.0) - v
+    want = lfilter([1.0], [1.0, -gamma * lam], delta[::-1])[::-1]
+    # a float32 recurrence that forgets with 0.94 a token: some 17 terms of |delta| <= 10 carry 2^-24 each, folds a few times as many
+    assert np.abs(adv.cpu().numpy() - want).max() <= 2e-5
+    assert np.abs(ret.cpu().numpy() - want - v).max() <= 2e-5
+
+
+# block sums (1024 tokens each) times groups at, below and above the number from which their statistics take a launch of
+# their own (256), and a last block of one token
+@pytest.mark.parametrize("n,n_roles", [(1, 3), (1025, 3), (85 * 1024, 3), (86 * 1024, 3), (255 * 1024 + 1, 1), (257 * 1024, 1), (4 * 1024, 64), (5 * 1024, 64)])
+def test_whitening_statistics(n, n_roles):
+    rng = np.random.default_rng(n)
+    adv = (3 + rng.normal(size=n)).astype(np.float32)
+    mask = (rng.random(n) < 0.8).astype(np.uint8)
+    role = rng.integers(0, n_roles, size=n).astype(np.int32)
+    out = umas.umas_whiten_advantages(P.to_dev(adv), P.to_dev(mask), P.to_dev(role), np.array([0, n]), n_roles, umas.WHITEN_MODEL_ROLE).cpu().numpy()
+    want = np.zeros(n)
+    for g in range(n_roles):
+        at = (mask == 1) & (role == g)
+        if at.any():
+            x = adv[at].astype(np.float64)
+            want[at] = (x - x.mean()) / np.sqrt(x.var() + 1e-8)
+    # a lane of one or two tokens of the same value has a deviation of 0; the others' sums are float64 from float32 parts
+    big = np.abs(want) < 1e3
+    assert np.abs(out - want)[big].max() <= 1e-4
