@@ -1214,9 +1214,12 @@ k_dh_reduce(DhSlices sl, int tiles_r, int tiles_d, const uint16_t* __restrict__ 
 // every token in the group is its leader; a wavefront sums the leader and its followers in registers, 2048 columns at
 // a time (16-byte loads, a lane owning eight consecutive columns of each of four pieces), turns every piece through
 // its corner of LDS so that consecutive lanes hold consecutive columns, and issues one atomic per element of the sum.
-// A wavefront needs about a microsecond per token, so with few groups each is worked on by several workgroups.
+// A wavefront needs about a microsecond per token, so with few groups each is worked on by several workgroups; and the
+// most frequent token's rows are a chain of loads, so they come four at a time (203 rows of 3584 37 -> 27 us, 725 of 2048 27 -> 20).
 constexpr int kOneHotRows = 128;
 constexpr int kOneHotPieces = 4;                    // pieces of 512 columns a wavefront holds at a time
+constexpr int kOneHotAhead = 4;                     // rows a wavefront loads together
+static_assert(kOneHotRows == 2 * kWave, "the rows of a token are two ballots");
 __global__ void __launch_bounds__(256)
 k_dw_onehot(const uint16_t* __restrict__ H, int d, const int32_t* __restrict__ rowsel, int64_t n_sel,
             const int32_t* __restrict__ ids, const float* __restrict__ g_c, float* __restrict__ dW) {
@@ -1273,28 +1276,39 @@ k_dw_onehot(const uint16_t* __restrict__ H, int d, const int32_t* __restrict__ r
       for (int q = 0; q < kOneHotPieces; ++q)
 #pragma unroll
         for (int k = 0; k < 8; ++k) acc[q][k] = 0.f;
+      unsigned long long lo = same[0], hi = same[1];
+      while (lo | hi) {                               // kOneHotAhead rows are in flight together
+        uint4 hv[kOneHotAhead][kOneHotPieces];
+        float g[kOneHotAhead];
 #pragma unroll
-      for (int k = 0; k < kOneHotRows / kWave; ++k) {
-        for (unsigned long long m = same[k]; m; m &= m - 1) {
-          const int u = kWave * k + __ffsll(static_cast<long long>(m)) - 1;
-          const uint16_t* h = H + s_row[u] * d;
-          const float g = s_g[u];
-          uint4 hv[kOneHotPieces];
+        for (int b = 0; b < kOneHotAhead; ++b) {
+          g[b] = 0.f;
+          if (!(lo | hi)) {
 #pragma unroll
-          for (int q = 0; q < kOneHotPieces; ++q) {   // the row's pieces are in flight together
-            const int c = c0 + (q * kWave + lane) * 8;
-            hv[q] = c < d ? *reinterpret_cast<const uint4*>(h + c) : make_uint4(0u, 0u, 0u, 0u);
+            for (int q = 0; q < kOneHotPieces; ++q) hv[b][q] = make_uint4(0u, 0u, 0u, 0u);
+            continue;
           }
+          const int u = lo ? __ffsll(static_cast<long long>(lo)) - 1 : kWave + __ffsll(static_cast<long long>(hi)) - 1;
+          if (lo) lo &= lo - 1; else hi &= hi - 1;
+          const uint16_t* h = H + s_row[u] * d;
+          g[b] = s_g[u];
 #pragma unroll
           for (int q = 0; q < kOneHotPieces; ++q) {
-            const uint32_t w4[4] = {hv[q].x, hv[q].y, hv[q].z, hv[q].w};
-#pragma unroll
-            for (int k2 = 0; k2 < 4; ++k2) {
-              acc[q][2 * k2] += g * bf2f(static_cast<uint16_t>(w4[k2] & 0xFFFFu));
-              acc[q][2 * k2 + 1] += g * bf2f(static_cast<uint16_t>(w4[k2] >> 16));
-            }
+            const int c = c0 + (q * kWave + lane) * 8;
+            hv[b][q] = c < d ? *reinterpret_cast<const uint4*>(h + c) : make_uint4(0u, 0u, 0u, 0u);
           }
         }
+#pragma unroll
+        for (int b = 0; b < kOneHotAhead; ++b)
+#pragma unroll
+          for (int q = 0; q < kOneHotPieces; ++q) {
+            const uint32_t w4[4] = {hv[b][q].x, hv[b][q].y, hv[b][q].z, hv[b][q].w};
+#pragma unroll
+            for (int k2 = 0; k2 < 4; ++k2) {
+              acc[q][2 * k2] += g[b] * bf2f(static_cast<uint16_t>(w4[k2] & 0xFFFFu));
+              acc[q][2 * k2 + 1] += g[b] * bf2f(static_cast<uint16_t>(w4[k2] >> 16));
+            }
+          }
       }
 #pragma unroll
       for (int q = 0; q < kOneHotPieces; ++q) {
