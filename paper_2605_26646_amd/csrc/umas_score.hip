@@ -986,38 +986,64 @@ __device__ __forceinline__ KContig blocked_rows_tile(const uint16_t* X, int64_t 
   return c;
 }
 
-// A tile's accumulators go out as float32 rows (or are added to what is there).  A 16x16 block's registers cover 64
-// bytes of four rows each; stored like that, half a line at a time, they kept the dW tiles of short selections waiting
-// (725 rows of 2048 against 151 936: both products 2.1 ms, through LDS 1.3 ms).  Every wavefront turns its 128 x 64 block
-// through its own part of LDS, 64 rows at a time, and stores 256 bytes of four rows.  at(row, column): where the tile's
-// row has its four columns from there, or NULL when they do not exist.
-constexpr int kAccPitch = 64 * 4 + 16;                               // a staged row: 64 floats
-static_assert(Cfg::WTN == 64 && Cfg::WM * Cfg::WN * 64 * kAccPitch <= MixedLdsBytes<Cfg>::value, "the staged halves fit the tile buffers");
-template <class F>
-__device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[Cfg::MI][Cfg::NI], uint16_t* lds, F at, int accumulate) {
+// A tile's accumulators go out as float32 rows, `ld` floats apart from `out` on (or are added to what is there); rows and cols
+// of them exist, cols a multiple of 4.  A 16x16 block's registers cover 64 bytes of four rows each; stored like that, half a
+// line at a time, they kept the dW tiles of short selections waiting (725 rows of 2048 against 151 936: both products 2.1
+// ms, through LDS 1.3 ms).  Every wavefront turns its 128 x 64 block through its own part of LDS, 32 rows at a time, and
+// stores 256 bytes of four rows.  In a tile that exists as a whole nothing depends on the row: what is there already is
+// under way during the turn, and a piece's LDS reads and stores go out together (waiting for each of 32 pieces by itself:
+// both products of 725 rows of 2048 that add to dW 1155 us, together 1020; 64 rows without adding 459 and 443).
+constexpr int kTurnBytes = 32 * 64 * 4;                              // 32 rows of 64 floats per wavefront
+static_assert(Cfg::WTN == 64 && Cfg::WM * Cfg::WN == 8 && 8 * kTurnBytes <= 2 * Cfg::BM * 128, "the turn fits two stages of an operand");
+__device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[Cfg::MI][Cfg::NI], uint16_t* lds, float* out, int64_t ld, int64_t rows, int cols,
+                                              int accumulate) {
   using C = Cfg;
   typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // dW has the alignment of a float
   const int tid = tile_thread(), lane = tid & 63, wave = tid >> 6;
-  char* stage = reinterpret_cast<char*>(lds) + wave * (64 * kAccPitch);
+  char* turn = reinterpret_cast<char*>(lds) + wave * kTurnBytes;
   const int r0 = wave / C::WN * C::WTM, c0 = wave % C::WN * C::WTN + (lane & 15) * 4;
+  const bool whole = rows >= C::BM && cols >= C::BN;                 // the same for every thread
+  float* const dst = out + (r0 + (lane >> 4)) * ld + c0;
+  floatx4 have[8];                                                   // what is there already, a piece ahead
+  auto fetch = [&](int h) {
 #pragma unroll
-  for (int h = 0; h < C::MI / 4; ++h) {
+    for (int i = 0; i < 8; ++i) have[i] = *reinterpret_cast<const f32x4_a4*>(dst + (h * 32 + i * 4) * ld);
+  };
+  if (whole && accumulate) fetch(0);
+#pragma unroll
+  for (int h = 0; h < C::MI / 2; ++h) {
+    // the 16-byte unit u of row r lies in unit u ^ 4 ((r >> 2) & 3): neither side meets a bank twice
 #pragma unroll
     for (int bj = 0; bj < C::NI; ++bj)
 #pragma unroll
-      for (int bi = 0; bi < 4; ++bi)
+      for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          *reinterpret_cast<float*>(stage + (bi * 16 + (lane >> 4) * 4 + r) * kAccPitch + (bj * 16 + (lane & 15)) * 4) = acc[h * 4 + bi][bj][r];
+          *reinterpret_cast<float*>(turn + (bi * 16 + (lane >> 4) * 4 + r) * 256 + (((bj * 4 + ((lane >> 2) & 3)) ^ (4 * (lane >> 4))) * 16) + (lane & 3) * 4) =
+              acc[h * 2 + bi][bj][r];
     __builtin_amdgcn_wave_barrier();
-#pragma unroll 8
-    for (int i = 0; i < 16; ++i) {
-      const int row = i * 4 + (lane >> 4);
-      if (f32x4_a4* dst = reinterpret_cast<f32x4_a4*>(at(r0 + h * 64 + row, c0))) {
-        f32x4_a4 x = *reinterpret_cast<const floatx4*>(stage + row * kAccPitch + (lane & 15) * 16);
-        if (accumulate) x += *dst;
-        __builtin_nontemporal_store(x, dst);
+    floatx4 x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      x[i] = *reinterpret_cast<const floatx4*>(turn + (i * 4 + (lane >> 4)) * 256 + (((lane & 15) ^ (4 * (i & 3))) * 16));
+    if (whole) {
+      if (accumulate) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] += have[i];
+        if (h + 1 < C::MI / 2) fetch(h + 1);
       }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const f32x4_a4 y = x[i];
+        __builtin_nontemporal_store(y, reinterpret_cast<f32x4_a4*>(dst + (h * 32 + i * 4) * ld));
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (r0 + h * 32 + i * 4 + (lane >> 4) < rows && c0 < cols) {
+          f32x4_a4* const at = reinterpret_cast<f32x4_a4*>(dst + (h * 32 + i * 4) * ld);
+          *at = accumulate ? x[i] + *at : x[i];
+        }
     }
     __builtin_amdgcn_wave_barrier();
   }
@@ -1053,7 +1079,7 @@ __device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, in
   mfma_mainloop_mixed<C, false, true, 2>(ca, KMajor{}, KContig{}, kb, k_len, lds, acc);
   if (sl.n > 1) {
     float* out = sl.part + ((static_cast<int64_t>(slice) * tiles_r + tile_m) * tiles_d + tile_n) * (C::BM * C::BN);
-    store_acc_f32(acc, lds, [&](int r, int c) { return out + r * C::BN + c; }, 0);
+    store_acc_f32(acc, lds, out, C::BN, C::BM, C::BN, 0);
     return;
   }
   const int tid = tile_thread();
@@ -1099,10 +1125,7 @@ __device__ __forceinline__ void dw_tile(int tile_m, int tile_n, const uint16_t* 
   floatx4 acc[C::MI][C::NI];
   zero_acc<C>(acc);
   if (k_len > 0) mfma_mainloop_mixed<C, true, true, 1>(KContig{}, ka, KContig{}, kb, k_len, lds, acc);
-  const int64_t v_end = V;
-  store_acc_f32(acc, lds, [&](int r, int c) -> float* {
-    return m0 + r < v_end && n0 + c < d ? dW + (m0 + r) * d + n0 + c : nullptr;     // d is a multiple of 8: four columns are all inside or all outside
-  }, accumulate);
+  store_acc_f32(acc, lds, dW + m0 * d + n0, d, V - m0, d - n0, accumulate);   // d is a multiple of 8
 }
 // Both products in one launch, in groups of 4 x 8 tiles that are worked on together on one XCD.  Every XCD owns a contiguous
 // range of the dH tiles (slice after slice, so that its workgroups share a slice of both operands) and behind it the share
