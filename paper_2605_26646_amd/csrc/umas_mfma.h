@@ -505,13 +505,8 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
 
 // Position of accumulator element r of block (i, j) inside the workgroup tile: row 4 (l / 16) + r, column l % 16 of the block.
 template <class C>
-__device__ __forceinline__ int acc_row(int i, int r, int t = threadIdx.x) {
-  const int lane = t & 63, wave = t >> 6;
-  return (wave / C::WN) * C::WTM + i * 16 + (lane >> 4) * 4 + r;
-}
-template <class C>
-__device__ __forceinline__ int acc_col(int j, int t = threadIdx.x) {
-  const int lane = t & 63, wave = t >> 6;
+__device__ __forceinline__ int acc_col(int j) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   return (wave % C::WN) * C::WTN + j * 16 + (lane & 15);
 }
 

@@ -995,6 +995,22 @@ __device__ __forceinline__ KContig blocked_rows_tile(const uint16_t* X, int64_t 
 // both products of 725 rows of 2048 that add to dW 1155 us, together 1020; 64 rows without adding 459 and 443).
 constexpr int kTurnBytes = 32 * 64 * 4;                              // 32 rows of 64 floats per wavefront
 static_assert(Cfg::WTN == 64 && Cfg::WM * Cfg::WN == 8 && 8 * kTurnBytes <= 2 * Cfg::BM * 128, "the turn fits two stages of an operand");
+// 32 rows (blocks 2 h and 2 h + 1) of a wavefront's accumulators into its part of LDS, and four columns of four rows (4 i + lane /
+// 16) back.  The 16-byte unit u of row r lies in unit u ^ 4 ((r >> 2) & 3): neither side meets a bank twice.
+__device__ __forceinline__ void turn_in(const floatx4 (&acc)[Cfg::MI][Cfg::NI], int h, char* turn, int lane) {
+#pragma unroll
+  for (int bj = 0; bj < Cfg::NI; ++bj)
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        *reinterpret_cast<float*>(turn + (bi * 16 + (lane >> 4) * 4 + r) * 256 + (((bj * 4 + ((lane >> 2) & 3)) ^ (4 * (lane >> 4))) * 16) + (lane & 3) * 4) =
+            acc[h * 2 + bi][bj][r];
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ floatx4 turn_out(const char* turn, int i, int lane) {
+  return *reinterpret_cast<const floatx4*>(turn + (i * 4 + (lane >> 4)) * 256 + (((lane & 15) ^ (4 * (i & 3))) * 16));
+}
 __device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[Cfg::MI][Cfg::NI], uint16_t* lds, float* out, int64_t ld, int64_t rows, int cols,
                                               int accumulate) {
   using C = Cfg;
@@ -1012,20 +1028,10 @@ __device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[Cfg::MI][Cfg:
   if (whole && accumulate) fetch(0);
 #pragma unroll
   for (int h = 0; h < C::MI / 2; ++h) {
-    // the 16-byte unit u of row r lies in unit u ^ 4 ((r >> 2) & 3): neither side meets a bank twice
-#pragma unroll
-    for (int bj = 0; bj < C::NI; ++bj)
-#pragma unroll
-      for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          *reinterpret_cast<float*>(turn + (bi * 16 + (lane >> 4) * 4 + r) * 256 + (((bj * 4 + ((lane >> 2) & 3)) ^ (4 * (lane >> 4))) * 16) + (lane & 3) * 4) =
-              acc[h * 2 + bi][bj][r];
-    __builtin_amdgcn_wave_barrier();
+    turn_in(acc, h, turn, lane);
     floatx4 x[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      x[i] = *reinterpret_cast<const floatx4*>(turn + (i * 4 + (lane >> 4)) * 256 + (((lane & 15) ^ (4 * (i & 3))) * 16));
+    for (int i = 0; i < 8; ++i) x[i] = turn_out(turn, i, lane);
     if (whole) {
       if (accumulate) {
 #pragma unroll
@@ -1082,23 +1088,45 @@ __device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, in
     store_acc_f32(acc, lds, out, C::BN, C::BM, C::BN, 0);
     return;
   }
-  const int tid = tile_thread();
+  // dH rows leave like the float32 ones: 32 rows at a time through LDS, 128 bytes of four rows to a store, the row numbers,
+  // factors and rows of W of a piece fetched together.  (One 2-byte entry after the other, each with its own chain of loads:
+  // both products of 39 000 rows of 2048 37.43 ms, like this 37.16, 12 000 rows 11.48 and 11.37.)
+  typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));   // dH has the alignment of its entries
+  const int tid = tile_thread(), lane = tid & 63, wave = tid >> 6;
+  char* turn = reinterpret_cast<char*>(lds) + wave * kTurnBytes;
+  const int64_t r0 = m0 + wave / C::WN * C::WTM + (lane >> 4);
+  const int j = n0 + wave % C::WN * C::WTN + (lane & 15) * 4, jw = min(j, d - 4);   // d is a multiple of 8: four columns are all inside or all outside
 #pragma unroll
-  for (int bj = 0; bj < C::NI; ++bj) {
-    const int j = n0 + acc_col<C>(bj, tid);
-    if (j >= d) continue;
+  for (int h = 0; h < C::MI / 2; ++h) {
+    int64_t row[8];
+    float g[8], f[8];
+    uint2 w[8];
 #pragma unroll
-    for (int bi = 0; bi < C::MI; ++bi)
+    for (int i = 0; i < 8; ++i) {
+      const int64_t n = c0 + min(r0 + h * 32 + i * 4, rows - 1);
+      row[i] = rowsel ? rowsel[n] : n;
+      g[i] = g_c[n];
+      f[i] = sc ? sc[n] : 1.f;
+    }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t m = m0 + acc_row<C>(bi, r, tid);
-        if (m >= rows) continue;
-        const int64_t row = rowsel ? rowsel[c0 + m] : c0 + m;
-        const float g = g_c[c0 + m];
-        float v = sc ? sc[c0 + m] * acc[bi][bj][r] : acc[bi][bj][r];
-        if (g != 0.f) v += g * bf2f(W[static_cast<int64_t>(ids[row]) * d + j]);   // g = 0 for invalid ids
-        dH[row * d + j] = f2bf(v);
+    for (int i = 0; i < 8; ++i) {                                    // g = 0 for invalid ids
+      const int64_t id = g[i] != 0.f ? ids[row[i]] : 0;
+      w[i] = *reinterpret_cast<const uint2*>(W + id * d + jw);
+    }
+    turn_in(acc, h, turn, lane);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      floatx4 v = turn_out(turn, i, lane);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        v[k] = sc ? f[i] * v[k] : v[k];
+        const uint32_t wk = k < 2 ? w[i].x : w[i].y;
+        if (g[i] != 0.f) v[k] += g[i] * __uint_as_float(k & 1 ? wk & 0xffff0000u : wk << 16);
       }
+      if (r0 + h * 32 + i * 4 < rows && j < d)
+        *reinterpret_cast<u32x2_a2*>(dH + row[i] * d + j) = u32x2_a2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+    }
+    __builtin_amdgcn_wave_barrier();
   }
 }
 // Hs: the rows of H that go with the rows of dZ (scaled by the keeping pass), in column blocks [d / 256][mcp][256] so that a
