@@ -418,7 +418,11 @@ k_gae_scan_cut(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
   }
 }
 
-inline int64_t scan_ranges(int64_t n_tokens) { return (n_tokens + chunk_tokens(n_tokens) - 1) / chunk_tokens(n_tokens); }
+inline int64_t scan_ranges(int64_t n_tokens, int64_t chunk) { return (n_tokens + chunk - 1) / chunk; }
+inline size_t scan_bytes(int64_t n_tokens, int64_t chunk) {   // ranges, records
+  const size_t n = static_cast<size_t>(n_tokens > 0 ? scan_ranges(n_tokens, chunk) : 1);
+  return align_up(n * sizeof(Range)) + align_up(n * kStateWords * sizeof(unsigned long long));
+}
 
 }  // namespace
 }  // namespace umas
@@ -427,8 +431,7 @@ using namespace umas;
 
 extern "C" size_t umas_advantages_workspace_bytes(int64_t n_tokens) {
   if (n_tokens < 0) return 0;
-  const size_t n = static_cast<size_t>(scan_ranges(n_tokens) > 0 ? scan_ranges(n_tokens) : 1);
-  return align_up(n * sizeof(Range)) + align_up(n * kStateWords * sizeof(unsigned long long));   // ranges, records
+  return scan_bytes(n_tokens, chunk_tokens(n_tokens));
 }
 
 extern "C" umas_status umas_advantages(const umas_streams* s, int64_t n_tokens, int32_t n_turns,
@@ -447,17 +450,20 @@ extern "C" umas_status umas_advantages(const umas_streams* s, int64_t n_tokens, 
                    reinterpret_cast<uintptr_t>(s->tok_flags) % 16 == 0 && reinterpret_cast<uintptr_t>(adv) % 16 == 0 &&
                    reinterpret_cast<uintptr_t>(ret) % 16 == 0,
                UMAS_EINVAL, "tok_reward, tok_flags, value, adv and ret must be 16-byte aligned");
-  UMAS_REQUIRE(scan_ranges(n_tokens) < (1LL << 31), UMAS_ESHAPE, "at most 2^43 tokens");
-  const size_t need = umas_advantages_workspace_bytes(n_tokens);
+  constexpr int64_t kMaxChunk = static_cast<int64_t>(kChunkTiles) * kTile;
+  UMAS_REQUIRE(scan_ranges(n_tokens, kMaxChunk) < (1LL << 31), UMAS_ESHAPE, "at most 2^43 tokens");
+  // a workspace for ranges of eight tiles will do: then they are no finer than it holds
+  const size_t need = scan_bytes(n_tokens, kMaxChunk);
   UMAS_REQUIRE(workspace && reinterpret_cast<uintptr_t>(workspace) % kAlign == 0 && workspace_bytes >= need, UMAS_EWORKSPACE,
                "workspace must be 256-byte aligned and hold %zu bytes (got %zu)", need, workspace_bytes);
   if (n_tokens == 0) return UMAS_OK;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   prof_mark(st);
-  const int64_t n_ranges = scan_ranges(n_tokens);
   ScanParams P;
   P.n_tokens = n_tokens;
   P.chunk = chunk_tokens(n_tokens);
+  while (scan_bytes(n_tokens, P.chunk) > workspace_bytes) P.chunk += kTile;
+  const int64_t n_ranges = scan_ranges(n_tokens, P.chunk);
   P.n_ranges = static_cast<uint32_t>(n_ranges);
   Range* ranges = static_cast<Range*>(workspace);
   P.ranges = ranges;

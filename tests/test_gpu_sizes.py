@@ -1,4 +1,6 @@
 """Sizes at which the update's dispatch changes: edges of tiles, slices and workspaces, against the oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -258,6 +260,15 @@ def test_scan_of_one_segment(n, with_value):
     v = np.zeros(n) if value is None else value.astype(np.float64)
     delta = reward.astype(np.float64) + gamma * np.append(v[1:], 0.0) - v
     want = lfilter([1.0], [1.0, -gamma * lam], delta[::-1])[::-1]
+    # the smallest workspace that is accepted (ranges of 8192 tokens, 32 + 40 bytes each) and one that holds ranges of three tiles
+    lib, cs = umas.load_library(), st._c()
+    for chunk in (8192, 3072):
+        ranges = -(-n // chunk)
+        ws = torch.empty(-(-32 * ranges // 256) * 256 + -(-40 * ranges // 256) * 256, dtype=torch.uint8, device="cuda")
+        adv2, ret2 = torch.empty_like(adv), torch.empty_like(ret)
+        rc = lib.umas_advantages(ctypes.addressof(cs), n, 1, None if value is None else (v_dev := P.to_dev(value)).data_ptr(), gamma, lam, 1.0, 0,
+                                 adv2.data_ptr(), ret2.data_ptr(), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+        assert rc == 0 and (adv2 - adv).abs().max().item() <= 2e-5 and (ret2 - ret).abs().max().item() <= 2e-5
     # a float32 recurrence that forgets with 0.94 a token: some 17 terms of |delta| <= 10 carry 2^-24 each, folds a few times as many
     assert np.abs(adv.cpu().numpy() - want).max() <= 2e-5
     assert np.abs(ret.cpu().numpy() - want - v).max() <= 2e-5
