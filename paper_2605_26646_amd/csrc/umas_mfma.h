@@ -503,7 +503,7 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
   __builtin_amdgcn_s_barrier();
 }
 
-// Position of accumulator element r of block (i, j) inside the workgroup tile: row 4 (l / 16) + r, column l % 16 of the block.
+// Column of the accumulators of blocks (., j) inside the workgroup tile: l % 16 of the block.
 template <class C>
 __device__ __forceinline__ int acc_col(int j) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
