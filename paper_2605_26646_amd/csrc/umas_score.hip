@@ -373,7 +373,10 @@ k_score_few(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int 
   const int per = (blocks + static_cast<int>(gridDim.x) - 1) / static_cast<int>(gridDim.x);
   const int b0 = static_cast<int>(blockIdx.x) * per, b1 = min(b0 + per, blocks);
   uint4 w[MB][PPW][2];
-  auto load = [&](int b, int p, int q, int i) {              // past the hidden size: some entry of the row, met by zeros of H
+  bool past[2];                                              // the last piece's columns that do not exist
+#pragma unroll
+  for (int q = 0; q < 2; ++q) past[q] = ((PPW - 1) * kFewWaves + wave) * 64 + q * 32 + piece >= d;
+  auto load = [&](int b, int p, int q, int i) {              // past the hidden size: some entry of the row, cleared where it is used
     const int v = min((b + i) * 16 + (lane & 15), V - 1), k = min((p * kFewWaves + wave) * 64 + q * 32 + piece, d - 8);
     w[i][p][q] = *reinterpret_cast<const uint4*>(W + static_cast<int64_t>(v) * d + k);
   };
@@ -391,7 +394,9 @@ k_score_few(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int 
   for (int l = 0; l < NL; ++l) {
     const int n = (2 * l + (tid >> 8)) * 16 + my_n;
     y[l] = mine && n < n_sel ? ids[rowsel ? rowsel[n] : n] : -1;
-    m[l] = kNegInf; s[l] = t[l] = zy[l] = 0.f;
+    // kMasked as in the tiles: against a maximum of -infinity a logit of -infinity makes the sums NaN, and the merge drops
+    // a partial whose maximum a NaN logit has left there
+    m[l] = kMasked; s[l] = t[l] = zy[l] = 0.f;
   }
   int buf = 0;
   for (int b = b0; b < b1; b += MB, buf ^= 1) {
@@ -407,7 +412,8 @@ k_score_few(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int 
       for (int p = 0; p < PPW; ++p)
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-          const bf16x8 a = __builtin_bit_cast(bf16x8, w[i][p][q]);
+          // zeros of H alone would not do: their product with a weight that is not finite is NaN
+          const bf16x8 a = __builtin_bit_cast(bf16x8, p == PPW - 1 && past[q] ? make_uint4(0u, 0u, 0u, 0u) : w[i][p][q]);
 #pragma unroll
           for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, hf[p][q][j], acc[i][j], 0, 0, 0);
           load(nb, p, q, i);

@@ -98,6 +98,48 @@ def test_scoring_of_few_rows(n_sel, d, V):
     check_scores(np.random.default_rng(n_sel + d), n_sel, d, V, select=n_sel % 2 == 1, static=n_sel in (16, 33, 65))
 
 
+# Logits that are not finite: a NaN or +inf logit makes the row's sums NaN, a -inf logit adds nothing to them (its place in the
+# entropy, 0 * inf, is NaN).  Few rows against the same rows among 129, which the tiles score, and against float64: one
+# vocabulary entry to a place of the register-resident kernel (V <= 4096) and many, first and last ones of a block of 16,
+# hidden sizes that fill eight wavefronts' pieces and that leave some of them without columns.
+@pytest.mark.parametrize("d,V", [(512, 5), (64, 1000), (512, 4096), (520, 4112), (1088, 4097), (64, 151936)])
+@pytest.mark.parametrize("n_sel", [1, 16, 17, 32, 33, 64, 65])
+def test_logits_that_are_not_finite(n_sel, d, V):
+    rng = np.random.default_rng(n_sel + d + V)
+    H = rng.normal(size=(n_sel, d)).astype(np.float32) / np.sqrt(d).astype(np.float32)
+    H[:, -1] = 0.5 + np.abs(H[:, -1])                                # a weight of -inf there is a logit of -inf
+    H, W = wl.round_to_bf16(H), wl.round_to_bf16(rng.normal(size=(V, d)).astype(np.float32))
+    ids = rng.integers(1, V - 1, size=n_sel).astype(np.int32)
+    at = np.unique([0, 16 * ((V - 1) // 32), V - 1])                 # none of them is a taken token
+    ids = np.where(np.isin(ids, at), 1, ids).astype(np.int32)
+    more = np.arange(129) % n_sel
+    inf = np.float32(np.inf)
+    for what, h_row, w_at, x in (("NaN weight, last", None, at[-1:], np.nan), ("NaN weight, first", None, at[:1], np.nan),
+                                 ("NaN row", n_sel // 2, [], np.nan), ("-inf logits", None, at, -inf), ("inf logit", None, at[1:2], inf)):
+        Hx, Wx = H.copy(), W.copy()
+        if h_row is not None:
+            Hx[h_row] = x
+        Wx[w_at, -1] = x
+        dev = [P.to_dev(Hx, torch.bfloat16), P.to_dev(Wx, torch.bfloat16), P.to_dev(ids)]
+        few = [a.cpu().numpy() for a in umas.umas_policy_logprobs(*dev)]
+        idx = P.to_dev(more.astype(np.int64))
+        tiles = [a.cpu().numpy()[:n_sel] for a in umas.umas_policy_logprobs(dev[0][idx].contiguous(), dev[1], dev[2][idx].contiguous())]
+        keep = np.setdiff1d(np.arange(V), w_at)
+        z = H.astype(np.float64) @ W[keep].T.astype(np.float64)
+        lse = np.log(np.exp(z - z.max(1, keepdims=True)).sum(1)) + z.max(1)
+        zy = np.einsum("nk,nk->n", H.astype(np.float64), W[ids].astype(np.float64))
+        bad = np.full(n_sel, what in ("NaN weight, last", "NaN weight, first", "inf logit"))
+        if h_row is not None:
+            bad[h_row] = True
+        # exact products: a logit carries d 2^-24 of its terms' magnitudes, the sum of V exponentials (V + 64) 2^-24 of itself at most
+        lim = (2 * d * (np.abs(H).astype(np.float64) @ np.abs(W).T.astype(np.float64)).max() + 64 + V / 16) * 2.0 ** -24 + 1e-5
+        for name, a, b, want in zip(("logp", "lse"), few, tiles, (zy - lse, lse)):
+            assert np.array_equal(np.isnan(a), bad) and np.array_equal(np.isnan(b), bad), (what, name, a, b)
+            assert (np.abs(a - want)[~bad] <= lim).all() and (np.abs(a - b)[~bad] <= 2 * lim).all(), (what, name)
+        assert np.array_equal(np.isnan(few[2]), np.isnan(tiles[2])), what
+        assert np.isnan(few[2]).all() if what == "-inf logits" else np.array_equal(np.isnan(few[2]), bad), what
+
+
 # enough rows for the merge that does not split a row's tiles over the workgroup, and one less
 @pytest.mark.parametrize("n_sel", [19999, 20000])
 def test_scoring_of_many_rows(n_sel):
