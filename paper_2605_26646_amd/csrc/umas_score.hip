@@ -1060,6 +1060,7 @@ __device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[Cfg::MI][Cfg:
     __builtin_amdgcn_wave_barrier();
   }
 }
+typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));     // dH has the alignment of its entries
 // What the sliced products leave behind: partial sums in blocks of 256 x 256 floats [slice][row tile][column tile].
 struct DhSlices {
   int n;                // slices of the vocabulary (1: the tiles write dH themselves)
@@ -1097,7 +1098,6 @@ __device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, in
   // dH rows leave like the float32 ones: 32 rows at a time through LDS, 128 bytes of four rows to a store, the row numbers,
   // factors and rows of W of a piece fetched together.  (One 2-byte entry after the other, each with its own chain of loads:
   // both products of 39 000 rows of 2048 37.43 ms, like this 37.16, 12 000 rows 11.48 and 11.37.)
-  typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));   // dH has the alignment of its entries
   const int tid = tile_thread(), lane = tid & 63, wave = tid >> 6;
   char* turn = reinterpret_cast<char*>(lds) + wave * kTurnBytes;
   const int64_t r0 = m0 + wave / C::WN * C::WTM + (lane >> 4);
@@ -1261,7 +1261,7 @@ k_dh_reduce(DhSlices sl, int tiles_r, int tiles_d, const uint16_t* __restrict__ 
     s.x += g * __uint_as_float(w.x << 16); s.y += g * __uint_as_float(w.x & 0xffff0000u);
     s.z += g * __uint_as_float(w.y << 16); s.w += g * __uint_as_float(w.y & 0xffff0000u);
   }
-  *reinterpret_cast<uint2*>(dH + row * d + j) = make_uint2(pack_bf16x2(s.x, s.y), pack_bf16x2(s.z, s.w));
+  *reinterpret_cast<u32x2_a2*>(dH + row * d + j) = u32x2_a2{pack_bf16x2(s.x, s.y), pack_bf16x2(s.z, s.w)};
 }
 
 // One-hot part of dW: dW[y_n, :] += g_n h_n for every selected row, in float32.  Rows that took the same token add
@@ -1441,8 +1441,10 @@ size_t chunk_bytes(int64_t mc, int d, int V, umas_dtype dt) {
 // 256 / tiles slices, a piece per compute unit (the dW tiles behind them fill the last round); partial sums cost 256 KB a
 // piece.  Gradients and k_dh_reduce together with 256 / 384 / 512 / 768 pieces: 64 rows of 2048 467 / 460 / 480 / 488 us, 203 rows
 // of 3584 859 / 875 / 869 / 892, 725 rows of 2048 947 / 956 / 959 / 984, 6000 rows 5.91 / 5.90 / 5.98 / 5.90 ms; whole
-// tiles took 3.6 to 4 ms for the first three.  Above the line dH stays bit for bit the same however the rows are chunked.
+// tiles took 3.6 to 4 ms for the first three.  Whether there are slices at all is decided by the rows of the call
+// (slices_dh), not of the chunk: from the line on dH is bit for bit the same however the rows are chunked.
 constexpr int kDhSliceTiles = 256;
+bool slices_dh(int64_t n_sel, int d) { return static_cast<int64_t>(cdiv(n_sel, 256)) * cdiv(d, 256) < kDhSliceTiles; }
 struct DhPlan {
   int slices, voc_blks;
 };
@@ -1450,7 +1452,6 @@ size_t dh_part_bytes(const DhPlan& p, int tiles_r, int tiles_d) {
   return p.slices > 1 ? static_cast<size_t>(p.slices) * tiles_r * tiles_d * (256 * 256 * sizeof(float)) : 0;
 }
 DhPlan plan_dh(int64_t tiles_r, int64_t tiles_d, int tiles_v, size_t room) {
-  if (tiles_r * tiles_d >= kDhSliceTiles) return DhPlan{1, tiles_v};
   int want = static_cast<int>((kDhSliceTiles + tiles_r * tiles_d - 1) / (tiles_r * tiles_d));
   const size_t one = static_cast<size_t>(tiles_r * tiles_d) * (256 * 256 * sizeof(float));
   if (static_cast<size_t>(want) > room / one) want = static_cast<int>(room / one);
@@ -1714,7 +1715,7 @@ extern "C" size_t umas_ppo_loss_workspace_bytes(int64_t n_sel, int32_t d, int32_
     mc = round_up((mc + nchunk - 1) / nchunk, 256);
   }
   size_t part = 0;
-  if (dtype == UMAS_BF16) {
+  if (dtype == UMAS_BF16 && slices_dh(n_sel, d)) {              // then there is one chunk
     const int tiles_r = static_cast<int>(round_up(mc, 256) / 256), tiles_d = (d + 255) / 256;
     part = dh_part_bytes(plan_dh(tiles_r, tiles_d, (V + 255) / 256, SIZE_MAX), tiles_r, tiles_d);
   }
@@ -1791,8 +1792,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     const int tiles_r = static_cast<int>(cdiv(rows, 256)), tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
     const size_t used = chunk_bytes(rows, d, V, dtype), behind = room > used ? room - used : 0;
     const size_t front = static_cast<size_t>(reinterpret_cast<char*>(w.score.logp_c) - reinterpret_cast<char*>(w.score.partial));
-    const bool aligned = reinterpret_cast<uintptr_t>(dH) % 8 == 0;      // the reducing kernel stores four columns at once
-    const DhPlan p = plan_dh(tiles_r, tiles_d, tiles_v, aligned ? (behind > front ? behind : front) : 0);
+    const DhPlan p = plan_dh(tiles_r, tiles_d, tiles_v, slices_dh(n_sel, d) ? std::max(behind, front) : 0);
     *sl = DhSlices{p.slices, p.voc_blks, behind > front ? reinterpret_cast<float*>(w.chunk + used) : reinterpret_cast<float*>(w.score.partial)};
   };
   auto gradients = [&](int64_t c0, int64_t rows, const DhSlices& sl, const uint16_t* op, const uint16_t* Hs, const float* sc) -> umas_status {

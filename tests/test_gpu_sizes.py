@@ -70,6 +70,42 @@ def test_update_with_dh_at_an_address_that_is_not_a_multiple_of_eight():
     check_update(np.random.default_rng(5), 300, 64, 3000, shift_dH=2)
 
 
+def updates(n, d, V, calls, **kw):
+    """dH and logp_new of the same update for every (bytes of workspace or None, entries by which dH is shifted)."""
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    H = torch.randn(n, d, device="cuda", generator=gen).bfloat16()
+    W = (torch.randn(V, d, device="cuda", generator=gen) / d ** 0.5).bfloat16()
+    ids = torch.randint(0, V, (n,), device="cuda", generator=gen, dtype=torch.int32)
+    adv = torch.randn(n, device="cuda", generator=gen)
+    out = []
+    for nbytes, shift in calls:
+        buf = torch.empty(n * d + 8, dtype=torch.bfloat16, device="cuda")
+        ws = None if nbytes is None else torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        _, logp, dH, _ = umas.umas_ppo_loss_fwd_bwd(H, W, ids, None, None, adv, None, 0, 0.2, dH=buf[shift:shift + n * d].view(n, d),
+                                                    workspace=ws, **kw)
+        out.append((dH.clone(), logp))
+    return out
+
+
+# from 256 tiles of 256 x 256 on (rows x hidden size) every row of dH is one sum over the vocabulary: chunks of 256 rows, with
+# room for partial sums and without, of some thousand and of all rows give the same bits
+@pytest.mark.parametrize("n,d,V", [(31 * 256 + 1, 2048, 8000), (65280 + 1, 256, 1500)])
+@pytest.mark.parametrize("entropy_coef", [0.0, 0.01])
+def test_large_updates_do_not_depend_on_the_workspace(n, d, V, entropy_coef):
+    least = umas.ppo_workspace_bytes(n, d, V, torch.bfloat16, 0, minimum=True)
+    calls = [(None, 0), (least, 0), (least + 4 * d * 1024, 0), (least + 5000 * 2 * (V + d), 0), (None, 2)]
+    first, *others = updates(n, d, V, calls, entropy_coef=entropy_coef)
+    assert first[0].float().abs().max() > 0
+    for (dH, logp), call in zip(others, calls[1:]):
+        assert torch.equal(dH, first[0]) and torch.equal(logp, first[1]), call
+
+
+@pytest.mark.parametrize("n,d,V", [(300, 64, 3000), (700, 1288, 5121)])
+def test_updates_do_not_depend_on_the_address_of_dh(n, d, V):
+    (a, _), (b, _), (c, _) = updates(n, d, V, [(None, 0), (None, 2), (None, 4)])
+    assert torch.equal(a, b) and torch.equal(a, c)
+
+
 def check_scores(rng, n_sel, d, V, select, static):
     n = n_sel + 7 if select else n_sel
     H = wl.round_to_bf16((rng.normal(size=(n, d)) / np.sqrt(d) * 3).astype(np.float32))
