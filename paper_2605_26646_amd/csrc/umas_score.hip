@@ -1769,7 +1769,8 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
   int64_t mc = n_sel > 0 ? n_sel : 1;
   const int64_t cap = dtype == UMAS_F32 ? kF32ChunkRows : kMaxChunkRows;
   if (mc > cap) mc = cap;
-  while (mc > 256 && chunk_bytes(mc, d, V, dtype) > room) mc = round_up(mc / 2, 256);
+  if (mc > 256 && chunk_bytes(mc, d, V, dtype) > room)   // as many blocks of 256 rows as fit: their bytes are multiples of 256
+    mc = std::max<int64_t>(static_cast<int64_t>(room / chunk_bytes(256, d, V, dtype)), 1) * 256;
   if (mc > 256) {   // balance the chunks
     const int64_t nchunk = (n_sel + mc - 1) / mc;
     const int64_t even = round_up((n_sel + nchunk - 1) / nchunk, 256);

@@ -100,6 +100,30 @@ def test_large_updates_do_not_depend_on_the_workspace(n, d, V, entropy_coef):
         assert torch.equal(dH, first[0]) and torch.equal(logp, first[1]), call
 
 
+# chunks of the update: as few as the workspace allows, from the smallest one (256 rows a chunk) to the recommended one (even
+# chunks of at most 131 072 rows), and never more rows than fit
+@pytest.mark.parametrize("dt,n,fit", [("bf16", 131073, None), ("bf16", 5000, 1792), ("bf16", 5000, 256), ("bf16", 3000, 2816),
+                                      ("bf16", 700, 700), ("f32", 4097, None), ("f32", 4000, 1300), ("f32", 300, 300)])
+def test_update_runs_in_as_few_chunks_as_the_workspace_allows(dt, n, fit):
+    d, V, dtype, cap = 8, 40, torch.bfloat16 if dt == "bf16" else torch.float32, 131072 if dt == "bf16" else 4096
+    row = 2 * (256 + 256) if dt == "bf16" else 4 * V
+    pad = lambda rows: -(-rows // 256) * 256
+    if fit is None:
+        nbytes, chunks = umas.ppo_workspace_bytes(n, d, V, dtype, 0), -(-n // cap)
+    else:
+        nbytes = umas.ppo_workspace_bytes(n, d, V, dtype, 0, minimum=True) + pad(row * (pad(fit) if dt == "bf16" else fit)) - row * 256
+        chunks = 1 if fit >= n else -(-n // (fit // 256 * 256))
+    H, W = torch.randn(n, d, device="cuda").to(dtype), torch.randn(V, d, device="cuda").to(dtype)
+    ids, adv = torch.randint(0, V, (n,), device="cuda", dtype=torch.int32), torch.randn(n, device="cuda")
+    umas.profile_enable(True)
+    try:
+        umas.umas_ppo_loss_fwd_bwd(H, W, ids, None, None, adv, None, 0, 0.2, workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+        launches = umas.profile_read()["k_gemm_dh_dw" if dt == "bf16" else "k_dw_f32"][1]
+    finally:
+        umas.profile_enable(False)
+    assert launches == chunks
+
+
 @pytest.mark.parametrize("n,d,V", [(300, 64, 3000), (700, 1288, 5121)])
 def test_updates_do_not_depend_on_the_address_of_dh(n, d, V):
     (a, _), (b, _), (c, _) = updates(n, d, V, [(None, 0), (None, 2), (None, 4)])
