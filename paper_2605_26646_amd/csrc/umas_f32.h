@@ -398,14 +398,17 @@ inline size_t score_room(int64_t n_sel, int V) {
 }
 // The row kernel where a thread of its has little to do (about 30 ns a product at 512 x 8192; the tiles cost a launch more):
 // 24 rows against 512 of width 64 / 128 take 10 / 13 us, in tiles 20 / 22, 768 rows of 64 19 and 18, 1 row of 128 against 3000
-// 47 and 20.  And where there is no room for statistics, as long as its workgroups outnumber the row blocks by more than
-// the tiles are faster: 16 rows of 512 against 8192 0.55 ms (in tiles by a single workgroup 2), 20 000 rows of 64 against
-// 512 320 us (80).
+// 47 and 20.  And where the room holds only `splits` of the parts that would be taken and the row kernel's rounds of 256
+// workgroups are few: tiles take the time of five to six rounds divided by the splits.  512 x 8192 without room: 256 / 1024 /
+// 1300 / 1500 / 8192 rows 0.57 / 2.11 / 3.17 / 3.14 / 17.4 ms in the row kernel, 2.88 / 2.88 / 2.87 / 2.87 / 3.04 in tiles; 256 x 32 000:
+// 700 rows 2.73, with two parts in tiles 2.94, 500 rows 1.95, three parts 1.98, 256 rows 1.10, five parts 1.19, six 1.00.
 inline umas_status score(const float* W, const float* H, int d, int V, const int32_t* rowsel, int64_t n_sel, const int32_t* ids, void* room,
                          size_t room_bytes, const ScoreOut& out, hipStream_t st) {
   const int splits = score_splits(n_sel, V, room_bytes);
   const int64_t per_thread = static_cast<int64_t>(cdiv(V, 256)) * d;
-  if ((n_sel <= 1024 && per_thread <= 128) || (n_sel <= 128 && per_thread <= 256) || (splits == 1 && V > kVocBlock && n_sel < 1024)) {
+  const int64_t rounds = (n_sel + 255) / 256;
+  const bool tight = splits < 6 && rounds < 6 && splits * rounds <= 6 && splits < score_splits(n_sel, V, SIZE_MAX);
+  if ((n_sel <= 1024 && per_thread <= 128) || (n_sel <= 128 && per_thread <= 256) || tight) {
     hipLaunchKernelGGL(k_score_f32_row, dim3(static_cast<unsigned>(n_sel)), dim3(256), d * sizeof(float), st, W, H, d, V, rowsel, ids, out);
     UMAS_LAUNCHED("k_score_f32_row");
     return UMAS_OK;

@@ -325,6 +325,22 @@ def test_float32_products(n, d, V, entropy_coef):
         assert np.abs(dW_g - dW0 - dW_o).max() <= 1e-5 * (np.abs(dW_o).max() + 1e-12) + 2.0 ** -23 * (np.abs(dW0) + np.abs(dW_o)).max(), (n, d, V)
 
 
+# float32 scoring with room for the statistics of one, two, five, six and all parts of the vocabulary, on both sides of the
+# numbers of rows from which tiles are taken without room, with room for two parts and for six
+@pytest.mark.parametrize("n", [1, 256, 257, 512, 768, 769, 1280, 1281])
+def test_float32_scoring_with_room_for_few_parts(n):
+    rng = np.random.default_rng(n)
+    d, V = 36, 2100
+    H, W = rng.normal(size=(n, d)).astype(np.float32), (rng.normal(size=(V, d)) / 6).astype(np.float32)
+    ids = rng.integers(0, V, size=n).astype(np.int32)
+    want = orc.score(H, W, ids)
+    dev = [P.to_dev(x) for x in (H, W, ids)]
+    for parts in (0, 1, 2, 5, 6, 17):
+        out = umas.umas_policy_logprobs(*dev, workspace=torch.empty(max(256, 40 * n * parts), dtype=torch.uint8, device="cuda"))
+        for x, o in zip(out, want):
+            assert np.abs(x.cpu().numpy() - o).max() <= 2.0 ** -22 * (np.abs(want[1]).max() + 1), (n, parts)
+
+
 def test_group_numbers_in_order_counted_and_sorted_give_the_same_streams():
     rng = np.random.default_rng(11)
     n_traj, n_roles = 513, 3
