@@ -184,7 +184,7 @@ size_t umas_policy_logprobs_workspace_bytes(int64_t n_sel, int32_t d, int32_t V,
  *           umas_assign_token_rewards writes them, or a part of a ready batch); NULL with n_sel = n_rows = all
  *   logp, lse, entropy  DEVICE float [n_rows]; rows not selected are set to 0; entropy may be NULL
  * bf16 needs d % 8 == 0.  float32 takes any workspace of at least 256 bytes; with less than
- * umas_policy_logprobs_workspace_bytes the vocabulary of a row is not shared among workgroups. */
+ * umas_policy_logprobs_workspace_bytes the vocabulary of a row is shared among fewer workgroups or not at all. */
 umas_status umas_policy_logprobs(const void* H, const void* W, umas_dtype dtype, int64_t n_rows,
                                  int32_t d, int32_t V, const int32_t* ids, const int32_t* rowsel,
                                  int64_t n_sel, float* logp, float* lse, float* entropy,
@@ -194,12 +194,14 @@ umas_status umas_policy_logprobs(const void* H, const void* W, umas_dtype dtype,
  * harnesses that forbid allocation.  No workspace argument and no allocation of any kind inside the call
  * (no hipMalloc, no hipFree, no host allocation): the per-tile partials that umas_policy_logprobs keeps in
  * its workspace go to a device array of UMAS_STATIC_SCRATCH_BYTES that is part of the library's code object;
- * each GPU the library runs on holds its own copy until the process ends.  Same arguments, outputs, kernels
- * and results as umas_policy_logprobs.
+ * each GPU the library runs on holds its own copy until the process ends.  Same arguments and outputs as
+ * umas_policy_logprobs; for bf16 the same kernels and the same bits.  float32 runs as umas_policy_logprobs does
+ * with its smallest workspace, so that it touches no scratch: float64 sums in another order than with the
+ * full workspace, rounded to float32 once, which may differ in the last bit.
  *   limit   umas_policy_logprobs_workspace_bytes(n_sel, d, V, dtype) <= UMAS_STATIC_SCRATCH_BYTES, i.e. for bf16
  *           ceil(V / 256) * roundup(n_sel, 256) * 16 bytes: 3328 selected rows per call at V = 151936;
  *           float32 needs no scratch.  More returns UMAS_EWORKSPACE, nothing launched.
- *   sharing every call on one GPU uses that GPU's one array: calls that overlap on a GPU (two streams, two
+ *   sharing every bf16 call on one GPU uses that GPU's one array: calls that overlap on a GPU (two streams, two
  *           threads) race; calls on one stream are ordered and safe.  Nothing in the array carries over
  *           between calls (each call overwrites what it reads).
  *   set-up  the first call on a device (with that device current) looks the array's address up once; make that

@@ -1,7 +1,7 @@
 """umas_policy_logprobs_static, the scoring entry point that allocates nothing, against umas_policy_logprobs.
 
-Both run the same kernels; the static one keeps the per-tile partials in the library's file-scope device array
-in place of a workspace.  Called through the C ABI with caller-made outputs, twice in a row, the second time on
+Both run the same kernels (float32: where a row's vocabulary is not shared among workgroups); the static one keeps
+the per-tile partials in the library's file-scope device array in place of a workspace.  Called through the C ABI with caller-made outputs, twice in a row, the second time on
 a smaller input, so that whatever the first call left in the shared array must not leak into the second result.
 """
 import ctypes as C
