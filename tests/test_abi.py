@@ -90,7 +90,7 @@ def test_malformed_graphs_are_rejected_before_any_launch(lib, kw, code, needle):
     assert needle in lib.umas_last_error().decode()
 
 
-# one bad entry among many: the array is checked as a whole first, the message still names the entry
+# one bad entry among many good ones: the message names it
 @pytest.mark.parametrize("name,at,value,needle", [
     ("turn_role", 171, 2, "turn_role[171]=2"), ("turn_role", 0, -1, "turn_role[0]=-1"), ("turn_tok_off", 130, 900, "turn_tok_off decreases at 130"),
     ("traj_turn_off", 7, 99, "traj_turn_off decreases at 7"), ("turn_pred_off", 64, 1, "turn_pred_off decreases at 63"),

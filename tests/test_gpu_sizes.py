@@ -22,6 +22,8 @@ def check_update(rng, n, d, V, *, select=0.8, workspace=None, shift_dH=0, entrop
     rng.shuffle(sel)
     adv = rng.normal(size=n).astype(np.float32)
     logp_o, lse_o, ent_o = orc.score(H, W, ids, sel)
+    # a logit more than 50 above the taken token's: the row's block is flagged and its dz computed from the logits once more
+    assert scale == 1.0 or logp_o[sel].min() < -50 - np.log(V)
     logp_old = np.zeros(n, np.float32)
     logp_old[sel] = (logp_o[sel] + 0.05 * rng.normal(size=len(sel))).astype(np.float32)
     _, g_o = orc.ppo_loss(logp_o, logp_old, adv, ent_o, sel, np.zeros(n, np.int32), 0, 0.2)
@@ -53,8 +55,14 @@ def check_update(rng, n, d, V, *, select=0.8, workspace=None, shift_dH=0, entrop
 # a last slice that is short and a last vocabulary block that is nearly empty
 @pytest.mark.parametrize("n,d,V", [(1, 64, 513), (30, 8, 1283), (320, 264, 2561), (650, 64, 9000), (400, 1032, 5121)])
 @pytest.mark.parametrize("accumulate", [False, True])
-def test_update_with_dh_cut_along_the_vocabulary(n, d, V, accumulate):
-    check_update(np.random.default_rng(n + d), n, d, V, accumulate=accumulate)
+@pytest.mark.parametrize("entropy_coef", [0.0, 0.01])
+def test_update_with_dh_cut_along_the_vocabulary(n, d, V, accumulate, entropy_coef):
+    check_update(np.random.default_rng(n + d), n, d, V, accumulate=accumulate, entropy_coef=entropy_coef)
+
+
+@pytest.mark.parametrize("n,d,V", [(320, 264, 2561), (650, 64, 9000)])
+def test_update_with_dh_cut_along_the_vocabulary_and_flagged_blocks(n, d, V):
+    check_update(np.random.default_rng(n), n, d, V, scale=10.0)
 
 
 # workspaces between the smallest and the recommended one: no room for slices, room in the scoring pass's place (many rows
@@ -401,12 +409,9 @@ def test_whitening_statistics(n, n_roles):
     mask = (rng.random(n) < 0.8).astype(np.uint8)
     role = rng.integers(0, n_roles, size=n).astype(np.int32)
     out = umas.umas_whiten_advantages(P.to_dev(adv), P.to_dev(mask), P.to_dev(role), np.array([0, n]), n_roles, umas.WHITEN_MODEL_ROLE).cpu().numpy()
-    want = np.zeros(n)
-    for g in range(n_roles):
-        at = (mask == 1) & (role == g)
-        if at.any():
-            x = adv[at].astype(np.float64)
-            want[at] = (x - x.mean()) / np.sqrt(x.var() + 1e-8)
-    # a lane of one or two tokens of the same value has a deviation of 0; the others' sums are float64 from float32 parts
-    big = np.abs(want) < 1e3
-    assert np.abs(out - want)[big].max() <= 1e-4
+    a64 = adv.astype(np.float64)
+    off = np.array([0, n])
+    want = orc.whiten_advantages(a64, mask, role, off, n_roles, orc.WHITEN_MODEL_ROLE)
+    bound = P.whiten_bounds(a64, mask, role, off, n_roles, True)
+    assert not out[mask == 0].any()
+    assert (np.abs(out - want) <= bound).all()
