@@ -765,8 +765,8 @@ void group_members(const int32_t* group, int n, std::vector<int32_t>* off, std::
     const int32_t top = *std::max_element(group, group + n);
     if (top < 4 * static_cast<int64_t>(n) + 1024) {
       std::vector<int32_t> at(static_cast<size_t>(top) + 2, 0);
-      for (int b = 0; b < n; ++b) ++at[group[b] + 1];
-      for (int32_t k = 0; k <= top; ++k) {
+      for (int b = 0; b < n; ++b) ++at[static_cast<size_t>(group[b]) + 1];
+      for (size_t k = 0; k <= static_cast<size_t>(top); ++k) {     // (top may be the largest int32)
         if (at[k + 1] > 0 && at[k] > 0) off->push_back(at[k]);
         at[k + 1] += at[k];
       }
