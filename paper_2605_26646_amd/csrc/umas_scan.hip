@@ -36,9 +36,10 @@ constexpr int kThreads = 256;
 constexpr int kIpt = 4;                          // tokens per thread: one 16-byte load per array, no transposition
 constexpr int kTile = kThreads * kIpt;           // tokens per tile
 constexpr int kChunkTiles = 8;                   // nominal tiles per range at most
-// Nominal tokens per range: a range's tiles are done one after the other, so a stream that makes fewer ranges than there are
-// compute units is cut finer (49 152 tokens: 6 ranges of eight tiles 19 us, 48 of one 7 us; the call, waited for, 40 -> 28 us,
-// 400 000 tokens 43 -> 33, 225 000 in segments that are cut 91 -> 60; 25 million 62 us both ways).
+// Nominal tokens per range: a range's tiles are done one after the other, so a stream that makes fewer than 512 ranges of
+// eight tiles (4.2 million tokens) is cut finer, into 512 and more where it has as many tiles: two for every compute unit
+// (49 152 tokens: 6 ranges of eight tiles 19 us, 48 of one 7 us; the call, waited for, 40 -> 28 us, 400 000 tokens 43 -> 33,
+// 225 000 in segments that are cut 91 -> 60; 25 million tokens keep ranges of eight, 62 us).
 inline int64_t chunk_tokens(int64_t n_tokens) {
   const int64_t tiles = n_tokens / (static_cast<int64_t>(kTile) * 512);
   return (tiles < 1 ? 1 : tiles > kChunkTiles ? kChunkTiles : tiles) * kTile;

@@ -7,8 +7,9 @@
 // Update (paragraph "Model-specific updates and synchronization", PPO after Schulman et al.
 // 2017): ratio = exp(logp - logp_old), L = max(-A ratio, -A clip(ratio)), g = dL/dlogp, then
 // dH = dz W and dW = dz^T H with dz = g (onehot - softmax) run as MFMA GEMMs over a bf16 operand
-// [rows, vocabulary] held in a bounded chunk buffer; W and H are read as they lie (operands that are not
-// K-contiguous go through transposing LDS reads), the one-hot part (one term per row) is added in float32.
+// [rows, vocabulary] held in a bounded chunk buffer; W is read as it lies, of H dW reads a copy of the chunk's rows
+// in column blocks (operands that are not K-contiguous go through transposing LDS reads); the one-hot part (one term
+// per row) is added in float32.
 // Without an entropy bonus the dense part of dz is a row factor times the softmax, so the scoring pass of
 // the update itself leaves that operand behind: E = bf16(exp(z - z_y)), the softmax numerators relative to
 // the taken token's logit, and the row factor -g exp(z_y - lse) is applied where dH is written and folded
