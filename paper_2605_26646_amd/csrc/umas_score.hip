@@ -1442,10 +1442,13 @@ size_t chunk_bytes(int64_t mc, int d, int V, umas_dtype dt) {
 // 256 / tiles slices, a piece per compute unit (the dW tiles behind them fill the last round); partial sums cost 256 KB a
 // piece.  Gradients and k_dh_reduce together with 256 / 384 / 512 / 768 pieces: 64 rows of 2048 467 / 460 / 480 / 488 us, 203 rows
 // of 3584 859 / 875 / 869 / 892, 725 rows of 2048 947 / 956 / 959 / 984, 6000 rows 5.91 / 5.90 / 5.98 / 5.90 ms; whole
-// tiles took 3.6 to 4 ms for the first three.  Whether there are slices at all is decided by the rows of the call
-// (slices_dh), not of the chunk: from the line on dH is bit for bit the same however the rows are chunked.
+// tiles took 3.6 to 4 ms for the first three.  A selection that a small workspace cuts into chunks keeps whole tiles, and so the
+// same bits of dH, down to chunks of half as many tiles (39 224 rows of 2048, whole and sliced: chunks of 256 tiles 57.8 and
+// 58.2 ms, 192 58.8 and 59.3, 160 59.6 and 59.5, 128 61.0 and 59.7, 96 71.9 and 61.6, 8 571 and 141).
 constexpr int kDhSliceTiles = 256;
-bool slices_dh(int64_t n_sel, int d) { return static_cast<int64_t>(cdiv(n_sel, 256)) * cdiv(d, 256) < kDhSliceTiles; }
+inline int64_t dh_tiles(int64_t rows, int d) { return static_cast<int64_t>(cdiv(rows, 256)) * cdiv(d, 256); }
+// decided by the rows of the call and its chunks, not by those of the last chunk, which may have fewer
+bool slices_dh(int64_t n_sel, int64_t chunk_rows, int d) { return dh_tiles(chunk_rows, d) < (chunk_rows < n_sel ? kDhSliceTiles / 2 : kDhSliceTiles); }
 struct DhPlan {
   int slices, voc_blks;
 };
@@ -1716,7 +1719,7 @@ extern "C" size_t umas_ppo_loss_workspace_bytes(int64_t n_sel, int32_t d, int32_
     mc = round_up((mc + nchunk - 1) / nchunk, 256);
   }
   size_t part = 0;
-  if (dtype == UMAS_BF16 && slices_dh(n_sel, d)) {              // then there is one chunk
+  if (dtype == UMAS_BF16 && slices_dh(n_sel, mc, d)) {
     const int tiles_r = static_cast<int>(round_up(mc, 256) / 256), tiles_d = (d + 255) / 256;
     part = dh_part_bytes(plan_dh(tiles_r, tiles_d, (V + 255) / 256, SIZE_MAX), tiles_r, tiles_d);
   }
@@ -1794,7 +1797,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     const int tiles_r = static_cast<int>(cdiv(rows, 256)), tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
     const size_t used = chunk_bytes(rows, d, V, dtype), behind = room > used ? room - used : 0;
     const size_t front = static_cast<size_t>(reinterpret_cast<char*>(w.score.logp_c) - reinterpret_cast<char*>(w.score.partial));
-    const DhPlan p = plan_dh(tiles_r, tiles_d, tiles_v, slices_dh(n_sel, d) ? std::max(behind, front) : 0);
+    const DhPlan p = plan_dh(tiles_r, tiles_d, tiles_v, slices_dh(n_sel, mc, d) ? std::max(behind, front) : 0);
     *sl = DhSlices{p.slices, p.voc_blks, behind > front ? reinterpret_cast<float*>(w.chunk + used) : reinterpret_cast<float*>(w.score.partial)};
   };
   auto gradients = [&](int64_t c0, int64_t rows, const DhSlices& sl, const uint16_t* op, const uint16_t* Hs, const float* sc) -> umas_status {

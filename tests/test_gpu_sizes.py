@@ -95,17 +95,30 @@ def updates(n, d, V, calls, **kw):
     return out
 
 
-# from 256 tiles of 256 x 256 on (rows x hidden size) every row of dH is one sum over the vocabulary: chunks of 256 rows, with
-# room for partial sums and without, of some thousand and of all rows give the same bits
-@pytest.mark.parametrize("n,d,V", [(31 * 256 + 1, 2048, 8000), (65280 + 1, 256, 1500)])
+# from 256 tiles of 256 x 256 on (rows x hidden size) every row of dH is one sum over the vocabulary, with every workspace that
+# holds chunks of 128 tiles: the same bits.  Smaller chunks are summed over slices: two sums of V + 1 terms in float32 in
+# different orders, rounded to bf16
+@pytest.mark.parametrize("n,d,V,rows", [(31 * 256 + 1, 2048, 8000, 4096), (65280 + 1, 256, 1500, 32768)])
 @pytest.mark.parametrize("entropy_coef", [0.0, 0.01])
-def test_large_updates_do_not_depend_on_the_workspace(n, d, V, entropy_coef):
-    least = umas.ppo_workspace_bytes(n, d, V, torch.bfloat16, 0, minimum=True)
-    calls = [(None, 0), (least, 0), (least + 4 * d * 1024, 0), (least + 5000 * 2 * (V + d), 0), (None, 2)]
-    first, *others = updates(n, d, V, calls, entropy_coef=entropy_coef)
-    assert first[0].float().abs().max() > 0
-    for (dH, logp), call in zip(others, calls[1:]):
-        assert torch.equal(dH, first[0]) and torch.equal(logp, first[1]), call
+def test_large_updates_do_not_depend_on_the_workspace(n, d, V, rows, entropy_coef):
+    sized = lambda r: umas.ppo_workspace_bytes(n, d, V, torch.bfloat16, 0, minimum=True) + (r - 256) * 2 * (-(-V // 256) * 256 + d)
+    calls = [(None, 0), (sized(rows), 0), (sized(rows + 512) - 256, 0), (sized(6 * rows // 5 // 256 * 256), 0), (None, 2),
+             (sized(256), 0), (sized(rows // 2), 0)]
+    (first, logp), *others = updates(n, d, V, calls, entropy_coef=entropy_coef)
+    assert first.float().abs().max() > 0
+    for dH, lp in others[:4]:
+        assert torch.equal(dH, first) and torch.equal(lp, logp)
+    # dz has magnitudes of |A| <= 6 over n and, with the bonus, entropy_coef |log p| over n; those of a row sum to twice that
+    dz = 2 * (6 + entropy_coef * 30) / n
+    for dH, lp in others[4:]:
+        bound = 2.0 ** -7 * first.float().abs() + (V + 1) * 2.0 ** -23 * dz * 6 / d ** 0.5
+        assert torch.equal(lp, logp) and ((dH.float() - first.float()).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("n,d,V", [(300, 64, 3000), (700, 1288, 5121)])
+def test_updates_do_not_depend_on_the_address_of_dh(n, d, V):
+    (a, _), (b, _), (c, _) = updates(n, d, V, [(None, 0), (None, 2), (None, 4)])
+    assert torch.equal(a, b) and torch.equal(a, c)
 
 
 # chunks of the update: as few as the workspace allows, from the smallest one (256 rows a chunk) to the recommended one (even
