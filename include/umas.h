@@ -224,7 +224,7 @@ typedef struct {
 /* Smallest workspace the call accepts and the size at which it runs in the fewest passes.  For bf16 the
  * workspace holds, per chunk of selected rows, the bf16 operand of the two gradient products
  * [rows, V] (rounded up to multiples of 256) and a scaled bf16 copy of the chunk's rows of H; the
- * smallest size runs in chunks of 256 rows, the full size in chunks of up to 131072 rows.  Where there is little of dH to
+ * smallest size runs in chunks of 256 rows, the full size in chunks of up to 65536 rows.  Where there is little of dH to
  * work on at a time (ceil(rows / 256) ceil(d / 256) blocks: a selection of fewer than 256, or chunks of fewer than 128) it is
  * summed over slices of the vocabulary, as many as the workspace has room for: there the rounding of dH depends on the
  * size of the workspace, and the full size holds the float32 partial sums.  Larger selections have the same bits of dH with

@@ -1390,7 +1390,9 @@ k_dw_onehot(const uint16_t* __restrict__ H, int d, const int32_t* __restrict__ r
 // ------------------------------------------------------------------ host side
 constexpr int64_t kF32ChunkRows = 4096;
 constexpr double kF32MaxWork = 137438953472.0;   // 2^37 multiply-adds per product
-constexpr int64_t kMaxChunkRows = 1 << 17;
+// A chunk of more rows is no faster: 73 728 rows of 2048 in one chunk 108.6 ms, in two 105.8; 122 880 of 3584 in one 326 ms, in two
+// 320.7, in three 315; 163 840 in two 432, in three 427.
+constexpr int64_t kMaxChunkRows = 1 << 16;
 
 int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 

@@ -122,11 +122,11 @@ def test_updates_do_not_depend_on_the_address_of_dh(n, d, V):
 
 
 # chunks of the update: as few as the workspace allows, from the smallest one (256 rows a chunk) to the recommended one (even
-# chunks of at most 131 072 rows), and never more rows than fit
-@pytest.mark.parametrize("dt,n,fit", [("bf16", 131073, None), ("bf16", 5000, 1792), ("bf16", 5000, 256), ("bf16", 3000, 2816),
+# chunks of at most 65 536 rows), and never more rows than fit
+@pytest.mark.parametrize("dt,n,fit", [("bf16", 131072, None), ("bf16", 131073, None), ("bf16", 5000, 1792), ("bf16", 5000, 256), ("bf16", 3000, 2816),
                                       ("bf16", 700, 700), ("f32", 4097, None), ("f32", 4000, 1300), ("f32", 300, 300)])
 def test_update_runs_in_as_few_chunks_as_the_workspace_allows(dt, n, fit):
-    d, V, dtype, cap = 8, 40, torch.bfloat16 if dt == "bf16" else torch.float32, 131072 if dt == "bf16" else 4096
+    d, V, dtype, cap = 8, 40, torch.bfloat16 if dt == "bf16" else torch.float32, 65536 if dt == "bf16" else 4096
     row = 2 * (256 + 256) if dt == "bf16" else 4 * V
     pad = lambda rows: -(-rows // 256) * 256
     if fit is None:
