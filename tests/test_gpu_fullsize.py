@@ -146,7 +146,7 @@ def test_full_size(cfg):
 
 
 def test_full_size_cfg4_with_three_fixed_rounds():
-    """The other reading of configuration 4 (every trajectory runs all three rounds: 245 760 tokens, two chunks of the
+    """The other reading of configuration 4 (every trajectory runs all three rounds: 245 760 tokens, four chunks of the
     backward at the recommended workspace): routing, rewards and advantages on the whole batch, log-probs, logsumexps
     and entropies on a stored sample of 4096 rows, dH on 128 of them, dW summing to zero over the vocabulary."""
     run_fullsize(4, fixed_rounds=3)
