@@ -517,9 +517,11 @@ __device__ __forceinline__ int acc_col(int j) {
 // working on one group at a time.  With at most GN column tiles the tiles themselves are numbered, column tiles of a row
 // tile next to each other, one to a workgroup: the same sharing, and the few rounds there are come out even (groups
 // half or more empty left 96 of 256 compute units idle with one column tile).
+// More column tiles than `panel` (a multiple of GN) are worked through a panel of them after the other, all XCDs in the same
+// panel: the B operand of a panel is read again for every GM row tiles, from the memory-side cache if it fits there.
 // Returns false when iteration `it` of this workgroup has no tile.
 template <int GM, int GN>
-__device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int* tm, int* tn, int it, int per_wg) {
+__device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int panel, int* tm, int* tn, int it, int per_wg) {
   const int xcd = static_cast<int>(blockIdx.x & 7), w = static_cast<int>(blockIdx.x >> 3);   // w: workgroup number inside its XCD
   if (tiles_n <= GN) {
     const int per_xcd = (tiles_m * tiles_n + 7) / 8, t = xcd * per_xcd + w;
@@ -527,14 +529,17 @@ __device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int* tm, i
     *tn = t % tiles_n;
     return it == 0 && w < per_xcd && *tm < tiles_m;
   }
-  const int total_groups_n = (tiles_n + GN - 1) / GN;
-  const int groups = (tiles_m + GM - 1) / GM * total_groups_n;
-  const int groups_per_xcd = (groups + 7) / 8;                             // contiguous range of groups per XCD
-  const int grp_in_xcd = w / (GM * GN) * per_wg + it, within = w % (GM * GN), grp = xcd * groups_per_xcd + grp_in_xcd;
+  const int groups_m = (tiles_m + GM - 1) / GM;
+  const int full = (groups_m * (panel / GN) + 7) / 8;                      // groups of a whole panel per XCD
+  const int grp_in_seq = w / (GM * GN) * per_wg + it, within = w % (GM * GN);
+  const int p = min(grp_in_seq / full, (tiles_n - 1) / panel), n0 = p * panel;
+  const int groups_n = (min(panel, tiles_n - n0) + GN - 1) / GN, groups = groups_m * groups_n;
+  const int groups_per_xcd = (groups + 7) / 8;                             // contiguous range of the panel's groups per XCD
+  const int grp_in_xcd = grp_in_seq - p * full, grp = xcd * groups_per_xcd + grp_in_xcd;
   if (grp_in_xcd >= groups_per_xcd || grp >= groups) return false;
-  const int gm = grp / total_groups_n;
+  const int gm = grp / groups_n;
   *tm = gm * GM + within % GM;
-  *tn = (grp - gm * total_groups_n) * GN + within / GM;
+  *tn = n0 + (grp - gm * groups_n) * GN + within / GM;
   return *tm < tiles_m && *tn < tiles_n;
 }
 // Shares of a sequence of tiles per XCD: XCD x owns tiles first[x] .. first[x + 1] - 1.
@@ -551,10 +556,11 @@ __device__ __forceinline__ void tile_of_groups(int t, int tiles_m, int tiles_n, 
   *tn = gn * GN + c;
 }
 template <int GM, int GN>
-inline unsigned tile_grid(int tiles_m, int tiles_n, int per_wg) {           // workgroups tile_coords needs
+inline unsigned tile_grid(int tiles_m, int tiles_n, int panel, int per_wg) {   // workgroups tile_coords needs
   if (tiles_n <= GN) return static_cast<unsigned>((static_cast<long long>(tiles_m) * tiles_n + 7) / 8 * 8);
-  const long long groups = static_cast<long long>((tiles_m + GM - 1) / GM) * ((tiles_n + GN - 1) / GN);
-  const long long groups_per_xcd = (groups + 7) / 8;
+  const long long groups_m = (tiles_m + GM - 1) / GM, panels = (tiles_n - 1) / panel;                  // whole panels in front of the last
+  const long long last = (tiles_n - panels * panel + GN - 1) / GN;
+  const long long groups_per_xcd = panels * ((groups_m * (panel / GN) + 7) / 8) + (groups_m * last + 7) / 8;
   const long long wg_groups = (groups_per_xcd + per_wg - 1) / per_wg;       // groups of workgroups per XCD
   return static_cast<unsigned>(wg_groups * (GM * GN) * 8);
 }

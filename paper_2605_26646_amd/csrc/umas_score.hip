@@ -152,13 +152,13 @@ struct KeepArgs {
 template <bool KEEP, class C>
 __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
                                             const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc,
-                                            const int32_t* __restrict__ ids, int tiles_m, int tiles_n,
+                                            const int32_t* __restrict__ ids, int tiles_m, int tiles_n, int panel,
                                             float4* __restrict__ partial, int64_t n_pad, const KeepArgs& keep,
                                             uint16_t* lds) {
   static_assert(!KEEP || C::BM * C::BN == Cfg::BM * Cfg::BN, "kept numerators lie in whole blocks");
   for (int it = 0; it < kTilesPerWg; ++it) {     // a workgroup walks the same place of kTilesPerWg consecutive tile groups
   int tile_m, tile_n;
-  if (!tile_coords<kGM, kGN>(tiles_m, tiles_n, &tile_m, &tile_n, it, kTilesPerWg)) continue;
+  if (!tile_coords<kGM, kGN>(tiles_m, tiles_n, panel, &tile_m, &tile_n, it, kTilesPerWg)) continue;
   const int m0 = tile_m * C::BM;
   const int64_t n0 = static_cast<int64_t>(tile_n) * C::BN;   // chunk-relative
   floatx4 acc[C::MI][C::NI];
@@ -306,9 +306,9 @@ __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, cons
 __global__ void __launch_bounds__(Cfg::T)
 k_score_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
               const int32_t* __restrict__ rowsel, int64_t n_sel, const int32_t* __restrict__ ids,
-              int tiles_m, int tiles_n, float4* __restrict__ partial, int64_t n_pad) {
+              int tiles_m, int tiles_n, int panel, float4* __restrict__ partial, int64_t n_pad) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[kLogitLds / 2];
-  score_tiles<false, Cfg>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, tiles_n, partial, n_pad, KeepArgs{}, lds);
+  score_tiles<false, Cfg>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{}, lds);
 }
 // Up to 128 selected rows: half-size tiles with a pipeline of their own, two workgroups to a compute unit, so that one
 // fills its stages while the other multiplies (64 rows of 2048 / 3584 against 151 936: 156 / 215 us against 182 / 274 with
@@ -318,18 +318,18 @@ constexpr int kNarrowLds = Ring2Cfg<NarrowCfg>::LDS_BYTES > NarrowCfg::LDS_BYTES
 __global__ void __launch_bounds__(NarrowCfg::T)
 k_score_narrow(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
                const int32_t* __restrict__ rowsel, int64_t n_sel, const int32_t* __restrict__ ids,
-               int tiles_m, int tiles_n, float4* __restrict__ partial, int64_t n_pad) {
+               int tiles_m, int tiles_n, int panel, float4* __restrict__ partial, int64_t n_pad) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[kNarrowLds / 2];
-  score_tiles<false, NarrowCfg>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, tiles_n, partial, n_pad, KeepArgs{}, lds);
+  score_tiles<false, NarrowCfg>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{}, lds);
 }
 __global__ void __launch_bounds__(Cfg::T)
 k_score_keep_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
                    const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc, const int32_t* __restrict__ ids,
-                   int tiles_m, int tiles_n, float4* __restrict__ partial, int64_t n_pad,
+                   int tiles_m, int tiles_n, int panel, float4* __restrict__ partial, int64_t n_pad,
                    const float* __restrict__ cref, uint16_t* __restrict__ E, int64_t Vp, int32_t* __restrict__ flags,
                    const int32_t* __restrict__ cidx) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[kLogitLds / 2];
-  score_tiles<true, Cfg>(W, H, d, V, rowsel, c0, mc, ids, tiles_m, tiles_n, partial, n_pad, KeepArgs{cref, E, Vp, flags, cidx}, lds);
+  score_tiles<true, Cfg>(W, H, d, V, rowsel, c0, mc, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{cref, E, Vp, flags, cidx}, lds);
 }
 
 // ------------------------------------------------------------------ bf16: a few rows
@@ -923,11 +923,11 @@ __global__ void __launch_bounds__(Cfg::T)
 k_dz_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
            const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc,
            const float* __restrict__ lse_c, const float* __restrict__ a_c, const float* __restrict__ kz_c,
-           int tiles_m, int tiles_n, uint16_t* __restrict__ dZ, int64_t Vp) {
+           int tiles_m, int tiles_n, int panel, uint16_t* __restrict__ dZ, int64_t Vp) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[kLogitLds / 2];
   for (int it = 0; it < kTilesPerWg; ++it) {     // a workgroup walks the same place of kTilesPerWg consecutive tile groups
     int tile_m, tile_n;
-    if (!tile_coords<kGM, kGN>(tiles_m, tiles_n, &tile_m, &tile_n, it, kTilesPerWg)) continue;
+    if (!tile_coords<kGM, kGN>(tiles_m, tiles_n, panel, &tile_m, &tile_n, it, kTilesPerWg)) continue;
     dz_tile(tile_m, tile_n, W, H, d, V, rowsel, c0, mc, lse_c, a_c, kz_c, dZ, Vp, tile_n, lds);
   }
 }
@@ -1562,6 +1562,17 @@ void launch_finalize(int64_t rows, int64_t n_sel, hipStream_t st, Args... args) 
   else hipLaunchKernelGGL(k_score_finalize<false>, dim3(cdiv(rows, 32)), dim3(256), 0, st, args...);
 }
 
+// Row tiles that the logit kernels work through together (see tile_coords): an XCD reads all rows of H once for every four
+// vocabulary tiles, all XCDs at about the same time, so a panel that stays in the memory-side cache (256 MB) comes from HBM once
+// instead of nineteen times.  40 960 rows of 3584 (293 MB), score: all rows 33.4 ms, panels of at most 40 / 64 / 96 / 128 / 160
+// MiB 31.5 / 30.6 / 30.7 / 30.5 / 30.7; 24 576 rows kept 20.6 -> 19.3 ms; 40 960 rows of 2048 (168 MB) 18.2 either way.
+constexpr int64_t kPanelBytes = int64_t{128} << 20;
+int row_panel(int tiles_n, int d) {
+  const int most = std::max(static_cast<int>(kPanelBytes / (static_cast<int64_t>(Cfg::BN) * d * 2)) / kGN * kGN, kGN);
+  const int panels = (tiles_n + most - 1) / most;
+  return ((tiles_n + panels - 1) / panels + kGN - 1) / kGN * kGN;
+}
+
 // Forward scoring of the selected rows into compact arrays and/or scattered outputs.  float32: `room` holds statistics of
 // parts of the vocabulary (no room: one workgroup per 32 rows walks all of it), rest_c goes with the compact arrays.
 umas_status run_score(const void* H, const void* W, umas_dtype dt, int d, int V, const int32_t* ids,
@@ -1583,14 +1594,14 @@ umas_status run_score(const void* H, const void* W, umas_dtype dt, int d, int V,
     } else if (n_sel <= NarrowCfg::BN) {                     // ceil(V / 128) 128 <= ceil(V / 256) 256: the partials fit as well
       n_pad = NarrowCfg::BN;
       tiles_m = (V + NarrowCfg::BM - 1) / NarrowCfg::BM;
-      hipLaunchKernelGGL(k_score_narrow, dim3(tile_grid<kGM, kGN>(tiles_m, 1, kTilesPerWg)), dim3(NarrowCfg::T), 0, st,
+      hipLaunchKernelGGL(k_score_narrow, dim3(tile_grid<kGM, kGN>(tiles_m, 1, kGN, kTilesPerWg)), dim3(NarrowCfg::T), 0, st,
                          static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), d, V, rowsel, n_sel, ids,
-                         tiles_m, 1, w.partial, n_pad);
+                         tiles_m, 1, kGN, w.partial, n_pad);
       UMAS_LAUNCHED("k_score_narrow");
     } else {
-      hipLaunchKernelGGL(k_score_tiles, dim3(tile_grid<kGM, kGN>(tiles_m, tiles_n, kTilesPerWg)), dim3(Cfg::T), 0, st,
+      hipLaunchKernelGGL(k_score_tiles, dim3(tile_grid<kGM, kGN>(tiles_m, tiles_n, row_panel(tiles_n, d), kTilesPerWg)), dim3(Cfg::T), 0, st,
                          static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), d, V, rowsel, n_sel, ids,
-                         tiles_m, tiles_n, w.partial, n_pad);
+                         tiles_m, tiles_n, row_panel(tiles_n, d), w.partial, n_pad);
       UMAS_LAUNCHED("k_score_tiles");
     }
     launch_finalize(n_sel, n_sel, st, w.partial, tiles_m, n_pad, static_cast<int64_t>(0), n_sel, static_cast<const float*>(nullptr), rowsel, ids, V,
@@ -1847,8 +1858,8 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, static_cast<int>(c0 >> 8), tiles_r, rows, kl_coef != 0.f ? 1 : 0, tiles_v,
                          tiles_d, Vp, sl.n, w.blk_live, w.blk_cidx, w.blk_orig, w.live);   // a KL term gives every row a gradient
       UMAS_LAUNCHED("k_live_scan");
-      hipLaunchKernelGGL(k_score_keep_tiles, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, kTilesPerWg)), dim3(Cfg::T), 0, st,
-                         Wb, Hb, d, V, rowsel, c0, rows, ids, tiles_v, tiles_r, w.score.partial, n_pad, w.cref, E, Vp, w.flags,
+      hipLaunchKernelGGL(k_score_keep_tiles, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, row_panel(tiles_r, d), kTilesPerWg)), dim3(Cfg::T), 0, st,
+                         Wb, Hb, d, V, rowsel, c0, rows, ids, tiles_v, tiles_r, row_panel(tiles_r, d), w.score.partial, n_pad, w.cref, E, Vp, w.flags,
                          w.blk_cidx);
       UMAS_LAUNCHED("k_score_keep_tiles");
       launch_finalize(rows, n_sel, st, w.score.partial, tiles_v, n_pad, c0, c0 + rows, w.cref, rowsel, ids, V, w.score.logp_c, w.score.lse_c,
@@ -1907,8 +1918,8 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     const int64_t mcp = round_up(rows, 256);
     uint16_t* dZ = reinterpret_cast<uint16_t*>(w.chunk);
     const int tiles_v = static_cast<int>(Vp / 256), tiles_r = static_cast<int>(mcp / 256), tiles_d = (d + 255) / 256;
-    hipLaunchKernelGGL(k_dz_tiles, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, kTilesPerWg)), dim3(Cfg::T), 0, st, Wb, Hb, d, V, rowsel,
-                       c0, rows, w.score.lse_c, w.a_c, w.kz_c, tiles_v, tiles_r, dZ, Vp);
+    hipLaunchKernelGGL(k_dz_tiles, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, row_panel(tiles_r, d), kTilesPerWg)), dim3(Cfg::T), 0, st, Wb, Hb, d, V, rowsel,
+                       c0, rows, w.score.lse_c, w.a_c, w.kz_c, tiles_v, tiles_r, row_panel(tiles_r, d), dZ, Vp);
     UMAS_LAUNCHED("k_dz_tiles");
     uint16_t* Hs = reinterpret_cast<uint16_t*>(w.chunk + align_up(static_cast<size_t>(mcp) * Vp * 2));
     hipLaunchKernelGGL(k_dz_rows, dim3(cdiv(rows, 4)), dim3(256), 0, st, Hb, d, V, rowsel, c0, rows, ids, dZ, static_cast<int64_t>(tiles_v), Hs,

@@ -229,6 +229,37 @@ def test_scoring_of_many_rows(n_sel):
 
 # the one-hot rows of dW: one group of 128 rows spread over many workgroups, several groups over a few, every row the same
 # token and every row another; and statistics per role when a wavefront holds one role, many, and roles outside the range
+# more rows than a panel of the logit kernels holds (32 tiles of 8192 columns): two panels of 24 and of 9 tiles, three of 24
+@pytest.mark.parametrize("n,V", [(8193, 600), (16641, 1300)])
+@pytest.mark.parametrize("entropy_coef", [None, 0.0, 0.01])
+def test_rows_beyond_a_panel(n, V, entropy_coef):
+    d = 8192
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    H = torch.randn(n, d, device="cuda", generator=gen).bfloat16()
+    W = (0.02 * torch.randn(V, d, device="cuda", generator=gen)).bfloat16()
+    ids = torch.randint(0, V, (n,), device="cuda", generator=gen, dtype=torch.int32)
+    z = H.double() @ W.double().T
+    p = torch.softmax(z, 1)
+    lse = torch.logsumexp(z, 1)
+    logp = z.gather(1, ids.long()[:, None])[:, 0] - lse
+    entropy = lse - (p * z).sum(1)
+    # float32 sums of d products in any order: a random walk of d roundings of the terms' size, four deviations
+    bound = 4 * d ** 0.5 * 2.0 ** -24 * float((H[:256].double().abs() @ W.double().abs().T).max())
+    if entropy_coef is None:
+        for got, want in zip(umas.umas_policy_logprobs(H, W, ids), (logp, lse, entropy)):
+            assert float((got.double() - want).abs().max()) <= bound
+        return
+    adv = torch.randn(n, device="cuda", generator=gen)
+    _, logp_new, dH, dW = umas.umas_ppo_loss_fwd_bwd(H, W, ids, None, None, adv, None, 0, 0.2, entropy_coef=entropy_coef)
+    assert float((logp_new.double() - logp).abs().max()) <= bound
+    k = entropy_coef / n                                             # on-policy: ratio 1, g = -adv / n
+    dz = p * (adv.double()[:, None] / n + k * (z - (lse - entropy)[:, None]))
+    dz.scatter_add_(1, ids.long()[:, None], -adv.double()[:, None] / n)
+    # every product carries two roundings to bf16 (2^-8 together at most), random in sign
+    for got, want in ((dH, dz @ W.double()), (dW, dz.T @ H.double())):
+        assert float((got.double() - want).norm() / want.norm()) <= 2.0 ** -8
+
+
 @pytest.mark.parametrize("n,n_tokens", [(1, 1), (127, 1), (129, 129), (700, 3), (5000, 400)])
 def test_one_hot_rows_and_statistics_per_role(n, n_tokens):
     rng = np.random.default_rng(n)
