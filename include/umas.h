@@ -224,7 +224,8 @@ typedef struct {
 /* Smallest workspace the call accepts and the size at which it runs in the fewest passes.  For bf16 the
  * workspace holds, per chunk of selected rows, the bf16 operand of the two gradient products
  * [rows, V] (rounded up to multiples of 256) and a scaled bf16 copy of the chunk's rows of H; the
- * smallest size runs in chunks of 256 rows, the full size in chunks of up to 65536 rows.  Where there is little of dH to
+ * smallest size runs in chunks of 256 rows, the full size in chunks of up to 65536 rows; it also holds the float32
+ * logits that an update with an entropy bonus keeps (of all rows up to 6 GiB, else of half a chunk).  Where there is little of dH to
  * work on at a time (ceil(rows / 256) ceil(d / 256) blocks: a selection of fewer than 256, or chunks of fewer than 128) it is
  * summed over slices of the vocabulary, as many as the workspace has room for: there the rounding of dH depends on the
  * size of the workspace, and the full size holds the float32 partial sums.  Larger selections have the same bits of dH with
@@ -264,9 +265,9 @@ size_t umas_ppo_loss_workspace_bytes(int64_t n_sel, int32_t d, int32_t V, umas_d
  * per (row, vocabulary entry) pair to the workspace and the two gradient products read that [rows, V] matrix back
  * (2 * rows * V bytes: 11.9 GB for 39 224 rows against V = 151 936 in one chunk).  With entropy_coef = 0 the
  * matrix holds the softmax numerators exp(z - z_y), written by the scoring pass itself, so the logits are computed
- * once; with an entropy bonus it holds dz, written by a second pass over the logits.  The float32 logits are
- * never stored, but a [rows, V] operand does pass through HBM; only umas_policy_logprobs keeps everything of that
- * shape on chip.  The workspace bounds it: the call works in chunks of as many rows as the workspace holds (256
+ * once; with an entropy bonus it holds dz, which overwrites the float32 logits that the scoring pass leaves there (4 *
+ * rows * V bytes) where the workspace has room for them, and is written by a second pass over the logits where it has
+ * not.  Only umas_policy_logprobs keeps everything of that shape on chip.  The workspace bounds it: the call works in chunks of as many rows as the workspace holds (256
  * at the least), at the price of one more pass over W per chunk.  The float32 path stores float32 dz per chunk. */
 umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_dtype dtype, int64_t n_rows,
                                   int32_t d, int32_t V, const int32_t* ids, const int32_t* rowsel,

@@ -13,8 +13,9 @@
 // Without an entropy bonus the dense part of dz is a row factor times the softmax, so the scoring pass of
 // the update itself leaves that operand behind: E = bf16(exp(z - z_y)), the softmax numerators relative to
 // the taken token's logit, and the row factor -g exp(z_y - lse) is applied where dH is written and folded
-// into the copy of H that dW reads; the logits are computed once.  With an entropy bonus (and for blocks
-// of rows whose logits spread too far for E) dz is recomputed tile by tile from H, W and lse instead.
+// into the copy of H that dW reads; the logits are computed once.  With an entropy bonus the
+// scoring pass leaves the float32 logits behind, which one pass over them turns into dz; in a workspace without room
+// for them (and for blocks of rows whose logits spread too far for E) dz is recomputed tile by tile from H, W and lse.
 // The float32 path, for small shapes, carries its sums in float64 (umas_f32.h).
 #include <math.h>
 
@@ -57,7 +58,7 @@ __device__ __forceinline__ Part part_merge(Part x, Part y) {
   if (y.m == kNegInf) return x;
   const float M = fmaxf(x.m, y.m);
   const float ex = __expf(x.m - M), ey = __expf(y.m - M);
-  return Part{M, x.s * ex + y.s * ey, x.t * ex + y.t * ey};
+  return Part{M, fmaf(x.s, ex, y.s * ey), fmaf(x.t, ex, y.t * ey)};   // written out: the same rounding in every kernel
 }
 
 // ------------------------------------------------------------------ small helpers
@@ -138,24 +139,29 @@ __host__ __device__ __forceinline__ int64_t blk_offset(int64_t row_blk, int64_t 
 constexpr int kStagePitch = Cfg::WTM * 2 + 16;                                  // one staged row: 128 bf16, 16-byte aligned
 constexpr int kStageBytes = Cfg::WM * Cfg::WN * Cfg::WTN * kStagePitch;         // every wavefront stages its block: 64 rows x 128 vocabulary entries
 constexpr int kPartBytes = (Cfg::WM * Cfg::BN * 3 + Cfg::BN) * 4;
+constexpr int kLogitPitch = Cfg::WTM * 4 + 16;                                  // one staged row of logits: 128 floats
+static_assert(16 * kLogitPitch <= Cfg::WTN * kStagePitch, "sixteen rows of logits fit a wavefront's stage");
 static_assert(kStageBytes + kPartBytes <= kLogitLds, "staging and the partials fit the tile buffers");
 static_assert(kLogitLds <= 160 * 1024, "LDS of one CU");
 
+enum class Leave { kNothing, kNumerators, kLogits };   // what a scoring pass leaves behind for the backward
 struct KeepArgs {
   const float* cref;   // [n_pad] reference per selected row, NaN for rows without a valid id
   uint16_t* E;         // [mcp, Vp]
   int64_t Vp;
   int32_t* flags;      // per block of 256 selected rows
   const int32_t* cidx; // per block of 256 selected rows: its place among the chunk's live blocks, -1 for a dead one
+  float* Z;            // Leave::kLogits: the logits, in blocks of 256 x 256 floats in the place and order of the operand's blocks
 };
 
-template <bool KEEP, class C>
+template <Leave LEAVE, class C>
 __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
                                             const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc,
                                             const int32_t* __restrict__ ids, int tiles_m, int tiles_n, int panel,
                                             float4* __restrict__ partial, int64_t n_pad, const KeepArgs& keep,
                                             uint16_t* lds) {
-  static_assert(!KEEP || C::BM * C::BN == Cfg::BM * Cfg::BN, "kept numerators lie in whole blocks");
+  constexpr bool KEEP = LEAVE == Leave::kNumerators;
+  static_assert(LEAVE == Leave::kNothing || C::BM * C::BN == Cfg::BM * Cfg::BN, "what is kept lies in whole blocks");
   for (int it = 0; it < kTilesPerWg; ++it) {     // a workgroup walks the same place of kTilesPerWg consecutive tile groups
   int tile_m, tile_n;
   if (!tile_coords<kGM, kGN>(tiles_m, tiles_n, panel, &tile_m, &tile_n, it, kTilesPerWg)) continue;
@@ -166,11 +172,11 @@ __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, cons
 
   // epilogue: the tile buffers are free now.  A lane holds, for each of its NI columns (selected rows), the
   // vocabulary entries vbase + 16 i + r (i < MI, r < 4); the four lanes l, l + 16, l + 32, l + 48 share a column.
-  float* s_part = reinterpret_cast<float*>(reinterpret_cast<char*>(lds) + (KEEP ? kStageBytes : 0));   // [WM][BN][3], behind the staging area
+  float* s_part = reinterpret_cast<float*>(reinterpret_cast<char*>(lds) + (LEAVE == Leave::kNothing ? 0 : kStageBytes));   // [WM][BN][3], behind the staging area
   float* s_zy = s_part + C::WM * C::BN * 3;               // [BN]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / C::WN;
-  char* stage = reinterpret_cast<char*>(lds) + wave * (C::WTN * kStagePitch);
+  char* stage = reinterpret_cast<char*>(lds) + wave * (LEAVE == Leave::kLogits ? 16 * kLogitPitch : C::WTN * kStagePitch);
   if (threadIdx.x < C::BN) s_zy[threadIdx.x] = 0.f;
   __syncthreads();                                        // every wavefront has left the main loop's LDS reads
   const int vbase = m0 + wm * C::WTM + (lane >> 4) * 4;   // vocabulary id of element (i = 0, r = 0)
@@ -250,6 +256,20 @@ __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, cons
       m = lane_max();
       column(m, std::false_type{});
     }
+    if (LEAVE == Leave::kLogits) {
+      // sixteen rows of 128 logits through the wavefront's part of LDS, so that a store covers 512 bytes of two rows
+#pragma unroll
+      for (int i = 0; i < C::MI; ++i)
+        *reinterpret_cast<floatx4*>(stage + (lane & 15) * kLogitPitch + (i * 16 + (lane >> 4) * 4) * 4) = acc[i][j];
+      __builtin_amdgcn_wave_barrier();
+      float* out = keep.Z + blk_offset(tile_n, tile_m, keep.Vp >> 8) + (wave % C::WN * C::WTN + j * 16 + (lane >> 5)) * 256 + wm * C::WTM + (lane & 31) * 4;
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (n0 + wave % C::WN * C::WTN + j * 16 + q * 2 + (lane >> 5) < mc)   // rows past the chunk: nobody reads them
+          __builtin_nontemporal_store(*reinterpret_cast<const floatx4*>(stage + (q * 2 + (lane >> 5)) * kLogitPitch + (lane & 31) * 16),
+                                      reinterpret_cast<floatx4*>(out + q * 512));
+      __builtin_amdgcn_wave_barrier();
+    }
     Part p{m, s, t};
 #pragma unroll
     for (int o = 16; o < kWave; o <<= 1) {
@@ -308,7 +328,7 @@ k_score_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, in
               const int32_t* __restrict__ rowsel, int64_t n_sel, const int32_t* __restrict__ ids,
               int tiles_m, int tiles_n, int panel, float4* __restrict__ partial, int64_t n_pad) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[kLogitLds / 2];
-  score_tiles<false, Cfg>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{}, lds);
+  score_tiles<Leave::kNothing, Cfg>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{}, lds);
 }
 // Up to 128 selected rows: half-size tiles with a pipeline of their own, two workgroups to a compute unit, so that one
 // fills its stages while the other multiplies (64 rows of 2048 / 3584 against 151 936: 156 / 215 us against 182 / 274 with
@@ -320,7 +340,7 @@ k_score_narrow(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, i
                const int32_t* __restrict__ rowsel, int64_t n_sel, const int32_t* __restrict__ ids,
                int tiles_m, int tiles_n, int panel, float4* __restrict__ partial, int64_t n_pad) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[kNarrowLds / 2];
-  score_tiles<false, NarrowCfg>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{}, lds);
+  score_tiles<Leave::kNothing, NarrowCfg>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{}, lds);
 }
 __global__ void __launch_bounds__(Cfg::T)
 k_score_keep_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
@@ -329,7 +349,14 @@ k_score_keep_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ 
                    const float* __restrict__ cref, uint16_t* __restrict__ E, int64_t Vp, int32_t* __restrict__ flags,
                    const int32_t* __restrict__ cidx) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[kLogitLds / 2];
-  score_tiles<true, Cfg>(W, H, d, V, rowsel, c0, mc, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{cref, E, Vp, flags, cidx}, lds);
+  score_tiles<Leave::kNumerators, Cfg>(W, H, d, V, rowsel, c0, mc, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{cref, E, Vp, flags, cidx, nullptr}, lds);
+}
+__global__ void __launch_bounds__(Cfg::T)
+k_score_logits(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
+               const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc, const int32_t* __restrict__ ids,
+               int tiles_m, int tiles_n, int panel, float4* __restrict__ partial, int64_t n_pad, float* __restrict__ Z, int64_t Vp) {
+  __shared__ __attribute__((aligned(16))) uint16_t lds[kLogitLds / 2];
+  score_tiles<Leave::kLogits, Cfg>(W, H, d, V, rowsel, c0, mc, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{nullptr, nullptr, Vp, nullptr, nullptr, Z}, lds);
 }
 
 // ------------------------------------------------------------------ bf16: a few rows
@@ -851,7 +878,8 @@ k_keep_rows(const uint16_t* __restrict__ H, int d, int V, const int32_t* __restr
 }
 
 // ------------------------------------------------------------------ bf16: dz tiles into the chunk buffer
-// Same tile product as k_score_tiles; the epilogue forms the dense part of dz = g (onehot - softmax),
+// For blocks of rows whose numerators do not serve, and with an entropy bonus in a small workspace (16 100 rows of 2048 in 2 GB,
+// chunks of 3300: 31.3 ms; chunks of logits of half that many rows would add to dW twice as often).  Same tile product as k_score_tiles; the epilogue forms the dense part of dz = g (onehot - softmax),
 // -g exp(z - lse), plus the entropy bonus's term when its coefficient is not 0, and writes it as bf16 to
 // dZ [mcp, Vp].  Rows past the chunk and vocabulary ids past V get 0.  The one-hot part g at v = y is a single term per row and is added in
 // float32 where dH and dW are written, so that it never meets the bf16 rounding of the dense part.
@@ -949,19 +977,71 @@ k_dz_flagged(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int
   }
 }
 
+// dz from the logits that k_score_logits has left, in place: a block of 256 x 256 floats becomes bf16 in its first half (so
+// the operand's blocks lie two block lengths apart).  A workgroup turns one block, 32 rows at a time, a row to a wavefront's
+// load; a group of rows is written once all wavefronts have what lies there and in front of it in registers, and the
+// next one is on its way meanwhile.  Bound by the 6 bytes a logit that are read and written: 16 100 rows against 151 936 in 2.75
+// ms (5.3 TB/s).  With the logits stored (1.05 ms more for the scoring pass) instead of computed twice, and so these two in place
+// of 7.6 ms of k_dz_tiles, that update takes 27.0 ms in two chunks instead of 30.2; 203 rows of 3584 1.21 instead of 1.43.
+constexpr int kTurnRows = 32, kTurnWaves = 4, kRowsPerWave = kTurnRows / kTurnWaves;
+__global__ void __launch_bounds__(kTurnWaves * kWave)
+k_dz_from_logits(float* Z, int tiles_v, int64_t c0, int64_t mc, const float* __restrict__ lse_c, const float* __restrict__ a_c,
+                 const float* __restrict__ kz_c) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t n0 = static_cast<int64_t>(blockIdx.x / tiles_v) * 256;     // chunk-relative
+  float* const blk = Z + static_cast<int64_t>(blockIdx.x) * kBlkElems;
+  uint16_t* const out = reinterpret_cast<uint16_t*>(blk);
+  floatx4 z[2][kRowsPerWave];
+  auto fetch = [&](int g, floatx4 (&x)[kRowsPerWave]) {
+#pragma unroll
+    for (int r = 0; r < kRowsPerWave; ++r) {
+      const int row = g * kTurnRows + wave * kRowsPerWave + r;
+      x[r] = floatx4{0.f, 0.f, 0.f, 0.f};
+      if (n0 + row < mc) x[r] = __builtin_nontemporal_load(reinterpret_cast<const floatx4*>(blk + row * 256 + lane * 4));
+    }
+  };
+  fetch(0, z[0]);
+#pragma unroll
+  for (int g = 0; g < 256 / kTurnRows; ++g) {
+    // this group has arrived: its registers are taken as used here, or the loads could sink below the barrier and meet what
+    // another wavefront has written there
+#pragma unroll
+    for (int r = 0; r < kRowsPerWave; ++r) asm volatile("" : "+v"(z[g & 1][r]) : : "memory");
+    __syncthreads();
+    if (g + 1 < 256 / kTurnRows) fetch(g + 1, z[(g + 1) & 1]);
+#pragma unroll
+    for (int r = 0; r < kRowsPerWave; ++r) {
+      const int row = g * kTurnRows + wave * kRowsPerWave + r;
+      float l2 = 1e30f, a = 0.f, kz = 0.f;                                 // rows past the chunk: 0
+      if (n0 + row < mc) {
+        l2 = lse_c[c0 + n0 + row] * 1.44269504088896341f;
+        a = a_c[c0 + n0 + row];
+        kz = kz_c[c0 + n0 + row];
+      }
+      float dz[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float x = z[g & 1][r][k];
+        dz[k] = __builtin_amdgcn_exp2f(fmaf(x, 1.44269504088896341f, -l2)) * fmaf(kz, x, a);
+      }
+      *reinterpret_cast<uint2*>(out + row * 256 + lane * 4) = make_uint2(pack_bf16x2(dz[0], dz[1]), pack_bf16x2(dz[2], dz[3]));
+    }
+  }
+}
+
 // What the gradient products need besides dZ: the taken token's entry of every row is cleared (that column goes through
 // g_c in float32, see k_ppo_rows), and the row of H goes to the operand that dW reads, in the column blocks of k_keep_rows.
 // One wavefront per row.  (dW reading the rows through the selection: two kinds of loads in flight, whose waits have to be
 // for all of them, 16 100 rows of 2048: both products 16.3 ms, with the copy, 25 us, 14.9.)
 __global__ void __launch_bounds__(256)
 k_dz_rows(const uint16_t* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel, int64_t c0, int64_t rows,
-          const int32_t* __restrict__ ids, uint16_t* __restrict__ dZ, int64_t tiles_v, uint16_t* __restrict__ Hs, int64_t mcp) {
+          const int32_t* __restrict__ ids, uint16_t* __restrict__ dZ, int64_t tiles_v, int blk_pitch, uint16_t* __restrict__ Hs, int64_t mcp) {
   const int lane = threadIdx.x & 63;
   const int64_t m = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave;
   if (m >= rows) return;
   const int64_t row = rowsel ? rowsel[c0 + m] : c0 + m;
   const int y = ids[row];
-  if (lane == 0 && y >= 0 && y < V) dZ[blk_offset(m >> 8, y >> 8, tiles_v) + (m & 255) * 256 + (y & 255)] = 0;
+  if (lane == 0 && y >= 0 && y < V) dZ[blk_offset(m >> 8, y >> 8, tiles_v) * blk_pitch + (m & 255) * 256 + (y & 255)] = 0;
   const uint4* h = reinterpret_cast<const uint4*>(H + row * d);
   for (int k = lane; k < d / 8; k += kWave) reinterpret_cast<uint4*>(Hs + (static_cast<int64_t>(k >> 5) * mcp + m) * 256)[k & 31] = h[k];
 }
@@ -982,10 +1062,10 @@ __device__ __forceinline__ void zero_acc(floatx4 (&acc)[C::MI][C::NI]) {
 // K-contiguous operand tile: block row `row_blk` of the blocked [rows, vocabulary] operand from vocabulary block `voc_blk`
 // on; K runs over the vocabulary, four steps of 64 per block
 template <class C>
-__device__ __forceinline__ KContig blocked_rows_tile(const uint16_t* X, int64_t tiles_v, int64_t row_blk, int voc_blk) {
+__device__ __forceinline__ KContig blocked_rows_tile(const uint16_t* X, int blk_pitch, int64_t tiles_v, int64_t row_blk, int voc_blk) {
   KContig c;
-  c.rsrc = make_rsrc(X + blk_offset(row_blk, voc_blk, tiles_v));
-  c.hi_bytes = static_cast<uint32_t>(kBlkElems * 2 - 4 * 128);        // from the fourth step of a block to the next block
+  c.rsrc = make_rsrc(X + blk_offset(row_blk, voc_blk, tiles_v) * blk_pitch);
+  c.hi_bytes = static_cast<uint32_t>(kBlkElems * 2 * blk_pitch - 4 * 128);        // from the fourth step of a block to the next block
   const int tid = tile_thread();
   const uint32_t kofs = ring2_kofs(tid);
 #pragma unroll
@@ -1070,7 +1150,7 @@ struct DhSlices {
 };
 // tile_m counts the chunk's live blocks of rows; orig_blk is the block's place in the chunk
 __device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, int slice, const DhSlices& sl, int tiles_r, int tiles_d,
-                                        const uint16_t* __restrict__ dZ, int64_t Vp,
+                                        const uint16_t* __restrict__ dZ, int blk_pitch, int64_t Vp,
                                         const uint16_t* __restrict__ W, int d, int V, uint16_t* __restrict__ dH,
                                         const int32_t* __restrict__ rowsel, int64_t c0, int64_t rows,
                                         const int32_t* __restrict__ ids, const float* __restrict__ g_c,
@@ -1080,7 +1160,7 @@ __device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, in
   const int n0 = tile_n * C::BN;
   const int voc_blk = slice * sl.voc_blks, tiles_v = static_cast<int>(Vp >> 8);
   const int k_len = min(sl.voc_blks, tiles_v - voc_blk) * 256;       // a multiple of 256, at least 256
-  const KContig ca = blocked_rows_tile<C>(dZ, tiles_v, tile_m, voc_blk);
+  const KContig ca = blocked_rows_tile<C>(dZ, blk_pitch, tiles_v, tile_m, voc_blk);
   KMajor kb;
   kb.base = reinterpret_cast<const char*>(W + static_cast<int64_t>(voc_blk) * 256 * d + n0);
   kb.ld_bytes = static_cast<int64_t>(d) * 2;
@@ -1139,16 +1219,16 @@ __device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, in
 // Hs: the rows of H that go with the rows of dZ (scaled by the keeping pass), in column blocks [d / 256][mcp][256] so that a
 // tile's k-rows are one run of memory
 // k_len: rows of the packed [rows, V] operand (a multiple of 256, 0 when no block is live); rows: those that exist
-__device__ __forceinline__ void dw_tile(int tile_m, int tile_n, const uint16_t* __restrict__ dZ, int64_t mcp, int64_t Vp,
+__device__ __forceinline__ void dw_tile(int tile_m, int tile_n, const uint16_t* __restrict__ dZ, int blk_pitch, int64_t mcp, int64_t Vp,
                                         const uint16_t* __restrict__ Hs, int d, int V, int k_len, int rows, float* __restrict__ dW,
                                         int accumulate, uint16_t* lds) {
   using C = Cfg;
   const int64_t m0 = static_cast<int64_t>(tile_m) * C::BM;
   const int n0 = tile_n * C::BN;
   KMajor ka;                                                         // blocked dZ: k = row of the chunk, entries = vocabulary
-  ka.base = reinterpret_cast<const char*>(dZ + blk_offset(0, tile_m, Vp >> 8));
+  ka.base = reinterpret_cast<const char*>(dZ + blk_offset(0, tile_m, Vp >> 8) * blk_pitch);
   ka.ld_bytes = 512;
-  ka.hi_bytes = (Vp >> 8) * kBlkElems * 2 - 256 * 512;               // from the last row of a block to the block below
+  ka.hi_bytes = (Vp >> 8) * kBlkElems * 2 * blk_pitch - 256 * 512;               // from the last row of a block to the block below
   ka.k_rows = k_len;
   ka.n_units = 32;
   KMajor kb;                                                         // rows of H: k = row of the chunk, entries = hidden columns
@@ -1174,7 +1254,7 @@ __device__ __forceinline__ void dw_tile(int tile_m, int tile_n, const uint16_t* 
 // its end goes on with the one that has most left.  203 rows of 3584 1316 -> 845 us, 64 rows of 2048 841 -> 455, 725 rows
 // 1098 -> 930, 2000 rows of 3584 3.93 -> 3.52 ms, 39 000 rows of 2048 37.5 -> 36.5 ms.
 __global__ void __launch_bounds__(Cfg::T)
-k_gemm_dh_dw(const uint16_t* __restrict__ dZ, int64_t Vp, int64_t mcp, const uint16_t* __restrict__ W,
+k_gemm_dh_dw(const uint16_t* __restrict__ dZ, int blk_pitch, int64_t Vp, int64_t mcp, const uint16_t* __restrict__ W,
              const uint16_t* __restrict__ Hs, int d, int V, int tiles_v,
              int tiles_d, DhSlices sl, int tiles_r, LiveInfo* __restrict__ info, const int32_t* __restrict__ blk_orig,
              uint16_t* __restrict__ dH, float* __restrict__ dW, int accumulate, const int32_t* __restrict__ rowsel,
@@ -1225,10 +1305,10 @@ k_gemm_dh_dw(const uint16_t* __restrict__ dZ, int64_t Vp, int64_t mcp, const uin
     if (seq < n_dh) {
       const int t = first_dh + seq, slice = t / tiles_mn;
       tile_of_groups<kGM, kGN>(t - slice * tiles_mn, n_live, tiles_d, &tile_m, &tile_n);
-      dh_tile(tile_m, blk_orig[(c0 >> 8) + tile_m], tile_n, slice, sl, tiles_r, tiles_d, dZ, Vp, W, d, V, dH, rowsel, c0, rows, ids, g_c, sc, lds);
+      dh_tile(tile_m, blk_orig[(c0 >> 8) + tile_m], tile_n, slice, sl, tiles_r, tiles_d, dZ, blk_pitch, Vp, W, d, V, dH, rowsel, c0, rows, ids, g_c, sc, lds);
     } else {
       tile_of_groups<kGM, kGN>(first_dw + seq - n_dh, tiles_v, tiles_d, &tile_m, &tile_n);
-      dw_tile(tile_m, tile_n, dZ, mcp, Vp, Hs, d, V, n_live * 256, k_rows, dW, accumulate, lds);
+      dw_tile(tile_m, tile_n, dZ, blk_pitch, mcp, Vp, Hs, d, V, n_live * 256, k_rows, dW, accumulate, lds);
     }
   }
 }
@@ -1438,6 +1518,10 @@ size_t chunk_bytes(int64_t mc, int d, int V, umas_dtype dt) {
   const int64_t Vp = round_up(V, 256), mcp = round_up(mc, 256);
   return align_up(static_cast<size_t>(mcp) * Vp * 2) + align_up(static_cast<size_t>(mcp) * round_up(d, 256) * 2);
 }
+// bytes one chunk of mc rows needs whose float32 logits are kept in place of the operand (entropy bonus)
+size_t logit_chunk_bytes(int64_t mc, int d, int V) {
+  return chunk_bytes(mc, d, V, UMAS_BF16) + static_cast<size_t>(round_up(mc, 256)) * round_up(V, 256) * 2;
+}
 // How the dH product of a chunk is cut along the vocabulary.  dH has tiles_r x tiles_d tiles of the whole vocabulary's K
 // each; with few row tiles that is fewer long tiles than compute units, and the launch lasts as long as one of them (3.6 ms
 // at V = 151 936 whether there are 64 rows or 2000).  Below kDhSliceTiles, one tile per compute unit, they are cut into about
@@ -1465,6 +1549,25 @@ DhPlan plan_dh(int64_t tiles_r, int64_t tiles_d, int tiles_v, size_t room) {
   if (want < 2) return DhPlan{1, tiles_v};
   const int blks = (tiles_v + want - 1) / want;
   return DhPlan{(tiles_v + blks - 1) / blks, blks};
+}
+// partial sums of as many slices as are wanted
+size_t full_part_bytes(int64_t n_sel, int64_t chunk_rows, int d, int V) {
+  if (!slices_dh(n_sel, chunk_rows, d)) return 0;
+  const int tiles_r = static_cast<int>(cdiv(chunk_rows, 256)), tiles_d = (d + 255) / 256;
+  return dh_part_bytes(plan_dh(tiles_r, tiles_d, (V + 255) / 256, SIZE_MAX), tiles_r, tiles_d);
+}
+// The update with an entropy bonus keeps the logits of a chunk in float32 instead of computing them a second time where the
+// workspace has room for chunks that are not small: the whole selection, or chunks whose dH tiles are whole ones (the same bits
+// of dH as from larger workspaces).  0: it has not, the logits are computed twice.
+constexpr size_t kLogitBytes = size_t{6} << 30;            // what the workspace is sized for (a second chunk adds to dW: 0.5 ms)
+int64_t logit_chunk_rows(int64_t n_sel, int d, int V, size_t room) {
+  if (round_up(V, 256) / 256 > 8192) return 0;             // 32-bit offsets along a row of blocks
+  if (dh_tiles(n_sel, d) < kDhSliceTiles) return logit_chunk_bytes(n_sel, d, V) + full_part_bytes(n_sel, n_sel, d, V) <= room ? n_sel : 0;
+  const int64_t fit = std::min(static_cast<int64_t>(room / logit_chunk_bytes(256, d, V)) * 256, kMaxChunkRows);
+  if (fit >= n_sel) return n_sel;
+  if (fit == 0) return 0;
+  const int64_t nchunk = (n_sel + fit - 1) / fit, mc = round_up((n_sel + nchunk - 1) / nchunk, 256);
+  return dh_tiles(mc, d) >= kDhSliceTiles / 2 ? mc : 0;
 }
 size_t carve_ppo(Carver& c, PpoWs& w, int64_t n_sel, int d, int V, umas_dtype dt, int n_roles) {
   (void)d;                                      // the per-chunk buffers depend on d, the fixed part does not
@@ -1731,12 +1834,11 @@ extern "C" size_t umas_ppo_loss_workspace_bytes(int64_t n_sel, int32_t d, int32_
     const int64_t nchunk = (mc + cap - 1) / cap;
     mc = round_up((mc + nchunk - 1) / nchunk, 256);
   }
-  size_t part = 0;
-  if (dtype == UMAS_BF16 && slices_dh(n_sel, mc, d)) {
-    const int tiles_r = static_cast<int>(round_up(mc, 256) / 256), tiles_d = (d + 255) / 256;
-    part = dh_part_bytes(plan_dh(tiles_r, tiles_d, (V + 255) / 256, SIZE_MAX), tiles_r, tiles_d);
-  }
-  return c.off + chunk_bytes(mc, d, V, dtype) + part;
+  // with an entropy bonus: the logits of the whole selection, of half a chunk where they are many
+  size_t chunk = chunk_bytes(mc, d, V, dtype);
+  if (dtype == UMAS_BF16)
+    chunk = std::max(chunk, logit_chunk_bytes(mc >= n_sel && logit_chunk_bytes(mc, d, V) <= kLogitBytes ? mc : round_up((mc + 1) / 2, 256), d, V));
+  return c.off + chunk + (dtype == UMAS_BF16 ? full_part_bytes(n_sel, mc, d, V) : 0);
 }
 
 extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_dtype dtype, int64_t n_rows, int32_t d,
@@ -1806,18 +1908,18 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
 
   // both gradient products of the chunk of `rows` rows from c0 on, and what the slices of dH leave; the partial sums lie
   // behind the chunk's operands or, once the scoring pass's own partials have been merged, in their place
-  auto dh_plan = [&](int64_t rows, DhSlices* sl) {
+  auto dh_plan = [&](int64_t rows, size_t used, DhSlices* sl) {
     const int tiles_r = static_cast<int>(cdiv(rows, 256)), tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
-    const size_t used = chunk_bytes(rows, d, V, dtype), behind = room > used ? room - used : 0;
+    const size_t behind = room > used ? room - used : 0;
     const size_t front = static_cast<size_t>(reinterpret_cast<char*>(w.score.logp_c) - reinterpret_cast<char*>(w.score.partial));
     const DhPlan p = plan_dh(tiles_r, tiles_d, tiles_v, slices_dh(n_sel, mc, d) ? std::max(behind, front) : 0);
     *sl = DhSlices{p.slices, p.voc_blks, behind > front ? reinterpret_cast<float*>(w.chunk + used) : reinterpret_cast<float*>(w.score.partial)};
   };
-  auto gradients = [&](int64_t c0, int64_t rows, const DhSlices& sl, const uint16_t* op, const uint16_t* Hs, const float* sc) -> umas_status {
+  auto gradients = [&](int64_t c0, int64_t rows, const DhSlices& sl, const uint16_t* op, int blk_pitch, const uint16_t* Hs, const float* sc) -> umas_status {
     const int64_t mcp = round_up(rows, 256);
     const int tiles_r = static_cast<int>(mcp / 256), tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
     const unsigned grid = static_cast<unsigned>(round_up(device_cus(), 8));      // every XCD's sequence needs somebody
-    hipLaunchKernelGGL(k_gemm_dh_dw, dim3(grid), dim3(Cfg::T), 0, st, op, Vp, mcp, Wb, Hs, d, V, tiles_v,
+    hipLaunchKernelGGL(k_gemm_dh_dw, dim3(grid), dim3(Cfg::T), 0, st, op, blk_pitch, Vp, mcp, Wb, Hs, d, V, tiles_v,
                        tiles_d, sl, tiles_r, w.live, w.blk_orig, static_cast<uint16_t*>(dH), dW, (accumulate_dW || c0 > 0) ? 1 : 0,
                        rowsel, c0, rows, ids, w.g_c, sc);
     UMAS_LAUNCHED("k_gemm_dh_dw");
@@ -1829,16 +1931,25 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     return UMAS_OK;
   };
 
-  if (!keep) {
+  // With one the logits are kept instead where the workspace allows it.
+  const int64_t mc_z = dtype == UMAS_BF16 && !keep && n_sel > 0 ? logit_chunk_rows(n_sel, d, V, room) : 0;
+  if (mc_z > 0) mc = mc_z;
+  auto ppo_rows = [&](int64_t c0, int64_t c1) -> umas_status {
+    hipLaunchKernelGGL(k_ppo_rows, dim3(std::max(cdiv(c1 - c0, kRowBlock), 1u)), dim3(kRowBlock), kPpoLds, st, norm, c0, c1, rowsel, ids, V,
+                       w.score.logp_c, w.score.ent_c, logp_old, adv, tok_role, n_roles, clip_eps, dual_clip, k_ent, logp_ref, kl_coef,
+                       dtype == UMAS_BF16 ? 1 : 0, w.score.lse_c, w.g_c, w.a_c, w.kz_c, w.blk_stats);
+    UMAS_LAUNCHED("k_ppo_rows");
+    return UMAS_OK;
+  };
+
+  if (mc_z > 0) {
+    // chunk by chunk, further down
+  } else if (!keep) {
     // forward scoring and the surrogate
     s = run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w.score, w.chunk, room, w.rest, logp_new, nullptr, nullptr, st);
     if (s != UMAS_OK) return s;
-    hipLaunchKernelGGL(k_ppo_rows, dim3(nblk), dim3(kRowBlock), kPpoLds, st, norm,
-                       static_cast<int64_t>(0), n_sel, rowsel, ids, V, w.score.logp_c, w.score.ent_c, logp_old, adv,
-                       tok_role, n_roles, clip_eps, dual_clip, k_ent, logp_ref, kl_coef, dtype == UMAS_BF16 ? 1 : 0, w.score.lse_c,
-                       w.g_c, w.a_c, w.kz_c,
-                       w.blk_stats);
-    UMAS_LAUNCHED("k_ppo_rows");
+    s = ppo_rows(0, n_sel);
+    if (s != UMAS_OK) return s;
   } else {
     OpenArgs O{Hb, Wb, d, V, rowsel, n_sel, ids, adv, nblk, w.blk_live, w.flags, w.cref, static_cast<uint32_t*>(dH),
                n_rows * static_cast<int64_t>(d) / 2, rowsel ? logp_new : nullptr, n_rows};
@@ -1854,7 +1965,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       uint16_t* E = reinterpret_cast<uint16_t*>(w.chunk);
       uint16_t* Hs = reinterpret_cast<uint16_t*>(w.chunk + align_up(static_cast<size_t>(mcp) * Vp * 2));
       DhSlices sl;
-      dh_plan(rows, &sl);
+      dh_plan(rows, chunk_bytes(rows, d, V, dtype), &sl);
       hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, static_cast<int>(c0 >> 8), tiles_r, rows, kl_coef != 0.f ? 1 : 0, tiles_v,
                          tiles_d, Vp, sl.n, w.blk_live, w.blk_cidx, w.blk_orig, w.live);   // a KL term gives every row a gradient
       UMAS_LAUNCHED("k_live_scan");
@@ -1865,10 +1976,8 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       launch_finalize(rows, n_sel, st, w.score.partial, tiles_v, n_pad, c0, c0 + rows, w.cref, rowsel, ids, V, w.score.logp_c, w.score.lse_c,
                       w.score.ent_c, logp_new, static_cast<float*>(nullptr), static_cast<float*>(nullptr));
       UMAS_LAUNCHED("k_score_finalize");
-      hipLaunchKernelGGL(k_ppo_rows, dim3(cdiv(rows, kRowBlock)), dim3(kRowBlock), kPpoLds, st, norm, c0, c0 + rows, rowsel, ids, V, w.score.logp_c, w.score.ent_c, logp_old, adv, tok_role,
-                         n_roles, clip_eps, dual_clip, k_ent, logp_ref, kl_coef, 1, w.score.lse_c, w.g_c, w.a_c, w.kz_c,
-                         w.blk_stats);
-      UMAS_LAUNCHED("k_ppo_rows");
+      s = ppo_rows(c0, c0 + rows);
+      if (s != UMAS_OK) return s;
       // blocks of rows the scoring pass flagged (a logit far above the row's reference) get dz the long way
       hipLaunchKernelGGL(k_dz_flagged, dim3(kFlaggedGrid), dim3(Cfg::T), 0, st, Wb, Hb, d, V, rowsel, c0, rows,
                          w.score.lse_c, w.a_c, w.kz_c, tiles_v, tiles_r, E, Vp, w.flags, w.blk_cidx);
@@ -1876,12 +1985,19 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       hipLaunchKernelGGL(k_keep_rows, dim3(cdiv(rows, 4)), dim3(256), 0, st, Hb, d, V, rowsel, c0, rows, ids, E,
                          static_cast<int64_t>(tiles_v), w.score.lse_c, w.a_c, w.cref, w.flags, w.blk_cidx, w.sc, Hs, mcp);
       UMAS_LAUNCHED("k_keep_rows");
-      s = gradients(c0, rows, sl, E, Hs, w.sc);
+      s = gradients(c0, rows, sl, E, 1, Hs, w.sc);
       if (s != UMAS_OK) return s;
     }
   }
-  hipLaunchKernelGGL(k_ppo_stats, dim3(1 + n_roles), dim3(256), 0, st, nblk, n_roles, entropy_coef, norm_rows, w.blk_stats, stats);
-  UMAS_LAUNCHED("k_ppo_stats");
+  auto ppo_stats = [&]() -> umas_status {
+    hipLaunchKernelGGL(k_ppo_stats, dim3(1 + n_roles), dim3(256), 0, st, nblk, n_roles, entropy_coef, norm_rows, w.blk_stats, stats);
+    UMAS_LAUNCHED("k_ppo_stats");
+    return UMAS_OK;
+  };
+  if (mc_z == 0) {
+    s = ppo_stats();
+    if (s != UMAS_OK) return s;
+  }
   if (n_sel == 0) return UMAS_OK;
   if (keep) {
     hipLaunchKernelGGL(k_dw_onehot, onehot_grid(n_sel), dim3(256), 0, st, Hb, d, rowsel, n_sel, ids, w.g_c, dW);
@@ -1918,20 +2034,40 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     const int64_t mcp = round_up(rows, 256);
     uint16_t* dZ = reinterpret_cast<uint16_t*>(w.chunk);
     const int tiles_v = static_cast<int>(Vp / 256), tiles_r = static_cast<int>(mcp / 256), tiles_d = (d + 255) / 256;
-    hipLaunchKernelGGL(k_dz_tiles, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, row_panel(tiles_r, d), kTilesPerWg)), dim3(Cfg::T), 0, st, Wb, Hb, d, V, rowsel,
-                       c0, rows, w.score.lse_c, w.a_c, w.kz_c, tiles_v, tiles_r, row_panel(tiles_r, d), dZ, Vp);
-    UMAS_LAUNCHED("k_dz_tiles");
-    uint16_t* Hs = reinterpret_cast<uint16_t*>(w.chunk + align_up(static_cast<size_t>(mcp) * Vp * 2));
-    hipLaunchKernelGGL(k_dz_rows, dim3(cdiv(rows, 4)), dim3(256), 0, st, Hb, d, V, rowsel, c0, rows, ids, dZ, static_cast<int64_t>(tiles_v), Hs,
-                       mcp);
+    const int blk_pitch = mc_z > 0 ? 2 : 1, panel = row_panel(tiles_r, d);
+    if (mc_z > 0) {
+      hipLaunchKernelGGL(k_score_logits, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, panel, kTilesPerWg)), dim3(Cfg::T), 0, st, Wb, Hb, d, V,
+                         rowsel, c0, rows, ids, tiles_v, tiles_r, panel, w.score.partial, round_up(n_sel, Cfg::BN),
+                         reinterpret_cast<float*>(w.chunk), Vp);
+      UMAS_LAUNCHED("k_score_logits");
+      launch_finalize(rows, n_sel, st, w.score.partial, tiles_v, round_up(n_sel, Cfg::BN), c0, c0 + rows, static_cast<const float*>(nullptr), rowsel,
+                      ids, V, w.score.logp_c, w.score.lse_c, w.score.ent_c, logp_new, static_cast<float*>(nullptr), static_cast<float*>(nullptr));
+      UMAS_LAUNCHED("k_score_finalize");
+      s = ppo_rows(c0, c0 + rows);
+      if (s != UMAS_OK) return s;
+      hipLaunchKernelGGL(k_dz_from_logits, dim3(static_cast<unsigned>(tiles_v * tiles_r)), dim3(kTurnWaves * kWave), 0, st,
+                         reinterpret_cast<float*>(w.chunk), tiles_v, c0, rows, w.score.lse_c, w.a_c, w.kz_c);
+      UMAS_LAUNCHED("k_dz_from_logits");
+    } else {
+      hipLaunchKernelGGL(k_dz_tiles, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, panel, kTilesPerWg)), dim3(Cfg::T), 0, st, Wb, Hb, d, V, rowsel,
+                         c0, rows, w.score.lse_c, w.a_c, w.kz_c, tiles_v, tiles_r, panel, dZ, Vp);
+      UMAS_LAUNCHED("k_dz_tiles");
+    }
+    uint16_t* Hs = reinterpret_cast<uint16_t*>(w.chunk + align_up(static_cast<size_t>(mcp) * Vp * 2 * blk_pitch));
+    hipLaunchKernelGGL(k_dz_rows, dim3(cdiv(rows, 4)), dim3(256), 0, st, Hb, d, V, rowsel, c0, rows, ids, dZ, static_cast<int64_t>(tiles_v),
+                       blk_pitch, Hs, mcp);
     UMAS_LAUNCHED("k_dz_rows");
     // with an entropy bonus every row has a gradient: all blocks are live
     DhSlices sl;
-    dh_plan(rows, &sl);
+    dh_plan(rows, mc_z > 0 ? logit_chunk_bytes(rows, d, V) : chunk_bytes(rows, d, V, dtype), &sl);
     hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, static_cast<int>(c0 >> 8), tiles_r, rows, 1, tiles_v, tiles_d, Vp, sl.n,
                        w.blk_live, w.blk_cidx, w.blk_orig, w.live);
     UMAS_LAUNCHED("k_live_scan");
-    s = gradients(c0, rows, sl, dZ, Hs, nullptr);
+    s = gradients(c0, rows, sl, dZ, blk_pitch, Hs, nullptr);
+    if (s != UMAS_OK) return s;
+  }
+  if (mc_z > 0) {
+    s = ppo_stats();
     if (s != UMAS_OK) return s;
   }
   hipLaunchKernelGGL(k_dw_onehot, onehot_grid(n_sel), dim3(256), 0, st, Hb, d, rowsel, n_sel, ids, w.g_c, dW);

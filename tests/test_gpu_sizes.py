@@ -115,6 +115,41 @@ def test_large_updates_do_not_depend_on_the_workspace(n, d, V, rows, entropy_coe
         assert torch.equal(lp, logp) and ((dH.float() - first.float()).abs() <= bound).all()
 
 
+# with an entropy bonus the logits are kept where the workspace has room for them: all rows at once, chunks of at least 128 tiles of
+# dH (rows x hidden size), and fewer rows only when they are the whole selection; else they are computed twice.  The same bits
+@pytest.mark.parametrize("n,d,V,fits", [(32 * 256 - 3, 2048, 700, {0: 1, 256: 0, 15 * 256: 0, 16 * 256: 2, 31 * 256: 2, 32 * 256: 1}),
+                                        (700, 264, 3001, {0: 1, 256: 0})])
+def test_kept_logits_and_logits_computed_twice_give_the_same(n, d, V, fits):
+    pad = lambda x: -(-x // 256) * 256
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    H = torch.randn(n, d, device="cuda", generator=gen).bfloat16()
+    W = (torch.randn(V, d, device="cuda", generator=gen) / d ** 0.5).bfloat16()
+    ids = torch.randint(0, V, (n,), device="cuda", generator=gen, dtype=torch.int32)
+    adv = torch.randn(n, device="cuda", generator=gen)
+    sliced = pad(n) // 256 * (pad(d) // 256) < 256
+    results = {}
+    for fit, chunks in fits.items():
+        ws = None
+        if fit:
+            nbytes = umas.ppo_workspace_bytes(n, d, V, torch.bfloat16, 0, minimum=True) + fit * (4 * pad(V) + 2 * pad(d)) - 512 * (pad(V) + pad(d))
+            ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda").fill_(255)     # old contents: NaN
+        umas.profile_enable(True)
+        try:
+            stats, logp, dH, dW = umas.umas_ppo_loss_fwd_bwd(H, W, ids, None, None, adv, None, 0, 0.2, entropy_coef=0.01, workspace=ws)
+            names = umas.profile_read()
+        finally:
+            umas.profile_enable(False)
+        assert names.get("k_score_logits", (0, 0))[1] == chunks and ("k_dz_tiles" in names) == (chunks == 0), (fit, names)
+        results[fit] = umas.read_stats(stats)["loss"][0], logp, dH, dW
+    first, *others = results.values()
+    for loss, logp, dH, dW in others:
+        assert loss == first[0] and torch.equal(logp, first[1])
+        assert sliced or torch.equal(dH, first[2])
+        # dW: the same products, added up over one chunk or several (float32)
+        assert float((dW - first[3]).norm()) <= 2.0 ** -20 * float(first[3].norm())
+        assert float((dH.float() - first[2].float()).norm()) <= 2.0 ** -8 * float(first[2].float().norm())
+
+
 @pytest.mark.parametrize("n,d,V", [(300, 64, 3000), (700, 1288, 5121)])
 def test_updates_do_not_depend_on_the_address_of_dh(n, d, V):
     (a, _), (b, _), (c, _) = updates(n, d, V, [(None, 0), (None, 2), (None, 4)])
