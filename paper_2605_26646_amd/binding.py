@@ -1,7 +1,8 @@
-"""ctypes binding of libumas.so (argument marshalling only)."""
+"""Binding of libumas.so: the entry points, whose argument marshalling is native (csrc/umas_torch.cpp), and the C ABI through ctypes."""
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from dataclasses import dataclass
 from typing import Optional
@@ -130,8 +131,59 @@ def load_library():
                                           C.c_int32, C.c_float, C.c_float, C.c_float, C.c_int32, C.c_int64, C.c_void_p,
                                           C.c_float, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t,
                                           C.c_void_p]
+    lib.umas_policy_logprobs_static.restype = C.c_int
+    lib.umas_policy_logprobs_static.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int64, C.c_int32, C.c_int32,
+                                                C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p,
+                                                C.c_void_p]
+    lib.umas_values.restype = C.c_int
+    lib.umas_values.argtypes = [C.c_void_p, C.c_void_p, C.c_float, C.c_int, C.c_int64, C.c_int32, C.c_void_p, C.c_int64,
+                                C.c_void_p, C.c_void_p]
+    lib.umas_value_workspace_bytes.restype = C.c_size_t
+    lib.umas_value_workspace_bytes.argtypes = [C.c_int64, C.c_int32, C.c_int, C.c_int32]
+    lib.umas_value_loss_fwd_bwd.restype = C.c_int
+    lib.umas_value_loss_fwd_bwd.argtypes = [C.c_void_p, C.c_void_p, C.c_float, C.c_int, C.c_int64, C.c_int32, C.c_void_p,
+                                            C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_float, C.c_int32,
+                                            C.c_int32, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
+                                            C.c_void_p, C.c_size_t, C.c_void_p]
+    lib.umas_kl_rewards_workspace_bytes.restype = C.c_size_t
+    lib.umas_kl_rewards_workspace_bytes.argtypes = [C.c_int64]
+    lib.umas_kl_rewards.restype = C.c_int
+    lib.umas_kl_rewards.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_float, C.c_void_p,
+                                    C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
+    lib.umas_whiten_workspace_bytes.restype = C.c_size_t
+    lib.umas_whiten_workspace_bytes.argtypes = [C.c_int64, C.c_int32, C.c_int32]
+    lib.umas_whiten_advantages.restype = C.c_int
+    lib.umas_whiten_advantages.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_int64,
+                                           C.c_int32, C.c_float, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
+    lib.umas_ready_batch_workspace_bytes.restype = C.c_size_t
+    lib.umas_ready_batch_workspace_bytes.argtypes = [C.c_int32, C.c_int32]
+    for fn in (lib.umas_ready_batch, lib.umas_ready_batch_balanced):
+        fn.restype = C.c_int
+        fn.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p,
+                       C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
+    lib.umas_ready_batch_packed.restype = C.c_int
+    lib.umas_ready_batch_packed.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p,
+                                            C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
     _LIB = lib
     return lib
+
+
+_NATIVE = None
+
+
+def _native():
+    """The native half of this module (csrc/umas_torch.cpp), built next to libumas.so; there is no fallback when it is missing."""
+    global _NATIVE
+    if _NATIVE is None:
+        load_library()
+        path = os.path.join(_HERE, "_umas_torch.so")
+        if not os.path.exists(path):
+            raise FileNotFoundError(f"{path} is missing: build it with `python -c 'import __graft_entry__ as g; g.build()'`")
+        spec = importlib.util.spec_from_file_location("_umas_torch", path)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        _NATIVE = module
+    return _NATIVE
 
 
 def _check(lib, status: int):
@@ -139,30 +191,15 @@ def _check(lib, status: int):
         raise UmasError(status, lib.umas_last_error().decode())
 
 
-def _host(arr, dtype):
-    """Contiguous host array of the ABI's type, or None; returns (array kept alive, pointer)."""
-    if arr is None:
-        return None, None
-    a = np.ascontiguousarray(arr, dtype=dtype)
-    return a, a.ctypes.data
-
-
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else t.data_ptr()
-
-
-def _sel_ptr(rowsel: Optional[torch.Tensor]):
-    """Pointer of a row selection; an empty selection still needs a non-NULL pointer (NULL means all rows)."""
-    if rowsel is None:
-        return None, None
-    if rowsel.numel() == 0:
-        dummy = torch.zeros(1, dtype=torch.int32, device=rowsel.device)
-        return dummy, dummy.data_ptr()
-    return rowsel, rowsel.data_ptr()
+def _done(result):
+    """The native module returns the outputs, or the status when the library refuses."""
+    if type(result) is int:
+        _check(load_library(), result)
+    return result
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 # Row selections are device data that the library cannot check.  With CHECK_ROWS on (the test suite switches it on)
@@ -172,100 +209,31 @@ def _stream():
 CHECK_ROWS = False
 
 
-def _check_rows(rowsel: Optional[torch.Tensor], n_rows: int):
+def _check_rows(rowsel: Optional[torch.Tensor], H: torch.Tensor):
     if not CHECK_ROWS or rowsel is None or rowsel.numel() == 0 or torch.cuda.is_current_stream_capturing():
         return
-    lo, hi = int(rowsel.min().item()), int(rowsel.max().item())
+    lo, hi, n_rows = int(rowsel.min().item()), int(rowsel.max().item()), H.shape[0]
     if lo < 0 or hi >= n_rows:
         raise UmasError(-1, f"row selection holds entries from {lo} to {hi}, outside [0, {n_rows})")
-
-
-def _workspace(nbytes: int, device) -> torch.Tensor:
-    return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
-
-
-def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return UMAS_F32
-    if t.dtype == torch.bfloat16:
-        return UMAS_BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
 
 
 def umas_assign_token_rewards(*, n_roles, n_models, role_to_model, traj_turn_off, turn_role, turn_tok_off,
                               tok_mask_global: torch.Tensor, turn_pred_off=None, turn_pred=None, traj_group=None,
                               role_reward=None, turn_reward=None, traj_reward=None, w_role=None, w_turn=None,
                               w_traj=None, place_mode=PLACE_LAST, norm_eps=1e-6) -> Streams:
-    lib = load_library()
-    keep = []
-
-    def h(a, dt):
-        arr, p = _host(a, dt)
-        keep.append(arr)
-        return p
-
-    traj_turn_off = np.asarray(traj_turn_off)
-    turn_tok_off = np.asarray(turn_tok_off)
-    n_traj, n_turns = len(traj_turn_off) - 1, len(turn_tok_off) - 1
-    n_tokens = int(tok_mask_global.numel())
-    g = _Graph(n_roles, n_models, n_traj, n_turns, n_tokens, h(role_to_model, np.int32), h(traj_turn_off, np.int32),
-               h(turn_role, np.int32), h(turn_tok_off, np.int64), h(turn_pred_off, np.int32), h(turn_pred, np.int32),
-               h(traj_group, np.int32))
-    r = _Rewards(h(role_reward, np.float32), h(turn_reward, np.float32), h(traj_reward, np.float32),
-                 h(w_role, np.float32), h(w_turn, np.float32), h(w_traj, np.float32), place_mode, norm_eps)
-    dev = tok_mask_global.device
-    i64 = dict(dtype=torch.int64, device=dev)
-    i32 = dict(dtype=torch.int32, device=dev)
-    f32 = dict(dtype=torch.float32, device=dev)
-    out = Streams(
-        n_tokens=n_tokens, n_turns=n_turns, n_models=n_models,
-        model_tok_off=torch.empty(n_models + 1, **i64), perm=torch.empty(n_tokens, **i64),
-        tok_turn=torch.empty(n_tokens, **i32), tok_role=torch.empty(n_tokens, **i32),
-        tok_mask=torch.empty(n_tokens, dtype=torch.uint8, device=dev), tok_reward=torch.empty(n_tokens, **f32),
-        turn_seg_off=torch.empty(n_turns + 1, **i64), seg_turn=torch.empty(max(n_turns, 1), **i32),
-        model_turn_off=torch.empty(n_models + 1, **i32), traj_seg_off=torch.empty(n_turns + 1, **i64),
-        model_trajrun_off=torch.empty(n_models + 1, **i32), rowsel=torch.empty(max(n_tokens, 1), **i32),
-        model_rowsel_off=torch.empty(n_models + 1, **i64), turn_scalar=torch.empty(max(n_turns, 1), **f32),
-        turn_step=torch.empty(max(n_turns, 1), **i32),
-        tok_flags=torch.empty(n_tokens, dtype=torch.uint8, device=dev))
-    ws = _workspace(lib.umas_assign_workspace_bytes(C.addressof(g)), dev)
-    cs = out._c()
-    _check(lib, lib.umas_assign_token_rewards(C.addressof(g), C.addressof(r), _ptr(tok_mask_global) or _dummy(dev).data_ptr(), C.addressof(cs),
-                                              ws.data_ptr(), ws.numel(), _stream()))
-    return out
+    return Streams(*_done(_native().assign(n_roles, n_models, role_to_model, traj_turn_off, turn_role, turn_tok_off, tok_mask_global,
+                                           turn_pred_off, turn_pred, traj_group, role_reward, turn_reward, traj_reward, w_role,
+                                           w_turn, w_traj, place_mode, norm_eps, _stream())))
 
 
 def umas_advantages(streams: Streams, value: Optional[torch.Tensor], gamma, lam, gamma_turn=1.0, seg_mode=SEG_TURN):
-    lib = load_library()
-    dev = streams.tok_reward.device
-    adv = torch.empty(streams.n_tokens, dtype=torch.float32, device=dev)
-    ret = torch.empty(streams.n_tokens, dtype=torch.float32, device=dev)
-    ws = _workspace(lib.umas_advantages_workspace_bytes(streams.n_tokens), dev)
-    cs = streams._c()
-    _check(lib, lib.umas_advantages(C.addressof(cs), streams.n_tokens, streams.n_turns, _ptr(value), gamma, lam,
-                                    gamma_turn, seg_mode, adv.data_ptr(), ret.data_ptr(), ws.data_ptr(), ws.numel(),
-                                    _stream()))
-    return adv, ret
+    return _done(_native().advantages(streams, value, gamma, lam, gamma_turn, seg_mode, _stream()))
 
 
 def umas_policy_logprobs(H: torch.Tensor, W: torch.Tensor, ids: torch.Tensor, rowsel: Optional[torch.Tensor] = None,
                          want_entropy=True, workspace: Optional[torch.Tensor] = None):
-    lib = load_library()
-    n_rows, d = H.shape
-    V = W.shape[0]
-    n_sel = n_rows if rowsel is None else int(rowsel.numel())
-    dt = _dtype_code(H)
-    dev = H.device
-    logp = torch.empty(n_rows, dtype=torch.float32, device=dev)
-    lse = torch.empty(n_rows, dtype=torch.float32, device=dev)
-    ent = torch.empty(n_rows, dtype=torch.float32, device=dev) if want_entropy else None
-    ws = workspace if workspace is not None else _workspace(lib.umas_policy_logprobs_workspace_bytes(n_sel, d, V, dt), dev)
-    _check_rows(rowsel, n_rows)
-    _keep, sel = _sel_ptr(rowsel)
-    _check(lib, lib.umas_policy_logprobs(H.data_ptr(), W.data_ptr(), dt, n_rows, d, V, ids.data_ptr(), sel,
-                                         n_sel, logp.data_ptr(), lse.data_ptr(), _ptr(ent), ws.data_ptr(), ws.numel(),
-                                         _stream()))
-    return logp, lse, ent
+    _check_rows(rowsel, H)
+    return _done(_native().policy_logprobs(H, W, ids, rowsel, want_entropy, workspace, _stream()))
 
 
 STATIC_SCRATCH_BYTES = 32 << 20
@@ -275,26 +243,8 @@ def umas_policy_logprobs_static(H: torch.Tensor, W: torch.Tensor, ids: torch.Ten
                                 logp=None, lse=None, entropy=None):
     """umas_policy_logprobs without a workspace (the library's static scratch); the outputs may be passed in, so that
     the call itself allocates nothing."""
-    lib = load_library()
-    lib.umas_policy_logprobs_static.restype = C.c_int
-    lib.umas_policy_logprobs_static.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int64, C.c_int32, C.c_int32,
-                                                C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p,
-                                                C.c_void_p]
-    n_rows, d = H.shape
-    V = W.shape[0]
-    n_sel = n_rows if rowsel is None else int(rowsel.numel())
-    dev = H.device
-    if logp is None:
-        logp = torch.empty(n_rows, dtype=torch.float32, device=dev)
-    if lse is None:
-        lse = torch.empty(n_rows, dtype=torch.float32, device=dev)
-    if entropy is None:
-        entropy = torch.empty(n_rows, dtype=torch.float32, device=dev)
-    _check_rows(rowsel, n_rows)
-    _keep, sel = _sel_ptr(rowsel)
-    _check(lib, lib.umas_policy_logprobs_static(H.data_ptr(), W.data_ptr(), _dtype_code(H), n_rows, d, V, ids.data_ptr(),
-                                                sel, n_sel, logp.data_ptr(), lse.data_ptr(), entropy.data_ptr(), _stream()))
-    return logp, lse, entropy
+    _check_rows(rowsel, H)
+    return _done(_native().policy_logprobs_static(H, W, ids, rowsel, logp, lse, entropy, _stream()))
 
 
 def ppo_workspace_bytes(n_sel, d, V, dtype: torch.dtype, n_roles, minimum=False) -> int:
@@ -307,31 +257,9 @@ def ppo_workspace_bytes(n_sel, d, V, dtype: torch.dtype, n_roles, minimum=False)
 def umas_ppo_loss_fwd_bwd(H, W, ids, rowsel, logp_old, adv, tok_role, n_roles, clip_eps, *, entropy_coef=0.0,
                           dual_clip=0.0, accumulate_dW=False, norm_rows=0, logp_ref=None, kl_coef=0.0, dW=None, dH=None,
                           logp_new=None, stats=None, workspace=None):
-    lib = load_library()
-    n_rows, d = H.shape
-    V = W.shape[0]
-    n_sel = n_rows if rowsel is None else int(rowsel.numel())
-    dt = _dtype_code(H)
-    dev = H.device
-    if dW is None:
-        dW = torch.empty((V, d), dtype=torch.float32, device=dev)
-    if dH is None:
-        dH = torch.empty_like(H)
-    if logp_new is None:
-        logp_new = torch.empty(n_rows, dtype=torch.float32, device=dev)
-    if stats is None:
-        stats = torch.empty((1 + n_roles) * STATS_DTYPE.itemsize, dtype=torch.uint8, device=dev)
-    ws = workspace if workspace is not None else _workspace(
-        lib.umas_ppo_loss_workspace_bytes(n_sel, d, V, dt, n_roles), dev)
-    _check_rows(rowsel, n_rows)
-    _keep, sel = _sel_ptr(rowsel)
-    _check(lib, lib.umas_ppo_loss_fwd_bwd(H.data_ptr(), W.data_ptr(), dt, n_rows, d, V, ids.data_ptr(), sel,
-                                          n_sel, _ptr(logp_old), adv.data_ptr(), _ptr(tok_role), n_roles,
-                                          clip_eps, entropy_coef, dual_clip, 1 if accumulate_dW else 0, int(norm_rows),
-                                          _ptr(logp_ref), kl_coef, stats.data_ptr(),
-                                          logp_new.data_ptr(), dH.data_ptr(), dW.data_ptr(), ws.data_ptr(), ws.numel(),
-                                          _stream()))
-    return stats, logp_new, dH, dW
+    _check_rows(rowsel, H)
+    return _done(_native().ppo_loss(H, W, ids, rowsel, logp_old, adv, tok_role, n_roles, clip_eps, entropy_coef, dual_clip, accumulate_dW,
+                                    norm_rows, logp_ref, kl_coef, dW, dH, logp_new, stats, workspace, _stream()))
 
 
 VALUE_STATS_DTYPE = np.dtype([("loss", "<f4"), ("clip_frac", "<f4"), ("value_mean", "<f4"), ("reserved", "<f4"),
@@ -339,53 +267,16 @@ VALUE_STATS_DTYPE = np.dtype([("loss", "<f4"), ("clip_frac", "<f4"), ("value_mea
 
 
 def umas_values(H, w, bias=0.0, rowsel=None, value=None):
-    lib = load_library()
-    lib.umas_values.restype = C.c_int
-    lib.umas_values.argtypes = [C.c_void_p, C.c_void_p, C.c_float, C.c_int, C.c_int64, C.c_int32, C.c_void_p, C.c_int64,
-                                C.c_void_p, C.c_void_p]
-    n_rows, d = H.shape
-    n_sel = n_rows if rowsel is None else int(rowsel.numel())
-    if value is None:
-        value = torch.empty(n_rows, dtype=torch.float32, device=H.device)
-    _check_rows(rowsel, n_rows)
-    _keep, sel = _sel_ptr(rowsel)
-    _check(lib, lib.umas_values(_ptr(H), w.data_ptr(), bias, _dtype_code(H), n_rows, d, sel, n_sel, _ptr(value), _stream()))
-    return value
+    _check_rows(rowsel, H)
+    return _done(_native().values(H, w, bias, rowsel, value, _stream()))
 
 
 def umas_value_loss_fwd_bwd(H, w, bias, rowsel, value_old, ret, tok_role, n_roles, clip_eps_v, *, accumulate_dH=False,
                             accumulate_dw=False, norm_rows=0, dH=None, dw=None, db=None, value_new=None, stats=None,
                             workspace=None):
-    lib = load_library()
-    lib.umas_value_workspace_bytes.restype = C.c_size_t
-    lib.umas_value_workspace_bytes.argtypes = [C.c_int64, C.c_int32, C.c_int, C.c_int32]
-    lib.umas_value_loss_fwd_bwd.restype = C.c_int
-    lib.umas_value_loss_fwd_bwd.argtypes = [C.c_void_p, C.c_void_p, C.c_float, C.c_int, C.c_int64, C.c_int32, C.c_void_p,
-                                            C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_float, C.c_int32,
-                                            C.c_int32, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
-                                            C.c_void_p, C.c_size_t, C.c_void_p]
-    n_rows, d = H.shape
-    n_sel = n_rows if rowsel is None else int(rowsel.numel())
-    dt = _dtype_code(H)
-    dev = H.device
-    if dH is None:
-        dH = torch.empty_like(H)
-    if dw is None:
-        dw = torch.empty(d, dtype=torch.float32, device=dev)
-    if db is None:
-        db = torch.empty(1, dtype=torch.float32, device=dev)
-    if value_new is None:
-        value_new = torch.empty(n_rows, dtype=torch.float32, device=dev)
-    if stats is None:
-        stats = torch.empty((1 + n_roles) * VALUE_STATS_DTYPE.itemsize, dtype=torch.uint8, device=dev)
-    ws = workspace if workspace is not None else _workspace(lib.umas_value_workspace_bytes(n_sel, d, dt, n_roles), dev)
-    _check_rows(rowsel, n_rows)
-    _keep, sel = _sel_ptr(rowsel)
-    _check(lib, lib.umas_value_loss_fwd_bwd(_ptr(H), w.data_ptr(), bias, dt, n_rows, d, sel, n_sel, _ptr(value_old),
-                                            _ptr(ret), _ptr(tok_role), n_roles, clip_eps_v, 1 if accumulate_dH else 0,
-                                            1 if accumulate_dw else 0, int(norm_rows), stats.data_ptr(), _ptr(value_new), _ptr(dH),
-                                            dw.data_ptr(), db.data_ptr(), ws.data_ptr(), ws.numel(), _stream()))
-    return stats, value_new, dH, dw, db
+    _check_rows(rowsel, H)
+    return _done(_native().value_loss(H, w, bias, rowsel, value_old, ret, tok_role, n_roles, clip_eps_v, accumulate_dH, accumulate_dw,
+                                      norm_rows, dH, dw, db, value_new, stats, workspace, _stream()))
 
 
 WHITEN_MODEL, WHITEN_MODEL_ROLE = 0, 1
@@ -393,93 +284,23 @@ WHITEN_MODEL, WHITEN_MODEL_ROLE = 0, 1
 
 def umas_kl_rewards(tok_reward, logp, logp_ref, tok_mask, beta, out=None):
     """Returns (penalised rewards, device float[1] mean of logp - logp_ref over the mask=1 tokens)."""
-    lib = load_library()
-    lib.umas_kl_rewards_workspace_bytes.restype = C.c_size_t
-    lib.umas_kl_rewards_workspace_bytes.argtypes = [C.c_int64]
-    lib.umas_kl_rewards.restype = C.c_int
-    lib.umas_kl_rewards.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int64, C.c_float, C.c_void_p,
-                                    C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
-    n = int(tok_reward.numel())
-    dev = tok_reward.device
-    if out is None:
-        out = torch.empty_like(tok_reward)
-    kl = torch.empty(1, dtype=torch.float32, device=dev)
-    ws = _workspace(lib.umas_kl_rewards_workspace_bytes(n), dev)
-    d = _dummy(dev).data_ptr()
-    p = (lambda t: t.data_ptr() if n else d)
-    _check(lib, lib.umas_kl_rewards(p(tok_reward), p(logp), p(logp_ref), p(tok_mask), n, beta, p(out), kl.data_ptr(),
-                                    ws.data_ptr(), ws.numel(), _stream()))
-    return out, kl
+    return _done(_native().kl_rewards(tok_reward, logp, logp_ref, tok_mask, beta, out, _stream()))
 
 
 def umas_whiten_advantages(adv, tok_mask, tok_role, model_tok_off, n_roles, scope=WHITEN_MODEL, eps=1e-8, out=None):
-    lib = load_library()
-    lib.umas_whiten_workspace_bytes.restype = C.c_size_t
-    lib.umas_whiten_workspace_bytes.argtypes = [C.c_int64, C.c_int32, C.c_int32]
-    lib.umas_whiten_advantages.restype = C.c_int
-    lib.umas_whiten_advantages.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_int64,
-                                           C.c_int32, C.c_float, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
-    n = int(adv.numel())
-    dev = adv.device
-    off_keep, off_ptr = _host(model_tok_off, np.int64)
-    n_models = len(off_keep) - 1
-    if out is None:
-        out = torch.empty_like(adv)
-    ws = _workspace(lib.umas_whiten_workspace_bytes(n, n_models, n_roles), dev)
-    d = _dummy(dev).data_ptr()
-    p = (lambda t: None if t is None else (t.data_ptr() if n else d))
-    _check(lib, lib.umas_whiten_advantages(p(adv), p(tok_mask), p(tok_role), off_ptr, n_models, n_roles, n, scope, eps,
-                                           p(out), ws.data_ptr(), ws.numel(), _stream()))
-    return out
+    return _done(_native().whiten(adv, tok_mask, tok_role, model_tok_off, n_roles, scope, eps, out, _stream()))
 
 
 def umas_ready_batch(streams: Streams, traj_turn_off, n_minibatch, traj_keep=None, traj_order=None, balance_rows=False):
     """Returns (mb_rowsel device int32, mb_off device int64 [n_models, n_minibatch + 1]); balance_rows selects
     umas_ready_batch_balanced (parts cut by scored rows per model instead of by trajectories)."""
-    lib = load_library()
-    lib.umas_ready_batch_workspace_bytes.restype = C.c_size_t
-    lib.umas_ready_batch_workspace_bytes.argtypes = [C.c_int32, C.c_int32]
-    fn = lib.umas_ready_batch_balanced if balance_rows else lib.umas_ready_batch
-    fn.restype = C.c_int
-    fn.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p,
-                   C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
-    dev = streams.rowsel.device
-    tto_keep, tto = _host(traj_turn_off, np.int32)
-    n_traj = len(tto_keep) - 1
-    keep_keep, keep = _host(traj_keep, np.uint8)
-    order_keep, order = _host(traj_order, np.int32)
-    mb_rowsel = torch.empty(max(int(streams.rowsel.numel()), 1), dtype=torch.int32, device=dev)
-    mb_off = torch.empty((streams.n_models, n_minibatch + 1), dtype=torch.int64, device=dev)
-    ws = _workspace(lib.umas_ready_batch_workspace_bytes(n_traj, streams.n_models), dev)
-    cs = streams._c()
-    _check(lib, fn(C.addressof(cs), streams.n_models, streams.n_turns, tto, n_traj, keep, order,
-                   n_minibatch, mb_rowsel.data_ptr(), mb_off.data_ptr(), ws.data_ptr(), ws.numel(), _stream()))
-    return mb_rowsel, mb_off
+    return _done(_native().ready_batch(streams, traj_turn_off, 1 if balance_rows else 0, n_minibatch, traj_keep, traj_order, _stream()))
 
 
 def umas_ready_batch_packed(streams: Streams, traj_turn_off, max_rows, traj_keep=None, traj_order=None):
     """Returns (mb_rowsel device int32, mb_off device int64 [n_models, n_traj + 1], n_parts device int32 [n_models]):
     micro-batches of whole trajectories under a budget of max_rows scored rows."""
-    lib = load_library()
-    lib.umas_ready_batch_workspace_bytes.restype = C.c_size_t
-    lib.umas_ready_batch_workspace_bytes.argtypes = [C.c_int32, C.c_int32]
-    fn = lib.umas_ready_batch_packed
-    fn.restype = C.c_int
-    fn.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p,
-                   C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
-    dev = streams.rowsel.device
-    tto_keep, tto = _host(traj_turn_off, np.int32)
-    n_traj = len(tto_keep) - 1
-    keep_keep, keep = _host(traj_keep, np.uint8)
-    order_keep, order = _host(traj_order, np.int32)
-    mb_rowsel = torch.empty(max(int(streams.rowsel.numel()), 1), dtype=torch.int32, device=dev)
-    mb_off = torch.empty((streams.n_models, n_traj + 1), dtype=torch.int64, device=dev)
-    n_parts = torch.empty(streams.n_models, dtype=torch.int32, device=dev)
-    ws = _workspace(lib.umas_ready_batch_workspace_bytes(n_traj, streams.n_models), dev)
-    cs = streams._c()
-    _check(lib, fn(C.addressof(cs), streams.n_models, streams.n_turns, tto, n_traj, keep, order, int(max_rows),
-                   mb_rowsel.data_ptr(), mb_off.data_ptr(), n_parts.data_ptr(), ws.data_ptr(), ws.numel(), _stream()))
-    return mb_rowsel, mb_off, n_parts
+    return _done(_native().ready_batch(streams, traj_turn_off, 2, max_rows, traj_keep, traj_order, _stream()))
 
 
 def read_value_stats(stats: torch.Tensor) -> np.ndarray:

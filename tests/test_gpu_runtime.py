@@ -153,6 +153,44 @@ def test_binding_refuses_a_row_selection_out_of_range():
             umas.umas_value_loss_fwd_bwd(H, torch.ones(64, dtype=torch.bfloat16, device="cuda"), 0.0, sel, z, z, None, 0, 0.2)
 
 
+@pytest.mark.parametrize("form", [
+    lambda a: None if a is None else np.asarray(a).tolist(),                                             # lists
+    lambda a: None if a is None else np.asarray(a).astype(np.float64 if np.asarray(a).dtype.kind == "f" else np.int64),   # other types
+    lambda a: None if a is None else np.repeat(np.asarray(a), 2)[::2],                                   # not contiguous
+    lambda a: None if a is None else np.asarray(a).astype(np.asarray(a).dtype.newbyteorder(">")),         # the other byte order
+    lambda a: None if a is None else torch.from_numpy(np.array(a)),                                      # tensors on the host
+])
+def test_host_arrays_in_any_form_give_the_same(form):
+    w = wl.make_workload(2, n_traj=9, tokens_per_turn=48, models=SMALL_BF16)
+    kw = assign_kwargs(w, P.to_dev(w.tok_mask))
+    arrays = [k for k, v in kw.items() if v is not None and k not in ("n_roles", "n_models", "tok_mask_global", "place_mode", "norm_eps")]
+    a, b = umas.umas_assign_token_rewards(**kw), umas.umas_assign_token_rewards(**{**kw, **{k: form(kw[k]) for k in arrays}})
+    keep, order = np.arange(9) % 3 != 1, np.random.default_rng(1).permutation(9).astype(np.int32)
+    for cut in (lambda s, f: umas.umas_ready_batch(s, f(w.traj_turn_off), 3, f(keep.astype(np.uint8)), f(order)),
+                lambda s, f: umas.umas_ready_batch_packed(s, f(w.traj_turn_off), 40, f(keep.astype(np.uint8)), f(order))):
+        kept = int(cut(a, np.asarray)[1].max())
+        for x, y in zip(cut(a, np.asarray), cut(b, form)):
+            assert torch.equal(x[:kept] if x.dim() == 1 else x, y[:kept] if y.dim() == 1 else y)
+    for name, x in vars(a).items():
+        y = getattr(b, name)
+        assert torch.equal(x, y) if torch.is_tensor(x) and name != "rowsel" else torch.is_tensor(x) or x == y, name
+    n = int(a.model_rowsel_off[-1])
+    assert torch.equal(a.rowsel[:n], b.rowsel[:n])
+
+
+def test_arguments_of_other_types_are_refused():
+    w = wl.make_workload(2, n_traj=3, tokens_per_turn=48, models=SMALL_BF16)
+    kw = assign_kwargs(w, P.to_dev(w.tok_mask))
+    H, x = torch.zeros(4, 64, device="cuda", dtype=torch.float16), torch.zeros(4, device="cuda")
+    for call in (lambda: umas.umas_assign_token_rewards(**{**kw, "n_roles": 2.0}), lambda: umas.umas_assign_token_rewards(**{**kw, "norm_eps": None}),
+                 lambda: umas.umas_assign_token_rewards(**{**kw, "tok_mask_global": w.tok_mask.tolist()}),
+                 lambda: umas.umas_values(H, x), lambda: umas.umas_policy_logprobs(H, H, x), lambda: umas.umas_kl_rewards(x, x, None, x, 0.1)):
+        with pytest.raises((TypeError, AttributeError)):
+            call()
+    with pytest.raises(umas.UmasError):
+        umas.umas_assign_token_rewards(**{**kw, "traj_turn_off": None})
+
+
 def test_two_pipelines_on_two_streams_at_once():
     """Routing, the scan and the ready batch have kernels whose workgroups wait for words that their other workgroups
     publish; their grids are a fraction of what the device holds, so two such pipelines on different streams (disjoint
