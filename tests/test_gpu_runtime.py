@@ -90,6 +90,23 @@ def test_staging_ring_keeps_every_queued_call_apart():
         P.check_front(w, s, adv, ret, rho, st, r, adv_o, ret_o)
 
 
+# thin arrays of about 11 to 340 KB: on both sides of the 16 KB from which a kernel copies them, one to many workgroups of it
+@pytest.mark.parametrize("n_traj", [150, 200, 215, 230, 430, 900, 4500])
+def test_thin_arrays_of_all_sizes_reach_the_device(n_traj):
+    from tests import arraywise as aw
+    w = wl.make_workload(1, n_traj=n_traj, tokens_per_turn=8, models=SMALL_BF16)
+    s, adv, ret = P.gpu_front(w)
+    sa = aw.streams(w)
+    for f in ("perm", "tok_turn", "tok_role", "tok_mask", "turn_seg_off", "tok_flags"):
+        assert np.array_equal(getattr(s, f).cpu().numpy(), sa[f]), f
+    P.close(s.turn_scalar.cpu().numpy(), aw.composed_rewards(w), 1e-5, "turn_scalar")
+    rng = np.random.default_rng(n_traj)
+    keep, order = (rng.random(n_traj) < 0.9).astype(np.uint8), rng.permutation(n_traj).astype(np.int32)
+    rows, off = umas.umas_ready_batch(s, w.traj_turn_off, 4, keep, order)
+    rows_a, off_a = aw.ready_batch(w, sa, keep, order, 4, False)
+    assert np.array_equal(off.cpu().numpy(), off_a) and np.array_equal(rows.cpu().numpy()[:len(rows_a)], rows_a)
+
+
 def test_results_do_not_depend_on_scheduling():
     """Two runs of the whole path on the same inputs: routing, placement, advantages, log-probs, statistics and dH are
     bit-equal (no atomics on their way); dW adds its one-hot rows with float atomics in whatever order the wavefronts
