@@ -95,6 +95,28 @@ __device__ __forceinline__ int model_of(const ModelOffsets& mo, int n_models, in
   return m;
 }
 
+// Sum over the wavefront, in its last lane: six moves between lanes that go with an add (row_shr 1, 2, 4, 8 inside the rows of
+// 16 lanes, then the rows' sums handed on), no trips through LDS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int lane_move(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false); }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float lane_move(float v) { return __int_as_float(lane_move<CTRL, ROWS>(__float_as_int(v))); }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lane_move(double v) {
+  return __hiloint2double(lane_move<CTRL, ROWS>(__double2hiint(v)), lane_move<CTRL, ROWS>(__double2loint(v)));
+}
+constexpr int kGroupRounds = 8;
+template <typename T>
+__device__ __forceinline__ T last_lane_sum(T v) {
+  v += lane_move<0x111, 0xF>(v);
+  v += lane_move<0x112, 0xF>(v);
+  v += lane_move<0x114, 0xF>(v);
+  v += lane_move<0x118, 0xF>(v);
+  v += lane_move<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+  v += lane_move<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
 // Pass 1: per block and group (sum A, sum A^2, count) over the mask=1 tokens, float64.
 __global__ void __launch_bounds__(kST)
 k_whiten_sums(int64_t n, const float* __restrict__ adv, const uint8_t* __restrict__ mask, const int32_t* __restrict__ role,
@@ -104,7 +126,10 @@ k_whiten_sums(int64_t n, const float* __restrict__ adv, const uint8_t* __restric
   for (int i = threadIdx.x; i < groups * 3; i += kST) s_acc[i] = 0.0;
   __syncthreads();
   const int64_t stride = static_cast<int64_t>(gridDim.x) * kST * 4;
-  for (int64_t p0 = (static_cast<int64_t>(blockIdx.x) * kST + threadIdx.x) * 4; p0 < n; p0 += stride) {
+  const int lane = threadIdx.x & (kWave - 1);
+  // whole wavefronts go round: their sums are taken across all lanes
+  for (int64_t w0 = (static_cast<int64_t>(blockIdx.x) * kST + (threadIdx.x - lane)) * 4; w0 < n; w0 += stride) {
+    const int64_t p0 = w0 + lane * 4;
     float a[4];
     uint8_t m[4];
     int rl[4] = {0, 0, 0, 0};
@@ -137,35 +162,70 @@ k_whiten_sums(int64_t n, const float* __restrict__ adv, const uint8_t* __restric
     }
     // Usual case: every counted token of the wavefront's 256 belongs to one group.  Their sums are formed in
     // float32 across the lanes (256 values: rounding far below the float32 inputs' own) and one lane adds them
-    // to the float64 accumulators; otherwise every lane adds its own tokens.
-    int g0 = -1;
+    // to the float64 accumulators.  Where turns of several groups meet in the 256 the groups take turns, in float64 (every lane
+    // adding its own tokens in LDS queued on the groups' three words: 40 million tokens in turns of 400 by five roles 356 us,
+    // in turns 98); only what is left after kGroupRounds groups goes lane by lane.
+    auto first_group = [&]() {
+      int g = -1;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) if (gk[k] >= 0 && g0 < 0) g0 = gk[k];
-    const unsigned long long have = __ballot(g0 >= 0);
-    const int gref = have ? __shfl(g0, __ffsll(static_cast<long long>(have)) - 1, kWave) : -1;
+      for (int k = 3; k >= 0; --k) g = gk[k] >= 0 ? gk[k] : g;
+      return g;
+    };
+    int g0 = first_group();
+    unsigned long long have = __ballot(g0 >= 0);
+    if (!have) continue;                                     // the same for every lane of the wavefront
+    int gref = __builtin_amdgcn_readlane(g0, __ffsll(static_cast<long long>(have)) - 1);
     bool same = true;
 #pragma unroll
     for (int k = 0; k < 4; ++k) same = same && (gk[k] < 0 || gk[k] == gref);
+    auto add = [&](double sa, double sq, int n_in) {         // the last lane has the sums
+      if (lane == kWave - 1) {
+        atomicAdd(s_acc + 3 * gref, sa);
+        atomicAdd(s_acc + 3 * gref + 1, sq);
+        atomicAdd(s_acc + 3 * gref + 2, static_cast<double>(n_in));
+      }
+    };
     if (__all(same)) {
-      if (have) {
-        float sa = 0.f, sq = 0.f, sc = 0.f;
+      float sa = 0.f, sq = 0.f;
+      int n_in = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (gk[k] >= 0) { sa += a[k]; sq = fmaf(a[k], a[k], sq); }
+        n_in += __popcll(__ballot(gk[k] >= 0));
+      }
+      sa = last_lane_sum(sa);
+      sq = last_lane_sum(sq);
+      add(static_cast<double>(sa), static_cast<double>(sq), n_in);
+      continue;
+    }
+    for (int round = 0;; ++round) {
+      if (round == kGroupRounds) {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-          if (gk[k] >= 0) { sa += a[k]; sq = fmaf(a[k], a[k], sq); sc += 1.f; }
-        sa = wave_sum(sa); sq = wave_sum(sq); sc = wave_sum(sc);
-        if ((threadIdx.x & (kWave - 1)) == 0) {
-          atomicAdd(s_acc + 3 * gref, static_cast<double>(sa));
-          atomicAdd(s_acc + 3 * gref + 1, static_cast<double>(sq));
-          atomicAdd(s_acc + 3 * gref + 2, static_cast<double>(sc));
-        }
+          if (gk[k] >= 0) {
+            const double x = static_cast<double>(a[k]);
+            atomicAdd(s_acc + 3 * gk[k], x); atomicAdd(s_acc + 3 * gk[k] + 1, x * x); atomicAdd(s_acc + 3 * gk[k] + 2, 1.0);
+          }
+        break;
       }
-    } else {
+      double sa = 0.0, sq = 0.0;
+      int n_in = 0;
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (gk[k] >= 0) {
-          const double x = static_cast<double>(a[k]);
-          atomicAdd(s_acc + 3 * gk[k], x); atomicAdd(s_acc + 3 * gk[k] + 1, x * x); atomicAdd(s_acc + 3 * gk[k] + 2, 1.0);
-        }
+      for (int k = 0; k < 4; ++k) {
+        const bool mine = gk[k] == gref;
+        const double x = mine ? static_cast<double>(a[k]) : 0.0;
+        sa += x;
+        sq = fma(x, x, sq);
+        n_in += __popcll(__ballot(mine));
+        if (mine) gk[k] = -1;
+      }
+      sa = last_lane_sum(sa);
+      sq = last_lane_sum(sq);
+      add(sa, sq, n_in);
+      g0 = first_group();
+      have = __ballot(g0 >= 0);
+      if (!have) break;
+      gref = __builtin_amdgcn_readlane(g0, __ffsll(static_cast<long long>(have)) - 1);
     }
   }
   __syncthreads();

@@ -494,3 +494,21 @@ def test_whitening_statistics(n, n_roles):
     bound = P.whiten_bounds(a64, mask, role, off, n_roles, True)
     assert not out[mask == 0].any()
     assert (np.abs(out - want) <= bound).all()
+
+
+# a wavefront's 256 tokens hold one group, two, a few, more than eight; whole wavefronts and a last one of 1, 3 or 255 tokens
+@pytest.mark.parametrize("turn", [2, 25, 100, 400])
+@pytest.mark.parametrize("n,n_roles", [(1, 3), (259, 3), (1023, 64), (40 * 1024 + 257, 5), (300 * 1024 + 511, 17)])
+def test_whitening_statistics_of_turns(n, n_roles, turn):
+    rng = np.random.default_rng([n, turn])
+    adv = (3 + rng.normal(size=n)).astype(np.float32)
+    mask = (rng.random(n) < 0.8).astype(np.uint8)
+    role = np.repeat(rng.integers(-1, n_roles + 1, size=n // turn + 1), turn)[:n].astype(np.int32)   # a role outside [0, n_roles) joins no group
+    off = np.array([0, n // 3, n])
+    out = umas.umas_whiten_advantages(P.to_dev(adv), P.to_dev(mask), P.to_dev(role), off, n_roles, umas.WHITEN_MODEL_ROLE).cpu().numpy()
+    known = (role >= 0) & (role < n_roles)
+    a64, counted = adv.astype(np.float64), (mask * known).astype(np.uint8)
+    want = orc.whiten_advantages(a64, counted, np.where(known, role, 0), off, n_roles, orc.WHITEN_MODEL_ROLE)
+    bound = P.whiten_bounds(a64, counted, np.where(known, role, 0), off, n_roles, True)
+    assert not out[counted == 0].any()
+    assert (np.abs(out - want) <= bound).all()
