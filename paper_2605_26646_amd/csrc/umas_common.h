@@ -86,6 +86,20 @@ inline unsigned cdiv(size_t a, size_t b) { return static_cast<unsigned>((a + b -
 // ------------------------------------------------------------------ device primitives
 constexpr int kWave = 64;
 
+// 16-byte load and store past the caches, for what is read once or not read again soon: the memory-side cache stays with what is.
+template <typename V>
+__device__ __forceinline__ V load_stream(const void* p) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  static_assert(sizeof(V) == 16, "16 bytes");
+  return __builtin_bit_cast(V, __builtin_nontemporal_load(static_cast<const u32x4*>(p)));
+}
+template <typename V>
+__device__ __forceinline__ void store_stream(void* p, const V& v) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  static_assert(sizeof(V) == 16, "16 bytes");
+  __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), static_cast<u32x4*>(p));
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll
