@@ -50,7 +50,7 @@ template <> struct Vec<uint16_t> {
     uint32_t w[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) w[i] = static_cast<uint32_t>(f2bf(x[2 * i])) | (static_cast<uint32_t>(f2bf(x[2 * i + 1])) << 16);
-    *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+    store_stream(p, make_uint4(w[0], w[1], w[2], w[3]));
   }
 };
 template <> struct Vec<float> {
@@ -59,7 +59,7 @@ template <> struct Vec<float> {
   __device__ static void unpack(const uint4& v, float (&x)[4]) {
     x[0] = __uint_as_float(v.x); x[1] = __uint_as_float(v.y); x[2] = __uint_as_float(v.z); x[3] = __uint_as_float(v.w);
   }
-  __device__ static void store(float* p, const float (&x)[4]) { *reinterpret_cast<float4*>(p) = make_float4(x[0], x[1], x[2], x[3]); }
+  __device__ static void store(float* p, const float (&x)[4]) { store_stream(p, make_float4(x[0], x[1], x[2], x[3])); }
 };
 
 __global__ void k_zero_u32(uint32_t* __restrict__ p, int64_t n) {
@@ -71,13 +71,13 @@ __global__ void k_zero_u32(uint32_t* __restrict__ p, int64_t n) {
 __global__ void __launch_bounds__(256)
 k_value_open(uint32_t* __restrict__ value_new, int64_t n, uint4* __restrict__ big, int64_t n16) {
   const int64_t i0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x, stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t i = i0; i < n16; i += stride) big[i] = make_uint4(0u, 0u, 0u, 0u);
+  for (int64_t i = i0; i < n16; i += stride) store_stream(big + i, make_uint4(0u, 0u, 0u, 0u));
   if (value_new)
     for (int64_t i = i0; i < n; i += stride) value_new[i] = 0u;
 }
 // Large selections: dH is cleared only where the row kernel does not write it.  A byte per row says which rows are selected
 // (in the memory of the partial sums, which come later); clearing all of dH first wrote the selected rows twice (39 224 of
-// 49 030 rows of 2048: 26.6 us, mark and clear together 13).
+// 49 030 rows of 2048: 26.6 us, mark and clear together 13.5).
 __global__ void __launch_bounds__(256)
 k_value_mark(const int32_t* __restrict__ rowsel, int64_t n_sel, int64_t n_rows, uint8_t* __restrict__ map) {
   const int64_t n = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -93,7 +93,7 @@ k_value_clear_rest(const uint8_t* __restrict__ map, int64_t n_rows, int row16, u
   // every wavefront looks at the same rows and takes its share of each unselected one
   for (unsigned long long rest = __ballot(mine < n_rows && map[mine] == 0); rest; rest &= rest - 1) {
     uint4* p = dH + (r0 + __ffsll(static_cast<long long>(rest)) - 1) * row16;
-    for (int i = threadIdx.x; i < row16; i += 256) p[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = threadIdx.x; i < row16; i += 256) store_stream(p + i, make_uint4(0u, 0u, 0u, 0u));
   }
 }
 // Below this many bytes of selected rows the two launches more cost as much as they save.
