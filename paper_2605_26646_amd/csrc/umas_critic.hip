@@ -8,8 +8,10 @@
 //   dH_i = g_i w,  dw = sum_i g_i h_i,  db = sum_i g_i
 // The whole step is one pass over H: one wavefront per row keeps the row in registers, forms the dot
 // product and the row's g, writes dH and adds g h to its dw accumulators; the next row is already in
-// flight.  A workgroup's partial sums meet in LDS, the workgroups' in one small kernel, both in a fixed order, so
-// results do not depend on scheduling.
+// flight.  dH leaves past the caches: nothing here reads it, and the rows of H that the value pass has just read stay in the
+// memory-side cache (values and update, 39 224 rows of 2048 125 -> 119 us on new rows, 112 -> 99 on the rows of the pass
+// before; 60 000 float32 rows of 1024 177 -> 153).  A workgroup's partial sums meet in LDS, the workgroups' in one small kernel,
+// both in a fixed order, so results do not depend on scheduling.
 #include <type_traits>
 
 #include <algorithm>
