@@ -3,10 +3,8 @@
 // A workgroup owns a BM x BN tile of C and walks K in steps of 64; each wavefront owns a
 // (BM/WM) x (BN/WN) sub-tile as a grid of 16x16 blocks of v_mfma_f32_16x16x32_bf16 with float
 // accumulators (on random operands a register-only loop of this instruction sustains 2.0 PFLOP/s on this
-// part, one of the 32x32x16 form 1.77: the chip runs into its power limit later).  Two main loops: a
-// general one (any K that is a multiple of 8: global memory is read in 16-byte vectors into registers one
-// K-step ahead and written to one of two LDS stages of row pitch 72 bf16) and a fast one for K % 64 == 0
-// that fills the LDS straight from global memory.
+// part, one of the 32x32x16 form 1.77: the chip runs into its power limit later).  The main loops fill the
+// LDS straight from global memory.
 //
 // Operand layout of one block (lane l): row (or column) l % 16, k = 8 (l / 16) .. 8 (l / 16) + 7.
 // Accumulator layout of one 16x16 block (register r of lane l):
@@ -28,97 +26,11 @@ template <int BM_, int BN_, int WM_, int WN_>
 struct TileCfg {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
   static constexpr int BK = 64;
-  static constexpr int LDP = 72;                       // LDS row pitch in bf16 elements
   static constexpr int T = 64 * WM * WN;               // threads per workgroup
   static constexpr int WTM = BM / WM, WTN = BN / WN;   // wavefront sub-tile
   static constexpr int MI = WTM / 16, NI = WTN / 16;   // 16x16 blocks per wavefront
-  static constexpr int NA = BM * 8 / T, NB = BN * 8 / T;   // 16-byte vectors per thread per K-step
-  static constexpr int ROWS_PER_PASS = T / 8;          // rows covered by one vector slot of all threads
-  static constexpr int STAGE = (BM + BN) * LDP;        // bf16 elements per LDS stage
-  static constexpr int LDS_BYTES = 2 * STAGE * 2;
   static_assert(BM % (32 * WM) == 0 && BN % (16 * WN) == 0, "sub-tiles are grids of 16x16 blocks, an even number along M");
-  static_assert((BM * 8) % T == 0 && (BN * 8) % T == 0, "vector slots divide evenly");
 };
-
-// Row of the tile that vector slot i of this thread loads, and the thread's 8-element K offset.
-template <class C>
-__device__ __forceinline__ int slot_row(int i) { return (threadIdx.x >> 3) + i * C::ROWS_PER_PASS; }
-__device__ __forceinline__ int slot_kofs() { return (threadIdx.x & 7) * 8; }
-
-// pa[i] / pb[i]: address of (row of slot i, k = slot_kofs()); always a readable row: callers clamp rows
-// outside the matrix to a valid one and ignore the results that come from them.  Only the K tail
-// (K not a multiple of 64) is zero-filled, because every output depends on it.
-template <class C>
-__device__ __forceinline__ void mfma_mainloop(const uint16_t* const (&pa)[C::NA], const uint16_t* const (&pb)[C::NB],
-                                              int K, uint16_t* lds, floatx4 (&acc)[C::MI][C::NI]) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  const int kofs = slot_kofs();
-  uint4 ra[C::NA], rb[C::NB];
-  const int nk = (K + C::BK - 1) / C::BK;
-  const bool ktail = (K % C::BK) != 0;
-
-  auto gload = [&](int kt) {
-    const int k = kt * C::BK;
-    if (ktail && kt == nk - 1) {
-      // clamp the address into the row and drop what lies past K
-      const bool kin = k + kofs < K;
-      const int kk = kin ? k : 0;
-#pragma unroll
-      for (int i = 0; i < C::NA; ++i) {
-        uint4 v = *reinterpret_cast<const uint4*>(pa[i] + kk);
-        ra[i] = make_uint4(kin ? v.x : 0u, kin ? v.y : 0u, kin ? v.z : 0u, kin ? v.w : 0u);
-      }
-#pragma unroll
-      for (int i = 0; i < C::NB; ++i) {
-        uint4 v = *reinterpret_cast<const uint4*>(pb[i] + kk);
-        rb[i] = make_uint4(kin ? v.x : 0u, kin ? v.y : 0u, kin ? v.z : 0u, kin ? v.w : 0u);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < C::NA; ++i) ra[i] = *reinterpret_cast<const uint4*>(pa[i] + k);
-#pragma unroll
-      for (int i = 0; i < C::NB; ++i) rb[i] = *reinterpret_cast<const uint4*>(pb[i] + k);
-    }
-  };
-  auto swrite = [&](int stage) {
-    uint16_t* sa = lds + stage * C::STAGE;
-    uint16_t* sb = sa + C::BM * C::LDP;
-#pragma unroll
-    for (int i = 0; i < C::NA; ++i) *reinterpret_cast<uint4*>(sa + slot_row<C>(i) * C::LDP + kofs) = ra[i];
-#pragma unroll
-    for (int i = 0; i < C::NB; ++i) *reinterpret_cast<uint4*>(sb + slot_row<C>(i) * C::LDP + kofs) = rb[i];
-  };
-  auto compute = [&](int stage) {
-    // operand of a 16x16x32 block: lane l holds row l % 16, k = 8 (l / 16) .. + 7 of the 32-wide slice
-    const uint16_t* sa = lds + stage * C::STAGE + (wm * C::WTM + (lane & 15)) * C::LDP + (lane >> 4) * 8;
-    const uint16_t* sb = lds + stage * C::STAGE + (C::BM + wn * C::WTN + (lane & 15)) * C::LDP + (lane >> 4) * 8;
-#pragma unroll
-    for (int kk = 0; kk < C::BK / 32; ++kk) {
-      bf16x8 af[C::MI], bfr[C::NI];
-#pragma unroll
-      for (int i = 0; i < C::MI; ++i) af[i] = *reinterpret_cast<const bf16x8*>(sa + i * 16 * C::LDP + kk * 32);
-#pragma unroll
-      for (int j = 0; j < C::NI; ++j) bfr[j] = *reinterpret_cast<const bf16x8*>(sb + j * 16 * C::LDP + kk * 32);
-#pragma unroll
-      for (int i = 0; i < C::MI; ++i)
-#pragma unroll
-        for (int j = 0; j < C::NI; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-    }
-  };
-
-  gload(0);
-  swrite(0);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) gload(kt + 1);
-    compute(cur);
-    if (kt + 1 < nk) swrite(cur ^ 1);
-    __syncthreads();
-  }
-}
 
 // The thread's number as a value that the compiler takes for a new one every time: what a tile derives from it (addresses of
 // loads and fragments, dozens of registers for each kind of tile) is then not kept over a loop of tiles.
@@ -133,7 +45,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Fast main loop for K % 64 == 0.
+// Main loop for K-contiguous operands, K a multiple of 8.
 //
 // K is walked in steps of 64: 128 bytes per row, the line size of the vector caches, so every line is
 // fetched once.  Tiles go from global memory straight into LDS stages of 256 rows x 128 bytes per operand
@@ -147,6 +59,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base) {
 // then the wavefront waits for its LDS reads and for all loads but the youngest ones (A of step j+2: loads into
 // LDS return in the order they were issued), the workgroup meets at the barrier, and phase 3 runs while the first
 // fragments of the next step are read.
+// With TAIL the last step holds fewer than 64 k: the chunks of a row past its end repeat the row's last chunk, and the threads that
+// loaded them clear them in LDS, in both operands (a product with a value that is not finite would not be 0 otherwise), in front
+// of the barrier behind which the step is read.  (A loop with registers and a second LDS pitch in place of this one: 2500 rows of
+// 1544 against 50 001 532 us, now 391; 700 rows of 3000 against 80 001 466 us, now 340; 5000 rows kept 3.95 ms, now 2.66.)
 template <class C>
 struct Ring2Cfg {
   static constexpr int BK = 64;
@@ -166,7 +82,7 @@ __device__ __forceinline__ int ring2_kofs(int t = threadIdx.x) {
   return 8 * ((t & 7) ^ (((t >> 3) >> 1) & 7));
 }
 
-template <class C>
+template <class C, bool TAIL>
 __device__ __forceinline__ void mfma_mainloop_ring2(__amdgpu_buffer_rsrc_t ra, const uint32_t (&oa)[Ring2Cfg<C>::NA],
                                                     __amdgpu_buffer_rsrc_t rb, const uint32_t (&ob)[Ring2Cfg<C>::NB],
                                                     int K, uint16_t* lds, floatx4 (&acc)[C::MI][C::NI]) {
@@ -176,24 +92,41 @@ __device__ __forceinline__ void mfma_mainloop_ring2(__amdgpu_buffer_rsrc_t ra, c
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / C::WN, wn = wave % C::WN;
   char* base = reinterpret_cast<char*>(lds);
-  const int nsub = K / R::BK;
+  const int nsub = (K + R::BK - 1) / R::BK;
+  // the last step's chunk of this thread when it lies past the end of the row: how far in front of it the row's last one is
+  const int k_last = (nsub - 1) * R::BK + ring2_kofs();
+  const bool past = TAIL && k_last >= K;
+  const uint32_t back = past ? static_cast<uint32_t>(k_last - (K - 8)) * 2u : 0u;
 
   static_assert(R::NA < 16, "the wait before the barrier leaves the loads of A outstanding");
   auto gload_a = [&](int sub, int ia) {
     const int kbytes = sub * R::BK * 2;
     char* sa = base + ia * R::ASTAGE + wave * 8 * R::ROWB;
+    const uint32_t cut = TAIL && sub == nsub - 1 ? back : 0u;
 #pragma unroll
     for (int i = 0; i < R::NA; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, reinterpret_cast<uint32_t*>(sa + i * R::ROWS_PER_PASS * R::ROWB), 16,
-                                               oa[i], kbytes, 0, 0);
+                                               TAIL ? oa[i] - cut : oa[i], kbytes, 0, 0);
   };
   auto gload_b = [&](int sub, int ib) {
     const int kbytes = sub * R::BK * 2;
     char* sb = base + R::BBASE + ib * R::BSTAGE + wave * 8 * R::ROWB;
+    const uint32_t cut = TAIL && sub == nsub - 1 ? back : 0u;
 #pragma unroll
     for (int i = 0; i < R::NB; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, reinterpret_cast<uint32_t*>(sb + i * R::ROWS_PER_PASS * R::ROWB), 16,
-                                               ob[i], kbytes, 0, 0);
+                                               TAIL ? ob[i] - cut : ob[i], kbytes, 0, 0);
+  };
+  auto clear_past = [&](int ia, int ib) {            // the last step's stages, once this thread's loads of it have landed
+    if (past) {
+      char* sa = base + ia * R::ASTAGE + wave * 8 * R::ROWB + lane * 16;
+      char* sb = base + R::BBASE + ib * R::BSTAGE + wave * 8 * R::ROWB + lane * 16;
+#pragma unroll
+      for (int i = 0; i < R::NA; ++i) *reinterpret_cast<uint4*>(sa + i * R::ROWS_PER_PASS * R::ROWB) = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+      for (int i = 0; i < R::NB; ++i) *reinterpret_cast<uint4*>(sb + i * R::ROWS_PER_PASS * R::ROWB) = make_uint4(0u, 0u, 0u, 0u);
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0)
   };
   // Operand of a 16x16x32 block: lane l holds row l % 16, k = 8 (l / 16) .. + 7 of the 32-wide slice, i.e. chunk
   // 4 s + l / 16 of the row.  A step is four phases of 16 MFMAs: (slice 0, upper half of the A rows), (slice 0,
@@ -235,6 +168,7 @@ __device__ __forceinline__ void mfma_mainloop_ring2(__amdgpu_buffer_rsrc_t ra, c
   gload_b(0, 0);
   gload_a(clamp_sub(1), 1);
   __builtin_amdgcn_s_waitcnt(0x0070);
+  if (TAIL && nsub == 1) clear_past(0, 0);
   __builtin_amdgcn_s_barrier();
   fload_b(0, 0, 0);
   fload_a(0, 0, 0, 0);
@@ -261,6 +195,7 @@ __device__ __forceinline__ void mfma_mainloop_ring2(__amdgpu_buffer_rsrc_t ra, c
     // own reads of this step done, own loads for the next step landed (the youngest, A of the step after
     // next, may still be on their way); then everybody's
     __builtin_amdgcn_s_waitcnt(0x0070 | R::NA);      // vmcnt(NA) and lgkmcnt(0), expcnt untouched (gfx9 encoding)
+    if (TAIL && j == nsub - 2) clear_past(ia1, ib ^ 1);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     fload_b(0, ib ^ 1, 0);

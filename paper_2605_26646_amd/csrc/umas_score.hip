@@ -31,7 +31,7 @@ namespace {
 
 using Cfg = TileCfg<256, 256, 2, 4>;   // 8 wavefronts, two per SIMD: one issues memory operations while the other feeds the matrix pipe
 using Ring = Ring2Cfg<Cfg>;
-constexpr int kLogitLds = Ring::LDS_BYTES > Cfg::LDS_BYTES ? Ring::LDS_BYTES : Cfg::LDS_BYTES;   // both main loops fit
+constexpr int kLogitLds = Ring::LDS_BYTES;
 constexpr int kGM = 4, kGN = 8;          // tile group resident on one XCD
 constexpr int kTilesPerWg = 4;           // logit tiles a workgroup computes one after the other (short K: launch gaps and store drain overlap)
 constexpr int kRowBlock = 256;
@@ -90,31 +90,19 @@ __device__ __forceinline__ void logit_tile(const uint16_t* __restrict__ W, const
   for (int i = 0; i < C::MI; ++i)
 #pragma unroll
     for (int j = 0; j < C::NI; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-  if (d % C::BK == 0) {
-    using R = Ring2Cfg<C>;
-    const uint32_t kofs = ring2_kofs();
-    uint32_t oa[R::NA], ob[R::NB];
+  using R = Ring2Cfg<C>;
+  const uint32_t kofs = ring2_kofs();
+  uint32_t oa[R::NA], ob[R::NB];
 #pragma unroll
-    for (int i = 0; i < R::NA; ++i) oa[i] = (static_cast<uint32_t>(min(ring2_row<C>(i), V - 1 - m0)) * d + kofs) * 2u;
+  for (int i = 0; i < R::NA; ++i) oa[i] = (static_cast<uint32_t>(min(ring2_row<C>(i), V - 1 - m0)) * d + kofs) * 2u;
 #pragma unroll
-    for (int i = 0; i < R::NB; ++i) {
-      const int64_t n = sel0 + min(n0 + ring2_row<C>(i), n_lim - 1);
-      ob[i] = (static_cast<uint32_t>(rowsel ? rowsel[n] : n) * d + kofs) * 2u;   // host checks n_rows*d*2 < 2^32
-    }
-    mfma_mainloop_ring2<C>(make_rsrc(W + static_cast<int64_t>(m0) * d), oa, make_rsrc(H), ob, d, lds, acc);
-  } else {
-    const int kofs = slot_kofs();
-    const uint16_t* pa[C::NA];
-    const uint16_t* pb[C::NB];
-#pragma unroll
-    for (int i = 0; i < C::NA; ++i) pa[i] = W + static_cast<int64_t>(min(m0 + slot_row<C>(i), V - 1)) * d + kofs;
-#pragma unroll
-    for (int i = 0; i < C::NB; ++i) {
-      const int64_t n = sel0 + min(n0 + slot_row<C>(i), n_lim - 1);
-      pb[i] = H + static_cast<int64_t>(rowsel ? rowsel[n] : n) * d + kofs;
-    }
-    mfma_mainloop<C>(pa, pb, d, lds, acc);
+  for (int i = 0; i < R::NB; ++i) {
+    const int64_t n = sel0 + min(n0 + ring2_row<C>(i), n_lim - 1);
+    ob[i] = (static_cast<uint32_t>(rowsel ? rowsel[n] : n) * d + kofs) * 2u;   // host checks n_rows*d*2 < 2^32
   }
+  const __amdgpu_buffer_rsrc_t ra = make_rsrc(W + static_cast<int64_t>(m0) * d), rb = make_rsrc(H);
+  if (d % C::BK == 0) mfma_mainloop_ring2<C, false>(ra, oa, rb, ob, d, lds, acc);
+  else mfma_mainloop_ring2<C, true>(ra, oa, rb, ob, d, lds, acc);
 }
 
 // ------------------------------------------------------------------ bf16: logit tiles -> partials
@@ -334,7 +322,7 @@ k_score_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, in
 // fills its stages while the other multiplies (64 rows of 2048 / 3584 against 151 936: 156 / 215 us against 182 / 274 with
 // the large tiles; 128x256 and 256x128 tiles 213 / 347 and 167 / 234).
 using NarrowCfg = TileCfg<128, 128, 2, 2>;
-constexpr int kNarrowLds = Ring2Cfg<NarrowCfg>::LDS_BYTES > NarrowCfg::LDS_BYTES ? Ring2Cfg<NarrowCfg>::LDS_BYTES : NarrowCfg::LDS_BYTES;
+constexpr int kNarrowLds = Ring2Cfg<NarrowCfg>::LDS_BYTES;
 __global__ void __launch_bounds__(NarrowCfg::T)
 k_score_narrow(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
                const int32_t* __restrict__ rowsel, int64_t n_sel, const int32_t* __restrict__ ids,

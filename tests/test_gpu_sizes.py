@@ -512,3 +512,15 @@ def test_whitening_statistics_of_turns(n, n_roles, turn):
     bound = P.whiten_bounds(a64, counted, np.where(known, role, 0), off, n_roles, True)
     assert not out[counted == 0].any()
     assert (np.abs(out - want) <= bound).all()
+
+
+# a last step of K of 8 to 56 columns, behind none, one and many whole ones of 64: in the narrow tiles (up to 128 rows) and the large
+@pytest.mark.parametrize("d", [16, 56, 72, 88, 120, 184, 1000, 1016])
+@pytest.mark.parametrize("n_sel", [100, 300])
+def test_hidden_sizes_between_multiples_of_64(n_sel, d):
+    rng = np.random.default_rng([n_sel, d])
+    check_scores(rng, n_sel, d, 1030, True, False)
+    check_update(rng, n_sel + 30, d, 1030)
+    check_update(rng, n_sel + 30, d, 1030, entropy_coef=0.01)
+    check_update(rng, n_sel + 30, d, 1030, entropy_coef=0.01,
+                 workspace=torch.empty(umas.ppo_workspace_bytes(int(0.8 * (n_sel + 30)), d, 1030, torch.bfloat16, 0, minimum=True), dtype=torch.uint8, device="cuda"))
