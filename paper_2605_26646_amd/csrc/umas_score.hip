@@ -62,20 +62,30 @@ __device__ __forceinline__ Part part_merge(Part x, Part y) {
 }
 
 // ------------------------------------------------------------------ small helpers
-__global__ void k_fill_u32(uint32_t* __restrict__ p, int64_t n, uint32_t v) {
-  int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (; i < n; i += stride) p[i] = v;
+// What a call defines on rows that are not selected, cleared in one launch (scoring through a selection, a launch for each array
+// and in one: 20 rows of 2048 121.9 and 119.0 us, 3 rows of 1024 against 30 001 24.3 and 21.3).
+struct ClearArgs {
+  uint32_t* p[3];        // NULL: nothing
+  int64_t words[3];
+};
+__global__ void __launch_bounds__(256) k_clear(ClearArgs A) {
+  const int64_t i0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x, stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    if (A.p[k])
+      for (int64_t i = i0; i < A.words[k]; i += stride) A.p[k][i] = 0u;
 }
 
-hipError_t fill_bytes_zero(void* p, size_t bytes, hipStream_t st) {
-  // bytes is a multiple of 4 for every buffer cleared here
-  const int64_t n = static_cast<int64_t>(bytes / 4);
-  if (n == 0) return hipSuccess;
-  const unsigned grid = static_cast<unsigned>(n / 256 + 1 < 65536 ? n / 256 + 1 : 65536);
-  hipLaunchKernelGGL(k_fill_u32, dim3(grid), dim3(256), 0, st, static_cast<uint32_t*>(p), n, 0u);
+// bytes are a multiple of 4 for every buffer cleared here
+hipError_t clear_bytes(hipStream_t st, void* a, size_t bytes_a, void* b = nullptr, size_t bytes_b = 0, void* c = nullptr, size_t bytes_c = 0) {
+  const ClearArgs A{{static_cast<uint32_t*>(a), static_cast<uint32_t*>(b), static_cast<uint32_t*>(c)},
+                    {static_cast<int64_t>(bytes_a / 4), static_cast<int64_t>(bytes_b / 4), static_cast<int64_t>(bytes_c / 4)}};
+  int64_t most = 0;
+  for (int k = 0; k < 3; ++k) most = A.p[k] ? std::max(most, A.words[k]) : most;
+  if (most == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_clear, dim3(static_cast<unsigned>(std::min<int64_t>(most / 256 + 1, 65536))), dim3(256), 0, st, A);
   const hipError_t e = hipGetLastError();
-  if (e == hipSuccess && g_prof_on) prof_kernel("k_fill_u32", st);
+  if (e == hipSuccess && g_prof_on) prof_kernel("k_clear", st);
   return e;
 }
 
@@ -1733,9 +1743,8 @@ extern "C" umas_status umas_policy_logprobs(const void* H, const void* W, umas_d
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   prof_mark(st);
   if (rowsel && n_rows > 0) {
-    UMAS_HIP(fill_bytes_zero(logp, n_rows * sizeof(float), st));
-    UMAS_HIP(fill_bytes_zero(lse, n_rows * sizeof(float), st));
-    if (entropy) UMAS_HIP(fill_bytes_zero(entropy, n_rows * sizeof(float), st));
+    const size_t bytes = n_rows * sizeof(float);
+    UMAS_HIP(clear_bytes(st, logp, bytes, lse, bytes, entropy, bytes));
   }
   Carver c(workspace);
   ScoreWs w;
@@ -1790,9 +1799,8 @@ extern "C" umas_status umas_policy_logprobs_static(const void* H, const void* W,
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   prof_mark(st);
   if (rowsel && n_rows > 0) {
-    UMAS_HIP(fill_bytes_zero(logp, n_rows * sizeof(float), st));
-    UMAS_HIP(fill_bytes_zero(lse, n_rows * sizeof(float), st));
-    if (entropy) UMAS_HIP(fill_bytes_zero(entropy, n_rows * sizeof(float), st));
+    const size_t bytes = n_rows * sizeof(float);
+    UMAS_HIP(clear_bytes(st, logp, bytes, lse, bytes, entropy, bytes));
   }
   Carver c(ws);
   ScoreWs w;
@@ -1866,10 +1874,9 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
   // rows that are not selected, and (keeping path, see k_update_open) selected rows in blocks without any gradient,
   // are not visited by the backward
   if (!keep && rowsel && n_rows > 0) {
-    if (logp_new) UMAS_HIP(fill_bytes_zero(logp_new, n_rows * sizeof(float), st));
-    UMAS_HIP(fill_bytes_zero(dH, static_cast<size_t>(n_rows) * d * esz, st));
+    UMAS_HIP(clear_bytes(st, logp_new, n_rows * sizeof(float), dH, static_cast<size_t>(n_rows) * d * esz));
   }
-  if (!accumulate_dW && n_sel == 0) UMAS_HIP(fill_bytes_zero(dW, static_cast<size_t>(V) * d * sizeof(float), st));
+  if (!accumulate_dW && n_sel == 0) UMAS_HIP(clear_bytes(st, dW, static_cast<size_t>(V) * d * sizeof(float)));
 
   // chunks of selected rows sized to the workspace
   const size_t room = workspace_bytes - w.fixed_bytes;
