@@ -119,6 +119,7 @@ __device__ __forceinline__ Stat shfl_xor(const Stat& x, int o) {
               __shfl_xor(x.zy, o, kWave)};
 }
 struct ScoreOut {
+  double* z;                                 // the logits [n_sel][V] for the backward (NULL: not kept)
   double* rest_c;                            // compact arrays (NULL: none): sum of the probabilities of the tokens not taken
   float *logp_c, *lse_c, *ent_c;
   float *logp, *lse, *entropy;               // scattered (NULL: none)
@@ -186,6 +187,7 @@ k_score_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int
           const int v = v0 + blk_row(i, r);
           if (v >= V) continue;
           const double z = acc[i][j][r], e = exp(z - m);
+          if (out.z && n0 + blk_index(j) < n_sel) out.z[(n0 + blk_index(j)) * V + v] = z;
           q.s += e;
           q.t = fma(e, z, q.t);
           if (v == y[j]) q.zy = z; else q.rest += e;
@@ -226,6 +228,7 @@ k_score_f32_row(const float* __restrict__ W, const float* __restrict__ H, int d,
     const float* w = W + static_cast<int64_t>(v) * d;
     double z = 0.0;
     for (int k = 0; k < d; ++k) z = fma(static_cast<double>(s_h[k]), static_cast<double>(w[k]), z);
+    if (out.z) out.z[n * V + v] = z;
     a = merge(a, Stat{z, 1.0, z, v == y ? 0.0 : 1.0, v == y ? z : 0.0});
   }
 #pragma unroll
@@ -257,6 +260,12 @@ k_score_f32_merge(const Stat* __restrict__ part, int splits, int V, const int32_
 // forward pass.  The taken token's entry g (1 - p_y): for a confident token (p_y > 1/2) 1 - p_y cancels down to the error
 // of p_y, and the sum of the other probabilities, which carries only their relative error, is taken in its place.
 // Rows on the A side, so that sixteen lanes store consecutive vocabulary entries.
+__device__ __forceinline__ float dz_entry(double z, double l, double g, double en, double k_ent, bool taken, const double* rest) {
+  const double p = exp(z - l);
+  const double e = k_ent != 0.0 ? k_ent * p * ((z - l) + en) : 0.0;     // entropy bonus: k p (log p + entropy)
+  const double dense = taken ? g * (p > 0.5 ? *rest : 1.0 - p) : -g * p;
+  return static_cast<float>(dense + e);
+}
 __global__ void __launch_bounds__(kWaves* kWave)
 k_dz_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel, int64_t c0,
          int64_t rows, const int32_t* __restrict__ ids, const float* __restrict__ lse_c, const double* __restrict__ rest_c,
@@ -289,12 +298,25 @@ k_dz_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int V,
       for (int j = 0; j < 2; ++j) {
         const int v = v0 + blk_index(j);
         if (v >= V) continue;
-        const double z = acc[i][j][r], p = exp(z - l);
-        const double e = k_ent != 0.0 ? k_ent * p * ((z - l) + en) : 0.0;     // entropy bonus: k p (log p + entropy)
-        const double dense = v == y ? g * (p > 0.5 ? rest_c[n] : 1.0 - p) : -g * p;
-        dz[m * V + v] = static_cast<float>(dense + e);
+        dz[m * V + v] = dz_entry(acc[i][j][r], l, g, en, k_ent, v == y, rest_c + n);
       }
     }
+}
+// The same from the logits that the scoring pass has kept, where the workspace holds them: one workgroup per row and 1024
+// vocabulary entries.  2400 rows of 300 against 4000 156 us as a product, now 22 (and 25 more in the
+// scoring pass), 1600 rows of 451 against 5001 253 and 17, 768 rows of 64 against 512 15 and 7.
+__global__ void __launch_bounds__(256)
+k_dz_kept_f32(const double* __restrict__ z, int V, const int32_t* __restrict__ rowsel, int64_t c0, const int32_t* __restrict__ ids,
+              const float* __restrict__ lse_c, const double* __restrict__ rest_c, const float* __restrict__ g_c,
+              const float* __restrict__ ent_c, const float* __restrict__ kz_c, float* __restrict__ dz) {
+  const int64_t m = blockIdx.y, n = c0 + m;
+  const int y = ids[rowsel ? rowsel[n] : n];
+  const double l = lse_c[n], g = g_c[n], en = ent_c[n], k_ent = kz_c[n];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int v = blockIdx.x * 1024 + k * 256 + threadIdx.x;
+    if (v < V) dz[m * V + v] = dz_entry(z[n * V + v], l, g, en, k_ent, v == y, rest_c + n);
+  }
 }
 
 // The two gradient products.  A workgroup of eight wavefronts takes WM x WN tiles of 32 x 32 and 8 / (WM WN) parts of K,

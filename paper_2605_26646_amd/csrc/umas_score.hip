@@ -1520,6 +1520,11 @@ size_t chunk_bytes(int64_t mc, int d, int V, umas_dtype dt) {
 size_t logit_chunk_bytes(int64_t mc, int d, int V) {
   return chunk_bytes(mc, d, V, UMAS_BF16) + static_cast<size_t>(round_up(mc, 256)) * round_up(V, 256) * 2;
 }
+// The float32 update keeps the logits (float64) of all its rows where that is no more than 1 GiB.
+size_t f32_logit_bytes(int64_t n_sel, int V) {
+  const double b = static_cast<double>(n_sel) * V * sizeof(double);
+  return b <= 1073741824.0 ? align_up(static_cast<size_t>(n_sel) * V * sizeof(double)) : 0;
+}
 // How the dH product of a chunk is cut along the vocabulary.  dH has tiles_r x tiles_d tiles of the whole vocabulary's K
 // each; with few row tiles that is fewer long tiles than compute units, and the launch lasts as long as one of them (3.6 ms
 // at V = 151 936 whether there are 64 rows or 2000).  Below kDhSliceTiles, one tile per compute unit, they are cut into about
@@ -1675,9 +1680,10 @@ int row_panel(int tiles_n, int d) {
 }
 
 // Forward scoring of the selected rows into compact arrays and/or scattered outputs.  float32: `room` holds statistics of
-// parts of the vocabulary (no room: one workgroup per 32 rows walks all of it), rest_c goes with the compact arrays.
+// parts of the vocabulary (no room: one workgroup per 32 rows walks all of it), rest_c goes with the compact arrays, z (may be
+// NULL) takes the logits.
 umas_status run_score(const void* H, const void* W, umas_dtype dt, int d, int V, const int32_t* ids,
-                      const int32_t* rowsel, int64_t n_sel, const ScoreWs& w, void* room, size_t room_bytes, double* rest_c,
+                      const int32_t* rowsel, int64_t n_sel, const ScoreWs& w, void* room, size_t room_bytes, double* z, double* rest_c,
                       float* logp, float* lse, float* entropy, hipStream_t st) {
   if (n_sel == 0) return UMAS_OK;
   if (dt == UMAS_BF16) {
@@ -1710,7 +1716,7 @@ umas_status run_score(const void* H, const void* W, umas_dtype dt, int d, int V,
     UMAS_LAUNCHED("k_score_finalize");
   } else {
     return f32::score(static_cast<const float*>(W), static_cast<const float*>(H), d, V, rowsel, n_sel, ids, room, room_bytes,
-                      f32::ScoreOut{rest_c, w.logp_c, w.lse_c, w.ent_c, logp, lse, entropy}, st);
+                      f32::ScoreOut{z, rest_c, w.logp_c, w.lse_c, w.ent_c, logp, lse, entropy}, st);
   }
   return UMAS_OK;
 }
@@ -1749,7 +1755,7 @@ extern "C" umas_status umas_policy_logprobs(const void* H, const void* W, umas_d
   Carver c(workspace);
   ScoreWs w;
   carve_score(c, w, n_sel, V, dtype, false);
-  return run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w, workspace, workspace_bytes, nullptr, logp, lse, entropy, st);
+  return run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w, workspace, workspace_bytes, nullptr, nullptr, logp, lse, entropy, st);
 }
 
 // ------------------------------------------------------------------ scoring without any allocation
@@ -1805,7 +1811,7 @@ extern "C" umas_status umas_policy_logprobs_static(const void* H, const void* W,
   Carver c(ws);
   ScoreWs w;
   carve_score(c, w, n_sel, V, dtype, false);
-  return run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w, nullptr, 0, nullptr, logp, lse, entropy, st);
+  return run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w, nullptr, 0, nullptr, nullptr, logp, lse, entropy, st);
 }
 
 extern "C" size_t umas_ppo_loss_workspace_bytes_min(int64_t n_sel, int32_t d, int32_t V, umas_dtype dtype,
@@ -1834,7 +1840,7 @@ extern "C" size_t umas_ppo_loss_workspace_bytes(int64_t n_sel, int32_t d, int32_
   size_t chunk = chunk_bytes(mc, d, V, dtype);
   if (dtype == UMAS_BF16)
     chunk = std::max(chunk, logit_chunk_bytes(mc >= n_sel && logit_chunk_bytes(mc, d, V) <= kLogitBytes ? mc : round_up((mc + 1) / 2, 256), d, V));
-  return c.off + chunk + (dtype == UMAS_BF16 ? full_part_bytes(n_sel, mc, d, V) : 0);
+  return c.off + chunk + (dtype == UMAS_BF16 ? full_part_bytes(n_sel, mc, d, V) : f32_logit_bytes(n_sel, V));
 }
 
 extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_dtype dtype, int64_t n_rows, int32_t d,
@@ -1937,11 +1943,15 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     return UMAS_OK;
   };
 
+  // float32: the logits lie behind the chunk's dz
+  const size_t z_at = dtype == UMAS_F32 ? chunk_bytes(mc, d, V, dtype) : 0;
+  double* const z_kept = dtype == UMAS_F32 && f32_logit_bytes(n_sel, V) > 0 && z_at + f32_logit_bytes(n_sel, V) <= room
+                             ? reinterpret_cast<double*>(w.chunk + z_at) : nullptr;
   if (mc_z > 0) {
     // chunk by chunk, further down
   } else if (!keep) {
     // forward scoring and the surrogate
-    s = run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w.score, w.chunk, room, w.rest, logp_new, nullptr, nullptr, st);
+    s = run_score(H, W, dtype, d, V, ids, rowsel, n_sel, w.score, w.chunk, z_kept ? z_at : room, z_kept, w.rest, logp_new, nullptr, nullptr, st);
     if (s != UMAS_OK) return s;
     s = ppo_rows(0, n_sel);
     if (s != UMAS_OK) return s;
@@ -2005,9 +2015,13 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     for (int64_t c0 = 0; c0 < n_sel; c0 += mc) {
       const int64_t rows = n_sel - c0 < mc ? n_sel - c0 : mc;
       const float *Wf = static_cast<const float*>(W), *Hf = static_cast<const float*>(H);
-      hipLaunchKernelGGL(f32::k_dz_f32, dim3(cdiv(V, f32::kVocBlock), cdiv(rows, f32::kTile)), dim3(f32::kWaves * kWave), 0, st, Wf, Hf, d, V,
-                         rowsel, c0, rows, ids, w.score.lse_c, w.rest, w.g_c, w.score.ent_c, w.kz_c, dz);
-      UMAS_LAUNCHED("k_dz_f32");
+      if (z_kept)
+        hipLaunchKernelGGL(f32::k_dz_kept_f32, dim3(cdiv(V, 1024), static_cast<unsigned>(rows)), dim3(256), 0, st, z_kept, V, rowsel, c0, ids,
+                           w.score.lse_c, w.rest, w.g_c, w.score.ent_c, w.kz_c, dz);
+      else
+        hipLaunchKernelGGL(f32::k_dz_f32, dim3(cdiv(V, f32::kVocBlock), cdiv(rows, f32::kTile)), dim3(f32::kWaves * kWave), 0, st, Wf, Hf, d, V,
+                           rowsel, c0, rows, ids, w.score.lse_c, w.rest, w.g_c, w.score.ent_c, w.kz_c, dz);
+      UMAS_LAUNCHED(z_kept ? "k_dz_kept_f32" : "k_dz_f32");
       auto grid = [](int64_t m, int64_t n, int tiles) { return dim3(cdiv(m, tiles * f32::kTile), cdiv(n, tiles * f32::kTile)); };
       if (f32::large_product(rows, d))
         hipLaunchKernelGGL((f32::k_dh_f32<2, 2>), grid(rows, d, 2), dim3(f32::kGradT), 0, st, dz, Wf, d, V, rowsel, c0, rows, static_cast<float*>(dH));

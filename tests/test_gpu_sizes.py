@@ -524,3 +524,27 @@ def test_hidden_sizes_between_multiples_of_64(n_sel, d):
     check_update(rng, n_sel + 30, d, 1030, entropy_coef=0.01)
     check_update(rng, n_sel + 30, d, 1030, entropy_coef=0.01,
                  workspace=torch.empty(umas.ppo_workspace_bytes(int(0.8 * (n_sel + 30)), d, 1030, torch.bfloat16, 0, minimum=True), dtype=torch.uint8, device="cuda"))
+
+
+# float32: the logits kept in the workspace (all rows, one chunk of them and several) and, in the smallest workspace, computed again
+@pytest.mark.parametrize("n,d,V", [(1, 3, 5), (40, 64, 1023), (300, 20, 1025), (1500, 33, 300), (4097, 16, 600)])
+@pytest.mark.parametrize("entropy_coef", [0.0, 0.05])
+def test_float32_logits_kept_and_computed_twice(n, d, V, entropy_coef):
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    H, W = torch.randn(n, d, device="cuda", generator=gen), 0.5 * torch.randn(V, d, device="cuda", generator=gen)
+    ids = torch.randint(0, V, (n,), device="cuda", generator=gen, dtype=torch.int32)
+    adv, old = torch.randn(n, device="cuda", generator=gen), -4 + torch.randn(n, device="cuda", generator=gen)
+    sel = torch.randperm(n, device="cuda", generator=gen)[:max(1, n - n // 5)].to(torch.int32)
+    sizes = [umas.ppo_workspace_bytes(len(sel), d, V, torch.float32, 0, minimum=m) for m in (False, True)]
+    out = []
+    for nbytes, kernel in zip(sizes, ("k_dz_kept_f32", "k_dz_f32")):
+        umas.profile_enable(True)
+        try:
+            out.append(umas.umas_ppo_loss_fwd_bwd(H, W, ids, sel, old, adv, None, 0, 0.2, entropy_coef=entropy_coef,
+                                                  workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda").fill_(255)))
+            assert kernel in umas.profile_read()
+        finally:
+            umas.profile_enable(False)
+    # float64 sums in other orders (the row kernel's, the tiles'), rounded to float32 where log-probs and dz are stored
+    for a, b in zip(out[0][1:], out[1][1:]):
+        assert float((a - b).norm()) <= 2.0 ** -21 * float(a.norm())
