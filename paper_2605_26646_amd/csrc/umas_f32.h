@@ -320,8 +320,8 @@ k_dz_kept_f32(const double* __restrict__ z, int V, const int32_t* __restrict__ r
 }
 
 // The two gradient products.  A workgroup of eight wavefronts takes WM x WN tiles of 32 x 32 and 8 / (WM WN) parts of K,
-// whose sums meet in LDS in a fixed order.  <1, 1> spreads small products over the chip (dW of 512 x 64: 32 workgroups);
-// from 256 tiles of 64 x 64 on <2, 2> reads half as much from L2.
+// whose sums meet in LDS in a fixed order.  <1, 1> spreads small products over the chip (dW of 512 x 64: 32 workgroups),
+// <2, 2> reads half as much from L2 (see large_product).
 constexpr int kGradWaves = 8, kGradT = kGradWaves * kWave;
 template <int WM, int WN, class OA, class OB, class F>
 __device__ __forceinline__ void gradient_tile(OA& a, OB& b, int K, F store) {
@@ -445,7 +445,13 @@ inline umas_status score(const float* W, const float* H, int d, int V, const int
   }
   return UMAS_OK;
 }
-inline bool large_product(int64_t m, int64_t n) { return cdiv(m, 2 * kTile) * static_cast<int64_t>(cdiv(n, 2 * kTile)) >= 256; }
+// <2, 2> where its tiles fill whole rounds of 256 compute units, or nearly: it takes as long as the rounds, <1, 1> a tenth longer than
+// the tiles would in full ones (dW of 4000 x 300, 315 tiles: 257 us in <2, 2>, 184 in <1, 1>; 5001 x 451, 632: 221 and 202; 8192
+// x 512, 1024: 164 and 179).
+inline bool large_product(int64_t m, int64_t n) {
+  const int64_t tiles = cdiv(m, 2 * kTile) * static_cast<int64_t>(cdiv(n, 2 * kTile));
+  return (tiles + 255) / 256 * 256 * 10 <= tiles * 11;
+}
 
 }  // namespace f32
 }  // namespace umas
