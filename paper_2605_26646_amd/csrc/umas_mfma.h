@@ -59,10 +59,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base) {
 // then the wavefront waits for its LDS reads and for all loads but the youngest ones (A of step j+2: loads into
 // LDS return in the order they were issued), the workgroup meets at the barrier, and phase 3 runs while the first
 // fragments of the next step are read.
+// A_POLICY is the cache policy of operand A's loads: kCached, or kStream for an operand that is read once.
 // With TAIL the last step holds fewer than 64 k: the chunks of a row past its end repeat the row's last chunk, and the threads that
 // loaded them clear them in LDS, in both operands (a product with a value that is not finite would not be 0 otherwise), in front
 // of the barrier behind which the step is read.  (A loop with registers and a second LDS pitch in place of this one: 2500 rows of
 // 1544 against 50 001 532 us, now 391; 700 rows of 3000 against 80 001 466 us, now 340; 5000 rows kept 3.95 ms, now 2.66.)
+constexpr int kCached = 0, kStream = 2;
 template <class C>
 struct Ring2Cfg {
   static constexpr int BK = 64;
@@ -82,7 +84,7 @@ __device__ __forceinline__ int ring2_kofs(int t = threadIdx.x) {
   return 8 * ((t & 7) ^ (((t >> 3) >> 1) & 7));
 }
 
-template <class C, bool TAIL>
+template <class C, bool TAIL, int A_POLICY>
 __device__ __forceinline__ void mfma_mainloop_ring2(__amdgpu_buffer_rsrc_t ra, const uint32_t (&oa)[Ring2Cfg<C>::NA],
                                                     __amdgpu_buffer_rsrc_t rb, const uint32_t (&ob)[Ring2Cfg<C>::NB],
                                                     int K, uint16_t* lds, floatx4 (&acc)[C::MI][C::NI]) {
@@ -106,7 +108,7 @@ __device__ __forceinline__ void mfma_mainloop_ring2(__amdgpu_buffer_rsrc_t ra, c
 #pragma unroll
     for (int i = 0; i < R::NA; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, reinterpret_cast<uint32_t*>(sa + i * R::ROWS_PER_PASS * R::ROWB), 16,
-                                               TAIL ? oa[i] - cut : oa[i], kbytes, 0, 0);
+                                               TAIL ? oa[i] - cut : oa[i], kbytes, 0, A_POLICY);
   };
   auto gload_b = [&](int sub, int ib) {
     const int kbytes = sub * R::BK * 2;

@@ -89,13 +89,18 @@ hipError_t clear_bytes(hipStream_t st, void* a, size_t bytes_a, void* b = nullpt
   return e;
 }
 
+// Where every weight is read by one tile only (one column tile) and W is larger than the memory-side cache, it is read past it: 203
+// rows of 3584 against 152 064, keeping 300 -> 270 us, 100 and 200 rows of 2048 against 151 936, scoring 153 -> 143 and 187 -> 182.
+// A smaller W may still lie there from the call before (250 rows of 1024 against 30 001, 61 MB: 28 us, past the cache 31).
+__device__ __forceinline__ bool beyond_cache(int d, int V) { return static_cast<int64_t>(V) * d * 2 > int64_t{256} << 20; }
+
 // Logit tile Z[v, n] = W[m0 + v, :] . H[row(n0 + n), :] for a 256x256 block of (vocabulary, selected rows),
 // row(n) = rowsel[sel0 + n] or sel0 + n.  Rows past V and past n_lim are clamped to valid ones; the
 // callers mask what comes out of them.
 template <class C>
 __device__ __forceinline__ void logit_tile(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
                                            const int32_t* __restrict__ rowsel, int64_t sel0, int64_t n_lim, int m0,
-                                           int64_t n0, uint16_t* lds, floatx4 (&acc)[C::MI][C::NI]) {
+                                           int64_t n0, bool w_once, uint16_t* lds, floatx4 (&acc)[C::MI][C::NI]) {
 #pragma unroll
   for (int i = 0; i < C::MI; ++i)
 #pragma unroll
@@ -111,8 +116,9 @@ __device__ __forceinline__ void logit_tile(const uint16_t* __restrict__ W, const
     ob[i] = (static_cast<uint32_t>(rowsel ? rowsel[n] : n) * d + kofs) * 2u;   // host checks n_rows*d*2 < 2^32
   }
   const __amdgpu_buffer_rsrc_t ra = make_rsrc(W + static_cast<int64_t>(m0) * d), rb = make_rsrc(H);
-  if (d % C::BK == 0) mfma_mainloop_ring2<C, false>(ra, oa, rb, ob, d, lds, acc);
-  else mfma_mainloop_ring2<C, true>(ra, oa, rb, ob, d, lds, acc);
+  if (d % C::BK != 0) mfma_mainloop_ring2<C, true, kCached>(ra, oa, rb, ob, d, lds, acc);
+  else if (w_once) mfma_mainloop_ring2<C, false, kStream>(ra, oa, rb, ob, d, lds, acc);
+  else mfma_mainloop_ring2<C, false, kCached>(ra, oa, rb, ob, d, lds, acc);
 }
 
 // ------------------------------------------------------------------ bf16: logit tiles -> partials
@@ -166,7 +172,7 @@ __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, cons
   const int m0 = tile_m * C::BM;
   const int64_t n0 = static_cast<int64_t>(tile_n) * C::BN;   // chunk-relative
   floatx4 acc[C::MI][C::NI];
-  logit_tile<C>(W, H, d, V, rowsel, c0, mc, m0, n0, lds, acc);
+  logit_tile<C>(W, H, d, V, rowsel, c0, mc, m0, n0, tiles_n == 1 && beyond_cache(d, V), lds, acc);
 
   // epilogue: the tile buffers are free now.  A lane holds, for each of its NI columns (selected rows), the
   // vocabulary entries vbase + 16 i + r (i < MI, r < 4); the four lanes l, l + 16, l + 32, l + 48 share a column.
@@ -890,7 +896,7 @@ __device__ __forceinline__ void dz_tile(int tile_m, int tile_n, const uint16_t* 
   const int m0 = tile_m * C::BM;
   const int64_t n0 = static_cast<int64_t>(tile_n) * C::BN;   // chunk-relative
   floatx4 acc[C::MI][C::NI];
-  logit_tile<C>(W, H, d, V, rowsel, c0, mc, m0, n0, lds, acc);
+  logit_tile<C>(W, H, d, V, rowsel, c0, mc, m0, n0, false, lds, acc);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / C::WN;
