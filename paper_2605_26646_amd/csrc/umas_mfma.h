@@ -242,7 +242,8 @@ struct KContig {                // an operand tile stored K-contiguous: per-slot
   uint32_t hi_bytes;            // added once more per 256 k (an operand stored in blocks of 256 columns), else 0
 };
 
-template <class C, bool ATR, bool BTR, int AHEAD>
+// B_STREAM: operand B is read once, past the caches
+template <class C, bool ATR, bool BTR, int AHEAD, bool B_STREAM = false>
 __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMajor& ka, const KContig& cb, const KMajor& kb,
                                                     int K, uint16_t* lds, floatx4 (&acc)[C::MI][C::NI]) {
   using R = Ring2Cfg<C>;
@@ -266,15 +267,29 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
   // l & 31 of row k = 16 p + 2 wave + (l >> 5) and fetches unit slot ^ 4 (k & 3) ^ 2 ((k >> 3) & 1)
   const int tr_krow = 2 * wave + (lane >> 5);        // + 16 p
   const int tr_slot_unit = (lane & 31) ^ (4 * (tr_krow & 3)) ^ (2 * ((tr_krow >> 3) & 1));
+  auto kmajor_units = [&](const KMajor& k) { return static_cast<uint32_t>(min(tr_slot_unit, k.n_units - 1)) * 16u; };
+  auto kmajor_step = [&](const KMajor& k, int sub) { return min(sub * R::BK, ((k.k_rows - 1) / R::BK) * R::BK); };   // first k-row of the (clamped) step
+  auto kmajor_rsrc = [&](const KMajor& k, int k0) { return make_rsrc(k.base + static_cast<int64_t>(k0) * k.ld_bytes + (k0 >> 8) * k.hi_bytes); };
+  auto kmajor_offset = [&](const KMajor& k, int k0, int p) {
+    return static_cast<uint32_t>(min(16 * p + tr_krow, k.k_rows - 1 - k0)) * static_cast<uint32_t>(k.ld_bytes);
+  };
   auto gload_kmajor = [&](const KMajor& k, int sub, char* region) {
-    const uint32_t ubytes = static_cast<uint32_t>(min(tr_slot_unit, k.n_units - 1)) * 16u;
-    const int k0 = min(sub * R::BK, ((k.k_rows - 1) / R::BK) * R::BK);          // first k-row of the (clamped) step
-    const __amdgpu_buffer_rsrc_t r = make_rsrc(k.base + static_cast<int64_t>(k0) * k.ld_bytes + (k0 >> 8) * k.hi_bytes);
+    const uint32_t ubytes = kmajor_units(k);
+    const int k0 = kmajor_step(k, sub);
+    const __amdgpu_buffer_rsrc_t r = kmajor_rsrc(k, k0);
 #pragma unroll
     for (int p = 0; p < 4; ++p)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(r, reinterpret_cast<uint32_t*>(region + (16 * p + 2 * wave) * 512), 16,
-                                               static_cast<uint32_t>(min(16 * p + tr_krow, k.k_rows - 1 - k0)) * static_cast<uint32_t>(k.ld_bytes) + ubytes,
-                                               0, 0, 0);
+                                               kmajor_offset(k, k0, p) + ubytes, 0, 0, kCached);
+  };
+  auto gload_kmajor_stream = [&](const KMajor& k, int sub, char* region) {     // the policy is part of the instruction
+    const uint32_t ubytes = kmajor_units(k);
+    const int k0 = kmajor_step(k, sub);
+    const __amdgpu_buffer_rsrc_t r = kmajor_rsrc(k, k0);
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, reinterpret_cast<uint32_t*>(region + (16 * p + 2 * wave) * 512), 16,
+                                               kmajor_offset(k, k0, p) + ubytes, 0, 0, kStream);
   };
   auto gload_kcontig = [&](const KContig& c, int sub, char* region) {
     const int kbytes = sub * R::BK * 2 + (sub >> 2) * static_cast<int>(c.hi_bytes);
@@ -289,7 +304,7 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
   };
   auto gload_b = [&](int sub, int ib) {
     char* sb = base + kBBase + ib * kBStage;
-    if (BTR) gload_kmajor(kb, sub, sb); else gload_kcontig(cb, sub, sb);
+    if (BTR && B_STREAM) gload_kmajor_stream(kb, sub, sb); else if (BTR) gload_kmajor(kb, sub, sb); else gload_kcontig(cb, sub, sb);
   };
 
   // fragment addresses (K-contiguous operands as in mfma_mainloop_ring2)
