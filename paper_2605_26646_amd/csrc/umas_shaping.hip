@@ -97,28 +97,32 @@ __device__ __forceinline__ int model_of(const ModelOffsets& mo, int n_models, in
 }
 
 // Sum over the wavefront, in its last lane: six moves between lanes that go with an add (row_shr 1, 2, 4, 8 inside the rows of
-// 16 lanes, then the rows' sums handed on), no trips through LDS.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int lane_move(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false); }
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float lane_move(float v) { return __int_as_float(lane_move<CTRL, ROWS>(__float_as_int(v))); }
-template <int CTRL, int ROWS>
+// 16 lanes, then lane 15 of every row handed to the next and lane 31 to the upper half), no trips through LDS. Lanes without a source add 0;
+// every move writes all rows, so that it and its float32 add are one instruction (what the other lanes hold is not used).
+template <int CTRL>
+__device__ __forceinline__ int lane_move(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true); }
+template <int CTRL>
+__device__ __forceinline__ float lane_move(float v) { return __int_as_float(lane_move<CTRL>(__float_as_int(v))); }
+template <int CTRL>
 __device__ __forceinline__ double lane_move(double v) {
-  return __hiloint2double(lane_move<CTRL, ROWS>(__double2hiint(v)), lane_move<CTRL, ROWS>(__double2loint(v)));
+  return __hiloint2double(lane_move<CTRL>(__double2hiint(v)), lane_move<CTRL>(__double2loint(v)));
 }
 constexpr int kGroupRounds = 8;
 template <typename T>
 __device__ __forceinline__ T last_lane_sum(T v) {
-  v += lane_move<0x111, 0xF>(v);
-  v += lane_move<0x112, 0xF>(v);
-  v += lane_move<0x114, 0xF>(v);
-  v += lane_move<0x118, 0xF>(v);
-  v += lane_move<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
-  v += lane_move<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+  v += lane_move<0x111>(v);
+  v += lane_move<0x112>(v);
+  v += lane_move<0x114>(v);
+  v += lane_move<0x118>(v);
+  v += lane_move<0x142>(v);   // row_bcast:15
+  v += lane_move<0x143>(v);   // row_bcast:31
   return v;
 }
 
 // Pass 1: per block and group (sum A, sum A^2, count) over the mask=1 tokens, float64.
+// 9 B/token are read at 3.9-4.8 TB/s; what a wavefront executes per 256 tokens counts as much as the memory does. With the model found once
+// per wavefront and the lanes' sums in one instruction a step (both were per token and two): 40 million tokens in turns of 400
+// 99 -> 87 us, 25 million in turns of 256 60 -> 58, 5.6 million in turns of 700 16.3 -> 14.0, 11.5 million in turns of 16 43 -> 36.
 __global__ void __launch_bounds__(kST)
 k_whiten_sums(int64_t n, const float* __restrict__ adv, const uint8_t* __restrict__ mask, const int32_t* __restrict__ role,
               ModelOffsets mo, int n_models, int n_roles, int by_role, double* __restrict__ blk) {
@@ -129,8 +133,12 @@ k_whiten_sums(int64_t n, const float* __restrict__ adv, const uint8_t* __restric
   const int64_t stride = static_cast<int64_t>(gridDim.x) * kST * 4;
   const int lane = threadIdx.x & (kWave - 1);
   // whole wavefronts go round: their sums are taken across all lanes
-  for (int64_t w0 = (static_cast<int64_t>(blockIdx.x) * kST + (threadIdx.x - lane)) * 4; w0 < n; w0 += stride) {
+  const int wave0 = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) - lane);
+  for (int64_t w0 = (static_cast<int64_t>(blockIdx.x) * kST + wave0) * 4; w0 < n; w0 += stride) {
     const int64_t p0 = w0 + lane * 4;
+    // the model, once for the 256 tokens where none begins among them
+    const int mw = model_of(mo, n_models, w0);
+    const bool one_model = mw + 1 == n_models || mo.off[mw + 1] >= w0 + 4 * kWave;
     float a[4];
     uint8_t m[4];
     int rl[4] = {0, 0, 0, 0};
@@ -155,17 +163,22 @@ k_whiten_sums(int64_t n, const float* __restrict__ adv, const uint8_t* __restric
     }
     // group of each of the four tokens (-1 = not counted)
     int gk[4];
+    const int per_model = by_role ? n_roles : 1;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      gk[k] = -1;
-      if (!m[k] || (by_role && (rl[k] < 0 || rl[k] >= n_roles))) continue;   // a role outside [0, n_roles) joins no group
-      gk[k] = by_role ? model_of(mo, n_models, p0 + k) * n_roles + rl[k] : model_of(mo, n_models, p0 + k);
+      const bool counted = m[k] && static_cast<unsigned>(rl[k]) < static_cast<unsigned>(per_model);   // a role outside [0, n_roles) joins no group
+      gk[k] = counted ? mw * per_model + rl[k] : -1;
+    }
+    if (!one_model) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (gk[k] >= 0) gk[k] += (model_of(mo, n_models, p0 + k) - mw) * per_model;
     }
     // Usual case: every counted token of the wavefront's 256 belongs to one group.  Their sums are formed in
     // float32 across the lanes (256 values: rounding far below the float32 inputs' own) and one lane adds them
     // to the float64 accumulators.  Where turns of several groups meet in the 256 the groups take turns, in float64 (every lane
     // adding its own tokens in LDS queued on the groups' three words: 40 million tokens in turns of 400 by five roles 356 us,
-    // in turns 98); only what is left after kGroupRounds groups goes lane by lane.
+    // in turns 87); only what is left after kGroupRounds groups goes lane by lane.
     auto first_group = [&]() {
       int g = -1;
 #pragma unroll
