@@ -445,8 +445,8 @@ def main():
             ms = event_times_ms(torch, lambda: umas.umas_ppo_loss_fwd_bwd(
                 H, W, ids, st0.rowsel[:n_sel], logp_old, adv_all, st0.tok_role, w.n_roles, w.clip_eps, dW=dW, dH=dH,
                 logp_new=logp_new, stats=stats, workspace=view), 5 if nbytes == ws_min else 10, 1)
-            # the same call on the path that recomputes the logits in the backward instead of keeping the numerators
-            # (an entropy coefficient too small to change a bit of the result selects it): the trade in numbers
+            # the same call on the path of an entropy bonus (a coefficient too small to change a bit of the result selects
+            # it), which keeps float32 logits, or recomputes them, instead of keeping the numerators: the trade in numbers
             if nbytes == ws_min:
                 rec = None                       # minutes at 256-row chunks: left out
             else:
