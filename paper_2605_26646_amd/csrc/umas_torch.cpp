@@ -27,10 +27,11 @@ struct Failed {};   // a Python error is set
   PyErr_Format(PyExc_TypeError, "%s expected, got %s", what, Py_TYPE(got)->tp_name);
   throw Failed();
 }
-// integers as ctypes takes them: no other number types, more bits than fit are cut off
+// anything with __index__ (Python's and numpy's integers), no floats; more bits than fit are cut off
 int64_t integer(PyObject* o) {
-  if (!PyLong_Check(o)) type_error("int", o);
-  return static_cast<int64_t>(PyLong_AsUnsignedLongLongMask(o));
+  const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
+  if (v == static_cast<unsigned long long>(-1) && PyErr_Occurred()) throw Failed();
+  return static_cast<int64_t>(v);
 }
 int32_t integer32(PyObject* o) { return static_cast<int32_t>(integer(o)); }
 int64_t as_int(PyObject* o) {                             // int(o)

@@ -1,0 +1,48 @@
+"""The native half of the binding reads its arguments on the host; every call here is refused by the library's own checks before
+any launch (no GPU)."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_26646_amd as umas
+from paper_2605_26646_amd import binding
+
+
+@pytest.fixture(scope="module")
+def native():
+    if not os.path.exists(umas.lib_path()):
+        import __graft_entry__ as g
+        g.build()
+    return binding._native()
+
+
+def assign(native, **kw):
+    """The native routing call on a graph that the library refuses (role 1 on a model that does not exist) and its message."""
+    a = dict(n_roles=2, n_models=1, role_to_model=np.array([0, 1], np.int32), traj_turn_off=np.array([0, 2], np.int32), turn_role=np.array([0, 1], np.int32),
+             turn_tok_off=np.array([0, 3, 5]), mask=torch.ones(5, dtype=torch.uint8), turn_pred_off=None, turn_pred=None, traj_group=None, role_reward=None,
+             turn_reward=None, traj_reward=None, w_role=None, w_turn=None, w_traj=None, place_mode=0, norm_eps=1e-6, stream=0)
+    status = native.assign(*{**a, **kw}.values())
+    return status, umas.load_library().umas_last_error().decode()
+
+
+class Index:
+    def __init__(self, value):
+        self.value = value
+
+    def __index__(self):
+        return self.value
+
+
+@pytest.mark.parametrize("number", [int, np.int64, np.int32, np.uint8, Index, lambda v: torch.tensor(v), lambda v: np.array(v)])
+def test_integers_of_every_kind_are_taken(native, number):
+    want = assign(native)
+    assert want[0] == -1 and "role_to_model" in want[1]
+    assert assign(native, n_roles=number(2), n_models=number(1), place_mode=number(0), stream=number(0)) == want
+
+
+@pytest.mark.parametrize("value", [2.0, np.float32(2), "2", None])
+def test_other_numbers_are_refused(native, value):
+    with pytest.raises(TypeError):
+        assign(native, n_roles=value)
