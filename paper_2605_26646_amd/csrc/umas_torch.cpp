@@ -104,7 +104,8 @@ struct Selection {                                        // None: all rows; an 
 };
 
 PyObject* ascontiguousarray = nullptr;                    // numpy's
-// A host array of the ABI's type: the object's own memory where it has that type and is contiguous, else numpy's copy.
+// A host array of the ABI's type: the object's own memory where it has that type, is contiguous and lies at a multiple of the type's
+// size, else numpy's copy.
 struct HostArray {
   Py_buffer view{};
   bool held = false;
@@ -118,7 +119,14 @@ struct HostArray {
       PyErr_Clear();
       PyObject* a = PyObject_CallFunction(ascontiguousarray, "Os", o, np_type);
       if (!a) throw Failed();
-      const bool ok = take(a, kind, size);                // the view holds the array
+      bool ok = take(a, kind, size);                      // the view holds the array
+      if (!ok) {                                          // the right type and contiguous, but not aligned
+        PyErr_Clear();
+        PyObject* const c = PyObject_CallMethod(a, "copy", nullptr);
+        Py_DECREF(a);
+        if (!(a = c)) throw Failed();
+        ok = take(a, kind, size);
+      }
       Py_DECREF(a);
       if (!ok) {
         if (!PyErr_Occurred()) PyErr_Format(PyExc_TypeError, "array of %s expected", np_type);
@@ -134,7 +142,7 @@ struct HostArray {
   bool take(PyObject* o, char kind, int size) {           // kind: i(nteger), u(nsigned), f(loat)
     if (PyObject_GetBuffer(o, &view, PyBUF_FORMAT | PyBUF_C_CONTIGUOUS) != 0) return false;
     const char* f = view.format;
-    bool ok = f && f[0] && !f[1] && view.itemsize == size;
+    bool ok = f && f[0] && !f[1] && view.itemsize == size && reinterpret_cast<uintptr_t>(view.buf) % size == 0;
     if (ok) ok = kind == 'i' ? f[0] == 'i' || f[0] == 'l' || f[0] == 'q' : kind == 'u' ? f[0] == 'B' : f[0] == 'f';
     if (!ok) PyBuffer_Release(&view);
     held = ok;

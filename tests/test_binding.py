@@ -46,3 +46,25 @@ def test_integers_of_every_kind_are_taken(native, number):
 def test_other_numbers_are_refused(native, value):
     with pytest.raises(TypeError):
         assign(native, n_roles=value)
+
+
+def unaligned(a):
+    """The same values at an odd address."""
+    raw = np.empty(a.nbytes + 1, np.uint8)
+    out = raw[1:].view(a.dtype)
+    out[:] = a
+    assert out.ctypes.data % a.itemsize
+    return out
+
+
+def as_view(a):
+    """... behind a buffer that names its type but not where it lies."""
+    return memoryview(unaligned(a).view(np.uint8)).cast(a.dtype.char)
+
+
+@pytest.mark.parametrize("place", [unaligned, as_view])
+def test_arrays_at_any_address_are_taken(native, place):
+    want = assign(native)
+    assert want[0] == -1 and "role_to_model" in want[1]
+    assert assign(native, role_to_model=place(np.array([0, 1], np.int32)), turn_tok_off=place(np.array([0, 3, 5])),
+                  norm_eps=1e-6, w_role=place(np.ones(2, np.float32))) == want
