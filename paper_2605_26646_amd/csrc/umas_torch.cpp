@@ -115,7 +115,7 @@ struct HostArray {
   ~HostArray() { if (held) PyBuffer_Release(&view); }
   void get(PyObject* o, char kind, int size, const char* np_type) {
     if (o == Py_None) return;
-    if (!(PyObject_CheckBuffer(o) && take(o, kind, size))) {
+    if (PyBytes_Check(o) || !(PyObject_CheckBuffer(o) && take(o, kind, size))) {   // bytes: text to numpy
       PyErr_Clear();
       PyObject* a = PyObject_CallFunction(ascontiguousarray, "Os", o, np_type);
       if (!a) throw Failed();

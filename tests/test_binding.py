@@ -68,3 +68,17 @@ def test_arrays_at_any_address_are_taken(native, place):
     assert want[0] == -1 and "role_to_model" in want[1]
     assert assign(native, role_to_model=place(np.array([0, 1], np.int32)), turn_tok_off=place(np.array([0, 3, 5])),
                   norm_eps=1e-6, w_role=place(np.ones(2, np.float32))) == want
+
+
+def streams(n_turns=2):
+    """A Streams object whose tensors nobody reads: the calls below are refused first."""
+    one = torch.zeros(1, dtype=torch.int64)
+    return umas.Streams(0, n_turns, 1, *[one] * 16)
+
+
+def test_bytes_are_no_array(native):
+    # numpy reads them as text, and so did the binding before it read buffers itself
+    with pytest.raises(ValueError):
+        native.ready_batch(streams(), np.array([0, 2], np.int32), 0, 0, b"\x01", None, 0)
+    status = native.ready_batch(streams(), np.array([0, 2], np.int32), 0, 0, bytearray(b"\x01"), None, 0)
+    assert status == -1 and "n_minibatch" in umas.load_library().umas_last_error().decode()
