@@ -133,7 +133,7 @@ struct HostArray {
         throw Failed();
       }
     }
-    len = view.ndim > 0 ? view.shape[0] : 0;
+    len = view.ndim > 0 ? view.shape[0] : 1;                // a single number: one entry
   }
   template <class T>
   const T* as() const { return held ? static_cast<const T*>(view.buf) : nullptr; }
@@ -233,6 +233,8 @@ PyObject* assign(PyObject* const* a) {
   umas_rewards r;
   g.n_roles = integer32(a[0]);
   g.n_models = integer32(a[1]);
+  for (int i : {3, 5})                                    // offsets have a length
+    if (a[i] != Py_None && PyObject_Size(a[i]) < 0) throw Failed();
   I32_ARRAY(role_to_model, a[2]);
   I32_ARRAY(traj_turn_off, a[3]);
   I32_ARRAY(turn_role, a[4]);

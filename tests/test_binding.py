@@ -82,3 +82,13 @@ def test_bytes_are_no_array(native):
         native.ready_batch(streams(), np.array([0, 2], np.int32), 0, 0, b"\x01", None, 0)
     status = native.ready_batch(streams(), np.array([0, 2], np.int32), 0, 0, bytearray(b"\x01"), None, 0)
     assert status == -1 and "n_minibatch" in umas.load_library().umas_last_error().decode()
+
+
+def test_offsets_without_a_dimension(native):
+    """A single number has one entry, as numpy's ascontiguousarray gives it; the offsets of trajectories and turns need a dimension."""
+    error = lambda: umas.load_library().umas_last_error().decode()
+    assert native.ready_batch(streams(), np.array(0, np.int32), 0, 1, None, None, 0) == -1 and "from 0 to n_turns" in error()
+    for zero in (np.array(0), np.array(0, np.int32), 0):
+        for name in ("traj_turn_off", "turn_tok_off"):
+            with pytest.raises(TypeError):
+                assign(native, **{name: zero})
