@@ -1572,8 +1572,14 @@ size_t full_part_bytes(int64_t n_sel, int64_t chunk_rows, int d, int V) {
 // The update with an entropy bonus keeps the logits of a chunk in float32 instead of computing them a second time where the
 // workspace has room for chunks that are not small: the whole selection, or chunks whose dH tiles are whole ones (the same bits
 // of dH as from larger workspaces).  0: it has not, the logits are computed twice.
+// So they are for hidden sizes below kLogitWidth: a second product costs by the hidden size, the 10 bytes a logit that are stored and
+// read more do not.  Update, computed twice / kept, 203, 700 and 3000 rows against 151 937: d = 256 211 / 220, 391 / 465, 1282 / 1622 us;
+// 512 288 / 282, 578 / 613, 1985 / 2067; 640 355 / 336, 714 / 738, 2414 / 2459; 768 383 / 356, 765 / 763, 2610 / 2579; 896 452 / 386,
+// 924 / 880, 3166 / 3011.
+constexpr int kLogitWidth = 768;
 constexpr size_t kLogitBytes = size_t{6} << 30;            // what the workspace is sized for (a second chunk adds to dW: 0.5 ms)
 int64_t logit_chunk_rows(int64_t n_sel, int d, int V, size_t room) {
+  if (d < kLogitWidth) return 0;
   if (round_up(V, 256) / 256 > 8192) return 0;             // 32-bit offsets along a row of blocks
   if (dh_tiles(n_sel, d) < kDhSliceTiles) return logit_chunk_bytes(n_sel, d, V) + full_part_bytes(n_sel, n_sel, d, V) <= room ? n_sel : 0;
   const int64_t fit = std::min(static_cast<int64_t>(room / logit_chunk_bytes(256, d, V)) * 256, kMaxChunkRows);
