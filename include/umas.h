@@ -221,17 +221,20 @@ typedef struct {
   int64_t n_invalid_ids;   /* selected rows whose token id is outside [0,V) */
 } umas_loss_stats;
 
-/* Smallest workspace the call accepts and the size at which it runs in the fewest passes.  For bf16 the
- * workspace holds, per chunk of selected rows, the bf16 operand of the two gradient products
+/* Smallest workspace the call accepts and the size at which it runs in the fewest passes, without and with an entropy
+ * bonus.  For bf16 the workspace holds, per chunk of selected rows, the bf16 operand of the two gradient products
  * [rows, V] (rounded up to multiples of 256) and a scaled bf16 copy of the chunk's rows of H; the
- * smallest size runs in chunks of 256 rows, the full size in chunks of up to 65536 rows; it also holds the float32
- * logits that an update with an entropy bonus keeps (of all rows up to 6 GiB, else of half a chunk).  Where there is little of dH to
+ * smallest size runs in chunks of 256 rows, the full size in chunks of up to 65536 rows.  Every call takes any of the sizes;
+ * the one with an entropy bonus also holds the float32 logits that such an update keeps (of all rows up to 6 GiB,
+ * else of half a chunk), twice the bytes of the operand, which other updates do not touch.  Where there is little of dH to
  * work on at a time (ceil(rows / 256) ceil(d / 256) blocks: a selection of fewer than 256, or chunks of fewer than 128) it is
  * summed over slices of the vocabulary, as many as the workspace has room for: there the rounding of dH depends on the
  * size of the workspace, and the full size holds the float32 partial sums.  Larger selections have the same bits of dH with
- * every workspace that holds chunks of 128 blocks.  (dW is summed in float32 chunk after chunk.) */
+ * every workspace that holds chunks of 128 blocks.  (dW is summed in float32 chunk after chunk.)  float32: the full
+ * sizes are the same. */
 size_t umas_ppo_loss_workspace_bytes_min(int64_t n_sel, int32_t d, int32_t V, umas_dtype dtype, int32_t n_roles);
 size_t umas_ppo_loss_workspace_bytes(int64_t n_sel, int32_t d, int32_t V, umas_dtype dtype, int32_t n_roles);
+size_t umas_ppo_loss_workspace_bytes_entropy(int64_t n_sel, int32_t d, int32_t V, umas_dtype dtype, int32_t n_roles);
 
 /* Steps a5-a7 for one model's stream (each worker group updates its own model, paragraph
  * "Model-specific updates and synchronization"): scoring as above, then the single-clip PPO

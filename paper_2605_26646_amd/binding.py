@@ -108,13 +108,14 @@ def load_library():
     lib.umas_last_error.restype = C.c_char_p
     for name in ("umas_assign_workspace_bytes", "umas_advantages_workspace_bytes",
                  "umas_policy_logprobs_workspace_bytes", "umas_ppo_loss_workspace_bytes",
-                 "umas_ppo_loss_workspace_bytes_min"):
+                 "umas_ppo_loss_workspace_bytes_min", "umas_ppo_loss_workspace_bytes_entropy"):
         getattr(lib, name).restype = C.c_size_t
     lib.umas_assign_workspace_bytes.argtypes = [C.c_void_p]
     lib.umas_advantages_workspace_bytes.argtypes = [C.c_int64]
     lib.umas_policy_logprobs_workspace_bytes.argtypes = [C.c_int64, C.c_int32, C.c_int32, C.c_int]
     lib.umas_ppo_loss_workspace_bytes.argtypes = [C.c_int64, C.c_int32, C.c_int32, C.c_int, C.c_int32]
     lib.umas_ppo_loss_workspace_bytes_min.argtypes = [C.c_int64, C.c_int32, C.c_int32, C.c_int, C.c_int32]
+    lib.umas_ppo_loss_workspace_bytes_entropy.argtypes = [C.c_int64, C.c_int32, C.c_int32, C.c_int, C.c_int32]
     lib.umas_assign_token_rewards.restype = C.c_int
     lib.umas_assign_token_rewards.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                               C.c_size_t, C.c_void_p]
@@ -247,10 +248,13 @@ def umas_policy_logprobs_static(H: torch.Tensor, W: torch.Tensor, ids: torch.Ten
     return _done(_native().policy_logprobs_static(H, W, ids, rowsel, logp, lse, entropy, _stream()))
 
 
-def ppo_workspace_bytes(n_sel, d, V, dtype: torch.dtype, n_roles, minimum=False) -> int:
+def ppo_workspace_bytes(n_sel, d, V, dtype: torch.dtype, n_roles, minimum=False, entropy_bonus=True) -> int:
+    """The size for updates with or without an entropy bonus; entropy_bonus=False leaves out what only one with a bonus uses (up
+    to half of the bytes)."""
     lib = load_library()
     code = UMAS_BF16 if dtype == torch.bfloat16 else UMAS_F32
-    f = lib.umas_ppo_loss_workspace_bytes_min if minimum else lib.umas_ppo_loss_workspace_bytes
+    f = (lib.umas_ppo_loss_workspace_bytes_min if minimum else
+         lib.umas_ppo_loss_workspace_bytes_entropy if entropy_bonus else lib.umas_ppo_loss_workspace_bytes)
     return int(f(n_sel, d, V, code, n_roles))
 
 

@@ -1840,8 +1840,9 @@ extern "C" size_t umas_ppo_loss_workspace_bytes_min(int64_t n_sel, int32_t d, in
   return c.off + chunk_bytes(mc, d, V, dtype);
 }
 
-extern "C" size_t umas_ppo_loss_workspace_bytes(int64_t n_sel, int32_t d, int32_t V, umas_dtype dtype,
-                                                int32_t n_roles) {
+namespace {
+// The size at which an update runs in the fewest passes; `bonus`: with room for the logits that one with an entropy bonus keeps.
+size_t full_ppo_bytes(int64_t n_sel, int d, int V, umas_dtype dtype, int n_roles, bool bonus) {
   if (n_sel < 0 || d < 1 || V < 1 || n_roles < 0) return 0;
   Carver c(nullptr);
   PpoWs w;
@@ -1852,11 +1853,20 @@ extern "C" size_t umas_ppo_loss_workspace_bytes(int64_t n_sel, int32_t d, int32_
     const int64_t nchunk = (mc + cap - 1) / cap;
     mc = round_up((mc + nchunk - 1) / nchunk, 256);
   }
-  // with an entropy bonus: the logits of the whole selection, of half a chunk where they are many
   size_t chunk = chunk_bytes(mc, d, V, dtype);
-  if (dtype == UMAS_BF16)
+  if (dtype == UMAS_F32) return c.off + chunk + f32_logit_bytes(n_sel, V);       // kept with any coefficient
+  // the logits of the whole selection, of half a chunk where they are many
+  if (bonus)
     chunk = std::max(chunk, logit_chunk_bytes(mc >= n_sel && logit_chunk_bytes(mc, d, V) <= kLogitBytes ? mc : round_up((mc + 1) / 2, 256), d, V));
-  return c.off + chunk + (dtype == UMAS_BF16 ? full_part_bytes(n_sel, mc, d, V) : f32_logit_bytes(n_sel, V));
+  return c.off + chunk + full_part_bytes(n_sel, mc, d, V);
+}
+}  // namespace
+
+extern "C" size_t umas_ppo_loss_workspace_bytes(int64_t n_sel, int32_t d, int32_t V, umas_dtype dtype, int32_t n_roles) {
+  return full_ppo_bytes(n_sel, d, V, dtype, n_roles, false);
+}
+extern "C" size_t umas_ppo_loss_workspace_bytes_entropy(int64_t n_sel, int32_t d, int32_t V, umas_dtype dtype, int32_t n_roles) {
+  return full_ppo_bytes(n_sel, d, V, dtype, n_roles, true);
 }
 
 extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_dtype dtype, int64_t n_rows, int32_t d,

@@ -350,11 +350,14 @@ PyObject* ppo_loss(PyObject* const* a) {
   const Output dH(a[16], [&] { return at::empty_like(H.t); });
   const Output logp_new(a[17], [&] { return fresh({H.n}, at::kFloat, dev); });
   const Output stats(a[18], [&] { return fresh({(1 + static_cast<int64_t>(n_roles)) * static_cast<int64_t>(sizeof(umas_loss_stats))}, at::kByte, dev); });
-  const Output ws(a[19], [&] { return workspace(umas_ppo_loss_workspace_bytes(sel.n, H.d, V, dt, n_roles), dev); });
+  const float clip_eps = real(a[8]), entropy_coef = real(a[9]), dual_clip = real(a[10]), kl_coef = real(a[14]);
+  const Output ws(a[19], [&] {
+    const auto bytes = entropy_coef > 0.f ? umas_ppo_loss_workspace_bytes_entropy : umas_ppo_loss_workspace_bytes;
+    return workspace(bytes(sel.n, H.d, V, dt, n_roles), dev);
+  });
   sel.point(ws.t.data_ptr(), a[3]);
   const float* const logp_old = ptr_or_null<const float>(a[4]);
   const int32_t* const role = ptr_or_null<const int32_t>(a[6]);
-  const float clip_eps = real(a[8]), entropy_coef = real(a[9]), dual_clip = real(a[10]), kl_coef = real(a[14]);
   const int32_t accumulate = truth(a[11]);
   const int64_t norm_rows = as_int(a[12]);
   const float* const logp_ref = ptr_or_null<const float>(a[13]);

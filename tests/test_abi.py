@@ -48,6 +48,20 @@ def test_workspace_queries(lib):
     assert lib.umas_policy_logprobs_workspace_bytes(1000, 64, 512, 0) > 0
 
 
+@pytest.mark.parametrize("n,d,V", [(203, 3584, 152064), (2900, 2048, 151936), (10000, 2048, 151936), (39224, 2048, 151936), (200000, 1024, 50001)])
+def test_room_for_kept_logits_is_asked_for_with_a_bonus_only(lib, n, d, V):
+    pad = lambda x: -(-x // 256) * 256
+    small, plain, bonus = (getattr(lib, "umas_ppo_loss_workspace_bytes" + which)(n, d, V, 1, 3) for which in ("_min", "", "_entropy"))
+    rows = n if n <= 65536 else pad(-(-n // -(-n // 65536)))
+    operands = 2 * pad(rows) * (pad(V) + pad(d))
+    slices = 0 if pad(rows) * pad(d) >= 256 ** 3 else 512 * 256 ** 2 * 4      # partial sums of dH: at most two per compute unit
+    assert operands <= plain - small + 2 * pad(min(n, 256)) * (pad(V) + pad(d)) <= operands + slices
+    logits = 4 * pad(rows) * pad(V)
+    assert bonus >= plain + (0.49 * logits - 2 ** 27 if n * V * 4 < 5 << 30 else 0)
+    sizes = [getattr(lib, "umas_ppo_loss_workspace_bytes" + which)(500, 100, 3000, 0, 3) for which in ("", "_entropy")]
+    assert sizes[0] == sizes[1] >= 500 * 3000 * (4 + 8)                       # float32 keeps its logits with any coefficient
+
+
 def graph(**kw):
     from paper_2605_26646_amd import binding as b
     base = dict(n_roles=2, n_models=2, role_to_model=[0, 1], traj_turn_off=[0, 2], turn_role=[0, 1],

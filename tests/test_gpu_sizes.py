@@ -157,6 +157,21 @@ def test_updates_do_not_depend_on_the_address_of_dh(n, d, V):
     assert torch.equal(a, b) and torch.equal(a, c)
 
 
+@pytest.mark.parametrize("entropy_coef", [0.0, 0.01])
+def test_an_update_allocates_what_its_coefficient_needs(entropy_coef):
+    n, d, V = 3000, 776, 5000
+    H, W = torch.zeros(n, d, dtype=torch.bfloat16, device="cuda"), torch.zeros(V, d, dtype=torch.bfloat16, device="cuda")
+    ids, adv = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.ones(n, device="cuda")
+    out = dict(dW=torch.empty(V, d, device="cuda"), dH=torch.empty_like(H), logp_new=torch.empty(n, device="cuda"), stats=torch.empty(64, dtype=torch.uint8, device="cuda"))
+    plain, bonus = (umas.ppo_workspace_bytes(n, d, V, torch.bfloat16, 0, entropy_bonus=b) for b in (False, True))
+    assert bonus > plain + (24 << 20)
+    before = torch.cuda.memory_allocated()
+    torch.cuda.reset_peak_memory_stats()
+    umas.umas_ppo_loss_fwd_bwd(H, W, ids, None, None, adv, None, 0, 0.2, entropy_coef=entropy_coef, **out)
+    used = torch.cuda.max_memory_allocated() - before
+    assert 0 <= used - (bonus if entropy_coef else plain) <= 4 << 20          # the allocator's rounding
+
+
 # chunks of the update: as few as the workspace allows, from the smallest one (256 rows a chunk) to the recommended one (even
 # chunks of at most 65 536 rows), and never more rows than fit
 @pytest.mark.parametrize("dt,n,fit", [("bf16", 131072, None), ("bf16", 131073, None), ("bf16", 5000, 1792), ("bf16", 5000, 256), ("bf16", 3000, 2816),
