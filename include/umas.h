@@ -225,8 +225,10 @@ typedef struct {
  * bonus.  For bf16 the workspace holds, per chunk of selected rows, the bf16 operand of the two gradient products
  * [rows, V] (rounded up to multiples of 256) and a scaled bf16 copy of the chunk's rows of H; the
  * smallest size runs in chunks of 256 rows, the full size in chunks of up to 65536 rows.  Every call takes any of the sizes;
- * the one with an entropy bonus also holds the float32 logits that such an update keeps (of all rows up to 6 GiB,
- * else of half a chunk), twice the bytes of the operand, which other updates do not touch.  Where there is little of dH to
+ * the one with an entropy bonus also holds the float32 logits that such an update keeps, twice the bytes of the operand, which
+ * other updates do not touch: of all rows up to 6 GiB, of half a chunk beyond.  With d < 768, or where half a
+ * chunk has fewer than 128 blocks of dH (see below; a whole selection of fewer than 256 that goes beyond 6 GiB), no logits are kept and
+ * the two sizes are the same.  Where there is little of dH to
  * work on at a time (ceil(rows / 256) ceil(d / 256) blocks: a selection of fewer than 256, or chunks of fewer than 128) it is
  * summed over slices of the vocabulary, as many as the workspace has room for: there the rounding of dH depends on the
  * size of the workspace, and the full size holds the float32 partial sums.  Larger selections have the same bits of dH with
@@ -269,9 +271,9 @@ size_t umas_ppo_loss_workspace_bytes_entropy(int64_t n_sel, int32_t d, int32_t V
  * (2 * rows * V bytes: 11.9 GB for 39 224 rows against V = 151 936 in one chunk).  With entropy_coef = 0 the
  * matrix holds the softmax numerators exp(z - z_y), written by the scoring pass itself, so the logits are computed
  * once; with an entropy bonus it holds dz, which overwrites the float32 logits that the scoring pass leaves there (4 *
- * rows * V bytes) where the workspace has room for them, and is written by a second pass over the logits where it has
- * not.  Only umas_policy_logprobs keeps everything of that shape on chip.  The workspace bounds it: the call works in chunks of as many rows as the workspace holds (256
- * at the least), at the price of one more pass over W per chunk.  The float32 path stores float32 dz per chunk and,
+ * rows * V bytes) where d >= 768 and the workspace has room for them, and is written by a second pass over the logits
+ * elsewhere.  Only umas_policy_logprobs keeps everything of that shape on chip.  The workspace bounds it: the call works in
+ * chunks of as many rows as the workspace holds (256 at the least), at the price of one more pass over W per chunk.  The float32 path stores float32 dz per chunk and,
  * where the workspace has room for them, the float64 logits of all rows (up to 1 GiB; else they are computed twice). */
 umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_dtype dtype, int64_t n_rows,
                                   int32_t d, int32_t V, const int32_t* ids, const int32_t* rowsel,

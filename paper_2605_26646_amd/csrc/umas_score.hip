@@ -1855,10 +1855,14 @@ size_t full_ppo_bytes(int64_t n_sel, int d, int V, umas_dtype dtype, int n_roles
   }
   size_t chunk = chunk_bytes(mc, d, V, dtype);
   if (dtype == UMAS_F32) return c.off + chunk + f32_logit_bytes(n_sel, V);       // kept with any coefficient
-  // the logits of the whole selection, of half a chunk where they are many
-  if (bonus)
-    chunk = std::max(chunk, logit_chunk_bytes(mc >= n_sel && logit_chunk_bytes(mc, d, V) <= kLogitBytes ? mc : round_up((mc + 1) / 2, 256), d, V));
-  return c.off + chunk + full_part_bytes(n_sel, mc, d, V);
+  const size_t parts = full_part_bytes(n_sel, mc, d, V);
+  if (bonus) {
+    // the logits of the whole selection, of half a chunk where they are many; no room that the call would not keep logits in
+    const int64_t rows = mc >= n_sel && logit_chunk_bytes(mc, d, V) <= kLogitBytes ? mc : round_up((mc + 1) / 2, 256);
+    const size_t with = std::max(chunk, logit_chunk_bytes(rows, d, V));
+    if (logit_chunk_rows(n_sel, d, V, with + parts) > 0) chunk = with;
+  }
+  return c.off + chunk + parts;
 }
 }  // namespace
 

@@ -62,6 +62,13 @@ def test_room_for_kept_logits_is_asked_for_with_a_bonus_only(lib, n, d, V):
     assert sizes[0] == sizes[1] >= 500 * 3000 * (4 + 8)                       # float32 keeps its logits with any coefficient
 
 
+# heads too narrow for kept logits, and selections of fewer than 256 blocks of dH whose logits are more than 6 GiB
+@pytest.mark.parametrize("n,d,V", [(3000, 512, 50001), (700, 264, 3001), (12000, 1024, 151937), (16000, 1024, 151937), (17000, 768, 110001), (203, 768, 2097153)])
+def test_no_room_is_asked_for_where_no_logits_are_kept(lib, n, d, V):
+    plain, bonus = (getattr(lib, "umas_ppo_loss_workspace_bytes" + which)(n, d, V, 1, 3) for which in ("", "_entropy"))
+    assert plain == bonus
+
+
 def graph(**kw):
     from paper_2605_26646_amd import binding as b
     base = dict(n_roles=2, n_models=2, role_to_model=[0, 1], traj_turn_off=[0, 2], turn_role=[0, 1],
