@@ -91,8 +91,13 @@ hipError_t clear_bytes(hipStream_t st, void* a, size_t bytes_a, void* b = nullpt
 
 // Where every weight is read by one tile only (one column tile) and W is larger than the memory-side cache, it is read past it: 203
 // rows of 3584 against 152 064, keeping 300 -> 270 us, 100 and 200 rows of 2048 against 151 936, scoring 153 -> 143 and 187 -> 182.
-// A smaller W may still lie there from the call before (250 rows of 1024 against 30 001, 61 MB: 28 us, past the cache 31).
-__device__ __forceinline__ bool beyond_cache(int d, int V) { return static_cast<int64_t>(V) * d * 2 > int64_t{256} << 20; }
+// A smaller W may still lie there from the call before (250 rows of 1024 against 30 001, 61 MB: 28 us, past the cache 31), and
+// the better part of one that is a little larger: scoring 256 rows through the cache and past it on two cards, W of 257 MiB 102 and 114, 109 and
+// 116 us (d = 2048), 87 and 96, 89 and 96 (4096), 272 MiB 108 and 116, 119 and 117, 288 MiB 115 and 117, 123 and 119, 312 MiB 117
+// and 117, 125 and 120.  dH, which reads its other operand several times meanwhile, has its line at 256 MiB (update of 256 rows
+// of 1024, 264 MiB: 370 and 343, 384 and 358).
+constexpr int64_t kLogitsOnceBytes = int64_t{300} << 20, kDhOnceBytes = int64_t{256} << 20;
+__device__ __forceinline__ bool beyond_cache(int d, int V, int64_t bytes) { return static_cast<int64_t>(V) * d * 2 > bytes; }
 
 // Logit tile Z[v, n] = W[m0 + v, :] . H[row(n0 + n), :] for a 256x256 block of (vocabulary, selected rows),
 // row(n) = rowsel[sel0 + n] or sel0 + n.  Rows past V and past n_lim are clamped to valid ones; the
@@ -172,7 +177,7 @@ __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, cons
   const int m0 = tile_m * C::BM;
   const int64_t n0 = static_cast<int64_t>(tile_n) * C::BN;   // chunk-relative
   floatx4 acc[C::MI][C::NI];
-  logit_tile<C>(W, H, d, V, rowsel, c0, mc, m0, n0, tiles_n == 1 && beyond_cache(d, V), lds, acc);
+  logit_tile<C>(W, H, d, V, rowsel, c0, mc, m0, n0, tiles_n == 1 && beyond_cache(d, V, kLogitsOnceBytes), lds, acc);
 
   // epilogue: the tile buffers are free now.  A lane holds, for each of its NI columns (selected rows), the
   // vocabulary entries vbase + 16 i + r (i < MI, r < 4); the four lanes l, l + 16, l + 32, l + 48 share a column.
@@ -1313,7 +1318,7 @@ k_gemm_dh_dw(const uint16_t* __restrict__ dZ, int blk_pitch, int64_t Vp, int64_t
     if (seq < n_dh) {
       const int t = first_dh + seq, slice = t / tiles_mn;
       tile_of_groups<kGM, kGN>(t - slice * tiles_mn, n_live, tiles_d, &tile_m, &tile_n);
-      dh_tile(tile_m, blk_orig[(c0 >> 8) + tile_m], tile_n, slice, sl, tiles_r, tiles_d, dZ, blk_pitch, Vp, W, d, V, dH, rowsel, c0, rows, ids, g_c, sc, n_live == 1 && beyond_cache(d, V), lds);
+      dh_tile(tile_m, blk_orig[(c0 >> 8) + tile_m], tile_n, slice, sl, tiles_r, tiles_d, dZ, blk_pitch, Vp, W, d, V, dH, rowsel, c0, rows, ids, g_c, sc, n_live == 1 && beyond_cache(d, V, kDhOnceBytes), lds);
     } else {
       tile_of_groups<kGM, kGN>(first_dw + seq - n_dh, tiles_v, tiles_d, &tile_m, &tile_n);
       dw_tile(tile_m, tile_n, dZ, blk_pitch, mcp, Vp, Hs, d, V, n_live * 256, k_rows, dW, accumulate, lds);
