@@ -107,7 +107,7 @@ template <int CTRL>
 __device__ __forceinline__ double lane_move(double v) {
   return __hiloint2double(lane_move<CTRL>(__double2hiint(v)), lane_move<CTRL>(__double2loint(v)));
 }
-constexpr int kGroupRounds = 8;
+constexpr int kFewChanges = 8;
 template <typename T>
 __device__ __forceinline__ T last_lane_sum(T v) {
   v += lane_move<0x111>(v);
@@ -117,6 +117,17 @@ __device__ __forceinline__ T last_lane_sum(T v) {
   v += lane_move<0x142>(v);   // row_bcast:15
   v += lane_move<0x143>(v);   // row_bcast:31
   return v;
+}
+
+__device__ __forceinline__ uint32_t last_lane_or(uint32_t b) {       // the same for bits, in every lane
+  int v = static_cast<int>(b);
+  v |= lane_move<0x111>(v);
+  v |= lane_move<0x112>(v);
+  v |= lane_move<0x114>(v);
+  v |= lane_move<0x118>(v);
+  v |= lane_move<0x142>(v);
+  v |= lane_move<0x143>(v);
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(v, kWave - 1));
 }
 
 // Pass 1: per block and group (sum A, sum A^2, count) over the mask=1 tokens, float64.
@@ -178,7 +189,7 @@ k_whiten_sums(int64_t n, const float* __restrict__ adv, const uint8_t* __restric
     // float32 across the lanes (256 values: rounding far below the float32 inputs' own) and one lane adds them
     // to the float64 accumulators.  Where turns of several groups meet in the 256 the groups take turns, in float64 (every lane
     // adding its own tokens in LDS queued on the groups' three words: 40 million tokens in turns of 400 by five roles 356 us,
-    // in turns 87); only what is left after kGroupRounds groups goes lane by lane.
+    // in turns 87), or every lane adds its own: see below.
     auto first_group = [&]() {
       int g = -1;
 #pragma unroll
@@ -212,16 +223,51 @@ k_whiten_sums(int64_t n, const float* __restrict__ adv, const uint8_t* __restric
       add(static_cast<double>(sa), static_cast<double>(sq), n_in);
       continue;
     }
-    for (int round = 0;; ++round) {
-      if (round == kGroupRounds) {
+    // Turns or lane by lane?  Turns cost by the groups, about 6 us each for 11.5 million tokens, on top of 17.  Adds of single lanes queue where
+    // neighbouring lanes have the same group, and are four times as many in a lane of mixed tokens.  So few places where the
+    // group changes: turns, without counting the groups; else by their number and by how many lanes are mixed.  11.5 million tokens, turns
+    // and lanes: 16 roles, turns of 4 tokens 71 and 21 us, of 7 72 and 31, of 16 70 and 28, of 25 68 and 35, of 64 38 and 47; 3 roles, of 4 32 and
+    // 26, of 7 32 and 48, of 64 30 and 46; 4 roles that change with every token 40 and 174, 8 roles 68 and 50.
+    bool lane_mixed = false;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) lane_mixed = lane_mixed || (gk[k] >= 0 && gk[k] != g0);
+    const int mixed = __popcll(__ballot(lane_mixed));
+    const int changes = __popcll(__ballot(__builtin_amdgcn_update_dpp(g0, g0, 0x111, 0xF, 0xF, false) != g0));   // row_shr:1; not from row to row
+    bool turns = one_model;
+    if (one_model && changes + mixed > kFewChanges) {
+      uint32_t lo = 0u, hi = 0u;                             // a bit per role of the model
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t r = static_cast<uint32_t>(gk[k] - mw * per_model), bit = gk[k] >= 0 ? 1u << (r & 31) : 0u;
+        lo |= r < 32 ? bit : 0u;
+        hi |= r < 32 ? 0u : bit;
+      }
+      const int present = __popc(last_lane_or(lo)) + (n_roles > 32 ? __popc(last_lane_or(hi)) : 0);
+      turns = present <= (mixed > kWave / 2 ? 6 : mixed > 0 ? 4 : 2);
+    }
+    if (!turns) {
+      double sa = 0.0, sq = 0.0;
+      int n_in = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const double x = gk[k] >= 0 ? static_cast<double>(a[k]) : 0.0;
+        sa += x;
+        sq = fma(x, x, sq);
+        n_in += gk[k] >= 0;
+      }
+      if (lane_mixed) {
 #pragma unroll
         for (int k = 0; k < 4; ++k)
           if (gk[k] >= 0) {
             const double x = static_cast<double>(a[k]);
             atomicAdd(s_acc + 3 * gk[k], x); atomicAdd(s_acc + 3 * gk[k] + 1, x * x); atomicAdd(s_acc + 3 * gk[k] + 2, 1.0);
           }
-        break;
+      } else if (n_in) {
+        atomicAdd(s_acc + 3 * g0, sa); atomicAdd(s_acc + 3 * g0 + 1, sq); atomicAdd(s_acc + 3 * g0 + 2, static_cast<double>(n_in));
       }
+      continue;
+    }
+    for (;;) {
       double sa = 0.0, sq = 0.0;
       int n_in = 0;
 #pragma unroll

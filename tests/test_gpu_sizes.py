@@ -513,7 +513,7 @@ def test_whitening_statistics(n, n_roles):
 
 
 # a wavefront's 256 tokens hold one group, two, a few, more than eight; whole wavefronts and a last one of 1, 3 or 255 tokens
-@pytest.mark.parametrize("turn", [2, 25, 100, 400])
+@pytest.mark.parametrize("turn", [1, 2, 4, 7, 16, 25, 100, 400])
 @pytest.mark.parametrize("n,n_roles", [(1, 3), (259, 3), (1023, 64), (40 * 1024 + 257, 5), (300 * 1024 + 511, 17)])
 def test_whitening_statistics_of_turns(n, n_roles, turn):
     rng = np.random.default_rng([n, turn])
