@@ -79,7 +79,8 @@ umas_status ThinStage::begin(size_t bytes) {
     size_t cap = 1 << 16;
     while (cap < bytes) cap <<= 1;
     void* p = nullptr;
-    hipError_t e = hipHostMalloc(&p, cap, hipHostMallocPortable | hipHostMallocMapped);
+    // coherent: a kernel reads the block, at the same address again four calls later, and must not find old lines in a cache
+    hipError_t e = hipHostMalloc(&p, cap, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent);
     if (e != hipSuccess) return bail(e, "hipHostMalloc");
     e = hipHostGetDevicePointer(&s.dev, p, 0);
     if (e != hipSuccess) {

@@ -107,6 +107,23 @@ def test_thin_arrays_of_all_sizes_reach_the_device(n_traj):
     assert np.array_equal(off.cpu().numpy(), off_a) and np.array_equal(rows.cpu().numpy()[:len(rows_a)], rows_a)
 
 
+def test_blocks_that_a_kernel_reads_are_used_again():
+    """Three rounds over the staging ring with arrays of one size and other contents, behind long-running work: every call's kernel
+    reads the pinned block that an earlier call's kernel has read, with what the host has written there since."""
+    from tests import arraywise as aw
+    cases = [wl.make_workload(1, n_traj=430, tokens_per_turn=8, models=SMALL_BF16, seed_offset=k) for k in range(12)]
+    masks = [P.to_dev(w.tok_mask) for w in cases]
+    torch.cuda.synchronize()
+    queue_long_work(30)
+    outs = [umas.umas_assign_token_rewards(**assign_kwargs(w, mask)) for w, mask in zip(cases, masks)]
+    torch.cuda.synchronize()
+    for w, s in zip(cases, outs):
+        sa = aw.streams(w)
+        for f in ("perm", "tok_mask", "tok_flags"):
+            assert np.array_equal(getattr(s, f).cpu().numpy(), sa[f]), f
+        P.close(s.turn_scalar.cpu().numpy(), aw.composed_rewards(w), 1e-5, "turn_scalar")
+
+
 def test_results_do_not_depend_on_scheduling():
     """Two runs of the whole path on the same inputs: routing, placement, advantages, log-probs, statistics and dH are
     bit-equal (no atomics on their way); dW adds its one-hot rows with float atomics in whatever order the wavefronts
