@@ -151,6 +151,54 @@ def test_kept_logits_and_logits_computed_twice_give_the_same(n, d, V, fits):
         assert float((dH.float() - first[2].float()).norm()) <= 2.0 ** -8 * float(first[2].float().norm())
 
 
+# the same through a selection: two chunks of kept logits, the second of which begins in the middle of the selection, against one
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_chunks_of_kept_logits_through_a_selection(accumulate):
+    n, n_sel, d, V, n_roles, k = 10000, 32 * 256 - 3, 2048, 700, 3, 0.01
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    H = torch.randn(n, d, device="cuda", generator=gen).bfloat16()
+    W = (torch.randn(V, d, device="cuda", generator=gen) / d ** 0.5).bfloat16()
+    ids = torch.randint(0, V, (n,), device="cuda", generator=gen, dtype=torch.int32)
+    adv = torch.randn(n, device="cuda", generator=gen)
+    role = torch.randint(0, n_roles, (n,), device="cuda", generator=gen, dtype=torch.int32)
+    sel = torch.randperm(n, device="cuda", generator=gen)[:n_sel].to(torch.int32)
+    base = torch.randn(V, d, device="cuda", generator=gen)
+    results = []
+    for fit, chunks in ((0, 1), (16 * 256, 2)):
+        ws = None
+        if fit:
+            nbytes = umas.ppo_workspace_bytes(n_sel, d, V, torch.bfloat16, n_roles, minimum=True) + fit * (4 * 768 + 2 * d) - 512 * (768 + d)
+            ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda").fill_(255)
+        dW, dH, logp_new = base.clone(), torch.full_like(H, float("nan")), torch.full((n,), float("nan"), device="cuda")
+        umas.profile_enable(True)
+        try:
+            stats, *_ = umas.umas_ppo_loss_fwd_bwd(H, W, ids, sel, None, adv, role, n_roles, 0.2, entropy_coef=k, accumulate_dW=accumulate,
+                                                   dW=dW, dH=dH, logp_new=logp_new, workspace=ws)
+            assert umas.profile_read()["k_score_logits"][1] == chunks
+        finally:
+            umas.profile_enable(False)
+        results.append((umas.read_stats(stats), logp_new, dH, dW - base if accumulate else dW))
+    (stats, logp_new, dH, dW), (stats_2, logp_2, dH_2, dW_2) = results
+    assert np.array_equal(stats, stats_2) and torch.equal(logp_new, logp_2) and torch.equal(dH, dH_2)
+    # float64: dz = p (adv / n + k / n (log p + entropy)) - adv / n at the taken token, on-policy (ratio 1)
+    x, y, a = H[sel.long()].double(), ids[sel.long()].long(), adv[sel.long()].double()[:, None] / n_sel
+    z = x @ W.double().T
+    log_p = torch.log_softmax(z, 1)
+    p = log_p.exp()
+    dz = p * (a + k / n_sel * (log_p - (p * log_p).sum(1, keepdim=True)))
+    dz.scatter_add_(1, y[:, None], -a)
+    rest = torch.ones(n, dtype=torch.bool, device="cuda")
+    rest[sel.long()] = False
+    assert not logp_new[rest].any() and not dH[rest].any()
+    # as in test_rows_beyond_a_panel: roundings of the logits' sums; two roundings to bf16 in every product
+    bound = 4 * d ** 0.5 * 2.0 ** -24 * float((x[:256].abs() @ W.double().abs().T).max())
+    assert float((logp_new[sel.long()].double() - log_p.gather(1, y[:, None])[:, 0]).abs().max()) <= bound
+    # dW added to old values and these taken away again: three roundings of 2^-24 of the old values
+    over = 3 * 2.0 ** -24 * float(base.double().norm()) if accumulate else 0.0
+    for got, want, slack in ((dH[sel.long()], dz @ W.double(), 0.0), (dW, dz.T @ x, over), (dW_2, dz.T @ x, over)):
+        assert float((got.double() - want).norm()) <= 2.0 ** -8 * float(want.norm()) + slack
+
+
 @pytest.mark.parametrize("n,d,V", [(300, 64, 3000), (700, 1288, 5121)])
 def test_updates_do_not_depend_on_the_address_of_dh(n, d, V):
     (a, _), (b, _), (c, _) = updates(n, d, V, [(None, 0), (None, 2), (None, 4)])
@@ -194,12 +242,6 @@ def test_update_runs_in_as_few_chunks_as_the_workspace_allows(dt, n, fit):
     finally:
         umas.profile_enable(False)
     assert launches == chunks
-
-
-@pytest.mark.parametrize("n,d,V", [(300, 64, 3000), (700, 1288, 5121)])
-def test_updates_do_not_depend_on_the_address_of_dh(n, d, V):
-    (a, _), (b, _), (c, _) = updates(n, d, V, [(None, 0), (None, 2), (None, 4)])
-    assert torch.equal(a, b) and torch.equal(a, c)
 
 
 def check_scores(rng, n_sel, d, V, select, static):
@@ -278,8 +320,6 @@ def test_scoring_of_many_rows(n_sel):
     check_scores(np.random.default_rng(n_sel), n_sel, 64, 700, select=False, static=False)
 
 
-# the one-hot rows of dW: one group of 128 rows spread over many workgroups, several groups over a few, every row the same
-# token and every row another; and statistics per role when a wavefront holds one role, many, and roles outside the range
 # more rows than a panel of the logit kernels holds (32 tiles of 8192 columns): two panels of 24 and of 9 tiles, three of 24
 @pytest.mark.parametrize("n,V", [(8193, 600), (16641, 1300)])
 @pytest.mark.parametrize("entropy_coef", [None, 0.0, 0.01])
@@ -311,6 +351,8 @@ def test_rows_beyond_a_panel(n, V, entropy_coef):
         assert float((got.double() - want).norm() / want.norm()) <= 2.0 ** -8
 
 
+# the one-hot rows of dW: one group of 128 rows spread over many workgroups, several groups over a few, every row the same
+# token and every row another; and statistics per role when a wavefront holds one role, many, and roles outside the range
 @pytest.mark.parametrize("n,n_tokens", [(1, 1), (127, 1), (129, 129), (700, 3), (5000, 400)])
 def test_one_hot_rows_and_statistics_per_role(n, n_tokens):
     rng = np.random.default_rng(n)
@@ -512,7 +554,7 @@ def test_whitening_statistics(n, n_roles):
     assert (np.abs(out - want) <= bound).all()
 
 
-# a wavefront's 256 tokens hold one group, two, a few, more than eight; whole wavefronts and a last one of 1, 3 or 255 tokens
+# a wavefront's 256 tokens hold one group, two, a few, many, in lanes of one group and of several; whole wavefronts and a last one of 1, 3 or 255 tokens
 @pytest.mark.parametrize("turn", [1, 2, 4, 7, 16, 25, 100, 400])
 @pytest.mark.parametrize("n,n_roles", [(1, 3), (259, 3), (1023, 64), (40 * 1024 + 257, 5), (300 * 1024 + 511, 17)])
 def test_whitening_statistics_of_turns(n, n_roles, turn):
