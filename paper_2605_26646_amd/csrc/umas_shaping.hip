@@ -21,9 +21,12 @@ struct ModelOffsets {
   int64_t off[UMAS_MAX_MODELS + 1];
 };
 
-// r_out = r - beta (logp - logp_ref) on mask=1 tokens; per block (sum of logp - logp_ref, count).  The two log-probs are read past
-// the caches, which hold the rewards that routing has just written and the scan reads next (25 million tokens 108 -> 85 us;
+constexpr int64_t kCacheBytes = int64_t{256} << 20;      // the memory-side cache
+
+// r_out = r - beta (logp - logp_ref) on mask=1 tokens; per block (sum of logp - logp_ref, count).  With PAST the two log-probs are
+// read past the caches, which hold the rewards that routing has just written and the scan reads next (25 million tokens 108 -> 85 us;
 // with the next trip's loads under way as well 107 instead of 104: it is the memory's time).
+template <bool PAST>
 __global__ void __launch_bounds__(kST)
 k_kl_rewards(int64_t n, const float* r, const float* __restrict__ logp, const float* __restrict__ logp_ref,
              const uint8_t* __restrict__ mask, float beta, float* r_out, double* __restrict__ blk) {   // r_out may be r
@@ -37,7 +40,8 @@ k_kl_rewards(int64_t n, const float* r, const float* __restrict__ logp, const fl
 #pragma unroll
       for (int k = 0; k < kSIpt / 4; ++k) {
         const float4 r4 = *reinterpret_cast<const float4*>(r + p0 + 4 * k);
-        const float4 a4 = load_stream<float4>(logp + p0 + 4 * k), b4 = load_stream<float4>(logp_ref + p0 + 4 * k);
+        const float4 a4 = PAST ? load_stream<float4>(logp + p0 + 4 * k) : *reinterpret_cast<const float4*>(logp + p0 + 4 * k);
+        const float4 b4 = PAST ? load_stream<float4>(logp_ref + p0 + 4 * k) : *reinterpret_cast<const float4*>(logp_ref + p0 + 4 * k);
         rr[4 * k] = r4.x; rr[4 * k + 1] = r4.y; rr[4 * k + 2] = r4.z; rr[4 * k + 3] = r4.w;
         a[4 * k] = a4.x; a[4 * k + 1] = a4.y; a[4 * k + 2] = a4.z; a[4 * k + 3] = a4.w;
         b[4 * k] = b4.x; b[4 * k + 1] = b4.y; b[4 * k + 2] = b4.z; b[4 * k + 3] = b4.w;
@@ -419,8 +423,12 @@ extern "C" umas_status umas_kl_rewards(const float* tok_reward, const float* log
   prof_mark(st);
   const unsigned grid = stream_grid(n_tokens, kST * kSIpt);
   double* blk = static_cast<double*>(workspace);
-  hipLaunchKernelGGL(k_kl_rewards, dim3(grid), dim3(kST), 0, st, n_tokens, tok_reward, logp, logp_ref, tok_mask, beta,
-                     tok_reward_out, blk);
+  // Past the caches where the rewards fit them and the 13 bytes a token that are read do not.  Smaller: the log-probs may lie there as
+  // well; larger: the rewards do not either.  In place again and again, through the caches and past them: 8 million tokens 27 and 30 us, 16 46
+  // and 51, 25 69 and 75 (behind routing 108 and 85), 40 138 and 113, 64 216 and 209, 80 269 and 276, 101 342 and 351.
+  const bool past = 13 * n_tokens > kCacheBytes && 4 * n_tokens <= kCacheBytes;
+  if (past) hipLaunchKernelGGL(k_kl_rewards<true>, dim3(grid), dim3(kST), 0, st, n_tokens, tok_reward, logp, logp_ref, tok_mask, beta, tok_reward_out, blk);
+  else hipLaunchKernelGGL(k_kl_rewards<false>, dim3(grid), dim3(kST), 0, st, n_tokens, tok_reward, logp, logp_ref, tok_mask, beta, tok_reward_out, blk);
   UMAS_LAUNCHED("k_kl_rewards");
   hipLaunchKernelGGL(k_kl_mean, dim3(1), dim3(256), 0, st, blk, static_cast<int>(grid), kl_mean);
   UMAS_LAUNCHED("k_kl_mean");

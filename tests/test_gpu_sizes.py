@@ -606,3 +606,19 @@ def test_float32_logits_kept_and_computed_twice(n, d, V, entropy_coef):
     # float64 sums in other orders (the row kernel's, the tiles'), rounded to float32 where log-probs and dz are stored
     for a, b in zip(out[0][1:], out[1][1:]):
         assert float((a - b).norm()) <= 2.0 ** -21 * float(a.norm())
+
+
+# the log-probs of the KL penalty are read through the caches or past them, by what of the call fits the 256 MiB of the last one
+@pytest.mark.parametrize("n", [(256 << 20) // 13, (256 << 20) // 13 + 1, 64 << 20, (64 << 20) + 1])
+def test_kl_rewards_on_both_sides_of_the_cache(n):
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    r, logp = torch.randn(n, device="cuda", generator=gen), -torch.rand(n, device="cuda", generator=gen)
+    ref = logp + 0.1 * torch.randn(n, device="cuda", generator=gen)
+    mask = (torch.rand(n, device="cuda", generator=gen) < 0.7).to(torch.uint8)
+    out, kl = umas.umas_kl_rewards(r, logp, ref, mask, 0.05)
+    diff = (logp - ref) * mask
+    want = r - 0.05 * diff
+    # one rounding of the product (or none) and one of the sum on either side
+    assert ((out - want).abs() <= 2.0 ** -23 * (r.abs() + diff.abs())).all() and torch.equal(out[mask == 0], r[mask == 0])
+    mean = float(diff.double().sum()) / int(mask.sum())
+    assert abs(float(kl) - mean) <= 2.0 ** -23 * abs(mean) + 2.0 ** -40
