@@ -622,3 +622,16 @@ def test_kl_rewards_on_both_sides_of_the_cache(n):
     assert ((out - want).abs() <= 2.0 ** -23 * (r.abs() + diff.abs())).all() and torch.equal(out[mask == 0], r[mask == 0])
     mean = float(diff.double().sum()) / int(mask.sum())
     assert abs(float(kl) - mean) <= 2.0 ** -23 * abs(mean) + 2.0 ** -40
+
+
+# ... and the whitened advantages leave the same two ways
+@pytest.mark.parametrize("n,scope", [((256 << 20) // 13, umas.WHITEN_MODEL_ROLE), ((256 << 20) // 13 + 1, umas.WHITEN_MODEL_ROLE), ((256 << 20) // 9 + 1, umas.WHITEN_MODEL)])
+def test_whitening_on_both_sides_of_the_cache(n, scope):
+    rng = np.random.default_rng(n)
+    adv, mask, role = (1 + rng.standard_normal(n, dtype=np.float32)), (rng.random(n, dtype=np.float32) < 0.8).astype(np.uint8), rng.integers(0, 2, size=n, dtype=np.int32)
+    off = np.array([0, n // 3, n])
+    out = umas.umas_whiten_advantages(P.to_dev(adv), P.to_dev(mask), P.to_dev(role), off, 2, scope).cpu().numpy()
+    a64 = adv.astype(np.float64)
+    want = orc.whiten_advantages(a64, mask, role, off, 2, scope)
+    assert not out[mask == 0].any()
+    assert (np.abs(out - want) <= P.whiten_bounds(a64, mask, role, off, 2, scope == umas.WHITEN_MODEL_ROLE)).all()
