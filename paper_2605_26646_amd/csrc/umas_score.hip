@@ -1535,9 +1535,15 @@ size_t chunk_bytes(int64_t mc, int d, int V, umas_dtype dt) {
 size_t logit_chunk_bytes(int64_t mc, int d, int V) {
   return chunk_bytes(mc, d, V, UMAS_BF16) + static_cast<size_t>(round_up(mc, 256)) * round_up(V, 256) * 2;
 }
-// The float32 update keeps the logits (float64) of all its rows where that is no more than 1 GiB.
-size_t f32_logit_bytes(int64_t n_sel, int V) {
-  const double b = static_cast<double>(n_sel) * V * sizeof(double);
+// The float32 update keeps the logits (float64) of all its rows where that is no more than 1 GiB; below 64 columns, whose second product
+// costs less than storing and reading them, only where they and dz stay in the memory-side cache.  Update, computed twice / kept: 20 000 rows
+// against 1000 (229 MiB of the two) d = 8 619 / 584, 32 720 / 669 us; 10 000 against 3200 (366) d = 16 553 / 585, 32 629 / 639, 48 674 / 668, 64
+// 718 / 693; 12 000 against 8000 d = 16 1121 / 1277, 32 1310 / 1404, 48 1517 / 1543, 64 1694 / 1639; 40 000 against 1000 d = 32
+// 1384 / 1434, 64 1499 / 1513, 96 1727 / 1703.
+constexpr int kF32LogitWidth = 64;
+size_t f32_logit_bytes(int64_t n_sel, int d, int V) {
+  const double n = static_cast<double>(n_sel) * V, b = n * sizeof(double);
+  if (d < kF32LogitWidth && n * (sizeof(double) + sizeof(float)) > 268435456.0) return 0;
   return b <= 1073741824.0 ? align_up(static_cast<size_t>(n_sel) * V * sizeof(double)) : 0;
 }
 // How the dH product of a chunk is cut along the vocabulary.  dH has tiles_r x tiles_d tiles of the whole vocabulary's K
@@ -1859,7 +1865,7 @@ size_t full_ppo_bytes(int64_t n_sel, int d, int V, umas_dtype dtype, int n_roles
     mc = round_up((mc + nchunk - 1) / nchunk, 256);
   }
   size_t chunk = chunk_bytes(mc, d, V, dtype);
-  if (dtype == UMAS_F32) return c.off + chunk + f32_logit_bytes(n_sel, V);       // kept with any coefficient
+  if (dtype == UMAS_F32) return c.off + chunk + f32_logit_bytes(n_sel, d, V);       // kept with any coefficient
   const size_t parts = full_part_bytes(n_sel, mc, d, V);
   if (bonus) {
     // the logits of the whole selection, of half a chunk where they are many; no room that the call would not keep logits in
@@ -1980,7 +1986,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
 
   // float32: the logits lie behind the chunk's dz
   const size_t z_at = dtype == UMAS_F32 ? chunk_bytes(mc, d, V, dtype) : 0;
-  double* const z_kept = dtype == UMAS_F32 && f32_logit_bytes(n_sel, V) > 0 && z_at + f32_logit_bytes(n_sel, V) <= room
+  double* const z_kept = dtype == UMAS_F32 && f32_logit_bytes(n_sel, d, V) > 0 && z_at + f32_logit_bytes(n_sel, d, V) <= room
                              ? reinterpret_cast<double*>(w.chunk + z_at) : nullptr;
   if (mc_z > 0) {
     // chunk by chunk, further down

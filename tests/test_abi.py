@@ -62,6 +62,16 @@ def test_room_for_kept_logits_is_asked_for_with_a_bonus_only(lib, n, d, V):
     assert sizes[0] == sizes[1] >= 500 * 3000 * (4 + 8)                       # float32 keeps its logits with any coefficient
 
 
+# float32: below 64 columns only logits that stay in the memory-side cache together with dz (12 bytes each, 256 MiB) are kept
+@pytest.mark.parametrize("n,d,V,kept", [(20000, 8, 1000, True), (22369, 63, 1000, True), (22370, 63, 1000, False), (22370, 64, 1000, True), (12000, 32, 8000, False),
+                                        (12000, 64, 8000, True), (134217, 64, 1000, True), (134218, 64, 1000, False)])
+def test_room_for_float32_logits(lib, n, d, V, kept):
+    sizes = [getattr(lib, "umas_ppo_loss_workspace_bytes" + which)(n, d, V, 0, 0) for which in ("_min", "")]
+    rows = n if n <= 4096 else -(-n // -(-n // 4096))                          # of a chunk
+    room = sizes[1] - sizes[0] - 4 * V * (rows - min(n, 256))
+    assert abs(room - (8 * n * V if kept else 0)) <= 4 * V * 256 + 512
+
+
 # heads too narrow for kept logits, and selections of fewer than 256 blocks of dH whose logits are more than 6 GiB
 @pytest.mark.parametrize("n,d,V", [(3000, 512, 50001), (700, 264, 3001), (12000, 1024, 151937), (16000, 1024, 151937), (17000, 768, 110001), (203, 768, 2097153)])
 def test_no_room_is_asked_for_where_no_logits_are_kept(lib, n, d, V):
