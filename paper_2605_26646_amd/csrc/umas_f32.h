@@ -141,8 +141,10 @@ __device__ __forceinline__ void write_scores(const Stat& a, int64_t n, int64_t r
 
 // A workgroup takes 32 rows and every gridDim.y-th block of 128 vocabulary entries, 32 to a wavefront; a lane holds 8
 // entries of each of two rows.  With one workgroup per row block the scores are final, else the statistics go to
-// part[gridDim.y][n_sel].
+// part[gridDim.y][n_sel].  KEEP_Z: the logits go to out.z (asked at run time, 3 % slower also where they do not: 12 000 rows of 32 against 8000
+// 368 and 378 us).
 constexpr int kWaves = 4, kVocBlock = kWaves * kTile;
+template <bool KEEP_Z>
 __global__ void __launch_bounds__(kWaves* kWave)
 k_score_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel, int64_t n_sel,
             const int32_t* __restrict__ ids, Stat* __restrict__ part, ScoreOut out) {
@@ -187,7 +189,7 @@ k_score_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int
           const int v = v0 + blk_row(i, r);
           if (v >= V) continue;
           const double z = acc[i][j][r], e = exp(z - m);
-          if (out.z && n0 + blk_index(j) < n_sel) out.z[(n0 + blk_index(j)) * V + v] = z;
+          if (KEEP_Z && n0 + blk_index(j) < n_sel) out.z[(n0 + blk_index(j)) * V + v] = z;
           q.s += e;
           q.t = fma(e, z, q.t);
           if (v == y[j]) q.zy = z; else q.rest += e;
@@ -214,6 +216,7 @@ k_score_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int
   write_scores(a, n, row, ids[row], V, out);
 }
 // One workgroup per row, every thread walks the vocabulary entries tid, tid + 256, ...: one launch and no room needed.
+template <bool KEEP_Z>
 __global__ void __launch_bounds__(256)
 k_score_f32_row(const float* __restrict__ W, const float* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel,
                 const int32_t* __restrict__ ids, ScoreOut out) {
@@ -228,7 +231,7 @@ k_score_f32_row(const float* __restrict__ W, const float* __restrict__ H, int d,
     const float* w = W + static_cast<int64_t>(v) * d;
     double z = 0.0;
     for (int k = 0; k < d; ++k) z = fma(static_cast<double>(s_h[k]), static_cast<double>(w[k]), z);
-    if (out.z) out.z[n * V + v] = z;
+    if (KEEP_Z) out.z[n * V + v] = z;
     a = merge(a, Stat{z, 1.0, z, v == y ? 0.0 : 1.0, v == y ? z : 0.0});
   }
 #pragma unroll
@@ -260,10 +263,12 @@ k_score_f32_merge(const Stat* __restrict__ part, int splits, int V, const int32_
 // forward pass.  The taken token's entry g (1 - p_y): for a confident token (p_y > 1/2) 1 - p_y cancels down to the error
 // of p_y, and the sum of the other probabilities, which carries only their relative error, is taken in its place.
 // Rows on the A side, so that sixteen lanes store consecutive vocabulary entries.
-__device__ __forceinline__ float dz_entry(double z, double l, double g, double en, double k_ent, bool taken, const double* rest) {
+// v and y as numbers: with v == y handed over the compiler turns the branches round, and k_dz_f32 is 2 % slower.
+template <class Rest>
+__device__ __forceinline__ float dz_entry(double z, double l, double g, double en, double k_ent, int v, int y, Rest rest) {
   const double p = exp(z - l);
   const double e = k_ent != 0.0 ? k_ent * p * ((z - l) + en) : 0.0;     // entropy bonus: k p (log p + entropy)
-  const double dense = taken ? g * (p > 0.5 ? *rest : 1.0 - p) : -g * p;
+  const double dense = v == y ? g * (p > 0.5 ? rest() : 1.0 - p) : -g * p;
   return static_cast<float>(dense + e);
 }
 __global__ void __launch_bounds__(kWaves* kWave)
@@ -298,7 +303,7 @@ k_dz_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int V,
       for (int j = 0; j < 2; ++j) {
         const int v = v0 + blk_index(j);
         if (v >= V) continue;
-        dz[m * V + v] = dz_entry(acc[i][j][r], l, g, en, k_ent, v == y, rest_c + n);
+        dz[m * V + v] = dz_entry(acc[i][j][r], l, g, en, k_ent, v, y, [&] { return rest_c[n]; });
       }
     }
 }
@@ -315,7 +320,7 @@ k_dz_kept_f32(const double* __restrict__ z, int V, const int32_t* __restrict__ r
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const int v = blockIdx.x * 1024 + k * 256 + threadIdx.x;
-    if (v < V) dz[m * V + v] = dz_entry(z[n * V + v], l, g, en, k_ent, v == y, rest_c + n);
+    if (v < V) dz[m * V + v] = dz_entry(z[n * V + v], l, g, en, k_ent, v, y, [&] { return rest_c[n]; });
   }
 }
 
@@ -431,12 +436,18 @@ inline umas_status score(const float* W, const float* H, int d, int V, const int
   const int64_t rounds = (n_sel + 255) / 256;
   const bool tight = splits < 6 && rounds < 6 && splits * rounds <= 6 && splits < score_splits(n_sel, V, SIZE_MAX);
   if ((n_sel <= 1024 && per_thread <= 128) || (n_sel <= 128 && per_thread <= 256) || tight) {
-    hipLaunchKernelGGL(k_score_f32_row, dim3(static_cast<unsigned>(n_sel)), dim3(256), d * sizeof(float), st, W, H, d, V, rowsel, ids, out);
+    auto row = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(n_sel)), dim3(256), d * sizeof(float), st, W, H, d, V, rowsel, ids, out); };
+    if (out.z) row(k_score_f32_row<true>);
+    else row(k_score_f32_row<false>);
     UMAS_LAUNCHED("k_score_f32_row");
     return UMAS_OK;
   }
-  hipLaunchKernelGGL(k_score_f32, dim3(cdiv(n_sel, kTile), splits), dim3(kWaves * kWave), 0, st, W, H, d, V, rowsel, n_sel, ids,
-                     static_cast<Stat*>(room), out);
+  auto tiles = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(cdiv(n_sel, kTile), splits), dim3(kWaves * kWave), 0, st, W, H, d, V, rowsel, n_sel, ids,
+                       static_cast<Stat*>(room), out);
+  };
+  if (out.z) tiles(k_score_f32<true>);
+  else tiles(k_score_f32<false>);
   UMAS_LAUNCHED("k_score_f32");
   if (splits > 1) {
     hipLaunchKernelGGL(k_score_f32_merge, dim3(cdiv(n_sel, 256 / kWave)), dim3(256), 0, st, static_cast<const Stat*>(room), splits, V,
