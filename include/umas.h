@@ -274,8 +274,8 @@ size_t umas_ppo_loss_workspace_bytes_entropy(int64_t n_sel, int32_t d, int32_t V
  * rows * V bytes) where d >= 768 and the workspace has room for them, and is written by a second pass over the logits
  * elsewhere.  Only umas_policy_logprobs keeps everything of that shape on chip.  The workspace bounds it: the call works in
  * chunks of as many rows as the workspace holds (256 at the least), at the price of one more pass over W per chunk.  The float32 path stores float32 dz per chunk and,
- * where the workspace has room for them, the float64 logits of all rows (up to 1 GiB, with d < 64 up to 170 MiB; else they are
- * computed twice). */
+ * where the workspace has room for them, the float64 logits of all rows (up to 1 GiB, with d < 64 up to 128 MiB, with d < 32
+ * up to 32 MiB; else they are computed twice). */
 umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_dtype dtype, int64_t n_rows,
                                   int32_t d, int32_t V, const int32_t* ids, const int32_t* rowsel,
                                   int64_t n_sel, const float* logp_old, const float* adv,

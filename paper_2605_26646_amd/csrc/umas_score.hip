@@ -1535,16 +1535,16 @@ size_t chunk_bytes(int64_t mc, int d, int V, umas_dtype dt) {
 size_t logit_chunk_bytes(int64_t mc, int d, int V) {
   return chunk_bytes(mc, d, V, UMAS_BF16) + static_cast<size_t>(round_up(mc, 256)) * round_up(V, 256) * 2;
 }
-// The float32 update keeps the logits (float64) of all its rows where that is no more than 1 GiB; below 64 columns, whose second product
-// costs less than storing and reading them, only where they and dz stay in the memory-side cache.  Update, computed twice / kept: 20 000 rows
-// against 1000 (229 MiB of the two) d = 8 619 / 584, 32 720 / 669 us; 10 000 against 3200 (366) d = 16 553 / 585, 32 629 / 639, 48 674 / 668, 64
-// 718 / 693; 12 000 against 8000 d = 16 1121 / 1277, 32 1310 / 1404, 48 1517 / 1543, 64 1694 / 1639; 40 000 against 1000 d = 32
-// 1384 / 1434, 64 1499 / 1513, 96 1727 / 1703.
-constexpr int kF32LogitWidth = 64;
+// The float32 update keeps the logits (float64) of all its rows where that is no more than 1 GiB.  Storing and reading them costs the same
+// at every hidden size, a second product costs by it: below 64 columns up to 128 MiB, which the memory-side cache holds together with
+// dz, below 32 up to 32 MiB.  Update on new rows, computed twice / kept: 500 rows of 8 against 8000 (30 MiB) 179 / 180 us, 2000 (122) 278 /
+// 298, 4000 of 16 against 4000 262 / 279, 1843 of 33 against 8001 359 / 346, 1000 of 40 against 16 000 446 / 458 (on the rows of the call
+// before 448 / 427), 2500 of 32 against 8000 (153) 353 / 363, 300 of 64 against 40 000 790 / 789; on the rows of the call before, 12 000
+// against 8000, d = 16 1121 / 1277, 32 1310 / 1404, 48 1517 / 1543, 64 1694 / 1639, 40 000 against 1000 d = 32 1384 / 1434, 64
+// 1499 / 1513, 96 1727 / 1703.
 size_t f32_logit_bytes(int64_t n_sel, int d, int V) {
-  const double n = static_cast<double>(n_sel) * V, b = n * sizeof(double);
-  if (d < kF32LogitWidth && n * (sizeof(double) + sizeof(float)) > 268435456.0) return 0;
-  return b <= 1073741824.0 ? align_up(static_cast<size_t>(n_sel) * V * sizeof(double)) : 0;
+  const double b = static_cast<double>(n_sel) * V * sizeof(double), most = d < 32 ? 33554432.0 : d < 64 ? 134217728.0 : 1073741824.0;
+  return b <= most ? align_up(static_cast<size_t>(n_sel) * V * sizeof(double)) : 0;
 }
 // How the dH product of a chunk is cut along the vocabulary.  dH has tiles_r x tiles_d tiles of the whole vocabulary's K
 // each; with few row tiles that is fewer long tiles than compute units, and the launch lasts as long as one of them (3.6 ms

@@ -62,9 +62,9 @@ def test_room_for_kept_logits_is_asked_for_with_a_bonus_only(lib, n, d, V):
     assert sizes[0] == sizes[1] >= 500 * 3000 * (4 + 8)                       # float32 keeps its logits with any coefficient
 
 
-# float32: below 64 columns only logits that stay in the memory-side cache together with dz (12 bytes each, 256 MiB) are kept
-@pytest.mark.parametrize("n,d,V,kept", [(20000, 8, 1000, True), (22369, 63, 1000, True), (22370, 63, 1000, False), (22370, 64, 1000, True), (12000, 32, 8000, False),
-                                        (12000, 64, 8000, True), (134217, 64, 1000, True), (134218, 64, 1000, False)])
+# float32: the logits that are kept, 8 bytes each: up to 1 GiB, below 64 columns 128 MiB, below 32 columns 32 MiB
+@pytest.mark.parametrize("n,d,V,kept", [(4194, 31, 1000, True), (4195, 31, 1000, False), (16777, 32, 1000, True), (16778, 32, 1000, False), (16778, 63, 1000, False), (16778, 64, 1000, True),
+                                        (12000, 32, 8000, False), (12000, 64, 8000, True), (134217, 64, 1000, True), (134218, 64, 1000, False)])
 def test_room_for_float32_logits(lib, n, d, V, kept):
     sizes = [getattr(lib, "umas_ppo_loss_workspace_bytes" + which)(n, d, V, 0, 0) for which in ("_min", "")]
     rows = n if n <= 4096 else -(-n // -(-n // 4096))                          # of a chunk
