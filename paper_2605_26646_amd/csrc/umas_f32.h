@@ -458,10 +458,11 @@ inline umas_status score(const float* W, const float* H, int d, int V, const int
 }
 // <2, 2> where its tiles fill whole rounds of 256 compute units, or nearly: it takes as long as the rounds, <1, 1> a tenth longer than
 // the tiles would in full ones (dW of 4000 x 300, 315 tiles: 257 us in <2, 2>, 184 in <1, 1>; 5001 x 451, 632: 221 and 202; 8192
-// x 512, 1024: 164 and 179).
+// x 512, 1024: 164 and 179).  Nearly one round is no case for them: a single workgroup to a compute unit (dW of 15 000 x 64, 235 tiles, 2000 rows
+// 166 in <2, 2>, 125 in <1, 1>, 4000 rows 338 and 235; 8000 x 120, 250: 153 and 124; 7600 x 128, 238: 87 and 70).
 inline bool large_product(int64_t m, int64_t n) {
   const int64_t tiles = cdiv(m, 2 * kTile) * static_cast<int64_t>(cdiv(n, 2 * kTile));
-  return (tiles + 255) / 256 * 256 * 10 <= tiles * 11;
+  return tiles >= 256 && (tiles + 255) / 256 * 256 * 10 <= tiles * 11;
 }
 
 }  // namespace f32
