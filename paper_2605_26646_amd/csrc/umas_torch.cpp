@@ -185,13 +185,14 @@ PyObject* pack(std::initializer_list<PyObject*> items) {  // takes the reference
   for (PyObject* o : items) PyTuple_SET_ITEM(r, i++, o);
   return r;
 }
+struct Unlocked {                                         // the interpreter lock is taken again also when the call throws
+  PyThreadState* const state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
 template <class Call>
 umas_status unlocked(Call call) {                         // the library needs no Python
-  umas_status s;
-  Py_BEGIN_ALLOW_THREADS
-  s = call();
-  Py_END_ALLOW_THREADS
-  return s;
+  const Unlocked without_lock;
+  return call();
 }
 #define UMAS_CALL(...)                                                        \
   do {                                                                        \

@@ -1,6 +1,8 @@
 """The native half of the binding reads its arguments on the host; every call here is refused by the library's own checks before
 any launch (no GPU)."""
 import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -92,3 +94,25 @@ def test_offsets_without_a_dimension(native):
         for name in ("traj_turn_off", "turn_tok_off"):
             with pytest.raises(TypeError):
                 assign(native, **{name: zero})
+
+
+def test_a_call_without_host_memory_raises():
+    """The check of a trajectory order needs a byte each; without them the call raises instead of ending the process."""
+    child = """
+import resource
+import numpy as np, torch
+import paper_2605_26646_amd as umas
+from paper_2605_26646_amd import binding
+native, n = binding._native(), 100_000_000
+s = umas.Streams(0, 0, 1, *[torch.zeros(1, dtype=torch.int64)] * 16)
+off, order = np.zeros(n + 1, np.int32), np.zeros(n, np.int32)
+native.ready_batch(s, off[:2], 0, 1, None, order[:1], 0)                 # refused: the workspace's address
+size = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (size + umas.load_library().umas_ready_batch_workspace_bytes(n, 1) + (64 << 20), -1))
+try:
+    native.ready_batch(s, off, 0, 1, None, order, 0)
+except RuntimeError as e:
+    print("raised", e)
+"""
+    done = subprocess.run([sys.executable, "-c", child], cwd=os.path.dirname(os.path.dirname(umas.lib_path())), capture_output=True, text=True)
+    assert done.returncode == 0 and "raised std::bad_alloc" in done.stdout, (done.returncode, done.stdout, done.stderr[-500:])
