@@ -10,7 +10,9 @@
 // product and the row's g, writes dH and adds g h to its dw accumulators; the next row is already in
 // flight.  dH leaves past the caches: nothing here reads it, and the rows of H that the value pass has just read stay in the
 // memory-side cache (values and update, 39 224 rows of 2048 125 -> 119 us on new rows, 112 -> 99 on the rows of the pass
-// before; 60 000 float32 rows of 1024 177 -> 153).  A workgroup's partial sums meet in LDS, the workgroups' in one small kernel,
+// before; 60 000 float32 rows of 1024 177 -> 153).  Who reads dH next does not pay for it: with a kernel behind them that multiplies dH by H,
+// 1000 rows of 2048 30.4 and 30.4 us, 6000 49 and 48, 39 224 221 and 204, 100 000 543 and 522; with a product of dH by 512 columns
+// 47 and 47, 61.5 and 62, 219 and 209, 505 and 497.  A workgroup's partial sums meet in LDS, the workgroups' in one small kernel,
 // both in a fixed order, so results do not depend on scheduling.
 #include <type_traits>
 

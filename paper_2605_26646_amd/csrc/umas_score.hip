@@ -15,7 +15,7 @@
 // the taken token's logit, and the row factor -g exp(z_y - lse) is applied where dH is written and folded
 // into the copy of H that dW reads; the logits are computed once.  With an entropy bonus the
 // scoring pass leaves the float32 logits behind, which one pass over them turns into dz; in a workspace without room
-// for them (and for blocks of rows whose logits spread too far for E) dz is recomputed tile by tile from H, W and lse.
+// for them, for narrow heads (and for blocks of rows whose logits spread too far for E) dz is recomputed tile by tile from H, W and lse.
 // The float32 path, for small shapes, carries its sums in float64 (umas_f32.h).
 #include <math.h>
 
@@ -887,7 +887,7 @@ k_keep_rows(const uint16_t* __restrict__ H, int d, int V, const int32_t* __restr
 }
 
 // ------------------------------------------------------------------ bf16: dz tiles into the chunk buffer
-// For blocks of rows whose numerators do not serve, and with an entropy bonus in a small workspace (16 100 rows of 2048 in 2 GB,
+// For blocks of rows whose numerators do not serve, and with an entropy bonus for narrow heads and in a small workspace (16 100 rows of 2048 in 2 GB,
 // chunks of 3300: 31.3 ms; chunks of logits of half that many rows would add to dW twice as often).  Same tile product as k_score_tiles; the epilogue forms the dense part of dz = g (onehot - softmax),
 // -g exp(z - lse), plus the entropy bonus's term when its coefficient is not 0, and writes it as bf16 to
 // dZ [mcp, Vp].  Rows past the chunk and vocabulary ids past V get 0.  The one-hot part g at v = y is a single term per row and is added in
@@ -1588,7 +1588,10 @@ size_t full_part_bytes(int64_t n_sel, int64_t chunk_rows, int d, int V) {
 // 512 288 / 282, 578 / 613, 1985 / 2067; 640 355 / 336, 714 / 738, 2414 / 2459; 768 383 / 356, 765 / 763, 2610 / 2579; 896 452 / 386,
 // 924 / 880, 3166 / 3011.
 constexpr int kLogitWidth = 768;
-constexpr size_t kLogitBytes = size_t{6} << 30;            // what the workspace is sized for (a second chunk adds to dW: 0.5 ms)
+// What the workspace is sized for.  A second chunk adds to dW, 0.3 to 0.5 ms at any size: in one and two chunks 8300 rows of 2048 14.15 and 14.43 ms,
+// 10 590 (6 GiB) 17.77 and 18.16, 16 100 26.4 and 26.9, 24 000 39.4 and 39.7, 10 500 of 3584 28.9 and 29.3.  Beyond 6 GiB it is 2 % or less, which
+// is not worth twice the memory.
+constexpr size_t kLogitBytes = size_t{6} << 30;
 int64_t logit_chunk_rows(int64_t n_sel, int d, int V, size_t room) {
   if (d < kLogitWidth) return 0;
   if (round_up(V, 256) / 256 > 8192) return 0;             // 32-bit offsets along a row of blocks
