@@ -19,14 +19,21 @@ void prof_mark(hipStream_t st);                     // opens an interval at the 
 void prof_kernel(const char* name, hipStream_t st); // closes the interval of the kernel just launched
 
 // Staging of thin host arrays.  The calls that take host arrays copy them into a block of pinned host memory that
-// the library keeps (a ring of kSlots blocks, each grown to the largest request it has seen) and enqueue ONE
-// asynchronous copy of the block to the device: the caller's arrays have been read when the call returns, and the
+// the library keeps (a ring of kSlots blocks, each grown to the largest request it has seen) and launch ONE kernel that
+// reads the block over the bus: the caller's arrays have been read when the call returns, and the
 // host never waits for the stream.  A block is reused kSlots calls later; only then does the host wait, and only
-// until the copy that was issued from that block has run.
+// until the kernel that was launched on that block has read it, which it says in words behind the block (Reader).
 class ThinStage {
  public:
   static constexpr int kSlots = 4;
-  // Takes the next block of the ring with room for `bytes`; 256-byte aligned.  Holds the ring's lock until flush().
+  // What a kernel that reads the block needs: the block, and a word for every workgroup that it sets to 1 when it has read what it
+  // wants (read_done; NULL under capture, where an event stands for the words).
+  struct Reader {
+    const char* block;
+    uint32_t* done;
+  };
+  // Takes the next block of the ring with room for `bytes`; 256-byte aligned.  Holds the ring's lock until the block is handed
+  // to a kernel (flush, or direct and launched).
   umas_status begin(size_t bytes);
   // Copies n bytes to offset `off` of the block (nothing for src == nullptr or n == 0).
   void put(size_t off, const void* src, size_t n);
@@ -37,8 +44,12 @@ class ThinStage {
   void abandon();
 
  private:
+  umas_status reader(unsigned n_wg, hipStream_t st, Reader* r);
+  umas_status launched(hipStream_t st, hipError_t e);
   char* cur_ = nullptr;
   int slot_ = -1;
+  size_t bytes_ = 0;
+  unsigned n_wg_ = 0;
 };
 
 #define UMAS_HIP(expr)                                                                 \
@@ -98,6 +109,13 @@ __device__ __forceinline__ void store_stream(void* p, const V& v) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   static_assert(sizeof(V) == 16, "16 bytes");
   __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), static_cast<u32x4*>(p));
+}
+
+// At the end of a kernel that reads a staging block: everything this workgroup reads of it has arrived.  Every thread calls it.
+__device__ __forceinline__ void stage_read_done(const ThinStage::Reader& r) {
+  __builtin_amdgcn_s_waitcnt(0);   // this wavefront's loads are back
+  __syncthreads();
+  if (threadIdx.x == 0 && r.done) __hip_atomic_store(r.done + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 template <typename T>
