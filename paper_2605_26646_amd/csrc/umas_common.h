@@ -33,19 +33,21 @@ class ThinStage {
     uint32_t* done;
   };
   // Takes the next block of the ring with room for `bytes`; 256-byte aligned.  Holds the ring's lock until the block is handed
-  // to a kernel (flush, or direct and launched).
+  // to a kernel (flush, or lend and launched).
   umas_status begin(size_t bytes);
   // Copies n bytes to offset `off` of the block (nothing for src == nullptr or n == 0).
   void put(size_t off, const void* src, size_t n);
   void zero(size_t off, size_t n);
   // Enqueues the copy of the first `bytes` bytes of the block to `dst` on `st` and releases the ring.
   umas_status flush(void* dst, size_t bytes, hipStream_t st);
+  // In place of flush: the block for a kernel of n_wg workgroups that reads it itself and is launched next on `st`, then, with what the
+  // launch said, the release of the ring.
+  umas_status lend(unsigned n_wg, hipStream_t st, Reader* r);
+  umas_status launched(hipStream_t st, hipError_t e);
   // Releases the ring without copying (an error between begin and flush).
   void abandon();
 
  private:
-  umas_status reader(unsigned n_wg, hipStream_t st, Reader* r);
-  umas_status launched(hipStream_t st, hipError_t e);
   char* cur_ = nullptr;
   int slot_ = -1;
   size_t bytes_ = 0;

@@ -140,7 +140,7 @@ void ThinStage::zero(size_t off, size_t n) {
 }
 
 // The block for a kernel of n_wg workgroups that is launched next on `st`.
-umas_status ThinStage::reader(unsigned n_wg, hipStream_t st, Reader* r) {
+umas_status ThinStage::lend(unsigned n_wg, hipStream_t st, Reader* r) {
   StageSlot& s = g_slots[slot_];
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   hipError_t e = hipStreamIsCapturing(st, &capture);
@@ -170,7 +170,7 @@ umas_status ThinStage::launched(hipStream_t st, hipError_t e) {
   slot_ = -1;
   cur_ = nullptr;
   g_stage_mutex.unlock();
-  if (e != hipSuccess) return fail(UMAS_EHIP, "staging copy failed: %s", hipGetErrorString(e));
+  if (e != hipSuccess) return fail(UMAS_EHIP, "staging failed: %s", hipGetErrorString(e));
   return UMAS_OK;
 }
 
@@ -203,7 +203,7 @@ umas_status ThinStage::flush(void* dst, size_t bytes, hipStream_t st) {
   const int64_t n16 = static_cast<int64_t>(bytes / 16);                // whole arrays of the carver: a multiple of 256
   const unsigned n_wg = cdiv(static_cast<size_t>(n16), 256 * kStageWords);
   Reader r;
-  const umas_status s = reader(n_wg, st, &r);
+  const umas_status s = lend(n_wg, st, &r);
   if (s != UMAS_OK) return s;
   hipLaunchKernelGGL(k_stage_copy, dim3(n_wg), dim3(256), 0, st, r, static_cast<uint4*>(dst), n16);
   return launched(st, hipGetLastError());

@@ -8,7 +8,8 @@
 // and the alignment of each turn's reward with its token sequence (paragraph "Batch
 // construction").
 //
-// Three kernels (four with normalisation groups).  k_turn_plan does everything that is per turn: one thread walks
+// Small graphs take one launch (k_route_small).  The others take a copy of the thin arrays and three kernels (four with
+// normalisation groups).  k_turn_plan does everything that is per turn: one thread walks
 // one trajectory's turns (a trajectory's turns are consecutive, and everything a turn needs from its neighbours -
 // whether it opens or closes the trajectory's run inside its model's stream, how many steps lie between it and the
 // run's next turn - lies inside its trajectory), blocks of 256 trajectories publish their per-model totals and read
@@ -97,14 +98,10 @@ size_t carve(Carver& c, RouteWs& w, int n_roles, int n_traj, int n_turns, int64_
 
 // ------------------------------------------------------------------ kernels
 
-// z-score of trajectory rewards inside a group; one wavefront per group, float64 statistics.
-__global__ void k_group_norm(const float* __restrict__ R, const int32_t* __restrict__ group_off,
-                             const int32_t* __restrict__ members, int n_groups, float eps,
-                             float* __restrict__ out) {
+// z-score of the trajectory rewards of one group, by one wavefront, float64 statistics.
+__device__ __forceinline__ void normalise_group(const float* __restrict__ R, const int32_t* __restrict__ members, int a, int e, float eps,
+                                                float* __restrict__ out) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int g = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-  if (g >= n_groups) return;
-  const int a = group_off[g], e = group_off[g + 1];
   if (e == a) return;
   double s = 0.0;
   for (int i = a + lane; i < e; i += kWave) s += static_cast<double>(R[members[i]]);
@@ -119,6 +116,12 @@ __global__ void k_group_norm(const float* __restrict__ R, const int32_t* __restr
     const int b = members[i];
     out[b] = static_cast<float>((static_cast<double>(R[b]) - mu) / (sigma + static_cast<double>(eps)));
   }
+}
+__global__ void k_group_norm(const float* __restrict__ R, const int32_t* __restrict__ group_off,
+                             const int32_t* __restrict__ members, int n_groups, float eps,
+                             float* __restrict__ out) {
+  const int g = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
+  if (g < n_groups) normalise_group(R, members, group_off[g], group_off[g + 1], eps, out);
 }
 
 // ------------------------------------------------------------------ the plan: everything per turn
@@ -171,8 +174,8 @@ struct TrajCounts {
   int64_t cnt[KM], tok[KM];
   uint32_t seen;
 };
-template <int KM>
-__device__ __forceinline__ void traj_counts(const PlanArgs& A, const uint8_t* s_phi, int b, TrajCounts<KM>& c) {
+template <int KM, class Phi>
+__device__ __forceinline__ void traj_counts(const PlanArgs& A, Phi phi, int b, TrajCounts<KM>& c) {
 #pragma unroll
   for (int k = 0; k < KM; ++k) { c.cnt[k] = 0; c.tok[k] = 0; }
   c.seen = 0;
@@ -180,7 +183,7 @@ __device__ __forceinline__ void traj_counts(const PlanArgs& A, const uint8_t* s_
   const int t0 = A.traj_turn_off[b], t1 = A.traj_turn_off[b + 1];
   int64_t g0 = A.turn_tok_off[t0];
   for (int u = t0; u < t1; ++u) {
-    const int m = s_phi[A.turn_role[u]];
+    const int m = phi[A.turn_role[u]];
     const int64_t g1 = A.turn_tok_off[u + 1];
     bump(c.cnt, m, int64_t{1});
     bump(c.tok, m, g1 - g0);
@@ -188,6 +191,89 @@ __device__ __forceinline__ void traj_counts(const PlanArgs& A, const uint8_t* s_
     g0 = g1;
   }
 }
+
+// One walk over the turns of trajectory b, whose first turn, token and run in every stream go to slot_at, tok_at and run_at: slots,
+// offsets, runs, composed rewards and the record of every segment, which go to `sink`.  What a segment's last token says about its
+// end - bit 1: last token of its turn; bit 2: also the last token of the trajectory's run (no later turn of the trajectory with
+// tokens in this stream); bits 3-7: else the number of steps to the run's next turn with tokens (31 = more than 30: look it
+// up) - is known only when that next turn comes by: the record is written as a run's end and its flags are written again then.
+template <int KM, class Phi, class Sink>
+__device__ __forceinline__ void walk_turns(const PlanArgs& A, Phi phi, int b, int64_t (&slot_at)[KM], int64_t (&tok_at)[KM],
+                                           const int64_t (&run_at)[KM], Sink sink) {
+  const int t0 = A.traj_turn_off[b], t1 = A.traj_turn_off[b + 1];
+  const float rj = A.traj_reward ? A.traj_reward[b] : 0.0f;
+  uint32_t seen = 0;
+  int last_slot[KM], last_step[KM];   // the model's latest turn with tokens in this trajectory
+#pragma unroll
+  for (int k = 0; k < KM; ++k) { last_slot[k] = -1; last_step[k] = 0; }
+  int64_t g0 = A.turn_tok_off[t0];
+  for (int u = t0; u < t1; ++u) {
+    const int v = A.turn_role[u];
+    const int m = phi[v];
+    const int64_t g1 = A.turn_tok_off[u + 1], len = g1 - g0;
+    const int64_t slot = pick(slot_at, m), off = pick(tok_at, m);
+    const int step = u - t0 + 1;
+    bump(slot_at, m, int64_t{1});
+    bump(tok_at, m, len);
+    if (!((seen >> m) & 1u)) {                       // the trajectory's one run in stream m starts here
+      sink.run(pick(run_at, m), off);
+      seen |= 1u << m;
+    }
+    const float rr = A.role_reward ? A.role_reward[static_cast<size_t>(b) * A.n_roles + v] : 0.0f;
+    const float rt = A.turn_reward ? A.turn_reward[u] : 0.0f;
+    const float wr = A.w_role ? A.w_role[v] : 1.0f;
+    const float wt = A.w_turn ? A.w_turn[v] : 1.0f;
+    const float wj = A.w_traj ? A.w_traj[v] : 1.0f;
+    // (node + turn) + traj with every product and sum rounded on its own: contraction into fused
+    // multiply-adds is switched off for this expression so that the result is reproducible bit for bit
+    float rho;
+    {
+#pragma clang fp contract(off)
+      const float pr = wr * rr, pt = wt * rt, pj = wj * rj;
+      const float s1 = pr + pt;
+      rho = s1 + pj;
+    }
+    SegMeta M;
+    M.src = g0;
+    M.turn = u;
+    M.role = v;
+    M.rho = rho;
+    M.end_flags = 2 | 4;
+    M.pad = 0;
+    sink.turn(slot, off, len, step, M);
+    if (len > 0) {
+      const int prev = pick(last_slot, m);
+      if (prev >= 0) {
+        const int ds = step - pick(last_step, m);
+        sink.end_flags(prev, 2 | ((ds < 31 ? ds : 31) << 3));
+      }
+#pragma unroll
+      for (int k = 0; k < KM; ++k) {
+        last_slot[k] = m == k ? static_cast<int>(slot) : last_slot[k];
+        last_step[k] = m == k ? step : last_step[k];
+      }
+    }
+    g0 = g1;
+  }
+}
+// What the plan says of a turn, in the outputs ...
+__device__ __forceinline__ void publish_turn(const PlanArgs& A, int64_t slot, int64_t off, int step, const SegMeta& M) {
+  A.seg_turn[slot] = M.turn;
+  A.turn_seg_off[slot] = off;
+  A.turn_scalar[M.turn] = M.rho;
+  A.turn_step[M.turn] = step;
+}
+// ... and, for the token kernel, in the workspace: the records, the first segment of every token block.
+struct PlanSink {
+  const PlanArgs& A;
+  __device__ __forceinline__ void run(int64_t r, int64_t off) const { A.traj_seg_off[r] = off; }
+  __device__ __forceinline__ void turn(int64_t slot, int64_t off, int64_t len, int step, const SegMeta& M) const {
+    publish_turn(A, slot, off, step, M);
+    for (int64_t blk = (off + kTokBlock - 1) / kTokBlock; blk * kTokBlock < off + len; ++blk) A.blk_first[blk] = static_cast<int32_t>(slot);
+    A.seg_meta[slot] = M;
+  }
+  __device__ __forceinline__ void end_flags(int slot, int32_t f) const { A.seg_meta[slot].end_flags = f; }
+};
 
 // KM: the smallest of 1, 2, 4, 8 that is at least the number of models (per-model state lives in registers).
 template <int KM>
@@ -305,72 +391,7 @@ k_turn_plan(PlanArgs A) {
       }
     }
     if (b < A.n_traj) {
-      const int t0 = A.traj_turn_off[b], t1 = A.traj_turn_off[b + 1];
-      const float rj = A.traj_reward ? A.traj_reward[b] : 0.0f;
-      // One walk over the trajectory's turns: slots, offsets, runs, composed rewards, the first segment of every token
-      // block, the record of every segment.  What a segment's last token says about its end - bit 1: last token of its
-      // turn; bit 2: also the last token of the trajectory's run (no later turn of the trajectory with tokens in this
-      // stream); bits 3-7: else the number of steps to the run's next turn with tokens (31 = more than 30: look it
-      // up) - is known only when that next turn comes by: the record is written as a run's end and its flags are
-      // written again then.
-      uint32_t seen = 0;
-      int last_slot[KM], last_step[KM];   // the model's latest turn with tokens in this trajectory
-#pragma unroll
-      for (int k = 0; k < KM; ++k) { last_slot[k] = -1; last_step[k] = 0; }
-      int64_t g0 = A.turn_tok_off[t0];
-      for (int u = t0; u < t1; ++u) {
-        const int v = A.turn_role[u];
-        const int m = s_phi[v];
-        const int64_t g1 = A.turn_tok_off[u + 1], len = g1 - g0;
-        const int64_t slot = pick(slot_at, m), off = pick(tok_at, m);
-        const int step = u - t0 + 1;
-        bump(slot_at, m, int64_t{1});
-        bump(tok_at, m, len);
-        A.seg_turn[slot] = u;
-        A.turn_seg_off[slot] = off;
-        if (!((seen >> m) & 1u)) {                   // the trajectory's one run in stream m starts here
-          A.traj_seg_off[pick(run_at, m)] = off;
-          seen |= 1u << m;
-        }
-        const float rr = A.role_reward ? A.role_reward[static_cast<size_t>(b) * A.n_roles + v] : 0.0f;
-        const float rt = A.turn_reward ? A.turn_reward[u] : 0.0f;
-        const float wr = A.w_role ? A.w_role[v] : 1.0f;
-        const float wt = A.w_turn ? A.w_turn[v] : 1.0f;
-        const float wj = A.w_traj ? A.w_traj[v] : 1.0f;
-        // (node + turn) + traj with every product and sum rounded on its own: contraction into fused
-        // multiply-adds is switched off for this expression so that the result is reproducible bit for bit
-        float rho;
-        {
-#pragma clang fp contract(off)
-          const float pr = wr * rr, pt = wt * rt, pj = wj * rj;
-          const float s1 = pr + pt;
-          rho = s1 + pj;
-        }
-        A.turn_scalar[u] = rho;
-        A.turn_step[u] = step;
-        for (int64_t blk = (off + kTokBlock - 1) / kTokBlock; blk * kTokBlock < off + len; ++blk) A.blk_first[blk] = static_cast<int32_t>(slot);
-        SegMeta M;
-        M.src = g0;
-        M.turn = u;
-        M.role = v;
-        M.rho = rho;
-        M.end_flags = 2 | 4;
-        M.pad = 0;
-        A.seg_meta[slot] = M;
-        if (len > 0) {
-          const int prev = pick(last_slot, m);
-          if (prev >= 0) {
-            const int ds = step - pick(last_step, m);
-            A.seg_meta[prev].end_flags = 2 | ((ds < 31 ? ds : 31) << 3);
-          }
-#pragma unroll
-          for (int k = 0; k < KM; ++k) {
-            last_slot[k] = m == k ? static_cast<int>(slot) : last_slot[k];
-            last_step[k] = m == k ? step : last_step[k];
-          }
-        }
-        g0 = g1;
-      }
+      walk_turns(A, s_phi, b, slot_at, tok_at, run_at, PlanSink{A});
     }
     __syncthreads();                                 // s_res is the next chunk's
   }
@@ -415,11 +436,10 @@ __device__ __forceinline__ uint32_t load_mask4(const uint8_t* __restrict__ mask,
   return static_cast<uint32_t>(mask[g0]) | (static_cast<uint32_t>(mask[g0 + 1]) << 8) |
          (static_cast<uint32_t>(mask[g0 + 2]) << 16) | (static_cast<uint32_t>(mask[g0 + 3]) << 24);
 }
-// One wavefront: does segment s, which goes on past position `from`, hold a scored token at or after it?
-__device__ __forceinline__ bool scored_token_ahead(const TokArgs& A, int s, int64_t from) {
+// One wavefront: does a segment, from its `skip`-th token on, hold a scored token?  (It lies at `src` and has len tokens.)
+__device__ __forceinline__ bool scored_token_ahead(const TokArgs& A, int64_t src, int64_t len, int64_t skip) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t seg_e = A.turn_seg_off[s + 1];
-  const int64_t g = A.seg_meta[s].src + (from - A.turn_seg_off[s]), n = seg_e - from;
+  const int64_t g = src + skip, n = len - skip;
   bool found = false;
   for (int64_t i0 = 0; i0 < n && !found; i0 += 8 * kWave) {   // eight bytes per lane, all in flight together
     uint32_t any = 0;
@@ -431,6 +451,95 @@ __device__ __forceinline__ bool scored_token_ahead(const TokArgs& A, int s, int6
     found = __any(any != 0);
   }
   return found;
+}
+
+// The segments that hold a block's tokens, in LDS: offsets, the same relative to the block's first token, records, and the
+// block-relative position of the segment's last scored token in this block (-1 at first).
+struct SegWindow {
+  const int64_t* off;
+  const int32_t* loc;
+  const SegMeta* meta;
+  int32_t* lastv;
+};
+// largest j in [0, n] with loc[j] <= pl: the segment that holds the token
+__device__ __forceinline__ int segment_of(const int32_t* loc, int n, int pl) {
+  int lo = 0, hi = n;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (loc[mid] <= pl) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+// This thread's four tokens from pl0 on: their masks as 0/1 bytes, the last scored token of every segment.  m4: the mask bytes when all
+// four lie in segment lo (fast).  Every lane of the wavefront calls it.
+__device__ __forceinline__ uint32_t four_masks(const TokArgs& A, const SegWindow& W, int64_t blk0, int ntok, int pl0, int lo, bool fast, uint32_t m4) {
+  const int lane = threadIdx.x & (kWave - 1);
+  uint32_t mk4 = 0;
+  int cand = -1;                                    // this thread's last scored token of segment lo
+  if (fast) {
+    mk4 = bytes_to_01(m4);
+    cand = mk4 ? pl0 + (31 - __clz(mk4)) / 8 : -1;
+  }
+  // when the whole wavefront sits in one segment, one update of the segment's last scored token does
+  const int lo0 = __shfl(lo, 0, kWave);
+  if (__all(fast && lo == lo0)) {
+    const int best = wave_max(cand);
+    if (lane == 0 && best >= 0) atomicMax(&W.lastv[lo], best);
+  } else if (cand >= 0) {
+    atomicMax(&W.lastv[lo], cand);
+  }
+  if (pl0 < ntok && !fast) {                        // a segment boundary or the stream's end inside the four tokens
+    int s = lo;
+    for (int k = 0; k < kTokPerThread; ++k) {
+      const int pl = pl0 + k;
+      if (pl >= ntok) break;
+      while (W.loc[s + 1] <= pl) ++s;               // also steps over empty segments
+      const uint32_t m = A.mask_global[W.meta[s].src + (blk0 + pl - W.off[s])] ? 1u : 0u;
+      mk4 |= m << (8 * k);
+      if (m) atomicMax(&W.lastv[s], pl);
+    }
+  }
+  return mk4;
+}
+// The six outputs of the four tokens, once every thread has been through four_masks; pl0 < ntok.
+__device__ __forceinline__ void store_four(const TokArgs& A, const SegWindow& W, int64_t blk0, int ntok, int pl0, int lo, bool fast, uint32_t mk4,
+                                           bool ahead) {
+  const int64_t p0 = blk0 + pl0;
+  int s = lo;
+  if (fast) {                                       // four tokens of one segment: no per-token bookkeeping
+    const SegMeta M = W.meta[s];
+    const int64_t g0 = M.src + (p0 - W.off[s]);
+    uint32_t fg4 = mk4;
+    if (pl0 + kTokPerThread == W.loc[s + 1]) fg4 |= static_cast<uint32_t>(M.end_flags) << 24;
+    // the segment's last scored token carries the reward, unless the segment goes on past the block and has another
+    const int lastv = W.loc[s + 1] <= kTokBlock || !ahead ? W.lastv[s] : -1;
+    float rw[kTokPerThread];
+#pragma unroll
+    for (int k = 0; k < kTokPerThread; ++k)
+      rw[k] = ((mk4 >> (8 * k)) & 1u) && (A.place_mode == UMAS_PLACE_ALL || pl0 + k == lastv) ? M.rho : 0.f;
+    *reinterpret_cast<longlong2*>(A.perm + p0) = make_longlong2(g0, g0 + 1);
+    *reinterpret_cast<longlong2*>(A.perm + p0 + 2) = make_longlong2(g0 + 2, g0 + 3);
+    *reinterpret_cast<int4*>(A.tok_turn + p0) = make_int4(M.turn, M.turn, M.turn, M.turn);
+    *reinterpret_cast<int4*>(A.tok_role + p0) = make_int4(M.role, M.role, M.role, M.role);
+    *reinterpret_cast<uint32_t*>(A.tok_mask + p0) = mk4;
+    *reinterpret_cast<uint32_t*>(A.tok_flags + p0) = fg4;
+    *reinterpret_cast<float4*>(A.tok_reward + p0) = make_float4(rw[0], rw[1], rw[2], rw[3]);
+    return;
+  }
+  for (int k = 0; k < kTokPerThread; ++k) {
+    const int pl = pl0 + k;
+    if (pl >= ntok) break;
+    while (W.loc[s + 1] <= pl) ++s;
+    const SegMeta M = W.meta[s];
+    const uint32_t m = (mk4 >> (8 * k)) & 1u;
+    const bool seg_done = W.loc[s + 1] <= kTokBlock || !ahead;
+    A.perm[p0 + k] = M.src + (p0 + k - W.off[s]);
+    A.tok_turn[p0 + k] = M.turn;
+    A.tok_role[p0 + k] = M.role;
+    A.tok_mask[p0 + k] = static_cast<uint8_t>(m);
+    A.tok_flags[p0 + k] = static_cast<uint8_t>(m | (pl + 1 == W.loc[s + 1] ? M.end_flags : 0));
+    A.tok_reward[p0 + k] = m && (A.place_mode == UMAS_PLACE_ALL || (seg_done && pl == W.lastv[s])) ? M.rho : 0.f;
+  }
 }
 
 // The plain path of a block with more than kSegWin segments: one token at a time, the segment found by a search in
@@ -492,6 +601,7 @@ k_tokens(TokArgs A) {
   const int n_seg = s_last - s_first + 1;
   const bool windowed = n_seg <= kSegWin;
   const bool mask_aligned = (reinterpret_cast<uintptr_t>(A.mask_global) & 3) == 0;
+  const SegWindow win{s_off, s_loc, s_meta, s_lastv};
   if (tid == 0) s_ahead = 0;
   *reinterpret_cast<uint4*>(s_mk + tid * kCompact) = make_uint4(0u, 0u, 0u, 0u);
   if (windowed) {
@@ -517,11 +627,7 @@ k_tokens(TokArgs A) {
       const int pl0 = rd * kTokRound + tid * kTokPerThread;
       m4_r[rd] = 0;
       if (pl0 >= ntok) continue;
-      int lo = 0, hi = n_seg;                       // largest j with s_loc[j] <= pl0: the segment that holds the token
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (s_loc[mid] <= pl0) lo = mid; else hi = mid - 1;
-      }
+      const int lo = segment_of(s_loc, n_seg, pl0);
       const bool fast = pl0 + kTokPerThread <= s_loc[lo + 1];
       lo_r[rd] = lo | (fast ? 1 << 30 : 0);
       if (fast) m4_r[rd] = load_mask4(A.mask_global, s_meta[lo].src + (blk0 + pl0 - s_off[lo]), mask_aligned);
@@ -529,41 +635,15 @@ k_tokens(TokArgs A) {
 #pragma unroll
     for (int rd = 0; rd < kTokRounds; ++rd) {
       const int pl0 = rd * kTokRound + tid * kTokPerThread;
-      const bool in = pl0 < ntok, fast = (lo_r[rd] >> 30) != 0;
-      const int lo = lo_r[rd] & ((1 << 30) - 1);
-      uint32_t mk4 = 0;
-      int cand = -1;                                // this thread's last scored token of segment lo
-      if (fast) {
-        mk4 = bytes_to_01(m4_r[rd]);
-        cand = mk4 ? pl0 + (31 - __clz(mk4)) / 8 : -1;
-      }
-      // when the whole wavefront sits in one segment, one update of the segment's last scored token does
-      const int lo0 = __shfl(lo, 0, kWave);
-      if (__all(fast && lo == lo0)) {
-        const int best = wave_max(cand);
-        if (lane == 0 && best >= 0) atomicMax(&s_lastv[lo], best);
-      } else if (cand >= 0) {
-        atomicMax(&s_lastv[lo], cand);
-      }
-      if (in && !fast) {                            // a segment boundary or the stream's end inside the four tokens
-        int s = lo;
-        for (int k = 0; k < kTokPerThread; ++k) {
-          const int pl = pl0 + k;
-          if (pl >= ntok) break;
-          while (s_loc[s + 1] <= pl) ++s;           // also steps over empty segments
-          const uint32_t m = A.mask_global[s_meta[s].src + (blk0 + pl - s_off[s])] ? 1u : 0u;
-          mk4 |= m << (8 * k);
-          if (m) atomicMax(&s_lastv[s], pl);
-        }
-      }
-      mk_r[rd] = mk4;
+      mk_r[rd] = four_masks(A, win, blk0, ntok, pl0, lo_r[rd] & ((1 << 30) - 1), (lo_r[rd] >> 30) != 0, m4_r[rd]);
     }
   } else {
     many_segments_masks(A, blk0, ntok, s_first, s_last, s_mk);
   }
   // the block's last segment, if it goes on past the block: is there a scored token further on?
   if (wave == 1 && A.place_mode == UMAS_PLACE_LAST && A.turn_seg_off[s_last + 1] > blk_end) {
-    const bool found = scored_token_ahead(A, s_last, blk_end);
+    const int64_t a = A.turn_seg_off[s_last];
+    const bool found = scored_token_ahead(A, A.seg_meta[s_last].src, A.turn_seg_off[s_last + 1] - a, blk_end - a);
     if (lane == 0) s_ahead = found ? 1 : 0;
   }
   __syncthreads();
@@ -592,44 +672,7 @@ k_tokens(TokArgs A) {
 #pragma unroll
     for (int rd = 0; rd < kTokRounds; ++rd) {
       const int pl0 = rd * kTokRound + tid * kTokPerThread;
-      const int64_t p0 = blk0 + pl0;
-      if (pl0 >= ntok) continue;
-      int s = lo_r[rd] & ((1 << 30) - 1);
-      const uint32_t mk4 = mk_r[rd];
-      if ((lo_r[rd] >> 30) != 0) {                  // four tokens of one segment: no per-token bookkeeping
-        const SegMeta M = s_meta[s];
-        const int64_t g0 = M.src + (p0 - s_off[s]);
-        uint32_t fg4 = mk4;
-        if (pl0 + kTokPerThread == s_loc[s + 1]) fg4 |= static_cast<uint32_t>(M.end_flags) << 24;
-        // the segment's last scored token carries the reward, unless the segment goes on past the block and has another
-        const int lastv = s_loc[s + 1] <= kTokBlock || !ahead ? s_lastv[s] : -1;
-        float rw[kTokPerThread];
-#pragma unroll
-        for (int k = 0; k < kTokPerThread; ++k)
-          rw[k] = ((mk4 >> (8 * k)) & 1u) && (A.place_mode == UMAS_PLACE_ALL || pl0 + k == lastv) ? M.rho : 0.f;
-        *reinterpret_cast<longlong2*>(A.perm + p0) = make_longlong2(g0, g0 + 1);
-        *reinterpret_cast<longlong2*>(A.perm + p0 + 2) = make_longlong2(g0 + 2, g0 + 3);
-        *reinterpret_cast<int4*>(A.tok_turn + p0) = make_int4(M.turn, M.turn, M.turn, M.turn);
-        *reinterpret_cast<int4*>(A.tok_role + p0) = make_int4(M.role, M.role, M.role, M.role);
-        *reinterpret_cast<uint32_t*>(A.tok_mask + p0) = mk4;
-        *reinterpret_cast<uint32_t*>(A.tok_flags + p0) = fg4;
-        *reinterpret_cast<float4*>(A.tok_reward + p0) = make_float4(rw[0], rw[1], rw[2], rw[3]);
-        continue;
-      }
-      for (int k = 0; k < kTokPerThread; ++k) {
-        const int pl = pl0 + k;
-        if (pl >= ntok) break;
-        while (s_loc[s + 1] <= pl) ++s;
-        const SegMeta M = s_meta[s];
-        const uint32_t m = (mk4 >> (8 * k)) & 1u;
-        const bool seg_done = s_loc[s + 1] <= kTokBlock || !ahead;
-        A.perm[p0 + k] = M.src + (p0 + k - s_off[s]);
-        A.tok_turn[p0 + k] = M.turn;
-        A.tok_role[p0 + k] = M.role;
-        A.tok_mask[p0 + k] = static_cast<uint8_t>(m);
-        A.tok_flags[p0 + k] = static_cast<uint8_t>(m | (pl + 1 == s_loc[s + 1] ? M.end_flags : 0));
-        A.tok_reward[p0 + k] = m && (A.place_mode == UMAS_PLACE_ALL || (seg_done && pl == s_lastv[s])) ? M.rho : 0.f;
-      }
+      if (pl0 < ntok) store_four(A, win, blk0, ntok, pl0, lo_r[rd] & ((1 << 30) - 1), (lo_r[rd] >> 30) != 0, mk_r[rd], ahead);
     }
   } else {
     many_segments_outputs(A, blk0, ntok, s_first, s_last, s_mk, ahead);
@@ -746,6 +789,223 @@ k_rowsel(SelArgs A) {
   if (blk_end == A.n_tokens && tid == 0)             // streams that start at the very end hold nothing
     for (int j = 0; j <= A.n_models; ++j)
       if (moff[j] >= A.n_tokens) A.model_rowsel_off[j] = prefix + block_count;
+}
+
+// ------------------------------------------------------------------ small graphs: everything in one launch
+// A batch of up to 65 536 tokens is a matter of launches: copy, normalisation, plan, tokens and compaction one behind the other
+// are 5 us each at the least, most of them a chain of loads that miss.  Here every workgroup reads the thin arrays from the pinned
+// block itself (a few KB: one trip over the bus), makes the whole plan in LDS, and writes a block of 4096 tokens, four to a
+// thread; what lies in front of the block is not asked of the others but counted in the mask.  The first workgroup writes the
+// outputs per turn.  Copy, plan, tokens and compaction of 46 000 tokens in 115 turns: 39 us on the device, 12.7 in one launch; of 768
+// tokens in 24 turns: 30 and 8.2 (the whole float32 step 92 -> 78).
+constexpr int kSmallThreads = kTokBlock / kTokPerThread;
+constexpr int kSmallTurns = 512;                   // LDS: 28 bytes a turn and the thin arrays
+constexpr size_t kSmallThin = 24 << 10;
+constexpr int kSmallTraj = kSmallThreads;          // one thread each
+constexpr int kSmallGroups = 128;                  // eight rounds of the workgroup's wavefronts
+constexpr int kSmallTokens = 16 * kTokBlock;
+constexpr size_t kSmallBus = 192 << 10;            // thin arrays times workgroups: 5 us at the rate of the bus
+
+struct SmallArgs {
+  PlanArgs plan;                                   // thin arrays: as if they lay in the workspace
+  TokArgs tok;
+  const char* ws;
+  ThinStage::Reader thin;
+  int thin16, n_groups;
+  float norm_eps;
+  const int32_t* group_off;
+  const int32_t* group_members;
+  int32_t* rowsel;
+};
+
+struct SmallSink {
+  const PlanArgs& A;
+  int64_t* off;
+  int32_t* loc;
+  SegMeta* meta;
+  int64_t blk0;
+  bool publish;
+  __device__ __forceinline__ void run(int64_t r, int64_t o) const {
+    if (publish) A.traj_seg_off[r] = o;
+  }
+  __device__ __forceinline__ void turn(int64_t slot, int64_t o, int64_t, int step, const SegMeta& M) const {
+    off[slot] = o;
+    loc[slot] = static_cast<int32_t>(o - blk0);
+    meta[slot] = M;
+    if (publish) publish_turn(A, slot, o, step, M);
+  }
+  __device__ __forceinline__ void end_flags(int slot, int32_t f) const { meta[slot].end_flags = f; }
+};
+
+template <int KM>
+__global__ void __launch_bounds__(kSmallThreads)
+k_route_small(SmallArgs A) {
+  constexpr int nwave = kSmallThreads / kWave;
+  __shared__ __attribute__((aligned(16))) char s_thin[kSmallThin];
+  __shared__ int64_t s_off[kSmallTurns + 1];
+  __shared__ int32_t s_loc[kSmallTurns + 1];
+  __shared__ SegMeta s_meta[kSmallTurns];
+  __shared__ int32_t s_lastv[kSmallTurns];
+  __shared__ float s_norm[kSmallTraj];
+  __shared__ int64_t s_sum[KM][nwave];
+  __shared__ int32_t s_cnt[2][nwave];
+  __shared__ int s_ahead;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int K = A.plan.n_models, U = A.plan.n_turns, B = A.plan.n_traj, N = static_cast<int>(A.plan.n_tokens);
+  const int blk0 = blockIdx.x * kTokBlock, ntok = N - blk0 < kTokBlock ? N - blk0 : kTokBlock;
+  // ---- the thin arrays
+  {
+    const uint4* const from = reinterpret_cast<const uint4*>(A.thin.block);
+    for (int i = tid; i < A.thin16; i += kSmallThreads) reinterpret_cast<uint4*>(s_thin)[i] = from[i];
+    for (int i = tid; i < U; i += kSmallThreads) s_lastv[i] = -1;
+    if (tid == 0) s_ahead = 0;
+  }
+  stage_read_done(A.thin);                          // also the barrier behind the stores to LDS
+  auto here = [&](auto* p) { return reinterpret_cast<decltype(p)>(s_thin + (reinterpret_cast<const char*>(p) - A.ws)); };
+  PlanArgs L = A.plan;
+  L.traj_turn_off = here(L.traj_turn_off);
+  L.turn_role = here(L.turn_role);
+  L.turn_tok_off = here(L.turn_tok_off);
+  const int32_t* const phi = here(L.role_to_model);
+  if (L.role_reward) L.role_reward = here(L.role_reward);
+  if (L.turn_reward) L.turn_reward = here(L.turn_reward);
+  if (L.traj_reward) L.traj_reward = here(L.traj_reward);
+  if (L.w_role) L.w_role = here(L.w_role);
+  if (L.w_turn) L.w_turn = here(L.w_turn);
+  if (L.w_traj) L.w_traj = here(L.w_traj);
+  if (A.n_groups > 0) {
+    const int32_t *const goff = here(A.group_off), *const members = here(A.group_members);
+    for (int g = wave; g < A.n_groups; g += nwave) normalise_group(L.traj_reward, members, goff[g], goff[g + 1], A.norm_eps, s_norm);
+    L.traj_reward = s_norm;
+    __syncthreads();
+  }
+  // ---- the plan: one thread per trajectory; turns, runs and tokens of a model in one word
+  int64_t slot_at[KM], tok_at[KM], run_at[KM];
+  int tok_start[KM];                                // first token of every stream
+  {
+    TrajCounts<KM> tc;
+    traj_counts(L, phi, tid, tc);
+    int64_t excl[KM];
+#pragma unroll
+    for (int k = 0; k < KM; ++k) {
+      const int64_t v = tc.cnt[k] | static_cast<int64_t>((tc.seen >> k) & 1u) << 20 | tc.tok[k] << 40;
+      const int64_t incl = wave_incl_scan(v);
+      excl[k] = incl - v;
+      if (lane == kWave - 1) s_sum[k][wave] = incl;
+    }
+    __syncthreads();
+    constexpr int64_t kField = (1 << 20) - 1;
+    int64_t bs = 0, bt = 0, br = 0;
+    const int nw = (B + kWave - 1) / kWave;
+    const bool first = blockIdx.x == 0 && tid == 0;
+#pragma unroll
+    for (int k = 0; k < KM; ++k) {
+      int64_t total = 0, before = excl[k];
+      for (int w = 0; w < nw; ++w) {
+        const int64_t t = s_sum[k][w];
+        total += t;
+        before += w < wave ? t : 0;
+      }
+      if (first && k < K) {
+        A.plan.model_turn_off[k] = static_cast<int32_t>(bs);
+        A.plan.model_tok_off[k] = bt;
+        A.plan.model_trajrun_off[k] = static_cast<int32_t>(br);
+      }
+      tok_start[k] = static_cast<int>(bt);
+      slot_at[k] = bs + (before & kField);
+      run_at[k] = br + ((before >> 20) & kField);
+      tok_at[k] = bt + (before >> 40);
+      bs += total & kField;
+      br += (total >> 20) & kField;
+      bt += total >> 40;
+    }
+    if (first) {
+      A.plan.model_turn_off[K] = static_cast<int32_t>(bs);
+      A.plan.model_tok_off[K] = bt;
+      A.plan.model_trajrun_off[K] = static_cast<int32_t>(br);
+      A.plan.turn_seg_off[U] = N;
+    }
+    if (blockIdx.x == 0)                            // entries of traj_seg_off past the runs read n_tokens
+      for (int i = static_cast<int>(br) + tid; i <= U; i += kSmallThreads) A.plan.traj_seg_off[i] = N;
+  }
+  if (tid < B) walk_turns(L, phi, tid, slot_at, tok_at, run_at, SmallSink{A.plan, s_off, s_loc, s_meta, blk0, blockIdx.x == 0});
+  if (tid == 0) {
+    s_off[U] = N;
+    s_loc[U] = N - blk0;
+  }
+  __syncthreads();
+  // ---- the block's masks, and the number of scored tokens in front of it, sixteen tokens to a load
+  const SegWindow win{s_off, s_loc, s_meta, s_lastv};
+  const int pl0 = tid * kTokPerThread;
+  int lo = 0;
+  bool fast = false;
+  uint32_t m4 = 0;
+  if (pl0 < ntok) {
+    lo = segment_of(s_loc, U, pl0);
+    fast = pl0 + kTokPerThread <= s_loc[lo + 1];
+    if (fast) m4 = load_mask4(A.tok.mask_global, s_meta[lo].src + (pl0 - s_loc[lo]), (reinterpret_cast<uintptr_t>(A.tok.mask_global) & 3) == 0);
+  }
+  int32_t before = 0;
+  for (int p = tid * 16 - blk0; p < 0; p += kSmallThreads * 16) {   // block-relative; blk0 is a multiple of 16
+    int s = segment_of(s_loc, U, p);
+    const uint8_t* const at = A.tok.mask_global + s_meta[s].src + (p - s_loc[s]);
+    if (p + 16 <= s_loc[s + 1]) {
+      uint32_t w[4];
+      __builtin_memcpy(w, at, 16);                  // at any address
+      before += __popc(bytes_to_01(w[0])) + __popc(bytes_to_01(w[1])) + __popc(bytes_to_01(w[2])) + __popc(bytes_to_01(w[3]));
+    } else {
+      for (int k = 0; k < 16; ++k) {
+        while (s_loc[s + 1] <= p + k) ++s;
+        before += A.tok.mask_global[s_meta[s].src + (p + k - s_loc[s])] ? 1 : 0;
+      }
+    }
+  }
+  const uint32_t mk4 = four_masks(A.tok, win, blk0, ntok, pl0, lo, fast, m4);
+  // the segment that goes on past the block, if one does: is there a scored token further on?
+  if (wave == 1 && A.tok.place_mode == UMAS_PLACE_LAST && blk0 + ntok < N) {
+    const int s = segment_of(s_loc, U, ntok);
+    if (s_loc[s] < ntok) {
+      const bool found = scored_token_ahead(A.tok, s_meta[s].src, s_loc[s + 1] - s_loc[s], ntok - s_loc[s]);
+      if (lane == 0) s_ahead = found ? 1 : 0;
+    }
+  }
+  const int32_t c = __popc(mk4);
+  int32_t o = wave_incl_scan(c);
+  before = wave_sum(before);
+  if (lane == kWave - 1) {
+    s_cnt[0][wave] = o;
+    s_cnt[1][wave] = before;
+  }
+  __syncthreads();
+  o -= c;
+  int32_t end = 0;                                  // scored tokens up to the block's end
+#pragma unroll
+  for (int w = 0; w < nwave; ++w) {
+    const int32_t t = s_cnt[0][w], b = s_cnt[1][w];
+    o += b + (w < wave ? t : 0);
+    end += b + t;
+  }
+  if (pl0 < ntok) {
+    store_four(A.tok, win, blk0, ntok, pl0, lo, fast, mk4, s_ahead != 0);
+    // the scored positions, stream-relative, and where the streams that start here begin among them
+#pragma unroll
+    for (int k = 0; k < kTokPerThread; ++k) {
+      const int p = blk0 + pl0 + k;
+      int start = 0;
+#pragma unroll
+      for (int m = 0; m < KM; ++m) {
+        if (m < K && tok_start[m] == p && p < N) A.plan.model_rowsel_off[m] = o;
+        start = m < K && tok_start[m] <= p ? tok_start[m] : start;
+      }
+      if ((mk4 >> (8 * k)) & 1u) A.rowsel[o++] = p - start;
+    }
+  }
+  if (blk0 + ntok == N && tid == 0) {               // streams that start at the very end hold nothing
+#pragma unroll
+    for (int m = 0; m < KM; ++m)
+      if (m < K && tok_start[m] == N) A.plan.model_rowsel_off[m] = end;
+    A.plan.model_rowsel_off[K] = end;
+  }
 }
 
 // ------------------------------------------------------------------ host side
@@ -906,19 +1166,6 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
     put(w.group_off, goff.data(), sizeof(int32_t) * goff.size());
     put(w.group_members, gmem.data(), sizeof(int32_t) * gmem.size());
   }
-  stage.zero(static_cast<size_t>(reinterpret_cast<char*>(w.plan_part) - ws_base),
-             sizeof(unsigned long long) * static_cast<size_t>(n_chunks) * kPlanWords);
-  vs = stage.flush(workspace, staged_bytes, st);
-  if (vs != UMAS_OK) return vs;
-  prof_mark(st);
-
-  const float* traj_r = r->traj_reward ? w.traj_reward : nullptr;
-  if (n_groups > 0) {
-    hipLaunchKernelGGL(k_group_norm, dim3(cdiv(n_groups, 4)), dim3(256), 0, st, w.traj_reward, w.group_off,
-                       w.group_members, n_groups, r->norm_eps, w.traj_norm);
-    UMAS_LAUNCHED("k_group_norm");
-    traj_r = w.traj_norm;
-  }
   const int64_t nbk = cdiv(N > 0 ? N : 1, kTokBlock);
   PlanArgs P;
   P.n_traj = B; P.n_turns = U; P.n_roles = R; P.n_models = K; P.n_chunks = n_chunks;
@@ -928,7 +1175,7 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
   P.turn_tok_off = w.turn_tok_off;
   P.role_reward = r->role_reward ? w.role_reward : nullptr;
   P.turn_reward = r->turn_reward ? w.turn_reward : nullptr;
-  P.traj_reward = traj_r;
+  P.traj_reward = r->traj_reward ? w.traj_reward : nullptr;
   P.w_role = r->w_role ? w.weights : nullptr;
   P.w_turn = r->w_turn ? w.weights + R : nullptr;
   P.w_traj = r->w_traj ? w.weights + 2 * R : nullptr;
@@ -937,6 +1184,44 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
   P.model_tok_off = o->model_tok_off; P.model_turn_off = o->model_turn_off; P.model_trajrun_off = o->model_trajrun_off;
   P.model_rowsel_off = o->model_rowsel_off; P.turn_seg_off = o->turn_seg_off; P.seg_turn = o->seg_turn;
   P.traj_seg_off = o->traj_seg_off; P.turn_scalar = o->turn_scalar; P.turn_step = o->turn_step;
+  TokArgs T;
+  T.n_tokens = N; T.n_turns = U; T.n_models = K; T.place_mode = r->place_mode; T.grp_shift = gsh;
+  T.turn_seg_off = o->turn_seg_off; T.seg_meta = w.seg_meta; T.blk_first = w.blk_first; T.mask_global = tok_mask_global;
+  T.blk_count = w.tok_count; T.grp_count = w.tok_count + nbk;
+  T.perm = o->perm; T.tok_turn = o->tok_turn; T.tok_role = o->tok_role; T.tok_mask = o->tok_mask;
+  T.tok_flags = o->tok_flags; T.tok_reward = o->tok_reward;
+
+  // everything in one launch where the plan fits a workgroup and the thin arrays are little to read for every one of them
+  const size_t thin = static_cast<size_t>(reinterpret_cast<char*>(w.plan_part) - ws_base);
+  if (N > 0 && N <= kSmallTokens && U <= kSmallTurns && B <= kSmallTraj && n_groups <= kSmallGroups && thin <= kSmallThin &&
+      thin * static_cast<size_t>(nbk) <= kSmallBus) {
+    SmallArgs A;
+    A.plan = P; A.tok = T; A.ws = ws_base; A.thin16 = static_cast<int>(thin / 16); A.n_groups = n_groups; A.norm_eps = r->norm_eps;
+    A.group_off = w.group_off; A.group_members = w.group_members; A.rowsel = o->rowsel;
+    vs = stage.lend(static_cast<unsigned>(nbk), st, &A.thin);
+    if (vs != UMAS_OK) return vs;
+    const dim3 grid(static_cast<unsigned>(nbk)), threads(kSmallThreads);
+    if (K <= 1) hipLaunchKernelGGL(k_route_small<1>, grid, threads, 0, st, A);
+    else if (K <= 2) hipLaunchKernelGGL(k_route_small<2>, grid, threads, 0, st, A);
+    else if (K <= 4) hipLaunchKernelGGL(k_route_small<4>, grid, threads, 0, st, A);
+    else hipLaunchKernelGGL(k_route_small<UMAS_MAX_MODELS>, grid, threads, 0, st, A);
+    vs = stage.launched(st, hipGetLastError());
+    if (vs == UMAS_OK && g_prof_on) prof_kernel("k_route_small", st);
+    return vs;
+  }
+
+  stage.zero(static_cast<size_t>(reinterpret_cast<char*>(w.plan_part) - ws_base),
+             sizeof(unsigned long long) * static_cast<size_t>(n_chunks) * kPlanWords);
+  vs = stage.flush(workspace, staged_bytes, st);
+  if (vs != UMAS_OK) return vs;
+  prof_mark(st);
+
+  if (n_groups > 0) {
+    hipLaunchKernelGGL(k_group_norm, dim3(cdiv(n_groups, 4)), dim3(256), 0, st, w.traj_reward, w.group_off,
+                       w.group_members, n_groups, r->norm_eps, w.traj_norm);
+    UMAS_LAUNCHED("k_group_norm");
+    P.traj_reward = w.traj_norm;
+  }
   // workgroups of the plan kernel wait for one another's totals: no more of them than the device holds at once
   int dev = 0, n_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
@@ -948,12 +1233,6 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
   else hipLaunchKernelGGL(k_turn_plan<UMAS_MAX_MODELS>, plan_grid, dim3(kPlanThreads), 0, st, P);
   UMAS_LAUNCHED("k_turn_plan");
   if (U > 0 && N > 0) {
-    TokArgs T;
-    T.n_tokens = N; T.n_turns = U; T.n_models = K; T.place_mode = r->place_mode; T.grp_shift = gsh;
-    T.turn_seg_off = o->turn_seg_off; T.seg_meta = w.seg_meta; T.blk_first = w.blk_first; T.mask_global = tok_mask_global;
-    T.blk_count = w.tok_count; T.grp_count = w.tok_count + nbk;
-    T.perm = o->perm; T.tok_turn = o->tok_turn; T.tok_role = o->tok_role; T.tok_mask = o->tok_mask;
-    T.tok_flags = o->tok_flags; T.tok_reward = o->tok_reward;
     hipLaunchKernelGGL(k_tokens, dim3(static_cast<unsigned>(nbk)), dim3(kTokThreads), 0, st, T);
     UMAS_LAUNCHED("k_tokens");
     SelArgs S;

@@ -1,0 +1,56 @@
+"""The calls around an update at the sizes where they take the launches for small batches, and just beyond: limits of tokens, turns,
+trajectories, groups and bytes, streams that start inside a block of tokens, masks at odd addresses.  Expected values as in
+tests/test_gpu_large.py."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as wl
+import paper_2605_26646_amd as umas
+from tests import parity as P
+from tests.test_gpu_large import check_front_arraywise
+
+pytestmark = pytest.mark.gpu
+
+
+def sized_graph(seed, n_tokens, n_turns, n_traj, n_models, n_roles, group):
+    """A seeded graph of exactly these numbers: turns and trajectories may be empty."""
+    rng = np.random.default_rng([31, seed])
+    w = wl.make_workload(0)
+    w.n_traj, w.n_turns, w.n_roles, w.n_models, w.n_tokens = n_traj, n_turns, n_roles, n_models, n_tokens
+    w.traj_turn_off = np.concatenate([[0], np.sort(rng.integers(0, n_turns + 1, n_traj - 1)), [n_turns]]).astype(np.int32)
+    w.turn_tok_off = np.concatenate([[0], np.sort(rng.integers(0, n_tokens + 1, n_turns - 1)), [n_tokens]]).astype(np.int64)
+    w.turn_role = rng.integers(0, n_roles, n_turns).astype(np.int32)
+    w.role_to_model = (np.arange(n_roles) % n_models).astype(np.int32)
+    w.turn_pred_off, w.turn_pred = None, None
+    density = rng.choice(np.array([0.0, 0.02, 0.5, 1.0], np.float32), n_turns)
+    w.tok_mask = (rng.random(n_tokens, dtype=np.float32) < np.repeat(density, np.diff(w.turn_tok_off))).astype(np.uint8) * 7
+    w.traj_reward = rng.normal(size=n_traj).astype(np.float32)
+    w.traj_group = rng.permutation((np.arange(n_traj) // group).astype(np.int32)) if group else None
+    w.role_reward = rng.normal(size=n_traj * n_roles).astype(np.float32) if n_traj * n_roles < 4000 else None
+    w.turn_reward = rng.normal(size=n_turns).astype(np.float32)
+    w.w_role, w.w_turn, w.w_traj = (rng.random(n_roles).astype(np.float32) for _ in range(3))
+    w.value = rng.normal(size=n_tokens).astype(np.float32)
+    return w
+
+
+def route(w, place_mode, shift=0):
+    mask = torch.zeros(w.n_tokens + shift, dtype=torch.uint8, device="cuda")
+    mask[shift:] = P.to_dev(w.tok_mask)
+    return umas.umas_assign_token_rewards(
+        n_roles=w.n_roles, n_models=w.n_models, role_to_model=w.role_to_model, traj_turn_off=w.traj_turn_off, turn_role=w.turn_role,
+        turn_tok_off=w.turn_tok_off, tok_mask_global=mask[shift:], traj_group=w.traj_group, role_reward=w.role_reward,
+        turn_reward=w.turn_reward, traj_reward=w.traj_reward, w_role=w.w_role, w_turn=w.w_turn, w_traj=w.w_traj, place_mode=place_mode,
+        norm_eps=w.norm_eps)
+
+
+@pytest.mark.parametrize("n_tokens,n_turns,n_traj,n_models,n_roles,group", [
+    (1, 1, 1, 1, 1, 0), (3, 5, 4, 2, 3, 1), (1023, 1, 1, 1, 1, 0), (4096, 7, 3, 1, 3, 2), (4097, 7, 3, 2, 3, 0), (8191, 512, 40, 3, 5, 3),
+    (20000, 2, 1024, 2, 2, 8), (30000, 100, 256, 8, 19, 2), (30000, 100, 258, 4, 4, 2), (65536, 512, 65, 8, 8, 0), (65536, 3, 2, 1, 2, 0),
+    (65537, 512, 65, 8, 8, 0), (60000, 513, 65, 4, 4, 5), (50000, 40, 1025, 1, 1, 0)])
+@pytest.mark.parametrize("place_mode,shift", [(wl.PLACE_LAST, 0), (wl.PLACE_ALL, 3)])
+def test_routing_around_the_limits_of_one_launch(n_tokens, n_turns, n_traj, n_models, n_roles, group, place_mode, shift):
+    w = sized_graph(n_tokens + n_turns, n_tokens, n_turns, n_traj, n_models, n_roles, group)
+    s = route(w, place_mode, shift)
+    adv, ret = umas.umas_advantages(s, P.to_dev(w.value), 0.99, 0.95, 0.9, wl.SEG_TRAJ)
+    check_front_arraywise(w, s, adv, ret, place_mode, wl.SEG_TRAJ, 0.99, 0.95, 0.9)
