@@ -7,8 +7,9 @@ import torch
 
 import workloads as wl
 import paper_2605_26646_amd as umas
+from tests import arraywise as aw
 from tests import parity as P
-from tests.test_gpu_large import check_front_arraywise
+from tests.test_gpu_large import check_front_arraywise, check_ready_batch_arraywise
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +55,23 @@ def test_routing_around_the_limits_of_one_launch(n_tokens, n_turns, n_traj, n_mo
     s = route(w, place_mode, shift)
     adv, ret = umas.umas_advantages(s, P.to_dev(w.value), 0.99, 0.95, 0.9, wl.SEG_TRAJ)
     check_front_arraywise(w, s, adv, ret, place_mode, wl.SEG_TRAJ, 0.99, 0.95, 0.9)
+
+
+@pytest.mark.parametrize("n_tokens,n_turns,n_traj,n_models", [
+    (1, 1, 1, 1), (500, 64, 33, 1), (3000, 65, 64, 2), (9000, 257, 65, 3), (60000, 1024, 256, 4), (200000, 9, 2, 1), (90000, 300, 128, 8),
+    (20000, 1025, 256, 4), (20000, 1000, 257, 1), (20000, 1000, 205, 5)])
+@pytest.mark.parametrize("share", [0.8, 0.0, None])
+def test_ready_batch_around_the_limits_of_one_launch(n_tokens, n_turns, n_traj, n_models, share):
+    w = sized_graph(n_tokens + n_turns, n_tokens, n_turns, n_traj, n_models, n_models + 1, 0)
+    s = route(w, wl.PLACE_LAST)
+    rng = np.random.default_rng(n_tokens)
+    keep = None if share is None else (rng.random(n_traj) < share).astype(np.uint8)
+    order = None if share is None else rng.permutation(n_traj).astype(np.int32)
+    sa = aw.streams(w)
+    for M in (1, 7, 300):
+        check_ready_batch_arraywise(w, s, sa, np.ones(n_traj, np.uint8) if keep is None else keep,
+                                    np.arange(n_traj, dtype=np.int32) if order is None else order, M)
+    if share is None:                                    # neither given
+        rows, off = umas.umas_ready_batch(s, w.traj_turn_off, 3)
+        want_rows, want_off = aw.ready_batch(w, sa, np.ones(n_traj, np.uint8), np.arange(n_traj, dtype=np.int32), 3, False)
+        assert np.array_equal(off.cpu().numpy(), want_off) and np.array_equal(rows.cpu().numpy()[:len(want_rows)], want_rows)
