@@ -27,6 +27,8 @@
 // only ever waits for maps of ranges to its right, written by the first kernel or by a workgroup that is running,
 // and publishing a map waits for nothing, so every wait ends.  When no segment is that long the second kernel finds
 // nothing to do and leaves at once.
+#include <type_traits>
+
 #include "umas_common.h"
 
 namespace umas {
@@ -45,6 +47,10 @@ inline int64_t chunk_tokens(int64_t n_tokens) {
   return (tiles < 1 ? 1 : tiles > kChunkTiles ? kChunkTiles : tiles) * kTile;
 }
 constexpr int64_t kLongSegment = 16 * kTile;     // a segment end farther away than this does not move a range's edge
+// Up to so many tokens a workgroup whose range ends inside a long segment reads on to its end itself instead of leaving the range to
+// a second launch, which costs 5 us also when there is nothing to do (46 000 tokens in turns: 11.4 us in two launches that follow each
+// other, 6.8 in one; 11 and 5.7 us of the host).
+constexpr int64_t kAloneTokens = 64 * kTile;
 constexpr int kAhead = 1;                        // tiles whose loads are in flight beyond the one in work
 
 enum : uint8_t { kFlagMask = 1, kFlagTurnEnd = 2, kFlagRunEnd = 4 };
@@ -140,13 +146,13 @@ __device__ __forceinline__ int64_t boundary_at_or_after(const int64_t* __restric
   return off[wave_last_le(off, n, x - 1) + 1];
 }
 // Where the range edge nominally at x really lies: at the next segment boundary unless that is farther than
-// kLongSegment away, in which case the edge stays at x, inside the segment (*cut = 1).
-__device__ __forceinline__ int64_t range_edge(const int64_t* __restrict__ off, int n, int64_t n_tokens, int64_t x, int* cut) {
+// kLongSegment away, in which case the edge stays at x, inside the segment (*cut = 1).  *boundary: that boundary.
+__device__ __forceinline__ int64_t range_edge(const int64_t* __restrict__ off, int n, int64_t n_tokens, int64_t x, int* cut, int64_t* boundary) {
   *cut = 0;
-  if (x <= 0) return 0;
-  if (x >= n_tokens) return n_tokens;
-  const int64_t b = boundary_at_or_after(off, n, x);
-  if (b - x < kLongSegment) return b;
+  *boundary = x <= 0 ? 0 : n_tokens;
+  if (x <= 0 || x >= n_tokens) return *boundary;
+  *boundary = boundary_at_or_after(off, n, x);
+  if (*boundary - x < kLongSegment) return *boundary;
   *cut = 1;
   return x;
 }
@@ -223,15 +229,14 @@ __device__ __forceinline__ void look_back(const ScanParams& P, uint32_t q, float
   *NV_in = HV ? M.f : 0.f;
 }
 
-// this thread's four consecutive tokens of a tile: 16 bytes per array, 4 bytes of flags; tokens past the end of the
+// four consecutive tokens from p on, a multiple of four: 16 bytes per array, 4 bytes of flags; tokens past the end of the
 // stream read as masked, without flags
 struct Raw {
   float4 r4, v4;
   uint32_t w;
 };
 template <bool HV>
-__device__ __forceinline__ void load_tile(const ScanParams& P, const Range& R, int64_t tile, Raw& x) {
-  const int64_t p = tile * kTile + static_cast<int64_t>(threadIdx.x) * kIpt;
+__device__ __forceinline__ void load_four(const ScanParams& P, const Range& R, int64_t p, Raw& x) {
   x.r4 = make_float4(0.f, 0.f, 0.f, 0.f);
   x.v4 = x.r4;
   x.w = 0;
@@ -252,6 +257,51 @@ __device__ __forceinline__ void load_tile(const ScanParams& P, const Range& R, i
   }
 }
 
+// Four consecutive tokens from p0 on as the walks use them.
+struct Four {
+  float r[kIpt], v[kIpt];
+  uint32_t fl[kIpt];
+  float kap[kIpt];                                  // step discount applied before the token (1 = none)
+  bool mine[kIpt];                                  // tokens outside the range belong to a neighbour
+};
+template <bool DECAY>
+__device__ __forceinline__ Four four_tokens(const ScanParams& P, const Range& R, int64_t p0, const Raw& x) {
+  Four T{{x.r4.x, x.r4.y, x.r4.z, x.r4.w}, {x.v4.x, x.v4.y, x.v4.z, x.v4.w}, {}, {}, {}};
+#pragma unroll
+  for (int k = 0; k < kIpt; ++k) {
+    T.fl[k] = (x.w >> (8 * k)) & 0xFFu;
+    T.mine[k] = p0 + k >= R.start && p0 + k < R.end;
+    T.kap[k] = 1.f;
+    if constexpr (DECAY) {
+      if (T.mine[k] && (T.fl[k] & kFlagTurnEnd) && !(T.fl[k] & P.seg_bit)) {   // a later turn of the same run follows: p + 1 exists
+        int ds = static_cast<int>(T.fl[k] >> kFlagStepShift);   // steps to the run's next turn; kFlagStepMany: more than fit
+        if (ds == kFlagStepMany) {
+          const int64_t p = p0 + k;
+          ds = P.turn_step[P.tok_turn[p + 1]] - P.turn_step[P.tok_turn[p]];
+        }
+        T.kap[k] = powf(P.gamma_turn, static_cast<float>(ds));
+      }
+    }
+  }
+  return T;
+}
+// fold of the four tokens, right to left
+template <bool HV, bool DECAY>
+__device__ __forceinline__ Aff fold_four(const ScanParams& P, const Four& T) {
+  Aff acc = aff_identity();
+#pragma unroll
+  for (int k = kIpt - 1; k >= 0; --k) {
+    if (!T.mine[k]) continue;
+    if (T.fl[k] & P.seg_bit) acc = Aff{0.f, 0.f, 0.f, 0.f, 0.f};
+    else if constexpr (DECAY) { acc.a *= T.kap[k]; acc.b *= T.kap[k]; acc.c *= T.kap[k]; acc.e *= T.kap[k]; acc.f *= T.kap[k]; }
+    if (T.fl[k] & kFlagMask) {
+      const Aff t{P.gamma * P.lam, P.gamma, T.r[k] - T.v[k], 0.f, T.v[k]};
+      acc = then<HV>(acc, t);
+    }
+  }
+  return acc;
+}
+
 // One walk over the tiles of a range, right to left.  REPLAY = false: fold only, returns the range's map in *total.
 // REPLAY = true: starts from the state (*G_io, *NV_io), writes advantages and returns, leaves the state at the
 // range's left edge in (*G_io, *NV_io) (valid in thread 0).
@@ -264,7 +314,7 @@ __device__ __forceinline__ void walk_range(const ScanParams& P, const Range& R, 
   Raw buf[kAhead + 1];
 #pragma unroll
   for (int a = 0; a <= kAhead; ++a)
-    if (t_hi - a >= t_lo) load_tile<HV>(P, R, t_hi - a, buf[a]);
+    if (t_hi - a >= t_lo) load_four<HV>(P, R, (t_hi - a) * kTile + tid * kIpt, buf[a]);
   Aff range_map = aff_identity();
   if (REPLAY && tid == 0) { s_carry[0][0] = *G_io; s_carry[0][1] = *NV_io; }
   int par = 0;
@@ -273,41 +323,10 @@ __device__ __forceinline__ void walk_range(const ScanParams& P, const Range& R, 
     const Raw x = buf[0];
 #pragma unroll
     for (int a = 0; a < kAhead; ++a) buf[a] = buf[a + 1];
-    if (tile - kAhead - 1 >= t_lo) load_tile<HV>(P, R, tile - kAhead - 1, buf[kAhead]);
+    if (tile - kAhead - 1 >= t_lo) load_four<HV>(P, R, (tile - kAhead - 1) * kTile + tid * kIpt, buf[kAhead]);
     const int64_t p0 = tile * kTile + static_cast<int64_t>(tid) * kIpt;
-    const float r[kIpt] = {x.r4.x, x.r4.y, x.r4.z, x.r4.w};
-    const float v[kIpt] = {x.v4.x, x.v4.y, x.v4.z, x.v4.w};
-    uint32_t fl[kIpt];
-    float kap[kIpt];                                // step discount applied before the token (1 = none)
-    bool mine[kIpt];                                // tokens outside the range belong to a neighbour
-#pragma unroll
-    for (int k = 0; k < kIpt; ++k) {
-      fl[k] = (x.w >> (8 * k)) & 0xFFu;
-      mine[k] = p0 + k >= R.start && p0 + k < R.end;
-      kap[k] = 1.f;
-      if constexpr (DECAY) {
-        if (mine[k] && (fl[k] & kFlagTurnEnd) && !(fl[k] & P.seg_bit)) {   // a later turn of the same run follows: p + 1 exists
-          int ds = static_cast<int>(fl[k] >> kFlagStepShift);   // steps to the run's next turn; kFlagStepMany: more than fit
-          if (ds == kFlagStepMany) {
-            const int64_t p = p0 + k;
-            ds = P.turn_step[P.tok_turn[p + 1]] - P.turn_step[P.tok_turn[p]];
-          }
-          kap[k] = powf(P.gamma_turn, static_cast<float>(ds));
-        }
-      }
-    }
-    // fold of this thread's tokens, right to left
-    Aff acc = aff_identity();
-#pragma unroll
-    for (int k = kIpt - 1; k >= 0; --k) {
-      if (!mine[k]) continue;
-      if (fl[k] & P.seg_bit) acc = Aff{0.f, 0.f, 0.f, 0.f, 0.f};
-      else if constexpr (DECAY) { acc.a *= kap[k]; acc.b *= kap[k]; acc.c *= kap[k]; acc.e *= kap[k]; acc.f *= kap[k]; }
-      if (fl[k] & kFlagMask) {
-        const Aff t{gl, P.gamma, r[k] - v[k], 0.f, v[k]};
-        acc = then<HV>(acc, t);
-      }
-    }
+    const Four T = four_tokens<DECAY>(P, R, p0, x);
+    const Aff acc = fold_four<HV, DECAY>(P, T);
     Aff tile_map;
     const Aff from_right = block_suffix_excl<HV>(acc, s_w[par], &tile_map);   // the one barrier of a tile
     if constexpr (!REPLAY) {
@@ -321,24 +340,24 @@ __device__ __forceinline__ void walk_range(const ScanParams& P, const Range& R, 
       for (int k = kIpt - 1; k >= 0; --k) {
         a[k] = 0.f;
         b[k] = 0.f;
-        if (!mine[k]) continue;
-        if (fl[k] & P.seg_bit) { G = 0.f; NV = 0.f; }
-        else if constexpr (DECAY) { G *= kap[k]; NV *= kap[k]; }
-        if (fl[k] & kFlagMask) {
-          G = (r[k] - v[k]) + P.gamma * NV + gl * G;
-          NV = v[k];
+        if (!T.mine[k]) continue;
+        if (T.fl[k] & P.seg_bit) { G = 0.f; NV = 0.f; }
+        else if constexpr (DECAY) { G *= T.kap[k]; NV *= T.kap[k]; }
+        if (T.fl[k] & kFlagMask) {
+          G = (T.r[k] - T.v[k]) + P.gamma * NV + gl * G;
+          NV = T.v[k];
           a[k] = G;
-          b[k] = G + v[k];
+          b[k] = G + T.v[k];
         }
       }
       if (tid == 0) { s_carry[par ^ 1][0] = G; s_carry[par ^ 1][1] = NV; }   // state at the tile's left edge
-      if (mine[0] && mine[kIpt - 1]) {
+      if (T.mine[0] && T.mine[kIpt - 1]) {
         *reinterpret_cast<float4*>(adv + p0) = make_float4(a[0], a[1], a[2], a[3]);
         *reinterpret_cast<float4*>(ret + p0) = make_float4(b[0], b[1], b[2], b[3]);
       } else {
 #pragma unroll
         for (int k = 0; k < kIpt; ++k)
-          if (mine[k]) { adv[p0 + k] = a[k]; ret[p0 + k] = b[k]; }
+          if (T.mine[k]) { adv[p0 + k] = a[k]; ret[p0 + k] = b[k]; }
       }
     }
     par ^= 1;
@@ -346,15 +365,46 @@ __device__ __forceinline__ void walk_range(const ScanParams& P, const Range& R, 
   if constexpr (REPLAY) { *G_io = G; *NV_io = NV; } else { *total = range_map; }
 }
 
-// One workgroup per range.  It finds the range's edges (two wavefront-wide searches, one wavefront each), leaves them
-// for the second kernel and clears the range's record; then, unless the range is empty or its right end lies inside a
-// long segment, it scans the range: nothing comes in from the right.
+// The map of the tokens R, which end a segment, for a workgroup that needs the state on their left: every wavefront folds a quarter of
+// them, 256 at a time, and needs a barrier only at the end.  Every thread gets the map.
 template <bool HV, bool DECAY>
+__device__ __forceinline__ Aff fold_ahead(const ScanParams& P, const Range& R, Aff* s_w) {
+  constexpr int nwave = kThreads / kWave, kStep = kWave * kIpt;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int64_t first = R.start / kStep, n = (R.end - 1) / kStep + 1 - first, per = (n + nwave - 1) / nwave;
+  const int64_t lo = first + wave * per, hi = lo + per < first + n ? lo + per : first + n;
+  Aff map = aff_identity();
+  Raw next;
+  if (hi > lo) load_four<HV>(P, R, (hi - 1) * kStep + lane * kIpt, next);
+  for (int64_t t = hi - 1; t >= lo; --t) {
+    const Raw x = next;
+    if (t > lo) load_four<HV>(P, R, (t - 1) * kStep + lane * kIpt, next);
+    Aff acc = fold_four<HV, DECAY>(P, four_tokens<DECAY>(P, R, t * kStep + lane * kIpt, x));
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const Aff right = aff_shfl_down<HV>(acc, o);
+      if (lane + o < kWave) acc = then<HV>(right, acc);
+    }
+    map = then<HV>(map, acc);                       // in lane 0
+  }
+  if (lane == 0) s_w[wave] = map;
+  __syncthreads();
+  Aff total = aff_identity();
+  for (int w = nwave - 1; w >= 0; --w) total = then<HV>(total, s_w[w]);
+  __syncthreads();
+  return total;
+}
+
+// One workgroup per range.  It finds the range's edges (two wavefront-wide searches, one wavefront each).  Unless the range is
+// empty or its right end lies inside a long segment, it scans the range: nothing comes in from the right.  What the second kernel needs is
+// left for it: the edges, the range's record cleared or published.  With ALONE there is no second kernel: a workgroup whose range ends inside a
+// segment reads on to the segment's end itself, for its map.
+template <bool HV, bool DECAY, bool ALONE>
 __global__ void __launch_bounds__(kThreads)
 k_gae_scan(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
   __shared__ Aff s_w[2][kThreads / kWave];
   __shared__ float s_carry[2][2];
-  __shared__ int64_t s_edge[2];
+  __shared__ int64_t s_edge[2], s_end;
   __shared__ int s_cut[2];
   const int tid = threadIdx.x;
   const uint32_t q = blockIdx.x;                                                   // from the right
@@ -362,8 +412,13 @@ k_gae_scan(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
   if (tid < 2 * kWave) {
     const int which = tid / kWave;                   // wavefront 0: left edge, wavefront 1: right edge
     int cut;
-    const int64_t edge = range_edge(P.seg_off, P.n_seg_entries, P.n_tokens, (i + which) * P.chunk, &cut);
-    if ((tid & (kWave - 1)) == 0) { s_edge[which] = edge; s_cut[which] = cut; }
+    int64_t boundary;
+    const int64_t edge = range_edge(P.seg_off, P.n_seg_entries, P.n_tokens, (i + which) * P.chunk, &cut, &boundary);
+    if ((tid & (kWave - 1)) == 0) {
+      s_edge[which] = edge;
+      s_cut[which] = cut;
+      if (which == 1) s_end = boundary;
+    }
   }
   __syncthreads();
   Range R;
@@ -372,14 +427,24 @@ k_gae_scan(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
   R.cut_left = s_cut[0];
   R.cut_right = s_cut[1];
   R.pad = 0;
-  if (tid == 0) P.ranges[q] = R;
-  if (tid < kStateWords) P.range_state[static_cast<size_t>(q) * kStateWords + tid] = 0ull;
-  if (R.start >= R.end || R.cut_right) return;      // the same for every thread
   float G = 0.f, NV = 0.f;
+  if constexpr (ALONE) {
+    if (R.start >= R.end) return;                   // the same for every thread, also below
+    if (R.cut_right) {
+      const Range ahead{R.end, s_end, 0, 0, 0};
+      const Aff m = fold_ahead<HV, DECAY>(P, ahead, s_w[0]);
+      G = m.c;                                      // a constant map: a segment ends there
+      NV = HV ? m.f : 0.f;
+    }
+  } else {
+    if (tid == 0) P.ranges[q] = R;
+    if (tid < kStateWords) P.range_state[static_cast<size_t>(q) * kStateWords + tid] = 0ull;
+    if (R.start >= R.end || R.cut_right) return;
+  }
   Aff unused;
   walk_range<HV, DECAY, true>(P, R, adv, ret, s_w, s_carry, &G, &NV, &unused);
   // a range that starts inside a long segment: what it hands to the left is a constant
-  if (R.cut_left && tid == 0)
+  if (!ALONE && R.cut_left && tid == 0)
     publish<HV>(P.range_state + static_cast<size_t>(q) * kStateWords, Aff{0.f, 0.f, G, 0.f, HV ? NV : 0.f});
 }
 
@@ -481,11 +546,16 @@ extern "C" umas_status umas_advantages(const umas_streams* s, int64_t n_tokens, 
   P.lam = lam;
   P.gamma_turn = gamma_turn;
   const bool decay = seg_mode == UMAS_SEG_TRAJ && gamma_turn != 1.0f;
-  void (*kernel)(ScanParams, float*, float*) =
-      value ? (decay ? k_gae_scan<true, true> : k_gae_scan<true, false>) : (decay ? k_gae_scan<false, true> : k_gae_scan<false, false>);
+  // no segment reaches far enough past a range's edge to be cut, or the tokens are few enough to be read again
+  const bool alone = n_tokens <= kAloneTokens || n_tokens - P.chunk < kLongSegment;
+  auto pick = [&](auto al) -> void (*)(ScanParams, float*, float*) {
+    constexpr bool A = decltype(al)::value;
+    return value ? (decay ? k_gae_scan<true, true, A> : k_gae_scan<true, false, A>) : (decay ? k_gae_scan<false, true, A> : k_gae_scan<false, false, A>);
+  };
+  void (*kernel)(ScanParams, float*, float*) = alone ? pick(std::true_type()) : pick(std::false_type());
   hipLaunchKernelGGL(kernel, dim3(P.n_ranges), dim3(kThreads), 0, st, P, adv, ret);
   UMAS_LAUNCHED("k_gae_scan");
-  if (n_tokens - P.chunk < kLongSegment) return UMAS_OK;   // no segment reaches far enough past a range's edge to be cut
+  if (alone) return UMAS_OK;
   // The ranges cut inside long segments: persistent workgroups that wait for each other's maps.  At most one workgroup
   // per compute unit, far fewer than the device holds at once: whatever else is running, all of them get to run
   // together, so no workgroup waits for one that cannot start.
