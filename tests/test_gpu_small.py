@@ -7,6 +7,7 @@ import torch
 
 import workloads as wl
 import paper_2605_26646_amd as umas
+from oracle import umas_oracle as orc
 from tests import arraywise as aw
 from tests import parity as P
 from tests.test_gpu_large import check_front_arraywise, check_ready_batch_arraywise
@@ -75,3 +76,34 @@ def test_ready_batch_around_the_limits_of_one_launch(n_tokens, n_turns, n_traj, 
         rows, off = umas.umas_ready_batch(s, w.traj_turn_off, 3)
         want_rows, want_off = aw.ready_batch(w, sa, np.ones(n_traj, np.uint8), np.arange(n_traj, dtype=np.int32), 3, False)
         assert np.array_equal(off.cpu().numpy(), want_off) and np.array_equal(rows.cpu().numpy()[:len(want_rows)], want_rows)
+
+
+@pytest.mark.parametrize("n_tokens,n_turns,n_traj", [(1, 1, 1), (16385, 1, 1), (18000, 2, 1), (65536, 1, 1), (65535, 3, 2), (65537, 3, 2), (50001, 40, 2)])
+@pytest.mark.parametrize("seg_mode,gamma,lam,gamma_turn,values", [
+    (wl.SEG_TURN, 1.0, 1.0, 1.0, False), (wl.SEG_TURN, 0.99, 0.95, 1.0, True), (wl.SEG_TRAJ, 1.0, 0.9, 0.9, False), (wl.SEG_TRAJ, 0.99, 0.95, 0.9, True)])
+def test_scan_of_few_tokens_in_long_segments(n_tokens, n_turns, n_traj, seg_mode, gamma, lam, gamma_turn, values):
+    w = sized_graph(n_tokens, n_tokens, n_turns, n_traj, 1, 2, 0)
+    if not values:
+        w.value = None
+    s, adv, ret = P.gpu_front(w, place_mode=wl.PLACE_ALL, seg_mode=seg_mode, gamma=gamma, lam=lam, gamma_turn=gamma_turn)
+    check_front_arraywise(w, s, adv, ret, wl.PLACE_ALL, seg_mode, gamma, lam, gamma_turn)
+
+
+@pytest.mark.parametrize("n", [1, 7, 8192, 8193, 49153, 65536, 65537])
+@pytest.mark.parametrize("density", [0.0, 0.6])
+def test_kl_rewards_of_few_tokens(n, density):
+    rng = np.random.default_rng(n)
+    r = rng.normal(size=n).astype(np.float32)
+    logp = rng.uniform(-3.0, 0.0, n).astype(np.float32)
+    ref = (logp + 0.1 * rng.standard_normal(n)).astype(np.float32)
+    mask = (rng.random(n) < density).astype(np.uint8)
+    want, kl_want = orc.kl_penalised_rewards(r, logp, ref, mask, 0.05)
+    for in_place in (False, True):
+        x = P.to_dev(r)
+        got, kl = umas.umas_kl_rewards(x, P.to_dev(logp), P.to_dev(ref), P.to_dev(mask), 0.05, out=x if in_place else None)
+        got = got.cpu().numpy()
+        assert np.array_equal(got[mask == 0].view(np.uint32), r[mask == 0].view(np.uint32))
+        # r - beta * kl in float32: the product and the difference round once each
+        assert (np.abs(got - want) <= 2.0 ** -23 * (np.abs(r) + 0.05 * np.abs(logp.astype(np.float64) - ref)) + 1e-30).all()
+        # each float32 difference is half a unit in its last place off, their float64 sum is exact to 1e-12
+        assert abs(float(kl.cpu()[0]) - kl_want) <= 2.0 ** -24 * (abs(kl_want) + np.abs(logp.astype(np.float64) - ref).max())
