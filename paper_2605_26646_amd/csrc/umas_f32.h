@@ -7,7 +7,7 @@
 // next 16 in flight; no LDS, no barrier in the loop.  The k of an instruction may be any four as long as both operands
 // agree: lane group l / 16 takes k = 4 (l / 16) .. + 3 of the 16 over four instructions, so that a K-contiguous operand is
 // read 16 bytes a lane.  With one thread per output element and scalar float64 chains dz, dH and dW took 17, 52 and 189 us at
-// 768 rows of 64 against 512, now 14, 12 and 17; a step of 847 rows of 512 against 8192 took 10.1 ms, now 0.88.
+// 768 rows of 64 against 512, now 7 and, the two products together, 12.5; a step of 847 rows of 512 against 8192 took 10.1 ms, now 0.62.
 //
 // Operand layout of a block (lane l): index l % 16, k by lane group l / 16.  Accumulator r of lane l: row 4 r + l / 16 (A
 // side), column l % 16 (B side); checked on the device.
@@ -22,15 +22,16 @@ typedef double double4v __attribute__((ext_vector_type(4)));
 constexpr int kK = 16;                       // k of one round
 constexpr int kTile = 32;                    // a wavefront's tile, both ways
 
-// Operand stored K-contiguous: row i of the tile is a run of K floats.
+// Operands of a tile of NB blocks of 16.  Stored K-contiguous: row i of the tile is a run of K floats.
+template <int NB>
 struct Rows {
-  const float* p[2];                         // the lane's row of each block
+  const float* p[NB];                        // the lane's row of each block
   bool vec;                                  // every row starts at a multiple of 16 bytes and K is a multiple of 4
   __device__ __forceinline__ void ahead(int, int) {}
-  __device__ __forceinline__ void load(int k0, int K, float (&x)[2][4]) const {
+  __device__ __forceinline__ void load(int k0, int K, float (&x)[NB][4]) const {
     const int k = k0 + 4 * ((threadIdx.x & 63) >> 4);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < NB; ++i) {
       if (vec) {
         const float4 v = k < K ? *reinterpret_cast<const float4*>(p[i] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
         x[i][0] = v.x; x[i][1] = v.y; x[i][2] = v.z; x[i][3] = v.w;
@@ -41,9 +42,10 @@ struct Rows {
     }
   }
 };
-// Operand stored K-major: k-row k (row map[k] of the matrix, where there is a map) holds the tile's entries next to each other.
+// Stored K-major: k-row k (row map[k] of the matrix, where there is a map) holds the tile's entries next to each other.
+template <int NB>
 struct Cols {
-  const float* p[2];                         // the lane's entry of each block in k-row 0
+  const float* p[NB];                        // the lane's entry of each block in k-row 0
   int64_t ld;
   const int32_t* map;
   int32_t row[4];                            // k-rows of the next round
@@ -52,51 +54,59 @@ struct Cols {
 #pragma unroll
     for (int s = 0; s < 4; ++s) row[s] = map ? map[k + s < K ? k + s : K - 1] : k + s;
   }
-  __device__ __forceinline__ void load(int k0, int K, float (&x)[2][4]) const {
+  __device__ __forceinline__ void load(int k0, int K, float (&x)[NB][4]) const {
     const int k = k0 + 4 * ((threadIdx.x & 63) >> 4);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
       for (int s = 0; s < 4; ++s) x[i][s] = k + s < K ? p[i][row[s] * ld] : 0.f;
   }
 };
 
-// acc += A[., k] B[., k] over k in [k0, k1), K of them altogether; k0 a multiple of 16
-template <class OA, class OB>
-__device__ __forceinline__ void product(OA& a, OB& b, int k0, int k1, int K, double4v (&acc)[2][2]) {
+// acc += A[., k] B[., k] over k in [k0, k1), K of them altogether; k0 a multiple of 16, k1 too unless it is K.  Loads run D rounds ahead:
+// one for tiles of 32, more registers than that take wavefronts off the unit; three for the tiles of 16 of products that are
+// a few rounds long and nothing but waiting.
+template <int NB> constexpr int kRoundsAhead = NB == 1 ? 3 : 1;
+template <int NB, class OA, class OB>
+__device__ __forceinline__ void product(OA& a, OB& b, int k0, int k1, int K, double4v (&acc)[NB][NB]) {
+  constexpr int D = kRoundsAhead<NB>;
   if (k0 >= k1) return;
-  float xa[2][4], xb[2][4];
-  a.ahead(k0, K);
-  b.ahead(k0, K);
-  a.load(k0, K, xa);
-  b.load(k0, K, xb);
-  a.ahead(k0 + kK, K);
-  b.ahead(k0 + kK, K);
+  float xa[D + 1][NB][4], xb[D + 1][NB][4];
+#pragma unroll
+  for (int t = 0; t < D; ++t) {              // past the end: zeros, no access
+    a.ahead(k0 + t * kK, K);
+    b.ahead(k0 + t * kK, K);
+    a.load(k0 + t * kK, k1, xa[t]);
+    b.load(k0 + t * kK, k1, xb[t]);
+  }
+  a.ahead(k0 + D * kK, K);
+  b.ahead(k0 + D * kK, K);
   for (int k = k0; k < k1; k += kK) {
-    float na[2][4], nb[2][4];
-    a.load(k + kK, K, na);                   // past the end: zeros, no access
-    b.load(k + kK, K, nb);
-    a.ahead(k + 2 * kK, K);
-    b.ahead(k + 2 * kK, K);
+    a.load(k + D * kK, k1, xa[D]);
+    b.load(k + D * kK, k1, xb[D]);
+    a.ahead(k + (D + 1) * kK, K);
+    b.ahead(k + (D + 1) * kK, K);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const double a0 = xa[0][s], a1 = xa[1][s], b0 = xb[0][s], b1 = xb[1][s];
-      acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
-    }
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < NB; ++i)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) { xa[i][s] = na[i][s]; xb[i][s] = nb[i][s]; }
+        for (int j = 0; j < NB; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(xa[0][i][s]), static_cast<double>(xb[0][j][s]), acc[i][j], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < D; ++t)
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) { xa[t][i][s] = xa[t + 1][i][s]; xb[t][i][s] = xb[t + 1][i][s]; }
   }
 }
-__device__ __forceinline__ void zero(double4v (&acc)[2][2]) {
+template <int NB>
+__device__ __forceinline__ void zero(double4v (&acc)[NB][NB]) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = double4v{0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < NB; ++j) acc[i][j] = double4v{0.0, 0.0, 0.0, 0.0};
 }
 __device__ __forceinline__ int blk_index(int i) { return i * 16 + (threadIdx.x & 15); }                       // operand entry / column
 __device__ __forceinline__ int blk_row(int i, int r) { return i * 16 + 4 * r + ((threadIdx.x & 63) >> 4); }   // accumulator row
@@ -151,7 +161,7 @@ k_score_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int
   __shared__ Stat s_stat[kWaves][kTile];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t n0 = static_cast<int64_t>(blockIdx.x) * kTile;
-  Rows h;
+  Rows<2> h;
   h.vec = d % 4 == 0;
   int y[2];
 #pragma unroll
@@ -164,7 +174,7 @@ k_score_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int
   for (int64_t vb = static_cast<int64_t>(blockIdx.y) * kVocBlock; vb < V; vb += static_cast<int64_t>(gridDim.y) * kVocBlock) {
     const int v0 = static_cast<int>(vb) + wave * kTile;
     if (v0 >= V) continue;
-    Rows w;
+    Rows<2> w;
     w.vec = h.vec;
 #pragma unroll
     for (int i = 0; i < 2; ++i) w.p[i] = W + static_cast<int64_t>(min(v0 + blk_index(i), V - 1)) * d;
@@ -279,7 +289,7 @@ k_dz_f32(const float* __restrict__ W, const float* __restrict__ H, int d, int V,
   const int64_t n0 = static_cast<int64_t>(blockIdx.y) * kTile, vb = static_cast<int64_t>(blockIdx.x) * kVocBlock + wave * kTile;
   if (vb >= V) return;
   const int v0 = static_cast<int>(vb);
-  Rows h, w;
+  Rows<2> h, w;
   h.vec = w.vec = d % 4 == 0;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -324,88 +334,107 @@ k_dz_kept_f32(const double* __restrict__ z, int V, const int32_t* __restrict__ r
   }
 }
 
-// The two gradient products.  A workgroup of eight wavefronts takes WM x WN tiles of 32 x 32 and 8 / (WM WN) parts of K,
-// whose sums meet in LDS in a fixed order.  <1, 1> spreads small products over the chip (dW of 512 x 64: 32 workgroups),
-// <2, 2> reads half as much from L2 (see large_product).
+// The two gradient products, in one launch: neither needs the other, and each alone leaves compute units idle at its end (small ones
+// all the time).  A workgroup of eight wavefronts takes WM x WN tiles of NB x NB blocks and 8 / (WM WN) parts of K, whose sums meet in
+// LDS in a fixed order: 16 x 16 (SIZE 0) for products that are few tiles altogether, 32 x 32 (1), and 64 x 64 (2), which reads half as
+// much from L2 (see gradient_sizes).
 constexpr int kGradWaves = 8, kGradT = kGradWaves * kWave;
-template <int WM, int WN, class OA, class OB, class F>
-__device__ __forceinline__ void gradient_tile(OA& a, OB& b, int K, F store) {
-  constexpr int WK = kGradWaves / (WM * WN);
-  __shared__ double s_acc[kGradWaves / 2][16][kWave];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, part = wave / (WM * WN);
+constexpr int grad_side(int size) { return 16 << size; }
+template <int SIZE>
+struct GradTile {
+  static constexpr int NB = SIZE == 0 ? 1 : 2, W = SIZE == 2 ? 2 : 1;   // blocks of a wavefront and wavefronts, both ways
+  static constexpr int kPerWave = NB * NB * 4;                         // accumulators of a lane
+  static constexpr int kSums = kGradWaves / 2 * kPerWave * kWave;
+};
+template <int SIZE, class OA, class OB, class F>
+__device__ __forceinline__ void gradient_tile(OA& a, OB& b, int K, double* s_acc, F store) {
+  using T = GradTile<SIZE>;
+  constexpr int WMN = T::W * T::W, WK = kGradWaves / WMN, NB = T::NB;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, part = wave / WMN;
   const int per = ((K + kK - 1) / kK + WK - 1) / WK * kK;            // k of one part
-  double4v acc[2][2];
-  zero(acc);
-  product(a, b, min(part * per, K), min((part + 1) * per, K), K, acc);
+  double4v acc[NB][NB];
+  zero<NB>(acc);
+  product<NB>(a, b, min(part * per, K), min((part + 1) * per, K), K, acc);
 #pragma unroll
   for (int o = WK / 2; o > 0; o >>= 1) {                             // parts o .. 2 o - 1 hand their sums to parts 0 .. o - 1
-    const int slot = wave % (o * WM * WN);
+    double* const slot = s_acc + static_cast<size_t>(wave % (o * WMN)) * (T::kPerWave * kWave) + lane;
     if (part >= o && part < 2 * o)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) s_acc[slot][q][lane] = acc[q >> 3][(q >> 2) & 1][q & 3];
+      for (int q = 0; q < T::kPerWave; ++q) slot[q * kWave] = acc[q / (4 * NB)][q / 4 % NB][q % 4];
     __syncthreads();
     if (part < o)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) acc[q >> 3][(q >> 2) & 1][q & 3] += s_acc[slot][q][lane];
+      for (int q = 0; q < T::kPerWave; ++q) acc[q / (4 * NB)][q / 4 % NB][q % 4] += slot[q * kWave];
     __syncthreads();
   }
   if (part != 0) return;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) store(blk_row(i, r), blk_index(j), acc[i][j][r]);
 }
+struct GradArgs {
+  const float *dz, *W, *H;                   // dz: [rows][V], of the chunk
+  int d, V;
+  const int32_t* rowsel;
+  int64_t c0;
+  int rows, accumulate;
+  float *dH, *dW;
+  int n_dh, n_dw, dw_first;                  // tiles; the longer ones go first
+};
 // dH[row(n), j] = sum_v dz[n, v] W[v, j]
-template <int WM, int WN>
-__global__ void __launch_bounds__(kGradT)
-k_dh_f32(const float* __restrict__ dz, const float* __restrict__ W, int d, int V, const int32_t* __restrict__ rowsel, int64_t c0,
-         int64_t rows, float* __restrict__ dH) {
-  const int wave = threadIdx.x >> 6;
-  const int64_t n0 = (static_cast<int64_t>(blockIdx.x) * WM + wave / WN % WM) * kTile;
-  const int j0 = (static_cast<int>(blockIdx.y) * WN + wave % WN) * kTile;
-  Rows a;
-  a.vec = V % 4 == 0;
-  Cols b;
-  b.ld = d;
+template <int SIZE>
+__device__ __forceinline__ void dh_tile(const GradArgs& A, int tile, double* s_acc) {
+  using T = GradTile<SIZE>;
+  const int wave = threadIdx.x >> 6, side = grad_side(SIZE), gx = (A.rows + side - 1) / side;
+  const int n0 = tile % gx * side + wave / T::W % T::W * (T::NB * 16), j0 = tile / gx * side + wave % T::W * (T::NB * 16);
+  Rows<T::NB> a;
+  a.vec = A.V % 4 == 0;
+  Cols<T::NB> b;
+  b.ld = A.d;
   b.map = nullptr;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    a.p[i] = dz + min(n0 + blk_index(i), rows - 1) * V;
-    b.p[i] = W + min(j0 + blk_index(i), d - 1);
+  for (int i = 0; i < T::NB; ++i) {
+    a.p[i] = A.dz + static_cast<int64_t>(min(n0 + blk_index(i), A.rows - 1)) * A.V;
+    b.p[i] = A.W + min(j0 + blk_index(i), A.d - 1);
   }
-  gradient_tile<WM, WN>(a, b, V, [&](int r, int c, double x) {
-    const int64_t m = n0 + r;
-    const int j = j0 + c;
-    if (m < rows && j < d) dH[(rowsel ? rowsel[c0 + m] : c0 + m) * d + j] = static_cast<float>(x);
+  gradient_tile<SIZE>(a, b, A.V, s_acc, [&](int r, int c, double x) {
+    const int m = n0 + r, j = j0 + c;
+    if (m < A.rows && j < A.d) A.dH[(A.rowsel ? A.rowsel[A.c0 + m] : A.c0 + m) * A.d + j] = static_cast<float>(x);
   });
 }
 // dW[v, j] (+)= sum_n dz[n, v] H[row(n), j]
-template <int WM, int WN>
-__global__ void __launch_bounds__(kGradT)
-k_dw_f32(const float* __restrict__ dz, const float* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel, int64_t c0,
-         int64_t rows, int accumulate, float* __restrict__ dW) {
-  const int wave = threadIdx.x >> 6;
-  const int64_t v0 = (static_cast<int64_t>(blockIdx.x) * WM + wave / WN % WM) * kTile;
-  const int j0 = (static_cast<int>(blockIdx.y) * WN + wave % WN) * kTile;
-  Cols a, b;
-  a.ld = V;
+template <int SIZE>
+__device__ __forceinline__ void dw_tile(const GradArgs& A, int tile, double* s_acc) {
+  using T = GradTile<SIZE>;
+  const int wave = threadIdx.x >> 6, side = grad_side(SIZE), gx = (A.V + side - 1) / side;
+  const int v0 = tile % gx * side + wave / T::W % T::W * (T::NB * 16), j0 = tile / gx * side + wave % T::W * (T::NB * 16);
+  Cols<T::NB> a, b;
+  a.ld = A.V;
   a.map = nullptr;
-  b.ld = d;
-  b.map = rowsel ? rowsel + c0 : nullptr;
+  b.ld = A.d;
+  b.map = A.rowsel ? A.rowsel + A.c0 : nullptr;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    a.p[i] = dz + min(v0 + blk_index(i), static_cast<int64_t>(V) - 1);
-    b.p[i] = (rowsel ? H : H + c0 * d) + min(j0 + blk_index(i), d - 1);
+  for (int i = 0; i < T::NB; ++i) {
+    a.p[i] = A.dz + min(v0 + blk_index(i), A.V - 1);
+    b.p[i] = (A.rowsel ? A.H : A.H + A.c0 * A.d) + min(j0 + blk_index(i), A.d - 1);
   }
-  gradient_tile<WM, WN>(a, b, static_cast<int>(rows), [&](int r, int c, double x) {
-    const int64_t v = v0 + r;
-    const int j = j0 + c;
-    if (v >= V || j >= d) return;
-    float* dst = dW + v * d + j;
-    *dst = accumulate ? static_cast<float>(static_cast<double>(*dst) + x) : static_cast<float>(x);
+  gradient_tile<SIZE>(a, b, A.rows, s_acc, [&](int r, int c, double x) {
+    const int v = v0 + r, j = j0 + c;
+    if (v >= A.V || j >= A.d) return;
+    float* dst = A.dW + static_cast<int64_t>(v) * A.d + j;
+    *dst = A.accumulate ? static_cast<float>(static_cast<double>(*dst) + x) : static_cast<float>(x);
   });
+}
+template <int DH, int DW>
+__global__ void __launch_bounds__(kGradT)
+k_gradients_f32(GradArgs A) {
+  __shared__ double s_acc[GradTile<DH>::kSums > GradTile<DW>::kSums ? GradTile<DH>::kSums : GradTile<DW>::kSums];
+  const int i = blockIdx.x, n_first = A.dw_first ? A.n_dw : A.n_dh;
+  if ((i < n_first) != (A.dw_first != 0)) dh_tile<DH>(A, i < n_first ? i : i - n_first, s_acc);
+  else dw_tile<DW>(A, i < n_first ? i : i - n_first, s_acc);
 }
 
 // ------------------------------------------------------------------ launches
@@ -456,13 +485,40 @@ inline umas_status score(const float* W, const float* H, int d, int V, const int
   }
   return UMAS_OK;
 }
-// <2, 2> where its tiles fill whole rounds of 256 compute units, or nearly: it takes as long as the rounds, <1, 1> a tenth longer than
-// the tiles would in full ones (dW of 4000 x 300, 315 tiles: 257 us in <2, 2>, 184 in <1, 1>; 5001 x 451, 632: 221 and 202; 8192
+// 64 x 64 where its tiles fill whole rounds of 256 compute units, or nearly: it takes as long as the rounds, 32 x 32 a tenth longer than
+// the tiles would in full ones (dW of 4000 x 300, 315 tiles: 257 us in 64 x 64, 184 in 32 x 32; 5001 x 451, 632: 221 and 202; 8192
 // x 512, 1024: 164 and 179).  Nearly one round is no case for them: a single workgroup to a compute unit (dW of 15 000 x 64, 235 tiles, 2000 rows
-// 166 in <2, 2>, 125 in <1, 1>, 4000 rows 338 and 235; 8000 x 120, 250: 153 and 124; 7600 x 128, 238: 87 and 70).
+// 166 in 64 x 64, 125 in 32 x 32, 4000 rows 338 and 235; 8000 x 120, 250: 153 and 124; 7600 x 128, 238: 87 and 70).
 inline bool large_product(int64_t m, int64_t n) {
-  const int64_t tiles = cdiv(m, 2 * kTile) * static_cast<int64_t>(cdiv(n, 2 * kTile));
+  const int64_t tiles = cdiv(m, 64) * static_cast<int64_t>(cdiv(n, 64));
   return tiles >= 256 && (tiles + 255) / 256 * 256 * 10 <= tiles * 11;
+}
+// 16 x 16 where the product's tiles of 32 x 32 are fewer than every second compute unit, or those of both together one each: then a
+// launch lasts as long as one tile, and that is a quarter as many instructions a round.  Both products, in two launches of 32 x 32 and
+// in one: 768 rows of 64 against 512 33 -> 12.5 us, 1500 of 64 against 2000 74 -> 38.5, 100 of 512
+// against 8000 153 -> 66 (122 with dH in 32 x 32), 6000 of 128 against 512 88 -> 43.5 (69 with dW in 32 x 32).
+constexpr int kSmallGradTiles = 256;
+inline void launch_gradients(GradArgs A, hipStream_t st) {
+  auto tiles = [](int64_t m, int64_t n, int size) { return static_cast<int>(cdiv(m, grad_side(size)) * cdiv(n, grad_side(size))); };
+  const int dh1 = tiles(A.rows, A.d, 1), dw1 = tiles(A.V, A.d, 1);
+  const bool small = dh1 + dw1 <= kSmallGradTiles;
+  auto size = [&](int64_t m, int tiles1) { return small || tiles1 <= kSmallGradTiles / 2 ? 0 : large_product(m, A.d) ? 2 : 1; };
+  const int dh = size(A.rows, dh1), dw = size(A.V, dw1);
+  A.n_dh = tiles(A.rows, A.d, dh);
+  A.n_dw = tiles(A.V, A.d, dw);
+  A.dw_first = A.rows > A.V ? 1 : 0;
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(A.n_dh + A.n_dw)), dim3(kGradT), 0, st, A); };
+  switch (3 * dh + dw) {
+    case 0: return launch(k_gradients_f32<0, 0>);
+    case 1: return launch(k_gradients_f32<0, 1>);
+    case 2: return launch(k_gradients_f32<0, 2>);
+    case 3: return launch(k_gradients_f32<1, 0>);
+    case 4: return launch(k_gradients_f32<1, 1>);
+    case 5: return launch(k_gradients_f32<1, 2>);
+    case 6: return launch(k_gradients_f32<2, 0>);
+    case 7: return launch(k_gradients_f32<2, 1>);
+    default: return launch(k_gradients_f32<2, 2>);
+  }
 }
 
 }  // namespace f32

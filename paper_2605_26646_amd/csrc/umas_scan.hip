@@ -26,7 +26,7 @@
 // (one per compute unit at most, a fraction of what the device holds at once, so all of them run together): a range
 // only ever waits for maps of ranges to its right, written by the first kernel or by a workgroup that is running,
 // and publishing a map waits for nothing, so every wait ends.  When no segment is that long the second kernel finds
-// nothing to do and leaves at once.
+// nothing to do and leaves at once.  Few tokens (kAloneTokens) are done without it.
 #include <type_traits>
 
 #include "umas_common.h"

@@ -2066,18 +2066,9 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
         hipLaunchKernelGGL(f32::k_dz_f32, dim3(cdiv(V, f32::kVocBlock), cdiv(rows, f32::kTile)), dim3(f32::kWaves * kWave), 0, st, Wf, Hf, d, V,
                            rowsel, c0, rows, ids, w.score.lse_c, w.rest, w.g_c, w.score.ent_c, w.kz_c, dz);
       UMAS_LAUNCHED(z_kept ? "k_dz_kept_f32" : "k_dz_f32");
-      auto grid = [](int64_t m, int64_t n, int tiles) { return dim3(cdiv(m, tiles * f32::kTile), cdiv(n, tiles * f32::kTile)); };
-      if (f32::large_product(rows, d))
-        hipLaunchKernelGGL((f32::k_dh_f32<2, 2>), grid(rows, d, 2), dim3(f32::kGradT), 0, st, dz, Wf, d, V, rowsel, c0, rows, static_cast<float*>(dH));
-      else
-        hipLaunchKernelGGL((f32::k_dh_f32<1, 1>), grid(rows, d, 1), dim3(f32::kGradT), 0, st, dz, Wf, d, V, rowsel, c0, rows, static_cast<float*>(dH));
-      UMAS_LAUNCHED("k_dh_f32");
-      const int acc_dW = accumulate_dW || c0 > 0 ? 1 : 0;
-      if (f32::large_product(V, d))
-        hipLaunchKernelGGL((f32::k_dw_f32<2, 2>), grid(V, d, 2), dim3(f32::kGradT), 0, st, dz, Hf, d, V, rowsel, c0, rows, acc_dW, dW);
-      else
-        hipLaunchKernelGGL((f32::k_dw_f32<1, 1>), grid(V, d, 1), dim3(f32::kGradT), 0, st, dz, Hf, d, V, rowsel, c0, rows, acc_dW, dW);
-      UMAS_LAUNCHED("k_dw_f32");
+      f32::launch_gradients(f32::GradArgs{dz, Wf, Hf, d, V, rowsel, c0, static_cast<int>(rows), accumulate_dW || c0 > 0 ? 1 : 0,
+                                          static_cast<float*>(dH), dW, 0, 0, 0}, st);
+      UMAS_LAUNCHED("k_dw_f32");                         // both products: one launch to a chunk
     }
     return UMAS_OK;
   }

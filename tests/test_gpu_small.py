@@ -107,3 +107,40 @@ def test_kl_rewards_of_few_tokens(n, density):
         assert (np.abs(got - want) <= 2.0 ** -23 * (np.abs(r) + 0.05 * np.abs(logp.astype(np.float64) - ref)) + 1e-30).all()
         # each float32 difference is half a unit in its last place off, their float64 sum is exact to 1e-12
         assert abs(float(kl.cpu()[0]) - kl_want) <= 2.0 ** -24 * (abs(kl_want) + np.abs(logp.astype(np.float64) - ref).max())
+
+
+@pytest.mark.parametrize("rows,d,V", [  # every pair of tile sizes of the two float32 gradient products, 16, 32 and 64 wide
+    (1, 1, 1), (60, 33, 100), (255, 64, 512), (1030, 127, 1001), (100, 100, 3000), (100, 512, 8000), (3000, 100, 101), (300, 500, 300),
+    (300, 512, 8190), (4001, 512, 60), (4000, 511, 401), (4096, 512, 2100)])
+@pytest.mark.parametrize("select", [False, True])
+def test_float32_gradient_products_in_every_tile_size(rows, d, V, select):
+    g = torch.Generator(device="cuda").manual_seed(rows + V)
+    n = rows + 9 if select else rows
+    H, W = torch.randn(n, d, device="cuda", generator=g), torch.randn(V, d, device="cuda", generator=g) / d ** 0.5
+    ids = torch.randint(0, V, (n,), device="cuda", dtype=torch.int32, generator=g)
+    adv = torch.randn(n, device="cuda", generator=g)
+    sel = torch.randperm(n, device="cuda", generator=g)[:rows].to(torch.int32) if select else None
+    dW0 = torch.randn(V, d, device="cuda", generator=g)
+    _, logp, dH, dW = umas.umas_ppo_loss_fwd_bwd(H, W, ids, sel, None, adv, None, 0, 0.2, accumulate_dW=True, dW=dW0.clone())
+    # the same in float64, on-policy: dz = (A / n) (softmax - onehot)
+    at = torch.arange(n, device="cuda") if sel is None else sel.long()
+    h, w, y = H[at].double(), W.double(), ids[at].long()
+    z = h @ w.T
+    lp = torch.log_softmax(z, 1)
+    dz = torch.exp(lp)
+    dz[torch.arange(rows, device="cuda"), y] -= 1.0
+    dz *= (adv[at].double() / rows)[:, None]
+    want_H, want_lp = torch.zeros(n, d, dtype=torch.float64, device="cuda"), torch.zeros(n, dtype=torch.float64, device="cuda")
+    want_H[at], want_lp[at] = dz @ w, lp.gather(1, y[:, None])[:, 0]
+    want_W = dW0.double() + dz.T @ h
+    # float32 dz and results round once each, the sums are float64: 2^-24 of the terms' magnitudes and of the result, twice that for what comes
+    # of the float32 logsumexp and g (a difference in the logsumexp's last place scales every probability of the row)
+    lse = torch.logsumexp(z, 1).abs()
+    mag = dz.abs() * (4.0 + 4.0 * lse[:, None]) * 2.0 ** -24
+    for got, want, bound in ((dH[at], want_H[at], mag @ w.abs()), (dW, want_W, mag.T @ h.abs())):
+        assert ((got.double() - want).abs() <= bound + 2.0 ** -23 * want.abs() + 1e-30).all()
+    assert (logp.double() - want_lp).abs().max() <= 1e-5 * max(1.0, float(want_lp.abs().max()))
+    if select:
+        rest = torch.ones(n, dtype=torch.bool, device="cuda")
+        rest[at] = False
+        assert (dH[rest] == 0).all() and (logp[rest] == 0).all()
