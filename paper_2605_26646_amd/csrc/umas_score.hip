@@ -25,6 +25,7 @@
 #include "umas_common.h"
 #include "umas_f32.h"
 #include "umas_mfma.h"
+#include "umas_surrogate.h"
 
 namespace umas {
 namespace {
@@ -62,18 +63,8 @@ __device__ __forceinline__ Part part_merge(Part x, Part y) {
 }
 
 // ------------------------------------------------------------------ small helpers
-// What a call defines on rows that are not selected, cleared in one launch (scoring through a selection, a launch for each array
-// and in one: 20 rows of 2048 121.9 and 119.0 us, 3 rows of 1024 against 30 001 24.3 and 21.3).
-struct ClearArgs {
-  uint32_t* p[3];        // NULL: nothing
-  int64_t words[3];
-};
 __global__ void __launch_bounds__(256) k_clear(ClearArgs A) {
-  const int64_t i0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x, stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-    if (A.p[k])
-      for (int64_t i = i0; i < A.words[k]; i += stride) A.p[k][i] = 0u;
+  clear_words(A, static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x, static_cast<int64_t>(gridDim.x) * blockDim.x);
 }
 
 // bytes are a multiple of 4 for every buffer cleared here
@@ -560,64 +551,37 @@ k_score_finalize(const float4* __restrict__ partial, int tiles_m, int64_t n_pad,
 }
 
 // ------------------------------------------------------------------ clipped surrogate
-// Per selected row: loss term (single clip, or dual clip when dual_clip > 1) and g = dloss/dlogp of the
-// clipped part; per block sums of (L, clipped, entropy,
-// logp_old - logp, rows, invalid ids) for the model and for each role, in float64.
-constexpr int kStat = 6;
+// Per selected row its surrogate, and what the backward needs of it; per block of rows the sums of the statistics for the model and for
+// each role.
 __global__ void __launch_bounds__(kRowBlock)
-k_ppo_rows(int64_t norm, int64_t n_begin, int64_t n_end, const int32_t* __restrict__ rowsel, const int32_t* __restrict__ ids, int V,
-           const float* __restrict__ logp_c, const float* __restrict__ ent_c, const float* __restrict__ logp_old,
-           const float* __restrict__ adv, const int32_t* __restrict__ tok_role, int n_roles, float clip_eps,
-           float dual_clip, float k_ent, const float* __restrict__ logp_ref, float kl_coef, int label_apart,
-           const float* __restrict__ lse_c, float* __restrict__ g_c,
+k_ppo_rows(Surrogate S, int64_t n_begin, int64_t n_end, const float* __restrict__ logp_c, const float* __restrict__ ent_c,
+           float k_ent, int label_apart, const float* __restrict__ lse_c, float* __restrict__ g_c,
            float* __restrict__ a_c, float* __restrict__ kz_c, double* __restrict__ blk_stats) {
   extern __shared__ double s_acc[];   // [wavefronts][(1+n_roles) * kStat]
-  const int nacc = (1 + n_roles) * kStat;
+  const int n_roles = S.n_roles, nacc = (1 + n_roles) * kStat;
   const int lane = threadIdx.x & (kWave - 1);
   double* const w_acc = s_acc + threadIdx.x / kWave * nacc;
   for (int i = lane; i < nacc; i += kWave) w_acc[i] = 0.0;
   __builtin_amdgcn_wave_barrier();
-  float L = 0.f, clipped = 0.f, en = 0.f, kl = 0.f;
-  int role = -1, valid = 0;
+  SurrogateRow R{0.f, 0.f, 0.f, 0.f, 0.f, -1, false};
   const int64_t n = n_begin + static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;   // n_begin is a multiple of the block size
   if (n < n_end) {
-    const int64_t row = rowsel ? rowsel[n] : n;
-    const int y = ids[row];
-    const bool ok = y >= 0 && y < V;
-    float g = 0.f, lp = 0.f;
-    valid = ok;
-    if (ok) {
-      lp = logp_c[n];
-      const float lo = logp_old ? logp_old[row] : lp, A = adv[row];   // no old log-probs: the update is on-policy, ratio 1
-      const float ratio = __expf(lp - lo);
-      const float u = -A * ratio;
-      const float c = -A * fminf(fmaxf(ratio, 1.f - clip_eps), 1.f + clip_eps);
-      bool unclipped = u >= c;
-      L = unclipped ? u : c;
-      if (dual_clip > 0.f && A < 0.f && -A * dual_clip < L) {   // dual clip: the term of a negative advantage is capped
-        L = -A * dual_clip;
-        unclipped = false;
-      }
-      g = unclipped ? u / static_cast<float>(norm) : 0.f;
-      clipped = unclipped ? 0.f : 1.f;
-      if (kl_coef != 0.f) {   // penalty towards the reference policy: kl_coef (e^x - x - 1), x = logp_ref - logp
-        const float x = logp_ref[row] - lp, ex = __expf(x);
-        L += kl_coef * (ex - x - 1.f);
-        g += kl_coef * (1.f - ex) / static_cast<float>(norm);
-      }
-      en = ent_c[n];
-      kl = lo - lp;
-    }
+    const int64_t row = S.rowsel ? S.rowsel[n] : n;
+    const int y = S.ids[row];
+    const bool ok = y >= 0 && y < S.V;
+    const float lp = ok ? logp_c[n] : 0.f, en = ok ? ent_c[n] : 0.f;
+    R = surrogate_row(S, row, ok, lp, en);
     // With label_apart the taken token's column is left out of the dense (bf16) part of dz and g_c carries all of
     // dz[n, y] = g (1 - p_y) + k_ent p_y (log p_y + entropy) in float32: for a confident token g and g p_y nearly
     // cancel, and the rounding of a bf16 g p_y would be as large as what is left.
-    g_c[n] = label_apart && ok ? fmaf(g, -expm1f(lp), k_ent * __expf(lp) * (lp + en)) : g;
+    g_c[n] = label_apart && ok ? fmaf(R.g, -expm1f(lp), k_ent * __expf(lp) * (lp + en)) : R.g;
     // coefficients of the backward's dense part dz = p (a + kz z): -g from the surrogate, the rest from the
     // entropy bonus k_ent p (log p + entropy); a row with an invalid id has neither
-    a_c[n] = ok ? -g + k_ent * (en - lse_c[n]) : 0.f;
+    a_c[n] = ok ? -R.g + k_ent * (en - lse_c[n]) : 0.f;
     kz_c[n] = ok ? k_ent : 0.f;
-    role = (tok_role && n_roles > 0) ? tok_role[row] : -1;
   }
+  const float L = R.L, clipped = R.clipped, en = R.en, kl = R.kl;
+  const int role = R.role, valid = R.valid;
   // Sums over the wavefront's rows, the model's and then each role's that occurs among them (usually one or two); the
   // wavefronts' sums are added in a fixed order.  (256 threads adding to six float64 words by atomics took 18 us.)
   const unsigned long long in = __ballot(n < n_end);
@@ -658,17 +622,7 @@ k_ppo_stats(int nblk, int n_roles, float entropy_coef, int64_t norm_rows, const 
 #pragma unroll
   for (int j = 0; j < kStat; ++j) sum[j] = block_sum<double>(v[j], smem);
   if (threadIdx.x != 0) return;
-  const double cnt = sum[4];
-  umas_loss_stats s;
-  // the model's loss over the caller's normaliser when one is given: micro-batch losses then add up
-  const double den = (k == 0 && norm_rows > 0) ? static_cast<double>(norm_rows) : cnt;
-  s.loss = cnt > 0 ? static_cast<float>((sum[0] - static_cast<double>(entropy_coef) * sum[2]) / den) : 0.f;
-  s.clip_frac = cnt > 0 ? static_cast<float>(sum[1] / cnt) : 0.f;
-  s.entropy_mean = cnt > 0 ? static_cast<float>(sum[2] / cnt) : 0.f;
-  s.approx_kl = cnt > 0 ? static_cast<float>(sum[3] / cnt) : 0.f;
-  s.n_scored = static_cast<int64_t>(cnt);
-  s.n_invalid_ids = static_cast<int64_t>(sum[5]);
-  stats[k] = s;
+  stats[k] = loss_stats(sum, k, entropy_coef, norm_rows);
 }
 
 // ------------------------------------------------------------------ bf16: blocks of rows that have a gradient
@@ -1546,6 +1500,12 @@ size_t f32_logit_bytes(int64_t n_sel, int d, int V) {
   const double b = static_cast<double>(n_sel) * V * sizeof(double), most = d < 32 ? 33554432.0 : d < 64 ? 134217728.0 : 1073741824.0;
   return b <= most ? align_up(static_cast<size_t>(n_sel) * V * sizeof(double)) : 0;
 }
+// ... and, behind them, the statistics of parts of the rows that the update in few launches merges where it makes dz (one chunk of rows).
+size_t f32_part_bytes(int64_t n_sel, int V) { return align_up(static_cast<size_t>(f32::part_plan(n_sel, V).splits) * n_sel * sizeof(f32::Stat)); }
+bool f32_few_launches(int64_t n_sel, int d, int V, size_t room) {
+  const size_t z = n_sel <= kF32ChunkRows ? f32_logit_bytes(n_sel, d, V) : 0;
+  return z > 0 && chunk_bytes(n_sel, d, V, UMAS_F32) + z + f32_part_bytes(n_sel, V) <= room;
+}
 // How the dH product of a chunk is cut along the vocabulary.  dH has tiles_r x tiles_d tiles of the whole vocabulary's K
 // each; with few row tiles that is fewer long tiles than compute units, and the launch lasts as long as one of them (3.6 ms
 // at V = 151 936 whether there are 64 rows or 2000).  Below kDhSliceTiles, one tile per compute unit, they are cut into about
@@ -1868,7 +1828,10 @@ size_t full_ppo_bytes(int64_t n_sel, int d, int V, umas_dtype dtype, int n_roles
     mc = round_up((mc + nchunk - 1) / nchunk, 256);
   }
   size_t chunk = chunk_bytes(mc, d, V, dtype);
-  if (dtype == UMAS_F32) return c.off + chunk + f32_logit_bytes(n_sel, d, V);       // kept with any coefficient
+  if (dtype == UMAS_F32) {                                                           // kept with any coefficient
+    const size_t z = f32_logit_bytes(n_sel, d, V);
+    return c.off + chunk + z + (z > 0 && n_sel <= kF32ChunkRows ? f32_part_bytes(n_sel, V) : 0);
+  }
   const size_t parts = full_part_bytes(n_sel, mc, d, V);
   if (bonus) {
     // the logits of the whole selection, of half a chunk where they are many; no room that the call would not keep logits in
@@ -1918,6 +1881,18 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
   PpoWs w;
   carve_ppo(c, w, n_sel, d, V, dtype, n_roles);
 
+  if (dtype == UMAS_F32 && n_sel > 0 && f32_few_launches(n_sel, d, V, workspace_bytes - w.fixed_bytes)) {
+    const int64_t norm = norm_rows > 0 ? norm_rows : n_sel;
+    float* const dz = reinterpret_cast<float*>(w.chunk);
+    const size_t z_at = chunk_bytes(n_sel, d, V, dtype), parts_at = z_at + f32_logit_bytes(n_sel, d, V);
+    const f32::UpdateArgs U{static_cast<const float*>(W), static_cast<const float*>(H), d, n_sel, n_rows,
+                            Surrogate{norm, rowsel, ids, V, logp_old, adv, tok_role, n_roles, clip_eps, dual_clip, logp_ref, kl_coef},
+                            entropy_coef / static_cast<float>(norm), entropy_coef, norm_rows, w.score.logp_c, w.score.ent_c, logp_new,
+                            reinterpret_cast<double*>(w.chunk + z_at), reinterpret_cast<f32::Stat*>(w.chunk + parts_at), dz,
+                            static_cast<float*>(dH), dW, accumulate_dW ? 1 : 0, stats};
+    return f32::update(U, st);
+  }
+
   // Without an entropy bonus dz is a row factor times the softmax: the scoring pass keeps the numerators
   // and the logits are not computed a second time.
   const bool keep = dtype == UMAS_BF16 && entropy_coef == 0.f && n_sel > 0;
@@ -1947,6 +1922,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
   const size_t kPpoLds = (kRowBlock / kWave) * (1 + n_roles) * kStat * sizeof(double);
   const int64_t norm = norm_rows > 0 ? norm_rows : n_sel;   // rows the token mean is taken over
   const float k_ent = norm > 0 ? entropy_coef / static_cast<float>(norm) : 0.f;
+  const Surrogate S{norm, rowsel, ids, V, logp_old, adv, tok_role, n_roles, clip_eps, dual_clip, logp_ref, kl_coef};
   const int64_t Vp = round_up(V, 256);
   const uint16_t* Wb = static_cast<const uint16_t*>(W);
   const uint16_t* Hb = static_cast<const uint16_t*>(H);
@@ -1980,9 +1956,8 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
   const int64_t mc_z = dtype == UMAS_BF16 && !keep && n_sel > 0 ? logit_chunk_rows(n_sel, d, V, room) : 0;
   if (mc_z > 0) mc = mc_z;
   auto ppo_rows = [&](int64_t c0, int64_t c1) -> umas_status {
-    hipLaunchKernelGGL(k_ppo_rows, dim3(std::max(cdiv(c1 - c0, kRowBlock), 1u)), dim3(kRowBlock), kPpoLds, st, norm, c0, c1, rowsel, ids, V,
-                       w.score.logp_c, w.score.ent_c, logp_old, adv, tok_role, n_roles, clip_eps, dual_clip, k_ent, logp_ref, kl_coef,
-                       dtype == UMAS_BF16 ? 1 : 0, w.score.lse_c, w.g_c, w.a_c, w.kz_c, w.blk_stats);
+    hipLaunchKernelGGL(k_ppo_rows, dim3(std::max(cdiv(c1 - c0, kRowBlock), 1u)), dim3(kRowBlock), kPpoLds, st, S, c0, c1, w.score.logp_c,
+                       w.score.ent_c, k_ent, dtype == UMAS_BF16 ? 1 : 0, w.score.lse_c, w.g_c, w.a_c, w.kz_c, w.blk_stats);
     UMAS_LAUNCHED("k_ppo_rows");
     return UMAS_OK;
   };
@@ -2067,7 +2042,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
                            rowsel, c0, rows, ids, w.score.lse_c, w.rest, w.g_c, w.score.ent_c, w.kz_c, dz);
       UMAS_LAUNCHED(z_kept ? "k_dz_kept_f32" : "k_dz_f32");
       f32::launch_gradients(f32::GradArgs{dz, Wf, Hf, d, V, rowsel, c0, static_cast<int>(rows), accumulate_dW || c0 > 0 ? 1 : 0,
-                                          static_cast<float*>(dH), dW, 0, 0, 0}, st);
+                                          static_cast<float*>(dH), dW, 0, 0, 0}, f32::StatArgs{}, st);
       UMAS_LAUNCHED("k_dw_f32");                         // both products: one launch to a chunk
     }
     return UMAS_OK;
