@@ -71,45 +71,89 @@ __global__ void k_zero_u32(uint32_t* __restrict__ p, int64_t n) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
   for (; i < n; i += stride) p[i] = 0u;
 }
-// Opens the update of a selection, in one launch: value_new[n] (may be NULL) and n16 16-byte words of `big` are cleared.
-__global__ void __launch_bounds__(256)
-k_value_open(uint32_t* __restrict__ value_new, int64_t n, uint4* __restrict__ big, int64_t n16) {
-  const int64_t i0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x, stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t i = i0; i < n16; i += stride) store_stream(big + i, make_uint4(0u, 0u, 0u, 0u));
-  if (value_new)
-    for (int64_t i = i0; i < n; i += stride) value_new[i] = 0u;
-}
-// Large selections: dH is cleared only where the row kernel does not write it.  A byte per row says which rows are selected
-// (in the memory of the partial sums, which come later); clearing all of dH first wrote the selected rows twice (39 224 of
-// 49 030 rows of 2048: 26.6 us, mark and clear together 13.5).
-__global__ void __launch_bounds__(256)
-k_value_mark(const int32_t* __restrict__ rowsel, int64_t n_sel, int64_t n_rows, uint8_t* __restrict__ map) {
-  const int64_t n = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (n >= n_sel) return;
-  const int64_t row = rowsel[n];
-  if (row >= 0 && row < n_rows) map[row] = 1;
-}
-constexpr int kClearRows = 64;             // rows of one workgroup: one ballot of a wavefront
-__global__ void __launch_bounds__(256)
-k_value_clear_rest(const uint8_t* __restrict__ map, int64_t n_rows, int row16, uint4* __restrict__ dH) {
-  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kClearRows;
-  const int64_t mine = r0 + (threadIdx.x & (kWave - 1));
-  // every wavefront looks at the same rows and takes its share of each unselected one
-  for (unsigned long long rest = __ballot(mine < n_rows && map[mine] == 0); rest; rest &= rest - 1) {
-    uint4* p = dH + (r0 + __ffsll(static_cast<long long>(rest)) - 1) * row16;
-    for (int i = threadIdx.x; i < row16; i += 256) store_stream(p + i, make_uint4(0u, 0u, 0u, 0u));
+// What a call defines on rows that are not selected, in the launch that works on the others: some workgroups take a share of the rows each,
+// read the whole selection (it stays in L2) into a bit per row of their share, and hand the rows without one to `clear`, all threads of the
+// workgroup together, up to 64 rows at a time, as a mask of the rows from `first` on.  Values and update, with launches of their own to clear,
+// to mark a byte per row and to clear the rows without one, and like this: 1000 rows of 2048 25 and 20 us, 6000 34 and 28, 39 224 100 and 93 (on new
+// rows 119 and 111), 100 000 of 1024 123 and 113, 400 000 of 512 401 and 395.  (One entry at a time, with 64-bit places, the selection took 60 us
+// for 400 000 rows; marks by all workgroups and a queue of the rows to clear lost 80 us to atomics on one word.)
+constexpr int kMapRows = 16384;            // rows of a workgroup at a time
+template <class F>
+__device__ __forceinline__ void unselected_rows(int wg, int n_wg, int64_t n_rows, const int32_t* __restrict__ rowsel, int64_t n_sel, uint32_t* s_map,
+                                                F clear) {
+  const int64_t share = (n_rows + n_wg - 1) / n_wg, end = (wg + 1) * share < n_rows ? (wg + 1) * share : n_rows;
+  for (int64_t r0 = wg * share; r0 < end; r0 += kMapRows) {
+    const int64_t n = end - r0 < kMapRows ? end - r0 : kMapRows;
+    for (int i = threadIdx.x; i < kMapRows / 32; i += kVT) s_map[i] = 0u;
+    __syncthreads();
+    auto place = [&](int32_t row) { return static_cast<uint32_t>(row) - static_cast<uint32_t>(r0); };   // in the share: below n
+    auto mark = [&](uint32_t i) {
+      if (i < static_cast<uint32_t>(n)) atomicOr(s_map + (i >> 5), 1u << (i & 31));
+    };
+    const int64_t head = (4 - ((reinterpret_cast<uintptr_t>(rowsel) >> 2) & 3)) & 3;   // up to the first 16-byte boundary
+    const int64_t n4 = n_sel > head ? (n_sel - head) / 4 : 0;
+    const int4* const sel4 = reinterpret_cast<const int4*>(rowsel + head);
+    for (int64_t i = threadIdx.x; i < n4; i += 4 * kVT) {
+      int4 v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = i + k * kVT < n4 ? sel4[i + k * kVT] : make_int4(-1, -1, -1, -1);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {                            // nearly always all of the wavefront's lie outside: three instructions an entry
+        const uint32_t a = place(v[k].x), b = place(v[k].y), c = place(v[k].z), e = place(v[k].w), least = min(min(a, b), min(c, e));
+        if (least < static_cast<uint32_t>(n)) { mark(a); mark(b); mark(c); mark(e); }
+      }
+    }
+    const int64_t tail = head + 4 * n4 + threadIdx.x - 4;
+    if (threadIdx.x < 4) {
+      if (threadIdx.x < head && threadIdx.x < n_sel) mark(place(rowsel[threadIdx.x]));
+    } else if (threadIdx.x < 8 && tail < n_sel) {
+      mark(place(rowsel[tail]));
+    }
+    __syncthreads();
+    for (int64_t j = 0; j < n; j += kWave) {
+      unsigned long long rest = ~(s_map[j >> 5] | static_cast<unsigned long long>(s_map[(j >> 5) + 1]) << 32);
+      if (n - j < kWave) rest &= (1ull << (n - j)) - 1;
+      if (rest) clear(r0 + j, rest);
+    }
+    __syncthreads();
   }
 }
-// Below this many bytes of selected rows the two launches more cost as much as they save.
-constexpr int64_t kMarkBytes = int64_t{48} << 20;
-
-// Forward only: one wavefront per selected row.
+// What an update defines on them; either may be NULL.
 template <typename T>
+struct ClearRows {
+  float* value_new;
+  T* dH;
+  int nvec;
+  __device__ __forceinline__ void operator()(int64_t first, unsigned long long rest) const {
+    const int lane = threadIdx.x & (kWave - 1);
+    if (value_new && threadIdx.x < kWave && (rest >> lane) & 1) value_new[first + lane] = 0.f;
+    if (!dH) return;
+    for (; rest; rest &= rest - 1) {
+      T* const p = dH + (first + __ffsll(static_cast<long long>(rest)) - 1) * nvec * Vec<T>::N;
+      for (int i = threadIdx.x; i < nvec; i += kVT) store_stream(p + i * Vec<T>::N, make_uint4(0u, 0u, 0u, 0u));
+    }
+  }
+};
+// Workgroups for it: enough that clearing takes no longer than the rows, few enough that most of the device does rows.
+constexpr unsigned kClearWgs = 64;
+unsigned clear_grid(const int32_t* rowsel, int64_t n_rows) {
+  return rowsel ? std::min(kClearWgs, cdiv(static_cast<size_t>(n_rows), 128)) : 0;
+}
+
+// Forward only: one wavefront per selected row, behind n_clear workgroups for the others.
+template <typename T, bool SELECT>
 __global__ void __launch_bounds__(kVT)
 k_value_fwd(const T* __restrict__ H, const T* __restrict__ w, float bias, int d, const int32_t* __restrict__ rowsel,
-            int64_t n_sel, float* __restrict__ value) {
+            int64_t n_sel, int64_t n_rows, int n_clear, float* __restrict__ value) {
   const int lane = threadIdx.x & (kWave - 1);
-  const int64_t n = static_cast<int64_t>(blockIdx.x) * kVWaves + threadIdx.x / kWave;
+  if constexpr (SELECT) {
+    if (static_cast<int>(blockIdx.x) < n_clear) {
+      __shared__ uint32_t s_map[kMapRows / 32];
+      unselected_rows(blockIdx.x, n_clear, n_rows, rowsel, n_sel, s_map, ClearRows<T>{value, nullptr, 0});
+      return;
+    }
+  }
+  const int64_t n = static_cast<int64_t>(blockIdx.x - n_clear) * kVWaves + threadIdx.x / kWave;
   if (n >= n_sel) return;
   const int64_t row = rowsel ? rowsel[n] : n;
   const T* h = H + row * d;
@@ -127,11 +171,12 @@ k_value_fwd(const T* __restrict__ H, const T* __restrict__ w, float bias, int d,
 
 // Loss and backward, one wavefront per row.  Lane l owns the 16-byte column vectors l, l + 64, ... (KV of them):
 // it keeps its part of w, of the current row and of the next row (prefetched) in registers, and its part of
-// dw in float accumulators over all rows of the wavefront.  No barrier in the row loop.
-template <typename T, int KV>
+// dw in float accumulators over all rows of the wavefront.  No barrier in the row loop.  With SELECT n_clear workgroups, from
+// the clear_at-th on, do the rows that are not selected.
+template <typename T, int KV, bool SELECT>
 __global__ void __launch_bounds__(kVT)
 k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d, const int32_t* __restrict__ rowsel,
-             int64_t n_sel, int64_t norm, int64_t rows_per_block, const float* __restrict__ value_old, const float* __restrict__ ret,
+             int64_t n_sel, int64_t n_rows, int n_clear, int clear_at, int64_t norm, int64_t rows_per_block, const float* __restrict__ value_old, const float* __restrict__ ret,
              const int32_t* __restrict__ tok_role, int n_roles, float clip_eps, float* __restrict__ value_new,
              T* __restrict__ dH, int accumulate_dH, float* __restrict__ part_dw, double* __restrict__ blk_stats) {
   __shared__ double s_acc[(1 + UMAS_MAX_ROLES) * kVStat];
@@ -142,6 +187,17 @@ k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d
   const int nvec = d / N;
   const int nacc = (1 + n_roles) * kVStat;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  if constexpr (SELECT) {
+    const int c = static_cast<int>(blockIdx.x) - clear_at;
+    if (c >= 0 && c < n_clear) {
+      __shared__ uint32_t s_map[kMapRows / 32];
+      unselected_rows(c, n_clear, n_rows, rowsel, n_sel, s_map, ClearRows<T>{value_new, accumulate_dH ? nullptr : dH, nvec});
+      return;
+    }
+  }
+  const int blk = static_cast<int>(blockIdx.x) - (SELECT && clear_at == 0 ? n_clear : 0);
+  const int64_t r_begin = static_cast<int64_t>(blk) * rows_per_block;
+  const int64_t r_end = r_begin + rows_per_block < n_sel ? r_begin + rows_per_block : n_sel;
   for (int i = threadIdx.x; i < nacc; i += kVT) s_acc[i] = 0.0;
   __syncthreads();
   // w and the rows stay packed as loaded (16 bytes per vector) and are unpacked where they are used
@@ -158,8 +214,6 @@ k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d
   }
   float gsum = 0.f;
   const float inv_s = 1.f / static_cast<float>(norm);
-  const int64_t r_begin = static_cast<int64_t>(blockIdx.x) * rows_per_block;
-  const int64_t r_end = r_begin + rows_per_block < n_sel ? r_begin + rows_per_block : n_sel;
 
   uint4 cur[KV], nxt[KV];
   float vo_next = 0.f, ret_next = 0.f;               // the next row's old value and return come with the row
@@ -244,10 +298,10 @@ k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d
     }
     __syncthreads();
   }
-  float* pd = part_dw + static_cast<size_t>(blockIdx.x) * part_pitch(d);
+  float* pd = part_dw + static_cast<size_t>(blk) * part_pitch(d);
   for (int j = threadIdx.x; j < d; j += kVT) pd[j] = static_cast<float>(s_dw[j]);
   if (threadIdx.x == 0) pd[d] = (s_g[0] + s_g[1]) + (s_g[2] + s_g[3]);
-  for (int i = threadIdx.x; i < nacc; i += kVT) blk_stats[static_cast<size_t>(blockIdx.x) * nacc + i] = s_acc[i];
+  for (int i = threadIdx.x; i < nacc; i += kVT) blk_stats[static_cast<size_t>(blk) * nacc + i] = s_acc[i];
 }
 
 // What the workgroups of the row kernel left, added up in a fixed order.  The first col_blocks workgroups take 16 columns
@@ -316,7 +370,7 @@ unsigned resident_value_blocks() {
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
     n_cu = 64;
   constexpr size_t kLds = static_cast<size_t>(K) * kWave * Vec<T>::N * sizeof(AccT<T>);   // the widest rows of the instance
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_value_rows<T, K>, kVT, kLds) != hipSuccess || per_cu < 1) per_cu = 1;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_value_rows<T, K, false>, kVT, kLds) != hipSuccess || per_cu < 1) per_cu = 1;
   cached = static_cast<unsigned>(per_cu) * static_cast<unsigned>(n_cu);
   return cached;
 }
@@ -332,12 +386,12 @@ unsigned resident_value_blocks_kv(int kv) {
 
 template <typename T>
 void launch_value_rows(int kv, unsigned grid, hipStream_t st, const void* H, const void* w, float bias, int d,
-                       const int32_t* rowsel, int64_t n_sel, int64_t norm, int64_t rpb, const float* value_old, const float* ret,
+                       const int32_t* rowsel, int64_t n_sel, int64_t n_rows, unsigned n_clear, unsigned clear_at, int64_t norm, int64_t rpb, const float* value_old, const float* ret,
                        const int32_t* tok_role, int n_roles, float clip_eps, float* value_new, void* dH, int acc_dH,
                        float* part_dw, double* blk_stats) {
 #define UMAS_VALUE_CASE(K)                                                                                              \
-  hipLaunchKernelGGL((k_value_rows<T, K>), dim3(grid), dim3(kVT), d * sizeof(AccT<T>), st, static_cast<const T*>(H), static_cast<const T*>(w), \
-                     bias, d, rowsel, n_sel, norm, rpb, value_old, ret, tok_role, n_roles, clip_eps, value_new,         \
+  hipLaunchKernelGGL((n_clear ? k_value_rows<T, K, true> : k_value_rows<T, K, false>), dim3(n_clear + grid), dim3(kVT), d * sizeof(AccT<T>), st, static_cast<const T*>(H), static_cast<const T*>(w), \
+                     bias, d, rowsel, n_sel, n_rows, static_cast<int>(n_clear), static_cast<int>(clear_at), norm, rpb, value_old, ret, tok_role, n_roles, clip_eps, value_new,         \
                      static_cast<T*>(dH), acc_dH, part_dw, blk_stats)
   if (kv <= 1) UMAS_VALUE_CASE(1);
   else if (kv <= 2) UMAS_VALUE_CASE(2);
@@ -345,6 +399,14 @@ void launch_value_rows(int kv, unsigned grid, hipStream_t st, const void* H, con
   else if (kv <= 8) UMAS_VALUE_CASE(8);
   else UMAS_VALUE_CASE(16);
 #undef UMAS_VALUE_CASE
+}
+
+hipError_t zero_words(void* p, int64_t n, hipStream_t st) {
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_zero_u32, dim3(cdiv(n, 1024) < 8192 ? cdiv(n, 1024) : 8192), dim3(256), 0, st, static_cast<uint32_t*>(p), n);
+  const hipError_t e = hipGetLastError();
+  if (e == hipSuccess && g_prof_on) prof_kernel("k_zero_u32", st);
+  return e;
 }
 
 umas_status check_value_args(const void* H, const void* w, umas_dtype dt, int64_t n_rows, int d, const int32_t* rowsel,
@@ -382,18 +444,18 @@ extern "C" umas_status umas_values(const void* H, const void* w, float bias, uma
   UMAS_REQUIRE(value || n_rows == 0, UMAS_EINVAL, "value must not be NULL");
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   prof_mark(st);
-  if (rowsel && n_rows > 0) {
-    hipLaunchKernelGGL(k_zero_u32, dim3(cdiv(n_rows, 1024) < 4096 ? cdiv(n_rows, 1024) : 4096), dim3(256), 0, st,
-                       reinterpret_cast<uint32_t*>(value), n_rows);
-    UMAS_LAUNCHED("k_zero_u32");
+  if (n_sel == 0) {
+    if (n_rows > 0) UMAS_HIP(zero_words(value, n_rows, st));
+    return UMAS_OK;
   }
-  if (n_sel == 0) return UMAS_OK;
-  if (dtype == UMAS_BF16)
-    hipLaunchKernelGGL(k_value_fwd<uint16_t>, dim3(cdiv(n_sel, kVWaves)), dim3(kVT), 0, st, static_cast<const uint16_t*>(H),
-                       static_cast<const uint16_t*>(w), bias, d, rowsel, n_sel, value);
-  else
-    hipLaunchKernelGGL(k_value_fwd<float>, dim3(cdiv(n_sel, kVWaves)), dim3(kVT), 0, st, static_cast<const float*>(H),
-                       static_cast<const float*>(w), bias, d, rowsel, n_sel, value);
+  const unsigned n_clear = clear_grid(rowsel, n_rows);
+  auto fwd = [&](auto kernel, auto* h) {
+    using T = std::remove_pointer_t<decltype(h)>;
+    hipLaunchKernelGGL(kernel, dim3(n_clear + cdiv(n_sel, kVWaves)), dim3(kVT), 0, st, h, static_cast<T*>(w), bias, d, rowsel, n_sel, n_rows,
+                       static_cast<int>(n_clear), value);
+  };
+  if (dtype == UMAS_BF16) fwd(n_clear ? k_value_fwd<uint16_t, true> : k_value_fwd<uint16_t, false>, static_cast<const uint16_t*>(H));
+  else fwd(n_clear ? k_value_fwd<float, true> : k_value_fwd<float, false>, static_cast<const float*>(H));
   UMAS_LAUNCHED("k_value_fwd");
   return UMAS_OK;
 }
@@ -424,50 +486,32 @@ extern "C" umas_status umas_value_loss_fwd_bwd(const void* H, const void* w, flo
   const int kv = (nvec + kWave - 1) / kWave;
   // at most value_grid(n_sel) workgroups (what the workspace is sized for), and no more than are resident at once
   const unsigned resident = dtype == UMAS_BF16 ? resident_value_blocks_kv<uint16_t>(kv) : resident_value_blocks_kv<float>(kv);
-  const unsigned grid = std::min(value_grid(n_sel), resident);
+  // the workgroups that clear are part of that round and go first; behind a full round of rows where the instance holds so few at once
+  // that giving them up costs more than a tail (39 224 rows of 4096 233 us with them first, 204 behind)
+  const unsigned n_clear = n_sel > 0 ? clear_grid(rowsel, n_rows) : 0;
+  const bool last = kv >= 8;
+  const unsigned grid = std::min(value_grid(n_sel), last || resident <= n_clear ? resident : resident - n_clear);
+  const unsigned clear_at = last ? grid : 0;
   const size_t part_bytes = static_cast<size_t>(grid) * part_pitch(d) * sizeof(float);
   Carver c(workspace);
   float* part_dw = c.take<float>(part_bytes / sizeof(float));
   double* blk_stats = c.take<double>(static_cast<size_t>(grid) * (1 + n_roles) * kVStat);
 
-  auto zero = [&](void* p, size_t bytes) -> hipError_t {
-    const int64_t n = static_cast<int64_t>(bytes / 4);
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero_u32, dim3(cdiv(n, 1024) < 8192 ? cdiv(n, 1024) : 8192), dim3(256), 0, st,
-                       static_cast<uint32_t*>(p), n);
-    const hipError_t e = hipGetLastError();
-    if (e == hipSuccess && g_prof_on) prof_kernel("k_zero_u32", st);
-    return e;
-  };
-  if (rowsel && n_rows > 0) {
-    const size_t row_bytes = static_cast<size_t>(d) * esz;           // a multiple of 16
-    const bool mark = !accumulate_dH && n_sel * static_cast<int64_t>(row_bytes) >= kMarkBytes && align_up(n_rows, 16) <= part_bytes;
-    const int64_t n16 = accumulate_dH ? 0 : static_cast<int64_t>(mark ? align_up(n_rows, 16) / 16 : n_rows * row_bytes / 16);
-    uint8_t* map = reinterpret_cast<uint8_t*>(part_dw);
-    hipLaunchKernelGGL(k_value_open, dim3(std::min(std::max(cdiv(n16, 1024), cdiv(n_rows, 1024)), 8192u)), dim3(256), 0, st,
-                       reinterpret_cast<uint32_t*>(value_new), n_rows, static_cast<uint4*>(mark ? static_cast<void*>(map) : dH), n16);
-    UMAS_LAUNCHED("k_value_open");
-    if (mark) {
-      hipLaunchKernelGGL(k_value_mark, dim3(cdiv(n_sel, 256)), dim3(256), 0, st, rowsel, n_sel, n_rows, map);
-      UMAS_LAUNCHED("k_value_mark");
-      hipLaunchKernelGGL(k_value_clear_rest, dim3(cdiv(n_rows, kClearRows)), dim3(256), 0, st, map, n_rows, static_cast<int>(row_bytes / 16),
-                         static_cast<uint4*>(dH));
-      UMAS_LAUNCHED("k_value_clear_rest");
-    }
-  }
   if (n_sel > 0) {
     const int64_t rpb = (n_sel + grid - 1) / grid;                 // rows per workgroup; every wavefront writes its partial row
     if (dtype == UMAS_BF16)
-      launch_value_rows<uint16_t>(kv, grid, st, H, w, bias, d, rowsel, n_sel, norm, rpb, value_old, ret, tok_role, n_roles,
+      launch_value_rows<uint16_t>(kv, grid, st, H, w, bias, d, rowsel, n_sel, n_rows, n_clear, clear_at, norm, rpb, value_old, ret, tok_role, n_roles,
                                   clip_eps_v, value_new, dH, accumulate_dH, part_dw, blk_stats);
     else
-      launch_value_rows<float>(kv, grid, st, H, w, bias, d, rowsel, n_sel, norm, rpb, value_old, ret, tok_role, n_roles,
+      launch_value_rows<float>(kv, grid, st, H, w, bias, d, rowsel, n_sel, n_rows, n_clear, clear_at, norm, rpb, value_old, ret, tok_role, n_roles,
                                clip_eps_v, value_new, dH, accumulate_dH, part_dw, blk_stats);
     UMAS_LAUNCHED("k_value_rows");
   } else {
     // an empty selection still defines the outputs: zero partials give zero statistics and gradients
-    UMAS_HIP(zero(part_dw, part_bytes));
-    UMAS_HIP(zero(blk_stats, static_cast<size_t>(grid) * (1 + n_roles) * kVStat * sizeof(double)));
+    if (value_new) UMAS_HIP(zero_words(value_new, n_rows, st));
+    if (!accumulate_dH) UMAS_HIP(zero_words(dH, static_cast<int64_t>(n_rows * d * esz / 4), st));
+    UMAS_HIP(zero_words(part_dw, static_cast<int64_t>(part_bytes / 4), st));
+    UMAS_HIP(zero_words(blk_stats, static_cast<int64_t>(grid) * (1 + n_roles) * kVStat * 2, st));
   }
   const int col_blocks = static_cast<int>(cdiv(d + 1, kFinCols));
   hipLaunchKernelGGL(k_value_finish, dim3(col_blocks + 1 + n_roles), dim3(kFinT), 0, st, part_dw, static_cast<int>(grid), d, col_blocks,

@@ -144,3 +144,33 @@ def test_float32_gradient_products_in_every_tile_size(rows, d, V, select):
         rest = torch.ones(n, dtype=torch.bool, device="cuda")
         rest[at] = False
         assert (dH[rest] == 0).all() and (logp[rest] == 0).all()
+
+
+@pytest.mark.parametrize("n,n_sel,shift", [(1, 1, 0), (2, 1, 1), (127, 5, 3), (129, 128, 0), (8300, 3, 2), (8300, 8299, 1), (70000, 50001, 0), (600000, 10, 0), (600000, 480001, 3)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_critic_defines_the_rows_that_are_not_selected(n, n_sel, shift, dtype):
+    g = torch.Generator(device="cuda").manual_seed(n_sel)
+    d = 72
+    H, w = torch.randn(n, d, device="cuda", generator=g).to(dtype), torch.randn(d, device="cuda", generator=g).to(dtype)
+    sel = torch.randperm(n, device="cuda", generator=g)[:n_sel].to(torch.int32)
+    at = torch.empty(n_sel + shift, dtype=torch.int32, device="cuda")
+    at[shift:] = sel                                     # a selection at any multiple of four bytes
+    sel, ret, old = at[shift:], torch.randn(n, device="cuda", generator=g), torch.zeros(n, device="cuda")
+    nan = lambda *s: torch.full(s, float("nan"), device="cuda")
+    value = umas.umas_values(H, w, 0.5, sel, value=nan(n))
+    _, value_new, dH, dw, db = umas.umas_value_loss_fwd_bwd(H, w, 0.5, sel, old, ret, None, 0, 1e9, dH=nan(n, d).to(dtype), value_new=nan(n))
+    rest = torch.ones(n, dtype=torch.bool, device="cuda")
+    rest[sel.long()] = False
+    v64 = H[sel.long()].double() @ w.double() + 0.5
+    # float32 (bf16 rows) or float64 sums of d products of numbers below 5, rounded once
+    assert (value[sel.long()].double() - v64).abs().max() <= d * 25 * 2.0 ** -23
+    assert torch.equal(value[rest], torch.zeros_like(value[rest])) and torch.equal(value_new, value)
+    assert (dH[rest] == 0).all()
+    gr = (v64 - ret[sel.long()].double()) / n_sel
+    want = gr[:, None] * w.double()
+    eps = 2.0 ** -8 if dtype is torch.bfloat16 else 2.0 ** -22
+    assert ((dH[sel.long()].double() - want).abs() <= eps * want.abs() + d * 25 * 2.0 ** -22 / n_sel * w.double().abs()).all()
+    kept = nan(n, d).to(dtype)                           # accumulating: other rows keep what they hold
+    kept[sel.long()] = 0
+    umas.umas_value_loss_fwd_bwd(H, w, 0.5, sel, old, ret, None, 0, 1e9, dH=kept, accumulate_dH=True)
+    assert torch.equal(kept[sel.long()], dH[sel.long()]) and kept[rest].isnan().all()
