@@ -153,8 +153,10 @@ __device__ __forceinline__ void mfma_mainloop_ring2(__amdgpu_buffer_rsrc_t ra, c
 #pragma unroll
     for (int i = 0; i < HA; ++i)
 #pragma unroll
-      for (int j = 0; j < C::NI; ++j)
+      for (int jj = 0; jj < C::NI; ++jj) {
+        const int j = i & 1 ? C::NI - 1 - jj : jj;
         acc[h * HA + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[abuf][i], bfr[bbuf][j], acc[h * HA + i][j], 0, 0, 0);
+      }
   };
   auto interleave = [&](int n_ds, int n_vm) {
 #pragma unroll
@@ -383,8 +385,10 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
 #pragma unroll
     for (int i = 0; i < HA; ++i)
 #pragma unroll
-      for (int j = 0; j < C::NI; ++j)
+      for (int jj = 0; jj < C::NI; ++jj) {
+        const int j = i & 1 ? C::NI - 1 - jj : jj;
         acc[h * HA + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[abuf][i], bfr[bbuf][j], acc[h * HA + i][j], 0, 0, 0);
+      }
   };
 
   constexpr int kDsA = (ATR ? 2 : 1) * HA, kDsB = (BTR ? 2 : 1) * C::NI;   // LDS reads of an A half, of a slice of B
