@@ -38,13 +38,17 @@ constexpr int kThreads = 256;
 constexpr int kIpt = 4;                          // tokens per thread: one 16-byte load per array, no transposition
 constexpr int kTile = kThreads * kIpt;           // tokens per tile
 constexpr int kChunkTiles = 8;                   // nominal tiles per range at most
+constexpr int kTurnChunkTiles = 4;               // ... of turns that are on average no longer than that
 // Nominal tokens per range: a range's tiles are done one after the other, so a stream that makes fewer than 512 ranges of
 // eight tiles (4.2 million tokens) is cut finer, into 512 and more where it has as many tiles: two for every compute unit
 // (49 152 tokens: 6 ranges of eight tiles 19 us, 48 of one 7 us; the call, waited for, 40 -> 28 us, 400 000 tokens 43 -> 33,
 // 225 000 in segments that are cut 91 -> 60; 25 million tokens keep ranges of eight, 62 us).
-inline int64_t chunk_tokens(int64_t n_tokens) {
+// Turns end every few tiles, so that finer ranges are even ones, and the last round of them is shorter (ranges of eight and four tiles: 42 million
+// tokens in turns of 1024 and 4096 155 and 149 us, 25.6 in turns of 512 94 and 90, 3.2 in turns of 400 22.1 and 20.7); runs of a trajectory
+// may be longer than a range, which is then empty as often as not (42 million in runs of 5120 to 15 360 165 and 209).
+inline int64_t chunk_tokens(int64_t n_tokens, int most) {
   const int64_t tiles = n_tokens / (static_cast<int64_t>(kTile) * 512);
-  return (tiles < 1 ? 1 : tiles > kChunkTiles ? kChunkTiles : tiles) * kTile;
+  return (tiles < 1 ? 1 : tiles > most ? most : tiles) * kTile;
 }
 constexpr int64_t kLongSegment = 16 * kTile;     // a segment end farther away than this does not move a range's edge
 // Up to so many tokens a workgroup whose range ends inside a long segment reads on to its end itself instead of leaving the range to
@@ -145,13 +149,39 @@ __device__ __forceinline__ int64_t boundary_at_or_after(const int64_t* __restric
   if (x <= 0) return 0;
   return off[wave_last_le(off, n, x - 1) + 1];
 }
+// The same, looked for in the flags of 1024 tokens first: a search in the offsets is three or four trips to memory one behind the other, of
+// lines all over them, and while all of memory is busy that is 6 us to find the eight tiles that a range takes 30 us for; the flags are
+// the range's own or its neighbour's, and one trip (25 million tokens in turns of 256 72 -> 66.5 us, 19 million in runs of 192 51.5 -> 47; 42 million in
+// runs of 5120 and more, where the offsets are searched as well, 165 either way).  0 < x < n_tokens.
+__device__ __forceinline__ int64_t boundary_from(const ScanParams& P, int64_t x) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t first = x - 1, p = (first & ~int64_t{15}) + lane * 16;
+  uint32_t w[4] = {0u, 0u, 0u, 0u};
+  if (p + 16 <= P.n_tokens) {
+    const uint4 v = *reinterpret_cast<const uint4*>(P.flags + p);
+    w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+  } else {
+    for (int k = 0; k < 16 && p + k < P.n_tokens; ++k) w[k >> 2] |= static_cast<uint32_t>(P.flags[p + k]) << (8 * (k & 3));
+  }
+  int at = -1;                                                       // first flagged one of this lane's sixteen tokens
+#pragma unroll
+  for (int k = 3; k >= 0; --k) {
+    const int skip = static_cast<int>(first - p) - 4 * k;            // bytes of the word in front of the first token
+    const uint32_t hit = w[k] & (P.seg_bit * 0x01010101u) & (skip <= 0 ? ~0u : skip >= 4 ? 0u : ~0u << (8 * skip));
+    at = hit ? 4 * k + (__ffs(static_cast<int>(hit)) - 1) / 8 : at;
+  }
+  const unsigned long long any = __ballot(at >= 0);
+  if (!any) return boundary_at_or_after(P.seg_off, P.n_seg_entries, x);
+  const int l = __ffsll(static_cast<long long>(any)) - 1;
+  return (first & ~int64_t{15}) + l * 16 + __builtin_amdgcn_readlane(at, l) + 1;
+}
 // Where the range edge nominally at x really lies: at the next segment boundary unless that is farther than
 // kLongSegment away, in which case the edge stays at x, inside the segment (*cut = 1).  *boundary: that boundary.
-__device__ __forceinline__ int64_t range_edge(const int64_t* __restrict__ off, int n, int64_t n_tokens, int64_t x, int* cut, int64_t* boundary) {
+__device__ __forceinline__ int64_t range_edge(const ScanParams& P, int64_t x, int* cut, int64_t* boundary) {
   *cut = 0;
-  *boundary = x <= 0 ? 0 : n_tokens;
-  if (x <= 0 || x >= n_tokens) return *boundary;
-  *boundary = boundary_at_or_after(off, n, x);
+  *boundary = x <= 0 ? 0 : P.n_tokens;
+  if (x <= 0 || x >= P.n_tokens) return *boundary;
+  *boundary = boundary_from(P, x);
   if (*boundary - x < kLongSegment) return *boundary;
   *cut = 1;
   return x;
@@ -264,8 +294,16 @@ struct Four {
   float kap[kIpt];                                  // step discount applied before the token (1 = none)
   bool mine[kIpt];                                  // tokens outside the range belong to a neighbour
 };
+// Discounts of 0 .. 30 steps: a power takes a hundred instructions, and where turns are short every wavefront has some in every tile (24 million
+// tokens in turns of 300 104 -> 101 us).
+constexpr int kKaps = kFlagStepMany;
 template <bool DECAY>
-__device__ __forceinline__ Four four_tokens(const ScanParams& P, const Range& R, int64_t p0, const Raw& x) {
+__device__ __forceinline__ void fill_kaps(const ScanParams& P, float* s_kap) {   // a barrier follows
+  if constexpr (DECAY)
+    if (threadIdx.x < kKaps) s_kap[threadIdx.x] = powf(P.gamma_turn, static_cast<float>(threadIdx.x));
+}
+template <bool DECAY>
+__device__ __forceinline__ Four four_tokens(const ScanParams& P, const Range& R, int64_t p0, const Raw& x, const float* s_kap) {
   Four T{{x.r4.x, x.r4.y, x.r4.z, x.r4.w}, {x.v4.x, x.v4.y, x.v4.z, x.v4.w}, {}, {}, {}};
 #pragma unroll
   for (int k = 0; k < kIpt; ++k) {
@@ -274,12 +312,13 @@ __device__ __forceinline__ Four four_tokens(const ScanParams& P, const Range& R,
     T.kap[k] = 1.f;
     if constexpr (DECAY) {
       if (T.mine[k] && (T.fl[k] & kFlagTurnEnd) && !(T.fl[k] & P.seg_bit)) {   // a later turn of the same run follows: p + 1 exists
-        int ds = static_cast<int>(T.fl[k] >> kFlagStepShift);   // steps to the run's next turn; kFlagStepMany: more than fit
-        if (ds == kFlagStepMany) {
+        const int ds = static_cast<int>(T.fl[k] >> kFlagStepShift);   // steps to the run's next turn; kFlagStepMany: more than fit
+        if (ds < kFlagStepMany) {
+          T.kap[k] = s_kap[ds];
+        } else {
           const int64_t p = p0 + k;
-          ds = P.turn_step[P.tok_turn[p + 1]] - P.turn_step[P.tok_turn[p]];
+          T.kap[k] = powf(P.gamma_turn, static_cast<float>(P.turn_step[P.tok_turn[p + 1]] - P.turn_step[P.tok_turn[p]]));
         }
-        T.kap[k] = powf(P.gamma_turn, static_cast<float>(ds));
       }
     }
   }
@@ -307,7 +346,7 @@ __device__ __forceinline__ Aff fold_four(const ScanParams& P, const Four& T) {
 // range's left edge in (*G_io, *NV_io) (valid in thread 0).
 template <bool HV, bool DECAY, bool REPLAY>
 __device__ __forceinline__ void walk_range(const ScanParams& P, const Range& R, float* __restrict__ adv, float* __restrict__ ret,
-                                           Aff (*s_w)[kThreads / kWave], float (*s_carry)[2], float* G_io, float* NV_io, Aff* total) {
+                                           Aff (*s_w)[kThreads / kWave], float (*s_carry)[2], const float* s_kap, float* G_io, float* NV_io, Aff* total) {
   const int tid = threadIdx.x;
   const float gl = P.gamma * P.lam;
   const int64_t t_hi = (R.end - 1) / kTile, t_lo = R.start / kTile;
@@ -325,7 +364,7 @@ __device__ __forceinline__ void walk_range(const ScanParams& P, const Range& R, 
     for (int a = 0; a < kAhead; ++a) buf[a] = buf[a + 1];
     if (tile - kAhead - 1 >= t_lo) load_four<HV>(P, R, (tile - kAhead - 1) * kTile + tid * kIpt, buf[kAhead]);
     const int64_t p0 = tile * kTile + static_cast<int64_t>(tid) * kIpt;
-    const Four T = four_tokens<DECAY>(P, R, p0, x);
+    const Four T = four_tokens<DECAY>(P, R, p0, x, s_kap);
     const Aff acc = fold_four<HV, DECAY>(P, T);
     Aff tile_map;
     const Aff from_right = block_suffix_excl<HV>(acc, s_w[par], &tile_map);   // the one barrier of a tile
@@ -368,7 +407,7 @@ __device__ __forceinline__ void walk_range(const ScanParams& P, const Range& R, 
 // The map of the tokens R, which end a segment, for a workgroup that needs the state on their left: every wavefront folds a quarter of
 // them, 256 at a time, and needs a barrier only at the end.  Every thread gets the map.
 template <bool HV, bool DECAY>
-__device__ __forceinline__ Aff fold_ahead(const ScanParams& P, const Range& R, Aff* s_w) {
+__device__ __forceinline__ Aff fold_ahead(const ScanParams& P, const Range& R, Aff* s_w, const float* s_kap) {
   constexpr int nwave = kThreads / kWave, kStep = kWave * kIpt;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int64_t first = R.start / kStep, n = (R.end - 1) / kStep + 1 - first, per = (n + nwave - 1) / nwave;
@@ -379,7 +418,7 @@ __device__ __forceinline__ Aff fold_ahead(const ScanParams& P, const Range& R, A
   for (int64_t t = hi - 1; t >= lo; --t) {
     const Raw x = next;
     if (t > lo) load_four<HV>(P, R, (t - 1) * kStep + lane * kIpt, next);
-    Aff acc = fold_four<HV, DECAY>(P, four_tokens<DECAY>(P, R, t * kStep + lane * kIpt, x));
+    Aff acc = fold_four<HV, DECAY>(P, four_tokens<DECAY>(P, R, t * kStep + lane * kIpt, x, s_kap));
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
       const Aff right = aff_shfl_down<HV>(acc, o);
@@ -395,7 +434,7 @@ __device__ __forceinline__ Aff fold_ahead(const ScanParams& P, const Range& R, A
   return total;
 }
 
-// One workgroup per range.  It finds the range's edges (two wavefront-wide searches, one wavefront each).  Unless the range is
+// One workgroup per range.  It finds the range's edges (one wavefront each).  Unless the range is
 // empty or its right end lies inside a long segment, it scans the range: nothing comes in from the right.  What the second kernel needs is
 // left for it: the edges, the range's record cleared or published.  With ALONE there is no second kernel: a workgroup whose range ends inside a
 // segment reads on to the segment's end itself, for its map.
@@ -406,14 +445,16 @@ k_gae_scan(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
   __shared__ float s_carry[2][2];
   __shared__ int64_t s_edge[2], s_end;
   __shared__ int s_cut[2];
+  __shared__ float s_kap[kKaps];
   const int tid = threadIdx.x;
+  fill_kaps<DECAY>(P, s_kap);
   const uint32_t q = blockIdx.x;                                                   // from the right
   const int64_t i = static_cast<int64_t>(P.n_ranges) - 1 - q;                      // from the left
   if (tid < 2 * kWave) {
     const int which = tid / kWave;                   // wavefront 0: left edge, wavefront 1: right edge
     int cut;
     int64_t boundary;
-    const int64_t edge = range_edge(P.seg_off, P.n_seg_entries, P.n_tokens, (i + which) * P.chunk, &cut, &boundary);
+    const int64_t edge = range_edge(P, (i + which) * P.chunk, &cut, &boundary);
     if ((tid & (kWave - 1)) == 0) {
       s_edge[which] = edge;
       s_cut[which] = cut;
@@ -432,7 +473,7 @@ k_gae_scan(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
     if (R.start >= R.end) return;                   // the same for every thread, also below
     if (R.cut_right) {
       const Range ahead{R.end, s_end, 0, 0, 0};
-      const Aff m = fold_ahead<HV, DECAY>(P, ahead, s_w[0]);
+      const Aff m = fold_ahead<HV, DECAY>(P, ahead, s_w[0], s_kap);
       G = m.c;                                      // a constant map: a segment ends there
       NV = HV ? m.f : 0.f;
     }
@@ -442,7 +483,7 @@ k_gae_scan(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
     if (R.start >= R.end || R.cut_right) return;
   }
   Aff unused;
-  walk_range<HV, DECAY, true>(P, R, adv, ret, s_w, s_carry, &G, &NV, &unused);
+  walk_range<HV, DECAY, true>(P, R, adv, ret, s_w, s_carry, s_kap, &G, &NV, &unused);
   // a range that starts inside a long segment: what it hands to the left is a constant
   if (!ALONE && R.cut_left && tid == 0)
     publish<HV>(P.range_state + static_cast<size_t>(q) * kStateWords, Aff{0.f, 0.f, G, 0.f, HV ? NV : 0.f});
@@ -460,6 +501,8 @@ k_gae_scan_cut(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
   int mine = 0;
   for (uint64_t q = blockIdx.x + static_cast<uint64_t>(tid) * gridDim.x; q < P.n_ranges; q += static_cast<uint64_t>(kThreads) * gridDim.x)
     mine |= P.ranges[q].cut_right;
+  __shared__ float s_kap[kKaps];
+  fill_kaps<DECAY>(P, s_kap);
   if (!__syncthreads_or(mine)) return;
   for (uint32_t q = blockIdx.x; q < P.n_ranges; q += gridDim.x) {
     const Range R = P.ranges[q];
@@ -468,7 +511,7 @@ k_gae_scan_cut(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
     // hand over, then the replay
     float G = 0.f, NV = 0.f;
     Aff range_map;
-    walk_range<HV, DECAY, false>(P, R, adv, ret, s_w, s_carry, &G, &NV, &range_map);
+    walk_range<HV, DECAY, false>(P, R, adv, ret, s_w, s_carry, s_kap, &G, &NV, &range_map);
     if (R.cut_left && tid == 0) publish<HV>(P.range_state + static_cast<size_t>(q) * kStateWords, range_map);
     if (tid < kWave) {
       float g_in, nv_in;
@@ -479,7 +522,7 @@ k_gae_scan_cut(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
     G = s_in[0];
     NV = s_in[1];
     Aff unused;
-    walk_range<HV, DECAY, true>(P, R, adv, ret, s_w, s_carry, &G, &NV, &unused);
+    walk_range<HV, DECAY, true>(P, R, adv, ret, s_w, s_carry, s_kap, &G, &NV, &unused);
     __syncthreads();
   }
 }
@@ -497,7 +540,7 @@ using namespace umas;
 
 extern "C" size_t umas_advantages_workspace_bytes(int64_t n_tokens) {
   if (n_tokens < 0) return 0;
-  return scan_bytes(n_tokens, chunk_tokens(n_tokens));
+  return scan_bytes(n_tokens, chunk_tokens(n_tokens, kTurnChunkTiles));
 }
 
 extern "C" umas_status umas_advantages(const umas_streams* s, int64_t n_tokens, int32_t n_turns,
@@ -527,7 +570,8 @@ extern "C" umas_status umas_advantages(const umas_streams* s, int64_t n_tokens, 
   prof_mark(st);
   ScanParams P;
   P.n_tokens = n_tokens;
-  P.chunk = chunk_tokens(n_tokens);
+  const bool short_turns = seg_mode == UMAS_SEG_TURN && n_tokens <= static_cast<int64_t>(n_turns) * (kTurnChunkTiles * kTile);
+  P.chunk = chunk_tokens(n_tokens, short_turns ? kTurnChunkTiles : kChunkTiles);
   while (scan_bytes(n_tokens, P.chunk) > workspace_bytes) P.chunk += kTile;
   const int64_t n_ranges = scan_ranges(n_tokens, P.chunk);
   P.n_ranges = static_cast<uint32_t>(n_ranges);
