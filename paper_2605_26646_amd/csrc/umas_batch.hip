@@ -298,14 +298,14 @@ k_mb_pack(int n_traj, int64_t max_rows, const int64_t* __restrict__ n_kept_p, co
 // Up to 256 trajectories the five kernels above and the copy in front of them are launches of 4 to 9 us each, on the device and on the
 // host, for a few KB of index work.  Here every workgroup reads the thin arrays from the pinned block itself, makes ranks, slices
 // and prefix sums in LDS, and moves its share of the slices, several wavefronts to a slice; the first one writes the offsets instead.
-// 32 trajectories, 28 000 rows, packed: 33 us in six launches, 10 in one, and 26 and 8.5 us of the host.
+// 32 trajectories, 28 000 rows, packed: 33 us in six launches, 9.3 in one (10 with the thin arrays waited for first), and 26 and 8.5 us of the host.
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallTraj = 256;
 constexpr int kSmallSlices = 1024;                  // models times trajectories
 constexpr int kSmallTurns = 1024;                   // runs are no more than turns; at least one lane searches for each
 constexpr size_t kSmallThin = 4 * 1024;
 constexpr unsigned kSmallMovers = 16;               // workgroups that move slices, and as many more as make a wavefront for each
-static_assert(kSmallTraj * 9 + 4 + 3 * kAlign <= kSmallThin, "offsets, order and flags");
+static_assert(kSmallTraj * 9 + 4 + 3 * kAlign <= kSmallThin && kSmallThin <= 16 * kSmallThreads, "offsets, order and flags, 16 bytes a thread");
 
 struct SmallArgs {
   ThinStage::Reader thin;
@@ -353,28 +353,18 @@ k_ready_small(SmallArgs A) {
   __shared__ int s_kept[kSmallTraj / kWave];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int B = A.n_traj, K = A.n_models, n_mq = K * B;
-  for (int i = tid; i < A.thin16; i += kSmallThreads) reinterpret_cast<uint4*>(s_thin)[i] = reinterpret_cast<const uint4*>(A.thin.block)[i];
+  // the thin arrays are on their way over the bus while the runs are searched, which needs none of them; the last wavefronts ask for
+  // them, for whose loads come back in order and few runs leave these nothing to search
+  const int t16 = kSmallThreads - 1 - tid;
+  uint4 thin = make_uint4(0u, 0u, 0u, 0u);
+  if (t16 < A.thin16) thin = reinterpret_cast<const uint4*>(A.thin.block)[t16];
   if (tid <= K) {
     s_tok[tid] = A.model_tok_off[tid];
     s_sel[tid] = A.model_rowsel_off[tid];
     s_run[tid] = A.model_trajrun_off[tid];
   }
   if (tid < n_mq) s_row[tid] = 0;
-  stage_read_done(A.thin);
-  const int32_t* const tto = reinterpret_cast<const int32_t*>(s_thin);
-  // ---- ranks of the kept trajectories in shuffled order
-  int b = -1;
-  bool kept = false;
-  int pos = 0;
-  if (wave < kSmallTraj / kWave) {
-    if (tid < B) {
-      b = A.at_order >= 0 ? reinterpret_cast<const int32_t*>(s_thin + A.at_order)[tid] : tid;
-      kept = A.at_keep < 0 || reinterpret_cast<const uint8_t*>(s_thin + A.at_keep)[b] != 0;
-    }
-    const unsigned long long k = __ballot(kept);
-    pos = __popcll(k & ((1ull << lane) - 1));
-    if (lane == 0) s_kept[wave] = __popcll(k);
-  }
+  __syncthreads();
   // ---- first rows of the runs: as many lanes to a run as there are
   const int n_runs = s_run[K] < A.n_turns ? s_run[K] : A.n_turns;
   auto model_of_run = [&](int j) {
@@ -394,6 +384,29 @@ k_ready_small(SmallArgs A) {
   if (n_runs <= kSmallThreads / 16) search(std::integral_constant<int, 16>());
   else if (n_runs <= kSmallThreads / 4) search(std::integral_constant<int, 4>());
   else search(std::integral_constant<int, 1>());
+  int64_t start = 0, end = 0;                       // this thread's run
+  int turn = 0;
+  if (tid < n_runs) {
+    start = A.traj_seg_off[tid];
+    end = A.traj_seg_off[tid + 1];
+    if (end > start) turn = A.tok_turn[start];
+  }
+  if (t16 < A.thin16) reinterpret_cast<uint4*>(s_thin)[t16] = thin;
+  stage_read_done(A.thin);                          // also the barrier behind the stores to LDS
+  const int32_t* const tto = reinterpret_cast<const int32_t*>(s_thin);
+  // ---- ranks of the kept trajectories in shuffled order
+  int b = -1;
+  bool kept = false;
+  int pos = 0;
+  if (wave < kSmallTraj / kWave) {
+    if (tid < B) {
+      b = A.at_order >= 0 ? reinterpret_cast<const int32_t*>(s_thin + A.at_order)[tid] : tid;
+      kept = A.at_keep < 0 || reinterpret_cast<const uint8_t*>(s_thin + A.at_keep)[b] != 0;
+    }
+    const unsigned long long k = __ballot(kept);
+    pos = __popcll(k & ((1ull << lane) - 1));
+    if (lane == 0) s_kept[wave] = __popcll(k);
+  }
   __syncthreads();
   int n_kept = 0;
   for (int w = 0; w < kSmallTraj / kWave; ++w) {
@@ -403,15 +416,12 @@ k_ready_small(SmallArgs A) {
   if (b >= 0) s_rank[b] = kept ? pos : -1;
   __syncthreads();
   // ---- the slice of every run whose trajectory is kept
-  if (tid < n_runs) {
-    const int64_t start = A.traj_seg_off[tid], end = A.traj_seg_off[tid + 1];
-    if (end > start) {
-      const int m = model_of_run(tid);
-      const int q = s_rank[last_le(tto, B, A.tok_turn[start])];
-      if (q >= 0) {
-        s_row[m * B + q] = (tid + 1 < s_run[m + 1] ? s_pos[tid + 1] : s_sel[m + 1]) - s_pos[tid];
-        s_src[m * B + q] = s_pos[tid];
-      }
+  if (end > start) {
+    const int m = model_of_run(tid);
+    const int q = s_rank[last_le(tto, B, turn)];
+    if (q >= 0) {
+      s_row[m * B + q] = (tid + 1 < s_run[m + 1] ? s_pos[tid + 1] : s_sel[m + 1]) - s_pos[tid];
+      s_src[m * B + q] = s_pos[tid];
     }
   }
   __syncthreads();
