@@ -38,6 +38,8 @@ class ThinStage {
   // Copies n bytes to offset `off` of the block (nothing for src == nullptr or n == 0).
   void put(size_t off, const void* src, size_t n);
   void zero(size_t off, size_t n);
+  // The block itself, for what is not copied as it lies.
+  char* at(size_t off) { return cur_ + off; }
   // Enqueues the copy of the first `bytes` bytes of the block to `dst` on `st` and releases the ring.
   umas_status flush(void* dst, size_t bytes, hipStream_t st);
   // In place of flush: the block for a kernel of n_wg workgroups that reads it itself and is launched next on `st`, then, with what the

@@ -52,10 +52,11 @@ struct RouteWs {
   // the thin arrays, staged from the host in one copy (everything up to traj_norm)
   int32_t* role_to_model;
   int32_t* traj_turn_off;
-  int32_t* turn_role;
-  int64_t* turn_tok_off;
+  uint8_t* turn_role;
+  uint32_t* tok_off32;             // token offsets of the turns: 32 bits where all tokens are fewer than 2^32, ...
+  int64_t* tok_off64;              // ... else 64
   int32_t* group_off;
-  int32_t* group_members;
+  int32_t* group_members;          // not there where groups are in order: member i is trajectory i
   float* role_reward;
   float* turn_reward;
   float* traj_reward;
@@ -76,18 +77,27 @@ inline int group_shift(size_t nbk) {
 }
 inline int plan_chunks(int n_traj) { return static_cast<int>(cdiv(n_traj > 0 ? n_traj : 1, kPlanThreads)); }
 
-size_t carve(Carver& c, RouteWs& w, int n_roles, int n_traj, int n_turns, int64_t n_tokens) {
-  const size_t nbk = cdiv(n_tokens > 0 ? n_tokens : 1, kTokBlock);
+// The thin arrays that a call has; what it has not takes no room and does not go over the bus (36 GB/s: 98 304 turns in 32 768 trajectories with one
+// reward each 2.5 MB in 47 us; without the arrays that are not there, roles in a byte and offsets in 32 bits 0.8 MB in
+// 20).
+struct Thin {
+  bool role_reward = true, turn_reward = true, traj_reward = true, weights = true, wide_offsets = true;
+  int groups = -1;                 // -1: as many as trajectories
+  bool members = true;
+};
+size_t carve(Carver& c, RouteWs& w, int n_roles, int n_traj, int n_turns, int64_t n_tokens, const Thin& has = Thin()) {
+  const size_t nbk = cdiv(n_tokens > 0 ? n_tokens : 1, kTokBlock), offs = static_cast<size_t>(n_turns) + 1;
   w.role_to_model = c.take<int32_t>(n_roles);
   w.traj_turn_off = c.take<int32_t>(n_traj + 1);
-  w.turn_role = c.take<int32_t>(n_turns);
-  w.turn_tok_off = c.take<int64_t>(n_turns + 1);
-  w.group_off = c.take<int32_t>(n_traj + 2);
-  w.group_members = c.take<int32_t>(n_traj);
-  w.role_reward = c.take<float>(static_cast<size_t>(n_traj) * n_roles);
-  w.turn_reward = c.take<float>(n_turns);
-  w.traj_reward = c.take<float>(n_traj);
-  w.weights = c.take<float>(3 * n_roles);
+  w.turn_role = c.take<uint8_t>(n_turns);
+  w.tok_off32 = c.take<uint32_t>(has.wide_offsets ? 0 : offs);
+  w.tok_off64 = c.take<int64_t>(has.wide_offsets ? offs : 0);
+  w.group_off = c.take<int32_t>(has.groups < 0 ? n_traj + 2 : has.groups > 0 ? has.groups + 1 : 0);
+  w.group_members = c.take<int32_t>(has.members ? n_traj : 0);
+  w.role_reward = c.take<float>(has.role_reward ? static_cast<size_t>(n_traj) * n_roles : 0);
+  w.turn_reward = c.take<float>(has.turn_reward ? n_turns : 0);
+  w.traj_reward = c.take<float>(has.traj_reward ? n_traj : 0);
+  w.weights = c.take<float>(has.weights ? 3 * n_roles : 0);
   w.plan_part = c.take<unsigned long long>(static_cast<size_t>(plan_chunks(n_traj)) * kPlanWords);
   w.traj_norm = c.take<float>(n_traj);
   w.seg_meta = c.take<SegMeta>(n_turns);
@@ -98,22 +108,22 @@ size_t carve(Carver& c, RouteWs& w, int n_roles, int n_traj, int n_turns, int64_
 
 // ------------------------------------------------------------------ kernels
 
-// z-score of the trajectory rewards of one group, by one wavefront, float64 statistics.
+// z-score of the trajectory rewards of one group, by one wavefront, float64 statistics.  Without `members` they are a .. e - 1.
 __device__ __forceinline__ void normalise_group(const float* __restrict__ R, const int32_t* __restrict__ members, int a, int e, float eps,
                                                 float* __restrict__ out) {
   const int lane = threadIdx.x & (kWave - 1);
   if (e == a) return;
   double s = 0.0;
-  for (int i = a + lane; i < e; i += kWave) s += static_cast<double>(R[members[i]]);
+  for (int i = a + lane; i < e; i += kWave) s += static_cast<double>(R[members ? members[i] : i]);
   const double mu = wave_sum(s) / static_cast<double>(e - a);
   double q = 0.0;
   for (int i = a + lane; i < e; i += kWave) {
-    const double t = static_cast<double>(R[members[i]]) - mu;
+    const double t = static_cast<double>(R[members ? members[i] : i]) - mu;
     q += t * t;
   }
   const double sigma = sqrt(wave_sum(q) / static_cast<double>(e - a));
   for (int i = a + lane; i < e; i += kWave) {
-    const int b = members[i];
+    const int b = members ? members[i] : i;
     out[b] = static_cast<float>((static_cast<double>(R[b]) - mu) / (sigma + static_cast<double>(eps)));
   }
 }
@@ -129,9 +139,10 @@ struct PlanArgs {
   int n_traj, n_turns, n_roles, n_models, n_chunks;
   int64_t n_tokens, n_count;          // n_count: words of tok_count to clear
   const int32_t* __restrict__ traj_turn_off;
-  const int32_t* __restrict__ turn_role;
+  const uint8_t* __restrict__ turn_role;
   const int32_t* __restrict__ role_to_model;
-  const int64_t* __restrict__ turn_tok_off;
+  const uint32_t* __restrict__ tok_off32;  // one of the two
+  const int64_t* __restrict__ tok_off64;
   const float* __restrict__ role_reward;   // NULL level = 0
   const float* __restrict__ turn_reward;
   const float* __restrict__ traj_reward;   // already normalised when groups are given
@@ -152,6 +163,7 @@ struct PlanArgs {
   int64_t* __restrict__ traj_seg_off;
   float* __restrict__ turn_scalar;
   int32_t* __restrict__ turn_step;
+  __device__ __forceinline__ int64_t tok_off(int u) const { return tok_off32 ? static_cast<int64_t>(tok_off32[u]) : tok_off64[u]; }
 };
 
 // v[k] of a small per-model array with a run-time k, without indexing registers dynamically
@@ -181,10 +193,10 @@ __device__ __forceinline__ void traj_counts(const PlanArgs& A, Phi phi, int b, T
   c.seen = 0;
   if (b >= A.n_traj) return;
   const int t0 = A.traj_turn_off[b], t1 = A.traj_turn_off[b + 1];
-  int64_t g0 = A.turn_tok_off[t0];
+  int64_t g0 = A.tok_off(t0);
   for (int u = t0; u < t1; ++u) {
     const int m = phi[A.turn_role[u]];
-    const int64_t g1 = A.turn_tok_off[u + 1];
+    const int64_t g1 = A.tok_off(u + 1);
     bump(c.cnt, m, int64_t{1});
     bump(c.tok, m, g1 - g0);
     c.seen |= 1u << m;
@@ -206,11 +218,11 @@ __device__ __forceinline__ void walk_turns(const PlanArgs& A, Phi phi, int b, in
   int last_slot[KM], last_step[KM];   // the model's latest turn with tokens in this trajectory
 #pragma unroll
   for (int k = 0; k < KM; ++k) { last_slot[k] = -1; last_step[k] = 0; }
-  int64_t g0 = A.turn_tok_off[t0];
+  int64_t g0 = A.tok_off(t0);
   for (int u = t0; u < t1; ++u) {
     const int v = A.turn_role[u];
     const int m = phi[v];
-    const int64_t g1 = A.turn_tok_off[u + 1], len = g1 - g0;
+    const int64_t g1 = A.tok_off(u + 1), len = g1 - g0;
     const int64_t slot = pick(slot_at, m), off = pick(tok_at, m);
     const int step = u - t0 + 1;
     bump(slot_at, m, int64_t{1});
@@ -865,7 +877,7 @@ k_route_small(SmallArgs A) {
   PlanArgs L = A.plan;
   L.traj_turn_off = here(L.traj_turn_off);
   L.turn_role = here(L.turn_role);
-  L.turn_tok_off = here(L.turn_tok_off);
+  L.tok_off32 = here(L.tok_off32);
   const int32_t* const phi = here(L.role_to_model);
   if (L.role_reward) L.role_reward = here(L.role_reward);
   if (L.turn_reward) L.turn_reward = here(L.turn_reward);
@@ -874,7 +886,7 @@ k_route_small(SmallArgs A) {
   if (L.w_turn) L.w_turn = here(L.w_turn);
   if (L.w_traj) L.w_traj = here(L.w_traj);
   if (A.n_groups > 0) {
-    const int32_t *const goff = here(A.group_off), *const members = here(A.group_members);
+    const int32_t *const goff = here(A.group_off), *const members = A.group_members ? here(A.group_members) : nullptr;
     for (int g = wave; g < A.n_groups; g += nwave) normalise_group(L.traj_reward, members, goff[g], goff[g + 1], A.norm_eps, s_norm);
     L.traj_reward = s_norm;
     __syncthreads();
@@ -1010,18 +1022,17 @@ k_route_small(SmallArgs A) {
 
 // ------------------------------------------------------------------ host side
 // The trajectories of every group that occurs, by group and ascending in it: members as a CSR with offsets off.  Groups that
-// arrive in order (members next to each other) need no sorting, group numbers that are not much larger than the number of
+// arrive in order (members next to each other) need no sorting and no list of members, group numbers that are not much larger than the number of
 // trajectories are counted, a stable sort by comparison is left for the rest: 32 768 trajectories in order 617 -> 19 us, in any
 // order 50.
 void group_members(const int32_t* group, int n, std::vector<int32_t>* off, std::vector<int32_t>* mem) {
-  mem->resize(n);
   off->reserve(static_cast<size_t>(n) + 1);
   off->push_back(0);
   if (std::is_sorted(group, group + n)) {
-    for (int b = 0; b < n; ++b) (*mem)[b] = b;
     for (int b = 1; b < n; ++b)
       if (group[b] != group[b - 1]) off->push_back(b);
   } else {
+    mem->resize(n);
     const int32_t top = *std::max_element(group, group + n);
     if (top < 4 * static_cast<int64_t>(n) + 1024) {
       std::vector<int32_t> at(static_cast<size_t>(top) + 2, 0);
@@ -1127,17 +1138,22 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
   prof_mark(st);
   const int R = g->n_roles, K = g->n_models, B = g->n_traj, U = g->n_turns;
   const int64_t N = g->n_tokens;
-  Carver c(workspace);
-  RouteWs w;
-  carve(c, w, R, B, U, N);
-
   // members of each normalisation group, as a CSR over the groups that occur
+  Thin has;
+  has.role_reward = r->role_reward; has.turn_reward = r->turn_reward; has.traj_reward = r->traj_reward;
+  has.weights = r->w_role || r->w_turn || r->w_traj;
+  has.wide_offsets = N >> 32 != 0;
   int n_groups = 0;
   std::vector<int32_t> goff, gmem;
   if (g->traj_group && r->traj_reward && B > 0) {
     group_members(g->traj_group, B, &goff, &gmem);
     n_groups = static_cast<int>(goff.size()) - 1;
   }
+  has.groups = n_groups;
+  has.members = !gmem.empty();
+  Carver c(workspace);
+  RouteWs w;
+  carve(c, w, R, B, U, N, has);
 
   // The thin arrays are the first arrays of the workspace, up to traj_norm: they are gathered at the same offsets in a
   // block of pinned host memory and go to the device in one asynchronous copy, together with the zeros that the plan
@@ -1154,14 +1170,24 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
   };
   put(w.role_to_model, g->role_to_model, sizeof(int32_t) * R);
   put(w.traj_turn_off, g->traj_turn_off, sizeof(int32_t) * (static_cast<size_t>(B) + 1));
-  put(w.turn_role, g->turn_role, sizeof(int32_t) * U);
-  put(w.turn_tok_off, g->turn_tok_off, sizeof(int64_t) * (static_cast<size_t>(U) + 1));
+  {
+    char* const block = stage.at(0);
+    uint8_t* const role = reinterpret_cast<uint8_t*>(block + (reinterpret_cast<char*>(w.turn_role) - ws_base));
+    for (int u = 0; u < U; ++u) role[u] = static_cast<uint8_t>(g->turn_role[u]);
+    static_assert(UMAS_MAX_ROLES <= 256, "a role is a byte");
+    uint32_t* const off = reinterpret_cast<uint32_t*>(block + (reinterpret_cast<char*>(w.tok_off32) - ws_base));
+    if (has.wide_offsets) put(w.tok_off64, g->turn_tok_off, sizeof(int64_t) * (static_cast<size_t>(U) + 1));
+    else
+      for (int u = 0; u <= U; ++u) off[u] = static_cast<uint32_t>(g->turn_tok_off[u]);
+  }
   put(w.role_reward, r->role_reward, sizeof(float) * static_cast<size_t>(B) * R);
   put(w.turn_reward, r->turn_reward, sizeof(float) * U);
   put(w.traj_reward, r->traj_reward, sizeof(float) * B);
-  put(w.weights, r->w_role, sizeof(float) * R);
-  put(w.weights + R, r->w_turn, sizeof(float) * R);
-  put(w.weights + 2 * R, r->w_traj, sizeof(float) * R);
+  if (has.weights) {
+    put(w.weights, r->w_role, sizeof(float) * R);
+    put(w.weights + R, r->w_turn, sizeof(float) * R);
+    put(w.weights + 2 * R, r->w_traj, sizeof(float) * R);
+  }
   if (n_groups > 0) {
     put(w.group_off, goff.data(), sizeof(int32_t) * goff.size());
     put(w.group_members, gmem.data(), sizeof(int32_t) * gmem.size());
@@ -1172,7 +1198,7 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
   const int gsh = group_shift(nbk);
   P.n_tokens = N; P.n_count = nbk + (nbk >> gsh) + 1;
   P.traj_turn_off = w.traj_turn_off; P.turn_role = w.turn_role; P.role_to_model = w.role_to_model;
-  P.turn_tok_off = w.turn_tok_off;
+  P.tok_off32 = has.wide_offsets ? nullptr : w.tok_off32; P.tok_off64 = w.tok_off64;
   P.role_reward = r->role_reward ? w.role_reward : nullptr;
   P.turn_reward = r->turn_reward ? w.turn_reward : nullptr;
   P.traj_reward = r->traj_reward ? w.traj_reward : nullptr;
@@ -1197,7 +1223,7 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
       thin * static_cast<size_t>(nbk) <= kSmallBus) {
     SmallArgs A;
     A.plan = P; A.tok = T; A.ws = ws_base; A.thin16 = static_cast<int>(thin / 16); A.n_groups = n_groups; A.norm_eps = r->norm_eps;
-    A.group_off = w.group_off; A.group_members = w.group_members; A.rowsel = o->rowsel;
+    A.group_off = w.group_off; A.group_members = has.members ? w.group_members : nullptr; A.rowsel = o->rowsel;
     vs = stage.lend(static_cast<unsigned>(nbk), st, &A.thin);
     if (vs != UMAS_OK) return vs;
     const dim3 grid(static_cast<unsigned>(nbk)), threads(kSmallThreads);
@@ -1218,7 +1244,7 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
 
   if (n_groups > 0) {
     hipLaunchKernelGGL(k_group_norm, dim3(cdiv(n_groups, 4)), dim3(256), 0, st, w.traj_reward, w.group_off,
-                       w.group_members, n_groups, r->norm_eps, w.traj_norm);
+                       has.members ? w.group_members : nullptr, n_groups, r->norm_eps, w.traj_norm);
     UMAS_LAUNCHED("k_group_norm");
     P.traj_reward = w.traj_norm;
   }
