@@ -174,3 +174,19 @@ def test_critic_defines_the_rows_that_are_not_selected(n, n_sel, shift, dtype):
     kept[sel.long()] = 0
     umas.umas_value_loss_fwd_bwd(H, w, 0.5, sel, old, ret, None, 0, 1e9, dH=kept, accumulate_dH=True)
     assert torch.equal(kept[sel.long()], dH[sel.long()]) and kept[rest].isnan().all()
+
+
+@pytest.mark.parametrize("shape", ["alike", "front", "back", "blocks", "none"])
+@pytest.mark.parametrize("n_models", [1, 3])
+def test_ready_batch_of_masks_that_are_not_alike(shape, n_models):
+    """The guesses at a run's first row and at a turn's trajectory, where the density of scored tokens or of turns says little."""
+    n_traj, rng = 3000, np.random.default_rng(5)
+    w = sized_graph(11, 500000, 9000, n_traj, n_models, n_models + 1, 0)
+    if shape != "alike":                                 # trajectories of very different numbers of turns
+        cuts = np.sort(rng.choice([0, 1, 2, 4500, 8999, 9000], n_traj - 1))
+        w.traj_turn_off = np.concatenate([[0], cuts, [9000]]).astype(np.int32)
+    at = np.arange(w.n_tokens)
+    w.tok_mask = {"alike": rng.random(w.n_tokens) < 0.8, "front": at < 7000, "back": at > w.n_tokens - 7000, "blocks": at // 30000 % 3 == 0,
+                  "none": at < 0}[shape].astype(np.uint8)
+    s = route(w, wl.PLACE_LAST)
+    check_ready_batch_arraywise(w, s, aw.streams(w), (rng.random(n_traj) < 0.9).astype(np.uint8), rng.permutation(n_traj).astype(np.int32), 5)
