@@ -609,12 +609,12 @@ k_ppo_rows(Surrogate S, int64_t n_begin, int64_t n_end, const float* __restrict_
   }
 }
 
-// One workgroup for the model and one for each role.
-__global__ void __launch_bounds__(256)
-k_ppo_stats(int nblk, int n_roles, float entropy_coef, int64_t norm_rows, const double* __restrict__ blk_stats,
+// The record of the model (k = 0) or of a role, a workgroup to each.
+__device__ __forceinline__ void
+ppo_stats(int k, int nblk, int n_roles, float entropy_coef, int64_t norm_rows, const double* __restrict__ blk_stats,
             umas_loss_stats* __restrict__ stats) {
   __shared__ double smem[32];
-  const int nacc = (1 + n_roles) * kStat, k = blockIdx.x;
+  const int nacc = (1 + n_roles) * kStat;
   double v[kStat] = {}, sum[kStat];
   for (int b = threadIdx.x; b < nblk; b += blockDim.x)
 #pragma unroll
@@ -1282,14 +1282,14 @@ k_gemm_dh_dw(const uint16_t* __restrict__ dZ, int blk_pitch, int64_t Vp, int64_t
 
 // The slices' partial sums of dH added up in slice order, with what the tile epilogue does otherwise: row factor, one-hot
 // part, bf16 row through the selection.  One workgroup per (row of the live blocks, 1024 columns), four columns a thread.
-__global__ void __launch_bounds__(256)
-k_dh_reduce(DhSlices sl, int tiles_r, int tiles_d, const uint16_t* __restrict__ W, int d, const LiveInfo* __restrict__ info,
-            const int32_t* __restrict__ blk_orig, uint16_t* __restrict__ dH, const int32_t* __restrict__ rowsel, int64_t c0,
-            int64_t rows, const int32_t* __restrict__ ids, const float* __restrict__ g_c, const float* __restrict__ sc) {
-  const int tile_m = blockIdx.x >> 8, r = blockIdx.x & 255;
+__device__ __forceinline__ void
+dh_reduce(int live_row, int piece, const DhSlices& sl, int tiles_r, int tiles_d, const uint16_t* __restrict__ W, int d, const LiveInfo* __restrict__ info,
+          const int32_t* __restrict__ blk_orig, uint16_t* __restrict__ dH, const int32_t* __restrict__ rowsel, int64_t c0,
+          int64_t rows, const int32_t* __restrict__ ids, const float* __restrict__ g_c, const float* __restrict__ sc) {
+  const int tile_m = live_row >> 8, r = live_row & 255;
   if (tile_m >= info->n_live) return;
   const int64_t m = static_cast<int64_t>(blk_orig[(c0 >> 8) + tile_m]) * 256 + r;
-  const int j = (blockIdx.y * 256 + threadIdx.x) * 4;
+  const int j = (piece * 256 + static_cast<int>(threadIdx.x)) * 4;
   if (m >= rows || j >= d) return;
   const float* src = sl.part + (static_cast<int64_t>(tile_m) * tiles_d + (j >> 8)) * 65536 + r * 256 + (j & 255);
   const int64_t stride = static_cast<int64_t>(tiles_r) * tiles_d * 65536;
@@ -1325,9 +1325,9 @@ constexpr int kOneHotRows = 128;
 constexpr int kOneHotPieces = 4;                    // pieces of 512 columns a wavefront holds at a time
 constexpr int kOneHotAhead = 4;                     // rows a wavefront loads together
 static_assert(kOneHotRows == 2 * kWave, "the rows of a token are two ballots");
-__global__ void __launch_bounds__(256)
-k_dw_onehot(const uint16_t* __restrict__ H, int d, const int32_t* __restrict__ rowsel, int64_t n_sel,
-            const int32_t* __restrict__ ids, const float* __restrict__ g_c, float* __restrict__ dW) {
+__device__ __forceinline__ void
+dw_onehot(int group, int part, int parts, const uint16_t* __restrict__ H, int d, const int32_t* __restrict__ rowsel, int64_t n_sel,
+          const int32_t* __restrict__ ids, const float* __restrict__ g_c, float* __restrict__ dW) {
   __shared__ __attribute__((aligned(16))) int32_t s_id[kOneHotRows];   // token of the row, -1 when the row adds nothing
   __shared__ float s_g[kOneHotRows];
   __shared__ int64_t s_row[kOneHotRows];
@@ -1336,7 +1336,7 @@ k_dw_onehot(const uint16_t* __restrict__ H, int d, const int32_t* __restrict__ r
   __shared__ float s_turn[256 / kWave][8 * kWave];  // one piece per wavefront, in column order
   const int tid = threadIdx.x, lane = tid & 63, wave = tid / kWave;
   if (tid < kOneHotRows) {
-    const int64_t n = static_cast<int64_t>(blockIdx.x) * kOneHotRows + tid;
+    const int64_t n = static_cast<int64_t>(group) * kOneHotRows + tid;
     float g = 0.f;
     int64_t row = 0;
     int32_t id = -1;
@@ -1368,8 +1368,8 @@ k_dw_onehot(const uint16_t* __restrict__ H, int d, const int32_t* __restrict__ r
   if (leader) s_leader[before + __popcll(leaders & ((1ull << lane) - 1))] = tid;
   __syncthreads();
   float* turn = s_turn[wave];
-  // the group's tokens are spread over the wavefronts of gridDim.y workgroups
-  for (int li = wave + blockIdx.y * (256 / kWave); li < n_leader; li += 256 / kWave * gridDim.y) {
+  // the group's tokens are spread over the wavefronts of `parts` workgroups
+  for (int li = wave + part * (256 / kWave); li < n_leader; li += 256 / kWave * parts) {
     const int32_t id = s_id[s_leader[li]];
     float* dst = dW + static_cast<int64_t>(id) * d;
     unsigned long long same[kOneHotRows / kWave];   // the rows of the group that took this token
@@ -1432,6 +1432,51 @@ k_dw_onehot(const uint16_t* __restrict__ H, int d, const int32_t* __restrict__ r
       }
     }
   }
+}
+
+// What is left of an update when its products are there, in one launch, as none of it needs the other: the one-hot part of dW,
+// the statistics, and the sum of the slices of dH.  The longest first: it is chains of loads, which the sum's bytes hide behind.
+// 203 rows of 3584 against 152 064: launches of 18 to 23, 5 and 12 us, in one 24 to 27.
+struct CloseArgs {
+  unsigned onehot_groups, onehot_parts;   // workgroups of dw_onehot; 0: none
+  const uint16_t* H;
+  int d;
+  const int32_t* rowsel;
+  int64_t n_sel;
+  const int32_t* ids;
+  const float* g_c;
+  float* dW;
+  unsigned n_stats;                       // workgroups of ppo_stats; 0: none
+  int nblk, n_roles;
+  float entropy_coef;
+  int64_t norm_rows;
+  const double* blk_stats;
+  umas_loss_stats* stats;
+  unsigned reduce_rows, reduce_pieces;    // workgroups of dh_reduce; 0: none
+  DhSlices sl;
+  int tiles_r, tiles_d;
+  const uint16_t* W;
+  const LiveInfo* info;
+  const int32_t* blk_orig;
+  uint16_t* dH;
+  int64_t c0, rows;
+  const float* sc;
+};
+__global__ void __launch_bounds__(256)
+k_update_close(CloseArgs A) {
+  unsigned i = blockIdx.x;
+  if (i < A.onehot_groups * A.onehot_parts) {
+    dw_onehot(i % A.onehot_groups, i / A.onehot_groups, A.onehot_parts, A.H, A.d, A.rowsel, A.n_sel, A.ids, A.g_c, A.dW);
+    return;
+  }
+  i -= A.onehot_groups * A.onehot_parts;
+  if (i < A.n_stats) {
+    ppo_stats(i, A.nblk, A.n_roles, A.entropy_coef, A.norm_rows, A.blk_stats, A.stats);
+    return;
+  }
+  i -= A.n_stats;
+  dh_reduce(i % A.reduce_rows, i / A.reduce_rows, A.sl, A.tiles_r, A.tiles_d, A.W, A.d, A.info, A.blk_orig, A.dH, A.rowsel, A.c0, A.rows,
+            A.ids, A.g_c, A.sc);
 }
 
 // ------------------------------------------------------------------ host side
@@ -1510,7 +1555,7 @@ bool f32_few_launches(int64_t n_sel, int d, int V, size_t room) {
 // each; with few row tiles that is fewer long tiles than compute units, and the launch lasts as long as one of them (3.6 ms
 // at V = 151 936 whether there are 64 rows or 2000).  Below kDhSliceTiles, one tile per compute unit, they are cut into about
 // 256 / tiles slices, a piece per compute unit (the dW tiles behind them fill the last round); partial sums cost 256 KB a
-// piece.  Gradients and k_dh_reduce together with 256 / 384 / 512 / 768 pieces: 64 rows of 2048 467 / 460 / 480 / 488 us, 203 rows
+// piece.  Gradients and the sum of the slices together with 256 / 384 / 512 / 768 pieces: 64 rows of 2048 467 / 460 / 480 / 488 us, 203 rows
 // of 3584 859 / 875 / 869 / 892, 725 rows of 2048 947 / 956 / 959 / 984, 6000 rows 5.91 / 5.90 / 5.98 / 5.90 ms; whole
 // tiles took 3.6 to 4 ms for the first three.  A selection that a small workspace cuts into chunks keeps whole tiles, and so the
 // same bits of dH, down to chunks of half as many tiles (39 224 rows of 2048, whole and sliced: chunks of 256 tiles 57.8 and
@@ -1936,6 +1981,37 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     const DhPlan p = plan_dh(tiles_r, tiles_d, tiles_v, slices_dh(n_sel, mc, d) ? std::max(behind, front) : 0);
     *sl = DhSlices{p.slices, p.voc_blks, behind > front ? reinterpret_cast<float*>(w.chunk + used) : reinterpret_cast<float*>(w.score.partial)};
   };
+  CloseArgs rest{};
+  rest.H = Hb;
+  rest.W = Wb;
+  rest.d = d;
+  rest.rowsel = rowsel;
+  rest.n_sel = n_sel;
+  rest.ids = ids;
+  rest.g_c = w.g_c;
+  rest.dW = dW;
+  rest.n_stats = 1 + n_roles;
+  rest.nblk = nblk;
+  rest.n_roles = n_roles;
+  rest.entropy_coef = entropy_coef;
+  rest.norm_rows = norm_rows;
+  rest.blk_stats = w.blk_stats;
+  rest.stats = stats;
+  rest.info = w.live;
+  rest.blk_orig = w.blk_orig;
+  rest.dH = static_cast<uint16_t*>(dH);
+  if (dtype == UMAS_BF16 && n_sel > 0) {
+    const dim3 grid = onehot_grid(n_sel);
+    rest.onehot_groups = grid.x;
+    rest.onehot_parts = grid.y;
+  }
+  auto close = [&](const CloseArgs& C) -> umas_status {
+    const unsigned grid = C.onehot_groups * C.onehot_parts + C.n_stats + C.reduce_rows * C.reduce_pieces;
+    if (grid == 0) return UMAS_OK;
+    hipLaunchKernelGGL(k_update_close, dim3(grid), dim3(256), 0, st, C);
+    UMAS_LAUNCHED("k_update_close");
+    return UMAS_OK;
+  };
   auto gradients = [&](int64_t c0, int64_t rows, const DhSlices& sl, const uint16_t* op, int blk_pitch, const uint16_t* Hs, const float* sc) -> umas_status {
     const int64_t mcp = round_up(rows, 256);
     const int tiles_r = static_cast<int>(mcp / 256), tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
@@ -1944,12 +2020,19 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
                        tiles_d, sl, tiles_r, w.live, w.blk_orig, static_cast<uint16_t*>(dH), dW, (accumulate_dW || c0 > 0) ? 1 : 0,
                        rowsel, c0, rows, ids, w.g_c, sc);
     UMAS_LAUNCHED("k_gemm_dh_dw");
+    CloseArgs C = rest;                                  // a chunk's slices are added up before the next one's are written
+    if (c0 + rows < n_sel) C.onehot_groups = C.n_stats = 0;
     if (sl.n > 1) {
-      hipLaunchKernelGGL(k_dh_reduce, dim3(static_cast<unsigned>(mcp), cdiv(d, 1024)), dim3(256), 0, st, sl, tiles_r, tiles_d, Wb, d, w.live,
-                         w.blk_orig, static_cast<uint16_t*>(dH), rowsel, c0, rows, ids, w.g_c, sc);
-      UMAS_LAUNCHED("k_dh_reduce");
+      C.reduce_rows = static_cast<unsigned>(mcp);
+      C.reduce_pieces = cdiv(d, 1024);
+      C.sl = sl;
+      C.tiles_r = tiles_r;
+      C.tiles_d = tiles_d;
+      C.c0 = c0;
+      C.rows = rows;
+      C.sc = sc;
     }
-    return UMAS_OK;
+    return close(C);
   };
 
   // With one the logits are kept instead where the workspace allows it.
@@ -2013,20 +2096,10 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       if (s != UMAS_OK) return s;
     }
   }
-  auto ppo_stats = [&]() -> umas_status {
-    hipLaunchKernelGGL(k_ppo_stats, dim3(1 + n_roles), dim3(256), 0, st, nblk, n_roles, entropy_coef, norm_rows, w.blk_stats, stats);
-    UMAS_LAUNCHED("k_ppo_stats");
-    return UMAS_OK;
-  };
-  if (mc_z == 0) {
-    s = ppo_stats();
-    if (s != UMAS_OK) return s;
-  }
-  if (n_sel == 0) return UMAS_OK;
-  if (keep) {
-    hipLaunchKernelGGL(k_dw_onehot, onehot_grid(n_sel), dim3(256), 0, st, Hb, d, rowsel, n_sel, ids, w.g_c, dW);
-    UMAS_LAUNCHED("k_dw_onehot");
-    return UMAS_OK;
+  if (keep) return UMAS_OK;
+  if (dtype == UMAS_F32 || n_sel == 0) {
+    s = close(rest);                                     // only the statistics
+    if (s != UMAS_OK || n_sel == 0) return s;
   }
 
   if (dtype == UMAS_F32) {
@@ -2085,11 +2158,5 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     s = gradients(c0, rows, sl, dZ, blk_pitch, Hs, nullptr);
     if (s != UMAS_OK) return s;
   }
-  if (mc_z > 0) {
-    s = ppo_stats();
-    if (s != UMAS_OK) return s;
-  }
-  hipLaunchKernelGGL(k_dw_onehot, onehot_grid(n_sel), dim3(256), 0, st, Hb, d, rowsel, n_sel, ids, w.g_c, dW);
-  UMAS_LAUNCHED("k_dw_onehot");
   return UMAS_OK;
 }

@@ -11,6 +11,7 @@ from oracle import umas_oracle as orc
 from tests import arraywise as aw
 from tests import parity as P
 from tests.test_gpu_large import check_front_arraywise, check_ready_batch_arraywise
+from tests.test_gpu_sizes import check_update
 
 pytestmark = pytest.mark.gpu
 
@@ -190,3 +191,12 @@ def test_ready_batch_of_masks_that_are_not_alike(shape, n_models):
                   "none": at < 0}[shape].astype(np.uint8)
     s = route(w, wl.PLACE_LAST)
     check_ready_batch_arraywise(w, s, aw.streams(w), (rng.random(n_traj) < 0.9).astype(np.uint8), rng.permutation(n_traj).astype(np.int32), 5)
+
+
+# chunks of 256 rows, each with slices of dH that are added up before the next chunk's; the last chunk's go with the rest of the update
+@pytest.mark.parametrize("n,d,V", [(257, 64, 3000), (600, 1032, 1300)])
+@pytest.mark.parametrize("entropy_coef", [0.0, 0.01])
+def test_update_with_slices_in_several_chunks(n, d, V, entropy_coef):
+    nbytes = umas.ppo_workspace_bytes(n, d, V, torch.bfloat16, 0, minimum=True) + 3 * -(-d // 256) * (256 * 256 * 4)
+    check_update(np.random.default_rng(n), n, d, V, select=1.0, entropy_coef=entropy_coef, accumulate=True,
+                 workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
