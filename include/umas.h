@@ -19,10 +19,10 @@
  *   - All work is enqueued on `hip_stream` (a hipStream_t passed as void*; NULL = default
  *     stream).  No call waits for the stream.  umas_assign_token_rewards and umas_ready_batch
  *     gather their thin host arrays in a block of pinned host memory that the library keeps (a
- *     ring of four blocks, each as large as the largest graph it has seen) and enqueue one
- *     asynchronous copy of it: the caller may free or overwrite its arrays on return, and the
+ *     ring of four blocks, each as large as the largest graph it has seen) and enqueue a kernel
+ *     that reads it over the bus: the caller may free or overwrite its arrays on return, and the
  *     host can queue the next step while this one runs.  The one wait there is: a block is
- *     reused four such calls later, after the copy that was issued from it has run.  Results,
+ *     reused four such calls later, after the kernel that was launched on it has read it.  Results,
  *     including loss statistics, stay on the device.  Every other call only launches kernels
  *     (memory is cleared by fill kernels, never by memset nodes), so it may be recorded into a
  *     HIP graph as long as profiling (umas_profile_enable) is off.

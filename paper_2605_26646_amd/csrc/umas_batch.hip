@@ -610,9 +610,9 @@ umas_status ready_batch(const umas_streams* s, int32_t n_models, int32_t n_turns
   Carver c(workspace);
   BatchWs w;
   carve_batch(c, w, n_traj, n_models);
-  // the thin arrays (the first arrays of the workspace, up to rank) go through pinned staging memory in one
-  // asynchronous copy, together with the zeros that the first kernel's tile counts start from: they have been read
-  // when the call returns, and the host does not wait for the stream
+  // the thin arrays (the first arrays of the workspace, up to rank) go through pinned staging memory, from where one
+  // kernel takes them over the bus, together with the zeros that the first kernel's tile counts start from: they have been
+  // read when the call returns, and the host does not wait for the stream
   char* const ws_base = static_cast<char*>(workspace);
   const size_t staged_bytes = static_cast<size_t>(reinterpret_cast<char*>(w.rank) - ws_base);
   const int ntile = scan_tiles(n_traj);

@@ -1156,7 +1156,7 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
   carve(c, w, R, B, U, N, has);
 
   // The thin arrays are the first arrays of the workspace, up to traj_norm: they are gathered at the same offsets in a
-  // block of pinned host memory and go to the device in one asynchronous copy, together with the zeros that the plan
+  // block of pinned host memory, from where one kernel takes them over the bus, together with the zeros that the plan
   // kernel's per-chunk totals start from.  The host arrays have been read when the call returns; the host does not
   // wait for the stream.
   char* const ws_base = static_cast<char*>(workspace);
