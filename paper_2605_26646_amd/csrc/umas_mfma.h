@@ -244,10 +244,11 @@ struct KContig {                // an operand tile stored K-contiguous: per-slot
   uint32_t hi_bytes;            // added once more per 256 k (an operand stored in blocks of 256 columns), else 0
 };
 
-// B_STREAM: operand B is read once, past the caches
-template <class C, bool ATR, bool BTR, int AHEAD, bool B_STREAM = false>
+// B_STREAM: operand B is read once, past the caches.  CUT: only m_rows rows of the tile are looked at; a wavefront whose sub-tile has none of
+// them loads for the others and multiplies nothing.
+template <class C, bool ATR, bool BTR, int AHEAD, bool B_STREAM = false, bool CUT = false>
 __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMajor& ka, const KContig& cb, const KMajor& kb,
-                                                    int K, uint16_t* lds, floatx4 (&acc)[C::MI][C::NI]) {
+                                                    int K, uint16_t* lds, floatx4 (&acc)[C::MI][C::NI], int m_rows = C::BM) {
   using R = Ring2Cfg<C>;
   static_assert(C::BM == 256 && C::BN == 256 && C::T == 512 && R::NA == 4 && R::NB == 4, "written for 256x256 tiles, 8 wavefronts");
   constexpr int HA = C::MI / 2;                      // A blocks of one half of the wavefront's sub-tile
@@ -409,10 +410,29 @@ __device__ __forceinline__ void mfma_mainloop_mixed(const KContig& ca, const KMa
   if (AHEAD == 2) gload_b(clamp_sub(1), 1);
   __builtin_amdgcn_s_waitcnt(0x0070);
   __builtin_amdgcn_s_barrier();
-  fload_b(0, 0, I0{});
-  fload_a(0, 0, I0{}, I0{});
   auto next3 = [](int i) { return i == 2 ? 0 : i + 1; };
   int ia = 0, ib = 0;                                // stages of the current step
+  if (CUT && wm * C::WTM >= m_rows) {                // the loads and barriers of the loop below
+    for (int j = 0; j < nsub; ++j) {
+      const int ia1 = AHEAD == 1 ? next3(ia) : (ia ^ 1), ib1 = AHEAD == 2 ? next3(ib) : (ib ^ 1);
+      if (AHEAD == 1) {
+        gload_b(clamp_sub(j + 1), ib1);
+        gload_a(clamp_sub(j + 2), next3(ia1));
+      } else {
+        gload_a(clamp_sub(j + 1), ia1);
+        gload_b(clamp_sub(j + 2), next3(ib1));
+      }
+      __builtin_amdgcn_s_waitcnt(0x0074);
+      __builtin_amdgcn_s_barrier();
+      ia = ia1;
+      ib = ib1;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);
+    __builtin_amdgcn_s_barrier();
+    return;
+  }
+  fload_b(0, 0, I0{});
+  fload_a(0, 0, I0{}, I0{});
   for (int j = 0; j < nsub; ++j) {
     const int ia1 = AHEAD == 1 ? next3(ia) : (ia ^ 1);              // stages of the next step
     const int ib1 = AHEAD == 2 ? next3(ib) : (ib ^ 1);

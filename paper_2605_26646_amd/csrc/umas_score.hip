@@ -136,8 +136,12 @@ constexpr int64_t kBlkElems = 256 * 256;
 __host__ __device__ __forceinline__ int64_t blk_offset(int64_t row_blk, int64_t voc_blk, int64_t tiles_v) {
   return (row_blk * tiles_v + voc_blk) * kBlkElems;
 }
-constexpr int kStagePitch = Cfg::WTM * 2 + 16;                                  // one staged row: 128 bf16, 16-byte aligned
-constexpr int kStageBytes = Cfg::WM * Cfg::WN * Cfg::WTN * kStagePitch;         // every wavefront stages its block: 64 rows x 128 vocabulary entries
+template <class C>
+struct Stage {                                                                  // every wavefront stages its block: WTN rows x WTM vocabulary entries
+  static constexpr int kPitch = C::WTM * 2 + 16;                                // one staged row of bf16, 16-byte aligned
+  static constexpr int kBytes = C::WM * C::WN * C::WTN * kPitch;
+};
+constexpr int kStagePitch = Stage<Cfg>::kPitch, kStageBytes = Stage<Cfg>::kBytes;
 constexpr int kPartBytes = (Cfg::WM * Cfg::BN * 3 + Cfg::BN) * 4;
 constexpr int kLogitPitch = Cfg::WTM * 4 + 16;                                  // one staged row of logits: 128 floats
 static_assert(16 * kLogitPitch <= Cfg::WTN * kStagePitch, "sixteen rows of logits fit a wavefront's stage");
@@ -161,22 +165,25 @@ __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, cons
                                             float4* __restrict__ partial, int64_t n_pad, const KeepArgs& keep,
                                             uint16_t* lds) {
   constexpr bool KEEP = LEAVE == Leave::kNumerators;
-  static_assert(LEAVE == Leave::kNothing || C::BM * C::BN == Cfg::BM * Cfg::BN, "what is kept lies in whole blocks");
+  static_assert(LEAVE != Leave::kLogits || C::BM * C::BN == Cfg::BM * Cfg::BN, "logits are kept in whole blocks");
+  static_assert(256 % C::BM == 0 && 256 % C::BN == 0, "numerators are kept inside a block");
+  constexpr int kPitch = Stage<C>::kPitch;
   for (int it = 0; it < kTilesPerWg; ++it) {     // a workgroup walks the same place of kTilesPerWg consecutive tile groups
   int tile_m, tile_n;
   if (!tile_coords<kGM, kGN>(tiles_m, tiles_n, panel, &tile_m, &tile_n, it, kTilesPerWg)) continue;
   const int m0 = tile_m * C::BM;
   const int64_t n0 = static_cast<int64_t>(tile_n) * C::BN;   // chunk-relative
   floatx4 acc[C::MI][C::NI];
-  logit_tile<C>(W, H, d, V, rowsel, c0, mc, m0, n0, tiles_n == 1 && beyond_cache(d, V, kLogitsOnceBytes), lds, acc);
+  // (a tile that lies past V as a whole, the second half of a block that is kept, reads the last entry)
+  logit_tile<C>(W, H, d, V, rowsel, c0, mc, min(m0, V - 1), n0, tiles_n == 1 && beyond_cache(d, V, kLogitsOnceBytes), lds, acc);
 
   // epilogue: the tile buffers are free now.  A lane holds, for each of its NI columns (selected rows), the
   // vocabulary entries vbase + 16 i + r (i < MI, r < 4); the four lanes l, l + 16, l + 32, l + 48 share a column.
-  float* s_part = reinterpret_cast<float*>(reinterpret_cast<char*>(lds) + (LEAVE == Leave::kNothing ? 0 : kStageBytes));   // [WM][BN][3], behind the staging area
+  float* s_part = reinterpret_cast<float*>(reinterpret_cast<char*>(lds) + (LEAVE == Leave::kNothing ? 0 : Stage<C>::kBytes));   // [WM][BN][3], behind the staging area
   float* s_zy = s_part + C::WM * C::BN * 3;               // [BN]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / C::WN;
-  char* stage = reinterpret_cast<char*>(lds) + wave * (LEAVE == Leave::kLogits ? 16 * kLogitPitch : C::WTN * kStagePitch);
+  char* stage = reinterpret_cast<char*>(lds) + wave * (LEAVE == Leave::kLogits ? 16 * kLogitPitch : C::WTN * kPitch);
   if (threadIdx.x < C::BN) s_zy[threadIdx.x] = 0.f;
   __syncthreads();                                        // every wavefront has left the main loop's LDS reads
   const int vbase = m0 + wm * C::WTM + (lane >> 4) * 4;   // vocabulary id of element (i = 0, r = 0)
@@ -193,7 +200,8 @@ __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, cons
   constexpr float kLog2e = 1.44269504088896341f;
   bool over = false;
   // a block of rows none of which has a gradient (all advantages 0) keeps nothing: the backward never looks at it
-  const int out_blk = KEEP ? keep.cidx[(c0 >> 8) + tile_n] : -1;
+  const int64_t row_blk = (c0 + n0) >> 8;
+  const int out_blk = KEEP ? keep.cidx[row_blk] : -1;
   const bool keeping = KEEP && out_blk >= 0;
 #pragma unroll
   for (int j = 0; j < C::NI; ++j) {
@@ -219,7 +227,7 @@ __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, cons
         }
         if (keeping) {
           const uint32_t p01 = pack_bf16x2(e[0], e[1]), p23 = pack_bf16x2(e[2], e[3]);
-          *reinterpret_cast<uint2*>(stage + (j * 16 + (lane & 15)) * kStagePitch + (i * 16 + (lane >> 4) * 4) * 2) =
+          *reinterpret_cast<uint2*>(stage + (j * 16 + (lane & 15)) * kPitch + (i * 16 + (lane >> 4) * 4) * 2) =
               make_uint2(p01, p23);
         }
       }
@@ -295,14 +303,15 @@ __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, cons
     }
   }
   if (keeping) {
-    if (over) keep.flags[(c0 >> 8) + tile_n] = 1;
-    // the staged block goes out 16 bytes per lane: one instruction covers 4 rows x 256 contiguous bytes
+    if (over) keep.flags[row_blk] = 1;
+    // the staged block goes out 16 bytes per lane: one instruction covers 4 rows x 256 contiguous bytes (of 64 entries a row, 8 x 128)
+    constexpr int kLanes = C::WTM / 8, kRows = kWave / kLanes;
     const int wn = wave % C::WN;
-    uint16_t* out = keep.E + blk_offset(out_blk, tile_m, keep.Vp >> 8) + (wn * C::WTN) * 256 + wm * C::WTM + (lane & 15) * 8;
+    uint16_t* out = keep.E + blk_offset(out_blk, m0 >> 8, keep.Vp >> 8) + ((n0 & 255) + wn * C::WTN) * 256 + (m0 & 255) + wm * C::WTM + lane % kLanes * 8;
 #pragma unroll 8
-    for (int i = 0; i < C::WTN / 4; ++i) {
-      const int row = i * 4 + (lane >> 4);
-      const uint4 v = *reinterpret_cast<const uint4*>(stage + row * kStagePitch + (lane & 15) * 16);
+    for (int i = 0; i < C::WTN / kRows; ++i) {
+      const int row = i * kRows + lane / kLanes;
+      const uint4 v = *reinterpret_cast<const uint4*>(stage + row * kPitch + lane % kLanes * 16);
       typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
       __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4*>(out + row * 256));
     }
@@ -350,6 +359,17 @@ k_score_keep_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ 
                    const int32_t* __restrict__ cidx) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[kLogitLds / 2];
   score_tiles<Leave::kNumerators, Cfg>(W, H, d, V, rowsel, c0, mc, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{cref, E, Vp, flags, cidx, nullptr}, lds);
+}
+// ... and what an update of so few rows keeps: half rows of half blocks of the operand, whose other rows are never read (100 rows of 3584 270 -> 211
+// us; the update, with shorter sums for dW and half the products for dH, 1000 -> 887, of 2048 608 -> 518).
+static_assert(Stage<NarrowCfg>::kBytes + (NarrowCfg::WM * NarrowCfg::BN * 3 + NarrowCfg::BN) * 4 <= kNarrowLds, "staging and the partials fit");
+__global__ void __launch_bounds__(NarrowCfg::T)
+k_score_keep_narrow(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
+                    const int32_t* __restrict__ rowsel, int64_t n_sel, const int32_t* __restrict__ ids,
+                    int tiles_m, float4* __restrict__ partial, int64_t n_pad, const float* __restrict__ cref, uint16_t* __restrict__ E, int64_t Vp,
+                    int32_t* __restrict__ flags, const int32_t* __restrict__ cidx) {
+  __shared__ __attribute__((aligned(16))) uint16_t lds[kNarrowLds / 2];
+  score_tiles<Leave::kNumerators, NarrowCfg>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, 1, kGN, partial, n_pad, KeepArgs{cref, E, Vp, flags, cidx, nullptr}, lds);
 }
 __global__ void __launch_bounds__(Cfg::T)
 k_score_logits(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
@@ -646,6 +666,10 @@ __device__ __forceinline__ int dh_first(int tiles_dh, int slices, int xcd) {
   const int unit = share_unit(tiles_dh, slices), units = (tiles_dh + unit - 1) / unit;
   return min(static_cast<int>(static_cast<int64_t>(units) * xcd / 8) * unit, tiles_dh);
 }
+// K of the dW tiles: whole steps of 64 rows.  (With whole blocks of 256, and dH tiles that read and
+// multiply the rows that are not there as well: both products of 30 / 100 rows of 3584 672 us, now 612 / 620; update of 300 / 550 rows of 2048 976 / 1327,
+// now 890 / 1252.)
+__device__ __forceinline__ int dw_k(int k_rows) { return (k_rows + 63) / 64 * 64; }
 // Called by one wavefront; lane x of every eight works for XCD x (all eights do the same).  (One thread walking the eight XCDs took 20 us.)
 __device__ void share_dw(int tiles_r, int tiles_v, int tiles_d, int64_t Vp, int slices, int64_t k_len, XcdShares* out) {
   const int x = threadIdx.x & 7;
@@ -733,13 +757,14 @@ k_live_scan(int blk0, int nblk, int64_t rows, int all_live, int tiles_v, int til
   __shared__ int s_last_live;
   if (t == nblk - 1) s_last_live = live;
   __syncthreads();
+  const int64_t last_rows = rows - static_cast<int64_t>(nblk - 1) * 256;       // rows of the chunk's last block
+  const int k_rows = static_cast<int>(s_last_live ? static_cast<int64_t>(total - 1) * 256 + last_rows : static_cast<int64_t>(total) * 256);
   if (t == 0) {
     info->n_live = total;
-    const int64_t last_rows = rows - static_cast<int64_t>(nblk - 1) * 256;     // rows of the chunk's last block
-    info->k_rows = static_cast<int32_t>(s_last_live ? static_cast<int64_t>(total - 1) * 256 + last_rows : static_cast<int64_t>(total) * 256);
+    info->k_rows = k_rows;
   }
   if (t < 8) info->next[t] = 0;
-  if (t < kWave) share_dw(total, tiles_v, tiles_d, Vp, slices, total > 0 ? static_cast<int64_t>(total) * 256 + kTileOverheadK : 0, &info->dw);
+  if (t < kWave) share_dw(total, tiles_v, tiles_d, Vp, slices, total > 0 ? dw_k(k_rows) + kTileOverheadK : 0, &info->dw);
 }
 
 // ------------------------------------------------------------------ bf16: row references and row factors of the keeping pass
@@ -1022,17 +1047,18 @@ __device__ __forceinline__ void zero_acc(floatx4 (&acc)[C::MI][C::NI]) {
 #pragma unroll
     for (int j = 0; j < C::NI; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 }
-// K-contiguous operand tile: block row `row_blk` of the blocked [rows, vocabulary] operand from vocabulary block `voc_blk`
-// on; K runs over the vocabulary, four steps of 64 per block
+// K-contiguous operand tile: block row `row_blk` of the blocked [rows, vocabulary] operand from vocabulary block `voc_blk` on, of which the
+// first `rows` rows are wanted: a pass of loads behind them takes the lines of the first one again, which are on their way to this
+// compute unit anyhow (the last row for all of them made one line hot: 203 rows of 2048 613 -> 650 us); K runs over the vocabulary, four steps of 64 per block
 template <class C>
-__device__ __forceinline__ KContig blocked_rows_tile(const uint16_t* X, int blk_pitch, int64_t tiles_v, int64_t row_blk, int voc_blk) {
+__device__ __forceinline__ KContig blocked_rows_tile(const uint16_t* X, int blk_pitch, int64_t tiles_v, int64_t row_blk, int voc_blk, int rows) {
   KContig c;
   c.rsrc = make_rsrc(X + blk_offset(row_blk, voc_blk, tiles_v) * blk_pitch);
   c.hi_bytes = static_cast<uint32_t>(kBlkElems * 2 * blk_pitch - 4 * 128);        // from the fourth step of a block to the next block
   const int tid = tile_thread();
   const uint32_t kofs = ring2_kofs(tid);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) c.off[i] = (static_cast<uint32_t>(ring2_row<C>(i, tid)) * 256u + kofs) * 2u;
+  for (int i = 0; i < 4; ++i) c.off[i] = (static_cast<uint32_t>(ring2_row<C>(ring2_row<C>(i, 0) < rows ? i : 0, tid)) * 256u + kofs) * 2u;
   return c;
 }
 
@@ -1111,8 +1137,8 @@ struct DhSlices {
   int voc_blks;         // vocabulary blocks of 256 per slice (the last slice may have fewer)
   float* part;
 };
-// tile_m counts the chunk's live blocks of rows; orig_blk is the block's place in the chunk
-__device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, int slice, const DhSlices& sl, int tiles_r, int tiles_d,
+// tile_m counts the chunk's live blocks of rows, of m_rows rows, nobody looks at those behind; orig_blk is the block's place in the chunk
+__device__ __forceinline__ void dh_tile(int tile_m, int m_rows, int orig_blk, int tile_n, int slice, const DhSlices& sl, int tiles_r, int tiles_d,
                                         const uint16_t* __restrict__ dZ, int blk_pitch, int64_t Vp,
                                         const uint16_t* __restrict__ W, int d, int V, uint16_t* __restrict__ dH,
                                         const int32_t* __restrict__ rowsel, int64_t c0, int64_t rows,
@@ -1123,7 +1149,7 @@ __device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, in
   const int n0 = tile_n * C::BN;
   const int voc_blk = slice * sl.voc_blks, tiles_v = static_cast<int>(Vp >> 8);
   const int k_len = min(sl.voc_blks, tiles_v - voc_blk) * 256;       // a multiple of 256, at least 256
-  const KContig ca = blocked_rows_tile<C>(dZ, blk_pitch, tiles_v, tile_m, voc_blk);
+  const KContig ca = blocked_rows_tile<C>(dZ, blk_pitch, tiles_v, tile_m, voc_blk, m_rows);
   KMajor kb;
   kb.base = reinterpret_cast<const char*>(W + static_cast<int64_t>(voc_blk) * 256 * d + n0);
   kb.ld_bytes = static_cast<int64_t>(d) * 2;
@@ -1136,7 +1162,11 @@ __device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, in
   // row tile W is read once: past the caches where it is larger than they are, so that the operand, which every column tile
   // reads, stays there (both products of 203 rows of 3584 762 -> 707 us, of 60 rows of 2048 449 -> 384; with up to four row tiles
   // 725 rows that add to dW gain 1.7 %, 1000 rows lose 1 to 3).
-  if (w_once) mfma_mainloop_mixed<C, false, true, 2, true>(ca, KMajor{}, KContig{}, kb, k_len, lds, acc);
+  // Up to half a tile of rows is multiplied by half of the wavefronts only, which halves the time of the matrix cores: every SIMD has one of either
+  // half.  (With the same loop for all numbers of rows 203 and 725 rows take 0.4 % longer.)
+  if (m_rows <= C::WTM && w_once) mfma_mainloop_mixed<C, false, true, 2, true, true>(ca, KMajor{}, KContig{}, kb, k_len, lds, acc, m_rows);
+  else if (m_rows <= C::WTM) mfma_mainloop_mixed<C, false, true, 2, false, true>(ca, KMajor{}, KContig{}, kb, k_len, lds, acc, m_rows);
+  else if (w_once) mfma_mainloop_mixed<C, false, true, 2, true>(ca, KMajor{}, KContig{}, kb, k_len, lds, acc);
   else mfma_mainloop_mixed<C, false, true, 2>(ca, KMajor{}, KContig{}, kb, k_len, lds, acc);
   if (sl.n > 1) {
     float* out = sl.part + ((static_cast<int64_t>(slice) * tiles_r + tile_m) * tiles_d + tile_n) * (C::BM * C::BN);
@@ -1185,7 +1215,7 @@ __device__ __forceinline__ void dh_tile(int tile_m, int orig_blk, int tile_n, in
 }
 // Hs: the rows of H that go with the rows of dZ (scaled by the keeping pass), in column blocks [d / 256][mcp][256] so that a
 // tile's k-rows are one run of memory
-// k_len: rows of the packed [rows, V] operand (a multiple of 256, 0 when no block is live); rows: those that exist
+// k_len: rows of the packed [rows, V] operand, whole steps of 64 (0 when no block is live); rows: those that exist
 __device__ __forceinline__ void dw_tile(int tile_m, int tile_n, const uint16_t* __restrict__ dZ, int blk_pitch, int64_t mcp, int64_t Vp,
                                         const uint16_t* __restrict__ Hs, int d, int V, int k_len, int rows, float* __restrict__ dW,
                                         int accumulate, uint16_t* lds) {
@@ -1272,10 +1302,10 @@ k_gemm_dh_dw(const uint16_t* __restrict__ dZ, int blk_pitch, int64_t Vp, int64_t
     if (seq < n_dh) {
       const int t = first_dh + seq, slice = t / tiles_mn;
       tile_of_groups<kGM, kGN>(t - slice * tiles_mn, n_live, tiles_d, &tile_m, &tile_n);
-      dh_tile(tile_m, blk_orig[(c0 >> 8) + tile_m], tile_n, slice, sl, tiles_r, tiles_d, dZ, blk_pitch, Vp, W, d, V, dH, rowsel, c0, rows, ids, g_c, sc, n_live == 1 && beyond_cache(d, V, kDhOnceBytes), lds);
+      dh_tile(tile_m, min(k_rows - tile_m * 256, 256), blk_orig[(c0 >> 8) + tile_m], tile_n, slice, sl, tiles_r, tiles_d, dZ, blk_pitch, Vp, W, d, V, dH, rowsel, c0, rows, ids, g_c, sc, n_live == 1 && beyond_cache(d, V, kDhOnceBytes), lds);
     } else {
       tile_of_groups<kGM, kGN>(first_dw + seq - n_dh, tiles_v, tiles_d, &tile_m, &tile_n);
-      dw_tile(tile_m, tile_n, dZ, blk_pitch, mcp, Vp, Hs, d, V, n_live * 256, k_rows, dW, accumulate, lds);
+      dw_tile(tile_m, tile_n, dZ, blk_pitch, mcp, Vp, Hs, d, V, dw_k(k_rows), k_rows, dW, accumulate, lds);
     }
   }
 }
@@ -2063,8 +2093,10 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     // a wavefront per row up to 8192 workgroups; at least 1024 for the clearing
     hipLaunchKernelGGL(k_update_open, dim3(nblk + std::min<unsigned>(std::max<unsigned>(cdiv(n_sel, 4), 1024), 8192)), dim3(256), 0, st, O);
     UMAS_LAUNCHED("k_update_open");
-    const int64_t n_pad = round_up(n_sel, Cfg::BN);
+    const bool narrow = n_sel <= NarrowCfg::BN;              // one chunk of one block
+    const int64_t n_pad = round_up(n_sel, narrow ? NarrowCfg::BN : Cfg::BN);
     const int tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
+    const int tiles_m = narrow ? static_cast<int>(Vp / NarrowCfg::BM) : tiles_v;   // of the scores: the partials are as large either way
     for (int64_t c0 = 0; c0 < n_sel; c0 += mc) {
       const int64_t rows = n_sel - c0 < mc ? n_sel - c0 : mc;
       const int64_t mcp = round_up(rows, 256);
@@ -2076,11 +2108,15 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, static_cast<int>(c0 >> 8), tiles_r, rows, kl_coef != 0.f ? 1 : 0, tiles_v,
                          tiles_d, Vp, sl.n, w.blk_live, w.blk_cidx, w.blk_orig, w.live);   // a KL term gives every row a gradient
       UMAS_LAUNCHED("k_live_scan");
-      hipLaunchKernelGGL(k_score_keep_tiles, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, row_panel(tiles_r, d), kTilesPerWg)), dim3(Cfg::T), 0, st,
-                         Wb, Hb, d, V, rowsel, c0, rows, ids, tiles_v, tiles_r, row_panel(tiles_r, d), w.score.partial, n_pad, w.cref, E, Vp, w.flags,
-                         w.blk_cidx);
-      UMAS_LAUNCHED("k_score_keep_tiles");
-      launch_finalize(rows, n_sel, st, w.score.partial, tiles_v, n_pad, c0, c0 + rows, w.cref, rowsel, ids, V, w.score.logp_c, w.score.lse_c,
+      if (narrow)
+        hipLaunchKernelGGL(k_score_keep_narrow, dim3(tile_grid<kGM, kGN>(tiles_m, 1, kGN, kTilesPerWg)), dim3(NarrowCfg::T), 0, st, Wb, Hb, d, V,
+                           rowsel, rows, ids, tiles_m, w.score.partial, n_pad, w.cref, E, Vp, w.flags, w.blk_cidx);
+      else
+        hipLaunchKernelGGL(k_score_keep_tiles, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, row_panel(tiles_r, d), kTilesPerWg)), dim3(Cfg::T), 0, st,
+                           Wb, Hb, d, V, rowsel, c0, rows, ids, tiles_v, tiles_r, row_panel(tiles_r, d), w.score.partial, n_pad, w.cref, E, Vp,
+                           w.flags, w.blk_cidx);
+      UMAS_LAUNCHED(narrow ? "k_score_keep_narrow" : "k_score_keep_tiles");
+      launch_finalize(rows, n_sel, st, w.score.partial, tiles_m, n_pad, c0, c0 + rows, w.cref, rowsel, ids, V, w.score.logp_c, w.score.lse_c,
                       w.score.ent_c, logp_new, static_cast<float*>(nullptr), static_cast<float*>(nullptr));
       UMAS_LAUNCHED("k_score_finalize");
       s = ppo_rows(c0, c0 + rows);

@@ -200,3 +200,24 @@ def test_update_with_slices_in_several_chunks(n, d, V, entropy_coef):
     nbytes = umas.ppo_workspace_bytes(n, d, V, torch.bfloat16, 0, minimum=True) + 3 * -(-d // 256) * (256 * 256 * 4)
     check_update(np.random.default_rng(n), n, d, V, select=1.0, entropy_coef=entropy_coef, accumulate=True,
                  workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+
+
+# Few rows, or few in the last block of 256: halves of a block (128 rows) change the scores' tiles and the half of the wavefronts that multiplies
+# for dH, steps of 64 rows the length of dW's sums and dH's loads; the vocabulary ends in either half of its last block
+@pytest.mark.parametrize("entropy_coef", [0.0, 0.01])
+@pytest.mark.parametrize("d,V", [(64, 2048), (72, 2049), (264, 5120 + 128), (512, 1281 + 128)])
+@pytest.mark.parametrize("rows", [1, 63, 64, 65, 127, 128, 129, 192, 193, 257, 320, 321, 384, 385])
+def test_update_of_rows_that_fill_part_of_a_block(rows, d, V, entropy_coef):
+    check_update(np.random.default_rng([rows, d, V]), rows, d, V, select=1.0, entropy_coef=entropy_coef, accumulate=rows % 3 == 0)
+
+
+# logits that spread far: the block's dz is computed once more, over what the half tiles have left
+@pytest.mark.parametrize("rows,d,V", [(100, 64, 2305), (128, 72, 2433), (300, 64, 3000)])
+def test_update_of_part_of_a_block_that_is_computed_again(rows, d, V):
+    check_update(np.random.default_rng([rows, d, V]), rows, d, V, select=1.0, scale=12.0)
+
+
+# a head that the caches don't hold, whose weights dH reads past them
+@pytest.mark.parametrize("rows", [90, 200])
+def test_update_of_few_rows_with_a_large_head(rows):
+    check_update(np.random.default_rng(rows), rows, 2048, 66000, select=1.0)
