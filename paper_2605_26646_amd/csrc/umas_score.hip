@@ -687,28 +687,24 @@ __device__ void share_dw(int tiles_r, int tiles_v, int tiles_d, int64_t Vp, int 
   if (k_len <= 0) {                                    // nothing to even out
     cnt = units / 8 + (x < units % 8 ? 1 : 0);
   } else {
-    // the lowest level T up to which the XCDs can be filled with whole units so that all are placed ...
-    // (a double quotient: the operands stay far below 2^53 and 64-bit integer division is slow here)
-    auto take = [&](int64_t T) { return T > load ? static_cast<int64_t>(static_cast<double>(T - load) / static_cast<double>(k_len)) : int64_t{0}; };
-    int64_t lo = load, hi = load;
-#pragma unroll
-    for (int o = 4; o > 0; o >>= 1) {
-      lo = min(lo, static_cast<int64_t>(__shfl_xor(static_cast<long long>(lo), o, kWave)));
-      hi = max(hi, static_cast<int64_t>(__shfl_xor(static_cast<long long>(hi), o, kWave)));
+    // the level up to which the XCDs would be filled if units could be cut: those that stand above it as they are take nothing ...
+    // (a search for it among whole numbers took 23 rounds: k_live_scan 9.6 us, now 5.1)
+    double level = 0.0;
+    bool takes = true;
+    for (int round = 0; round < 8; ++round) {
+      level = static_cast<double>(units * k_len + sum8(takes ? load : 0)) / static_cast<double>(sum8(takes ? 1 : 0));
+      const bool above = takes && static_cast<double>(load) >= level;
+      if (!__any(above)) break;
+      takes = takes && !above;
     }
-    hi += units * k_len;
-    while (lo < hi) {                                  // the same in every lane
-      const int64_t mid = lo + (hi - lo) / 2;
-      if (sum8(take(mid)) >= units) hi = mid; else lo = mid + 1;
-    }
-    cnt = take(lo);
-    // ... and the few units too many at that level come off the XCDs that would finish last
-    for (int64_t total = sum8(cnt); total > units; --total) {
-      int64_t worst = cnt > 0 ? load + cnt * k_len : -1;
+    cnt = takes ? static_cast<int64_t>((level - static_cast<double>(load)) / static_cast<double>(k_len)) : 0;
+    // ... and of the few units that are left every one goes where it is done first (or comes, by rounding, from where it would be last)
+    for (int64_t left = units - sum8(cnt); left != 0; left -= left > 0 ? 1 : -1) {
+      const int64_t end = left > 0 ? -(load + cnt * k_len) : cnt > 0 ? load + cnt * k_len : INT64_MIN;
+      int64_t best = end;
 #pragma unroll
-      for (int o = 4; o > 0; o >>= 1) worst = max(worst, static_cast<int64_t>(__shfl_xor(static_cast<long long>(worst), o, kWave)));
-      const unsigned long long who = __ballot(cnt > 0 && load + cnt * k_len == worst);
-      if (x == __ffsll(static_cast<long long>(who)) - 1) --cnt;
+      for (int o = 4; o > 0; o >>= 1) best = max(best, static_cast<int64_t>(__shfl_xor(static_cast<long long>(best), o, kWave)));
+      if (x == __ffsll(static_cast<long long>(__ballot(end == best))) - 1) cnt += left > 0 ? 1 : -1;
     }
   }
   int first = static_cast<int>(cnt);                   // inclusive prefix sums: where the next XCD's units start
@@ -720,9 +716,50 @@ __device__ void share_dw(int tiles_r, int tiles_v, int tiles_d, int64_t Vp, int 
   if (threadIdx.x == 0) out->first[0] = 0;
   if (threadIdx.x < 8) out->first[x + 1] = static_cast<int>(min(static_cast<int64_t>(first) * unit, static_cast<int64_t>(tiles_dw)));
 }
+// Packs the live blocks of a chunk, blk0 its first block; one workgroup, thread t has block t and knows if it is live.
+struct LiveArgs {
+  int blk0, nblk;
+  int64_t rows;
+  int all_live, tiles_v, tiles_d;
+  int64_t Vp;
+  int slices;
+  const int32_t* blk_live;
+  int32_t *blk_cidx, *blk_orig;
+  LiveInfo* info;
+};
+__device__ __forceinline__ void live_scan(const LiveArgs& A, int live) {
+  __shared__ int smem[32];
+  __shared__ int s_last_live;
+  const int t = threadIdx.x;
+  int total;
+  const int pos = block_excl_scan<int>(live, smem, &total);
+  if (t < A.nblk) {
+    A.blk_cidx[A.blk0 + t] = live ? pos : -1;
+    if (live) A.blk_orig[A.blk0 + pos] = t;
+  }
+  if (t == A.nblk - 1) s_last_live = live;
+  __syncthreads();
+  const int64_t last_rows = A.rows - static_cast<int64_t>(A.nblk - 1) * 256;   // rows of the chunk's last block
+  const int k_rows = static_cast<int>(s_last_live ? static_cast<int64_t>(total - 1) * 256 + last_rows : static_cast<int64_t>(total) * 256);
+  if (t == 0) {
+    A.info->n_live = total;
+    A.info->k_rows = k_rows;
+  }
+  if (t < 8) A.info->next[t] = 0;
+  if (t < kWave) share_dw(total, A.tiles_v, A.tiles_d, A.Vp, A.slices, total > 0 ? dw_k(k_rows) + kTileOverheadK : 0, &A.info->dw);
+}
+// One launch per chunk (all blocks live with all_live).
+__global__ void __launch_bounds__(512)
+k_live_scan(LiveArgs A) {
+  const int t = threadIdx.x;
+  live_scan(A, t < A.nblk && (A.all_live || A.blk_live[A.blk0 + t]));
+}
+
 // What opens the keeping update, in one launch: the first nblk workgroups mark the live blocks of 256 selected rows and
 // clear their flags, the others take the rows' references and clear what the call defines everywhere (logp_new when rows
-// are left out, dH), each its share.
+// are left out, dH), each its share.  Up to kFewBlocks blocks in one chunk the first workgroup alone marks them and packs them as well, under the
+// others' work (203 rows of 3584 1025 -> 1018 us, 2000 of 2048 3137 -> 3099).
+constexpr int kFewBlocks = 8;
 struct OpenArgs {
   const uint16_t* H;
   const uint16_t* W;
@@ -739,34 +776,9 @@ struct OpenArgs {
   int64_t dh_words;
   float* logp_new;       // NULL: nothing to clear
   int64_t n_rows;
+  int pack;              // few blocks: nblk is 1, the blocks are live.nblk
+  LiveArgs live;
 };
-// One workgroup per chunk: packs the live blocks (all of them with all_live), blk0 = first block of the chunk.
-__global__ void __launch_bounds__(512)
-k_live_scan(int blk0, int nblk, int64_t rows, int all_live, int tiles_v, int tiles_d, int64_t Vp, int slices,
-            const int32_t* __restrict__ blk_live, int32_t* __restrict__ blk_cidx, int32_t* __restrict__ blk_orig,
-            LiveInfo* __restrict__ info) {
-  __shared__ int smem[32];
-  const int t = threadIdx.x;
-  const int live = t < nblk && (all_live || blk_live[blk0 + t]);
-  int total;
-  const int pos = block_excl_scan<int>(live, smem, &total);
-  if (t < nblk) {
-    blk_cidx[blk0 + t] = live ? pos : -1;
-    if (live) blk_orig[blk0 + pos] = t;
-  }
-  __shared__ int s_last_live;
-  if (t == nblk - 1) s_last_live = live;
-  __syncthreads();
-  const int64_t last_rows = rows - static_cast<int64_t>(nblk - 1) * 256;       // rows of the chunk's last block
-  const int k_rows = static_cast<int>(s_last_live ? static_cast<int64_t>(total - 1) * 256 + last_rows : static_cast<int64_t>(total) * 256);
-  if (t == 0) {
-    info->n_live = total;
-    info->k_rows = k_rows;
-  }
-  if (t < 8) info->next[t] = 0;
-  if (t < kWave) share_dw(total, tiles_v, tiles_d, Vp, slices, total > 0 ? dw_k(k_rows) + kTileOverheadK : 0, &info->dw);
-}
-
 // ------------------------------------------------------------------ bf16: row references and row factors of the keeping pass
 __device__ __forceinline__ void bf16x8_to_f32(const uint4 v, float (&o)[8]) {
   o[0] = __uint_as_float(v.x << 16); o[1] = __uint_as_float(v.x & 0xffff0000u);
@@ -776,6 +788,25 @@ __device__ __forceinline__ void bf16x8_to_f32(const uint4 v, float (&o)[8]) {
 }
 __global__ void __launch_bounds__(256)
 k_update_open(OpenArgs A) {
+  if (A.pack && blockIdx.x == 0) {
+    float adv[kFewBlocks];
+#pragma unroll
+    for (int b = 0; b < kFewBlocks; ++b) {
+      const int64_t n = b * 256 + threadIdx.x;
+      adv[b] = n < A.n_sel ? A.adv[A.rowsel ? A.rowsel[n] : n] : 0.f;
+    }
+    int live = 0;
+#pragma unroll
+    for (int b = 0; b < kFewBlocks; ++b) {
+      const int any = __syncthreads_or(adv[b] != 0.f);
+      if (static_cast<int>(threadIdx.x) == b && b < A.live.nblk) {
+        live = any || A.live.all_live;
+        A.flags[b] = 0;
+      }
+    }
+    live_scan(A.live, live);
+    return;
+  }
   if (static_cast<int>(blockIdx.x) < A.nblk) {
     const int64_t n = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     const int live = n < A.n_sel && A.adv[A.rowsel ? A.rowsel[n] : n] != 0.f;
@@ -2088,14 +2119,24 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     s = ppo_rows(0, n_sel);
     if (s != UMAS_OK) return s;
   } else {
+    const int tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
+    auto live_args = [&](int64_t c0, int64_t rows, int slices) {
+      return LiveArgs{static_cast<int>(c0 >> 8), static_cast<int>(round_up(rows, 256) / 256), rows, kl_coef != 0.f ? 1 : 0,   // a KL term gives every row a gradient
+                      tiles_v, tiles_d, Vp, slices, w.blk_live, w.blk_cidx, w.blk_orig, w.live};
+    };
     OpenArgs O{Hb, Wb, d, V, rowsel, n_sel, ids, adv, nblk, w.blk_live, w.flags, w.cref, static_cast<uint32_t*>(dH),
-               n_rows * static_cast<int64_t>(d) / 2, rowsel ? logp_new : nullptr, n_rows};
+               n_rows * static_cast<int64_t>(d) / 2, rowsel ? logp_new : nullptr, n_rows, 0, {}};
+    if (mc >= n_sel && nblk <= kFewBlocks) {
+      DhSlices sl;
+      dh_plan(n_sel, chunk_bytes(n_sel, d, V, dtype), &sl);
+      O.nblk = O.pack = 1;
+      O.live = live_args(0, n_sel, sl.n);
+    }
     // a wavefront per row up to 8192 workgroups; at least 1024 for the clearing
-    hipLaunchKernelGGL(k_update_open, dim3(nblk + std::min<unsigned>(std::max<unsigned>(cdiv(n_sel, 4), 1024), 8192)), dim3(256), 0, st, O);
+    hipLaunchKernelGGL(k_update_open, dim3(O.nblk + std::min<unsigned>(std::max<unsigned>(cdiv(n_sel, 4), 1024), 8192)), dim3(256), 0, st, O);
     UMAS_LAUNCHED("k_update_open");
     const bool narrow = n_sel <= NarrowCfg::BN;              // one chunk of one block
     const int64_t n_pad = round_up(n_sel, narrow ? NarrowCfg::BN : Cfg::BN);
-    const int tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
     const int tiles_m = narrow ? static_cast<int>(Vp / NarrowCfg::BM) : tiles_v;   // of the scores: the partials are as large either way
     for (int64_t c0 = 0; c0 < n_sel; c0 += mc) {
       const int64_t rows = n_sel - c0 < mc ? n_sel - c0 : mc;
@@ -2105,9 +2146,10 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       uint16_t* Hs = reinterpret_cast<uint16_t*>(w.chunk + align_up(static_cast<size_t>(mcp) * Vp * 2));
       DhSlices sl;
       dh_plan(rows, chunk_bytes(rows, d, V, dtype), &sl);
-      hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, static_cast<int>(c0 >> 8), tiles_r, rows, kl_coef != 0.f ? 1 : 0, tiles_v,
-                         tiles_d, Vp, sl.n, w.blk_live, w.blk_cidx, w.blk_orig, w.live);   // a KL term gives every row a gradient
-      UMAS_LAUNCHED("k_live_scan");
+      if (!O.pack) {
+        hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, live_args(c0, rows, sl.n));
+        UMAS_LAUNCHED("k_live_scan");
+      }
       if (narrow)
         hipLaunchKernelGGL(k_score_keep_narrow, dim3(tile_grid<kGM, kGN>(tiles_m, 1, kGN, kTilesPerWg)), dim3(NarrowCfg::T), 0, st, Wb, Hb, d, V,
                            rowsel, rows, ids, tiles_m, w.score.partial, n_pad, w.cref, E, Vp, w.flags, w.blk_cidx);
@@ -2188,8 +2230,8 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     // with an entropy bonus every row has a gradient: all blocks are live
     DhSlices sl;
     dh_plan(rows, mc_z > 0 ? logit_chunk_bytes(rows, d, V) : chunk_bytes(rows, d, V, dtype), &sl);
-    hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, static_cast<int>(c0 >> 8), tiles_r, rows, 1, tiles_v, tiles_d, Vp, sl.n,
-                       w.blk_live, w.blk_cidx, w.blk_orig, w.live);
+    hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, LiveArgs{static_cast<int>(c0 >> 8), tiles_r, rows, 1, tiles_v, tiles_d, Vp, sl.n,
+                       w.blk_live, w.blk_cidx, w.blk_orig, w.live});
     UMAS_LAUNCHED("k_live_scan");
     s = gradients(c0, rows, sl, dZ, blk_pitch, Hs, nullptr);
     if (s != UMAS_OK) return s;
