@@ -472,7 +472,9 @@ extern "C" umas_status umas_kl_rewards(const float* tok_reward, const float* log
                "workspace must be 256-byte aligned and hold %zu bytes (got %zu)", need, workspace_bytes);
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   prof_mark(st);
-  if (n_tokens <= kKlAlone) {
+  // (its last workgroup reads the log-probs while the others write: not where they write over them)
+  auto apart = [&](const float* p) { return tok_reward_out + n_tokens <= p || p + n_tokens <= tok_reward_out; };
+  if (n_tokens <= kKlAlone && apart(logp) && apart(logp_ref)) {
     const unsigned wg = cdiv(static_cast<size_t>(n_tokens), kKlThreads * kSIpt) + 1;
     hipLaunchKernelGGL(k_kl_rewards_few, dim3(wg), dim3(kKlThreads), 0, st, n_tokens, tok_reward, logp, logp_ref, tok_mask, beta, tok_reward_out, kl_mean);
     UMAS_LAUNCHED("k_kl_rewards");

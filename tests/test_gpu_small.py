@@ -110,6 +110,19 @@ def test_kl_rewards_of_few_tokens(n, density):
         assert abs(float(kl.cpu()[0]) - kl_want) <= 2.0 ** -24 * (abs(kl_want) + np.abs(logp.astype(np.float64) - ref).max())
 
 
+@pytest.mark.parametrize("over", ["logp", "logp_ref"])
+def test_kl_rewards_written_over_the_log_probs(over):
+    n, g = 46000, torch.Generator(device="cuda").manual_seed(1)
+    r, logp, ref = (torch.randn(n, device="cuda", generator=g) for _ in range(3))
+    mask = (torch.rand(n, device="cuda", generator=g) < 0.8).to(torch.uint8)
+    want, want_kl = umas.umas_kl_rewards(r, logp, ref, mask, 0.05)
+    for _ in range(20):
+        a, b = logp.clone(), ref.clone()
+        out, kl = umas.umas_kl_rewards(r, a, b, mask, 0.05, out=a if over == "logp" else b)
+        assert torch.equal(out, want)
+        assert abs(float(kl) - float(want_kl)) <= 2.0 ** -23 * abs(float(want_kl))   # float64 sums in two orders, rounded once
+
+
 @pytest.mark.parametrize("rows,d,V", [  # every pair of tile sizes of the two float32 gradient products, 16, 32 and 64 wide
     (1, 1, 1), (60, 33, 100), (255, 64, 512), (1030, 127, 1001), (100, 100, 3000), (100, 512, 8000), (3000, 100, 101), (300, 500, 300),
     (300, 512, 8190), (4001, 512, 60), (4000, 511, 401), (4096, 512, 2100)])
