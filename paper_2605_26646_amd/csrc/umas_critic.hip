@@ -77,45 +77,42 @@ __global__ void k_zero_u32(uint32_t* __restrict__ p, int64_t n) {
 // to mark a byte per row and to clear the rows without one, and like this: 1000 rows of 2048 25 and 20 us, 6000 34 and 28, 39 224 100 and 93 (on new
 // rows 119 and 111), 100 000 of 1024 123 and 113, 400 000 of 512 401 and 395.  (One entry at a time, with 64-bit places, the selection took 60 us
 // for 400 000 rows; marks by all workgroups and a queue of the rows to clear lost 80 us to atomics on one word.)
-constexpr int kMapRows = 16384;            // rows of a workgroup at a time
+constexpr int kMapRows = 16384;            // rows of a workgroup at most
 template <class F>
-__device__ __forceinline__ void unselected_rows(int wg, int n_wg, int64_t n_rows, const int32_t* __restrict__ rowsel, int64_t n_sel, uint32_t* s_map,
+__device__ __forceinline__ void unselected_rows(int wg, int n_wg, int n_rows, const int32_t* __restrict__ rowsel, int64_t n_sel, uint32_t* s_map,
                                                 F clear) {
-  const int64_t share = (n_rows + n_wg - 1) / n_wg, end = (wg + 1) * share < n_rows ? (wg + 1) * share : n_rows;
-  for (int64_t r0 = wg * share; r0 < end; r0 += kMapRows) {
-    const int64_t n = end - r0 < kMapRows ? end - r0 : kMapRows;
-    for (int i = threadIdx.x; i < kMapRows / 32; i += kVT) s_map[i] = 0u;
-    __syncthreads();
-    auto place = [&](int32_t row) { return static_cast<uint32_t>(row) - static_cast<uint32_t>(r0); };   // in the share: below n
-    auto mark = [&](uint32_t i) {
-      if (i < static_cast<uint32_t>(n)) atomicOr(s_map + (i >> 5), 1u << (i & 31));
-    };
-    const int64_t head = (4 - ((reinterpret_cast<uintptr_t>(rowsel) >> 2) & 3)) & 3;   // up to the first 16-byte boundary
-    const int64_t n4 = n_sel > head ? (n_sel - head) / 4 : 0;
-    const int4* const sel4 = reinterpret_cast<const int4*>(rowsel + head);
-    for (int64_t i = threadIdx.x; i < n4; i += 4 * kVT) {
-      int4 v[4];
+  const int share = (n_rows + n_wg - 1) / n_wg, r0 = wg * share, n = min(share, n_rows - r0);   // share <= kMapRows (clear_grid)
+  if (n <= 0) return;
+  for (int i = threadIdx.x; i < kMapRows / 32; i += kVT) s_map[i] = 0u;
+  __syncthreads();
+  auto place = [&](int32_t row) { return static_cast<uint32_t>(row) - static_cast<uint32_t>(r0); };   // in the share: below n
+  auto mark = [&](uint32_t i) {
+    if (i < static_cast<uint32_t>(n)) atomicOr(s_map + (i >> 5), 1u << (i & 31));
+  };
+  const int64_t head = (4 - ((reinterpret_cast<uintptr_t>(rowsel) >> 2) & 3)) & 3;   // up to the first 16-byte boundary
+  const int64_t n4 = n_sel > head ? (n_sel - head) / 4 : 0;
+  const int4* const sel4 = reinterpret_cast<const int4*>(rowsel + head);
+  for (int64_t i = threadIdx.x; i < n4; i += 4 * kVT) {
+    int4 v[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) v[k] = i + k * kVT < n4 ? sel4[i + k * kVT] : make_int4(-1, -1, -1, -1);
+    for (int k = 0; k < 4; ++k) v[k] = i + k * kVT < n4 ? sel4[i + k * kVT] : make_int4(-1, -1, -1, -1);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {                            // nearly always all of the wavefront's lie outside: three instructions an entry
-        const uint32_t a = place(v[k].x), b = place(v[k].y), c = place(v[k].z), e = place(v[k].w), least = min(min(a, b), min(c, e));
-        if (least < static_cast<uint32_t>(n)) { mark(a); mark(b); mark(c); mark(e); }
-      }
+    for (int k = 0; k < 4; ++k) {                              // nearly always all of the wavefront's lie outside: three instructions an entry
+      const uint32_t a = place(v[k].x), b = place(v[k].y), c = place(v[k].z), e = place(v[k].w), least = min(min(a, b), min(c, e));
+      if (least < static_cast<uint32_t>(n)) { mark(a); mark(b); mark(c); mark(e); }
     }
-    const int64_t tail = head + 4 * n4 + threadIdx.x - 4;
-    if (threadIdx.x < 4) {
-      if (threadIdx.x < head && threadIdx.x < n_sel) mark(place(rowsel[threadIdx.x]));
-    } else if (threadIdx.x < 8 && tail < n_sel) {
-      mark(place(rowsel[tail]));
-    }
-    __syncthreads();
-    for (int64_t j = 0; j < n; j += kWave) {
-      unsigned long long rest = ~(s_map[j >> 5] | static_cast<unsigned long long>(s_map[(j >> 5) + 1]) << 32);
-      if (n - j < kWave) rest &= (1ull << (n - j)) - 1;
-      if (rest) clear(r0 + j, rest);
-    }
-    __syncthreads();
+  }
+  const int64_t tail = head + 4 * n4 + threadIdx.x - 4;
+  if (threadIdx.x < 4) {
+    if (threadIdx.x < head && threadIdx.x < n_sel) mark(place(rowsel[threadIdx.x]));
+  } else if (threadIdx.x < 8 && tail < n_sel) {
+    mark(place(rowsel[tail]));
+  }
+  __syncthreads();
+  for (int j = 0; j < n; j += kWave) {
+    unsigned long long rest = ~(s_map[j >> 5] | static_cast<unsigned long long>(s_map[(j >> 5) + 1]) << 32);
+    if (n - j < kWave) rest &= (1ull << (n - j)) - 1;
+    if (rest) clear(static_cast<int64_t>(r0) + j, rest);
   }
 }
 // What an update defines on them; either may be NULL.
@@ -134,17 +131,55 @@ struct ClearRows {
     }
   }
 };
-// Workgroups for it: enough that clearing takes no longer than the rows, few enough that most of the device does rows.
+// Workgroups for it: enough that clearing takes no longer than the rows, few enough that most of the device does rows.  Every one of them
+// reads the whole selection, so that the rows it is for are limited; beyond, launches go over all rows first.  Short rows leave
+// nothing to read it behind (values and update in launches and along: 20 000 rows of 16 bytes 29.4 and 25.0 us, 30 000 30.2 and 31.2, 200 000 116
+// and 138, 800 000 412 and 527; of 512 bytes 200 000 149 and 157; of 768 bytes 400 000 360 and 356, of 1 KB 800 000 794 and 785); rows of two to
+// four KB hold fewer workgroups at once, which 64 of them delay by more than the launches (100 000 of 2176 bytes 187 and 185.5 us,
+// 200 000 342 and 344, 380 000 628 and 636; of 4 KB 100 000 263 and 258, 380 000 966 and 984); behind the rows it costs longer ones nothing
+// (268 000 of 6.9 KB 1472 and 1455).
 constexpr unsigned kClearWgs = 64;
-unsigned clear_grid(const int32_t* rowsel, int64_t n_rows) {
-  return rowsel ? std::min(kClearWgs, cdiv(static_cast<size_t>(n_rows), 128)) : 0;
+unsigned clear_grid(const int32_t* rowsel, int64_t n_rows, int64_t row_bytes) {
+  static_assert(1 << 20 <= kClearWgs * kMapRows, "every share fits its map");
+  const int64_t most = row_bytes < 768 ? 1 << 15 : row_bytes <= 1024 || row_bytes > 4096 ? 1 << 20 : 1 << 17;
+  return rowsel && n_rows <= most ? std::min(kClearWgs, cdiv(static_cast<size_t>(n_rows), 128)) : 0;
 }
+// Those of an update: value_new[n] (may be NULL) and n16 16-byte words of `big` are cleared.
+__global__ void __launch_bounds__(256)
+k_value_open(uint32_t* __restrict__ value_new, int64_t n, uint4* __restrict__ big, int64_t n16) {
+  const int64_t i0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x, stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+  for (int64_t i = i0; i < n16; i += stride) store_stream(big + i, make_uint4(0u, 0u, 0u, 0u));
+  if (value_new)
+    for (int64_t i = i0; i < n; i += stride) value_new[i] = 0u;
+}
+// Large selections: dH is cleared only where the row kernel does not write it.  A byte per row says which rows are selected
+// (in the memory of the partial sums, which come later); clearing all of dH first would write the selected rows twice.
+__global__ void __launch_bounds__(256)
+k_value_mark(const int32_t* __restrict__ rowsel, int64_t n_sel, int64_t n_rows, uint8_t* __restrict__ map) {
+  const int64_t n = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (n >= n_sel) return;
+  const int64_t row = rowsel[n];
+  if (row >= 0 && row < n_rows) map[row] = 1;
+}
+constexpr int kClearRows = 64;             // rows of one workgroup: one ballot of a wavefront
+__global__ void __launch_bounds__(256)
+k_value_clear_rest(const uint8_t* __restrict__ map, int64_t n_rows, int row16, uint4* __restrict__ dH) {
+  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kClearRows;
+  const int64_t mine = r0 + (threadIdx.x & (kWave - 1));
+  // every wavefront looks at the same rows and takes its share of each unselected one
+  for (unsigned long long rest = __ballot(mine < n_rows && map[mine] == 0); rest; rest &= rest - 1) {
+    uint4* p = dH + (r0 + __ffsll(static_cast<long long>(rest)) - 1) * row16;
+    for (int i = threadIdx.x; i < row16; i += 256) store_stream(p + i, make_uint4(0u, 0u, 0u, 0u));
+  }
+}
+// Below this many bytes of selected rows the two launches more cost as much as they save.
+constexpr int64_t kMarkBytes = int64_t{48} << 20;
 
 // Forward only: one wavefront per selected row, behind n_clear workgroups for the others.
 template <typename T, bool SELECT>
 __global__ void __launch_bounds__(kVT)
 k_value_fwd(const T* __restrict__ H, const T* __restrict__ w, float bias, int d, const int32_t* __restrict__ rowsel,
-            int64_t n_sel, int64_t n_rows, int n_clear, float* __restrict__ value) {
+            int64_t n_sel, int n_rows, int n_clear, float* __restrict__ value) {
   const int lane = threadIdx.x & (kWave - 1);
   if constexpr (SELECT) {
     if (static_cast<int>(blockIdx.x) < n_clear) {
@@ -176,7 +211,7 @@ k_value_fwd(const T* __restrict__ H, const T* __restrict__ w, float bias, int d,
 template <typename T, int KV, bool SELECT>
 __global__ void __launch_bounds__(kVT)
 k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d, const int32_t* __restrict__ rowsel,
-             int64_t n_sel, int64_t n_rows, int n_clear, int clear_at, int64_t norm, int64_t rows_per_block, const float* __restrict__ value_old, const float* __restrict__ ret,
+             int64_t n_sel, int n_rows, int n_clear, int clear_at, int64_t norm, int64_t rows_per_block, const float* __restrict__ value_old, const float* __restrict__ ret,
              const int32_t* __restrict__ tok_role, int n_roles, float clip_eps, float* __restrict__ value_new,
              T* __restrict__ dH, int accumulate_dH, float* __restrict__ part_dw, double* __restrict__ blk_stats) {
   __shared__ double s_acc[(1 + UMAS_MAX_ROLES) * kVStat];
@@ -391,7 +426,7 @@ void launch_value_rows(int kv, unsigned grid, hipStream_t st, const void* H, con
                        float* part_dw, double* blk_stats) {
 #define UMAS_VALUE_CASE(K)                                                                                              \
   hipLaunchKernelGGL((n_clear ? k_value_rows<T, K, true> : k_value_rows<T, K, false>), dim3(n_clear + grid), dim3(kVT), d * sizeof(AccT<T>), st, static_cast<const T*>(H), static_cast<const T*>(w), \
-                     bias, d, rowsel, n_sel, n_rows, static_cast<int>(n_clear), static_cast<int>(clear_at), norm, rpb, value_old, ret, tok_role, n_roles, clip_eps, value_new,         \
+                     bias, d, rowsel, n_sel, n_clear ? static_cast<int>(n_rows) : 0, static_cast<int>(n_clear), static_cast<int>(clear_at), norm, rpb, value_old, ret, tok_role, n_roles, clip_eps, value_new,         \
                      static_cast<T*>(dH), acc_dH, part_dw, blk_stats)
   if (kv <= 1) UMAS_VALUE_CASE(1);
   else if (kv <= 2) UMAS_VALUE_CASE(2);
@@ -448,11 +483,12 @@ extern "C" umas_status umas_values(const void* H, const void* w, float bias, uma
     if (n_rows > 0) UMAS_HIP(zero_words(value, n_rows, st));
     return UMAS_OK;
   }
-  const unsigned n_clear = clear_grid(rowsel, n_rows);
+  const unsigned n_clear = clear_grid(rowsel, n_rows, static_cast<int64_t>(d) * (dtype == UMAS_BF16 ? 2 : 4));
+  if (rowsel && n_clear == 0) UMAS_HIP(zero_words(value, n_rows, st));
   auto fwd = [&](auto kernel, auto* h) {
     using T = std::remove_pointer_t<decltype(h)>;
-    hipLaunchKernelGGL(kernel, dim3(n_clear + cdiv(n_sel, kVWaves)), dim3(kVT), 0, st, h, static_cast<T*>(w), bias, d, rowsel, n_sel, n_rows,
-                       static_cast<int>(n_clear), value);
+    hipLaunchKernelGGL(kernel, dim3(n_clear + cdiv(n_sel, kVWaves)), dim3(kVT), 0, st, h, static_cast<T*>(w), bias, d, rowsel, n_sel,
+                       n_clear ? static_cast<int>(n_rows) : 0, static_cast<int>(n_clear), value);
   };
   if (dtype == UMAS_BF16) fwd(n_clear ? k_value_fwd<uint16_t, true> : k_value_fwd<uint16_t, false>, static_cast<const uint16_t*>(H));
   else fwd(n_clear ? k_value_fwd<float, true> : k_value_fwd<float, false>, static_cast<const float*>(H));
@@ -488,7 +524,7 @@ extern "C" umas_status umas_value_loss_fwd_bwd(const void* H, const void* w, flo
   const unsigned resident = dtype == UMAS_BF16 ? resident_value_blocks_kv<uint16_t>(kv) : resident_value_blocks_kv<float>(kv);
   // the workgroups that clear are part of that round and go first; behind a full round of rows where the instance holds so few at once
   // that giving them up costs more than a tail (39 224 rows of 4096 233 us with them first, 204 behind)
-  const unsigned n_clear = n_sel > 0 ? clear_grid(rowsel, n_rows) : 0;
+  const unsigned n_clear = n_sel > 0 ? clear_grid(rowsel, n_rows, static_cast<int64_t>(d) * esz) : 0;
   const bool last = kv >= 8;
   const unsigned grid = std::min(value_grid(n_sel), last || resident <= n_clear ? resident : resident - n_clear);
   const unsigned clear_at = last ? grid : 0;
@@ -497,6 +533,22 @@ extern "C" umas_status umas_value_loss_fwd_bwd(const void* H, const void* w, flo
   float* part_dw = c.take<float>(part_bytes / sizeof(float));
   double* blk_stats = c.take<double>(static_cast<size_t>(grid) * (1 + n_roles) * kVStat);
 
+  if (rowsel && n_rows > 0 && n_clear == 0) {
+    const size_t row_bytes = static_cast<size_t>(d) * esz;           // a multiple of 16
+    const bool mark = !accumulate_dH && n_sel * static_cast<int64_t>(row_bytes) >= kMarkBytes && align_up(n_rows, 16) <= part_bytes;
+    const int64_t n16 = accumulate_dH ? 0 : static_cast<int64_t>(mark ? align_up(n_rows, 16) / 16 : n_rows * row_bytes / 16);
+    uint8_t* map = reinterpret_cast<uint8_t*>(part_dw);
+    hipLaunchKernelGGL(k_value_open, dim3(std::min(std::max(cdiv(n16, 1024), cdiv(n_rows, 1024)), 8192u)), dim3(256), 0, st,
+                       reinterpret_cast<uint32_t*>(value_new), n_rows, static_cast<uint4*>(mark ? static_cast<void*>(map) : dH), n16);
+    UMAS_LAUNCHED("k_value_open");
+    if (mark) {
+      hipLaunchKernelGGL(k_value_mark, dim3(cdiv(n_sel, 256)), dim3(256), 0, st, rowsel, n_sel, n_rows, map);
+      UMAS_LAUNCHED("k_value_mark");
+      hipLaunchKernelGGL(k_value_clear_rest, dim3(cdiv(n_rows, kClearRows)), dim3(256), 0, st, map, n_rows, static_cast<int>(row_bytes / 16),
+                         static_cast<uint4*>(dH));
+      UMAS_LAUNCHED("k_value_clear_rest");
+    }
+  }
   if (n_sel > 0) {
     const int64_t rpb = (n_sel + grid - 1) / grid;                 // rows per workgroup; every wavefront writes its partial row
     if (dtype == UMAS_BF16)
@@ -508,8 +560,6 @@ extern "C" umas_status umas_value_loss_fwd_bwd(const void* H, const void* w, flo
     UMAS_LAUNCHED("k_value_rows");
   } else {
     // an empty selection still defines the outputs: zero partials give zero statistics and gradients
-    if (value_new) UMAS_HIP(zero_words(value_new, n_rows, st));
-    if (!accumulate_dH) UMAS_HIP(zero_words(dH, static_cast<int64_t>(n_rows * d * esz / 4), st));
     UMAS_HIP(zero_words(part_dw, static_cast<int64_t>(part_bytes / 4), st));
     UMAS_HIP(zero_words(blk_stats, static_cast<int64_t>(grid) * (1 + n_roles) * kVStat * 2, st));
   }

@@ -190,6 +190,42 @@ def test_critic_defines_the_rows_that_are_not_selected(n, n_sel, shift, dtype):
     assert torch.equal(kept[sel.long()], dH[sel.long()]) and kept[rest].isnan().all()
 
 
+# where rows are cleared in the launch that works on the selected ones, up to 2^20 of them, and where in launches of their own, with a byte a row where it fits
+@pytest.mark.parametrize("n,n_sel,d", [(1 << 15, 9, 8), ((1 << 15) + 1, 1 << 15, 16), (1 << 20, 9, 8), ((1 << 20) + 1, (1 << 20) - 77, 16), (1 << 20, 700001, 192),
+                                       ((1 << 20) + 1, 400001, 384), (1 << 17, 100001, 640), ((1 << 17) + 1, 9, 640), (2200000, 1900000, 16)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_critic_of_many_rows(n, n_sel, d, dtype):
+    g = torch.Generator(device="cuda").manual_seed(n_sel)
+    H, w = torch.randn(n, d, device="cuda", generator=g).to(dtype), torch.randn(d, device="cuda", generator=g).to(dtype)
+    sel = torch.randperm(n, device="cuda", generator=g)[:n_sel].to(torch.int32)
+    ret, old, at = torch.randn(n, device="cuda", generator=g), torch.zeros(n, device="cuda"), sel.long()
+    nan = lambda *s: torch.full(s, float("nan"), device="cuda")
+    value = umas.umas_values(H, w, 0.5, sel, value=nan(n))
+    _, value_new, dH, _, _ = umas.umas_value_loss_fwd_bwd(H, w, 0.5, sel, old, ret, None, 0, 1e9, dH=nan(n, d).to(dtype), value_new=nan(n))
+    # the selected rows alone are the same rows, bit for bit
+    _, want_value, want_dH, _, _ = umas.umas_value_loss_fwd_bwd(H[at], w, 0.5, None, old[at], ret[at], None, 0, 1e9)
+    rest = torch.ones(n, dtype=torch.bool, device="cuda")
+    rest[at] = False
+    for got in (value, value_new):
+        assert torch.equal(got[at], want_value) and (got[rest] == 0).all()
+    assert torch.equal(dH[at], want_dH) and (dH[rest] == 0).all()
+
+
+def test_values_of_more_rows_than_32_bits_count():
+    """Row 2^32 + 5 is not selected by an entry 5 (the values of 2^32 rows are 17 GB, their rows of 16 bytes, of which three are read, 69 GB)."""
+    n, d = (1 << 32) + (1 << 20), 4
+    H, value = torch.empty(n, d, device="cuda"), torch.empty(n, device="cuda")
+    sel = torch.tensor([5, 70000, (1 << 31) - 1], dtype=torch.int32, device="cuda")
+    H[sel.long()] = 1.0
+    value.fill_(float("nan"))
+    umas.umas_values(H, torch.ones(d, device="cuda"), 0.5, sel, value=value)
+    assert torch.equal(value[sel.long()], torch.full((3,), 4.5, device="cuda"))
+    value[sel.long()] = 0.0
+    assert all((part == 0).all() for part in value.split(1 << 30))
+    del H, value
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("shape", ["alike", "front", "back", "blocks", "none"])
 @pytest.mark.parametrize("n_models", [1, 3])
 def test_ready_batch_of_masks_that_are_not_alike(shape, n_models):
