@@ -523,9 +523,11 @@ extern "C" umas_status umas_value_loss_fwd_bwd(const void* H, const void* w, flo
   // at most value_grid(n_sel) workgroups (what the workspace is sized for), and no more than are resident at once
   const unsigned resident = dtype == UMAS_BF16 ? resident_value_blocks_kv<uint16_t>(kv) : resident_value_blocks_kv<float>(kv);
   // the workgroups that clear are part of that round and go first; behind a full round of rows where the instance holds so few at once
-  // that giving them up costs more than a tail (39 224 rows of 4096 233 us with them first, 204 behind)
+  // that giving them up costs more than a tail, those for rows of more than 4 KB (39 224 rows of 4096 233 us with them first, 204 behind;
+  // values and update of 48 651 rows of 3008 246 and 222, of 268 000 float32 rows of 1728 1733 and 1455; the other way round shorter rows: 100 000 of 1088
+  // 185.5 first, 195 behind)
   const unsigned n_clear = n_sel > 0 ? clear_grid(rowsel, n_rows, static_cast<int64_t>(d) * esz) : 0;
-  const bool last = kv >= 8;
+  const bool last = kv > 4;
   const unsigned grid = std::min(value_grid(n_sel), last || resident <= n_clear ? resident : resident - n_clear);
   const unsigned clear_at = last ? grid : 0;
   const size_t part_bytes = static_cast<size_t>(grid) * part_pitch(d) * sizeof(float);

@@ -192,7 +192,7 @@ def test_critic_defines_the_rows_that_are_not_selected(n, n_sel, shift, dtype):
 
 # where rows are cleared in the launch that works on the selected ones, up to 2^20 of them, and where in launches of their own, with a byte a row where it fits
 @pytest.mark.parametrize("n,n_sel,d", [(1 << 15, 9, 8), ((1 << 15) + 1, 1 << 15, 16), (1 << 20, 9, 8), ((1 << 20) + 1, (1 << 20) - 77, 16), (1 << 20, 700001, 192),
-                                       ((1 << 20) + 1, 400001, 384), (1 << 17, 100001, 640), ((1 << 17) + 1, 9, 640), (2200000, 1900000, 16)])
+                                       ((1 << 20) + 1, 400001, 384), (1 << 17, 100001, 640), ((1 << 17) + 1, 9, 640), (2200000, 1900000, 16), (5000, 4001, 2624)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_critic_of_many_rows(n, n_sel, d, dtype):
     g = torch.Generator(device="cuda").manual_seed(n_sel)
