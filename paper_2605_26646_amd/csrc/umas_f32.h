@@ -362,8 +362,9 @@ k_row_dz_f32(const double* __restrict__ z, const Stat* __restrict__ part, int sp
   const int y = S.ids[row];
   Stat a = empty_stat();
   for (int k = lane; k < splits; k += kWave) a = merge(a, part[k * n_sel + n]);
+  if (a.s == 0.0) a = Stat{-INFINITY, 0.0, 0.0, 0.0, a.zy};   // logits of -infinity only: t is 0 times that
   // every lane's sums relative to the maximum of all, then plain sums: one exponential a lane
-  const double m = wave_max(a.s == 0.0 ? -INFINITY : a.m), e = a.s == 0.0 ? 0.0 : exp(a.m - m);
+  const double m = wave_max(a.m), e = a.s == 0.0 ? 0.0 : exp(a.m - m);
   a = Stat{m, wave_sum(a.s * e), wave_sum(a.t * e), wave_sum(a.rest * e), wave_sum(a.zy)};
   const Scores sc = scores_of(a, y, V);
   const SurrogateRow r = surrogate_row(S, row, sc.ok, sc.lp, sc.en);

@@ -160,6 +160,23 @@ def test_float32_gradient_products_in_every_tile_size(rows, d, V, select):
         assert (dH[rest] == 0).all() and (logp[rest] == 0).all()
 
 
+@pytest.mark.parametrize("rows,V,dead", [(1100, 512, (64, 192)), (1100, 512, (0, 64)), (2000, 2000, (128, 384))])
+def test_float32_update_of_vocabulary_that_cannot_be_taken(rows, V, dead):
+    """Weights of -infinity on whole parts of the vocabulary: no probability, and nothing for the entropy, as the scoring call has it."""
+    g, d = torch.Generator(device="cuda").manual_seed(rows + V), 32
+    H, W = torch.randn(rows, d, device="cuda", generator=g).abs() + 0.1, torch.randn(V, d, device="cuda", generator=g) / 8
+    W[dead[0]:dead[1]] = 0.0
+    W[dead[0]:dead[1], 3] = -float("inf")
+    ids = torch.randint(dead[1], V, (rows,), device="cuda", dtype=torch.int32, generator=g)
+    lp, _, entropy = umas.umas_policy_logprobs(H, W, ids, None)
+    assert entropy.isfinite().all() and (entropy > 0).all()
+    stats, logp, _, _ = umas.umas_ppo_loss_fwd_bwd(H, W, ids, None, lp, torch.ones(rows, device="cuda"), None, 0, 0.2)
+    st = umas.read_stats(stats)[0]
+    # float64 sums in two orders, each entropy and log-prob rounded to float32 once
+    assert abs(float(st["entropy_mean"]) - float(entropy.double().mean())) <= 2.0 ** -22 * float(entropy.max())
+    assert (logp.double() - lp.double()).abs().max() <= 2.0 ** -22 * float(lp.abs().max()) and abs(float(st["loss"]) + 1.0) <= 1e-5
+
+
 @pytest.mark.parametrize("n,n_sel,shift", [(1, 1, 0), (2, 1, 1), (127, 5, 3), (129, 128, 0), (8300, 3, 2), (8300, 8299, 1), (70000, 50001, 0), (600000, 10, 0), (600000, 480001, 3)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_critic_defines_the_rows_that_are_not_selected(n, n_sel, shift, dtype):
