@@ -14,7 +14,6 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <algorithm>
-#include <array>
 #include <initializer_list>
 
 #include "../../include/umas.h"
@@ -162,47 +161,6 @@ at::Tensor fresh(at::IntArrayRef size, at::ScalarType type, const at::Device& de
 at::Tensor workspace(size_t bytes, const at::Device& dev) {
   return fresh({static_cast<int64_t>(std::max<size_t>(bytes, 256))}, at::kByte, dev);
 }
-// Several small arrays of one call in one allocation, each a tensor of its own on the shared storage: the allocator takes 0.9 us a time, which
-// is most of what a call of a few thousand tokens costs the host (routing allocates seventeen arrays: 16 -> 6.6 us; the calls around
-// a batch of 46 000 tokens 49 -> 34).  Larger ones are allocated one by one: whoever keeps one of them does not keep the others.
-struct Spec {
-  int64_t size[2];
-  size_t dims;
-  at::ScalarType type;
-  at::IntArrayRef sizes() const { return at::IntArrayRef(size, dims); }
-  bool negative() const { return size[0] < 0 || size[1] < 0; }
-  int64_t count() const { return size[0] * size[1]; }
-};
-Spec vec(int64_t n, at::ScalarType type) { return Spec{{n, 1}, 1, type}; }
-Spec mat(int64_t n, int64_t m, at::ScalarType type) { return Spec{{n, m}, 2, type}; }
-Spec room(size_t bytes) { return vec(static_cast<int64_t>(std::max<size_t>(bytes, 256)), at::kByte); }   // a workspace
-constexpr int64_t kSharedBytes = 2 << 20;
-template <size_t N>
-std::array<at::Tensor, N> fresh_all(const Spec (&specs)[N], const at::Device& dev) {
-  std::array<at::Tensor, N> out;
-  int64_t at_byte[N], total = 0;
-  for (size_t i = 0; i < N; ++i) {
-    if (specs[i].negative()) {                            // at::empty says what is wrong
-      total = kSharedBytes + 1;
-      break;
-    }
-    at_byte[i] = total;
-    total += (specs[i].count() * static_cast<int64_t>(c10::elementSize(specs[i].type)) + 255) / 256 * 256;
-    if (total > kSharedBytes) break;
-  }
-  const at::Tensor base = total > 0 && total <= kSharedBytes ? fresh({total}, at::kByte, dev) : at::Tensor();
-  for (size_t i = 0; i < N; ++i) {
-    if (!base.defined() || specs[i].count() == 0) {       // an empty tensor has no storage
-      out[i] = fresh(specs[i].sizes(), specs[i].type, dev);
-      continue;
-    }
-    out[i] = at::detail::make_tensor<c10::TensorImpl>(c10::Storage(base.storage()), base.key_set(), c10::scalarTypeToTypeMeta(specs[i].type));
-    c10::TensorImpl* const t = out[i].unsafeGetTensorImpl();
-    t->set_storage_offset(at_byte[i] / static_cast<int64_t>(c10::elementSize(specs[i].type)));
-    t->set_sizes_contiguous(specs[i].sizes());
-  }
-  return out;
-}
 struct Output {                                           // what the caller passed, or a new tensor
   at::Tensor t;
   PyObject* given;
@@ -315,12 +273,11 @@ PyObject* assign(PyObject* const* a) {
   const at::Device dev = mask.device();
   const int64_t U1 = std::max<int64_t>(U, 1), N1 = std::max<int64_t>(N, 1);
   const auto i64 = at::kLong, i32 = at::kInt, f32 = at::kFloat, u8 = at::kByte;
-  const Spec specs[kStreamTensors + 1] = {
-      vec(M + 1, i64), vec(N, i64), vec(N, i32), vec(N, i32), vec(N, u8), vec(N, f32), vec(U + 1, i64), vec(U1, i32), vec(M + 1, i32),
-      vec(U + 1, i64), vec(M + 1, i32), vec(N1, i32), vec(M + 1, i64), vec(U1, f32), vec(U1, i32), vec(N, u8),
-      room(umas_assign_workspace_bytes(&g))};
-  const auto out = fresh_all(specs, dev);
-  const at::Tensor& ws = out[kStreamTensors];
+  const at::Tensor out[kStreamTensors] = {
+      fresh({M + 1}, i64, dev), fresh({N}, i64, dev), fresh({N}, i32, dev), fresh({N}, i32, dev), fresh({N}, u8, dev), fresh({N}, f32, dev),
+      fresh({U + 1}, i64, dev), fresh({U1}, i32, dev), fresh({M + 1}, i32, dev), fresh({U + 1}, i64, dev), fresh({M + 1}, i32, dev),
+      fresh({N1}, i32, dev), fresh({M + 1}, i64, dev), fresh({U1}, f32, dev), fresh({U1}, i32, dev), fresh({N}, u8, dev)};
+  const at::Tensor ws = workspace(umas_assign_workspace_bytes(&g), dev);
   umas_streams s;
   for (int i = 0; i < kStreamTensors; ++i) reinterpret_cast<void**>(&s)[i] = ptr_or<void>(out[i], ws.data_ptr());
   UMAS_CALL(umas_assign_token_rewards(&g, &r, ptr_or<uint8_t>(mask, ws.data_ptr()), &s, ws.data_ptr(), ws.numel(), st));
@@ -339,8 +296,7 @@ PyObject* advantages(PyObject* const* a) {                // streams, value, gam
   const int32_t U = static_cast<int32_t>(int_attr(a[0], g_n_turns));
   const float gamma = real(a[2]), lam = real(a[3]), gamma_turn = real(a[4]);
   const int32_t seg = integer32(a[5]);
-  const auto out = fresh_all({vec(N, at::kFloat), vec(N, at::kFloat), room(umas_advantages_workspace_bytes(N))}, dev);
-  const at::Tensor &adv = out[0], &ret = out[1], &ws = out[2];
+  const at::Tensor adv = fresh({N}, at::kFloat, dev), ret = fresh({N}, at::kFloat, dev), ws = workspace(umas_advantages_workspace_bytes(N), dev);
   const umas_streams s = streams_of(a[0], ws.data_ptr());
   const float* value = ptr_or_null<const float>(a[1]);
   void* const st = stream_of(a[6]);
@@ -459,8 +415,7 @@ PyObject* kl_rewards(PyObject* const* a) {                // tok_reward, logp, l
   const int64_t n = r.numel();
   const at::Device dev = r.device();
   const Output out(a[5], [&] { return at::empty_like(r); });
-  const auto both = fresh_all({vec(1, at::kFloat), room(umas_kl_rewards_workspace_bytes(n))}, dev);
-  const at::Tensor &kl = both[0], &ws = both[1];
+  const at::Tensor kl = fresh({1}, at::kFloat, dev), ws = workspace(umas_kl_rewards_workspace_bytes(n), dev);
   auto at_ = [&](const at::Tensor& t) { return n ? t.data_ptr() : ws.data_ptr(); };
   const at::Tensor &logp = tensor(a[1]), &ref = tensor(a[2]), &mask = tensor(a[3]);
   const float beta = real(a[4]);
@@ -502,9 +457,10 @@ PyObject* ready_batch(PyObject* const* a) {               // streams, traj_turn_
     n_rowsel = tensor(t.o).numel();
   }
   const int64_t arg = cut == 2 ? as_int(a[3]) : integer32(a[3]);
-  const auto out = fresh_all({vec(std::max<int64_t>(n_rowsel, 1), at::kInt), mat(M, (cut == 2 ? B : arg) + 1, at::kLong), vec(cut == 2 ? M : 0, at::kInt),
-                              room(umas_ready_batch_workspace_bytes(B, M))}, dev);
-  const at::Tensor &rows = out[0], &off = out[1], &parts = out[2], &ws = out[3];
+  const at::Tensor rows = fresh({std::max<int64_t>(n_rowsel, 1)}, at::kInt, dev);
+  const at::Tensor off = fresh({M, (cut == 2 ? B : arg) + 1}, at::kLong, dev);
+  const at::Tensor parts = cut == 2 ? fresh({M}, at::kInt, dev) : at::Tensor();
+  const at::Tensor ws = workspace(umas_ready_batch_workspace_bytes(B, M), dev);
   const umas_streams s = streams_of(a[0], ws.data_ptr());
   const int32_t* const t = tto.as<int32_t>();
   const uint8_t* const k = keep.as<uint8_t>();

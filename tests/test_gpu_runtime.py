@@ -262,3 +262,24 @@ def test_two_pipelines_on_two_streams_at_once():
         assert torch.equal(off0, off1)
         n_kept = int(off0[-1, -1].item())
         assert torch.equal(rows0[:n_kept], rows1[:n_kept])
+
+
+def test_every_output_has_memory_of_its_own():
+    """One that is resized, freed or written to a file is that and no more."""
+    w = wl.make_workload(2, n_traj=8, tokens_per_turn=48, models=SMALL_BF16)
+    s = umas.umas_assign_token_rewards(**assign_kwargs(w, P.to_dev(w.tok_mask)))
+    streams = [t for t in vars(s).values() if isinstance(t, torch.Tensor)]
+    assert len(streams) == 16
+    adv, ret = umas.umas_advantages(s, P.to_dev(w.value), w.gamma, w.lam)
+    logp = torch.zeros_like(adv)
+    out, kl = umas.umas_kl_rewards(s.tok_reward, logp, logp, s.tok_mask, 0.05)
+    rows, off, parts = umas.umas_ready_batch_packed(s, w.traj_turn_off, 100)
+    outputs = streams + [adv, ret, out, kl, rows, off, parts]
+    for t in outputs:
+        assert t.storage_offset() == 0 and t.untyped_storage().nbytes() == t.numel() * t.element_size()
+    before = [t.clone() for t in outputs]
+    for t in outputs:
+        t.resize_(t.numel() + 5000).fill_(1)
+    for t, b in zip(outputs, before):
+        t.copy_(torch.cat([b.flatten(), torch.ones(5000, dtype=b.dtype, device="cuda")]))
+    assert all(torch.equal(t[:b.numel()], b.flatten()) and (t[b.numel():] == 1).all() for t, b in zip(outputs, before))
