@@ -339,7 +339,7 @@ constexpr unsigned kSmallMovers = 16;               // workgroups that move slic
 static_assert(kSmallTraj * 9 + 4 + 3 * kAlign <= kSmallThin && kSmallThin <= 16 * kSmallThreads, "offsets, order and flags, 16 bytes a thread");
 
 struct SmallArgs {
-  ThinStage::Reader thin;
+  const char* thin;
   int thin16, at_order, at_keep;                    // byte offsets in the block, -1: none; traj_turn_off is at 0
   int n_turns, n_traj, n_models, n_minibatch, balance_rows;
   int64_t max_rows;                                 // packed parts when n_parts is given
@@ -389,7 +389,7 @@ k_ready_small(SmallArgs A) {
   // them, for whose loads come back in order and few runs leave these nothing to search
   const int t16 = kSmallThreads - 1 - tid;
   uint4 thin = make_uint4(0u, 0u, 0u, 0u);
-  if (t16 < A.thin16) thin = reinterpret_cast<const uint4*>(A.thin.block)[t16];
+  if (t16 < A.thin16) thin = reinterpret_cast<const uint4*>(A.thin)[t16];
   if (tid <= K) {
     s_tok[tid] = A.model_tok_off[tid];
     s_sel[tid] = A.model_rowsel_off[tid];
@@ -424,7 +424,7 @@ k_ready_small(SmallArgs A) {
     if (end > start) turn = A.tok_turn[start];
   }
   if (t16 < A.thin16) reinterpret_cast<uint4*>(s_thin)[t16] = thin;
-  stage_read_done(A.thin);                          // also the barrier behind the stores to LDS
+  __syncthreads();
   const int32_t* const tto = reinterpret_cast<const int32_t*>(s_thin);
   // ---- ranks of the kept trajectories in shuffled order
   int b = -1;
@@ -634,8 +634,7 @@ umas_status ready_batch(const umas_streams* s, int32_t n_models, int32_t n_turns
     A.model_rowsel_off = s->model_rowsel_off; A.rowsel = s->rowsel; A.tok_turn = s->tok_turn;
     A.mb_rowsel = mb_rowsel; A.mb_off = mb_off; A.n_parts = n_parts;
     const unsigned grid = 1 + std::max(kSmallMovers, cdiv(static_cast<size_t>(n_mq), kSmallThreads / kWave));
-    vs = stage.lend(grid, st, &A.thin);
-    if (vs != UMAS_OK) return vs;
+    A.thin = stage.lend();
     hipLaunchKernelGGL(k_ready_small, dim3(grid), dim3(kSmallThreads), 0, st, A);
     vs = stage.launched(st, hipGetLastError());
     if (vs == UMAS_OK && g_prof_on) prof_kernel("k_ready_small", st);

@@ -22,16 +22,10 @@ void prof_kernel(const char* name, hipStream_t st); // closes the interval of th
 // the library keeps (a ring of kSlots blocks, each grown to the largest request it has seen) and launch ONE kernel that
 // reads the block over the bus: the caller's arrays have been read when the call returns, and the
 // host never waits for the stream.  A block is reused kSlots calls later; only then does the host wait, and only
-// until the kernel that was launched on that block has read it, which it says in words behind the block (Reader).
+// until the kernel that was launched on that block has run.
 class ThinStage {
  public:
   static constexpr int kSlots = 4;
-  // What a kernel that reads the block needs: the block, and a word for every workgroup that it sets to 1 when it has read what it
-  // wants (read_done; NULL under capture, where an event stands for the words).
-  struct Reader {
-    const char* block;
-    uint32_t* done;
-  };
   // Takes the next block of the ring with room for `bytes`; 256-byte aligned.  Holds the ring's lock until the block is handed
   // to a kernel (flush, or lend and launched).
   umas_status begin(size_t bytes);
@@ -42,9 +36,9 @@ class ThinStage {
   char* at(size_t off) { return cur_ + off; }
   // Enqueues the copy of the first `bytes` bytes of the block to `dst` on `st` and releases the ring.
   umas_status flush(void* dst, size_t bytes, hipStream_t st);
-  // In place of flush: the block for a kernel of n_wg workgroups that reads it itself and is launched next on `st`, then, with what the
+  // In place of flush: the block's address on the device, for a kernel that reads it itself and is launched next on `st`, then, with what the
   // launch said, the release of the ring.
-  umas_status lend(unsigned n_wg, hipStream_t st, Reader* r);
+  const char* lend() const;
   umas_status launched(hipStream_t st, hipError_t e);
   // Releases the ring without copying (an error between begin and flush).
   void abandon();
@@ -52,8 +46,6 @@ class ThinStage {
  private:
   char* cur_ = nullptr;
   int slot_ = -1;
-  size_t bytes_ = 0;
-  unsigned n_wg_ = 0;
 };
 
 #define UMAS_HIP(expr)                                                                 \
@@ -113,13 +105,6 @@ __device__ __forceinline__ void store_stream(void* p, const V& v) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   static_assert(sizeof(V) == 16, "16 bytes");
   __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), static_cast<u32x4*>(p));
-}
-
-// At the end of a kernel that reads a staging block: everything this workgroup reads of it has arrived.  Every thread calls it.
-__device__ __forceinline__ void stage_read_done(const ThinStage::Reader& r) {
-  __builtin_amdgcn_s_waitcnt(0);   // this wavefront's loads are back
-  __syncthreads();
-  if (threadIdx.x == 0 && r.done) __hip_atomic_store(r.done + blockIdx.x, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 template <typename T>

@@ -822,7 +822,7 @@ struct SmallArgs {
   PlanArgs plan;                                   // thin arrays: as if they lay in the workspace
   TokArgs tok;
   const char* ws;
-  ThinStage::Reader thin;
+  const char* thin;
   int thin16, n_groups;
   float norm_eps;
   const int32_t* group_off;
@@ -867,12 +867,12 @@ k_route_small(SmallArgs A) {
   const int blk0 = blockIdx.x * kTokBlock, ntok = N - blk0 < kTokBlock ? N - blk0 : kTokBlock;
   // ---- the thin arrays
   {
-    const uint4* const from = reinterpret_cast<const uint4*>(A.thin.block);
+    const uint4* const from = reinterpret_cast<const uint4*>(A.thin);
     for (int i = tid; i < A.thin16; i += kSmallThreads) reinterpret_cast<uint4*>(s_thin)[i] = from[i];
     for (int i = tid; i < U; i += kSmallThreads) s_lastv[i] = -1;
     if (tid == 0) s_ahead = 0;
   }
-  stage_read_done(A.thin);                          // also the barrier behind the stores to LDS
+  __syncthreads();
   auto here = [&](auto* p) { return reinterpret_cast<decltype(p)>(s_thin + (reinterpret_cast<const char*>(p) - A.ws)); };
   PlanArgs L = A.plan;
   L.traj_turn_off = here(L.traj_turn_off);
@@ -1224,8 +1224,7 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
     SmallArgs A;
     A.plan = P; A.tok = T; A.ws = ws_base; A.thin16 = static_cast<int>(thin / 16); A.n_groups = n_groups; A.norm_eps = r->norm_eps;
     A.group_off = w.group_off; A.group_members = has.members ? w.group_members : nullptr; A.rowsel = o->rowsel;
-    vs = stage.lend(static_cast<unsigned>(nbk), st, &A.thin);
-    if (vs != UMAS_OK) return vs;
+    A.thin = stage.lend();
     const dim3 grid(static_cast<unsigned>(nbk)), threads(kSmallThreads);
     if (K <= 1) hipLaunchKernelGGL(k_route_small<1>, grid, threads, 0, st, A);
     else if (K <= 2) hipLaunchKernelGGL(k_route_small<2>, grid, threads, 0, st, A);
