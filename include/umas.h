@@ -22,7 +22,8 @@
  *     ring of four blocks, each as large as the largest graph it has seen) and enqueue a kernel
  *     that reads it over the bus: the caller may free or overwrite its arrays on return, and the
  *     host can queue the next step while this one runs.  The one wait there is: a block is
- *     reused four such calls later, after the kernel that was launched on it has run.  Results,
+ *     reused four such calls later, after the kernel that was launched on it has run.  A stream that
+ *     is being captured is refused by these two calls (UMAS_EINVAL).  Results,
  *     including loss statistics, stay on the device.  Every other call only launches kernels
  *     (memory is cleared by fill kernels, never by memset nodes), so it may be recorded into a
  *     HIP graph as long as profiling (umas_profile_enable) is off.

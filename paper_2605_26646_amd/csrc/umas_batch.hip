@@ -617,7 +617,7 @@ umas_status ready_batch(const umas_streams* s, int32_t n_models, int32_t n_turns
   const size_t staged_bytes = static_cast<size_t>(reinterpret_cast<char*>(w.rank) - ws_base);
   const int ntile = scan_tiles(n_traj);
   ThinStage stage;
-  umas_status vs = stage.begin(staged_bytes);
+  umas_status vs = stage.begin(staged_bytes, st);
   if (vs != UMAS_OK) return vs;
   stage.put(static_cast<size_t>(reinterpret_cast<char*>(w.traj_turn_off) - ws_base), traj_turn_off, (static_cast<size_t>(n_traj) + 1) * sizeof(int32_t));
   stage.put(static_cast<size_t>(reinterpret_cast<char*>(w.order) - ws_base), traj_order, static_cast<size_t>(n_traj) * sizeof(int32_t));

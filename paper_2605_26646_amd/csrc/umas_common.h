@@ -27,8 +27,8 @@ class ThinStage {
  public:
   static constexpr int kSlots = 4;
   // Takes the next block of the ring with room for `bytes`; 256-byte aligned.  Holds the ring's lock until the block is handed
-  // to a kernel (flush, or lend and launched).
-  umas_status begin(size_t bytes);
+  // to a kernel (flush, or lend and launched).  Refuses a stream that is being captured.
+  umas_status begin(size_t bytes, hipStream_t st);
   // Copies n bytes to offset `off` of the block (nothing for src == nullptr or n == 0).
   void put(size_t off, const void* src, size_t n);
   void zero(size_t off, size_t n);

@@ -53,7 +53,11 @@ int g_next_slot = 0;
 std::mutex g_stage_mutex;
 }  // namespace
 
-umas_status ThinStage::begin(size_t bytes) {
+umas_status ThinStage::begin(size_t bytes, hipStream_t st) {
+  // a graph would read the block again when later calls have overwritten it
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  UMAS_HIP(hipStreamIsCapturing(st, &capture));
+  UMAS_REQUIRE(capture == hipStreamCaptureStatusNone, UMAS_EINVAL, "a call that takes host arrays cannot be recorded into a graph: hip_stream is being captured");
   g_stage_mutex.lock();
   slot_ = g_next_slot;
   g_next_slot = (g_next_slot + 1) % kSlots;

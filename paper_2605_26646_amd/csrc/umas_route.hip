@@ -1163,7 +1163,7 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
   const size_t staged_bytes = static_cast<size_t>(reinterpret_cast<char*>(w.traj_norm) - ws_base);
   const int n_chunks = plan_chunks(B);
   ThinStage stage;
-  vs = stage.begin(staged_bytes);
+  vs = stage.begin(staged_bytes, st);
   if (vs != UMAS_OK) return vs;
   auto put = [&](const void* dst, const void* src, size_t bytes) {
     stage.put(static_cast<size_t>(static_cast<const char*>(dst) - ws_base), src, bytes);

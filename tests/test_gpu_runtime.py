@@ -283,3 +283,30 @@ def test_every_output_has_memory_of_its_own():
     for t, b in zip(outputs, before):
         t.copy_(torch.cat([b.flatten(), torch.ones(5000, dtype=b.dtype, device="cuda")]))
     assert all(torch.equal(t[:b.numel()], b.flatten()) and (t[b.numel():] == 1).all() for t, b in zip(outputs, before))
+
+
+def test_calls_with_host_arrays_are_not_recorded():
+    """A graph would read the staging block again after later calls have overwritten it: refused, and the ring stays as it was."""
+    w = wl.make_workload(2, n_traj=8, tokens_per_turn=48, models=SMALL_BF16)
+    front = P.oracle_front(w)
+    kw = assign_kwargs(w, P.to_dev(w.tok_mask))
+    s = umas.umas_assign_token_rewards(**kw)
+    rows, off = umas.umas_ready_batch(s, w.traj_turn_off, 2)
+    graph, x = torch.cuda.CUDAGraph(), torch.zeros(1, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        for _ in range(5):                               # more than the ring has blocks
+            with pytest.raises(Exception, match="cannot be recorded"):
+                umas.umas_assign_token_rewards(**kw)
+            with pytest.raises(Exception, match="cannot be recorded"):
+                umas.umas_ready_batch(s, w.traj_turn_off, 2)
+        x += 1                                           # the capture itself goes on
+    for k in range(3):
+        graph.replay()
+        for _ in range(5):
+            s2 = umas.umas_assign_token_rewards(**kw)
+            rows2, off2 = umas.umas_ready_batch(s2, w.traj_turn_off, 2)
+        torch.cuda.synchronize()
+        assert float(x) == k + 1 and torch.equal(off, off2) and torch.equal(rows[:int(off[-1, -1])], rows2[:int(off[-1, -1])])
+    adv, ret = umas.umas_advantages(s2, P.to_dev(w.value), w.gamma, w.lam, w.gamma_turn, w.seg_mode)
+    P.check_front(w, s2, adv, ret, *front)
