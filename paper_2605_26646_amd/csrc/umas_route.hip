@@ -1171,14 +1171,18 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
   put(w.role_to_model, g->role_to_model, sizeof(int32_t) * R);
   put(w.traj_turn_off, g->traj_turn_off, sizeof(int32_t) * (static_cast<size_t>(B) + 1));
   {
+    // Pointers of their own that do not overlap: a store of bytes may change anything, also where the graph says that its arrays lie, and then
+    // the host takes one turn at a time (2.4 million turns of 16 tokens 5.7 ms a call with its scan, 4.9 like this; 250 000 565 and 486 us).
     char* const block = stage.at(0);
-    uint8_t* const role = reinterpret_cast<uint8_t*>(block + (reinterpret_cast<char*>(w.turn_role) - ws_base));
-    for (int u = 0; u < U; ++u) role[u] = static_cast<uint8_t>(g->turn_role[u]);
+    const int32_t* __restrict__ const turn_role = g->turn_role;
+    const int64_t* __restrict__ const turn_tok_off = g->turn_tok_off;
+    uint8_t* __restrict__ const role = reinterpret_cast<uint8_t*>(block + (reinterpret_cast<char*>(w.turn_role) - ws_base));
+    for (int u = 0; u < U; ++u) role[u] = static_cast<uint8_t>(turn_role[u]);
     static_assert(UMAS_MAX_ROLES <= 256, "a role is a byte");
-    uint32_t* const off = reinterpret_cast<uint32_t*>(block + (reinterpret_cast<char*>(w.tok_off32) - ws_base));
-    if (has.wide_offsets) put(w.tok_off64, g->turn_tok_off, sizeof(int64_t) * (static_cast<size_t>(U) + 1));
+    uint32_t* __restrict__ const off = reinterpret_cast<uint32_t*>(block + (reinterpret_cast<char*>(w.tok_off32) - ws_base));
+    if (has.wide_offsets) put(w.tok_off64, turn_tok_off, sizeof(int64_t) * (static_cast<size_t>(U) + 1));
     else
-      for (int u = 0; u <= U; ++u) off[u] = static_cast<uint32_t>(g->turn_tok_off[u]);
+      for (int u = 0; u <= U; ++u) off[u] = static_cast<uint32_t>(turn_tok_off[u]);
   }
   put(w.role_reward, r->role_reward, sizeof(float) * static_cast<size_t>(B) * R);
   put(w.turn_reward, r->turn_reward, sizeof(float) * U);
