@@ -38,17 +38,16 @@ constexpr int kThreads = 256;
 constexpr int kIpt = 4;                          // tokens per thread: one 16-byte load per array, no transposition
 constexpr int kTile = kThreads * kIpt;           // tokens per tile
 constexpr int kChunkTiles = 8;                   // nominal tiles per range at most
-constexpr int kTurnChunkTiles = 4;               // ... of turns that are on average no longer than that
 // Nominal tokens per range: a range's tiles are done one after the other, so a stream that makes fewer than 512 ranges of
 // eight tiles (4.2 million tokens) is cut finer, into 512 and more where it has as many tiles: two for every compute unit
 // (49 152 tokens: 6 ranges of eight tiles 19 us, 48 of one 7 us; the call, waited for, 40 -> 28 us, 400 000 tokens 43 -> 33,
 // 225 000 in segments that are cut 91 -> 60; 25 million tokens keep ranges of eight, 62 us).
-// Turns end every few tiles, so that finer ranges are even ones, and the last round of them is shorter (ranges of eight and four tiles: 42 million
-// tokens in turns of 1024 and 4096 155 and 149 us, 25.6 in turns of 512 94 and 90, 3.2 in turns of 400 22.1 and 20.7); runs of a trajectory
-// may be longer than a range, which is then empty as often as not (42 million in runs of 5120 to 15 360 165 and 209).
-inline int64_t chunk_tokens(int64_t n_tokens, int most) {
+// Finer ranges are 3 to 7 % faster where all turns are short (42 million tokens in turns of 256 110.5 and 108 us, of 1024 and 4096 154
+// and 143), but the number of turns does not say that: of 30 000 tokens and twenty of 100 each 265 and 334 us, 6 million in turns of 15 000 and 128 30
+// and 36; and runs of a trajectory may be longer than a range, which is then empty as often as not.
+inline int64_t chunk_tokens(int64_t n_tokens) {
   const int64_t tiles = n_tokens / (static_cast<int64_t>(kTile) * 512);
-  return (tiles < 1 ? 1 : tiles > most ? most : tiles) * kTile;
+  return (tiles < 1 ? 1 : tiles > kChunkTiles ? kChunkTiles : tiles) * kTile;
 }
 constexpr int64_t kLongSegment = 16 * kTile;     // a segment end farther away than this does not move a range's edge
 // Up to so many tokens a workgroup whose range ends inside a long segment reads on to its end itself instead of leaving the range to
@@ -540,7 +539,7 @@ using namespace umas;
 
 extern "C" size_t umas_advantages_workspace_bytes(int64_t n_tokens) {
   if (n_tokens < 0) return 0;
-  return scan_bytes(n_tokens, chunk_tokens(n_tokens, kTurnChunkTiles));
+  return scan_bytes(n_tokens, chunk_tokens(n_tokens));
 }
 
 extern "C" umas_status umas_advantages(const umas_streams* s, int64_t n_tokens, int32_t n_turns,
@@ -570,8 +569,7 @@ extern "C" umas_status umas_advantages(const umas_streams* s, int64_t n_tokens, 
   prof_mark(st);
   ScanParams P;
   P.n_tokens = n_tokens;
-  const bool short_turns = seg_mode == UMAS_SEG_TURN && n_tokens <= static_cast<int64_t>(n_turns) * (kTurnChunkTiles * kTile);
-  P.chunk = chunk_tokens(n_tokens, short_turns ? kTurnChunkTiles : kChunkTiles);
+  P.chunk = chunk_tokens(n_tokens);
   while (scan_bytes(n_tokens, P.chunk) > workspace_bytes) P.chunk += kTile;
   const int64_t n_ranges = scan_ranges(n_tokens, P.chunk);
   P.n_ranges = static_cast<uint32_t>(n_ranges);
