@@ -26,7 +26,7 @@
 // (one per compute unit at most, a fraction of what the device holds at once, so all of them run together): a range
 // only ever waits for maps of ranges to its right, written by the first kernel or by a workgroup that is running,
 // and publishing a map waits for nothing, so every wait ends.  When no segment is that long the second kernel finds
-// nothing to do and leaves at once.  Few tokens (kAloneTokens) are done without it.
+// nothing to do and leaves at once.  Few tokens (alone_tokens) are done without it.
 #include <type_traits>
 
 #include "umas_common.h"
@@ -51,9 +51,10 @@ inline int64_t chunk_tokens(int64_t n_tokens) {
 }
 constexpr int64_t kLongSegment = 16 * kTile;     // a segment end farther away than this does not move a range's edge
 // Up to so many tokens a workgroup whose range ends inside a long segment reads on to its end itself instead of leaving the range to
-// a second launch, which costs 5 us also when there is nothing to do (46 000 tokens in turns: 11.4 us in two launches that follow each
-// other, 6.8 in one; 11 and 5.7 us of the host).
-constexpr int64_t kAloneTokens = 64 * kTile;
+// a second launch, which costs 4 us also when there is nothing to do (turns of 400, 20 000 to 65 000 tokens 10.1 us in two launches that follow each
+// other, 6.5 in one; 11 and 5.7 us of the host).  With one segment of all tokens, the longest way to read: 49 152 and 65 536 tokens 28.8
+// and 29.9 us in two, 21.5 and 25.1 in one, with values 38.6 and 40.3, 31.5 and 40.3; with step discounts too 42.6 and 44.5, 40.8 and 52.5.
+inline int64_t alone_tokens(bool decay) { return (decay ? 48 : 64) * kTile; }
 constexpr int kAhead = 1;                        // tiles whose loads are in flight beyond the one in work
 
 enum : uint8_t { kFlagMask = 1, kFlagTurnEnd = 2, kFlagRunEnd = 4 };
@@ -404,20 +405,30 @@ __device__ __forceinline__ void walk_range(const ScanParams& P, const Range& R, 
 }
 
 // The map of the tokens R, which end a segment, for a workgroup that needs the state on their left: every wavefront folds a quarter of
-// them, 256 at a time, and needs a barrier only at the end.  Every thread gets the map.
+// them, 1024 at a time, sixteen to a lane, and needs a barrier only at the end.  Every thread gets the map.  (Four to a lane make four
+// times as many compositions across lanes: one segment of 65 536 tokens with values 59 us, 70 with step discounts.)
 template <bool HV, bool DECAY>
 __device__ __forceinline__ Aff fold_ahead(const ScanParams& P, const Range& R, Aff* s_w, const float* s_kap) {
-  constexpr int nwave = kThreads / kWave, kStep = kWave * kIpt;
+  constexpr int nwave = kThreads / kWave, kFours = 4, kLane = kFours * kIpt, kStep = kWave * kLane;
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   const int64_t first = R.start / kStep, n = (R.end - 1) / kStep + 1 - first, per = (n + nwave - 1) / nwave;
   const int64_t lo = first + wave * per, hi = lo + per < first + n ? lo + per : first + n;
   Aff map = aff_identity();
-  Raw next;
-  if (hi > lo) load_four<HV>(P, R, (hi - 1) * kStep + lane * kIpt, next);
+  Raw next[kFours];
+  auto load = [&](int64_t t) {
+#pragma unroll
+    for (int i = 0; i < kFours; ++i) load_four<HV>(P, R, t * kStep + lane * kLane + i * kIpt, next[i]);
+  };
+  if (hi > lo) load(hi - 1);
   for (int64_t t = hi - 1; t >= lo; --t) {
-    const Raw x = next;
-    if (t > lo) load_four<HV>(P, R, (t - 1) * kStep + lane * kIpt, next);
-    Aff acc = fold_four<HV, DECAY>(P, four_tokens<DECAY>(P, R, t * kStep + lane * kIpt, x, s_kap));
+    Raw x[kFours];
+#pragma unroll
+    for (int i = 0; i < kFours; ++i) x[i] = next[i];
+    if (t > lo) load(t - 1);
+    Aff acc = aff_identity();
+#pragma unroll
+    for (int i = kFours - 1; i >= 0; --i)
+      acc = then<HV>(acc, fold_four<HV, DECAY>(P, four_tokens<DECAY>(P, R, t * kStep + lane * kLane + i * kIpt, x[i], s_kap)));
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
       const Aff right = aff_shfl_down<HV>(acc, o);
@@ -588,8 +599,7 @@ extern "C" umas_status umas_advantages(const umas_streams* s, int64_t n_tokens, 
   P.lam = lam;
   P.gamma_turn = gamma_turn;
   const bool decay = seg_mode == UMAS_SEG_TRAJ && gamma_turn != 1.0f;
-  // no segment reaches far enough past a range's edge to be cut, or the tokens are few enough to be read again
-  const bool alone = n_tokens <= kAloneTokens || n_tokens - P.chunk < kLongSegment;
+  const bool alone = n_tokens <= alone_tokens(decay);
   auto pick = [&](auto al) -> void (*)(ScanParams, float*, float*) {
     constexpr bool A = decltype(al)::value;
     return value ? (decay ? k_gae_scan<true, true, A> : k_gae_scan<true, false, A>) : (decay ? k_gae_scan<false, true, A> : k_gae_scan<false, false, A>);
