@@ -599,7 +599,9 @@ extern "C" umas_status umas_advantages(const umas_streams* s, int64_t n_tokens, 
   P.lam = lam;
   P.gamma_turn = gamma_turn;
   const bool decay = seg_mode == UMAS_SEG_TRAJ && gamma_turn != 1.0f;
-  const bool alone = n_tokens <= alone_tokens(decay);
+  // (alone, workgroups read tokens that are others' to write the outputs of: not where these lie over the inputs)
+  auto apart = [&](const float* out, const float* in) { return !in || out + n_tokens <= in || in + n_tokens <= out; };
+  const bool alone = n_tokens <= alone_tokens(decay) && apart(adv, s->tok_reward) && apart(adv, value) && apart(ret, s->tok_reward) && apart(ret, value);
   auto pick = [&](auto al) -> void (*)(ScanParams, float*, float*) {
     constexpr bool A = decltype(al)::value;
     return value ? (decay ? k_gae_scan<true, true, A> : k_gae_scan<true, false, A>) : (decay ? k_gae_scan<false, true, A> : k_gae_scan<false, false, A>);

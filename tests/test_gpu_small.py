@@ -90,6 +90,29 @@ def test_scan_of_few_tokens_in_long_segments(n_tokens, n_turns, n_traj, seg_mode
     check_front_arraywise(w, s, adv, ret, wl.PLACE_ALL, seg_mode, gamma, lam, gamma_turn)
 
 
+@pytest.mark.parametrize("n_tokens,n_turns,seg_mode,gamma_turn", [(20000, 1, wl.SEG_TURN, 1.0), (49152, 2, wl.SEG_TRAJ, 0.9), (49153, 2, wl.SEG_TRAJ, 0.9), (65536, 2, wl.SEG_TRAJ, 1.0),
+                                                                  (5000, 40, wl.SEG_TURN, 1.0), (100000, 3, wl.SEG_TRAJ, 0.9)])
+@pytest.mark.parametrize("over", ["adv over the rewards, ret over the values", "ret over the rewards", "adv over the values"])
+def test_scan_written_over_its_inputs(n_tokens, n_turns, seg_mode, gamma_turn, over):
+    from paper_2605_26646_amd import binding
+    w = sized_graph(n_tokens, n_tokens, n_turns, 1, 1, 2, 0)
+    w.tok_mask[:] = 1
+    s, lib = route(w, wl.PLACE_ALL), umas.load_library()
+    value = P.to_dev(w.value)
+    want = umas.umas_advantages(s, value, 0.99, 0.95, gamma_turn, seg_mode)
+    ws = torch.empty(lib.umas_advantages_workspace_bytes(n_tokens), dtype=torch.uint8, device="cuda")
+    for _ in range(10):
+        r, v, adv, ret = s.tok_reward.clone(), value.clone(), torch.empty_like(value), torch.empty_like(value)
+        out = {"adv over the rewards, ret over the values": (r, v), "ret over the rewards": (adv, r), "adv over the values": (v, ret)}[over]
+        fields = {f: getattr(s, f).data_ptr() for f, _ in binding._Streams._fields_}
+        st = binding._Streams(**{**fields, "tok_reward": r.data_ptr()})
+        status = lib.umas_advantages(binding.C.addressof(st), n_tokens, n_turns, v.data_ptr(), 0.99, 0.95, gamma_turn, seg_mode, out[0].data_ptr(), out[1].data_ptr(),
+                                     ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+        assert status == 0, lib.umas_last_error().decode()
+        for got, x in zip(out, want):   # float32 maps composed in two orders: the tolerance of the scan's own tests
+            assert (got - x).abs().max() <= 1e-5 * max(1.0, float(x.abs().max()))
+
+
 @pytest.mark.parametrize("n", [1, 7, 8192, 8193, 49153, 65536, 65537])
 @pytest.mark.parametrize("density", [0.0, 0.6])
 def test_kl_rewards_of_few_tokens(n, density):
