@@ -649,7 +649,7 @@ inline umas_status update(const UpdateArgs& A, hipStream_t st) {
   const int per_wg = static_cast<int>(cdiv(most, wgs < most ? wgs : most)) * 1024;
   hipLaunchKernelGGL(k_row_dz_f32, dim3(cdiv(V, per_wg), static_cast<unsigned>(A.n_sel)), dim3(256), 0, st, A.z, A.part, splits, A.n_sel, per_wg, A.S, A.k_ent,
                      A.logp_c, A.ent_c, A.logp_new, A.dz);
-  UMAS_LAUNCHED("k_dz_kept_f32");
+  UMAS_LAUNCHED("k_dz_kept_f32");            // the timing aid's names are those of the steps, in few launches or many: kept logits into dz, the gradients
   launch_gradients(GradArgs{A.dz, A.W, A.H, A.d, V, A.S.rowsel, 0, static_cast<int>(A.n_sel), A.accumulate, A.dH, A.dW, 0, 0, 0},
                    StatArgs{A.S, A.n_sel, A.logp_c, A.ent_c, A.entropy_coef, A.norm_rows, A.stats}, st);
   UMAS_LAUNCHED("k_dw_f32");

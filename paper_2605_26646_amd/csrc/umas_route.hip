@@ -809,14 +809,17 @@ k_rowsel(SelArgs A) {
 // block itself (a few KB: one trip over the bus), makes the whole plan in LDS, and writes a block of 4096 tokens, four to a
 // thread; what lies in front of the block is not asked of the others but counted in the mask.  The first workgroup writes the
 // outputs per turn.  Copy, plan, tokens and compaction of 46 000 tokens in 115 turns: 39 us on the device, 12.7 in one launch; of 768
-// tokens in 24 turns: 30 and 8.2 (the whole float32 step 92 -> 78).
+// tokens in 24 turns: 30 and 8.2 (the whole float32 step 92 -> 78).  At the limit of tokens, each call waited for: in 16 turns 54 and 45 us, in
+// 512 72 and 56, in 500 of eight models and 25 groups 172 and 94.
 constexpr int kSmallThreads = kTokBlock / kTokPerThread;
-constexpr int kSmallTurns = 512;                   // LDS: 28 bytes a turn and the thin arrays
+constexpr int kSmallTurns = 512;                   // LDS: 48 bytes a turn, 4 a trajectory and the thin arrays
 constexpr size_t kSmallThin = 24 << 10;
 constexpr int kSmallTraj = kSmallThreads;          // one thread each
 constexpr int kSmallGroups = 128;                  // eight rounds of the workgroup's wavefronts
 constexpr int kSmallTokens = 16 * kTokBlock;
 constexpr size_t kSmallBus = 192 << 10;            // thin arrays times workgroups: 5 us at the rate of the bus
+static_assert(kSmallThin + kSmallTurns * (sizeof(int64_t) + sizeof(SegMeta) + 2 * sizeof(int32_t)) + kSmallTraj * sizeof(float) + 2048 <= 64 << 10,
+              "what a workgroup holds fits its LDS, 2 KB for sums and counts");
 
 struct SmallArgs {
   PlanArgs plan;                                   // thin arrays: as if they lay in the workspace

@@ -477,7 +477,7 @@ extern "C" umas_status umas_kl_rewards(const float* tok_reward, const float* log
   if (n_tokens <= kKlAlone && apart(logp) && apart(logp_ref)) {
     const unsigned wg = cdiv(static_cast<size_t>(n_tokens), kKlThreads * kSIpt) + 1;
     hipLaunchKernelGGL(k_kl_rewards_few, dim3(wg), dim3(kKlThreads), 0, st, n_tokens, tok_reward, logp, logp_ref, tok_mask, beta, tok_reward_out, kl_mean);
-    UMAS_LAUNCHED("k_kl_rewards");
+    UMAS_LAUNCHED("k_kl_rewards_few");
     return UMAS_OK;
   }
   const unsigned grid = stream_grid(n_tokens, kST * kSIpt);
