@@ -592,22 +592,30 @@ inline void launch_gradients(GradArgs A, const StatArgs& T, hipStream_t st) {
   const bool small = dh1 + dw1 <= kSmallGradTiles;
   auto size = [&](int64_t m, int tiles1) { return small || tiles1 <= kSmallGradTiles / 2 ? 0 : large_product(m, A.d) ? 2 : 1; };
   const int dh = size(A.rows, dh1), dw = size(A.V, dw1);
-  A.n_dh = tiles(A.rows, A.d, dh);
-  A.n_dw = tiles(A.V, A.d, dw);
+  const int n_dh = tiles(A.rows, A.d, dh), n_dw = tiles(A.V, A.d, dw);
   A.dw_first = A.rows > A.V ? 1 : 0;
-  const int n_stats = T.stats ? 1 + T.S.n_roles : 0;
-  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(A.n_dh + A.n_dw + n_stats)), dim3(kGradT), 0, st, A, T); };
-  switch (3 * dh + dw) {
-    case 0: return launch(k_gradients_f32<0, 0>);
-    case 1: return launch(k_gradients_f32<0, 1>);
-    case 2: return launch(k_gradients_f32<0, 2>);
-    case 3: return launch(k_gradients_f32<1, 0>);
-    case 4: return launch(k_gradients_f32<1, 1>);
-    case 5: return launch(k_gradients_f32<1, 2>);
-    case 6: return launch(k_gradients_f32<2, 0>);
-    case 7: return launch(k_gradients_f32<2, 1>);
-    default: return launch(k_gradients_f32<2, 2>);
-  }
+  auto launch = [&](int some_dh, int some_dw, const StatArgs& S) {
+    A.n_dh = some_dh;
+    A.n_dw = some_dw;
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(some_dh + some_dw + (S.stats ? 1 + S.S.n_roles : 0))), dim3(kGradT), 0, st, A, S);
+    };
+    switch (3 * dh + dw) {
+      case 0: return go(k_gradients_f32<0, 0>);
+      case 1: return go(k_gradients_f32<0, 1>);
+      case 2: return go(k_gradients_f32<0, 2>);
+      case 3: return go(k_gradients_f32<1, 0>);
+      case 4: return go(k_gradients_f32<1, 1>);
+      case 5: return go(k_gradients_f32<1, 2>);
+      case 6: return go(k_gradients_f32<2, 0>);
+      case 7: return go(k_gradients_f32<2, 1>);
+      default: return go(k_gradients_f32<2, 2>);
+    }
+  };
+  const int64_t n_w = static_cast<int64_t>(A.V) * A.d;
+  if (A.dW + n_w <= A.W || A.W + n_w <= A.dW) return launch(n_dh, n_dw, T);
+  launch(n_dh, 0, StatArgs{});               // dW lies over the weights, which dH has to have read by then
+  launch(0, n_dw, T);
 }
 
 // An update of one chunk of rows that keeps its logits, in three launches: the scores of parts of the vocabulary and the clearing, dz with all

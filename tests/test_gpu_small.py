@@ -183,6 +183,19 @@ def test_float32_gradient_products_in_every_tile_size(rows, d, V, select):
         assert (dH[rest] == 0).all() and (logp[rest] == 0).all()
 
 
+@pytest.mark.parametrize("rows,d,V", [(60, 33, 100), (300, 64, 512), (300, 512, 8190), (3000, 100, 101)])
+def test_float32_gradient_added_to_the_weights(rows, d, V):
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    H, W = torch.randn(rows, d, device="cuda", generator=g), torch.randn(V, d, device="cuda", generator=g) / d ** 0.5
+    ids = torch.randint(0, V, (rows,), device="cuda", dtype=torch.int32, generator=g)
+    adv = torch.randn(rows, device="cuda", generator=g)
+    stats, logp, dH, dW = umas.umas_ppo_loss_fwd_bwd(H, W, ids, None, None, adv, None, 0, 0.2, accumulate_dW=True, dW=W.clone())
+    for _ in range(5):
+        X = W.clone()
+        got = umas.umas_ppo_loss_fwd_bwd(H, X, ids, None, None, adv, None, 0, 0.2, accumulate_dW=True, dW=X)
+        assert all(torch.equal(a, b) for a, b in zip(got, (stats, logp, dH, dW)))   # the same sums
+
+
 @pytest.mark.parametrize("rows,V,dead", [(1100, 512, (64, 192)), (1100, 512, (0, 64)), (2000, 2000, (128, 384))])
 def test_float32_update_of_vocabulary_that_cannot_be_taken(rows, V, dead):
     """Weights of -infinity on whole parts of the vocabulary: no probability, and nothing for the entropy, as the scoring call has it."""
