@@ -711,10 +711,16 @@ constexpr int kSelBlock = kTokBlock * kSelMul;
 constexpr int kSelPerThread = kSelBlock / kTokThreads;
 constexpr int kSelWords = kSelPerThread / 4;
 
+// Place of compacted entry i in LDS: eight bytes are left out after every 32 entries.  Where most tokens are scored, neighbouring threads
+// write 32 entries apart, which would be four banks of the 64 for a whole wavefront (42 million tokens, all scored: 54 us, spread like
+// this 37 to 44; 25 million of which 80 % are scored 25.5 and 23).
+__host__ __device__ constexpr int sel_slot(int i) { return i + 4 * (i / 32); }
+static_assert(kSelPerThread == 32, "what a thread writes where all its tokens are scored");
+
 __global__ void __launch_bounds__(kTokThreads)
 k_rowsel(SelArgs A) {
   __shared__ int64_t smem[32];
-  __shared__ __attribute__((aligned(8))) uint16_t s_out[kSelBlock + 4];   // the block's scored positions, block-relative, compacted
+  __shared__ __attribute__((aligned(8))) uint16_t s_out[sel_slot(kSelBlock + 4)];   // the block's scored positions, block-relative, compacted
   __shared__ int64_t moff[UMAS_MAX_MODELS + 1];
   __shared__ int32_t s_mro[UMAS_MAX_MODELS + 1];    // scored tokens of the block in front of a stream that starts in it, -1
   const int tid = threadIdx.x;
@@ -758,7 +764,7 @@ k_rowsel(SelArgs A) {
   const int e = o;
 #pragma unroll
   for (int k = 0; k < kSelPerThread; ++k)
-    if ((w4[k >> 2] >> (8 * (k & 3))) & 1u) s_out[pad + o++] = static_cast<uint16_t>(tid * kSelPerThread + k);
+    if ((w4[k >> 2] >> (8 * (k & 3))) & 1u) s_out[sel_slot(pad + o++)] = static_cast<uint16_t>(tid * kSelPerThread + k);
   for (int j = 0; j <= A.n_models; ++j) {
     const int64_t q = moff[j] - p0;
     if (q >= 0 && q < kSelPerThread && moff[j] < A.n_tokens) {
@@ -774,7 +780,7 @@ k_rowsel(SelArgs A) {
   int m0 = 0;                                        // the stream of the block's first token
   while (m0 < A.n_models && moff[m0 + 1] <= blk0) ++m0;
   auto entry = [&](int i) -> int32_t {               // compacted entry i of the block, stream-relative
-    const int64_t p = blk0 + s_out[pad + i];
+    const int64_t p = blk0 + s_out[sel_slot(pad + i)];
     int m = m0;
     while (m < A.n_models && moff[m + 1] <= p) ++m;
     return static_cast<int32_t>(p - moff[m]);
@@ -787,7 +793,7 @@ k_rowsel(SelArgs A) {
   for (int v = tid; v < n_vec; v += kTokThreads) {
     const int i = head + 4 * v;
     if (one_stream) {
-      const uint2 q = *reinterpret_cast<const uint2*>(s_out + pad + i);
+      const uint2 q = *reinterpret_cast<const uint2*>(s_out + sel_slot(pad + i));
       *reinterpret_cast<int4*>(dst + i) = make_int4(rel0 + static_cast<int32_t>(q.x & 0xffffu), rel0 + static_cast<int32_t>(q.x >> 16),
                                                    rel0 + static_cast<int32_t>(q.y & 0xffffu), rel0 + static_cast<int32_t>(q.y >> 16));
     } else {
