@@ -514,28 +514,91 @@ __device__ __forceinline__ uint32_t four_masks(const TokArgs& A, const SegWindow
   return mk4;
 }
 // The six outputs of the four tokens, once every thread has been through four_masks; pl0 < ntok.
+// With PAST what the calls around the update do not read again (source index, turn, role) is stored past the caches, which leaves these to the
+// mask, the flags and the rewards.  Such a store has to cover whole lines, also where a segment ends inside the wavefront's 256 tokens, and
+// perm's in one instruction: two tokens to a lane, first of one half of the wavefront's tokens, then of the other (sixteen of
+// every 32 bytes at a time, past the caches, are slower than plain stores: 25 million tokens 139 and 112 us, whole lines 103; 42 million
+// 180 and 163, and what follows finds its inputs in the cache: KL penalty of 25 million 82 -> 71 us, second pass of the whitening 56 -> 51).
+template <bool PAST>
 __device__ __forceinline__ void store_four(const TokArgs& A, const SegWindow& W, int64_t blk0, int ntok, int pl0, int lo, bool fast, uint32_t mk4,
                                            bool ahead) {
   const int64_t p0 = blk0 + pl0;
+  const int lane = threadIdx.x & (kWave - 1);
+  // a segment's last scored token carries the reward, unless the segment goes on past the block and has another
+  auto last_scored = [&](int s) { return W.loc[s + 1] <= kTokBlock || !ahead ? W.lastv[s] : -1; };
+  auto reward = [&](int k, int lastv, float rho) {
+    return ((mk4 >> (8 * k)) & 1u) && (A.place_mode == UMAS_PLACE_ALL || pl0 + k == lastv) ? rho : 0.f;
+  };
+  auto put_words = [&](uint32_t fg4, const float (&rw)[kTokPerThread]) {
+    *reinterpret_cast<uint32_t*>(A.tok_mask + p0) = mk4;
+    *reinterpret_cast<uint32_t*>(A.tok_flags + p0) = fg4;
+    *reinterpret_cast<float4*>(A.tok_reward + p0) = make_float4(rw[0], rw[1], rw[2], rw[3]);
+  };
+  // the two tokens of a lane in half h of the wavefront's 256: whose lane's four they belong to, and the first one's place in the block
+  auto from = [&](int h) { return h * (kWave / 2) + (lane >> 1); };
+  auto pair = [&](int h) { return pl0 - lane * kTokPerThread + h * 2 * kWave + lane * 2; };
   int s = lo;
+  if (PAST && __ballot(fast) == ~0ull) {            // all lanes are here and have four tokens of one segment
+    const SegMeta M = W.meta[s];
+    const int64_t g0 = M.src + (p0 - W.off[s]);
+    const int lastv = last_scored(s);
+    float rw[kTokPerThread];
+#pragma unroll
+    for (int k = 0; k < kTokPerThread; ++k) rw[k] = reward(k, lastv, M.rho);
+    const uint32_t fg4 = pl0 + kTokPerThread == W.loc[s + 1] ? mk4 | static_cast<uint32_t>(M.end_flags) << 24 : mk4;
+    const int64_t a = __shfl(static_cast<long long>(g0), from(0), kWave) + 2 * (lane & 1);
+    const int64_t b = __shfl(static_cast<long long>(g0), from(1), kWave) + 2 * (lane & 1);
+    store_stream(A.perm + blk0 + pair(0), make_longlong2(a, a + 1));
+    store_stream(A.perm + blk0 + pair(1), make_longlong2(b, b + 1));
+    store_stream(A.tok_turn + p0, make_int4(M.turn, M.turn, M.turn, M.turn));
+    store_stream(A.tok_role + p0, make_int4(M.role, M.role, M.role, M.role));
+    put_words(fg4, rw);
+    asm volatile("");                               // or these stores and the plain ones below would be made one, and plain
+    return;
+  }
+  if (PAST && __ballot(pl0 + kTokPerThread <= ntok) == ~0ull) {   // four tokens, some lanes' of several segments
+    int64_t g[kTokPerThread];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      int t = __shfl(lo, from(h), kWave);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        while (W.loc[t + 1] <= pair(h) + k) ++t;
+        g[h * 2 + k] = W.meta[t].src + (blk0 + pair(h) + k - W.off[t]);
+      }
+    }
+    int32_t turn[kTokPerThread], role[kTokPerThread];
+    float rw[kTokPerThread];
+    uint32_t fg4 = mk4;
+#pragma unroll
+    for (int k = 0; k < kTokPerThread; ++k) {
+      while (W.loc[s + 1] <= pl0 + k) ++s;
+      const SegMeta M = W.meta[s];
+      turn[k] = M.turn;
+      role[k] = M.role;
+      rw[k] = reward(k, last_scored(s), M.rho);
+      if (pl0 + k + 1 == W.loc[s + 1]) fg4 |= static_cast<uint32_t>(M.end_flags) << (8 * k);
+    }
+    store_stream(A.perm + blk0 + pair(0), make_longlong2(g[0], g[1]));
+    store_stream(A.perm + blk0 + pair(1), make_longlong2(g[2], g[3]));
+    store_stream(A.tok_turn + p0, make_int4(turn[0], turn[1], turn[2], turn[3]));
+    store_stream(A.tok_role + p0, make_int4(role[0], role[1], role[2], role[3]));
+    put_words(fg4, rw);
+    asm volatile("");
+    return;
+  }
   if (fast) {                                       // four tokens of one segment: no per-token bookkeeping
     const SegMeta M = W.meta[s];
     const int64_t g0 = M.src + (p0 - W.off[s]);
-    uint32_t fg4 = mk4;
-    if (pl0 + kTokPerThread == W.loc[s + 1]) fg4 |= static_cast<uint32_t>(M.end_flags) << 24;
-    // the segment's last scored token carries the reward, unless the segment goes on past the block and has another
-    const int lastv = W.loc[s + 1] <= kTokBlock || !ahead ? W.lastv[s] : -1;
+    const int lastv = last_scored(s);
     float rw[kTokPerThread];
 #pragma unroll
-    for (int k = 0; k < kTokPerThread; ++k)
-      rw[k] = ((mk4 >> (8 * k)) & 1u) && (A.place_mode == UMAS_PLACE_ALL || pl0 + k == lastv) ? M.rho : 0.f;
+    for (int k = 0; k < kTokPerThread; ++k) rw[k] = reward(k, lastv, M.rho);
     *reinterpret_cast<longlong2*>(A.perm + p0) = make_longlong2(g0, g0 + 1);
     *reinterpret_cast<longlong2*>(A.perm + p0 + 2) = make_longlong2(g0 + 2, g0 + 3);
     *reinterpret_cast<int4*>(A.tok_turn + p0) = make_int4(M.turn, M.turn, M.turn, M.turn);
     *reinterpret_cast<int4*>(A.tok_role + p0) = make_int4(M.role, M.role, M.role, M.role);
-    *reinterpret_cast<uint32_t*>(A.tok_mask + p0) = mk4;
-    *reinterpret_cast<uint32_t*>(A.tok_flags + p0) = fg4;
-    *reinterpret_cast<float4*>(A.tok_reward + p0) = make_float4(rw[0], rw[1], rw[2], rw[3]);
+    put_words(pl0 + kTokPerThread == W.loc[s + 1] ? mk4 | static_cast<uint32_t>(M.end_flags) << 24 : mk4, rw);
     return;
   }
   for (int k = 0; k < kTokPerThread; ++k) {
@@ -544,13 +607,12 @@ __device__ __forceinline__ void store_four(const TokArgs& A, const SegWindow& W,
     while (W.loc[s + 1] <= pl) ++s;
     const SegMeta M = W.meta[s];
     const uint32_t m = (mk4 >> (8 * k)) & 1u;
-    const bool seg_done = W.loc[s + 1] <= kTokBlock || !ahead;
     A.perm[p0 + k] = M.src + (p0 + k - W.off[s]);
     A.tok_turn[p0 + k] = M.turn;
     A.tok_role[p0 + k] = M.role;
     A.tok_mask[p0 + k] = static_cast<uint8_t>(m);
     A.tok_flags[p0 + k] = static_cast<uint8_t>(m | (pl + 1 == W.loc[s + 1] ? M.end_flags : 0));
-    A.tok_reward[p0 + k] = m && (A.place_mode == UMAS_PLACE_ALL || (seg_done && pl == W.lastv[s])) ? M.rho : 0.f;
+    A.tok_reward[p0 + k] = reward(k, last_scored(s), M.rho);
   }
 }
 
@@ -593,6 +655,7 @@ __device__ __forceinline__ void many_segments_outputs(const TokArgs& A, int64_t 
   }
 }
 
+template <bool PAST>
 __global__ void __launch_bounds__(kTokThreads)
 k_tokens(TokArgs A) {
   __shared__ int64_t smem[32];
@@ -684,7 +747,7 @@ k_tokens(TokArgs A) {
 #pragma unroll
     for (int rd = 0; rd < kTokRounds; ++rd) {
       const int pl0 = rd * kTokRound + tid * kTokPerThread;
-      if (pl0 < ntok) store_four(A, win, blk0, ntok, pl0, lo_r[rd] & ((1 << 30) - 1), (lo_r[rd] >> 30) != 0, mk_r[rd], ahead);
+      if (pl0 < ntok) store_four<PAST>(A, win, blk0, ntok, pl0, lo_r[rd] & ((1 << 30) - 1), (lo_r[rd] >> 30) != 0, mk_r[rd], ahead);
     }
   } else {
     many_segments_outputs(A, blk0, ntok, s_first, s_last, s_mk, ahead);
@@ -1007,7 +1070,7 @@ k_route_small(SmallArgs A) {
     end += b + t;
   }
   if (pl0 < ntok) {
-    store_four(A.tok, win, blk0, ntok, pl0, lo, fast, mk4, s_ahead != 0);
+    store_four<false>(A.tok, win, blk0, ntok, pl0, lo, fast, mk4, s_ahead != 0);
     // the scored positions, stream-relative, and where the streams that start here begin among them
 #pragma unroll
     for (int k = 0; k < kTokPerThread; ++k) {
@@ -1271,7 +1334,8 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
   else hipLaunchKernelGGL(k_turn_plan<UMAS_MAX_MODELS>, plan_grid, dim3(kPlanThreads), 0, st, P);
   UMAS_LAUNCHED("k_turn_plan");
   if (U > 0 && N > 0) {
-    hipLaunchKernelGGL(k_tokens, dim3(static_cast<unsigned>(nbk)), dim3(kTokThreads), 0, st, T);
+    if (N >= kPastTokens) hipLaunchKernelGGL(k_tokens<true>, dim3(static_cast<unsigned>(nbk)), dim3(kTokThreads), 0, st, T);
+    else hipLaunchKernelGGL(k_tokens<false>, dim3(static_cast<unsigned>(nbk)), dim3(kTokThreads), 0, st, T);
     UMAS_LAUNCHED("k_tokens");
     SelArgs S;
     S.n_tokens = N; S.n_models = K; S.grp_shift = gsh;

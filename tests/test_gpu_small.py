@@ -90,6 +90,19 @@ def test_scan_of_few_tokens_in_long_segments(n_tokens, n_turns, n_traj, seg_mode
     check_front_arraywise(w, s, adv, ret, wl.PLACE_ALL, seg_mode, gamma, lam, gamma_turn)
 
 
+# from 8 388 608 tokens on routing and scan store past the caches: the last block whole, with a wavefront of part of its tokens, with a thread of part of
+# its four; turns of a few tokens (blocks of more segments than are held), of some hundred (several in a wavefront's 256 tokens) and long
+@pytest.mark.parametrize("n_tokens", [(1 << 23) - 1, 1 << 23, (1 << 23) + 1023, (1 << 23) + 2050])
+@pytest.mark.parametrize("n_turns,n_models,seg_mode,gamma_turn,values", [
+    (300, 1, wl.SEG_TRAJ, 0.9, True), (40001, 3, wl.SEG_TURN, 1.0, False), (400001, 2, wl.SEG_TRAJ, 0.9, True)])
+def test_front_end_on_both_sides_of_the_cache(n_tokens, n_turns, n_models, seg_mode, gamma_turn, values):
+    w = sized_graph(n_tokens, n_tokens, n_turns, max(n_turns // 3, 1), n_models, n_models + 1, 0)
+    if not values:
+        w.value = None
+    s, adv, ret = P.gpu_front(w, place_mode=wl.PLACE_LAST, seg_mode=seg_mode, gamma=0.99, lam=0.95, gamma_turn=gamma_turn)
+    check_front_arraywise(w, s, adv, ret, wl.PLACE_LAST, seg_mode, 0.99, 0.95, gamma_turn)
+
+
 @pytest.mark.parametrize("n_tokens,n_turns,seg_mode,gamma_turn", [(20000, 1, wl.SEG_TURN, 1.0), (49152, 2, wl.SEG_TRAJ, 0.9), (49153, 2, wl.SEG_TRAJ, 0.9), (65536, 2, wl.SEG_TRAJ, 1.0),
                                                                   (5000, 40, wl.SEG_TURN, 1.0), (100000, 3, wl.SEG_TRAJ, 0.9)])
 @pytest.mark.parametrize("over", ["adv over the rewards, ret over the values", "ret over the rewards", "adv over the values"])
