@@ -16,7 +16,7 @@
 //
 // One pass over memory (17 bytes per token).  Segments are independent, so the stream is cut into ranges of about
 // `chunk` tokens (chunk_tokens) at segment boundaries; a workgroup walks the tiles of one range from right to left and carries the
-// state from tile to tile itself, the loads of the next tile in flight.  Ranges of ordinary segments need nothing
+// state from tile to tile itself, the loads of the next two tiles in flight.  Ranges of ordinary segments need nothing
 // from each other: one workgroup per range, in any order (k_gae_scan).
 // Only a segment longer than kLongSegment tokens is cut inside.  A range whose right end lies inside such a segment
 // is left to a second kernel (k_gae_scan_cut): it first folds all of its tiles into one map and publishes it (a
@@ -55,7 +55,6 @@ constexpr int64_t kLongSegment = 16 * kTile;     // a segment end farther away t
 // other, 6.5 in one; 11 and 5.7 us of the host).  With one segment of all tokens, the longest way to read: 49 152 and 65 536 tokens 28.8
 // and 29.9 us in two, 21.5 and 25.1 in one, with values 38.6 and 40.3, 31.5 and 40.3; with step discounts too 42.6 and 44.5, 40.8 and 52.5.
 inline int64_t alone_tokens(bool decay) { return (decay ? 48 : 64) * kTile; }
-constexpr int kAhead = 1;                        // tiles whose loads are in flight beyond the one in work
 
 enum : uint8_t { kFlagMask = 1, kFlagTurnEnd = 2, kFlagRunEnd = 4 };
 constexpr int kFlagStepShift = 3, kFlagStepMany = 31;   // bits 3-7 of a turn end inside a run: steps to the next turn
@@ -83,15 +82,47 @@ __device__ __forceinline__ Aff then(const Aff& first, const Aff& second) {
   }
   return r;
 }
+// Inclusive prefix over the wavefront, lane 0's map acting first: moves between lanes that go with the multiplication that uses them (row_shr 1,
+// 2, 4, 8 inside the rows of 16 lanes, then the last lane of a row handed to the next row and lane 31 to the upper half); lanes
+// without a source are not written.  The composition of "first" (moved) and "second" (own) in place, eight instructions a step against
+// the twenty and five trips through LDS of shuffles.  A move reads a register two instructions after it was written at the earliest.
+#define UMAS_SCAN_STEP(ctrl)                                                                                                        \
+  if constexpr (HV) {                                                                                                               \
+    float t;                                                                                                                        \
+    asm("s_nop 1\n\tv_mov_b32 %5, %1\n\tv_fmac_f32_dpp %2, %2, %0 " ctrl "\n\tv_fmac_f32_dpp %2, %4, %1 " ctrl                      \
+        "\n\tv_mul_f32_dpp %1, %3, %1 " ctrl "\n\tv_fmac_f32_dpp %1, %5, %0 " ctrl "\n\tv_fmac_f32_dpp %4, %4, %3 " ctrl               \
+        "\n\tv_mul_f32_dpp %0, %0, %0 " ctrl "\n\tv_mul_f32_dpp %3, %3, %3 " ctrl                                                   \
+        : "+v"(m.a), "+v"(m.b), "+v"(m.c), "+v"(m.e), "+v"(m.f), "=&v"(t));                                                         \
+  } else {                                                                                                                          \
+    asm("s_nop 1\n\tv_fmac_f32_dpp %1, %1, %0 " ctrl "\n\tv_mul_f32_dpp %0, %0, %0 " ctrl : "+v"(m.a), "+v"(m.c));                  \
+  }
 template <bool HV>
-__device__ __forceinline__ Aff aff_shfl_down(const Aff& m, int o) {
-  if constexpr (HV)
-    return Aff{__shfl_down(m.a, o, kWave), __shfl_down(m.b, o, kWave), __shfl_down(m.c, o, kWave),
-               __shfl_down(m.e, o, kWave), __shfl_down(m.f, o, kWave)};
-  else
-    return Aff{__shfl_down(m.a, o, kWave), 0.f, __shfl_down(m.c, o, kWave), 0.f, 0.f};
+__device__ __forceinline__ void wave_prefix(Aff& m) {   // every lane of the wavefront takes part
+  UMAS_SCAN_STEP("row_shr:1 row_mask:0xf bank_mask:0xf")
+  UMAS_SCAN_STEP("row_shr:2 row_mask:0xf bank_mask:0xf")
+  UMAS_SCAN_STEP("row_shr:4 row_mask:0xf bank_mask:0xf")
+  UMAS_SCAN_STEP("row_shr:8 row_mask:0xf bank_mask:0xf")
+  UMAS_SCAN_STEP("row_bcast:15 row_mask:0xa bank_mask:0xf")
+  UMAS_SCAN_STEP("row_bcast:31 row_mask:0xc bank_mask:0xf")
+  asm("s_nop 1" : "+v"(m.a), "+v"(m.b), "+v"(m.c), "+v"(m.e), "+v"(m.f));
 }
-
+#undef UMAS_SCAN_STEP
+// the map of the lane below, identity in lane 0
+template <bool HV>
+__device__ __forceinline__ Aff lane_below(const Aff& m) {
+  auto move = [](float old, float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(x), 0x138, 0xF, 0xF, false));   // wave_shr:1
+  };
+  Aff r = aff_identity();
+  r.a = move(1.f, m.a);
+  r.c = move(0.f, m.c);
+  if constexpr (HV) {
+    r.b = move(0.f, m.b);
+    r.e = move(1.f, m.e);
+    r.f = move(0.f, m.f);
+  }
+  return r;
+}
 // One range of the stream.  Ranges are numbered from the right end of the stream.
 struct __attribute__((aligned(16))) Range {
   int64_t start, end;          // tokens [start, end); empty when start == end
@@ -119,6 +150,7 @@ struct ScanParams {
   const int32_t* turn_step;    // only read when the step discount is on
   uint8_t seg_bit;             // kFlagTurnEnd or kFlagRunEnd: which flag ends a segment
   float gamma, lam, gamma_turn;
+  float gl, gl4, gl3g;         // gamma lam as a float, its fourth power, its third times gamma (each rounded once)
 };
 
 // A record is published word by word; every word carries its own ready mark, so no ordering between the words
@@ -187,32 +219,6 @@ __device__ __forceinline__ int64_t range_edge(const ScanParams& P, int64_t x, in
   return x;
 }
 // ------------------------------------------------------------------ the scan
-// For every thread, the composition of the folds of all threads to its right inside the block (exclusive, in
-// application order right to left); *block_total gets the composition of all folds.  s_w holds one map per
-// wavefront; the caller alternates between two such arrays so that one barrier per tile is enough.
-template <bool HV>
-__device__ __forceinline__ Aff block_suffix_excl(Aff mine, Aff* s_w, Aff* block_total) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = threadIdx.x / kWave;
-  constexpr int nwave = kThreads / kWave;
-  Aff incl = mine;   // inclusive suffix inside the wavefront: fold(63) then ... then fold(lane)
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const Aff right = aff_shfl_down<HV>(incl, o);
-    if (lane + o < kWave) incl = then<HV>(right, incl);
-  }
-  Aff excl = aff_shfl_down<HV>(incl, 1);
-  if (lane == kWave - 1) excl = aff_identity();
-  if (lane == 0) s_w[wave] = incl;
-  __syncthreads();
-  Aff right_waves = aff_identity();
-  for (int w = nwave - 1; w > wave; --w) right_waves = then<HV>(right_waves, s_w[w]);
-  Aff total = right_waves;
-  for (int w = wave; w >= 0; --w) total = then<HV>(total, s_w[w]);
-  *block_total = total;
-  return then<HV>(right_waves, excl);
-}
-
 // The state that enters range q from the right, found by one wavefront: lane l looks at range q - 1 - l (ranges are
 // numbered from the right), and the maps are composed up to the nearest range whose map is a constant, i.e. which
 // holds the segment's end.  Only the records up to that range are waited for.
@@ -265,7 +271,7 @@ struct Raw {
   float4 r4, v4;
   uint32_t w;
 };
-template <bool HV>
+template <bool HV, bool PAST = false>
 __device__ __forceinline__ void load_four(const ScanParams& P, const Range& R, int64_t p, Raw& x) {
   x.r4 = make_float4(0.f, 0.f, 0.f, 0.f);
   x.v4 = x.r4;
@@ -273,7 +279,7 @@ __device__ __forceinline__ void load_four(const ScanParams& P, const Range& R, i
   if (p + kIpt <= R.start || p >= R.end) return;    // none of these tokens belongs to the range: a neighbour reads them
   if (p + kIpt <= P.n_tokens) {
     x.r4 = *reinterpret_cast<const float4*>(P.reward + p);
-    if constexpr (HV) x.v4 = *reinterpret_cast<const float4*>(P.value + p);
+    if constexpr (HV) x.v4 = PAST ? load_stream<float4>(P.value + p) : *reinterpret_cast<const float4*>(P.value + p);
     x.w = *reinterpret_cast<const uint32_t*>(P.flags + p);
   } else {
     float* rp = &x.r4.x;
@@ -287,12 +293,11 @@ __device__ __forceinline__ void load_four(const ScanParams& P, const Range& R, i
   }
 }
 
-// Four consecutive tokens from p0 on as the walks use them.
+// Four consecutive tokens as the walks use them.
 struct Four {
   float r[kIpt], v[kIpt];
-  uint32_t fl[kIpt];
+  uint32_t w;                                       // the flags, 0 for tokens that belong to a neighbour: they change nothing
   float kap[kIpt];                                  // step discount applied before the token (1 = none)
-  bool mine[kIpt];                                  // tokens outside the range belong to a neighbour
 };
 // Discounts of 0 .. 30 steps: a power takes a hundred instructions, and where turns are short every wavefront has some in every tile (24 million
 // tokens in turns of 300 104 -> 101 us).
@@ -302,104 +307,206 @@ __device__ __forceinline__ void fill_kaps(const ScanParams& P, float* s_kap) {  
   if constexpr (DECAY)
     if (threadIdx.x < kKaps) s_kap[threadIdx.x] = powf(P.gamma_turn, static_cast<float>(threadIdx.x));
 }
+// 0xFF in the bytes of those of the four tokens from p0 on that lie in the range
+__device__ __forceinline__ uint32_t own_bytes(const Range& R, int64_t p0) {
+  const int64_t skip = R.start - p0, left = R.end - p0;
+  const uint32_t from = skip <= 0 ? ~0u : skip >= kIpt ? 0u : ~0u << (8 * static_cast<int>(skip));
+  return left >= kIpt ? from : left <= 0 ? 0u : from & ~(~0u << (8 * static_cast<int>(left)));
+}
+__device__ __forceinline__ bool has(uint32_t w, int k, uint32_t flag) { return (w >> (8 * k)) & flag; }
+constexpr uint32_t kPlainFour = kFlagMask * 0x01010101u;   // four scored tokens, none of which ends anything
 template <bool DECAY>
-__device__ __forceinline__ Four four_tokens(const ScanParams& P, const Range& R, int64_t p0, const Raw& x, const float* s_kap) {
-  Four T{{x.r4.x, x.r4.y, x.r4.z, x.r4.w}, {x.v4.x, x.v4.y, x.v4.z, x.v4.w}, {}, {}, {}};
+__device__ __forceinline__ Four four_tokens(const ScanParams& P, int64_t p0, const Raw& x, uint32_t w, const float* s_kap) {
+  Four T{{x.r4.x, x.r4.y, x.r4.z, x.r4.w}, {x.v4.x, x.v4.y, x.v4.z, x.v4.w}, w, {1.f, 1.f, 1.f, 1.f}};
+  if constexpr (DECAY) {
+    if (w & (kFlagTurnEnd * 0x01010101u)) {
+      uint32_t many = 0u;
 #pragma unroll
-  for (int k = 0; k < kIpt; ++k) {
-    T.fl[k] = (x.w >> (8 * k)) & 0xFFu;
-    T.mine[k] = p0 + k >= R.start && p0 + k < R.end;
-    T.kap[k] = 1.f;
-    if constexpr (DECAY) {
-      if (T.mine[k] && (T.fl[k] & kFlagTurnEnd) && !(T.fl[k] & P.seg_bit)) {   // a later turn of the same run follows: p + 1 exists
-        const int ds = static_cast<int>(T.fl[k] >> kFlagStepShift);   // steps to the run's next turn; kFlagStepMany: more than fit
-        if (ds < kFlagStepMany) {
-          T.kap[k] = s_kap[ds];
-        } else {
-          const int64_t p = p0 + k;
-          T.kap[k] = powf(P.gamma_turn, static_cast<float>(P.turn_step[P.tok_turn[p + 1]] - P.turn_step[P.tok_turn[p]]));
+      for (int k = 0; k < kIpt; ++k) {
+        if (has(w, k, kFlagTurnEnd) && !has(w, k, P.seg_bit)) {   // a later turn of the same run follows: p + 1 exists
+          const uint32_t ds = (w >> (8 * k + kFlagStepShift)) & kFlagStepMany;   // steps to the run's next turn; kFlagStepMany: more than fit
+          if (ds < kFlagStepMany) T.kap[k] = s_kap[ds];
+          else many |= 1u << k;
         }
+      }
+      while (many) {                                  // rare, and a hundred instructions each
+        const int k = __ffs(static_cast<int>(many)) - 1;
+        const int64_t p = p0 + k;
+        const float kap = powf(P.gamma_turn, static_cast<float>(P.turn_step[P.tok_turn[p + 1]] - P.turn_step[P.tok_turn[p]]));
+#pragma unroll
+        for (int j = 0; j < kIpt; ++j) T.kap[j] = j == k ? kap : T.kap[j];
+        many &= many - 1;
       }
     }
   }
   return T;
 }
+// What a run of plain tokens does not need to look at is the whole of its wavefront's: `plain` is the same in every lane.
 // fold of the four tokens, right to left
 template <bool HV, bool DECAY>
-__device__ __forceinline__ Aff fold_four(const ScanParams& P, const Four& T) {
-  Aff acc = aff_identity();
+__device__ __forceinline__ Aff fold_four(const ScanParams& P, const Four& T, bool plain) {
+  const float gl = P.gl;
+  Aff m = aff_identity();
+  if (plain) {
+    float c = T.r[kIpt - 1] - T.v[kIpt - 1];
+#pragma unroll
+    for (int k = kIpt - 2; k >= 0; --k) c = fmaf(gl, c, HV ? fmaf(P.gamma, T.v[k + 1], T.r[k] - T.v[k]) : T.r[k]);
+    m.a = P.gl4;
+    m.b = HV ? P.gl3g : 0.f;
+    m.c = c;
+    m.e = 0.f;
+    m.f = T.v[0];
+    return m;
+  }
 #pragma unroll
   for (int k = kIpt - 1; k >= 0; --k) {
-    if (!T.mine[k]) continue;
-    if (T.fl[k] & P.seg_bit) acc = Aff{0.f, 0.f, 0.f, 0.f, 0.f};
-    else if constexpr (DECAY) { acc.a *= T.kap[k]; acc.b *= T.kap[k]; acc.c *= T.kap[k]; acc.e *= T.kap[k]; acc.f *= T.kap[k]; }
-    if (T.fl[k] & kFlagMask) {
-      const Aff t{P.gamma * P.lam, P.gamma, T.r[k] - T.v[k], 0.f, T.v[k]};
-      acc = then<HV>(acc, t);
+    const bool end = has(T.w, k, P.seg_bit), scored = has(T.w, k, kFlagMask);
+    if constexpr (DECAY) { m.a *= T.kap[k]; m.b *= T.kap[k]; m.c *= T.kap[k]; m.e *= T.kap[k]; m.f *= T.kap[k]; }
+    m.a = end ? 0.f : m.a;
+    m.c = end ? 0.f : m.c;
+    if constexpr (HV) {
+      m.b = end ? 0.f : m.b;
+      m.e = end ? 0.f : m.e;
+      m.f = end ? 0.f : m.f;
+    }
+    const float d = HV ? T.r[k] - T.v[k] : T.r[k];
+    m.c = scored ? fmaf(gl, m.c, HV ? fmaf(P.gamma, m.f, d) : d) : m.c;
+    m.a = scored ? gl * m.a : m.a;
+    if constexpr (HV) {
+      m.b = scored ? fmaf(gl, m.b, P.gamma * m.e) : m.b;
+      m.e = scored ? 0.f : m.e;
+      m.f = scored ? T.v[k] : m.f;
     }
   }
-  return acc;
+  return m;
 }
 
-// One walk over the tiles of a range, right to left.  REPLAY = false: fold only, returns the range's map in *total.
-// REPLAY = true: starts from the state (*G_io, *NV_io), writes advantages and returns, leaves the state at the
-// range's left edge in (*G_io, *NV_io) (valid in thread 0).
-template <bool HV, bool DECAY, bool REPLAY>
+// One walk over the tiles of a range, right to left, thread 0 at a tile's right end.  REPLAY = false: fold only, returns the range's map in
+// *total.  REPLAY = true: starts from the state (*G_io, *NV_io), writes advantages and returns, leaves the state at the
+// range's left edge in (*G_io, *NV_io) (valid in the last thread).
+// Bound by memory: 25 million tokens without values 66 -> 51 us (6.4 TB/s), of them with values and step discounts 97 -> 75; 42 million in runs of
+// 10 240 with both 180 -> 172 behind the routing call, which leaves 250 MB of stores behind in the cache, on its own 170 -> 124
+// (5.8 TB/s).  Before, every token's flags, place in the range and map were looked at by branches, the maps moved by shuffles, and
+// a tile waited for the stores of the one before it; what a wavefront executes for its 256 tokens took longer than their 17 bytes.
+// With PAST the values are read and both outputs stored past the caches (kPastTokens), which hold the rewards and flags that routing has left.
+template <bool HV, bool DECAY, bool REPLAY, bool PAST>
 __device__ __forceinline__ void walk_range(const ScanParams& P, const Range& R, float* __restrict__ adv, float* __restrict__ ret,
                                            Aff (*s_w)[kThreads / kWave], float (*s_carry)[2], const float* s_kap, float* G_io, float* NV_io, Aff* total) {
-  const int tid = threadIdx.x;
-  const float gl = P.gamma * P.lam;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  constexpr int nwave = kThreads / kWave;
+  const float gl = P.gl;
   const int64_t t_hi = (R.end - 1) / kTile, t_lo = R.start / kTile;
-  Raw buf[kAhead + 1];
-#pragma unroll
-  for (int a = 0; a <= kAhead; ++a)
-    if (t_hi - a >= t_lo) load_four<HV>(P, R, (t_hi - a) * kTile + tid * kIpt, buf[a]);
+  const int at = (kThreads - 1 - tid) * kIpt;
   Aff range_map = aff_identity();
   if (REPLAY && tid == 0) { s_carry[0][0] = *G_io; s_carry[0][1] = *NV_io; }
   int par = 0;
   float G = 0.f, NV = 0.f;
-  for (int64_t tile = t_hi; tile >= t_lo; --tile) {
-    const Raw x = buf[0];
-#pragma unroll
-    for (int a = 0; a < kAhead; ++a) buf[a] = buf[a + 1];
-    if (tile - kAhead - 1 >= t_lo) load_four<HV>(P, R, (tile - kAhead - 1) * kTile + tid * kIpt, buf[kAhead]);
-    const int64_t p0 = tile * kTile + static_cast<int64_t>(tid) * kIpt;
-    const Four T = four_tokens<DECAY>(P, R, p0, x, s_kap);
-    const Aff acc = fold_four<HV, DECAY>(P, T);
-    Aff tile_map;
-    const Aff from_right = block_suffix_excl<HV>(acc, s_w[par], &tile_map);   // the one barrier of a tile
+  // A tile in front of the range's last; one past its first is not read.  Always the same number of loads: what is waited for is known.
+  auto fetch = [&](int64_t tile, Raw& x) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const int64_t t = tile < t_lo ? t_lo : tile;
+    const int n = tile < t_lo ? 0 : kTile;            // tokens that can be read
+    auto rsrc = [&](const void* p, int bytes) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000); };
+    constexpr int kPolicy = REPLAY && PAST ? 2 : 0;   // 2: past the caches
+    x.r4 = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc(P.reward + t * kTile, n * 4), at * 4, 0, 0));
+    x.v4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    if constexpr (HV) x.v4 = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrc(P.value + t * kTile, n * 4), at * 4, 0, kPolicy));
+    x.w = __builtin_amdgcn_raw_buffer_load_b32(rsrc(P.flags + t * kTile, n), at, 0, 0);
+  };
+  auto step = [&](int64_t tile, const Raw& x, auto whole) {   // whole: all of the tile's tokens belong to the range
+    constexpr bool kWhole = decltype(whole)::value;
+    const int64_t p0 = tile * kTile + at;
+    const uint32_t own = kWhole ? ~0u : own_bytes(R, p0), w = x.w & own;
+    const bool plain = __all(w == kPlainFour);
+    const Four T = four_tokens<DECAY>(P, p0, x, w, s_kap);
+    Aff m = fold_four<HV, DECAY>(P, T, plain);
+    wave_prefix<HV>(m);
+    if (lane == kWave - 1) s_w[par][wave] = m;
+    m = lane_below<HV>(m);
+    __syncthreads();                                  // the one barrier of a tile
     if constexpr (!REPLAY) {
-      range_map = then<HV>(range_map, tile_map);    // tiles further right act first
-    } else {
-      G = from_right.a * s_carry[par][0] + from_right.b * s_carry[par][1] + from_right.c;
-      NV = 0.f;
-      if constexpr (HV) NV = from_right.e * s_carry[par][1] + from_right.f;
-      float a[kIpt], b[kIpt];
 #pragma unroll
-      for (int k = kIpt - 1; k >= 0; --k) {
-        a[k] = 0.f;
-        b[k] = 0.f;
-        if (!T.mine[k]) continue;
-        if (T.fl[k] & P.seg_bit) { G = 0.f; NV = 0.f; }
-        else if constexpr (DECAY) { G *= T.kap[k]; NV *= T.kap[k]; }
-        if (T.fl[k] & kFlagMask) {
-          G = (T.r[k] - T.v[k]) + P.gamma * NV + gl * G;
+      for (int q = 0; q < nwave; ++q) range_map = then<HV>(range_map, s_w[par][q]);   // what lies further right acts first
+    } else {
+      Aff right = aff_identity();                   // the tile's own tokens first and the state last: one rounding at its size
+#pragma unroll
+      for (int q = 0; q < nwave - 1; ++q)
+        if (q < wave) right = then<HV>(right, s_w[par][q]);
+      m = then<HV>(right, m);
+      const float g_in = s_carry[par][0], nv_in = HV ? s_carry[par][1] : 0.f;
+      G = HV ? fmaf(m.a, g_in, fmaf(m.b, nv_in, m.c)) : fmaf(m.a, g_in, m.c);
+      NV = HV ? fmaf(m.e, nv_in, m.f) : 0.f;
+      float a[kIpt], b[kIpt];
+      if (plain) {
+#pragma unroll
+        for (int k = kIpt - 1; k >= 0; --k) {
+          G = fmaf(gl, G, HV ? fmaf(P.gamma, NV, T.r[k] - T.v[k]) : T.r[k]);
           NV = T.v[k];
           a[k] = G;
-          b[k] = G + T.v[k];
+          b[k] = HV ? G + NV : G;
+        }
+      } else {
+#pragma unroll
+        for (int k = kIpt - 1; k >= 0; --k) {
+          const bool end = has(w, k, P.seg_bit), scored = has(w, k, kFlagMask);
+          if constexpr (DECAY) { G *= T.kap[k]; NV *= T.kap[k]; }
+          G = end ? 0.f : G;
+          if constexpr (HV) NV = end ? 0.f : NV;
+          const float g = fmaf(gl, G, HV ? fmaf(P.gamma, NV, T.r[k] - T.v[k]) : T.r[k]);
+          G = scored ? g : G;
+          if constexpr (HV) NV = scored ? T.v[k] : NV;
+          a[k] = scored ? g : 0.f;
+          b[k] = scored ? (HV ? g + T.v[k] : g) : 0.f;
         }
       }
-      if (tid == 0) { s_carry[par ^ 1][0] = G; s_carry[par ^ 1][1] = NV; }   // state at the tile's left edge
-      if (T.mine[0] && T.mine[kIpt - 1]) {
-        *reinterpret_cast<float4*>(adv + p0) = make_float4(a[0], a[1], a[2], a[3]);
-        *reinterpret_cast<float4*>(ret + p0) = make_float4(b[0], b[1], b[2], b[3]);
+      if (tid == kThreads - 1) { s_carry[par ^ 1][0] = G; s_carry[par ^ 1][1] = NV; }   // state at the tile's left edge
+      if (kWhole || own == ~0u) {
+        const float4 a4 = make_float4(a[0], a[1], a[2], a[3]), b4 = make_float4(b[0], b[1], b[2], b[3]);
+        if (PAST) {
+          store_stream(adv + p0, a4);
+          store_stream(ret + p0, b4);
+        } else {
+          *reinterpret_cast<float4*>(adv + p0) = a4;
+          *reinterpret_cast<float4*>(ret + p0) = b4;
+        }
       } else {
 #pragma unroll
         for (int k = 0; k < kIpt; ++k)
-          if (T.mine[k]) { adv[p0 + k] = a[k]; ret[p0 + k] = b[k]; }
+          if (has(own, k, 1u)) { adv[p0 + k] = a[k]; ret[p0 + k] = b[k]; }
       }
     }
     par ^= 1;
+  };
+  using Whole = std::true_type;
+  using Part = std::false_type;
+  Raw x, even, odd;
+  load_four<HV, REPLAY && PAST>(P, R, t_hi * kTile + at, x);
+  fetch(t_hi - 1, even);
+  fetch(t_hi - 2, odd);
+  step(t_hi, x, Part());
+  int64_t tile = t_hi - 1;
+  const int64_t t_in = (R.start + kTile - 1) / kTile;   // first whole tile
+  __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0): from here on it is known what is under way in the loop
+  // (moved by instructions of its own, so that the next loads go to the registers that the last ones came to: the compiler would leave the
+  // values there and move the new ones at the end of a turn, for which it waits)
+  auto take = [&](const Raw& from) {
+    auto move = [](float& to, float v) { asm volatile("v_mov_b32 %0, %1" : "=v"(to) : "v"(v) : "memory"); };
+    move(x.r4.x, from.r4.x); move(x.r4.y, from.r4.y); move(x.r4.z, from.r4.z); move(x.r4.w, from.r4.w);
+    if constexpr (HV) { move(x.v4.x, from.v4.x); move(x.v4.y, from.v4.y); move(x.v4.z, from.v4.z); move(x.v4.w, from.v4.w); }
+    asm volatile("v_mov_b32 %0, %1" : "=v"(x.w) : "v"(from.w) : "memory");
+  };
+  for (; tile > t_in; tile -= 2) {
+    take(even);
+    fetch(tile - 2, even);
+    step(tile, x, Whole());
+    take(odd);
+    fetch(tile - 3, odd);
+    step(tile - 1, x, Whole());
+  }
+#pragma unroll 1
+  for (; tile >= t_lo; --tile) {
+    step(tile, even, Part());
+    even = odd;
   }
   if constexpr (REPLAY) { *G_io = G; *NV_io = NV; } else { *total = range_map; }
 }
@@ -410,14 +517,14 @@ __device__ __forceinline__ void walk_range(const ScanParams& P, const Range& R, 
 template <bool HV, bool DECAY>
 __device__ __forceinline__ Aff fold_ahead(const ScanParams& P, const Range& R, Aff* s_w, const float* s_kap) {
   constexpr int nwave = kThreads / kWave, kFours = 4, kLane = kFours * kIpt, kStep = kWave * kLane;
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, at = (kWave - 1 - lane) * kLane;   // lane 0 at the right end
   const int64_t first = R.start / kStep, n = (R.end - 1) / kStep + 1 - first, per = (n + nwave - 1) / nwave;
   const int64_t lo = first + wave * per, hi = lo + per < first + n ? lo + per : first + n;
   Aff map = aff_identity();
   Raw next[kFours];
   auto load = [&](int64_t t) {
 #pragma unroll
-    for (int i = 0; i < kFours; ++i) load_four<HV>(P, R, t * kStep + lane * kLane + i * kIpt, next[i]);
+    for (int i = 0; i < kFours; ++i) load_four<HV>(P, R, t * kStep + at + i * kIpt, next[i]);
   };
   if (hi > lo) load(hi - 1);
   for (int64_t t = hi - 1; t >= lo; --t) {
@@ -427,16 +534,15 @@ __device__ __forceinline__ Aff fold_ahead(const ScanParams& P, const Range& R, A
     if (t > lo) load(t - 1);
     Aff acc = aff_identity();
 #pragma unroll
-    for (int i = kFours - 1; i >= 0; --i)
-      acc = then<HV>(acc, fold_four<HV, DECAY>(P, four_tokens<DECAY>(P, R, t * kStep + lane * kLane + i * kIpt, x[i], s_kap)));
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-      const Aff right = aff_shfl_down<HV>(acc, o);
-      if (lane + o < kWave) acc = then<HV>(right, acc);
+    for (int i = kFours - 1; i >= 0; --i) {
+      const int64_t p0 = t * kStep + at + i * kIpt;
+      const uint32_t w = x[i].w & own_bytes(R, p0);
+      acc = then<HV>(acc, fold_four<HV, DECAY>(P, four_tokens<DECAY>(P, p0, x[i], w, s_kap), __all(w == kPlainFour)));
     }
-    map = then<HV>(map, acc);                       // in lane 0
+    wave_prefix<HV>(acc);
+    map = then<HV>(map, acc);                       // in the last lane
   }
-  if (lane == 0) s_w[wave] = map;
+  if (lane == kWave - 1) s_w[wave] = map;
   __syncthreads();
   Aff total = aff_identity();
   for (int w = nwave - 1; w >= 0; --w) total = then<HV>(total, s_w[w]);
@@ -448,7 +554,7 @@ __device__ __forceinline__ Aff fold_ahead(const ScanParams& P, const Range& R, A
 // empty or its right end lies inside a long segment, it scans the range: nothing comes in from the right.  What the second kernel needs is
 // left for it: the edges, the range's record cleared or published.  With ALONE there is no second kernel: a workgroup whose range ends inside a
 // segment reads on to the segment's end itself, for its map.
-template <bool HV, bool DECAY, bool ALONE>
+template <bool HV, bool DECAY, bool ALONE, bool PAST>
 __global__ void __launch_bounds__(kThreads)
 k_gae_scan(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
   __shared__ Aff s_w[2][kThreads / kWave];
@@ -493,14 +599,14 @@ k_gae_scan(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
     if (R.start >= R.end || R.cut_right) return;
   }
   Aff unused;
-  walk_range<HV, DECAY, true>(P, R, adv, ret, s_w, s_carry, s_kap, &G, &NV, &unused);
+  walk_range<HV, DECAY, true, PAST>(P, R, adv, ret, s_w, s_carry, s_kap, &G, &NV, &unused);
   // a range that starts inside a long segment: what it hands to the left is a constant
-  if (!ALONE && R.cut_left && tid == 0)
+  if (!ALONE && R.cut_left && tid == kThreads - 1)
     publish<HV>(P.range_state + static_cast<size_t>(q) * kStateWords, Aff{0.f, 0.f, G, 0.f, HV ? NV : 0.f});
 }
 
 // The ranges whose right end lies inside a long segment; persistent workgroups.
-template <bool HV, bool DECAY>
+template <bool HV, bool DECAY, bool PAST>
 __global__ void __launch_bounds__(kThreads)
 k_gae_scan_cut(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
   __shared__ Aff s_w[2][kThreads / kWave];
@@ -521,7 +627,7 @@ k_gae_scan_cut(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
     // hand over, then the replay
     float G = 0.f, NV = 0.f;
     Aff range_map;
-    walk_range<HV, DECAY, false>(P, R, adv, ret, s_w, s_carry, s_kap, &G, &NV, &range_map);
+    walk_range<HV, DECAY, false, PAST>(P, R, adv, ret, s_w, s_carry, s_kap, &G, &NV, &range_map);
     if (R.cut_left && tid == 0) publish<HV>(P.range_state + static_cast<size_t>(q) * kStateWords, range_map);
     if (tid < kWave) {
       float g_in, nv_in;
@@ -532,7 +638,7 @@ k_gae_scan_cut(ScanParams P, float* __restrict__ adv, float* __restrict__ ret) {
     G = s_in[0];
     NV = s_in[1];
     Aff unused;
-    walk_range<HV, DECAY, true>(P, R, adv, ret, s_w, s_carry, s_kap, &G, &NV, &unused);
+    walk_range<HV, DECAY, true, PAST>(P, R, adv, ret, s_w, s_carry, s_kap, &G, &NV, &unused);
     __syncthreads();
   }
 }
@@ -598,24 +704,33 @@ extern "C" umas_status umas_advantages(const umas_streams* s, int64_t n_tokens, 
   P.gamma = gamma;
   P.lam = lam;
   P.gamma_turn = gamma_turn;
+  P.gl = gamma * lam;
+  const double gl = P.gl;
+  P.gl4 = static_cast<float>(gl * gl * gl * gl);
+  P.gl3g = static_cast<float>(gl * gl * gl * gamma);
   const bool decay = seg_mode == UMAS_SEG_TRAJ && gamma_turn != 1.0f;
   // (alone, workgroups read tokens that are others' to write the outputs of: not where these lie over the inputs)
   auto apart = [&](const float* out, const float* in) { return !in || out + n_tokens <= in || in + n_tokens <= out; };
   const bool alone = n_tokens <= alone_tokens(decay) && apart(adv, s->tok_reward) && apart(adv, value) && apart(ret, s->tok_reward) && apart(ret, value);
-  auto pick = [&](auto al) -> void (*)(ScanParams, float*, float*) {
-    constexpr bool A = decltype(al)::value;
-    return value ? (decay ? k_gae_scan<true, true, A> : k_gae_scan<true, false, A>) : (decay ? k_gae_scan<false, true, A> : k_gae_scan<false, false, A>);
+  const bool past = !alone && n_tokens >= kPastTokens;
+  auto pick = [&](auto al, auto pa) -> void (*)(ScanParams, float*, float*) {
+    constexpr bool A = decltype(al)::value, S = decltype(pa)::value;
+    return value ? (decay ? k_gae_scan<true, true, A, S> : k_gae_scan<true, false, A, S>) : (decay ? k_gae_scan<false, true, A, S> : k_gae_scan<false, false, A, S>);
   };
-  void (*kernel)(ScanParams, float*, float*) = alone ? pick(std::true_type()) : pick(std::false_type());
+  using Yes = std::true_type;
+  using No = std::false_type;
+  void (*kernel)(ScanParams, float*, float*) = alone ? pick(Yes(), No()) : past ? pick(No(), Yes()) : pick(No(), No());
   hipLaunchKernelGGL(kernel, dim3(P.n_ranges), dim3(kThreads), 0, st, P, adv, ret);
   UMAS_LAUNCHED("k_gae_scan");
   if (alone) return UMAS_OK;
   // The ranges cut inside long segments: persistent workgroups that wait for each other's maps.  At most one workgroup
   // per compute unit, far fewer than the device holds at once: whatever else is running, all of them get to run
   // together, so no workgroup waits for one that cannot start.
-  void (*kernel_cut)(ScanParams, float*, float*) =
-      value ? (decay ? k_gae_scan_cut<true, true> : k_gae_scan_cut<true, false>)
-            : (decay ? k_gae_scan_cut<false, true> : k_gae_scan_cut<false, false>);
+  auto pick_cut = [&](auto pa) -> void (*)(ScanParams, float*, float*) {
+    constexpr bool S = decltype(pa)::value;
+    return value ? (decay ? k_gae_scan_cut<true, true, S> : k_gae_scan_cut<true, false, S>) : (decay ? k_gae_scan_cut<false, true, S> : k_gae_scan_cut<false, false, S>);
+  };
+  void (*kernel_cut)(ScanParams, float*, float*) = past ? pick_cut(Yes()) : pick_cut(No());
   int dev = 0, n_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
     n_cu = 64;
