@@ -1099,7 +1099,9 @@ __device__ __forceinline__ KContig blocked_rows_tile(const uint16_t* X, int blk_
 // ms, through LDS 1.3 ms).  Every wavefront turns its 128 x 64 block through its own part of LDS, 32 rows at a time, and
 // stores 256 bytes of four rows.  In a tile that exists as a whole nothing depends on the row: what is there already is
 // under way during the turn, and a piece's LDS reads and stores go out together (waiting for each of 32 pieces by itself:
-// both products of 725 rows of 2048 that add to dW 1155 us, together 1020; 64 rows without adding 459 and 443).
+// both products of 725 rows of 2048 that add to dW 1155 us, together 1020; 64 rows without adding 459 and 443).  What is there is read past the
+// caches, which leaves them to the operands (two updates of which the second adds, 203 rows of 2048 1454 -> 1380 us, 300 1950 -> 1885, 725 rows
+// four times 5.82 -> 5.73 ms).
 constexpr int kTurnBytes = 32 * 64 * 4;                              // 32 rows of 64 floats per wavefront
 static_assert(Cfg::WTN == 64 && Cfg::WM * Cfg::WN == 8 && 8 * kTurnBytes <= 2 * Cfg::BM * 128, "the turn fits two stages of an operand");
 // 32 rows (blocks 2 h and 2 h + 1) of a wavefront's accumulators into its part of LDS, and four columns of four rows (4 i + lane /
@@ -1130,7 +1132,7 @@ __device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[Cfg::MI][Cfg:
   floatx4 have[8];                                                   // what is there already, a piece ahead
   auto fetch = [&](int h) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) have[i] = *reinterpret_cast<const f32x4_a4*>(dst + (h * 32 + i * 4) * ld);
+    for (int i = 0; i < 8; ++i) have[i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_a4*>(dst + (h * 32 + i * 4) * ld));
   };
   if (whole && accumulate) fetch(0);
 #pragma unroll
