@@ -159,23 +159,20 @@ struct KeepArgs {
 };
 
 template <Leave LEAVE, class C>
-__device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
-                                            const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc,
-                                            const int32_t* __restrict__ ids, int tiles_m, int tiles_n, int panel,
-                                            float4* __restrict__ partial, int64_t n_pad, const KeepArgs& keep,
-                                            uint16_t* lds) {
+__device__ __forceinline__ void score_tile(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
+                                           const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc,
+                                           const int32_t* __restrict__ ids, int tile_m, int tile_n, bool w_once,
+                                           float4* __restrict__ partial, int64_t n_pad, const KeepArgs& keep,
+                                           uint16_t* lds) {
   constexpr bool KEEP = LEAVE == Leave::kNumerators;
   static_assert(LEAVE != Leave::kLogits || C::BM * C::BN == Cfg::BM * Cfg::BN, "logits are kept in whole blocks");
   static_assert(256 % C::BM == 0 && 256 % C::BN == 0, "numerators are kept inside a block");
   constexpr int kPitch = Stage<C>::kPitch;
-  for (int it = 0; it < kTilesPerWg; ++it) {     // a workgroup walks the same place of kTilesPerWg consecutive tile groups
-  int tile_m, tile_n;
-  if (!tile_coords<kGM, kGN>(tiles_m, tiles_n, panel, &tile_m, &tile_n, it, kTilesPerWg)) continue;
   const int m0 = tile_m * C::BM;
   const int64_t n0 = static_cast<int64_t>(tile_n) * C::BN;   // chunk-relative
   floatx4 acc[C::MI][C::NI];
   // (a tile that lies past V as a whole, the second half of a block that is kept, reads the last entry)
-  logit_tile<C>(W, H, d, V, rowsel, c0, mc, min(m0, V - 1), n0, tiles_n == 1 && beyond_cache(d, V, kLogitsOnceBytes), lds, acc);
+  logit_tile<C>(W, H, d, V, rowsel, c0, mc, min(m0, V - 1), n0, w_once, lds, acc);
 
   // epilogue: the tile buffers are free now.  A lane holds, for each of its NI columns (selected rows), the
   // vocabulary entries vbase + 16 i + r (i < MI, r < 4); the four lanes l, l + 16, l + 32, l + 48 share a column.
@@ -328,6 +325,34 @@ __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, cons
     if (c0 + n0 + col < n_pad) partial[static_cast<int64_t>(tile_m) * n_pad + c0 + n0 + col] = make_float4(p.m, p.s, p.t, s_zy[col]);
   }
   __syncthreads();                              // the LDS is the next tile's again
+}
+
+// The tiles of a workgroup.  With few column tiles a workgroup has one tile, and the last round of compute units is often nearly empty: the tiles of
+// one that is at most half full are cut into two of 128 rows of the selection.  594 tiles on 256 compute units, 256 rows: 2048 columns 190 -> 173 us, 3584
+// 283 -> 270; 150 rows 188 -> 170 and 271 -> 262; the update of 203 rows of 3584 1037 -> 1022.
+using HalfCfg = TileCfg<256, 128, 2, 4>;                 // the lanes of a row as in a whole tile: the same bits
+template <Leave LEAVE, class C>
+__device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
+                                            const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc,
+                                            const int32_t* __restrict__ ids, int tiles_m, int tiles_n, int panel,
+                                            float4* __restrict__ partial, int64_t n_pad, const KeepArgs& keep,
+                                            uint16_t* lds, int halved = 0) {
+  const bool w_once = tiles_n == 1 && beyond_cache(d, V, kLogitsOnceBytes);
+  if constexpr (C::BM == 256 && C::BN == 256 && LEAVE != Leave::kLogits) {
+    if (halved > 0) {                             // the last `halved` tiles of every XCD
+      const int per_xcd = (tiles_m * tiles_n + 7) / 8, xcd = static_cast<int>(blockIdx.x & 7), w = static_cast<int>(blockIdx.x >> 3), whole = per_xcd - halved;
+      if (w >= whole) {
+        const int in_xcd = whole + (w - whole) / 2, t = xcd * per_xcd + in_xcd, tile_m = t / tiles_n, half = t % tiles_n * 2 + ((w - whole) & 1);
+        if (in_xcd < per_xcd && tile_m < tiles_m && half * HalfCfg::BN < mc)
+          score_tile<LEAVE, HalfCfg>(W, H, d, V, rowsel, c0, mc, ids, tile_m, half, false, partial, n_pad, keep, lds);
+        return;
+      }
+    }
+  }
+  for (int it = 0; it < kTilesPerWg; ++it) {     // a workgroup walks the same place of kTilesPerWg consecutive tile groups
+    int tile_m, tile_n;
+    if (!tile_coords<kGM, kGN>(tiles_m, tiles_n, panel, &tile_m, &tile_n, it, kTilesPerWg)) continue;
+    score_tile<LEAVE, C>(W, H, d, V, rowsel, c0, mc, ids, tile_m, tile_n, w_once, partial, n_pad, keep, lds);
   }
 }
 
@@ -335,9 +360,9 @@ __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, cons
 __global__ void __launch_bounds__(Cfg::T)
 k_score_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
               const int32_t* __restrict__ rowsel, int64_t n_sel, const int32_t* __restrict__ ids,
-              int tiles_m, int tiles_n, int panel, float4* __restrict__ partial, int64_t n_pad) {
+              int tiles_m, int tiles_n, int panel, int halved, float4* __restrict__ partial, int64_t n_pad) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[kLogitLds / 2];
-  score_tiles<Leave::kNothing, Cfg>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{}, lds);
+  score_tiles<Leave::kNothing, Cfg>(W, H, d, V, rowsel, 0, n_sel, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{}, lds, halved);
 }
 // Up to 128 selected rows: half-size tiles with a pipeline of their own, two workgroups to a compute unit, so that one
 // fills its stages while the other multiplies (64 rows of 2048 / 3584 against 151 936: 156 / 215 us against 182 / 274 with
@@ -354,11 +379,11 @@ k_score_narrow(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, i
 __global__ void __launch_bounds__(Cfg::T)
 k_score_keep_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
                    const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc, const int32_t* __restrict__ ids,
-                   int tiles_m, int tiles_n, int panel, float4* __restrict__ partial, int64_t n_pad,
+                   int tiles_m, int tiles_n, int panel, int halved, float4* __restrict__ partial, int64_t n_pad,
                    const float* __restrict__ cref, uint16_t* __restrict__ E, int64_t Vp, int32_t* __restrict__ flags,
                    const int32_t* __restrict__ cidx) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[kLogitLds / 2];
-  score_tiles<Leave::kNumerators, Cfg>(W, H, d, V, rowsel, c0, mc, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{cref, E, Vp, flags, cidx, nullptr}, lds);
+  score_tiles<Leave::kNumerators, Cfg>(W, H, d, V, rowsel, c0, mc, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{cref, E, Vp, flags, cidx, nullptr}, lds, halved);
 }
 // ... and what an update of so few rows keeps: half rows of half blocks of the operand, whose other rows are never read (100 rows of 3584 270 -> 211
 // us; the update, with shorter sums for dW and half the products for dH, 1000 -> 887, of 2048 608 -> 518).
@@ -1777,6 +1802,16 @@ int row_panel(int tiles_n, int d) {
   return ((tiles_n + panels - 1) / panels + kGN - 1) / kGN * kGN;
 }
 
+// Tiles of every XCD that are cut in two (see score_tiles): those of the last round of compute units where it is at most half full.
+int halved_tiles(int tiles_m, int tiles_n) {
+  if (tiles_n > kGN) return 0;
+  const int per_xcd = static_cast<int>(cdiv(static_cast<size_t>(tiles_m) * tiles_n, 8)), cus = std::max(device_cus() / 8, 1), rest = per_xcd % cus;
+  return rest * 2 <= cus ? rest : 0;
+}
+dim3 score_grid(int tiles_m, int tiles_n, int panel, int halved) {
+  return dim3(tile_grid<kGM, kGN>(tiles_m, tiles_n, panel, kTilesPerWg) + 8 * static_cast<unsigned>(halved));
+}
+
 // Forward scoring of the selected rows into compact arrays and/or scattered outputs.  float32: `room` holds statistics of
 // parts of the vocabulary (no room: one workgroup per 32 rows walks all of it), rest_c goes with the compact arrays, z (may be
 // NULL) takes the logits.
@@ -1804,9 +1839,9 @@ umas_status run_score(const void* H, const void* W, umas_dtype dt, int d, int V,
                          tiles_m, 1, kGN, w.partial, n_pad);
       UMAS_LAUNCHED("k_score_narrow");
     } else {
-      hipLaunchKernelGGL(k_score_tiles, dim3(tile_grid<kGM, kGN>(tiles_m, tiles_n, row_panel(tiles_n, d), kTilesPerWg)), dim3(Cfg::T), 0, st,
-                         static_cast<const uint16_t*>(W), static_cast<const uint16_t*>(H), d, V, rowsel, n_sel, ids,
-                         tiles_m, tiles_n, row_panel(tiles_n, d), w.partial, n_pad);
+      const int panel = row_panel(tiles_n, d), halved = halved_tiles(tiles_m, tiles_n);
+      hipLaunchKernelGGL(k_score_tiles, score_grid(tiles_m, tiles_n, panel, halved), dim3(Cfg::T), 0, st, static_cast<const uint16_t*>(W),
+                         static_cast<const uint16_t*>(H), d, V, rowsel, n_sel, ids, tiles_m, tiles_n, panel, halved, w.partial, n_pad);
       UMAS_LAUNCHED("k_score_tiles");
     }
     launch_finalize(n_sel, n_sel, st, w.partial, tiles_m, n_pad, static_cast<int64_t>(0), n_sel, static_cast<const float*>(nullptr), rowsel, ids, V,
@@ -2143,7 +2178,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     for (int64_t c0 = 0; c0 < n_sel; c0 += mc) {
       const int64_t rows = n_sel - c0 < mc ? n_sel - c0 : mc;
       const int64_t mcp = round_up(rows, 256);
-      const int tiles_r = static_cast<int>(mcp / 256);
+      const int tiles_r = static_cast<int>(mcp / 256), panel = row_panel(tiles_r, d), halved = halved_tiles(tiles_v, tiles_r);
       uint16_t* E = reinterpret_cast<uint16_t*>(w.chunk);
       uint16_t* Hs = reinterpret_cast<uint16_t*>(w.chunk + align_up(static_cast<size_t>(mcp) * Vp * 2));
       DhSlices sl;
@@ -2156,9 +2191,8 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
         hipLaunchKernelGGL(k_score_keep_narrow, dim3(tile_grid<kGM, kGN>(tiles_m, 1, kGN, kTilesPerWg)), dim3(NarrowCfg::T), 0, st, Wb, Hb, d, V,
                            rowsel, rows, ids, tiles_m, w.score.partial, n_pad, w.cref, E, Vp, w.flags, w.blk_cidx);
       else
-        hipLaunchKernelGGL(k_score_keep_tiles, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, row_panel(tiles_r, d), kTilesPerWg)), dim3(Cfg::T), 0, st,
-                           Wb, Hb, d, V, rowsel, c0, rows, ids, tiles_v, tiles_r, row_panel(tiles_r, d), w.score.partial, n_pad, w.cref, E, Vp,
-                           w.flags, w.blk_cidx);
+        hipLaunchKernelGGL(k_score_keep_tiles, score_grid(tiles_v, tiles_r, panel, halved), dim3(Cfg::T), 0, st, Wb, Hb, d, V, rowsel, c0, rows, ids,
+                           tiles_v, tiles_r, panel, halved, w.score.partial, n_pad, w.cref, E, Vp, w.flags, w.blk_cidx);
       UMAS_LAUNCHED(narrow ? "k_score_keep_narrow" : "k_score_keep_tiles");
       launch_finalize(rows, n_sel, st, w.score.partial, tiles_m, n_pad, c0, c0 + rows, w.cref, rowsel, ids, V, w.score.logp_c, w.score.lse_c,
                       w.score.ent_c, logp_new, static_cast<float*>(nullptr), static_cast<float*>(nullptr));
