@@ -709,7 +709,7 @@ __device__ void share_dw(int tiles_r, int tiles_v, int tiles_d, int64_t Vp, int 
   const int64_t units = (tiles_dw + unit - 1) / unit;
   k_len *= unit;
   int64_t cnt;
-  if (k_len <= 0) {                                    // nothing to even out
+  if (k_len <= 0 || units == 0) {                      // nothing to even out
     cnt = units / 8 + (x < units % 8 ? 1 : 0);
   } else {
     // the level up to which the XCDs would be filled if units could be cut: those that stand above it as they are take nothing ...
@@ -1145,12 +1145,13 @@ __device__ __forceinline__ void turn_in(const floatx4 (&acc)[Cfg::MI][Cfg::NI], 
 __device__ __forceinline__ floatx4 turn_out(const char* turn, int i, int lane) {
   return *reinterpret_cast<const floatx4*>(turn + (i * 4 + (lane >> 4)) * 256 + (((lane & 15) ^ (4 * (i & 3))) * 16));
 }
-__device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[Cfg::MI][Cfg::NI], uint16_t* lds, float* out, int64_t ld, int64_t rows, int cols,
+// `turn` is the wavefront's own part of LDS
+template <class C>
+__device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[C::MI][C::NI], char* turn, float* out, int64_t ld, int64_t rows, int cols,
                                               int accumulate) {
-  using C = Cfg;
+  static_assert(C::WTM == Cfg::WTM && C::WTN == Cfg::WTN, "the turn is written for these");
   typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // dW has the alignment of a float
   const int tid = tile_thread(), lane = tid & 63, wave = tid >> 6;
-  char* turn = reinterpret_cast<char*>(lds) + wave * kTurnBytes;
   const int r0 = wave / C::WN * C::WTM, c0 = wave % C::WN * C::WTN + (lane & 15) * 4;
   const bool whole = rows >= C::BM && cols >= C::BN;                 // the same for every thread
   float* const dst = out + (r0 + (lane >> 4)) * ld + c0;
@@ -1228,7 +1229,7 @@ __device__ __forceinline__ void dh_tile(int tile_m, int m_rows, int orig_blk, in
   else mfma_mainloop_mixed<C, false, true, 2>(ca, KMajor{}, KContig{}, kb, k_len, lds, acc);
   if (sl.n > 1) {
     float* out = sl.part + ((static_cast<int64_t>(slice) * tiles_r + tile_m) * tiles_d + tile_n) * (C::BM * C::BN);
-    store_acc_f32(acc, lds, out, C::BN, C::BM, C::BN, 0);
+    store_acc_f32<C>(acc, reinterpret_cast<char*>(lds) + (tile_thread() >> 6) * kTurnBytes, out, C::BN, C::BM, C::BN, 0);
     return;
   }
   // dH rows leave like the float32 ones: 32 rows at a time through LDS, 128 bytes of four rows to a store, the row numbers,
@@ -1295,7 +1296,114 @@ __device__ __forceinline__ void dw_tile(int tile_m, int tile_n, const uint16_t* 
   floatx4 acc[C::MI][C::NI];
   zero_acc<C>(acc);
   if (k_len > 0) mfma_mainloop_mixed<C, true, true, 1>(KContig{}, ka, KContig{}, kb, k_len, lds, acc);
-  store_acc_f32(acc, lds, dW + m0 * d + n0, d, V - m0, d - n0, accumulate);   // d is a multiple of 8
+  store_acc_f32<C>(acc, reinterpret_cast<char*>(lds) + (tile_thread() >> 6) * kTurnBytes, dW + m0 * d + n0, d, V - m0, d - n0, accumulate);   // d is a multiple of 8
+}
+
+// dW of at most 256 rows.  A tile of 256 x 256 that a compute unit works on alone is products, then stores, and the next tile's first loads wait for these
+// stores (a wavefront's memory operations are counted in order): 203 rows of 3584 against 152 064 485 us, of which the products alone are 235 and the
+// stores of 2.2 GB 396 (5.5 TB/s, as much as a kernel that only stores such tiles reaches).  Here tiles of 256 x 128 have two workgroups to
+// a compute unit, so that one multiplies while the other stores, and a workgroup of its own each, which ends without waiting for its stores: 400
+// to 430 us.  K is walked in steps of 32 rows through three LDS stages of 24 KB, loaded two steps ahead.  (Stored through the caches: 1075 us for
+// the update in place of 972.)
+using ShortCfg = TileCfg<256, 128, 2, 2>;
+constexpr int kShortA = 32 * 512, kShortStage = kShortA + 32 * 256, kShortLds = 3 * kShortStage;
+static_assert(2 * kShortLds <= 160 * 1024 && 3 * kTurnBytes <= kShortStage, "two workgroups to a compute unit; the turns of three wavefronts fit a stage");
+constexpr int kShortGM = 4, kShortGN = 16;               // tiles that the 64 workgroups of an XCD work on together
+__global__ void __launch_bounds__(ShortCfg::T, 2)
+k_dw_short(const uint16_t* __restrict__ dZ, int blk_pitch, int64_t Vp, int64_t mcp, const uint16_t* __restrict__ Hs, int d, int V, int tiles_v,
+           int tiles_n, const LiveInfo* __restrict__ info, float* __restrict__ dW, int accumulate) {
+  using C = ShortCfg;
+  __shared__ __attribute__((aligned(16))) char lds[kShortLds];
+  const int total = tiles_v * tiles_n, per = (total + 7) / 8, t = static_cast<int>(blockIdx.x & 7) * per + static_cast<int>(blockIdx.x >> 3);
+  if (static_cast<int>(blockIdx.x >> 3) >= per || t >= total) return;
+  int tile_m, tile_n;
+  tile_of_groups<kShortGM, kShortGN>(t, tiles_v, tiles_n, &tile_m, &tile_n);
+  const int k_rows = info->k_rows, nsub = (k_rows + 31) / 32;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / C::WN, wn = wave % C::WN;
+  const char* const a0 = reinterpret_cast<const char*>(dZ + blk_offset(0, tile_m, Vp >> 8) * blk_pitch);
+  const int64_t blk_row = (Vp >> 8) * kBlkElems * 2 * blk_pitch;                                     // from a block of rows to the next
+  const char* const b0 = reinterpret_cast<const char*>(Hs + (static_cast<int64_t>(tile_n >> 1) * mcp) * 256 + (tile_n & 1) * 128);
+  // loads (K-major operands as in mfma_mainloop_mixed): one fills two k-rows of A, four of B
+  const int ka = 2 * wave + (lane >> 5), kb = 4 * wave + (lane >> 4);                                // + 8 p; + 16 p
+  const uint32_t ua = static_cast<uint32_t>((lane & 31) ^ (4 * (ka & 3))), ub = static_cast<uint32_t>((lane & 15) ^ (4 * (kb & 3)) ^ (2 * ((kb >> 3) & 1)));
+  auto load = [&](int sub) {
+    char* const st = lds + sub % 3 * kShortStage;
+    const int k0 = sub * 32;
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(a0 + (k0 >> 8) * blk_row + (k0 & 255) * 512), rb = make_rsrc(b0 + static_cast<int64_t>(k0) * 512);
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, reinterpret_cast<uint32_t*>(st + (8 * p + 2 * wave) * 512), 16,
+                                               static_cast<uint32_t>(8 * p + ka) * 512u + (ua ^ (2u * (p & 1))) * 16u, 0, 0, kCached);
+#pragma unroll
+    for (int p = 0; p < 2; ++p)                            // dz is zero for rows that do not exist: the last one in their place
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, reinterpret_cast<uint32_t*>(st + kShortA + (16 * p + 4 * wave) * 256), 16,
+                                               static_cast<uint32_t>(min(16 * p + kb, k_rows - 1 - k0)) * 512u + ub * 16u, 0, 0, kCached);
+  };
+  // fragments through the transposing reads
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)(lds)));
+  const int tq = lane & 3, tj = (lane >> 2) & 3, tg = lane >> 4;
+  uint32_t tra[C::MI], trb[C::NI];
+#pragma unroll
+  for (int i = 0; i < C::MI; ++i)
+    tra[i] = lds0 + (tg * 8 + tj) * 512 + (tq & 1) * 8 + (((wm * (C::WTM / 8) + i * 2 + (tq >> 1)) ^ (4 * tj) ^ (2 * (tg & 1))) * 16);
+#pragma unroll
+  for (int j = 0; j < C::NI; ++j)
+    trb[j] = lds0 + kShortA + (tg * 8 + tj) * 256 + (tq & 1) * 8 + (((wn * (C::WTN / 8) + j * 2 + (tq >> 1)) ^ (4 * tj) ^ (2 * (tg & 1))) * 16);
+  typedef short short8v __attribute__((ext_vector_type(8)));
+  constexpr int HA = C::MI / 2;
+  bf16x8 af[2][HA], bfr[C::NI];
+  auto read = [&](uint32_t addr, auto row_c) {
+    short4v lo, hi;
+    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(lo) : "v"(addr));
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(addr), "n"(4 * decltype(row_c)::value));
+    const short8v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+  };
+  using RowA = std::integral_constant<int, 512>;
+  using RowB = std::integral_constant<int, 256>;
+  floatx4 acc[C::MI][C::NI];
+  zero_acc<C>(acc);
+  auto mfmas = [&](int h) {
+#pragma unroll
+    for (int i = 0; i < HA; ++i)
+#pragma unroll
+      for (int jj = 0; jj < C::NI; ++jj) {
+        const int j = i & 1 ? C::NI - 1 - jj : jj;
+        acc[h * HA + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[h][i], bfr[j], acc[h * HA + i][j], 0, 0, 0);
+      }
+  };
+  if (nsub > 0) load(0);
+  if (nsub > 1) load(1);
+  for (int sub = 0; sub < nsub; ++sub) {
+    // this step's loads have landed, the next one's may be on their way; everybody has read the step before, whose stage is loaded again
+    if (sub + 1 < nsub) __builtin_amdgcn_s_waitcnt(0x0F70 | 6); else __builtin_amdgcn_s_waitcnt(0x0F70);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    if (sub + 2 < nsub) load(sub + 2);
+    const uint32_t st = static_cast<uint32_t>(sub % 3 * kShortStage);
+#pragma unroll
+    for (int j = 0; j < C::NI; ++j) bfr[j] = read(trb[j] + st, RowB{});
+#pragma unroll
+    for (int i = 0; i < HA; ++i) af[0][i] = read(tra[i] + st, RowA{});
+#pragma unroll
+    for (int j = 0; j < C::NI; ++j) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bfr[j]));
+#pragma unroll
+    for (int i = 0; i < HA; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(af[0][i]));
+#pragma unroll
+    for (int i = 0; i < HA; ++i) af[1][i] = read(tra[HA + i] + st, RowA{});
+    mfmas(0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < HA; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(af[1][i]));
+    mfmas(1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // the turns lie in the two stages that nobody reads any more and no load is under way to
+  char* const turn = lds + (nsub + (wave == 3 ? 1 : 0)) % 3 * kShortStage + (wave == 3 ? 0 : wave) * kTurnBytes;
+  const int64_t m0 = static_cast<int64_t>(tile_m) * C::BM;
+  const int n0 = tile_n * C::BN;
+  store_acc_f32<C>(acc, turn, dW + m0 * d + n0, d, V - m0, d - n0, accumulate);
 }
 // Both products in one launch, in groups of 4 x 8 tiles that are worked on together on one XCD.  Every XCD owns a contiguous
 // range of the dH tiles (slice after slice, so that its workgroups share a slice of both operands) and behind it the share
@@ -1652,14 +1760,20 @@ constexpr int kDhSliceTiles = 256;
 inline int64_t dh_tiles(int64_t rows, int d) { return static_cast<int64_t>(cdiv(rows, 256)) * cdiv(d, 256); }
 // decided by the rows of the call and its chunks, not by those of the last chunk, which may have fewer
 bool slices_dh(int64_t n_sel, int64_t chunk_rows, int d) { return dh_tiles(chunk_rows, d) < (chunk_rows < n_sel ? kDhSliceTiles / 2 : kDhSliceTiles); }
+// dW of one block of rows gets a launch of its own (k_dw_short) where it is large: its stores, which everything else then waits for, are longer than the launch
+// and the dH tiles' uneven end that it pays for.  Update in one launch and two: 203 rows of 3584 against 152 064 (2.2 GB) 1023 and 972 us, 100 892 and
+// 859, 30 859 and 837, of 2048 against 151 936 (1.24 GB) 203 614 and 612, of 1096 against 50 001 (0.22 GB) 194 and 203; the products themselves: 300
+// rows of 2048 887 and 943, 725 of 3584 2262 and 2258, 2500 6594 and 8070.
+constexpr int64_t kDwApartRows = 256, kDwApartBytes = int64_t{1} << 30;
 struct DhPlan {
   int slices, voc_blks;
 };
 size_t dh_part_bytes(const DhPlan& p, int tiles_r, int tiles_d) {
   return p.slices > 1 ? static_cast<size_t>(p.slices) * tiles_r * tiles_d * (256 * 256 * sizeof(float)) : 0;
 }
-DhPlan plan_dh(int64_t tiles_r, int64_t tiles_d, int tiles_v, size_t room) {
-  int want = static_cast<int>((kDhSliceTiles + tiles_r * tiles_d - 1) / (tiles_r * tiles_d));
+// `alone`: nothing fills a last round, there must be none
+DhPlan plan_dh(int64_t tiles_r, int64_t tiles_d, int tiles_v, size_t room, bool alone = false) {
+  int want = static_cast<int>((kDhSliceTiles + (alone ? 0 : tiles_r * tiles_d - 1)) / (tiles_r * tiles_d));
   const size_t one = static_cast<size_t>(tiles_r * tiles_d) * (256 * 256 * sizeof(float));
   if (static_cast<size_t>(want) > room / one) want = static_cast<int>(room / one);
   if (want > tiles_v) want = tiles_v;
@@ -2072,12 +2186,15 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
 
   // both gradient products of the chunk of `rows` rows from c0 on, and what the slices of dH leave; the partial sums lie
   // behind the chunk's operands or, once the scoring pass's own partials have been merged, in their place
+  // (true: dW gets a launch of its own)
   auto dh_plan = [&](int64_t rows, size_t used, DhSlices* sl) {
     const int tiles_r = static_cast<int>(cdiv(rows, 256)), tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
     const size_t behind = room > used ? room - used : 0;
     const size_t front = static_cast<size_t>(reinterpret_cast<char*>(w.score.logp_c) - reinterpret_cast<char*>(w.score.partial));
-    const DhPlan p = plan_dh(tiles_r, tiles_d, tiles_v, slices_dh(n_sel, mc, d) ? std::max(behind, front) : 0);
+    const bool may = n_sel <= kDwApartRows && static_cast<int64_t>(V) * d * 4 >= kDwApartBytes;
+    const DhPlan p = plan_dh(tiles_r, tiles_d, tiles_v, slices_dh(n_sel, mc, d) ? std::max(behind, front) : 0, may);
     *sl = DhSlices{p.slices, p.voc_blks, behind > front ? reinterpret_cast<float*>(w.chunk + used) : reinterpret_cast<float*>(w.score.partial)};
+    return may && p.slices * tiles_r * tiles_d >= kDhSliceTiles * 3 / 4;
   };
   CloseArgs rest{};
   rest.H = Hb;
@@ -2110,7 +2227,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     UMAS_LAUNCHED("k_update_close");
     return UMAS_OK;
   };
-  auto gradients = [&](int64_t c0, int64_t rows, const DhSlices& sl, const uint16_t* op, int blk_pitch, const uint16_t* Hs, const float* sc) -> umas_status {
+  auto gradients = [&](int64_t c0, int64_t rows, const DhSlices& sl, bool dw_apart, const uint16_t* op, int blk_pitch, const uint16_t* Hs, const float* sc) -> umas_status {
     const int64_t mcp = round_up(rows, 256);
     const int tiles_r = static_cast<int>(mcp / 256), tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
     const unsigned grid = static_cast<unsigned>(round_up(device_cus(), 8));      // every XCD's sequence needs somebody
@@ -2118,6 +2235,12 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
                        tiles_d, sl, tiles_r, w.live, w.blk_orig, static_cast<uint16_t*>(dH), dW, (accumulate_dW || c0 > 0) ? 1 : 0,
                        rowsel, c0, rows, ids, w.g_c, sc);
     UMAS_LAUNCHED("k_gemm_dh_dw");
+    if (dw_apart) {
+      const int tiles_n = (d + ShortCfg::BN - 1) / ShortCfg::BN;
+      hipLaunchKernelGGL(k_dw_short, dim3(static_cast<unsigned>(round_up(static_cast<int64_t>(tiles_v) * tiles_n, 8))), dim3(ShortCfg::T), 0, st, op, blk_pitch,
+                         Vp, mcp, Hs, d, V, tiles_v, tiles_n, w.live, dW, (accumulate_dW || c0 > 0) ? 1 : 0);
+      UMAS_LAUNCHED("k_dw_short");
+    }
     CloseArgs C = rest;                                  // a chunk's slices are added up before the next one's are written
     if (c0 + rows < n_sel) C.onehot_groups = C.n_stats = 0;
     if (sl.n > 1) {
@@ -2157,17 +2280,17 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     if (s != UMAS_OK) return s;
   } else {
     const int tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
-    auto live_args = [&](int64_t c0, int64_t rows, int slices) {
+    auto live_args = [&](int64_t c0, int64_t rows, int slices, bool dw_apart) {
       return LiveArgs{static_cast<int>(c0 >> 8), static_cast<int>(round_up(rows, 256) / 256), rows, kl_coef != 0.f ? 1 : 0,   // a KL term gives every row a gradient
-                      tiles_v, tiles_d, Vp, slices, w.blk_live, w.blk_cidx, w.blk_orig, w.live};
+                      dw_apart ? 0 : tiles_v, tiles_d, Vp, slices, w.blk_live, w.blk_cidx, w.blk_orig, w.live};
     };
     OpenArgs O{Hb, Wb, d, V, rowsel, n_sel, ids, adv, nblk, w.blk_live, w.flags, w.cref, static_cast<uint32_t*>(dH),
                n_rows * static_cast<int64_t>(d) / 2, rowsel ? logp_new : nullptr, n_rows, 0, {}};
     if (mc >= n_sel && nblk <= kFewBlocks) {
       DhSlices sl;
-      dh_plan(n_sel, chunk_bytes(n_sel, d, V, dtype), &sl);
+      const bool dw_apart = dh_plan(n_sel, chunk_bytes(n_sel, d, V, dtype), &sl);
       O.nblk = O.pack = 1;
-      O.live = live_args(0, n_sel, sl.n);
+      O.live = live_args(0, n_sel, sl.n, dw_apart);
     }
     // a wavefront per row up to 8192 workgroups; at least 1024 for the clearing
     hipLaunchKernelGGL(k_update_open, dim3(O.nblk + std::min<unsigned>(std::max<unsigned>(cdiv(n_sel, 4), 1024), 8192)), dim3(256), 0, st, O);
@@ -2182,9 +2305,9 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       uint16_t* E = reinterpret_cast<uint16_t*>(w.chunk);
       uint16_t* Hs = reinterpret_cast<uint16_t*>(w.chunk + align_up(static_cast<size_t>(mcp) * Vp * 2));
       DhSlices sl;
-      dh_plan(rows, chunk_bytes(rows, d, V, dtype), &sl);
+      const bool dw_apart = dh_plan(rows, chunk_bytes(rows, d, V, dtype), &sl);
       if (!O.pack) {
-        hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, live_args(c0, rows, sl.n));
+        hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, live_args(c0, rows, sl.n, dw_apart));
         UMAS_LAUNCHED("k_live_scan");
       }
       if (narrow)
@@ -2206,7 +2329,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       hipLaunchKernelGGL(k_keep_rows, dim3(cdiv(rows, 4)), dim3(256), 0, st, Hb, d, V, rowsel, c0, rows, ids, E,
                          static_cast<int64_t>(tiles_v), w.score.lse_c, w.a_c, w.cref, w.flags, w.blk_cidx, w.sc, Hs, mcp);
       UMAS_LAUNCHED("k_keep_rows");
-      s = gradients(c0, rows, sl, E, 1, Hs, w.sc);
+      s = gradients(c0, rows, sl, dw_apart, E, 1, Hs, w.sc);
       if (s != UMAS_OK) return s;
     }
   }
@@ -2265,11 +2388,11 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     UMAS_LAUNCHED("k_dz_rows");
     // with an entropy bonus every row has a gradient: all blocks are live
     DhSlices sl;
-    dh_plan(rows, mc_z > 0 ? logit_chunk_bytes(rows, d, V) : chunk_bytes(rows, d, V, dtype), &sl);
-    hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, LiveArgs{static_cast<int>(c0 >> 8), tiles_r, rows, 1, tiles_v, tiles_d, Vp, sl.n,
+    const bool dw_apart = dh_plan(rows, mc_z > 0 ? logit_chunk_bytes(rows, d, V) : chunk_bytes(rows, d, V, dtype), &sl);
+    hipLaunchKernelGGL(k_live_scan, dim3(1), dim3(512), 0, st, LiveArgs{static_cast<int>(c0 >> 8), tiles_r, rows, 1, dw_apart ? 0 : tiles_v, tiles_d, Vp, sl.n,
                        w.blk_live, w.blk_cidx, w.blk_orig, w.live});
     UMAS_LAUNCHED("k_live_scan");
-    s = gradients(c0, rows, sl, dZ, blk_pitch, Hs, nullptr);
+    s = gradients(c0, rows, sl, dw_apart, dZ, blk_pitch, Hs, nullptr);
     if (s != UMAS_OK) return s;
   }
   return UMAS_OK;

@@ -336,3 +336,9 @@ def test_update_of_part_of_a_block_that_is_computed_again(rows, d, V):
 @pytest.mark.parametrize("rows", [90, 200])
 def test_update_of_few_rows_with_a_large_head(rows):
     check_update(np.random.default_rng(rows), rows, 2048, 66000, select=1.0)
+
+
+# dW of 1 GiB and more, which has a launch of its own up to 256 rows: a column tile of eight columns, a step of 32 rows that is partly filled
+@pytest.mark.parametrize("rows,entropy_coef,accumulate", [(70, 0.0, True), (200, 0.01, False), (256, 0.0, True), (257, 0.0, False)])
+def test_update_of_few_rows_with_a_large_gradient(rows, entropy_coef, accumulate):
+    check_update(np.random.default_rng(rows), rows, 4104, 65500, select=1.0, entropy_coef=entropy_coef, accumulate=accumulate)
