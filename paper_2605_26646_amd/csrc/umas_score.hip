@@ -1155,38 +1155,59 @@ __device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[C::MI][C::NI]
   const int r0 = wave / C::WN * C::WTM, c0 = wave % C::WN * C::WTN + (lane & 15) * 4;
   const bool whole = rows >= C::BM && cols >= C::BN;                 // the same for every thread
   float* const dst = out + (r0 + (lane >> 4)) * ld + c0;
-  floatx4 have[8];                                                   // what is there already, a piece ahead
-  auto fetch = [&](int h) {
+  constexpr int kPieces = C::MI / 2;
+  // Each case is a run of its own: with the branches inside, the waits cannot tell what is under way and are for everything, the stores of
+  // the piece before included.
+  auto pieces = [&](auto add) {
+    constexpr bool kAdd = decltype(add)::value;
+    // (one offset a lane and one a piece: 32 addresses of 64 bits would be a quarter of the registers)
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const int w_row = __builtin_amdgcn_readfirstlane(r0), w_col = __builtin_amdgcn_readfirstlane(wave) % C::WN * C::WTN;
+    const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(out + w_row * ld + w_col);
+    const int at = static_cast<int>((lane >> 4) * ld + (lane & 15) * 4) * 4, step = static_cast<int>(ld) * 16;   // four rows
+    floatx4 have[8];                                                 // what is there already, a piece ahead
+    auto fetch = [&](int h) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) have[i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_a4*>(dst + (h * 32 + i * 4) * ld));
-  };
-  if (whole && accumulate) fetch(0);
+      for (int i = 0; i < 8; ++i)
+        have[i] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, (h * 8 + i) * step, kStream));
+    };
+    if constexpr (kAdd) fetch(0);
 #pragma unroll
-  for (int h = 0; h < C::MI / 2; ++h) {
-    turn_in(acc, h, turn, lane);
-    floatx4 x[8];
+    for (int h = 0; h < kPieces; ++h) {
+      turn_in(acc, h, turn, lane);
+      floatx4 x[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = turn_out(turn, i, lane);
-    if (whole) {
-      if (accumulate) {
+      for (int i = 0; i < 8; ++i) x[i] = turn_out(turn, i, lane);
+      if constexpr (kAdd) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] += have[i];
-        if (h + 1 < C::MI / 2) fetch(h + 1);
+        if (h + 1 < kPieces) fetch(h + 1);
       }
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const f32x4_a4 y = x[i];
-        __builtin_nontemporal_store(y, reinterpret_cast<f32x4_a4*>(dst + (h * 32 + i * 4) * ld));
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x[i]), rsrc, at, (h * 8 + i) * step, kStream);
       }
-    } else {
+      __builtin_amdgcn_wave_barrier();
+    }
+  };
+  if (whole && accumulate) {
+    pieces(std::true_type());
+  } else if (whole) {
+    pieces(std::false_type());
+  } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+    for (int h = 0; h < kPieces; ++h) {
+      turn_in(acc, h, turn, lane);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const floatx4 x = turn_out(turn, i, lane);
         if (r0 + h * 32 + i * 4 + (lane >> 4) < rows && c0 < cols) {
           f32x4_a4* const at = reinterpret_cast<f32x4_a4*>(dst + (h * 32 + i * 4) * ld);
-          *at = accumulate ? x[i] + *at : x[i];
+          *at = accumulate ? x + *at : x;
         }
+      }
+      __builtin_amdgcn_wave_barrier();
     }
-    __builtin_amdgcn_wave_barrier();
   }
 }
 typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));     // dH has the alignment of its entries
@@ -1761,10 +1782,15 @@ inline int64_t dh_tiles(int64_t rows, int d) { return static_cast<int64_t>(cdiv(
 // decided by the rows of the call and its chunks, not by those of the last chunk, which may have fewer
 bool slices_dh(int64_t n_sel, int64_t chunk_rows, int d) { return dh_tiles(chunk_rows, d) < (chunk_rows < n_sel ? kDhSliceTiles / 2 : kDhSliceTiles); }
 // dW of one block of rows gets a launch of its own (k_dw_short) where it is large: its stores, which everything else then waits for, are longer than the launch
-// and the dH tiles' uneven end that it pays for.  Update in one launch and two: 203 rows of 3584 against 152 064 (2.2 GB) 1023 and 972 us, 100 892 and
-// 859, 30 859 and 837, of 2048 against 151 936 (1.24 GB) 203 614 and 612, of 1096 against 50 001 (0.22 GB) 194 and 203; the products themselves: 300
-// rows of 2048 887 and 943, 725 of 3584 2262 and 2258, 2500 6594 and 8070.
-constexpr int64_t kDwApartRows = 256, kDwApartBytes = int64_t{1} << 30;
+// and the dH tiles' uneven end that it pays for.  Update against 151 936 in one launch and two, 203 rows of 2048 (1.16 GiB) 614 and 604 us, 2304 693
+// and 666, 2560 754 and 735, 3072 892 and 853, 4096 1164 and 1092, of 1096 against 50 001 (0.2 GiB) 194 and 203; 100 rows, whose dH tiles are half as
+// long, of 2048 518 and 524, 2304 597 and 580, 3072 763 and 758, 3584 892 and 859; 30 rows of 2048 508 and 517, 2304 582 and 569, 3072 722 and
+// 731.  More than a block: 300 rows of 2048 876 and 922, 725 of 3584 2262 and 2258, 2500 6594 and 8070.
+constexpr int64_t kDwApartBytes = int64_t{1} << 30;
+bool dw_apart(int64_t n_sel, int d, int V) {
+  const int64_t bytes = static_cast<int64_t>(V) * d * 4;
+  return n_sel > 64 && n_sel <= 256 && bytes >= (n_sel > 128 ? kDwApartBytes : kDwApartBytes / 4 * 5);
+}
 struct DhPlan {
   int slices, voc_blks;
 };
@@ -2191,7 +2217,7 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     const int tiles_r = static_cast<int>(cdiv(rows, 256)), tiles_v = static_cast<int>(Vp / 256), tiles_d = (d + 255) / 256;
     const size_t behind = room > used ? room - used : 0;
     const size_t front = static_cast<size_t>(reinterpret_cast<char*>(w.score.logp_c) - reinterpret_cast<char*>(w.score.partial));
-    const bool may = n_sel <= kDwApartRows && static_cast<int64_t>(V) * d * 4 >= kDwApartBytes;
+    const bool may = dw_apart(n_sel, d, V);
     const DhPlan p = plan_dh(tiles_r, tiles_d, tiles_v, slices_dh(n_sel, mc, d) ? std::max(behind, front) : 0, may);
     *sl = DhSlices{p.slices, p.voc_blks, behind > front ? reinterpret_cast<float*>(w.chunk + used) : reinterpret_cast<float*>(w.score.partial)};
     return may && p.slices * tiles_r * tiles_d >= kDhSliceTiles * 3 / 4;
