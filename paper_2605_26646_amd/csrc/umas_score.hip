@@ -165,7 +165,7 @@ __device__ __forceinline__ void score_tile(const uint16_t* __restrict__ W, const
                                            float4* __restrict__ partial, int64_t n_pad, const KeepArgs& keep,
                                            uint16_t* lds) {
   constexpr bool KEEP = LEAVE == Leave::kNumerators;
-  static_assert(LEAVE != Leave::kLogits || C::BM * C::BN == Cfg::BM * Cfg::BN, "logits are kept in whole blocks");
+  static_assert(LEAVE != Leave::kLogits || (C::BM == 256 && C::WTM == Cfg::WTM), "logits are kept in rows of 128 of a block's 256 entries");
   static_assert(256 % C::BM == 0 && 256 % C::BN == 0, "numerators are kept inside a block");
   constexpr int kPitch = Stage<C>::kPitch;
   const int m0 = tile_m * C::BM;
@@ -267,7 +267,7 @@ __device__ __forceinline__ void score_tile(const uint16_t* __restrict__ W, const
       for (int i = 0; i < C::MI; ++i)
         *reinterpret_cast<floatx4*>(stage + (lane & 15) * kLogitPitch + (i * 16 + (lane >> 4) * 4) * 4) = acc[i][j];
       __builtin_amdgcn_wave_barrier();
-      float* out = keep.Z + blk_offset(tile_n, tile_m, keep.Vp >> 8) + (wave % C::WN * C::WTN + j * 16 + (lane >> 5)) * 256 + wm * C::WTM + (lane & 31) * 4;
+      float* out = keep.Z + blk_offset(n0 >> 8, tile_m, keep.Vp >> 8) + ((n0 & 255) + wave % C::WN * C::WTN + j * 16 + (lane >> 5)) * 256 + wm * C::WTM + (lane & 31) * 4;
 #pragma unroll
       for (int q = 0; q < 8; ++q)
         if (n0 + wave % C::WN * C::WTN + j * 16 + q * 2 + (lane >> 5) < mc)   // rows past the chunk: nobody reads them
@@ -329,7 +329,8 @@ __device__ __forceinline__ void score_tile(const uint16_t* __restrict__ W, const
 
 // The tiles of a workgroup.  With few column tiles a workgroup has one tile, and the last round of compute units is often nearly empty: the tiles of
 // one that is at most half full are cut into two of 128 rows of the selection.  594 tiles on 256 compute units, 256 rows: 2048 columns 190 -> 173 us, 3584
-// 283 -> 270; 150 rows 188 -> 170 and 271 -> 262; the update of 203 rows of 3584 1037 -> 1022.
+// 283 -> 270; 150 rows 188 -> 170 and 271 -> 262; the update of 203 rows of 3584 1037 -> 1022, with an entropy bonus 1056 -> 1026, 100 rows of 2048 609 ->
+// 584.  (Up to 128 rows all tiles cut, whose other halves have no rows: 100 rows with a bonus 611, of 3584 957 -> 1036.)
 using HalfCfg = TileCfg<256, 128, 2, 4>;                 // the lanes of a row as in a whole tile: the same bits
 template <Leave LEAVE, class C>
 __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
@@ -338,7 +339,7 @@ __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, cons
                                             float4* __restrict__ partial, int64_t n_pad, const KeepArgs& keep,
                                             uint16_t* lds, int halved = 0) {
   const bool w_once = tiles_n == 1 && beyond_cache(d, V, kLogitsOnceBytes);
-  if constexpr (C::BM == 256 && C::BN == 256 && LEAVE != Leave::kLogits) {
+  if constexpr (C::BM == 256 && C::BN == 256) {
     if (halved > 0) {                             // the last `halved` tiles of every XCD
       const int per_xcd = (tiles_m * tiles_n + 7) / 8, xcd = static_cast<int>(blockIdx.x & 7), w = static_cast<int>(blockIdx.x >> 3), whole = per_xcd - halved;
       if (w >= whole) {
@@ -399,9 +400,9 @@ k_score_keep_narrow(const uint16_t* __restrict__ W, const uint16_t* __restrict__
 __global__ void __launch_bounds__(Cfg::T)
 k_score_logits(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
                const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc, const int32_t* __restrict__ ids,
-               int tiles_m, int tiles_n, int panel, float4* __restrict__ partial, int64_t n_pad, float* __restrict__ Z, int64_t Vp) {
+               int tiles_m, int tiles_n, int panel, int halved, float4* __restrict__ partial, int64_t n_pad, float* __restrict__ Z, int64_t Vp) {
   __shared__ __attribute__((aligned(16))) uint16_t lds[kLogitLds / 2];
-  score_tiles<Leave::kLogits, Cfg>(W, H, d, V, rowsel, c0, mc, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{nullptr, nullptr, Vp, nullptr, nullptr, Z}, lds);
+  score_tiles<Leave::kLogits, Cfg>(W, H, d, V, rowsel, c0, mc, ids, tiles_m, tiles_n, panel, partial, n_pad, KeepArgs{nullptr, nullptr, Vp, nullptr, nullptr, Z}, lds, halved);
 }
 
 // ------------------------------------------------------------------ bf16: a few rows
@@ -2391,8 +2392,9 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
     const int tiles_v = static_cast<int>(Vp / 256), tiles_r = static_cast<int>(mcp / 256), tiles_d = (d + 255) / 256;
     const int blk_pitch = mc_z > 0 ? 2 : 1, panel = row_panel(tiles_r, d);
     if (mc_z > 0) {
-      hipLaunchKernelGGL(k_score_logits, dim3(tile_grid<kGM, kGN>(tiles_v, tiles_r, panel, kTilesPerWg)), dim3(Cfg::T), 0, st, Wb, Hb, d, V,
-                         rowsel, c0, rows, ids, tiles_v, tiles_r, panel, w.score.partial, round_up(n_sel, Cfg::BN),
+      const int halved = halved_tiles(tiles_v, tiles_r);
+      hipLaunchKernelGGL(k_score_logits, score_grid(tiles_v, tiles_r, panel, halved), dim3(Cfg::T), 0, st, Wb, Hb, d, V,
+                         rowsel, c0, rows, ids, tiles_v, tiles_r, panel, halved, w.score.partial, round_up(n_sel, Cfg::BN),
                          reinterpret_cast<float*>(w.chunk), Vp);
       UMAS_LAUNCHED("k_score_logits");
       launch_finalize(rows, n_sel, st, w.score.partial, tiles_v, round_up(n_sel, Cfg::BN), c0, c0 + rows, static_cast<const float*>(nullptr), rowsel,
