@@ -537,20 +537,14 @@ k_score_few(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int 
 // 24 rows of 594 tiles 41 -> 7 us, 16 100 rows 53 -> 36; with enough rows to fill the chip the extra merge only costs
 // (39 000 rows, 373 MB: 82 us split, 69 not).
 constexpr int64_t kFinSplitRows = 20000;
+// Row n's parts merged; true in the thread that has the result (SPLIT: one of the first eight of the workgroup).
 template <bool SPLIT>
-__global__ void __launch_bounds__(256)
-k_score_finalize(const float4* __restrict__ partial, int tiles_m, int64_t n_pad, int64_t n_begin,
-                 int64_t n_end, const float* __restrict__ zy_c, const int32_t* __restrict__ rowsel,
-                 const int32_t* __restrict__ ids, int V,
-                 float* __restrict__ logp_c, float* __restrict__ lse_c, float* __restrict__ ent_c,
-                 float* __restrict__ logp, float* __restrict__ lse, float* __restrict__ entropy) {
+__device__ __forceinline__ bool merge_parts(const float4* __restrict__ partial, int tiles_m, int64_t n_pad, int64_t n, bool live, Part& p, float& zy) {
   __shared__ float4 s_part[4][8];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t n = n_begin + (SPLIT ? static_cast<int64_t>(blockIdx.x) : static_cast<int64_t>(blockIdx.x) * 4 + wave) * 8 + (lane & 7);
-  const bool live = n < n_end;
   constexpr int kParts = SPLIT ? 32 : 8;
-  Part p{kNegInf, 0.f, 0.f};
-  float zy = 0.f;
+  p = Part{kNegInf, 0.f, 0.f};
+  zy = 0.f;
   if (live) {
     for (int t0 = SPLIT ? threadIdx.x >> 3 : lane >> 3; t0 < tiles_m; t0 += 4 * kParts) {
       float4 q[4];
@@ -582,18 +576,35 @@ k_score_finalize(const float4* __restrict__ partial, int tiles_m, int64_t n_pad,
       }
     }
   }
-  if (lane >= 8 || !live || (SPLIT && wave != 0)) return;
+  return lane < 8 && live && (!SPLIT || wave == 0);
+}
+struct RowScore {
+  float logp, lse, entropy;
+};
+__device__ __forceinline__ RowScore row_score(const Part& p, float zy, bool ok) {
+  const float l = p.m + logf(p.s);
+  return RowScore{ok ? zy - l : 0.f, l, ok ? l - p.t / p.s : 0.f};
+}
+template <bool SPLIT>
+__global__ void __launch_bounds__(256)
+k_score_finalize(const float4* __restrict__ partial, int tiles_m, int64_t n_pad, int64_t n_begin,
+                 int64_t n_end, const float* __restrict__ zy_c, const int32_t* __restrict__ rowsel,
+                 const int32_t* __restrict__ ids, int V,
+                 float* __restrict__ logp_c, float* __restrict__ lse_c, float* __restrict__ ent_c,
+                 float* __restrict__ logp, float* __restrict__ lse, float* __restrict__ entropy) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t n = n_begin + (SPLIT ? static_cast<int64_t>(blockIdx.x) : static_cast<int64_t>(blockIdx.x) * 4 + wave) * 8 + (lane & 7);
+  Part p;
+  float zy;
+  if (!merge_parts<SPLIT>(partial, tiles_m, n_pad, n, n < n_end, p, zy)) return;
   if (zy_c) zy = zy_c[n];                                   // taken logits computed beforehand
   const int64_t row = rowsel ? rowsel[n] : n;
   const int y = ids[row];
-  const bool ok = y >= 0 && y < V;
-  const float l = p.m + logf(p.s);
-  const float lp = ok ? zy - l : 0.f;
-  const float en = ok ? l - p.t / p.s : 0.f;
-  if (logp_c) { logp_c[n] = lp; lse_c[n] = l; ent_c[n] = en; }
-  if (logp) logp[row] = lp;
-  if (lse) lse[row] = l;
-  if (entropy) entropy[row] = en;
+  const RowScore r = row_score(p, zy, y >= 0 && y < V);
+  if (logp_c) { logp_c[n] = r.logp; lse_c[n] = r.lse; ent_c[n] = r.entropy; }
+  if (logp) logp[row] = r.logp;
+  if (lse) lse[row] = r.lse;
+  if (entropy) entropy[row] = r.entropy;
 }
 
 // ------------------------------------------------------------------ clipped surrogate
@@ -665,6 +676,29 @@ ppo_stats(int k, int nblk, int n_roles, float entropy_coef, int64_t norm_rows, c
   for (int b = threadIdx.x; b < nblk; b += blockDim.x)
 #pragma unroll
     for (int j = 0; j < kStat; ++j) v[j] += blk_stats[static_cast<int64_t>(b) * nacc + k * kStat + j];
+#pragma unroll
+  for (int j = 0; j < kStat; ++j) sum[j] = block_sum<double>(v[j], smem);
+  if (threadIdx.x != 0) return;
+  stats[k] = loss_stats(sum, k, entropy_coef, norm_rows);
+}
+
+// The same from the rows, where they are few and k_rows_few has left no sums.
+__device__ __forceinline__ void ppo_stats_by_row(int k, const Surrogate& S, int64_t n_sel, float entropy_coef, int64_t norm_rows, const float* __restrict__ logp_c,
+                                                 const float* __restrict__ ent_c, umas_loss_stats* __restrict__ stats) {
+  __shared__ double smem[32];
+  double v[kStat] = {}, sum[kStat];
+  for (int64_t n = threadIdx.x; n < n_sel; n += blockDim.x) {
+    const int64_t row = S.rowsel ? S.rowsel[n] : n;
+    const int y = S.ids[row];
+    const SurrogateRow R = surrogate_row(S, row, y >= 0 && y < S.V, logp_c[n], ent_c[n]);
+    if (k > 0 && R.role != k - 1) continue;
+    v[0] += static_cast<double>(R.L);
+    v[1] += R.clipped != 0.f ? 1.0 : 0.0;
+    v[2] += static_cast<double>(R.en);
+    v[3] += static_cast<double>(R.kl);
+    v[4] += 1.0;
+    v[5] += R.valid ? 0.0 : 1.0;
+  }
 #pragma unroll
   for (int j = 0; j < kStat; ++j) sum[j] = block_sum<double>(v[j], smem);
   if (threadIdx.x != 0) return;
@@ -884,33 +918,35 @@ k_update_open(OpenArgs A) {
 // column blocks [d / 256][mcp][256].
 // Rows of a flagged block get factor 1: their dz comes complete from the recomputing kernel.  The entry of the
 // taken token is cleared in the [rows, V] operand (see k_ppo_rows).
-__global__ void __launch_bounds__(256)
-k_keep_rows(const uint16_t* __restrict__ H, int d, int V, const int32_t* __restrict__ rowsel, int64_t c0, int64_t rows,
-            const int32_t* __restrict__ ids, uint16_t* __restrict__ E, int64_t tiles_v, const float* __restrict__ lse_c,
-            const float* __restrict__ a_c,
-            const float* __restrict__ cref, const int32_t* __restrict__ flags, const int32_t* __restrict__ cidx,
-            float* __restrict__ sc, uint16_t* __restrict__ Hs, int64_t mcp) {
+struct KeptRows {
+  const uint16_t* H;
+  int d, V;
+  uint16_t* E;
+  int64_t tiles_v;
+  const float* cref;
+  const int32_t* flags;
+  const int32_t* cidx;
+  float* sc;
+  uint16_t* Hs;
+  int64_t mcp;
+};
+__device__ __forceinline__ float kept_factor(const KeptRows& K, int64_t n, float a, float lse) {
+  if (K.cidx[n >> 8] < 0) return 0.f;                        // a dead block: no row of it has a gradient
+  if (K.flags[n >> 8]) return 1.f;
+  return a != 0.f ? a * __expf(K.cref[n] - lse) : 0.f;       // a = 0: invalid id (reference NaN) or no gradient
+}
+// one wavefront; m: the row's place in the chunk, n: in the selection
+__device__ __forceinline__ void kept_row(const KeptRows& K, int64_t m, int64_t n, int64_t row, int y, float f) {
   const int lane = threadIdx.x & 63;
-  const int64_t m = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave;
-  if (m >= rows) return;
-  const int64_t n = c0 + m;
-  const int64_t row = rowsel ? rowsel[n] : n;
-  const float a = a_c[n];
-  const int blk = cidx[n >> 8];                              // place of the row's block among the live ones
-  if (blk < 0) {                                             // a dead block: no row of it has a gradient
-    if (lane == 0) sc[n] = 0.f;
-    return;
-  }
+  const int blk = K.cidx[n >> 8];                            // place of the row's block among the live ones
+  if (lane == 0) K.sc[n] = f;
+  if (blk < 0) return;
   const int64_t mp = static_cast<int64_t>(blk) * 256 + (m & 255);   // row in the packed operands
-  const int y = ids[row];
-  if (lane == 0 && y >= 0 && y < V)                          // the taken token's column goes through g_c in float32
-    E[blk_offset(blk, y >> 8, tiles_v) + (m & 255) * 256 + (y & 255)] = 0;
-  float f = 1.f;
-  if (!flags[n >> 8]) f = a != 0.f ? a * __expf(cref[n] - lse_c[n]) : 0.f;   // a = 0: invalid id (reference NaN) or no gradient
-  if (lane == 0) sc[n] = f;
-  const uint4* h = reinterpret_cast<const uint4*>(H + row * d);
-  for (int k = lane; k < d / 8; k += kWave) {
-    uint4* o = reinterpret_cast<uint4*>(Hs + (static_cast<int64_t>(k >> 5) * mcp + mp) * 256);   // column block k / 32 of the row
+  if (lane == 0 && y >= 0 && y < K.V)                        // the taken token's column goes through g_c in float32
+    K.E[blk_offset(blk, y >> 8, K.tiles_v) + (m & 255) * 256 + (y & 255)] = 0;
+  const uint4* h = reinterpret_cast<const uint4*>(K.H + row * K.d);
+  for (int k = lane; k < K.d / 8; k += kWave) {
+    uint4* o = reinterpret_cast<uint4*>(K.Hs + (static_cast<int64_t>(k >> 5) * K.mcp + mp) * 256);   // column block k / 32 of the row
     float x[8];
     bf16x8_to_f32(h[k], x);
     uint4 v;
@@ -921,6 +957,56 @@ k_keep_rows(const uint16_t* __restrict__ H, int d, int V, const int32_t* __restr
     o[k & 31] = v;
   }
 }
+__global__ void __launch_bounds__(256)
+k_keep_rows(KeptRows K, const int32_t* __restrict__ rowsel, int64_t c0, int64_t rows, const int32_t* __restrict__ ids, const float* __restrict__ lse_c,
+            const float* __restrict__ a_c) {
+  const int64_t m = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + threadIdx.x / kWave;
+  if (m >= rows) return;
+  const int64_t n = c0 + m, row = rowsel ? rowsel[n] : n;
+  kept_row(K, m, n, row, ids[row], kept_factor(K, n, a_c[n], lse_c[n]));
+}
+// Few rows (one chunk of up to kFewBlocks blocks): k_score_finalize, k_ppo_rows and k_keep_rows in one launch, eight rows to a workgroup; the statistics are left
+// to k_update_close, which goes over the rows once more.  Bound by its chain of loads, as the three were: update of 203 rows of 1096 against 50 001 191.6 and
+// 184.5 us, 60 rows of 1024 against 151 936 271 and 266, 500 562 and 558, 725 of 2048 1361.6 and 1355.8, 2000 3193 and 3198.
+struct RowsArgs {
+  const float4* partial;
+  int tiles_m;
+  int64_t n_pad, n_sel;
+  Surrogate S;
+  float *logp_c, *lse_c, *ent_c, *logp_new, *g_c, *a_c, *kz_c;
+  KeptRows K;
+};
+__global__ void __launch_bounds__(256)
+k_rows_few(RowsArgs A) {
+  __shared__ float s_f[8];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t n0 = static_cast<int64_t>(blockIdx.x) * 8, n = n0 + (lane & 7);
+  Part p;
+  float zy;
+  if (merge_parts<true>(A.partial, A.tiles_m, A.n_pad, n, n < A.n_sel, p, zy)) {
+    const int64_t row = A.S.rowsel ? A.S.rowsel[n] : n;
+    const int y = A.S.ids[row];
+    const bool ok = y >= 0 && y < A.S.V;
+    const RowScore r = row_score(p, A.K.cref[n], ok);
+    const SurrogateRow R = surrogate_row(A.S, row, ok, r.logp, r.entropy);
+    const float a = ok ? -R.g : 0.f;
+    A.logp_c[n] = r.logp;
+    A.lse_c[n] = r.lse;
+    A.ent_c[n] = r.entropy;
+    if (A.logp_new) A.logp_new[row] = r.logp;
+    A.g_c[n] = ok ? R.g * -expm1f(r.logp) : R.g;             // all of dz[n, y] (see k_ppo_rows)
+    A.a_c[n] = a;                                            // for the blocks that are computed once more
+    A.kz_c[n] = 0.f;
+    s_f[lane] = kept_factor(A.K, n, a, r.lse);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = wave; k < 8; k += 4) {
+    if (n0 + k >= A.n_sel) continue;
+    const int64_t row = A.S.rowsel ? A.S.rowsel[n0 + k] : n0 + k;
+    kept_row(A.K, n0 + k, n0 + k, row, A.S.ids[row], s_f[k]);
+  }
+}
 
 // ------------------------------------------------------------------ bf16: dz tiles into the chunk buffer
 // For blocks of rows whose numerators do not serve, and with an entropy bonus for narrow heads and in a small workspace (16 100 rows of 2048 in 2 GB,
@@ -928,8 +1014,10 @@ k_keep_rows(const uint16_t* __restrict__ H, int d, int V, const int32_t* __restr
 // -g exp(z - lse), plus the entropy bonus's term when its coefficient is not 0, and writes it as bf16 to
 // dZ [mcp, Vp].  Rows past the chunk and vocabulary ids past V get 0.  The one-hot part g at v = y is a single term per row and is added in
 // float32 where dH and dW are written, so that it never meets the bf16 rounding of the dense part.
+// CLEAR: the taken token's entry of every row is left at 0 (see k_ppo_rows); the others leave that to who goes over the rows afterwards.
+template <bool CLEAR>
 __device__ __forceinline__ void dz_tile(int tile_m, int tile_n, const uint16_t* __restrict__ W, const uint16_t* __restrict__ H,
-                                        int d, int V, const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc,
+                                        int d, int V, const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc, const int32_t* __restrict__ ids,
                                         const float* __restrict__ lse_c, const float* __restrict__ a_c,
                                         const float* __restrict__ kz_c, uint16_t* __restrict__ dZ, int64_t Vp, int out_blk,
                                         uint16_t* lds) {
@@ -961,10 +1049,12 @@ __device__ __forceinline__ void dz_tile(int tile_m, int tile_n, const uint16_t* 
     // dz = p (a + kz z) with p = exp(z - lse), a = -g + k (entropy - lse), kz = k = entropy_coef / n_sel: the
     // dense part of g (onehot - p) plus the entropy bonus's k p (log p + entropy).  Rows past the chunk: p = 0.
     float l2 = 1e30f, a = 0.f, kz = 0.f;
+    int y = -1;
     if (n < mc) {
       l2 = lse_c[c0 + n] * 1.44269504088896341f;
       a = a_c[c0 + n];
       kz = kz_c[c0 + n];
+      if constexpr (CLEAR) y = ids[rowsel ? rowsel[c0 + n] : c0 + n] - vbase;
     }
 #pragma unroll
     for (int i = 0; i < C::MI; ++i) {
@@ -973,6 +1063,7 @@ __device__ __forceinline__ void dz_tile(int tile_m, int tile_n, const uint16_t* 
       for (int r = 0; r < 4; ++r) {
         const float z = acc[i][j][r];
         dz[r] = __builtin_amdgcn_exp2f(fmaf(z, 1.44269504088896341f, -l2)) * fmaf(kz, z, a);
+        if (CLEAR && i * 16 + r == y) dz[r] = 0.f;
       }
       const uint32_t p01 = pack_bf16x2(dz[0], dz[1]), p23 = pack_bf16x2(dz[2], dz[3]);
       // staged in this wavefront's LDS region, stored in full lines below
@@ -1001,7 +1092,7 @@ k_dz_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d
   for (int it = 0; it < kTilesPerWg; ++it) {     // a workgroup walks the same place of kTilesPerWg consecutive tile groups
     int tile_m, tile_n;
     if (!tile_coords<kGM, kGN>(tiles_m, tiles_n, panel, &tile_m, &tile_n, it, kTilesPerWg)) continue;
-    dz_tile(tile_m, tile_n, W, H, d, V, rowsel, c0, mc, lse_c, a_c, kz_c, dZ, Vp, tile_n, lds);
+    dz_tile<false>(tile_m, tile_n, W, H, d, V, rowsel, c0, mc, nullptr, lse_c, a_c, kz_c, dZ, Vp, tile_n, lds);
   }
 }
 // The same tiles for the blocks of 256 rows that the keeping scoring pass has flagged, and only those: a fixed,
@@ -1009,7 +1100,7 @@ k_dz_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d
 constexpr int kFlaggedGrid = 256;
 __global__ void __launch_bounds__(Cfg::T)
 k_dz_flagged(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
-             const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc,
+             const int32_t* __restrict__ rowsel, int64_t c0, int64_t mc, const int32_t* __restrict__ ids,
              const float* __restrict__ lse_c, const float* __restrict__ a_c, const float* __restrict__ kz_c,
              int tiles_m, int tiles_n, uint16_t* __restrict__ dZ, int64_t Vp, const int32_t* __restrict__ flags,
              const int32_t* __restrict__ cidx) {
@@ -1018,7 +1109,7 @@ k_dz_flagged(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int
     const int out_blk = cidx[(c0 >> 8) + tile_n];
     if (!flags[(c0 >> 8) + tile_n] || out_blk < 0) continue;        // the same for every thread of the grid
     for (int tile_m = blockIdx.x; tile_m < tiles_m; tile_m += gridDim.x)
-      dz_tile(tile_m, tile_n, W, H, d, V, rowsel, c0, mc, lse_c, a_c, kz_c, dZ, Vp, out_blk, lds);
+      dz_tile<true>(tile_m, tile_n, W, H, d, V, rowsel, c0, mc, ids, lse_c, a_c, kz_c, dZ, Vp, out_blk, lds);
   }
 }
 
@@ -1668,7 +1759,9 @@ struct CloseArgs {
   int nblk, n_roles;
   float entropy_coef;
   int64_t norm_rows;
-  const double* blk_stats;
+  const double* blk_stats;                // NULL: from the rows
+  Surrogate S;
+  const float *logp_c, *ent_c;
   umas_loss_stats* stats;
   unsigned reduce_rows, reduce_pieces;    // workgroups of dh_reduce; 0: none
   DhSlices sl;
@@ -1689,7 +1782,8 @@ k_update_close(CloseArgs A) {
   }
   i -= A.onehot_groups * A.onehot_parts;
   if (i < A.n_stats) {
-    ppo_stats(i, A.nblk, A.n_roles, A.entropy_coef, A.norm_rows, A.blk_stats, A.stats);
+    if (A.blk_stats) ppo_stats(i, A.nblk, A.n_roles, A.entropy_coef, A.norm_rows, A.blk_stats, A.stats);
+    else ppo_stats_by_row(i, A.S, A.n_sel, A.entropy_coef, A.norm_rows, A.logp_c, A.ent_c, A.stats);
     return;
   }
   i -= A.n_stats;
@@ -2238,6 +2332,9 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
   rest.entropy_coef = entropy_coef;
   rest.norm_rows = norm_rows;
   rest.blk_stats = w.blk_stats;
+  rest.S = S;
+  rest.logp_c = w.score.logp_c;
+  rest.ent_c = w.score.ent_c;
   rest.stats = stats;
   rest.info = w.live;
   rest.blk_orig = w.blk_orig;
@@ -2319,6 +2416,12 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
       O.nblk = O.pack = 1;
       O.live = live_args(0, n_sel, sl.n, dw_apart);
     }
+    // (the statistics read the old log-probs and the advantages again once the new log-probs are written)
+    auto apart = [&](const void* in) {
+      const uintptr_t i = reinterpret_cast<uintptr_t>(in), o = reinterpret_cast<uintptr_t>(logp_new), bytes = static_cast<uintptr_t>(n_rows) * 4;
+      return !in || !o || i + bytes <= o || o + bytes <= i;
+    };
+    const bool logp_new_apart = apart(logp_old) && apart(logp_ref) && apart(adv) && apart(tok_role) && apart(ids);
     // a wavefront per row up to 8192 workgroups; at least 1024 for the clearing
     hipLaunchKernelGGL(k_update_open, dim3(O.nblk + std::min<unsigned>(std::max<unsigned>(cdiv(n_sel, 4), 1024), 8192)), dim3(256), 0, st, O);
     UMAS_LAUNCHED("k_update_open");
@@ -2344,18 +2447,25 @@ extern "C" umas_status umas_ppo_loss_fwd_bwd(const void* H, const void* W, umas_
         hipLaunchKernelGGL(k_score_keep_tiles, score_grid(tiles_v, tiles_r, panel, halved), dim3(Cfg::T), 0, st, Wb, Hb, d, V, rowsel, c0, rows, ids,
                            tiles_v, tiles_r, panel, halved, w.score.partial, n_pad, w.cref, E, Vp, w.flags, w.blk_cidx);
       UMAS_LAUNCHED(narrow ? "k_score_keep_narrow" : "k_score_keep_tiles");
-      launch_finalize(rows, n_sel, st, w.score.partial, tiles_m, n_pad, c0, c0 + rows, w.cref, rowsel, ids, V, w.score.logp_c, w.score.lse_c,
-                      w.score.ent_c, logp_new, static_cast<float*>(nullptr), static_cast<float*>(nullptr));
-      UMAS_LAUNCHED("k_score_finalize");
-      s = ppo_rows(c0, c0 + rows);
-      if (s != UMAS_OK) return s;
+      const KeptRows K{Hb, d, V, E, tiles_v, w.cref, w.flags, w.blk_cidx, w.sc, Hs, mcp};
+      if (O.pack && logp_new_apart) {
+        const RowsArgs A{w.score.partial, tiles_m, n_pad, n_sel, S, w.score.logp_c, w.score.lse_c, w.score.ent_c, logp_new, w.g_c, w.a_c, w.kz_c, K};
+        hipLaunchKernelGGL(k_rows_few, dim3(cdiv(n_sel, 8)), dim3(256), 0, st, A);
+        UMAS_LAUNCHED("k_rows_few");
+        rest.blk_stats = nullptr;
+      } else {
+        launch_finalize(rows, n_sel, st, w.score.partial, tiles_m, n_pad, c0, c0 + rows, w.cref, rowsel, ids, V, w.score.logp_c, w.score.lse_c,
+                        w.score.ent_c, logp_new, static_cast<float*>(nullptr), static_cast<float*>(nullptr));
+        UMAS_LAUNCHED("k_score_finalize");
+        s = ppo_rows(c0, c0 + rows);
+        if (s != UMAS_OK) return s;
+        hipLaunchKernelGGL(k_keep_rows, dim3(cdiv(rows, 4)), dim3(256), 0, st, K, rowsel, c0, rows, ids, w.score.lse_c, w.a_c);
+        UMAS_LAUNCHED("k_keep_rows");
+      }
       // blocks of rows the scoring pass flagged (a logit far above the row's reference) get dz the long way
-      hipLaunchKernelGGL(k_dz_flagged, dim3(kFlaggedGrid), dim3(Cfg::T), 0, st, Wb, Hb, d, V, rowsel, c0, rows,
+      hipLaunchKernelGGL(k_dz_flagged, dim3(kFlaggedGrid), dim3(Cfg::T), 0, st, Wb, Hb, d, V, rowsel, c0, rows, ids,
                          w.score.lse_c, w.a_c, w.kz_c, tiles_v, tiles_r, E, Vp, w.flags, w.blk_cidx);
       UMAS_LAUNCHED("k_dz_flagged");
-      hipLaunchKernelGGL(k_keep_rows, dim3(cdiv(rows, 4)), dim3(256), 0, st, Hb, d, V, rowsel, c0, rows, ids, E,
-                         static_cast<int64_t>(tiles_v), w.score.lse_c, w.a_c, w.cref, w.flags, w.blk_cidx, w.sc, Hs, mcp);
-      UMAS_LAUNCHED("k_keep_rows");
       s = gradients(c0, rows, sl, dw_apart, E, 1, Hs, w.sc);
       if (s != UMAS_OK) return s;
     }

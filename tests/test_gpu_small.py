@@ -342,3 +342,20 @@ def test_update_of_few_rows_with_a_large_head(rows):
 @pytest.mark.parametrize("rows,entropy_coef,accumulate", [(70, 0.0, True), (200, 0.01, False), (256, 0.0, True), (257, 0.0, False)])
 def test_update_of_few_rows_with_a_large_gradient(rows, entropy_coef, accumulate):
     check_update(np.random.default_rng(rows), rows, 4104, 65500, select=1.0, entropy_coef=entropy_coef, accumulate=accumulate)
+
+
+# New log-probs written over the old ones: these are gone when the surrogate looks at them, as if none were given.  One launch for the rows would
+# read some of them first; more rows than one launch takes, for comparison
+@pytest.mark.parametrize("rows", [60, 300, 2100])
+def test_update_that_writes_the_new_log_probs_over_the_old_ones(rows):
+    rng = np.random.default_rng(rows)
+    n, d, V = rows + rows // 4, 64, 700
+    H, W = (P.to_dev(wl.round_to_bf16(rng.normal(size=s).astype(np.float32)), torch.bfloat16) for s in ((n, d), (V, d)))
+    ids, sel = P.to_dev(rng.integers(0, V, n).astype(np.int32)), P.to_dev(np.sort(rng.choice(n, rows, replace=False)).astype(np.int32))
+    adv, old, role = P.to_dev(rng.normal(size=n).astype(np.float32)), P.to_dev(rng.normal(size=n).astype(np.float32)), P.to_dev(rng.integers(0, 2, n).astype(np.int32))
+    want = umas.umas_ppo_loss_fwd_bwd(H, W, ids, sel, None, adv, role, 2, 0.2)
+    got = umas.umas_ppo_loss_fwd_bwd(H, W, ids, sel, old, adv, role, 2, 0.2, logp_new=old)
+    assert torch.equal(got[1], want[1]) and torch.equal(got[2], want[2])
+    assert (got[3] - want[3]).norm() <= 1e-4 * want[3].norm()        # atomic order of the one-hot rows
+    a, b = umas.read_stats(got[0]), umas.read_stats(want[0])
+    assert all(np.allclose(a[k], b[k], rtol=1e-6, atol=1e-9) for k in a.dtype.names)
