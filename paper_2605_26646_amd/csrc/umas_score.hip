@@ -1416,7 +1416,8 @@ __device__ __forceinline__ void dw_tile(int tile_m, int tile_n, const uint16_t* 
 // stores (a wavefront's memory operations are counted in order): 203 rows of 3584 against 152 064 485 us, of which the products alone are 235 and the
 // stores of 2.2 GB 396 (5.5 TB/s, as much as a kernel that only stores such tiles reaches).  Here tiles of 256 x 128 have two workgroups to
 // a compute unit, so that one multiplies while the other stores, and a workgroup of its own each, which ends without waiting for its stores: 400
-// to 430 us.  K is walked in steps of 32 rows through three LDS stages of 24 KB, loaded two steps ahead.  (Stored through the caches: 1075 us for
+// to 430 us.  K is walked in steps of 32 rows through three LDS stages of 24 KB, loaded two steps ahead, the fragments half a step ahead (read when they are
+// wanted: updates of 100 and 203 rows 1 % slower).  (Stored through the caches: 1075 us for
 // the update in place of 972.)
 using ShortCfg = TileCfg<256, 128, 2, 2>;
 constexpr int kShortA = 32 * 512, kShortStage = kShortA + 32 * 256, kShortLds = 3 * kShortStage;
@@ -1465,7 +1466,7 @@ k_dw_short(const uint16_t* __restrict__ dZ, int blk_pitch, int64_t Vp, int64_t m
     trb[j] = lds0 + kShortA + (tg * 8 + tj) * 256 + (tq & 1) * 8 + (((wn * (C::WTN / 8) + j * 2 + (tq >> 1)) ^ (4 * tj) ^ (2 * (tg & 1))) * 16);
   typedef short short8v __attribute__((ext_vector_type(8)));
   constexpr int HA = C::MI / 2;
-  bf16x8 af[2][HA], bfr[C::NI];
+  bf16x8 af[2][HA], bfr[2][C::NI];
   auto read = [&](uint32_t addr, auto row_c) {
     short4v lo, hi;
     asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(lo) : "v"(addr));
@@ -1475,42 +1476,68 @@ k_dw_short(const uint16_t* __restrict__ dZ, int blk_pitch, int64_t Vp, int64_t m
   };
   using RowA = std::integral_constant<int, 512>;
   using RowB = std::integral_constant<int, 256>;
+  auto read_a = [&](int h, uint32_t st) {
+#pragma unroll
+    for (int i = 0; i < HA; ++i) af[h][i] = read(tra[h * HA + i] + st, RowA{});
+  };
+  auto read_b = [&](int buf, uint32_t st) {
+#pragma unroll
+    for (int j = 0; j < C::NI; ++j) bfr[buf][j] = read(trb[j] + st, RowB{});
+  };
+  auto wait_a = [&](int h) {
+#pragma unroll
+    for (int i = 0; i < HA; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(af[h][i]));
+  };
+  auto wait_b = [&](int buf) {
+#pragma unroll
+    for (int j = 0; j < C::NI; ++j) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bfr[buf][j]));
+  };
   floatx4 acc[C::MI][C::NI];
   zero_acc<C>(acc);
-  auto mfmas = [&](int h) {
+  auto mfmas = [&](int h, int buf) {
 #pragma unroll
     for (int i = 0; i < HA; ++i)
 #pragma unroll
       for (int jj = 0; jj < C::NI; ++jj) {
         const int j = i & 1 ? C::NI - 1 - jj : jj;
-        acc[h * HA + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[h][i], bfr[j], acc[h * HA + i][j], 0, 0, 0);
+        acc[h * HA + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[h][i], bfr[buf][j], acc[h * HA + i][j], 0, 0, 0);
       }
   };
-  if (nsub > 0) load(0);
-  if (nsub > 1) load(1);
-  for (int sub = 0; sub < nsub; ++sub) {
-    // this step's loads have landed, the next one's may be on their way; everybody has read the step before, whose stage is loaded again
-    if (sub + 1 < nsub) __builtin_amdgcn_s_waitcnt(0x0F70 | 6); else __builtin_amdgcn_s_waitcnt(0x0F70);
+  auto stage = [&](int sub) { return static_cast<uint32_t>(sub % 3 * kShortStage); };
+  // One step: the second half of its A fragments is read under the products of the first, the next step's B and first half under those of the
+  // second.  The barrier in between: the next step's loads have landed, and everybody has read this step's stage, which is loaded again.
+  auto step = [&](int sub, auto buf_c) {
+    constexpr int buf = decltype(buf_c)::value;
+    wait_b(buf);
+    wait_a(0);
+    read_a(1, stage(sub));
+    mfmas(0, buf);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_a(1);
+    if (sub + 1 < nsub) {
+      if (sub + 2 < nsub) __builtin_amdgcn_s_waitcnt(0x0F70 | 6); else __builtin_amdgcn_s_waitcnt(0x0F70);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      if (sub + 3 < nsub) load(sub + 3);
+      read_b(buf ^ 1, stage(sub + 1));
+      read_a(0, stage(sub + 1));
+    }
+    mfmas(1, buf);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (nsub > 0) {
+    load(0);
+    if (nsub > 1) load(1);
+    if (nsub > 2) load(2);
+    if (nsub > 2) __builtin_amdgcn_s_waitcnt(0x0F70 | 12); else if (nsub > 1) __builtin_amdgcn_s_waitcnt(0x0F70 | 6); else __builtin_amdgcn_s_waitcnt(0x0F70);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    if (sub + 2 < nsub) load(sub + 2);
-    const uint32_t st = static_cast<uint32_t>(sub % 3 * kShortStage);
-#pragma unroll
-    for (int j = 0; j < C::NI; ++j) bfr[j] = read(trb[j] + st, RowB{});
-#pragma unroll
-    for (int i = 0; i < HA; ++i) af[0][i] = read(tra[i] + st, RowA{});
-#pragma unroll
-    for (int j = 0; j < C::NI; ++j) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(bfr[j]));
-#pragma unroll
-    for (int i = 0; i < HA; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(af[0][i]));
-#pragma unroll
-    for (int i = 0; i < HA; ++i) af[1][i] = read(tra[HA + i] + st, RowA{});
-    mfmas(0);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < HA; ++i) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(af[1][i]));
-    mfmas(1);
-    __builtin_amdgcn_sched_barrier(0);
+    read_b(0, 0);
+    read_a(0, 0);
+    for (int sub = 0; sub < nsub; sub += 2) {
+      step(sub, std::integral_constant<int, 0>());
+      if (sub + 1 < nsub) step(sub + 1, std::integral_constant<int, 1>());
+    }
   }
   // the turns lie in the two stages that nobody reads any more and no load is under way to
   char* const turn = lds + (nsub + (wave == 3 ? 1 : 0)) % 3 * kShortStage + (wave == 3 ? 0 : wave) * kTurnBytes;
