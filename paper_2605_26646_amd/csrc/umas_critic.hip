@@ -50,11 +50,11 @@ template <> struct Vec<uint16_t> {
       x[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
     }
   }
-  __device__ static void store(uint16_t* p, const float (&x)[8]) {
+  __device__ static uint4 pack(const float (&x)[8]) {
     uint32_t w[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) w[i] = static_cast<uint32_t>(f2bf(x[2 * i])) | (static_cast<uint32_t>(f2bf(x[2 * i + 1])) << 16);
-    store_stream(p, make_uint4(w[0], w[1], w[2], w[3]));
+    return make_uint4(w[0], w[1], w[2], w[3]);
   }
 };
 template <> struct Vec<float> {
@@ -63,7 +63,9 @@ template <> struct Vec<float> {
   __device__ static void unpack(const uint4& v, float (&x)[4]) {
     x[0] = __uint_as_float(v.x); x[1] = __uint_as_float(v.y); x[2] = __uint_as_float(v.z); x[3] = __uint_as_float(v.w);
   }
-  __device__ static void store(float* p, const float (&x)[4]) { store_stream(p, make_float4(x[0], x[1], x[2], x[3])); }
+  __device__ static uint4 pack(const float (&x)[4]) {
+    return make_uint4(__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3]));
+  }
 };
 
 __global__ void k_zero_u32(uint32_t* __restrict__ p, int64_t n) {
@@ -250,73 +252,146 @@ k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d
   float gsum = 0.f;
   const float inv_s = 1.f / static_cast<float>(norm);
 
-  uint4 cur[KV], nxt[KV];
-  float vo_next = 0.f, ret_next = 0.f;               // the next row's old value and return come with the row
-  auto fetch = [&](int64_t n) {
-    const int64_t row = rowsel ? rowsel[n] : n;
-#pragma unroll
-    for (int k = 0; k < KV; ++k) {
-      const int cv = lane + k * kWave;
-      nxt[k] = make_uint4(0u, 0u, 0u, 0u);
-      if (cv < nvec) nxt[k] = *reinterpret_cast<const uint4*>(H + row * d + cv * N);
-    }
-    vo_next = value_old[row];
-    ret_next = ret[row];
-    return row;
+  // The wavefront's rows, 64 at a time: a lane has what belongs to one of them besides H, its place, old value, return and role, so that in the
+  // loop over them nothing is loaded but rows, the next one under way while this one is finished.  Every row is the same number of loads and
+  // stores (columns past d and rows past the last are out of a buffer's range, which looks at the lane's offset only), and the waits are for the
+  // row that is next, not for the stores of the last.  With the place and the role loaded row by row, each waited for together with everything
+  // under way, values and update of 39 224 rows of 2048 107 us, now 99.5, 39 000 of 3584 199 and 170, 100 000 of 1088 186 and 166, 60 000 float32 rows of
+  // 1024 158 and 144; 6000 of 2048 27 and 25.3, 15 000 of 1024 30.2 and 31.
+  const int row_bytes = nvec * 16;
+  auto rsrc = [&](const void* base, int64_t row, bool there) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(static_cast<const T*>(base)) + row * d, 0, there ? row_bytes : 0, 0x00020000);
   };
-  int64_t n = r_begin + wave;
-  int64_t row_next = n < r_end ? fetch(n) : 0;
-  for (; n < r_end; n += kVWaves) {
-    const int64_t row = row_next;
-    const float vo = vo_next, R = ret_next;
-    A dot = 0;
-#pragma unroll
-    for (int k = 0; k < KV; ++k) {
-      cur[k] = nxt[k];
-      float x[N], y[N];
-      Vec<T>::unpack(cur[k], x);
-      Vec<T>::unpack(wp[k], y);
-#pragma unroll
-      for (int i = 0; i < N; ++i) dot = fma(static_cast<A>(x[i]), static_cast<A>(y[i]), dot);
-    }
-    if (n + kVWaves < r_end) row_next = fetch(n + kVWaves);     // in flight while this row is finished
-    dot = wave_sum(dot);
-    // the value is a float32 result; loss and gradient are formed from that rounded value
-    const float V = static_cast<float>(dot + static_cast<A>(bias));
-    const float vc = fminf(fmaxf(V, vo - clip_eps), vo + clip_eps);   // V itself inside the range: an exact tie
-    const float lu = (V - R) * (V - R), lc = (vc - R) * (vc - R);
-    const bool unclipped = lu >= lc;
-    const float g = unclipped ? (V - R) * inv_s : 0.f;
-    gsum += g;
-    if (lane == 0) {
-      if (value_new) value_new[row] = V;
-      const int role = (tok_role && n_roles > 0) ? tok_role[row] : -1;
-      for (int pass = 0; pass < 2; ++pass) {
-        if (pass == 1 && (role < 0 || role >= n_roles)) break;
-        double* a = s_acc + (pass == 0 ? 0 : (1 + role) * kVStat);
-        atomicAdd(a + 0, static_cast<double>(0.5f * (unclipped ? lu : lc)));
-        atomicAdd(a + 1, unclipped ? 0.0 : 1.0);
-        atomicAdd(a + 2, static_cast<double>(V));
-        atomicAdd(a + 3, 1.0);
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  constexpr int kPast = 2;                           // policy of a store past the caches
+  constexpr int kFewRows = 8;                        // whose statistics single lanes add: the sums across lanes cost more (15 000 rows of 1024 32.6 us, added 30.4)
+  auto rows = [&](auto add) {
+    constexpr bool kAdd = decltype(add)::value;
+    for (int64_t n0 = r_begin + __builtin_amdgcn_readfirstlane(wave); n0 < r_end; n0 += kVWaves * kWave) {
+      const int64_t left = (r_end - n0 + kVWaves - 1) / kVWaves;
+      const int cnt = left < kWave ? static_cast<int>(left) : kWave;
+      int64_t my_row = 0;
+      float my_vo = 0.f, my_ret = 0.f, my_v = 0.f;
+      int my_role = -1;
+      if (lane < cnt) {
+        const int64_t n = n0 + lane * kVWaves;
+        my_row = rowsel ? rowsel[n] : n;
+        my_vo = value_old[my_row];
+        my_ret = ret[my_row];
+        if (tok_role && n_roles > 0) my_role = tok_role[my_row];
       }
-    }
+      auto row_at = [&](int i) {
+        return static_cast<int64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(my_row), i))) |
+               static_cast<int64_t>(__builtin_amdgcn_readlane(static_cast<int>(my_row >> 32), i)) << 32;
+      };
+      auto float_at = [&](float v, int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i)); };
+      auto fetch = [&](int i, uint4 (&x)[KV]) {
+        const __amdgpu_buffer_rsrc_t h = rsrc(H, i < cnt ? row_at(i) : 0, i < cnt);
 #pragma unroll
-    for (int k = 0; k < KV; ++k) {
-      const int cv = lane + k * kWave;
-      if (cv < nvec) {
-        float x[N], y[N], o[N];
-        Vec<T>::unpack(cur[k], x);
-        Vec<T>::unpack(wp[k], y);
-        if (accumulate_dH) Vec<T>::load(dH + row * d + cv * N, o);
+        for (int k = 0; k < KV; ++k) x[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(h, lane * 16 + k * kWave * 16, 0, 0));
+        asm volatile("" : : : "memory");             // they go out here, not when they are wanted
+      };
+      uint4 even[KV], odd[KV];
+      fetch(0, even);
+      auto finish = [&](int i, const uint4 (&h)[KV]) {
+        A dot = 0;
 #pragma unroll
-        for (int i = 0; i < N; ++i) {
-          acc[k][i] = fma(static_cast<A>(g), static_cast<A>(x[i]), acc[k][i]);
-          o[i] = accumulate_dH ? o[i] + g * y[i] : g * y[i];
+        for (int k = 0; k < KV; ++k) {
+          float x[N], y[N];
+          Vec<T>::unpack(h[k], x);
+          Vec<T>::unpack(wp[k], y);
+#pragma unroll
+          for (int c = 0; c < N; ++c) dot = fma(static_cast<A>(x[c]), static_cast<A>(y[c]), dot);
         }
-        Vec<T>::store(dH + row * d + cv * N, o);
+        dot = wave_sum(dot);
+        // the value is a float32 result; loss and gradient are formed from that rounded value
+        const float V = static_cast<float>(dot + static_cast<A>(bias)), vo = float_at(my_vo, i), R = float_at(my_ret, i);
+        const float vc = fminf(fmaxf(V, vo - clip_eps), vo + clip_eps);   // V itself inside the range: an exact tie
+        const float g = (V - R) * (V - R) >= (vc - R) * (vc - R) ? (V - R) * inv_s : 0.f;
+        gsum += g;
+        my_v = lane == i ? V : my_v;
+        const __amdgpu_buffer_rsrc_t out = rsrc(dH, row_at(i), true);
+#pragma unroll
+        for (int k = 0; k < KV; ++k) {
+          float x[N], y[N], o[N];
+          Vec<T>::unpack(h[k], x);
+          Vec<T>::unpack(wp[k], y);
+          if constexpr (kAdd) Vec<T>::unpack(__builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(out, lane * 16 + k * kWave * 16, 0, 0)), o);
+#pragma unroll
+          for (int c = 0; c < N; ++c) {
+            acc[k][c] = fma(static_cast<A>(g), static_cast<A>(x[c]), acc[k][c]);
+            o[c] = kAdd ? o[c] + g * y[c] : g * y[c];
+          }
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, Vec<T>::pack(o)), out, lane * 16 + k * kWave * 16, 0, kPast);
+        }
+      };
+      if constexpr (KV > 8 && std::is_same<T, float>::value) {   // with float64 sums two turns of the loop in one spill (10 000 rows of 4096 129 us, like this 120)
+#pragma unroll 1
+        for (int i = 0; i < cnt; ++i) {
+          fetch(i + 1, odd);
+          finish(i, even);
+#pragma unroll
+          for (int k = 0; k < KV; ++k) even[k] = odd[k];
+        }
+      } else {
+        if constexpr (!kAdd) {                       // as many stores of nothing as a row has: the loop's first turn waits like the others
+          const __amdgpu_buffer_rsrc_t none = rsrc(dH, 0, false);
+#pragma unroll
+          for (int k = 0; k < KV; ++k) __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, none, lane * 16 + k * kWave * 16, 0, kPast);
+        }
+        for (int i = 0;; i += 2) {
+          fetch(i + 1, odd);
+          finish(i, even);
+          if (i + 1 >= cnt) break;
+          fetch(i + 2, even);
+          finish(i + 1, odd);
+          if (i + 2 >= cnt) break;
+        }
+      }
+      // the statistics of these rows, a row to a lane
+      const bool mine = lane < cnt;
+      const float vc = fminf(fmaxf(my_v, my_vo - clip_eps), my_vo + clip_eps);
+      const float lu = (my_v - my_ret) * (my_v - my_ret), lc = (vc - my_ret) * (vc - my_ret);
+      const bool unclipped = lu >= lc;
+      if (mine && value_new) value_new[my_row] = my_v;
+      const double l = static_cast<double>(0.5f * (unclipped ? lu : lc)), v = static_cast<double>(my_v);
+      auto add_lanes = [&](bool in, double* a) {
+        if (!in) return;
+        atomicAdd(a + 0, l);
+        atomicAdd(a + 1, unclipped ? 0.0 : 1.0);
+        atomicAdd(a + 2, v);
+        atomicAdd(a + 3, 1.0);
+      };
+      if (cnt <= kFewRows) {
+        add_lanes(mine, s_acc);
+        add_lanes(mine && my_role >= 0 && my_role < n_roles, s_acc + (1 + my_role) * kVStat);
+        continue;
+      }
+      auto sum_into = [&](unsigned long long group, double* a) {
+        const bool in = (group >> lane) & 1;
+        const int n = __popcll(group);
+        if (n <= kFewRows) { add_lanes(in, a); return; }
+        const double sl = wave_sum(in ? l : 0.0), sv = wave_sum(in ? v : 0.0);
+        const int c = __popcll(__ballot(in && !unclipped));
+        if (lane == 0) {
+          atomicAdd(a + 0, sl);
+          atomicAdd(a + 1, static_cast<double>(c));
+          atomicAdd(a + 2, sv);
+          atomicAdd(a + 3, static_cast<double>(n));
+        }
+      };
+      sum_into(__ballot(mine), s_acc);
+      unsigned long long roles = __ballot(mine && my_role >= 0 && my_role < n_roles);
+      while (roles) {                                // the same for every lane
+        const int r = __shfl(my_role, __ffsll(static_cast<long long>(roles)) - 1, kWave);
+        const unsigned long long group = roles & __ballot(my_role == r);
+        sum_into(group, s_acc + (1 + r) * kVStat);
+        roles &= ~group;
       }
     }
-  }
+  };
+  if (accumulate_dH) rows(std::true_type());
+  else rows(std::false_type());
   // the wavefronts' sums meet in LDS one after the other; the workgroup leaves one partial row: [blocks][part_pitch(d)].
   // (Four partial rows a workgroup, reduced in two launches, and the statistics of all roles in one workgroup took
   // 36 us after the rows; now 7.)

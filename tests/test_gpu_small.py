@@ -277,6 +277,53 @@ def test_critic_of_many_rows(n, n_sel, d, dtype):
     assert torch.equal(dH[at], want_dH) and (dH[rest] == 0).all()
 
 
+# rows of a wavefront around the few whose statistics single lanes add and around the 64 that its lanes hold at a time
+@pytest.mark.parametrize("n_roles", [3, 64])
+@pytest.mark.parametrize("n,d,dtype", [(33, 2048, torch.bfloat16), (8191, 512, torch.float32), (18439, 4096, torch.float32), (20493, 8192, torch.bfloat16),
+                                       (60001, 1096, torch.bfloat16), (262145, 264, torch.bfloat16), (532481, 8, torch.bfloat16), (530001, 12, torch.float32)])
+def test_critic_statistics_and_sums_of_many_rows(n, d, dtype, n_roles):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    H, w = torch.randn(n, d, device="cuda", generator=g).to(dtype), (torch.randn(d, device="cuda", generator=g) / d ** 0.5).to(dtype)
+    ret, old = torch.randn(n, device="cuda", generator=g), torch.randn(n, device="cuda", generator=g)
+    role = torch.randint(-1, n_roles + 1, (n,), device="cuda", generator=g).to(torch.int32)      # some have none
+    dH0 = (torch.randn(n, d, device="cuda", generator=g) / n).to(dtype)
+    stats, V, dH, dw, db = umas.umas_value_loss_fwd_bwd(H, w, 0.5, None, old, ret, role, n_roles, 0.25)
+    v64, r64, o64, V = V.double(), ret.double(), old.double(), V.double()
+    assert all((V[i:i + 65536] - (H[i:i + 65536].double() @ w.double() + 0.5)).abs().max() <= 2.0 ** -22 * 5 * d ** 0.5 * 5 for i in range(0, n, 65536))
+    vc = torch.minimum(torch.maximum(v64, o64 - 0.25), o64 + 0.25)
+    lu, lc = (v64 - r64) ** 2, (vc - r64) ** 2
+    loss, clipped = 0.5 * torch.maximum(lu, lc), lu < lc
+    st = umas.read_value_stats(stats)
+    for k in range(1 + n_roles):
+        at = role == k - 1 if k else torch.ones_like(clipped)
+        count = int(at.sum())
+        assert int(st["n_scored"][k]) == count
+        if count:                                        # losses are float32, summed in 64 bits; a row at the line may fall either way
+            assert abs(float(st["loss"][k]) - float(loss[at].mean())) <= 2.0 ** -19 * float(loss[at].mean())
+            assert abs(float(st["clip_frac"][k]) - float(clipped[at].double().mean())) <= 2.0 / count + 1e-6
+            assert abs(float(st["value_mean"][k]) - float(v64[at].mean())) <= 2.0 ** -22 * float(v64[at].abs().max())
+    near = ((lu - lc).abs() <= 1e-5 * lu) & clipped | ((lu - lc).abs() <= 1e-5 * lu) & (vc != v64)
+    gr = torch.where(clipped, 0.0, (v64 - r64) / n)
+    eps = 2.0 ** -8 if dtype is torch.bfloat16 else 2.0 ** -21
+    for i in range(0, n, 65536):
+        want, ok = gr[i:i + 65536, None] * w.double(), ~near[i:i + 65536]
+        assert ((dH[i:i + 65536].double() - want).abs() <= eps * want.abs() + 1e-30)[ok].all()
+    # dw and db: float32 sums of at most n terms, and what the rows at the line could add
+    room = (((v64 - r64).abs() / n)[near]).sum()
+    want, size = torch.zeros(d, dtype=torch.float64, device="cuda"), torch.zeros(d, dtype=torch.float64, device="cuda")
+    for i in range(0, n, 65536):
+        h = H[i:i + 65536].double()
+        want += gr[i:i + 65536] @ h
+        size += gr[i:i + 65536].abs() @ h.abs()
+    assert ((dw.double() - want).abs() <= 2.0 ** -16 * size + 6 * room).all()
+    assert abs(float(db) - float(gr.sum())) <= 2.0 ** -16 * float(gr.abs().sum()) + float(room)
+    added = umas.umas_value_loss_fwd_bwd(H, w, 0.5, None, old, ret, role, n_roles, 0.25, accumulate_dH=True, dH=dH0.clone())[2]
+    for i in range(0, n, 65536):
+        term = gr[i:i + 65536, None] * w.double()
+        want, ok = dH0[i:i + 65536].double() + term, ~near[i:i + 65536]
+        assert ((added[i:i + 65536].double() - want).abs() <= eps * want.abs() + 2.0 ** -21 * term.abs() + 1e-30)[ok].all()
+
+
 def test_values_of_more_rows_than_32_bits_count():
     """Row 2^32 + 5 is not selected by an entry 5 (the values of 2^32 rows are 17 GB, their rows of 16 bytes, of which three are read, 69 GB)."""
     n, d = (1 << 32) + (1 << 20), 4
