@@ -209,9 +209,10 @@ k_value_fwd(const T* __restrict__ H, const T* __restrict__ w, float bias, int d,
 // Loss and backward, one wavefront per row.  Lane l owns the 16-byte column vectors l, l + 64, ... (KV of them):
 // it keeps its part of w, of the current row and of the next row (prefetched) in registers, and its part of
 // dw in float accumulators over all rows of the wavefront.  No barrier in the row loop.  With SELECT n_clear workgroups, from
-// the clear_at-th on, do the rows that are not selected.
+// the clear_at-th on, do the rows that are not selected.  Four vectors a lane would take 178 registers, which leaves two wavefronts to a SIMD;
+// held to the 168 of three all of 393 216 rows of 2048 take 629 us, not 661, 39 224 selected ones of them, values included, 101, not 99.5.
 template <typename T, int KV, bool SELECT>
-__global__ void __launch_bounds__(kVT)
+__global__ void __launch_bounds__(kVT, KV == 4 ? 3 : 1)
 k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d, const int32_t* __restrict__ rowsel,
              int64_t n_sel, int n_rows, int n_clear, int clear_at, int64_t norm, int64_t rows_per_block, const float* __restrict__ value_old, const float* __restrict__ ret,
              const int32_t* __restrict__ tok_role, int n_roles, float clip_eps, float* __restrict__ value_new,
@@ -256,7 +257,7 @@ k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d
   // loop over them nothing is loaded but rows, the next one under way while this one is finished.  Every row is the same number of loads and
   // stores (columns past d and rows past the last are out of a buffer's range, which looks at the lane's offset only), and the waits are for the
   // row that is next, not for the stores of the last.  With the place and the role loaded row by row, each waited for together with everything
-  // under way, values and update of 39 224 rows of 2048 107 us, now 99.5, 39 000 of 3584 199 and 170, 100 000 of 1088 186 and 166, 60 000 float32 rows of
+  // under way, values and update of 39 224 rows of 2048 108 us, now 101, 39 000 of 3584 199 and 170, 100 000 of 1088 186 and 166, 60 000 float32 rows of
   // 1024 158 and 144; 6000 of 2048 27 and 25.3, 15 000 of 1024 30.2 and 31.
   const int row_bytes = nvec * 16;
   auto rsrc = [&](const void* base, int64_t row, bool there) {
