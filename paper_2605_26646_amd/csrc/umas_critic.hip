@@ -206,17 +206,25 @@ k_value_fwd(const T* __restrict__ H, const T* __restrict__ w, float bias, int d,
   if (lane == 0) value[row] = static_cast<float>(acc + static_cast<AccT<T>>(bias));
 }
 
+__device__ __forceinline__ void add_stats(double* a, double loss, double clipped, double v, double rows) {
+  atomicAdd(a + 0, loss);
+  atomicAdd(a + 1, clipped);
+  atomicAdd(a + 2, v);
+  atomicAdd(a + 3, rows);
+}
 // Loss and backward, one wavefront per row.  Lane l owns the 16-byte column vectors l, l + 64, ... (KV of them):
 // it keeps its part of w, of the current row and of the next row (prefetched) in registers, and its part of
 // dw in float accumulators over all rows of the wavefront.  No barrier in the row loop.  With SELECT n_clear workgroups, from
-// the clear_at-th on, do the rows that are not selected.  Four vectors a lane would take 178 registers, which leaves two wavefronts to a SIMD;
-// held to the 168 of three all of 393 216 rows of 2048 take 629 us, not 661, 39 224 selected ones of them, values included, 101, not 99.5.
-template <typename T, int KV, bool SELECT>
-__global__ void __launch_bounds__(kVT, KV == 4 ? 3 : 1)
+// the clear_at-th on, do the rows that are not selected.  With ADD dH is added to, in a kernel of its own: both loops in one share a register
+// budget (up to 860 bytes of scratch a lane, 10 000 rows of 8192 174 us, added to 246; apart and with the statistics below 125 and 170).  Four
+// bf16 vectors a lane are held to the 168 registers of three wavefronts to a SIMD; float ones, with float64 sums, spill there (250 000 rows of
+// 1024 650 us, not held 643).
+template <typename T, int KV, bool SELECT, bool ADD>
+__global__ void __launch_bounds__(kVT, KV == 4 && sizeof(T) == 2 ? 3 : 1)
 k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d, const int32_t* __restrict__ rowsel,
              int64_t n_sel, int n_rows, int n_clear, int clear_at, int64_t norm, int64_t rows_per_block, const float* __restrict__ value_old, const float* __restrict__ ret,
              const int32_t* __restrict__ tok_role, int n_roles, float clip_eps, float* __restrict__ value_new,
-             T* __restrict__ dH, int accumulate_dH, float* __restrict__ part_dw, double* __restrict__ blk_stats) {
+             T* __restrict__ dH, float* __restrict__ part_dw, double* __restrict__ blk_stats) {
   __shared__ double s_acc[(1 + UMAS_MAX_ROLES) * kVStat];
   __shared__ float s_g[kVWaves];
   extern __shared__ __attribute__((aligned(16))) char s_raw[];
@@ -229,7 +237,7 @@ k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d
     const int c = static_cast<int>(blockIdx.x) - clear_at;
     if (c >= 0 && c < n_clear) {
       __shared__ uint32_t s_map[kMapRows / 32];
-      unselected_rows(c, n_clear, n_rows, rowsel, n_sel, s_map, ClearRows<T>{value_new, accumulate_dH ? nullptr : dH, nvec});
+      unselected_rows(c, n_clear, n_rows, rowsel, n_sel, s_map, ClearRows<T>{value_new, ADD ? nullptr : dH, nvec});
       return;
     }
   }
@@ -257,142 +265,116 @@ k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d
   // loop over them nothing is loaded but rows, the next one under way while this one is finished.  Every row is the same number of loads and
   // stores (columns past d and rows past the last are out of a buffer's range, which looks at the lane's offset only), and the waits are for the
   // row that is next, not for the stores of the last.  With the place and the role loaded row by row, each waited for together with everything
-  // under way, values and update of 39 224 rows of 2048 108 us, now 101, 39 000 of 3584 199 and 170, 100 000 of 1088 186 and 166, 60 000 float32 rows of
-  // 1024 158 and 144; 6000 of 2048 27 and 25.3, 15 000 of 1024 30.2 and 31.
+  // under way, values and update of 39 224 rows of 2048 108 us, now 97, 60 000 of 2560 247 and 184, 100 000 of 1088 186 and 157, 60 000 float32 rows of
+  // 1024 159 and 146, 190 000 of 4032 1890 and 1892.
   const int row_bytes = nvec * 16;
   auto rsrc = [&](const void* base, int64_t row, bool there) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(static_cast<const T*>(base)) + row * d, 0, there ? row_bytes : 0, 0x00020000);
   };
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   constexpr int kPast = 2;                           // policy of a store past the caches
-  constexpr int kFewRows = 8;                        // whose statistics single lanes add: the sums across lanes cost more (15 000 rows of 1024 32.6 us, added 30.4)
-  auto rows = [&](auto add) {
-    constexpr bool kAdd = decltype(add)::value;
-    for (int64_t n0 = r_begin + __builtin_amdgcn_readfirstlane(wave); n0 < r_end; n0 += kVWaves * kWave) {
-      const int64_t left = (r_end - n0 + kVWaves - 1) / kVWaves;
-      const int cnt = left < kWave ? static_cast<int>(left) : kWave;
-      int64_t my_row = 0;
-      float my_vo = 0.f, my_ret = 0.f, my_v = 0.f;
-      int my_role = -1;
-      if (lane < cnt) {
-        const int64_t n = n0 + lane * kVWaves;
-        my_row = rowsel ? rowsel[n] : n;
-        my_vo = value_old[my_row];
-        my_ret = ret[my_row];
-        if (tok_role && n_roles > 0) my_role = tok_role[my_row];
-      }
-      auto row_at = [&](int i) {
-        return static_cast<int64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(my_row), i))) |
-               static_cast<int64_t>(__builtin_amdgcn_readlane(static_cast<int>(my_row >> 32), i)) << 32;
-      };
-      auto float_at = [&](float v, int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i)); };
-      auto fetch = [&](int i, uint4 (&x)[KV]) {
-        const __amdgpu_buffer_rsrc_t h = rsrc(H, i < cnt ? row_at(i) : 0, i < cnt);
-#pragma unroll
-        for (int k = 0; k < KV; ++k) x[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(h, lane * 16 + k * kWave * 16, 0, 0));
-        asm volatile("" : : : "memory");             // they go out here, not when they are wanted
-      };
-      uint4 even[KV], odd[KV];
-      fetch(0, even);
-      auto finish = [&](int i, const uint4 (&h)[KV]) {
-        A dot = 0;
-#pragma unroll
-        for (int k = 0; k < KV; ++k) {
-          float x[N], y[N];
-          Vec<T>::unpack(h[k], x);
-          Vec<T>::unpack(wp[k], y);
-#pragma unroll
-          for (int c = 0; c < N; ++c) dot = fma(static_cast<A>(x[c]), static_cast<A>(y[c]), dot);
-        }
-        dot = wave_sum(dot);
-        // the value is a float32 result; loss and gradient are formed from that rounded value
-        const float V = static_cast<float>(dot + static_cast<A>(bias)), vo = float_at(my_vo, i), R = float_at(my_ret, i);
-        const float vc = fminf(fmaxf(V, vo - clip_eps), vo + clip_eps);   // V itself inside the range: an exact tie
-        const float g = (V - R) * (V - R) >= (vc - R) * (vc - R) ? (V - R) * inv_s : 0.f;
-        gsum += g;
-        my_v = lane == i ? V : my_v;
-        const __amdgpu_buffer_rsrc_t out = rsrc(dH, row_at(i), true);
-#pragma unroll
-        for (int k = 0; k < KV; ++k) {
-          float x[N], y[N], o[N];
-          Vec<T>::unpack(h[k], x);
-          Vec<T>::unpack(wp[k], y);
-          if constexpr (kAdd) Vec<T>::unpack(__builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(out, lane * 16 + k * kWave * 16, 0, 0)), o);
-#pragma unroll
-          for (int c = 0; c < N; ++c) {
-            acc[k][c] = fma(static_cast<A>(g), static_cast<A>(x[c]), acc[k][c]);
-            o[c] = kAdd ? o[c] + g * y[c] : g * y[c];
-          }
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, Vec<T>::pack(o)), out, lane * 16 + k * kWave * 16, 0, kPast);
-        }
-      };
-      if constexpr (KV > 8 && std::is_same<T, float>::value) {   // with float64 sums two turns of the loop in one spill (10 000 rows of 4096 129 us, like this 120)
-#pragma unroll 1
-        for (int i = 0; i < cnt; ++i) {
-          fetch(i + 1, odd);
-          finish(i, even);
-#pragma unroll
-          for (int k = 0; k < KV; ++k) even[k] = odd[k];
-        }
-      } else {
-        if constexpr (!kAdd) {                       // as many stores of nothing as a row has: the loop's first turn waits like the others
-          const __amdgpu_buffer_rsrc_t none = rsrc(dH, 0, false);
-#pragma unroll
-          for (int k = 0; k < KV; ++k) __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, none, lane * 16 + k * kWave * 16, 0, kPast);
-        }
-        for (int i = 0;; i += 2) {
-          fetch(i + 1, odd);
-          finish(i, even);
-          if (i + 1 >= cnt) break;
-          fetch(i + 2, even);
-          finish(i + 1, odd);
-          if (i + 2 >= cnt) break;
-        }
-      }
-      // the statistics of these rows, a row to a lane
-      const bool mine = lane < cnt;
-      const float vc = fminf(fmaxf(my_v, my_vo - clip_eps), my_vo + clip_eps);
-      const float lu = (my_v - my_ret) * (my_v - my_ret), lc = (vc - my_ret) * (vc - my_ret);
-      const bool unclipped = lu >= lc;
-      if (mine && value_new) value_new[my_row] = my_v;
-      const double l = static_cast<double>(0.5f * (unclipped ? lu : lc)), v = static_cast<double>(my_v);
-      auto add_lanes = [&](bool in, double* a) {
-        if (!in) return;
-        atomicAdd(a + 0, l);
-        atomicAdd(a + 1, unclipped ? 0.0 : 1.0);
-        atomicAdd(a + 2, v);
-        atomicAdd(a + 3, 1.0);
-      };
-      if (cnt <= kFewRows) {
-        add_lanes(mine, s_acc);
-        add_lanes(mine && my_role >= 0 && my_role < n_roles, s_acc + (1 + my_role) * kVStat);
-        continue;
-      }
-      auto sum_into = [&](unsigned long long group, double* a) {
-        const bool in = (group >> lane) & 1;
-        const int n = __popcll(group);
-        if (n <= kFewRows) { add_lanes(in, a); return; }
-        const double sl = wave_sum(in ? l : 0.0), sv = wave_sum(in ? v : 0.0);
-        const int c = __popcll(__ballot(in && !unclipped));
-        if (lane == 0) {
-          atomicAdd(a + 0, sl);
-          atomicAdd(a + 1, static_cast<double>(c));
-          atomicAdd(a + 2, sv);
-          atomicAdd(a + 3, static_cast<double>(n));
-        }
-      };
-      sum_into(__ballot(mine), s_acc);
-      unsigned long long roles = __ballot(mine && my_role >= 0 && my_role < n_roles);
-      while (roles) {                                // the same for every lane
-        const int r = __shfl(my_role, __ffsll(static_cast<long long>(roles)) - 1, kWave);
-        const unsigned long long group = roles & __ballot(my_role == r);
-        sum_into(group, s_acc + (1 + r) * kVStat);
-        roles &= ~group;
+  // Statistics of the wavefront's rows of role `lane`, of those without a role in lane n_roles (if 64 roles leave a lane), as the rows are finished;
+  // kept for 64 rows and added up across lanes behind them they took the registers that sixteen vectors spilled.
+  double sum_l = 0.0, sum_v = 0.0;
+  unsigned n_in = 0, n_clipped = 0;
+  for (int64_t n0 = r_begin + __builtin_amdgcn_readfirstlane(wave); n0 < r_end; n0 += kVWaves * kWave) {
+    const int64_t left = (r_end - n0 + kVWaves - 1) / kVWaves;
+    const int cnt = left < kWave ? static_cast<int>(left) : kWave;
+    int64_t my_row = 0;
+    float my_vo = 0.f, my_ret = 0.f, my_v = 0.f;
+    int my_slot = n_roles;
+    if (lane < cnt) {
+      const int64_t n = n0 + lane * kVWaves;
+      my_row = rowsel ? rowsel[n] : n;
+      my_vo = value_old[my_row];
+      my_ret = ret[my_row];
+      if (tok_role && n_roles > 0) {
+        const int role = tok_role[my_row];
+        my_slot = role >= 0 && role < n_roles ? role : n_roles;
       }
     }
-  };
-  if (accumulate_dH) rows(std::true_type());
-  else rows(std::false_type());
+    auto row_at = [&](int i) {
+      return static_cast<int64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(my_row), i))) |
+             static_cast<int64_t>(__builtin_amdgcn_readlane(static_cast<int>(my_row >> 32), i)) << 32;
+    };
+    auto float_at = [&](float v, int i) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i)); };
+    auto fetch = [&](int i, uint4 (&x)[KV]) {
+      const __amdgpu_buffer_rsrc_t h = rsrc(H, i < cnt ? row_at(i) : 0, i < cnt);
+#pragma unroll
+      for (int k = 0; k < KV; ++k) x[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(h, lane * 16 + k * kWave * 16, 0, 0));
+      asm volatile("" : : : "memory");             // they go out here, not when they are wanted
+    };
+    uint4 even[KV], odd[KV];
+    fetch(0, even);
+    auto finish = [&](int i, const uint4 (&h)[KV]) {
+      A dot = 0;
+#pragma unroll
+      for (int k = 0; k < KV; ++k) {
+        float x[N], y[N];
+        Vec<T>::unpack(h[k], x);
+        Vec<T>::unpack(wp[k], y);
+#pragma unroll
+        for (int c = 0; c < N; ++c) dot = fma(static_cast<A>(x[c]), static_cast<A>(y[c]), dot);
+      }
+      dot = wave_sum(dot);
+      // the value is a float32 result; loss and gradient are formed from that rounded value
+      const float V = static_cast<float>(dot + static_cast<A>(bias)), vo = float_at(my_vo, i), R = float_at(my_ret, i);
+      const float vc = fminf(fmaxf(V, vo - clip_eps), vo + clip_eps);   // V itself inside the range: an exact tie
+      const float lu = (V - R) * (V - R), lc = (vc - R) * (vc - R);
+      const bool unclipped = lu >= lc;
+      const float g = unclipped ? (V - R) * inv_s : 0.f;
+      gsum += g;
+      my_v = lane == i ? V : my_v;
+      const int slot = __builtin_amdgcn_readlane(my_slot, i);
+      const float loss = 0.5f * (unclipped ? lu : lc);
+      if (slot == lane) {
+        sum_l += static_cast<double>(loss);
+        sum_v += static_cast<double>(V);
+        ++n_in;
+        n_clipped += unclipped ? 0u : 1u;
+      }
+      if (slot == kWave && lane == 0) add_stats(s_acc, static_cast<double>(loss), unclipped ? 0.0 : 1.0, static_cast<double>(V), 1.0);
+      const __amdgpu_buffer_rsrc_t out = rsrc(dH, row_at(i), true);
+#pragma unroll
+      for (int k = 0; k < KV; ++k) {
+        float x[N], y[N], o[N];
+        Vec<T>::unpack(h[k], x);
+        Vec<T>::unpack(wp[k], y);
+        if constexpr (ADD) Vec<T>::unpack(__builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(out, lane * 16 + k * kWave * 16, 0, 0)), o);
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+          acc[k][c] = fma(static_cast<A>(g), static_cast<A>(x[c]), acc[k][c]);
+          o[c] = ADD ? o[c] + g * y[c] : g * y[c];
+        }
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, Vec<T>::pack(o)), out, lane * 16 + k * kWave * 16, 0, kPast);
+      }
+    };
+    if constexpr (KV > 8 && std::is_same<T, float>::value) {   // with float64 sums two turns of the loop in one spill (10 000 rows of 4096 129 us, like this 120)
+#pragma unroll 1
+      for (int i = 0; i < cnt; ++i) {
+        fetch(i + 1, odd);
+        finish(i, even);
+#pragma unroll
+        for (int k = 0; k < KV; ++k) even[k] = odd[k];
+      }
+    } else {
+      if constexpr (!ADD) {                       // as many stores of nothing as a row has: the loop's first turn waits like the others
+        const __amdgpu_buffer_rsrc_t none = rsrc(dH, 0, false);
+#pragma unroll
+        for (int k = 0; k < KV; ++k) __builtin_amdgcn_raw_buffer_store_b128(u32x4{0u, 0u, 0u, 0u}, none, lane * 16 + k * kWave * 16, 0, kPast);
+      }
+      for (int i = 0;; i += 2) {
+        fetch(i + 1, odd);
+        finish(i, even);
+        if (i + 1 >= cnt) break;
+        fetch(i + 2, even);
+        finish(i + 1, odd);
+        if (i + 2 >= cnt) break;
+      }
+    }
+    if (lane < cnt && value_new) value_new[my_row] = my_v;
+  }
+  if (n_in) add_stats(s_acc + (lane < n_roles ? 1 + lane : 0) * kVStat, sum_l, static_cast<double>(n_clipped), sum_v, static_cast<double>(n_in));
   // the wavefronts' sums meet in LDS one after the other; the workgroup leaves one partial row: [blocks][part_pitch(d)].
   // (Four partial rows a workgroup, reduced in two launches, and the statistics of all roles in one workgroup took
   // 36 us after the rows; now 7.)
@@ -412,7 +394,12 @@ k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d
   float* pd = part_dw + static_cast<size_t>(blk) * part_pitch(d);
   for (int j = threadIdx.x; j < d; j += kVT) pd[j] = static_cast<float>(s_dw[j]);
   if (threadIdx.x == 0) pd[d] = (s_g[0] + s_g[1]) + (s_g[2] + s_g[3]);
-  for (int i = threadIdx.x; i < nacc; i += kVT) blk_stats[static_cast<size_t>(blk) * nacc + i] = s_acc[i];
+  for (int i = threadIdx.x; i < nacc; i += kVT) {
+    double x = s_acc[i];
+    if (i < kVStat)                                  // all rows: those without a role and every role's
+      for (int r = 1; r <= n_roles; ++r) x += s_acc[r * kVStat + i];
+    blk_stats[static_cast<size_t>(blk) * nacc + i] = x;
+  }
 }
 
 // What the workgroups of the row kernel left, added up in a fixed order.  The first col_blocks workgroups take 16 columns
@@ -473,7 +460,7 @@ int max_d(umas_dtype dt) { return dt == UMAS_BF16 ? kWave * kMaxKV * 8 : kWave *
 
 // Workgroups of the row kernel that the device holds at once (the kernel's register use differs with KV): its grid is
 // one resident round, so that no second, partly filled round follows.  Looked up once per instance.
-template <typename T, int K>
+template <typename T, int K, bool ADD>
 unsigned resident_value_blocks() {
   static unsigned cached = 0;
   if (cached) return cached;
@@ -481,29 +468,29 @@ unsigned resident_value_blocks() {
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n_cu < 1)
     n_cu = 64;
   constexpr size_t kLds = static_cast<size_t>(K) * kWave * Vec<T>::N * sizeof(AccT<T>);   // the widest rows of the instance
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_value_rows<T, K, false>, kVT, kLds) != hipSuccess || per_cu < 1) per_cu = 1;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_value_rows<T, K, false, ADD>, kVT, kLds) != hipSuccess || per_cu < 1) per_cu = 1;
   cached = static_cast<unsigned>(per_cu) * static_cast<unsigned>(n_cu);
   return cached;
 }
 
-template <typename T>
+template <typename T, bool ADD>
 unsigned resident_value_blocks_kv(int kv) {
-  if (kv <= 1) return resident_value_blocks<T, 1>();
-  if (kv <= 2) return resident_value_blocks<T, 2>();
-  if (kv <= 4) return resident_value_blocks<T, 4>();
-  if (kv <= 8) return resident_value_blocks<T, 8>();
-  return resident_value_blocks<T, 16>();
+  if (kv <= 1) return resident_value_blocks<T, 1, ADD>();
+  if (kv <= 2) return resident_value_blocks<T, 2, ADD>();
+  if (kv <= 4) return resident_value_blocks<T, 4, ADD>();
+  if (kv <= 8) return resident_value_blocks<T, 8, ADD>();
+  return resident_value_blocks<T, 16, ADD>();
 }
 
-template <typename T>
+template <typename T, bool ADD>
 void launch_value_rows(int kv, unsigned grid, hipStream_t st, const void* H, const void* w, float bias, int d,
                        const int32_t* rowsel, int64_t n_sel, int64_t n_rows, unsigned n_clear, unsigned clear_at, int64_t norm, int64_t rpb, const float* value_old, const float* ret,
-                       const int32_t* tok_role, int n_roles, float clip_eps, float* value_new, void* dH, int acc_dH,
+                       const int32_t* tok_role, int n_roles, float clip_eps, float* value_new, void* dH,
                        float* part_dw, double* blk_stats) {
 #define UMAS_VALUE_CASE(K)                                                                                              \
-  hipLaunchKernelGGL((n_clear ? k_value_rows<T, K, true> : k_value_rows<T, K, false>), dim3(n_clear + grid), dim3(kVT), d * sizeof(AccT<T>), st, static_cast<const T*>(H), static_cast<const T*>(w), \
+  hipLaunchKernelGGL((n_clear ? k_value_rows<T, K, true, ADD> : k_value_rows<T, K, false, ADD>), dim3(n_clear + grid), dim3(kVT), d * sizeof(AccT<T>), st, static_cast<const T*>(H), static_cast<const T*>(w), \
                      bias, d, rowsel, n_sel, n_clear ? static_cast<int>(n_rows) : 0, static_cast<int>(n_clear), static_cast<int>(clear_at), norm, rpb, value_old, ret, tok_role, n_roles, clip_eps, value_new,         \
-                     static_cast<T*>(dH), acc_dH, part_dw, blk_stats)
+                     static_cast<T*>(dH), part_dw, blk_stats)
   if (kv <= 1) UMAS_VALUE_CASE(1);
   else if (kv <= 2) UMAS_VALUE_CASE(2);
   else if (kv <= 4) UMAS_VALUE_CASE(4);
@@ -597,7 +584,8 @@ extern "C" umas_status umas_value_loss_fwd_bwd(const void* H, const void* w, flo
   const int nvec = d / (dtype == UMAS_BF16 ? 8 : 4);
   const int kv = (nvec + kWave - 1) / kWave;
   // at most value_grid(n_sel) workgroups (what the workspace is sized for), and no more than are resident at once
-  const unsigned resident = dtype == UMAS_BF16 ? resident_value_blocks_kv<uint16_t>(kv) : resident_value_blocks_kv<float>(kv);
+  const unsigned resident = dtype == UMAS_BF16 ? (accumulate_dH ? resident_value_blocks_kv<uint16_t, true>(kv) : resident_value_blocks_kv<uint16_t, false>(kv))
+                                               : (accumulate_dH ? resident_value_blocks_kv<float, true>(kv) : resident_value_blocks_kv<float, false>(kv));
   // the workgroups that clear are part of that round and go first; behind a full round of rows where the instance holds so few at once
   // that giving them up costs more than a tail, those for rows of more than 4 KB (39 224 rows of 4096 233 us with them first, 204 behind;
   // values and update of 48 651 rows of 3008 246 and 222, of 268 000 float32 rows of 1728 1733 and 1455; the other way round shorter rows: 100 000 of 1088
@@ -629,12 +617,10 @@ extern "C" umas_status umas_value_loss_fwd_bwd(const void* H, const void* w, flo
   }
   if (n_sel > 0) {
     const int64_t rpb = (n_sel + grid - 1) / grid;                 // rows per workgroup; every wavefront writes its partial row
-    if (dtype == UMAS_BF16)
-      launch_value_rows<uint16_t>(kv, grid, st, H, w, bias, d, rowsel, n_sel, n_rows, n_clear, clear_at, norm, rpb, value_old, ret, tok_role, n_roles,
-                                  clip_eps_v, value_new, dH, accumulate_dH, part_dw, blk_stats);
-    else
-      launch_value_rows<float>(kv, grid, st, H, w, bias, d, rowsel, n_sel, n_rows, n_clear, clear_at, norm, rpb, value_old, ret, tok_role, n_roles,
-                               clip_eps_v, value_new, dH, accumulate_dH, part_dw, blk_stats);
+    const auto launch = dtype == UMAS_BF16 ? (accumulate_dH ? launch_value_rows<uint16_t, true> : launch_value_rows<uint16_t, false>)
+                                           : (accumulate_dH ? launch_value_rows<float, true> : launch_value_rows<float, false>);
+    launch(kv, grid, st, H, w, bias, d, rowsel, n_sel, n_rows, n_clear, clear_at, norm, rpb, value_old, ret, tok_role, n_roles, clip_eps_v, value_new, dH,
+           part_dw, blk_stats);
     UMAS_LAUNCHED("k_value_rows");
   } else {
     // an empty selection still defines the outputs: zero partials give zero statistics and gradients
