@@ -74,7 +74,7 @@ __global__ void k_zero_u32(uint32_t* __restrict__ p, int64_t n) {
   for (; i < n; i += stride) p[i] = 0u;
 }
 // What a call defines on rows that are not selected, in the launch that works on the others: some workgroups take a share of the rows each,
-// read the whole selection (it stays in L2) into a bit per row of their share, and hand the rows without one to `clear`, all threads of the
+// read the whole selection (it stays in L2; eight loads of a thread under way) into a bit per row of their share, and hand the rows without one to `clear`, all threads of the
 // workgroup together, up to 64 rows at a time, as a mask of the rows from `first` on.  Values and update, with launches of their own to clear,
 // to mark a byte per row and to clear the rows without one, and like this: 1000 rows of 2048 25 and 20 us, 6000 34 and 28, 39 224 100 and 93 (on new
 // rows 119 and 111), 100 000 of 1024 123 and 113, 400 000 of 512 401 and 395.  (One entry at a time, with 64-bit places, the selection took 60 us
@@ -94,12 +94,12 @@ __device__ __forceinline__ void unselected_rows(int wg, int n_wg, int n_rows, co
   const int64_t head = (4 - ((reinterpret_cast<uintptr_t>(rowsel) >> 2) & 3)) & 3;   // up to the first 16-byte boundary
   const int64_t n4 = n_sel > head ? (n_sel - head) / 4 : 0;
   const int4* const sel4 = reinterpret_cast<const int4*>(rowsel + head);
-  for (int64_t i = threadIdx.x; i < n4; i += 4 * kVT) {
-    int4 v[4];
+  for (int64_t i = threadIdx.x; i < n4; i += 8 * kVT) {
+    int4 v[8];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = i + k * kVT < n4 ? sel4[i + k * kVT] : make_int4(-1, -1, -1, -1);
+    for (int k = 0; k < 8; ++k) v[k] = i + k * kVT < n4 ? sel4[i + k * kVT] : make_int4(-1, -1, -1, -1);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {                              // nearly always all of the wavefront's lie outside: three instructions an entry
+    for (int k = 0; k < 8; ++k) {                              // nearly always all of the wavefront's lie outside: three instructions an entry
       const uint32_t a = place(v[k].x), b = place(v[k].y), c = place(v[k].z), e = place(v[k].w), least = min(min(a, b), min(c, e));
       if (least < static_cast<uint32_t>(n)) { mark(a); mark(b); mark(c); mark(e); }
     }
@@ -139,12 +139,16 @@ struct ClearRows {
 // and 138, 800 000 412 and 527; of 512 bytes 200 000 149 and 157; of 768 bytes 400 000 360 and 356, of 1 KB 800 000 794 and 785); rows of two to
 // four KB hold fewer workgroups at once, which 64 of them delay by more than the launches (100 000 of 2176 bytes 187 and 185.5 us,
 // 200 000 342 and 344, 380 000 628 and 636; of 4 KB 100 000 263 and 258, 380 000 966 and 984); behind the rows it costs longer ones nothing
-// (268 000 of 6.9 KB 1472 and 1455).
+// (268 000 of 6.9 KB 1472 and 1455).  Rows of up to 2 KB, two vectors a lane, hold five workgroups to a compute unit and have 1024 at most
+// (kMaxGrid), which leaves room for 256 more: with 64 of them the rows, loaded two ahead, are done first and wait for the selection to be read and the
+// stores behind it (64 and 128, values and update: 30 000 rows of 1408 bytes 43.0 and 39.3 us, 60 000 of 1280 70 and 58, 100 000 float32 ones of 1 KB
+// 103 and 81, 120 000 of 1 KB 116 and 97, 300 000 304 and 258, 15 000 of 2 KB 31.1 and 31.2; 192 and 256 as 128).  Longer rows give up what the
+// clearing takes: 64 and 128, 39 224 of 4 KB 98 and 101, 100 000 of 2176 bytes 157 and 161.
 constexpr unsigned kClearWgs = 64;
 unsigned clear_grid(const int32_t* rowsel, int64_t n_rows, int64_t row_bytes) {
   static_assert(1 << 20 <= kClearWgs * kMapRows, "every share fits its map");
   const int64_t most = row_bytes < 768 ? 1 << 15 : row_bytes <= 1024 || row_bytes > 4096 ? 1 << 20 : 1 << 17;
-  return rowsel && n_rows <= most ? std::min(kClearWgs, cdiv(static_cast<size_t>(n_rows), 128)) : 0;
+  return rowsel && n_rows <= most ? std::min(row_bytes <= 2048 ? 2 * kClearWgs : kClearWgs, cdiv(static_cast<size_t>(n_rows), 128)) : 0;
 }
 // Those of an update: value_new[n] (may be NULL) and n16 16-byte words of `big` are cleared.
 __global__ void __launch_bounds__(256)

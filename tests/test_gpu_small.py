@@ -277,7 +277,26 @@ def test_critic_of_many_rows(n, n_sel, d, dtype):
     assert torch.equal(dH[at], want_dH) and (dH[rest] == 0).all()
 
 
-# rows of a wavefront around the few whose statistics single lanes add and around the 64 that its lanes hold at a time
+# the selection as the workgroups that clear read it: in front of, at and behind a multiple of 16 bytes, rounds of 8192 entries, 64 and 128 shares of the rows
+@pytest.mark.parametrize("d,dtype", [(512, torch.bfloat16), (512, torch.float32), (1032, torch.bfloat16)])
+@pytest.mark.parametrize("n,n_sel", [(127, 3), (8193, 2), (16385, 8192), (20000, 8195), (33000, 32771)])
+def test_critic_clears_what_a_shuffled_selection_leaves_out(n, n_sel, d, dtype):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    H, w = torch.randn(n, d, device="cuda", generator=g).to(dtype), torch.randn(d, device="cuda", generator=g).to(dtype)
+    old, ret = torch.zeros(n, device="cuda"), torch.randn(n, device="cuda", generator=g)
+    order = torch.randperm(n, device="cuda", generator=g).to(torch.int32)
+    for first in range(4):
+        sel = order[first:first + n_sel]
+        rest = torch.ones(n, dtype=torch.bool, device="cuda")
+        rest[sel.long()] = False
+        value = umas.umas_values(H, w, 0.5, sel, value=torch.full((n,), float("nan"), device="cuda"))
+        _, value_new, dH, _, _ = umas.umas_value_loss_fwd_bwd(H, w, 0.5, sel, old, ret, None, 0, 1e9, dH=torch.full_like(H, float("nan")),
+                                                              value_new=torch.full((n,), float("nan"), device="cuda"))
+        for got in (value[:, None], value_new[:, None], dH):
+            assert (got[rest] == 0).all() and (got[sel.long()] != 0).any(dim=1).all()
+
+
+# rows of a wavefront around the 64 that its lanes hold at a time, and few
 @pytest.mark.parametrize("n_roles", [3, 64])
 @pytest.mark.parametrize("n,d,dtype", [(33, 2048, torch.bfloat16), (8191, 512, torch.float32), (18439, 4096, torch.float32), (20493, 8192, torch.bfloat16),
                                        (60001, 1096, torch.bfloat16), (262145, 264, torch.bfloat16), (532481, 8, torch.bfloat16), (530001, 12, torch.float32)])
