@@ -1218,8 +1218,11 @@ __device__ __forceinline__ KContig blocked_rows_tile(const uint16_t* X, int blk_
 // under way during the turn, and a piece's LDS reads and stores go out together (waiting for each of 32 pieces by itself:
 // both products of 725 rows of 2048 that add to dW 1155 us, together 1020; 64 rows without adding 459 and 443).  What is there is read past the
 // caches, which leaves them to the operands (two updates of which the second adds, 203 rows of 2048 1454 -> 1380 us, 300 1950 -> 1885, 725 rows
-// four times 5.82 -> 5.73 ms).
+// four times 5.82 -> 5.73 ms).  Such a piece is addressed by 32-bit offsets from the wavefront's first row; rows farther apart than
+// kPieceLd take the way of the tiles that end early, with 64-bit addresses.
 constexpr int kTurnBytes = 32 * 64 * 4;                              // 32 rows of 64 floats per wavefront
+constexpr int64_t kPieceLd = int64_t{1} << 22;                       // floats
+static_assert(((Cfg::WTM - 1) * kPieceLd + Cfg::WTN) * 4 < int64_t{1} << 31, "the last row of a wavefront's block is in reach");
 static_assert(Cfg::WTN == 64 && Cfg::WM * Cfg::WN == 8 && 8 * kTurnBytes <= 2 * Cfg::BM * 128, "the turn fits two stages of an operand");
 // 32 rows (blocks 2 h and 2 h + 1) of a wavefront's accumulators into its part of LDS, and four columns of four rows (4 i + lane /
 // 16) back.  The 16-byte unit u of row r lies in unit u ^ 4 ((r >> 2) & 3): neither side meets a bank twice.
@@ -1245,7 +1248,7 @@ __device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[C::MI][C::NI]
   typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // dW has the alignment of a float
   const int tid = tile_thread(), lane = tid & 63, wave = tid >> 6;
   const int r0 = wave / C::WN * C::WTM, c0 = wave % C::WN * C::WTN + (lane & 15) * 4;
-  const bool whole = rows >= C::BM && cols >= C::BN;                 // the same for every thread
+  const bool whole = rows >= C::BM && cols >= C::BN && ld <= kPieceLd;   // the same for every thread
   float* const dst = out + (r0 + (lane >> 4)) * ld + c0;
   constexpr int kPieces = C::MI / 2;
   // Each case is a run of its own: with the branches inside, the waits cannot tell what is under way and are for everything, the stores of
@@ -1997,6 +2000,8 @@ umas_status check_model_args(const void* H, const void* W, umas_dtype dt, int64_
   UMAS_REQUIRE(dt != UMAS_BF16 || static_cast<uint64_t>(n_rows) * d * 2 < (1ull << 32), UMAS_ESHAPE,
                "bf16 H must be smaller than 4 GiB (32-bit buffer offsets): n_rows=%lld d=%d",
                static_cast<long long>(n_rows), d);
+  UMAS_REQUIRE(dt != UMAS_BF16 || static_cast<uint64_t>(std::min(V, 256)) * d * 2 < (1ull << 32), UMAS_ESHAPE,
+               "256 rows of a bf16 W must be smaller than 4 GiB (32-bit buffer offsets): V=%d d=%d", V, d);
   UMAS_REQUIRE(rowsel || n_sel == n_rows, UMAS_EINVAL, "rowsel is NULL but n_sel != n_rows");
   UMAS_REQUIRE(n_sel <= n_rows, UMAS_EINVAL, "n_sel=%lld exceeds n_rows=%lld", static_cast<long long>(n_sel),
                static_cast<long long>(n_rows));

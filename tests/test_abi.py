@@ -153,6 +153,11 @@ def test_bad_scalar_arguments(lib):
     assert lib.umas_policy_logprobs(256, 256, 1, 1 << 28, 8, 8, 256, None, 1 << 28, 256, 256, None, 256, 1 << 20, None) == -2
     assert "4 GiB" in lib.umas_last_error().decode()
     assert lib.umas_policy_logprobs(256, 256, 1, (1 << 28) - 1, 8, 8, 256, None, (1 << 28) - 1, 256, 256, None, 256, 1 << 20, None) == -4
+    # so are rows of a bf16 W of which 256 (all, where there are fewer) reach 4 GiB; a vector less gets as far as the workspace check
+    for V, d in ((300, 1 << 23), (8, 1 << 28)):
+        assert lib.umas_policy_logprobs(256, 256, 1, 1, d, V, 256, None, 1, 256, 256, None, 256, 16, None) == -2
+        assert "256 rows of a bf16 W" in lib.umas_last_error().decode()
+        assert lib.umas_policy_logprobs(256, 256, 1, 1, d - 8, V, 256, None, 1, 256, 256, None, 256, 16, None) == -4
     # clip_eps outside (0,1)
     st = lib.umas_ppo_loss_fwd_bwd(256, 256, 0, 4, 8, 8, 256, None, 4, 256, 256, None, 0, 1.5, 0.0, 0.0, 0, 0, None, 0.0, 256, None,
                                    256, 256, 256, 1 << 30, None)

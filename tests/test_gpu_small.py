@@ -410,6 +410,32 @@ def test_update_of_few_rows_with_a_large_gradient(rows, entropy_coef, accumulate
     check_update(np.random.default_rng(rows), rows, 4104, 65500, select=1.0, entropy_coef=entropy_coef, accumulate=accumulate)
 
 
+# rows so wide that dW's lie farther apart than 32-bit offsets of a tile's pieces reach (a product of the two overflows from 4.33 million columns on), and
+# the widest that are not; in a launch of its own and beside dH; a vocabulary block that is whole and one that is not
+@pytest.mark.parametrize("rows,accumulate", [(70, False), (70, True), (40, True)])
+@pytest.mark.parametrize("d", [1 << 22, 4400008])
+def test_update_of_very_wide_rows(rows, d, accumulate):
+    V, g = 259, torch.Generator(device="cuda").manual_seed(rows)
+    H = torch.randn(rows, d, device="cuda", generator=g).bfloat16()
+    W = (torch.randn(V, d, device="cuda", generator=g) / d ** 0.5 / 64).bfloat16()
+    ids, adv = torch.randint(0, V, (rows,), device="cuda", generator=g, dtype=torch.int32), torch.randn(rows, device="cuda", generator=g)
+    dW0 = torch.randn(V, d, device="cuda", generator=g) / rows if accumulate else None
+    dW = umas.umas_ppo_loss_fwd_bwd(H, W, ids, None, None, adv, None, 0, 0.2, accumulate_dW=accumulate, dW=dW0.clone() if accumulate else None)[3]
+    z = sum(H[:, i:i + 65536].double() @ W[:, i:i + 65536].double().T for i in range(0, d, 65536))
+    dz = torch.softmax(z, 1) - torch.nn.functional.one_hot(ids.long(), V)
+    dz *= adv.double()[:, None] / rows
+    for i in range(0, d, 65536):
+        h = H[:, i:i + 65536].double()
+        want, size = dz.T @ h, dz.abs().T @ h.abs()
+        got = dW[:, i:i + 65536].double()
+        if accumulate:
+            want, size = want + dW0[:, i:i + 65536].double(), size + 2.0 ** -16 * dW0[:, i:i + 65536].double().abs()
+        # probability and scaled row are bf16, 2^-9 each.  A logit, below 5/64, is a float32 sum of d / 32 products that may each lose 2^-23 of it:
+        # less than 2^-9, and the logsumexp as much.  (With logits of unit size, 64 times that, three quarters of 2^-7 were not enough.)
+        worst = float(((got - want).abs() / size).max())
+        assert worst <= 2.0 ** -7, (i, worst)
+
+
 # New log-probs written over the old ones: these are gone when the surrogate looks at them, as if none were given.  One launch for the rows would
 # read some of them first; more rows than one launch takes, for comparison
 @pytest.mark.parametrize("rows", [60, 300, 2100])
