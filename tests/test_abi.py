@@ -145,6 +145,51 @@ def test_the_malformed_entry_is_named(lib, name, at, value, needle):
     assert needle in lib.umas_last_error().decode()
 
 
+def first_malformed(kw, n_roles):
+    """What of a graph of well-formed trajectories is named: one entry after the other."""
+    off, role, traj = kw["turn_tok_off"].tolist(), kw["turn_role"].tolist(), kw["traj_turn_off"].tolist()
+    for u in range(len(role)):
+        if off[u] > off[u + 1]:
+            return f"turn_tok_off decreases at {u}"
+        if not 0 <= role[u] < n_roles:
+            return f"turn_role[{u}]={role[u]}"
+    pred_off, pred = kw["turn_pred_off"].tolist(), kw["turn_pred"].tolist()
+    for u in range(len(role)):
+        if pred_off[u] > pred_off[u + 1]:
+            return f"turn_pred_off decreases at {u}"
+    for b in range(len(traj) - 1):
+        for u in range(traj[b], traj[b + 1]):
+            for e in range(pred_off[u], pred_off[u + 1]):
+                if not traj[b] <= pred[e] < u:
+                    return f"predecessor {pred[e]} of turn {u}"
+    return "16-byte aligned"             # nothing: the dummy output pointers are refused
+
+
+# entries anywhere, also so large or small that a difference of two of them does not fit their type
+@pytest.mark.parametrize("seed", range(60))
+def test_the_first_of_several_malformed_entries_is_named(lib, seed):
+    from paper_2605_26646_amd import binding as b
+    rng = np.random.default_rng(seed)
+    traj = np.concatenate([[0], np.cumsum(rng.integers(0, 9, 40))])
+    turns = int(traj[-1])
+    first = np.repeat(traj[:-1], np.diff(traj))
+    edges = [rng.integers(first[u], u, rng.integers(0, 3)) if u > first[u] else [] for u in range(turns)]
+    kw = dict(traj_turn_off=traj.astype(np.int32), turn_role=rng.integers(0, 2, turns).astype(np.int32),
+              turn_tok_off=np.concatenate([[0], np.cumsum(rng.integers(0, 4, turns))]).astype(np.int64),
+              turn_pred_off=np.concatenate([[0], np.cumsum([len(e) for e in edges])]).astype(np.int32),
+              turn_pred=np.concatenate(edges).astype(np.int32))
+    for name in rng.choice(["turn_role", "turn_tok_off", "turn_pred_off", "turn_pred"], rng.integers(0, 3)):
+        a = kw[name]
+        info = np.iinfo(a.dtype)
+        lo, hi = (1, len(a) - 1) if name.endswith("_off") else (0, len(a))      # the ends are checked by themselves
+        for at in rng.integers(lo, hi, rng.integers(1, 4)):
+            a[at] = rng.choice([info.min, info.min + 1, info.min // 2 - 1, -1, 0, 1, 2, a[at] - 1, info.max // 2 + 1, info.max])
+    g, keep = graph(**kw)
+    r, s = b._Rewards(None, None, None, None, None, None, 0, 1e-6), b._Streams(*([1] * 16))
+    assert lib.umas_assign_token_rewards(C.addressof(g), C.addressof(r), 1, C.addressof(s), 256, 1 << 20, None) == -1
+    assert first_malformed(kw, 2) in lib.umas_last_error().decode()
+
+
 def test_bad_scalar_arguments(lib):
     assert lib.umas_policy_logprobs(256, 256, 7, 4, 8, 8, 256, None, 4, 256, 256, None, 256, 1 << 20, None) == -3
     assert lib.umas_policy_logprobs(256, 256, 1, 4, 12, 8, 256, None, 4, 256, 256, None, 256, 1 << 20, None) == -2
