@@ -236,7 +236,10 @@ k_mb_scan(int n_models, int n_traj, int ntile, int n_minibatch, int balance_rows
 
 // One wavefront per (model, kept trajectory): its rowsel slice goes to its place in mb_rowsel, 16 bytes at a time from the first 16-byte boundary there
 // on (at any 4-byte boundary of rowsel).  A slice is a few hundred entries, so a wavefront's time is its chain of loads: what says where
-// the slice lies is asked for together, whether the trajectory was kept or not.  29 500 slices of 614 entries (145 MB) 32 us, now 26.
+// the slice lies is asked for together, whether the trajectory was kept or not, and so are a slice's whole vectors and its ends; slices of up to a
+// wavefront's entries have only ends.  36 million tokens in trajectories of 101, 202, 280, 420, 616 and 2800 scored ones, 4 bytes at a time 69,
+// 55.5, 48.5, 43.7, 40.3 and 40.5 us, 16 bytes and the ends with trips of their own 74, 49.5, 41.3, 35.3, 33.9 and 35.6, now 61.6, 41.7, 36, 35,
+// 34.8 and 36.2; 18 million in trajectories of 50 54.5, 62 and 48.5; 4 million of 11 47, 54.6 and 39.7.
 __global__ void __launch_bounds__(256)
 k_mb_copy(int n_models, int n_traj, const int64_t* __restrict__ n_kept_p, const int64_t* __restrict__ scan_mq,
           const int64_t* __restrict__ src_mq, const int64_t* __restrict__ totals, const int32_t* __restrict__ rowsel,
@@ -251,26 +254,34 @@ k_mb_copy(int n_models, int n_traj, const int64_t* __restrict__ n_kept_p, const 
   int64_t base = 0;
   for (; q >= n_traj; q -= n_traj) base += totals[m++];
   const int64_t n_kept = *n_kept_p, first = scan_mq[at], next = q + 1 < n_traj ? scan_mq[at + 1] : totals[m];
-  const int32_t* src = rowsel + src_mq[at];
+  const int32_t* const src = rowsel + src_mq[at];
   if (q >= n_kept) return;
-  int64_t len = next - first;
-  int32_t* dst = mb_rowsel + base + first;
+  const int64_t len = next - first;
+  int32_t* const dst = mb_rowsel + base + first;
+  if (len <= kWave) {
+    if (lane < len) dst[lane] = src[lane];
+    return;
+  }
   const int64_t off = static_cast<int64_t>((16 - (reinterpret_cast<uintptr_t>(dst) & 15)) & 15) / 4, head = off < len ? off : len;
-  if (lane < head) dst[lane] = src[lane];
-  src += head;
-  dst += head;
-  len -= head;
-  const int64_t n4 = len / 4;
+  const int64_t n4 = (len - head) / 4, tail = head + n4 * 4;
+  int32_t first_entry = 0, last_entry = 0;                   // up to three in front of the whole vectors, up to three behind
+  if (lane < head) first_entry = src[lane];
+  if (tail + lane < len) last_entry = src[tail + lane];
+  const i32x4_a4* const src4 = reinterpret_cast<const i32x4_a4*>(src + head);
+  i32x4* const dst4 = reinterpret_cast<i32x4*>(dst + head);
   for (int64_t i0 = lane; i0 < n4; i0 += 4 * kWave) {        // four loads in flight per lane
     i32x4 v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (i0 + k * kWave < n4) v[k] = reinterpret_cast<const i32x4_a4*>(src)[i0 + k * kWave];
+      if (i0 + k * kWave < n4) v[k] = src4[i0 + k * kWave];
+    if (i0 == lane) {                                        // (a slice has 15 vectors here at least)
+      if (lane < head) dst[lane] = first_entry;
+      if (tail + lane < len) dst[tail + lane] = last_entry;
+    }
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (i0 + k * kWave < n4) reinterpret_cast<i32x4*>(dst)[i0 + k * kWave] = v[k];
+      if (i0 + k * kWave < n4) dst4[i0 + k * kWave] = v[k];
   }
-  if (n4 * 4 + lane < len) dst[n4 * 4 + lane] = src[n4 * 4 + lane];
 }
 
 // Parts under a budget of scored rows, one wavefront per model: starting from the model's first row, a part ends at

@@ -374,6 +374,22 @@ def test_ready_batch_of_masks_that_are_not_alike(shape, n_models):
     check_ready_batch_arraywise(w, s, aw.streams(w), (rng.random(n_traj) < 0.9).astype(np.uint8), rng.permutation(n_traj).astype(np.int32), 5)
 
 
+# slices around one entry a lane, around one and four 16-byte vectors a lane, at every boundary of 4 bytes on either side
+@pytest.mark.parametrize("lengths", [(0, 1, 2, 3, 5), (63, 64, 65, 66, 67, 68, 71), (255, 256, 257, 260, 263), (1023, 1024, 1025, 1027, 1031, 2111)])
+@pytest.mark.parametrize("n_models", [1, 2])
+def test_ready_batch_slices_of_these_lengths(lengths, n_models):
+    n_traj, rng = 1500, np.random.default_rng(len(lengths))
+    w = sized_graph(3, 16, 2 * n_traj, n_traj, n_models, n_models, 0)
+    tokens = rng.choice(np.array(lengths), 2 * n_traj)
+    w.n_tokens, w.turn_tok_off = int(tokens.sum()), np.concatenate([[0], np.cumsum(tokens)]).astype(np.int64)
+    w.traj_turn_off, w.turn_role = np.arange(n_traj + 1, dtype=np.int32) * 2, (np.arange(2 * n_traj) % 2 % n_models).astype(np.int32)
+    w.tok_mask, w.value = np.ones(w.n_tokens, np.uint8), None
+    if n_models == 1:                                    # one turn of a trajectory is all there is
+        w.tok_mask[np.repeat(np.arange(2 * n_traj) % 2 == 1, tokens)] = 0
+    s = route(w, wl.PLACE_LAST)
+    check_ready_batch_arraywise(w, s, aw.streams(w), (rng.random(n_traj) < 0.8).astype(np.uint8), rng.permutation(n_traj).astype(np.int32), 7)
+
+
 # chunks of 256 rows, each with slices of dH that are added up before the next chunk's; the last chunk's go with the rest of the update
 @pytest.mark.parametrize("n,d,V", [(257, 64, 3000), (600, 1032, 1300)])
 @pytest.mark.parametrize("entropy_coef", [0.0, 0.01])
