@@ -56,7 +56,7 @@ def kernel_source_hash():
     invalidates the stored counters, a change of a comment does not."""
     import hashlib, re
     h = hashlib.sha256()
-    for fn in ("umas_score.hip", "umas_mfma.h", "umas_common.h"):
+    for fn in ("umas_score.hip", "umas_plan.h", "umas_mfma.h", "umas_common.h"):
         text = open(os.path.join(ROOT, "paper_2605_26646_amd", "csrc", fn)).read()
         text = re.sub(r"//[^\n]*", "", text)
         h.update(re.sub(r"\s+", "", text).encode())
