@@ -19,14 +19,17 @@ inline int64_t dh_tiles(int64_t rows, int d) { return (rows + 255) / 256 * ((d +
 // decided by the rows of the call and its chunks, not by those of the last chunk, which may have fewer
 inline bool slices_dh(int64_t n_sel, int64_t chunk_rows, int d) { return dh_tiles(chunk_rows, d) < (chunk_rows < n_sel ? kDhSliceTiles / 2 : kDhSliceTiles); }
 // dW of one block of rows gets a launch of its own (k_dw_short) where it is large: its stores, which everything else then waits for, are longer than the launch
-// and the dH tiles' uneven end that it pays for.  Update against 151 936 in one launch and two, 203 rows of 2048 (1.16 GiB) 614 and 604 us, 2304 693
-// and 666, 2560 754 and 735, 3072 892 and 853, 4096 1164 and 1092, of 1096 against 50 001 (0.2 GiB) 194 and 203; 100 rows, whose dH tiles are half as
-// long, of 2048 518 and 524, 2304 597 and 580, 3072 763 and 758, 3584 892 and 859; 30 rows of 2048 508 and 517, 2304 582 and 569, 3072 722 and
-// 731.  More than a block: 300 rows of 2048 876 and 922, 725 of 3584 2262 and 2258, 2500 6594 and 8070.
+// and the dH tiles' uneven end that it pays for.  Update in two launches over one, geometric mean over 129 to 256 rows, dW of 0.5, 0.7, 0.9, 1.1, 1.3
+// and 1.6 GiB: 2048 columns 1.019, 1.012, 1.008, 0.994 (151 936 entries are 1.16), 2560 1.025, 1.039, 1.017, 0.976, 0.975, 0.957, 3584
+// 0.931, 0.920, 0.916, 0.940, 0.952, 0.966, 8192 0.981, 0.983, 0.988, 0.938, 0.949, 0.965.  65 to 128 rows, whose dH tiles are half as long: 2048 columns
+// 1.044, 1.031, 0.998, 1.009, 2560 1.052, 1.032, 1.018, 0.975, 1.000, 0.973, 3584 0.983, 0.970, 0.970, 0.954, 0.954, 0.977, 4096 above 1.25 GiB
+// 0.978, 4608 1.009, 8192 1.009 to 1.017, 16 384 1.02; 30 rows of 2048 508 and 517 us, 3072 722 and 731.  More than a block: 300 rows of 2048 876 and
+// 922, 725 of 3584 2262 and 2258, 2500 6594 and 8070.
 constexpr int64_t kDwApartBytes = int64_t{1} << 30;
 inline bool dw_apart(int64_t n_sel, int d, int V) {
   const int64_t bytes = static_cast<int64_t>(V) * d * 4;
-  return n_sel > 64 && n_sel <= 256 && bytes >= (n_sel > 128 ? kDwApartBytes : kDwApartBytes / 4 * 5);
+  if (n_sel <= 128) return n_sel > 64 && d <= 4096 && bytes >= kDwApartBytes / 4 * 5;
+  return n_sel <= 256 && bytes >= kDwApartBytes;
 }
 struct DhPlan {
   int slices, voc_blks;

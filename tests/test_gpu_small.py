@@ -420,15 +420,25 @@ def test_update_of_few_rows_with_a_large_head(rows):
     check_update(np.random.default_rng(rows), rows, 2048, 66000, select=1.0)
 
 
-# dW of 1 GiB and more, which has a launch of its own up to 256 rows: a column tile of eight columns, a step of 32 rows that is partly filled
-@pytest.mark.parametrize("rows,entropy_coef,accumulate", [(70, 0.0, True), (200, 0.01, False), (256, 0.0, True), (257, 0.0, False)])
-def test_update_of_few_rows_with_a_large_gradient(rows, entropy_coef, accumulate):
-    check_update(np.random.default_rng(rows), rows, 4104, 65500, select=1.0, entropy_coef=entropy_coef, accumulate=accumulate)
+# dW of 1 GiB and more (1.25 below 129 rows), which has a launch of its own up to 256 rows: a column tile of eight columns, a step of 32 rows that is partly
+# filled; up to 128 rows the operand comes in halves of its blocks, whose other rows nobody has written
+@pytest.mark.parametrize("d,V,rows,entropy_coef,accumulate,apart", [
+    (4088, 82200, 65, 0.0, False, True), (4088, 82200, 96, 0.0, True, True), (4088, 82200, 97, 0.0, False, True), (4088, 82200, 128, 0.0, True, True),
+    (4088, 82200, 100, 0.01, True, True), (4104, 65500, 70, 0.0, True, False), (4104, 65500, 200, 0.01, False, True), (4104, 65500, 256, 0.0, True, True),
+    (4104, 65500, 257, 0.0, False, False)])
+def test_update_of_few_rows_with_a_large_gradient(d, V, rows, entropy_coef, accumulate, apart):
+    umas.profile_enable(True)
+    try:
+        check_update(np.random.default_rng(rows), rows, d, V, select=1.0, entropy_coef=entropy_coef, accumulate=accumulate)
+        launched = umas.profile_read()
+    finally:
+        umas.profile_enable(False)
+    assert ("k_dw_short" in launched) == apart and ("k_score_keep_narrow" in launched) == (rows <= 128 and entropy_coef == 0)
 
 
 # rows so wide that dW's lie farther apart than 32-bit offsets of a tile's pieces reach (a product of the two overflows from 4.33 million columns on), and
 # the widest that are not; in a launch of its own and beside dH; a vocabulary block that is whole and one that is not
-@pytest.mark.parametrize("rows,accumulate", [(70, False), (70, True), (40, True)])
+@pytest.mark.parametrize("rows,accumulate", [(130, False), (130, True), (40, True)])
 @pytest.mark.parametrize("d", [1 << 22, 4400008])
 def test_update_of_very_wide_rows(rows, d, accumulate):
     V, g = 259, torch.Generator(device="cuda").manual_seed(rows)

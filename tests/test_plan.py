@@ -51,6 +51,7 @@ def test_dh_alone_is_cut_into_whole_rounds_and_else_as_beside_dw(plan):
     assert len(kinds) == 4
 
 
-def test_rows_that_have_their_dw_beside_dh(plan):
+def test_rows_that_have_a_launch_for_dw(plan):
     cases = [(n, n, 3584, 152064, GIB) for n in (1, 64, 65, 256, 257, 700)] + [(200, 200, 2048, V, GIB) for V in ((1 << 17) - 1, 1 << 17)]
-    assert [p[2] for p in plan(cases)] == [0, 0, 1, 1, 0, 0, 0, 1]
+    cases += [(128, 128, 4096, V, GIB) for V in (81919, 81920)] + [(128, 128, 4104, 90000, GIB), (129, 129, 4104, 90000, GIB)]
+    assert [p[2] for p in plan(cases)] == [0, 0, 1, 1, 0, 0, 0, 1, 0, 1, 0, 1]
