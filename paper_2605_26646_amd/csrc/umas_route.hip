@@ -553,7 +553,7 @@ __device__ __forceinline__ void store_four(const TokArgs& A, const SegWindow& W,
     store_stream(A.tok_turn + p0, make_int4(M.turn, M.turn, M.turn, M.turn));
     store_stream(A.tok_role + p0, make_int4(M.role, M.role, M.role, M.role));
     put_words(fg4, rw);
-    asm volatile("");                               // or these stores and the plain ones below would be made one, and plain
+    asm volatile("");                               // keeps this end apart from the paths below: stores joined with theirs would be plain (a test reads the built code)
     return;
   }
   if (PAST && __ballot(pl0 + kTokPerThread <= ntok) == ~0ull) {   // four tokens, some lanes' of several segments

@@ -47,3 +47,22 @@ def test_critic_rows_stay_in_registers(scratch):
     assert len(rows) == 2 * 5 * 4
     for name, size in rows.items():
         assert size <= (64 if name.startswith("k_value_rows<unsigned short, 16,") else 0), (name, size)
+
+
+@pytest.fixture(scope="module")
+def token_kernels(code_objects):
+    """The instructions of the two routing kernels that write the per-token outputs: {stores past the caches or not: text}."""
+    found = {}
+    for path in code_objects:
+        text = subprocess.run([f"{LLVM}/llvm-objdump", "-d", "--no-show-raw-insn", path], check=True, capture_output=True, text=True).stdout
+        for past, body in re.findall(r"<\w*k_tokensILb([01])E\w*>:\n(.*?)(?=\n\n|\Z)", text, re.S):
+            found[past == "1"] = body
+    return found
+
+
+# source index (two), turn and role of four tokens, where a wavefront's tokens are one segment's a lane and where they are not, in four rounds: stores that a
+# compiler would make one with the plain ones of the paths beside them, and plain
+def test_routing_stores_past_the_caches(token_kernels):
+    past = re.compile(r"global_store_dwordx4 .* nt\b")
+    assert len(past.findall(token_kernels[True])) == 4 * 2 * 4
+    assert not past.findall(token_kernels[False])
