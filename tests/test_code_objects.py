@@ -49,6 +49,11 @@ def test_critic_rows_stay_in_registers(scratch):
         assert size <= (64 if name.startswith("k_value_rows<unsigned short, 16,") else 0), (name, size)
 
 
+# the accumulators of a tile are half of its registers; who clears the taken tokens' entries must not keep them for that
+def test_flagged_blocks_spill_little(scratch):
+    assert scratch["k_dz_flagged"] <= 32
+
+
 @pytest.fixture(scope="module")
 def token_kernels(code_objects):
     """The instructions of the two routing kernels that write the per-token outputs: {stores past the caches or not: text}."""
