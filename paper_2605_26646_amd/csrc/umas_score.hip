@@ -142,11 +142,8 @@ struct Stage {                                                                  
   static constexpr int kPitch = C::WTM * 2 + 16;                                // one staged row of bf16, 16-byte aligned
   static constexpr int kBytes = C::WM * C::WN * C::WTN * kPitch;
 };
-constexpr int kStagePitch = Stage<Cfg>::kPitch, kStageBytes = Stage<Cfg>::kBytes;
-constexpr int kPartBytes = (Cfg::WM * Cfg::BN * 3 + Cfg::BN) * 4;
+constexpr int kStagePitch = Stage<Cfg>::kPitch;
 constexpr int kLogitPitch = Cfg::WTM * 4 + 16;                                  // one staged row of logits: 128 floats
-static_assert(16 * kLogitPitch <= Cfg::WTN * kStagePitch, "sixteen rows of logits fit a wavefront's stage");
-static_assert(kStageBytes + kPartBytes <= kLogitLds, "staging and the partials fit the tile buffers");
 static_assert(kLogitLds <= 160 * 1024, "LDS of one CU");
 
 enum class Leave { kNothing, kNumerators, kLogits };   // what a scoring pass leaves behind for the backward
@@ -169,6 +166,10 @@ __device__ __forceinline__ void score_tile(const uint16_t* __restrict__ W, const
   static_assert(LEAVE != Leave::kLogits || (C::BM == 256 && C::WTM == Cfg::WTM), "logits are kept in rows of 128 of a block's 256 entries");
   static_assert(256 % C::BM == 0 && 256 % C::BN == 0, "numerators are kept inside a block");
   constexpr int kPitch = Stage<C>::kPitch;
+  constexpr int kLds = C::T == Cfg::T ? kLogitLds : Ring2Cfg<C>::LDS_BYTES;   // halves of a tile use the whole one's buffers
+  static_assert(Ring2Cfg<C>::LDS_BYTES <= kLds, "the main loop's stages fit");
+  static_assert((LEAVE == Leave::kNothing ? 0 : Stage<C>::kBytes) + (C::WM * C::BN * 3 + C::BN) * 4 <= kLds, "staging and the partials fit the tile buffers");
+  static_assert(LEAVE != Leave::kLogits || 16 * kLogitPitch <= C::WTN * kPitch, "sixteen rows of logits fit a wavefront's stage");
   const int m0 = tile_m * C::BM;
   const int64_t n0 = static_cast<int64_t>(tile_n) * C::BN;   // chunk-relative
   floatx4 acc[C::MI][C::NI];
@@ -331,7 +332,10 @@ __device__ __forceinline__ void score_tile(const uint16_t* __restrict__ W, const
 // The tiles of a workgroup.  With few column tiles a workgroup has one tile, and the last round of compute units is often nearly empty: the tiles of
 // one that is at most half full are cut into two of 128 rows of the selection.  594 tiles on 256 compute units, 256 rows: 2048 columns 190 -> 173 us, 3584
 // 283 -> 270; 150 rows 188 -> 170 and 271 -> 262; the update of 203 rows of 3584 1037 -> 1022, with an entropy bonus 1056 -> 1026, 100 rows of 2048 609 ->
-// 584.  (Up to 128 rows all tiles cut, whose other halves have no rows: 100 rows with a bonus 611, of 3584 957 -> 1036.)
+// 584.  (Up to 128 rows all tiles cut, whose other halves have no rows: 100 rows with a bonus 611, of 3584 957 -> 1036.)  Up to eight column tiles, beyond which
+// a workgroup has several: 300, 1000 and 2000 rows of 1536 against 33 001 86.7 -> 76.6, 126.5 -> 114.9 and 204.9 -> 193.5, of 1024 against 100 001
+// 130.1 -> 119.9, 217.8 -> 208.5 and 389.7 -> 382.4, of 2048 against 151 936 294.2 -> 276.9, 553.2 -> 547.4 and 1014 -> 1023, 900 of 3584 918 -> 900; where
+// the last round is fuller nothing changes.
 using HalfCfg = TileCfg<256, 128, 2, 4>;                 // the lanes of a row as in a whole tile: the same bits
 template <Leave LEAVE, class C>
 __device__ __forceinline__ void score_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
@@ -389,7 +393,6 @@ k_score_keep_tiles(const uint16_t* __restrict__ W, const uint16_t* __restrict__ 
 }
 // ... and what an update of so few rows keeps: half rows of half blocks of the operand, whose other rows are never read (100 rows of 3584 270 -> 211
 // us; the update, with shorter sums for dW and half the products for dH, 1000 -> 887, of 2048 608 -> 518).
-static_assert(Stage<NarrowCfg>::kBytes + (NarrowCfg::WM * NarrowCfg::BN * 3 + NarrowCfg::BN) * 4 <= kNarrowLds, "staging and the partials fit");
 __global__ void __launch_bounds__(NarrowCfg::T)
 k_score_keep_narrow(const uint16_t* __restrict__ W, const uint16_t* __restrict__ H, int d, int V,
                     const int32_t* __restrict__ rowsel, int64_t n_sel, const int32_t* __restrict__ ids,
@@ -971,7 +974,8 @@ k_keep_rows(KeptRows K, const int32_t* __restrict__ rowsel, int64_t c0, int64_t 
 }
 // Few rows (one chunk of up to kFewBlocks blocks): k_score_finalize, k_ppo_rows and k_keep_rows in one launch, eight rows to a workgroup; the statistics are left
 // to k_update_close, which goes over the rows once more.  Bound by its chain of loads, as the three were: update of 203 rows of 1096 against 50 001 191.6 and
-// 184.5 us, 60 rows of 1024 against 151 936 271 and 266, 500 562 and 558, 725 of 2048 1361.6 and 1355.8, 2000 3193 and 3198.
+// 184.5 us, 60 rows of 1024 against 151 936 271 and 266, 500 of 512 against 30 001 138.9 and 126.7, 2000 270.3 and 262.2, 2000 of 2048 against 151 936
+// 3218 and 3194, of 3584 against 50 001 1875 and 1868.
 struct RowsArgs {
   const float4* partial;
   int tiles_m;
