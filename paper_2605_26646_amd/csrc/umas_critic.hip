@@ -26,7 +26,14 @@ namespace {
 constexpr int kVT = 256;                 // threads per workgroup
 constexpr int kVWaves = kVT / kWave;
 constexpr int kMaxKV = 16;               // 16-byte column vectors per lane: d <= 64 * 16 * (8 bf16 | 4 float)
-constexpr int kMaxGrid = 1024;           // workgroups of the row kernel at most (the launch takes no more than are resident at once)
+constexpr unsigned kMaxGrid = 1024;      // workgroups of the row kernel at most (the launch takes no more than are resident at once)
+// Rows of 768 bytes to 2 KB, two vectors a lane: three workgroups to a compute unit, those that clear among them.  640 of rows and 128 that clear against 1024 and 128, four
+// and a half, values and update: 12 000 rows of 512 bf16 columns 27.9 and 26.7 us, 40 000 45.5 and 42.1, 18 000 of 896 38.6 and 36.7, 40 000 58.8
+// and 56, 40 000 of 1024 62.4 and 59.7, 70 000 92.4 and 88.7, 40 000 float32 rows of 256 45.8 and 42, of 512 60.2 and 59.1 (with
+// one row in flight 40 000 of 896 57, of 1024 61.2); 640 and 64, 96, 192, 256 for 40 000 of 896 61.2, 55.8, 60.2 and 59.8.  Shorter
+// rows are bound by what a wavefront does for one, not by memory: the update of all of 250 000 of 256 columns 73.4 us with 768, 68.3 with 1024, of 384 73.8
+// and 76.7.
+constexpr unsigned kShortRowsGrid = 768;
 constexpr int kVStat = 4;                // (sum L, clipped rows, sum V, rows)
 __host__ __device__ constexpr int part_pitch(int d) { return (d + 1 + 15) / 16 * 16; }   // floats of a partial row: dw, then db
 
@@ -139,10 +146,9 @@ struct ClearRows {
 // and 138, 800 000 412 and 527; of 512 bytes 200 000 149 and 157; of 768 bytes 400 000 360 and 356, of 1 KB 800 000 794 and 785); rows of two to
 // four KB hold fewer workgroups at once, which 64 of them delay by more than the launches (100 000 of 2176 bytes 187 and 185.5 us,
 // 200 000 342 and 344, 380 000 628 and 636; of 4 KB 100 000 263 and 258, 380 000 966 and 984); behind the rows it costs longer ones nothing
-// (268 000 of 6.9 KB 1472 and 1455).  Rows of up to 2 KB, two vectors a lane, hold five workgroups to a compute unit and have 1024 at most
-// (kMaxGrid), which leaves room for 256 more: with 64 of them the rows, loaded two ahead, are done first and wait for the selection to be read and the
-// stores behind it (64 and 128, values and update: 30 000 rows of 1408 bytes 43.0 and 39.3 us, 60 000 of 1280 70 and 58, 100 000 float32 ones of 1 KB
-// 103 and 81, 120 000 of 1 KB 116 and 97, 300 000 304 and 258, 15 000 of 2 KB 31.1 and 31.2; 192 and 256 as 128).  Longer rows give up what the
+// (268 000 of 6.9 KB 1472 and 1455).  Rows of up to 2 KB, two vectors a lane, have room for 128 (kShortRowsGrid): with 64 the rows, loaded two ahead, are done
+// first and wait for the selection to be read and the stores behind it (64 and 128, values and update: 40 000 rows of 1 KB 46.7 and 42.1 us, of
+// 1408 bytes 54.7 and 50.5, 70 000 float32 ones of 1 KB 70.8 and 59.3, 15 000 of 2 KB 31.1 and 31.2).  Longer rows give up what the
 // clearing takes: 64 and 128, 39 224 of 4 KB 98 and 101, 100 000 of 2176 bytes 157 and 161.
 constexpr unsigned kClearWgs = 64;
 unsigned clear_grid(const int32_t* rowsel, int64_t n_rows, int64_t row_bytes) {
@@ -286,16 +292,13 @@ k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d
     const int cnt = left < kWave ? static_cast<int>(left) : kWave;
     int64_t my_row = 0;
     float my_vo = 0.f, my_ret = 0.f, my_v = 0.f;
-    int my_slot = n_roles;
+    int my_role = -1;                                  // as it is: looked at here it would be waited for before the first row is asked for
     if (lane < cnt) {
       const int64_t n = n0 + lane * kVWaves;
       my_row = rowsel ? rowsel[n] : n;
       my_vo = value_old[my_row];
       my_ret = ret[my_row];
-      if (tok_role && n_roles > 0) {
-        const int role = tok_role[my_row];
-        my_slot = role >= 0 && role < n_roles ? role : n_roles;
-      }
+      if (tok_role && n_roles > 0) my_role = tok_role[my_row];
     }
     auto row_at = [&](int i) {
       return static_cast<int64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(my_row), i))) |
@@ -329,7 +332,7 @@ k_value_rows(const T* __restrict__ H, const T* __restrict__ w, float bias, int d
       const float g = unclipped ? (V - R) * inv_s : 0.f;
       gsum += g;
       my_v = lane == i ? V : my_v;
-      const int slot = __builtin_amdgcn_readlane(my_slot, i);
+      const int role = __builtin_amdgcn_readlane(my_role, i), slot = role >= 0 && role < n_roles ? role : n_roles;
       const float loss = 0.5f * (unclipped ? lu : lc);
       if (slot == lane) {
         sum_l += static_cast<double>(loss);
@@ -594,9 +597,10 @@ extern "C" umas_status umas_value_loss_fwd_bwd(const void* H, const void* w, flo
   // that giving them up costs more than a tail, those for rows of more than 4 KB (39 224 rows of 4096 233 us with them first, 204 behind;
   // values and update of 48 651 rows of 3008 246 and 222, of 268 000 float32 rows of 1728 1733 and 1455; the other way round shorter rows: 100 000 of 1088
   // 185.5 first, 195 behind)
-  const unsigned n_clear = n_sel > 0 ? clear_grid(rowsel, n_rows, static_cast<int64_t>(d) * esz) : 0;
+  const size_t row_bytes = static_cast<size_t>(d) * esz;             // a multiple of 16
+  const unsigned n_clear = n_sel > 0 ? clear_grid(rowsel, n_rows, row_bytes) : 0;
   const bool last = kv > 4;
-  const unsigned grid = std::min(value_grid(n_sel), last || resident <= n_clear ? resident : resident - n_clear);
+  const unsigned grid = std::min({value_grid(n_sel), kv <= 2 && row_bytes >= 768 ? kShortRowsGrid - n_clear : kMaxGrid, last || resident <= n_clear ? resident : resident - n_clear});
   const unsigned clear_at = last ? grid : 0;
   const size_t part_bytes = static_cast<size_t>(grid) * part_pitch(d) * sizeof(float);
   Carver c(workspace);
@@ -604,7 +608,6 @@ extern "C" umas_status umas_value_loss_fwd_bwd(const void* H, const void* w, flo
   double* blk_stats = c.take<double>(static_cast<size_t>(grid) * (1 + n_roles) * kVStat);
 
   if (rowsel && n_rows > 0 && n_clear == 0) {
-    const size_t row_bytes = static_cast<size_t>(d) * esz;           // a multiple of 16
     const bool mark = !accumulate_dH && n_sel * static_cast<int64_t>(row_bytes) >= kMarkBytes && align_up(n_rows, 16) <= part_bytes;
     const int64_t n16 = accumulate_dH ? 0 : static_cast<int64_t>(mark ? align_up(n_rows, 16) / 16 : n_rows * row_bytes / 16);
     uint8_t* map = reinterpret_cast<uint8_t*>(part_dw);
