@@ -184,7 +184,7 @@ size_t umas_policy_logprobs_workspace_bytes(int64_t n_sel, int32_t d, int32_t V,
  *   rowsel  DEVICE int32 [n_sel] rows to score, distinct, each in [0, n_rows), in any order (ascending as
  *           umas_assign_token_rewards writes them, or a part of a ready batch); NULL with n_sel = n_rows = all
  *   logp, lse, entropy  DEVICE float [n_rows]; rows not selected are set to 0; entropy may be NULL
- * bf16 needs d % 8 == 0.  float32 takes any workspace of at least 256 bytes; with less than
+ * bf16 needs d % 8 == 0, H smaller than 4 GiB and 256 rows of W smaller than 4 GiB.  float32 takes any workspace of at least 256 bytes; with less than
  * umas_policy_logprobs_workspace_bytes the vocabulary of a row is shared among fewer workgroups or not at all. */
 umas_status umas_policy_logprobs(const void* H, const void* W, umas_dtype dtype, int64_t n_rows,
                                  int32_t d, int32_t V, const int32_t* ids, const int32_t* rowsel,
