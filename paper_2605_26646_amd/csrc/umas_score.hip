@@ -1231,9 +1231,8 @@ __device__ __forceinline__ KContig blocked_rows_tile(const uint16_t* X, int blk_
 // ms, through LDS 1.3 ms).  Every wavefront turns its 128 x 64 block through its own part of LDS, 32 rows at a time, and
 // stores 256 bytes of four rows.  In a tile that exists as a whole nothing depends on the row: what is there already is
 // under way during the turn, and a piece's LDS reads and stores go out together (waiting for each of 32 pieces by itself:
-// both products of 725 rows of 2048 that add to dW 1155 us, together 1020; 64 rows without adding 459 and 443).  What is there is read past the
-// caches, which leaves them to the operands (two updates of which the second adds, 203 rows of 2048 1454 -> 1380 us, 300 1950 -> 1885, 725 rows
-// four times 5.82 -> 5.73 ms).  Such a piece is addressed by 32-bit offsets from the wavefront's first row; rows farther apart than
+// both products of 725 rows of 2048 that add to dW 1155 us, together 1020; 64 rows without adding 459 and 443).  With `past` what is there is read
+// past the caches, which leaves them to the operands (see past_caches).  Such a piece is addressed by 32-bit offsets from the wavefront's first row; rows farther apart than
 // kPieceLd take the way of the tiles that end early, with 64-bit addresses.
 constexpr int kTurnBytes = 32 * 64 * 4;                              // 32 rows of 64 floats per wavefront
 constexpr int64_t kPieceLd = int64_t{1} << 22;                       // floats
@@ -1255,10 +1254,16 @@ __device__ __forceinline__ void turn_in(const floatx4 (&acc)[Cfg::MI][Cfg::NI], 
 __device__ __forceinline__ floatx4 turn_out(const char* turn, int i, int lane) {
   return *reinterpret_cast<const floatx4*>(turn + (i * 4 + (lane >> 4)) * 256 + (((lane & 15) ^ (4 * (i & 3))) * 16));
 }
+// dW that is added to is read past the caches (two updates of which the second adds, 203 rows of 2048 1454 -> 1380 us, 300 1950 -> 1885, 725 rows four times 5.82 ->
+// 5.73 ms) unless its rows start in the middle of 64 bytes: then every piece of a row shares lines with its neighbours, which read them once more.  Four updates of 200
+// rows of 2048 against 115 915, first of all through the caches, past them: 2056 columns 1943.6 and 2199.1 us (both products), 3592 against 60 001 1777.9 and
+// 2136.5, but 2064 1861.1 and 1930.8 in an update of 2966.7 and 2806.  A dW that the memory-side cache holds is read past the others all the same: eight of 367 rows
+// of 1096 against 50 001 (209 MiB) 2461 us and 2383.
+__device__ __forceinline__ bool past_caches(int d, int V) { return d % 16 == 0 || !beyond_cache(d, V, int64_t{128} << 20); }   // twice that in dW
 // `turn` is the wavefront's own part of LDS
 template <class C>
 __device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[C::MI][C::NI], char* turn, float* out, int64_t ld, int64_t rows, int cols,
-                                              int accumulate) {
+                                              int accumulate, bool past) {
   static_assert(C::WTM == Cfg::WTM && C::WTN == Cfg::WTN, "the turn is written for these");
   typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // dW has the alignment of a float
   const int tid = tile_thread(), lane = tid & 63, wave = tid >> 6;
@@ -1268,8 +1273,9 @@ __device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[C::MI][C::NI]
   constexpr int kPieces = C::MI / 2;
   // Each case is a run of its own: with the branches inside, the waits cannot tell what is under way and are for everything, the stores of
   // the piece before included.
-  auto pieces = [&](auto add) {
+  auto pieces = [&](auto add, auto past) {
     constexpr bool kAdd = decltype(add)::value;
+    constexpr int kRead = decltype(past)::value ? kStream : kCached;
     // (one offset a lane and one a piece: 32 addresses of 64 bits would be a quarter of the registers)
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     const int w_row = __builtin_amdgcn_readfirstlane(r0), w_col = __builtin_amdgcn_readfirstlane(wave) % C::WN * C::WTN;
@@ -1279,7 +1285,7 @@ __device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[C::MI][C::NI]
     auto fetch = [&](int h) {
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        have[i] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, (h * 8 + i) * step, kStream));
+        have[i] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, (h * 8 + i) * step, kRead));
     };
     if constexpr (kAdd) fetch(0);
 #pragma unroll
@@ -1300,10 +1306,12 @@ __device__ __forceinline__ void store_acc_f32(const floatx4 (&acc)[C::MI][C::NI]
       __builtin_amdgcn_wave_barrier();
     }
   };
-  if (whole && accumulate) {
-    pieces(std::true_type());
+  if (whole && accumulate && past) {
+    pieces(std::true_type(), std::true_type());
+  } else if (whole && accumulate) {
+    pieces(std::true_type(), std::false_type());
   } else if (whole) {
-    pieces(std::false_type());
+    pieces(std::false_type(), std::false_type());
   } else {
 #pragma unroll
     for (int h = 0; h < kPieces; ++h) {
@@ -1360,7 +1368,7 @@ __device__ __forceinline__ void dh_tile(int tile_m, int m_rows, int orig_blk, in
   else mfma_mainloop_mixed<C, false, true, 2>(ca, KMajor{}, KContig{}, kb, k_len, lds, acc);
   if (sl.n > 1) {
     float* out = sl.part + ((static_cast<int64_t>(slice) * tiles_r + tile_m) * tiles_d + tile_n) * (C::BM * C::BN);
-    store_acc_f32<C>(acc, reinterpret_cast<char*>(lds) + (tile_thread() >> 6) * kTurnBytes, out, C::BN, C::BM, C::BN, 0);
+    store_acc_f32<C>(acc, reinterpret_cast<char*>(lds) + (tile_thread() >> 6) * kTurnBytes, out, C::BN, C::BM, C::BN, 0, false);
     return;
   }
   // dH rows leave like the float32 ones: 32 rows at a time through LDS, 128 bytes of four rows to a store, the row numbers,
@@ -1427,7 +1435,7 @@ __device__ __forceinline__ void dw_tile(int tile_m, int tile_n, const uint16_t* 
   floatx4 acc[C::MI][C::NI];
   zero_acc<C>(acc);
   if (k_len > 0) mfma_mainloop_mixed<C, true, true, 1>(KContig{}, ka, KContig{}, kb, k_len, lds, acc);
-  store_acc_f32<C>(acc, reinterpret_cast<char*>(lds) + (tile_thread() >> 6) * kTurnBytes, dW + m0 * d + n0, d, V - m0, d - n0, accumulate);   // d is a multiple of 8
+  store_acc_f32<C>(acc, reinterpret_cast<char*>(lds) + (tile_thread() >> 6) * kTurnBytes, dW + m0 * d + n0, d, V - m0, d - n0, accumulate, past_caches(d, V));   // d is a multiple of 8
 }
 
 // dW of at most 256 rows.  A tile of 256 x 256 that a compute unit works on alone is products, then stores, and the next tile's first loads wait for these
@@ -1561,7 +1569,7 @@ k_dw_short(const uint16_t* __restrict__ dZ, int blk_pitch, int64_t Vp, int64_t m
   char* const turn = lds + (nsub + (wave == 3 ? 1 : 0)) % 3 * kShortStage + (wave == 3 ? 0 : wave) * kTurnBytes;
   const int64_t m0 = static_cast<int64_t>(tile_m) * C::BM;
   const int n0 = tile_n * C::BN;
-  store_acc_f32<C>(acc, turn, dW + m0 * d + n0, d, V - m0, d - n0, accumulate);
+  store_acc_f32<C>(acc, turn, dW + m0 * d + n0, d, V - m0, d - n0, accumulate, past_caches(d, V));
 }
 // Both products in one launch, in groups of 4 x 8 tiles that are worked on together on one XCD.  Every XCD owns a contiguous
 // range of the dH tiles (slice after slice, so that its workgroups share a slice of both operands) and behind it the share
