@@ -1363,7 +1363,13 @@ extern "C" umas_status umas_assign_token_rewards(const umas_graph* g, const umas
   else hipLaunchKernelGGL(k_turn_plan<UMAS_MAX_MODELS>, plan_grid, dim3(kPlanThreads), 0, st, P);
   UMAS_LAUNCHED("k_turn_plan");
   if (U > 0 && N > 0) {
-    if (N >= kPastTokens) hipLaunchKernelGGL(k_tokens<true>, dim3(static_cast<unsigned>(nbk)), dim3(kTokThreads), 0, st, T);
+    // Turns of 16 tokens and less on average leave most blocks one token at a time and plain stores (kSegWin).  The instance that knows nothing else needs 38
+    // registers, the other 68, of which seven workgroups fit a compute unit and not eight: a last round of them more at many sizes, and no other path to make
+    // up for it.  Routing and scan with it and without, turns of 16: 10 million tokens 347 and 342 us, 25 million 671 and 750, 30 million 826 and 892, 40 million 1117 and
+    // 1202; of 17 and more the other way round (40 million in turns of 17 603, before 792).  (Held to the 64 registers of eight it spills 12 bytes: 10 million
+    // tokens in turns of 256 120 and 115 us.)
+    const bool one_by_one = N < (kTokBlock / kSegWin + 1) * static_cast<int64_t>(U);
+    if (N >= kPastTokens && !one_by_one) hipLaunchKernelGGL(k_tokens<true>, dim3(static_cast<unsigned>(nbk)), dim3(kTokThreads), 0, st, T);
     else hipLaunchKernelGGL(k_tokens<false>, dim3(static_cast<unsigned>(nbk)), dim3(kTokThreads), 0, st, T);
     UMAS_LAUNCHED("k_tokens");
     SelArgs S;
