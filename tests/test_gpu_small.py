@@ -426,11 +426,11 @@ def test_update_of_few_rows_with_a_large_head(rows):
 
 
 # dW of 1 GiB and more (1.25 below 129 rows), which has a launch of its own up to 256 rows: a column tile of eight columns, a step of 32 rows that is partly
-# filled; up to 128 rows the operand comes in halves of its blocks, whose other rows nobody has written
+# filled; up to 128 rows the operand comes in halves of its blocks, whose other rows nobody has written; added to in rows that start at 64 bytes and in the middle
 @pytest.mark.parametrize("d,V,rows,entropy_coef,accumulate,apart", [
     (4088, 82200, 65, 0.0, False, True), (4088, 82200, 96, 0.0, True, True), (4088, 82200, 97, 0.0, False, True), (4088, 82200, 128, 0.0, True, True),
     (4088, 82200, 100, 0.01, True, True), (4104, 65500, 70, 0.0, True, False), (4104, 65500, 200, 0.01, False, True), (4104, 65500, 256, 0.0, True, True),
-    (4104, 65500, 257, 0.0, False, False)])
+    (4104, 65500, 257, 0.0, False, False), (4096, 82200, 99, 0.0, True, True), (2064, 66000, 60, 0.0, True, False)])
 def test_update_of_few_rows_with_a_large_gradient(d, V, rows, entropy_coef, accumulate, apart):
     umas.profile_enable(True)
     try:
